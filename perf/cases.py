@@ -133,8 +133,9 @@ def _rowptr(deg):
     return torch.cat([deg.new_zeros(1), torch.cumsum(deg, 0)])
 
 
-def _graph(types, rels, g):
-    """The handle, built from device arrays; a transpose is declared as its base's reverse."""
+def _adjacency(types, rels, g):
+    """What the handle is built from: (source type, destination type, row offsets, columns) on the device; a
+    transpose is declared as its base's reverse."""
     made = []
     for s, t, e, exponent, base in rels:
         if base < 0:
@@ -148,6 +149,10 @@ def _graph(types, rels, g):
             keys, order = torch.sort(col0, stable=True)
             made.append((s, t, _rowptr(torch.bincount(keys, minlength=types[t][0])), rows[order], {"reverse_of": base}))
     torch.cuda.synchronize()
+    return made
+
+
+def _graph(types, made):
     return hb.heta_graph_create(types, made, hb.HETA_PTRS_ON_DEVICE)
 
 
@@ -180,29 +185,44 @@ def _glorot(d_in, d_out, g, dtype=torch.float32):
 
 # ---- preparation and one pass -----------------------------------------------------------------------------
 
-def prepare(case, seed):
+def _inputs(case, seed):
+    """Everything that is drawn for a case, the same for `prepare` and `exact`."""
     g = _gen(seed)
     types, rels = _spec(case["graph"], case["scale"])
-    return globals()["_prepare_" + case["kind"]](case, types, rels, g, seed)
+    return types, rels, globals()["_inputs_" + case["kind"]](case, types, rels, g)
+
+
+def prepare(case, seed):
+    types, rels, x = _inputs(case, seed)
+    return globals()["_prepare_" + case["kind"]](case, types, rels, x, seed)
 
 
 def run(state):
     return state["run"](state)
 
 
-def _prepare_layer(case, types, rels, g, seed):
+def _inputs_layer(case, types, rels, g):
     dtype, d_out = DTYPES[case["dtype"]], case["d_out"]
-    graph = _graph(types, rels, g)
-    op = hb.HETA_MEAN if case["op"] == "mean" else hb.HETA_SUM
+    made = _adjacency(types, rels, g)
     if case["graph"] == "fixed_map":
         pre = [_uniform(d, 32, 1.0 / math.sqrt(d), g) for _, d, _ in types]
         widths = [32] * len(rels)
     else:
         pre, widths = None, [types[s][1] for s, *_ in rels]
     W = [_glorot(d, d_out, g, dtype) for d in widths]
-    layer = RafLayer(graph, op, _tables(types, g, dtype), W, d_out, pre_proj=pre, relu=case["relu"])
-    G = {t: torch.randn(h.shape, generator=g, device="cuda") for t, h in layer.H.items()} if case["backward"] else None
-    return {"run": _run_layer, "layer": layer, "G": G}
+    tables = _tables(types, g, dtype)
+    G = {t: torch.randn((types[t][0], d_out), generator=g, device="cuda") for t in _targets(rels)} if case["backward"] else None
+    return {"made": made, "pre": pre, "W": W, "tables": tables, "G": G}
+
+
+def _targets(rels):
+    return list(dict.fromkeys(t for _, t, *_ in rels))
+
+
+def _prepare_layer(case, types, rels, x, seed):
+    op = hb.HETA_MEAN if case["op"] == "mean" else hb.HETA_SUM
+    layer = RafLayer(_graph(types, x["made"]), op, x["tables"], x["W"], case["d_out"], pre_proj=x["pre"], relu=case["relu"])
+    return {"run": _run_layer, "layer": layer, "G": x["G"]}
 
 
 def _run_layer(state):
@@ -213,15 +233,20 @@ def _run_layer(state):
     return {"H": H, "dW": dW, "d_table": d_table}
 
 
-def _prepare_rgat(case, types, rels, g, seed):
+def _inputs_rgat(case, types, rels, g):
     dtype, d_out, heads = DTYPES[case["dtype"]], case["d_out"], case["heads"]
-    graph = _graph(types, rels, g)
+    made = _adjacency(types, rels, g)
     W = [_glorot(types[s][1], d_out, g, dtype) for s, *_ in rels]
     a = [_glorot(heads, d_out // heads, g).contiguous() for _ in rels]
     q = [_uniform(heads, types[t][1], math.sqrt(6.0 / (types[t][1] + 1)), g).contiguous() for _, t, *_ in rels]
-    layer = RgatLayer(graph, _tables(types, g, dtype), W, a, q, d_out, heads)
-    G = {t: torch.randn(h.shape, generator=g, device="cuda") for t, h in layer.H.items()}
-    return {"run": _run_rgat, "layer": layer, "G": G}
+    tables = _tables(types, g, dtype)
+    G = {t: torch.randn((types[t][0], d_out), generator=g, device="cuda") for t in _targets(rels)}
+    return {"made": made, "W": W, "a": a, "q": q, "tables": tables, "G": G}
+
+
+def _prepare_rgat(case, types, rels, x, seed):
+    layer = RgatLayer(_graph(types, x["made"]), x["tables"], x["W"], x["a"], x["q"], case["d_out"], case["heads"])
+    return {"run": _run_rgat, "layer": layer, "G": x["G"]}
 
 
 def _run_rgat(state):
@@ -230,14 +255,17 @@ def _run_rgat(state):
     return {"H": H, "dW": dW, "da": da, "dq": dq, "dH0": dH0}
 
 
-def _prepare_train(case, types, rels, g, seed):
-    dtype, hidden = DTYPES[case["dtype"]], case["d_hidden"]
-    graph = _graph(types, rels, g)
-    W = [[_glorot(types[s][1] if l == 0 else hidden, hidden, g, dtype) for s, *_ in rels] for l in range(2)]
-    trainer = MiniBatchTrainer(graph, _tables(types, g, dtype), W, [case["fan_outer"], case["fan_inner"]], hidden, hb.HETA_MEAN, 0, seed=seed)
-    seeds = _seeds(case, types, g)
-    target = torch.randn((seeds.numel(), hidden), generator=g, device="cuda")
-    return {"run": _run_train, "trainer": trainer, "seeds": seeds, "loss_grad": lambda H: H - target}
+def _inputs_train(case, types, rels, g):
+    x = _inputs_serve(case, types, rels, g)
+    x["target"] = torch.randn((x["seeds"].numel(), case["d_hidden"]), generator=g, device="cuda")
+    return x
+
+
+def _prepare_train(case, types, rels, x, seed):
+    trainer = MiniBatchTrainer(_graph(types, x["made"]), x["tables"], x["W"], [case["fan_outer"], case["fan_inner"]], case["d_hidden"], hb.HETA_MEAN, 0,
+                               seed=seed)
+    target = x["target"]
+    return {"run": _run_train, "trainer": trainer, "seeds": x["seeds"], "loss_grad": lambda H: H - target}
 
 
 def _seeds(case, types, g):
@@ -253,11 +281,16 @@ def _run_train(state):
     return {"H": H, "W": tr.W, "mW": tr.mW, "tables": {t: tr.tables[t] for t in tr.learnable}, "mT": tr.mT}
 
 
-def _prepare_serve(case, types, rels, g, seed):
+def _inputs_serve(case, types, rels, g):
     dtype, hidden = DTYPES[case["dtype"]], case["d_hidden"]
-    graph = _graph(types, rels, g)
+    made = _adjacency(types, rels, g)
     W = [[_glorot(types[s][1] if l == 0 else hidden, hidden, g, dtype) for s, *_ in rels] for l in range(2)]
-    return {"run": _run_serve, "graph": graph, "tables": _tables(types, g, dtype), "W": W, "hidden": hidden, "seeds": _seeds(case, types, g),
+    tables = _tables(types, g, dtype)
+    return {"made": made, "W": W, "tables": tables, "seeds": _seeds(case, types, g)}
+
+
+def _prepare_serve(case, types, rels, x, seed):
+    return {"run": _run_serve, "graph": _graph(types, x["made"]), "tables": x["tables"], "W": x["W"], "hidden": case["d_hidden"], "seeds": x["seeds"],
             "fanouts": [case["fan_outer"], case["fan_inner"]], "seed": int(seed), "calls": 0}
 
 
@@ -281,7 +314,7 @@ def _run_serve(state):
     return H[T]  # the seeds' type in its destination role
 
 
-def _prepare_adam(case, types, rels, g, seed):
+def _inputs_adam(case, types, rels, g):
     dtype, items = DTYPES[case["dtype"]], []
     for n, d, learnable in types:
         if learnable:
@@ -289,13 +322,171 @@ def _prepare_adam(case, types, rels, g, seed):
             ids = torch.randperm(n, generator=g, device="cuda")[:rows].sort().values
             items.append((_uniform(n, d, 0.1, g, dtype), torch.zeros((n, d), device="cuda"), torch.zeros((n, d), device="cuda"),
                           torch.randn((rows, d), generator=g, device="cuda").mul_(0.01), ids))
-    return {"run": _run_adam, "items": items, "step": 0}
+    return items
+
+
+def _prepare_adam(case, types, rels, x, seed):
+    return {"run": _run_adam, "items": x, "step": 0}
 
 
 def _run_adam(state):
     state["step"] += 1
     hb.heta_sparse_adam_multi(state["items"], step=state["step"])
     return [i[:3] for i in state["items"]]
+
+
+# ---- the same in 64 bits, in plain torch ----------------------------------------------------------------------
+
+def exact(case, seed):
+    """What the first `run` on a new state returns.  Left out (None): gradients behind a (Leaky)ReLU, where one
+    argument that changes sign in its last bit moves a whole row, and weights and rows after Adam's first step, which
+    moves a value by the sign of its gradient; their gradients stand in the moments."""
+    _, rels, x = _inputs(case, seed)
+    return globals()["_exact_" + case["kind"]](case, rels, x, seed)
+
+
+def _edges(relation):
+    """(destination, source) of every edge."""
+    rowptr, col = relation[2:4]
+    return torch.repeat_interleave(torch.arange(rowptr.numel() - 1, device="cuda"), rowptr.diff()), col.long()
+
+
+def _add_rows(out, to, rows, of, weight=None):
+    """out[to] += weight * rows[of], `to` ascending: a million edges at a time, at most 256 of one row in one sum."""
+    for e in range(0, to.numel(), 1 << 20):
+        c = slice(e, e + (1 << 20))
+        at, part = to[c], rows[of[c]].double()
+        if weight is not None:
+            part *= weight[c].unsqueeze(1)
+        first = torch.arange(at.numel(), device="cuda") % 256 == 0
+        first[1:] |= at[1:] != at[:-1]
+        start = first.nonzero().squeeze(1)
+        lengths = torch.diff(start, append=start.new_tensor([at.numel()]))
+        out.index_add_(0, at[start], torch.segment_reduce(part, "sum", lengths=lengths, axis=0, unsafe=True))
+    return out
+
+
+def _zeros(n, d):
+    return torch.zeros((n, d), dtype=torch.float64, device="cuda")
+
+
+def _mean(dst, n):
+    """1 / in-degree of every edge's destination."""
+    return 1.0 / torch.bincount(dst, minlength=n).double()[dst]
+
+
+def _exact_layer(case, rels, x, seed):
+    X, W = x["tables"], [w.double() for w in x["W"]]
+    if x["pre"] is not None:
+        X = [t.double() @ p.double() for t, p in zip(X, x["pre"])]
+    n_rows = [t.shape[0] for t in X]
+    H = {t: _zeros(n_rows[t], case["d_out"]) for t in _targets(rels)}
+    back = case["backward"] and not case["relu"]
+    dW, dX = {}, {s: _zeros(*X[s].shape) for s in dict.fromkeys(s for s, *_ in rels)} if back else None
+    for i, (s, t, *_) in enumerate(rels):
+        dst, src = _edges(x["made"][i])
+        weight = _mean(dst, n_rows[t]) if case["op"] == "mean" else None
+        M = _add_rows(_zeros(n_rows[t], X[s].shape[1]), dst, X[s], src, weight)
+        H[t] += M @ W[i]
+        if back:
+            G = x["G"][t].double()
+            dW[i] = M.T @ G
+            src, order = torch.sort(src)
+            _add_rows(dX[s], src, G @ W[i].T, dst[order], None if weight is None else weight[order])
+    if case["relu"]:
+        H = {t: h.relu_() for t, h in H.items()}
+    if not back:
+        return {"H": H}
+    return {"H": H, "dW": dW, "d_table": dX if x["pre"] is None else {s: d @ x["pre"][s].double().T for s, d in dX.items()}}
+
+
+def _exact_rgat(case, rels, x, seed):
+    X, K, F = x["tables"], case["heads"], case["d_out"] // case["heads"]
+    H = {t: _zeros(X[t].shape[0], K * F) for t in _targets(rels)}
+    for i, (s, t, *_) in enumerate(rels):
+        dst, src = _edges(x["made"][i])
+        Z = X[s].double() @ x["W"][i].double()
+        el, er = (Z.view(-1, K, F) * x["a"][i].double()).sum(2), X[t].double() @ x["q"][i].double().T
+        logit = torch.nn.functional.leaky_relu(el[src] + er[dst], 0.2)
+        p = logit.exp_()  # below e^100: the softmax needs no shift in 64 bits
+        p /= _add_rows(_zeros(*er.shape), dst, p, torch.arange(dst.numel(), device="cuda"))[dst]
+        for k in range(K):
+            H[t][:, k * F:(k + 1) * F] += _add_rows(_zeros(X[t].shape[0], F), dst, Z[:, k * F:(k + 1) * F], src, p[:, k].contiguous())
+    return {"H": {t: h.relu_() for t, h in H.items()}}
+
+
+def _s64(x):
+    return (x & (1 << 64) - 1) - (x >> 63 & 1) * (1 << 64)
+
+
+def _mix(x):
+    """SplitMix64's next() on int64 tensors."""
+    z = x + _s64(0x9E3779B97F4A7C15)
+    z = (z ^ (z >> 30 & (1 << 34) - 1)) * _s64(0xBF58476D1CE4E5B9)
+    z = (z ^ (z >> 27 & (1 << 37) - 1)) * _s64(0x94D049BB133111EB)
+    return z ^ (z >> 31 & (1 << 33) - 1)
+
+
+def _sampled(relation, nodes, fanout, seed):
+    """(position in nodes, global source) of the edges sampled for them: all, or `fanout` by Floyd's algorithm."""
+    rowptr, col = relation[2:4]
+    start, deg = rowptr[nodes], rowptr[nodes + 1] - rowptr[nodes]
+    key = _mix(seed ^ _mix(nodes))
+    slots = torch.arange(fanout, device="cuda").repeat(nodes.numel(), 1)
+    drawn = torch.full_like(slots, -1)
+    for k in range(fanout):
+        j = deg - fanout + k
+        at = (_mix(key + k) >> 32 & (1 << 32) - 1) * (j + 1) >> 32
+        drawn[:, k] = torch.where((drawn == at.unsqueeze(1)).any(1), j, at)
+    few = (deg <= fanout).unsqueeze(1)
+    slots = torch.where(few, slots, drawn)
+    row, k = torch.nonzero(~few | (slots < deg.unsqueeze(1)), as_tuple=True)
+    return row, col[start[row] + slots[row, k]].long()
+
+
+def _exact_blocks(case, rels, x, seed):
+    """Embeddings of the seeds, and the inner layer's M_r."""
+    types = range(len(x["tables"]))
+    frontier, hops = {0: x["seeds"]}, []
+    for hop, fanout in enumerate((case["fan_inner"], case["fan_outer"])):
+        edges = {i: _sampled(x["made"][i], frontier[t], fanout, _s64(seed + 0x100000001B3 * (hop * 4096 + i + 1)))
+                 for i, (_, t, *_) in enumerate(rels) if t in frontier}
+        ids = {s: torch.unique(torch.cat([e[1] for i, e in edges.items() if rels[i][0] == s] or [x["seeds"][:0]])) for s in types}
+        ids = {s: v for s, v in ids.items() if v.numel()}
+        hops.append((edges, ids, {t: v.numel() for t, v in frontier.items()}))
+        frontier = ids
+    X = {s: x["tables"][s][v].double() for s, v in frontier.items()}
+    for l, (edges, ids, count) in enumerate(reversed(hops)):
+        H, M = {t: _zeros(n, case["d_hidden"]) for t, n in count.items()}, {}
+        for i, (dst, src) in edges.items():
+            s, t = rels[i][:2]
+            M[i] = _zeros(count[t], x["W"][l][i].shape[0])
+            if src.numel():
+                _add_rows(M[i], dst, X[s], torch.searchsorted(ids[s], src), _mean(dst, count[t]))
+            H[t] += M[i] @ x["W"][l][i].double()
+        X = H if l else {t: h.relu_() for t, h in H.items()}
+    return X[0], M
+
+
+def _exact_serve(case, rels, x, seed):
+    return _exact_blocks(case, rels, x, seed + 1)[0]
+
+
+def _exact_train(case, rels, x, seed):
+    H, M = _exact_blocks(case, rels, x, seed + 1)
+    G = H - x["target"]
+    inner = [(M[i].T @ G).mul_(1.0 - 0.9) if i in M else torch.zeros_like(w, dtype=torch.float64) for i, w in enumerate(x["W"][1])]
+    return {"H": H, "W": None, "mW": [[None] * len(rels), inner], "tables": None, "mT": None}
+
+
+def _exact_adam(case, rels, x, seed):
+    out = []
+    for table, m, v, grad, ids in x:
+        table, m, v, g = table.double(), m.double(), v.double(), grad.double()
+        m[ids], v[ids] = (1.0 - 0.9) * g, (1.0 - 0.999) * g * g
+        table[ids] -= 1e-3 * g / (g.abs() + 1e-8)
+        out.append((table, m, v))
+    return out
 
 
 # ---- what a pass cannot do without, and how close another correct implementation comes -------------------------
