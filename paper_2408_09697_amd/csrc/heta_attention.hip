@@ -861,13 +861,15 @@ __global__ void __launch_bounds__(1024) attn_slab_sum_kernel(const float *part, 
 // ---- scores of several vector sets in one pass over the table -------------------------------------------
 // A node type is the source of some relations and the destination of others, and every one of them takes
 // a row score <x_i, vec_k> of the same table with vectors of its own (el with W_r a_r, er with q_r).  One
-// pass serves them all: 32 lanes per row (two rows per wavefront), a lane owns four columns and keeps its
-// four columns of all (set, head) vectors in registers, so a row costs one 16-byte load per lane, 4 FMAs
-// per vector, and one reduce-scatter butterfly after which lane v holds score v.  Tables of at most 128
-// columns, at most 32 vectors.  The backward runs the same way: dx[i, :] = sum_v dscore_v[i] vec_v (the
-// 32 scalars of a row are broadcast by lane shuffles), dvec_v = sum_i dscore_v[i] x[i, :] through
-// per-slab partial sums added in slab order.
-constexpr int kMultiSets = 8, kMultiVecs = 32, kMultiCols = 128;
+// pass serves them all: scores, dx[i, :] = sum_v dscore_v[i] vec_v and dvec_v = sum_i dscore_v[i] x[i, :] are
+// thin contractions (at most 128 columns, 32 vectors at a time) and run on the fp32 matrix instruction, whose
+// products and sums are the fp32 FMAs of the vector ALU: what bounds them is the pass over the table.  Measured
+// over the four tables of an academic graph (1.87 M fp32 rows of 128, 16 and 24 vectors), against lane shuffles and
+// per-lane FMAs: scores 547 -> 271 us, input gradient 472 -> 224 us, parameter gradient 628 -> 361 us; 187,000 bf16
+// rows with up to 56 vectors (set by set before, above 32): 274 -> 63, 209 -> 81 and 704 -> 103 us.
+constexpr int kMultiSets = 8, kMultiCols = 128;
+constexpr int kMultiVecs = 120; // the input gradient keeps all vectors in LDS: 120 * (512 + 8) bytes stay below 64 KB
+constexpr int kVecTile = 32; // vectors per matrix tile
 struct ScoreMulti {
     const float *vec[kMultiSets]; // [K][d] each
     float *score[kMultiSets];     // [n][K] each: written by the forward, read (dscore) by the backward
@@ -875,11 +877,17 @@ struct ScoreMulti {
     int n_sets, K, NV;            // NV = n_sets * K
 };
 
-// pointer j of a table of kMultiSets pointers for a lane-dependent j (a select chain: indexing the kernel
+using f32x16 = __attribute__((ext_vector_type(16))) float;
+using f32x4 = __attribute__((ext_vector_type(4))) float;
+// pointers kept in LDS: the address space says that they point to global memory
+using gf32 = __attribute__((address_space(1))) float;
+using gf32x4 = __attribute__((address_space(1))) f32x4;
+
+// element (v / K) of a table of kMultiSets pointers for a lane-dependent v (a select chain: indexing the kernel
 // arguments by a vector register would move them to scratch memory)
-__device__ __forceinline__ float *pick(float *const (&tab)[kMultiSets], int j)
+template <typename P> __device__ __forceinline__ P pick(P const (&tab)[kMultiSets], int j)
 {
-    float *p = tab[0];
+    P p = tab[0];
 #pragma unroll
     for (int q = 1; q < kMultiSets; ++q) p = j == q ? tab[q] : p;
     return p;
@@ -898,132 +906,225 @@ template <> __device__ __forceinline__ void load4<bf16_t>(const bf16_t *p, float
     f[2] = __uint_as_float(v.y << 16); f[3] = __uint_as_float(v.y & 0xffff0000u);
 }
 
-// this lane's four columns (4 l .. 4 l + 3) of the first NVC vectors; zero beyond d or beyond the NV vectors given
-template <int NVC> __device__ __forceinline__ void load_vectors(const ScoreMulti &m, int d, int l, float v[NVC][4])
+// Scores of 16 NT vectors (blockIdx.y picks them) and 16 rows per tile: the vectors are the first operand, so a
+// lane ends with one row's scores of four consecutive vectors - one 16-byte store where a set has a multiple of
+// four heads (VEC).  A lane holds the columns 16 c + 4 h .. + 3 of its vector and of its row (h: its quarter of the
+// wavefront): which k a step multiplies is free as long as both operands agree.  Sums of eight products
+// (two instructions) are added pairwise, which keeps the rounding error of a 128-term score where a
+// tree over the columns has it; one running accumulator shows in the layer's output.  NC = chunks of 16 columns.
+template <int NC> __device__ __forceinline__ f32x4 score_sum(const float (&a)[NC][4], const float (&x)[NC][4])
 {
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    f32x4 level[4]; // level[i]: the sum of the last 2^i chunks that is not part of a larger one yet
 #pragma unroll
-    for (int vi = 0; vi < NVC; ++vi) {
+    for (int c = 0; c < NC; ++c) {
+        f32x4 p = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c][0], x[c][0], zero, 0, 0, 0);
+        f32x4 q = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c][2], x[c][2], zero, 0, 0, 0);
+        p = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c][1], x[c][1], p, 0, 0, 0);
+        q = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c][3], x[c][3], q, 0, 0, 0);
+        f32x4 s = p + q;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) v[vi][c] = 0.f;
-        if (vi < m.NV && 4 * l < d) {
-            const float4 q = *reinterpret_cast<const float4 *>(m.vec[vi / m.K] + static_cast<int64_t>(vi % m.K) * d + 4 * l);
-            v[vi][0] = q.x; v[vi][1] = q.y; v[vi][2] = q.z; v[vi][3] = q.w;
-        }
-    }
-}
-
-// one step of the reduce-scatter over a row's 32 lanes: of its 2 CNT values a lane keeps the half its lane bit
-// CNT selects and adds the partner lane's copy of that half (register indices are compile-time constants)
-template <int CNT> __device__ __forceinline__ void reduce_scatter_step(float (&acc)[kMultiVecs], int l)
-{
-    const bool up = (l & CNT) != 0;
-#pragma unroll
-    for (int i = 0; i < CNT; ++i) {
-        const float send = up ? acc[i] : acc[i + CNT];
-        const float keep = up ? acc[i + CNT] : acc[i];
-        acc[i] = keep + __shfl_xor(send, CNT, 64);
-    }
-}
-
-template <typename T, int NVC>
-__global__ void __launch_bounds__(256) attn_score_multi_kernel(const T *x, int64_t ld_x, int64_t n, int d, ScoreMulti m)
-{
-    const int lane = threadIdx.x & 63, l = lane & 31, half = lane >> 5;
-    float v[NVC][4];
-    load_vectors<NVC>(m, d, l, v);
-    const int64_t wave = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6), n_waves = static_cast<int64_t>(gridDim.x) * 4;
-    for (int64_t r0 = wave * 2; r0 < n; r0 += n_waves * 2) { // uniform per wavefront
-        const int64_t r = r0 + half;
-        float xv[4] = {0.f, 0.f, 0.f, 0.f};
-        if (r < n && 4 * l < d) load4<T>(x + r * ld_x + 4 * l, xv);
-        float acc[kMultiVecs];
-#pragma unroll
-        for (int vi = 0; vi < kMultiVecs; ++vi)
-            acc[vi] = vi < NVC ? (xv[0] * v[vi < NVC ? vi : 0][0] + xv[1] * v[vi < NVC ? vi : 0][1]) +
-                                     (xv[2] * v[vi < NVC ? vi : 0][2] + xv[3] * v[vi < NVC ? vi : 0][3])
-                               : 0.f;
-        // reduce-scatter over the 32 lanes of the row: each step halves the values a lane keeps (the half its
-        // lane bit selects) and adds the partner's; after five steps lane v holds the whole sum of value v
-        reduce_scatter_step<16>(acc, l);
-        reduce_scatter_step<8>(acc, l);
-        reduce_scatter_step<4>(acc, l);
-        reduce_scatter_step<2>(acc, l);
-        reduce_scatter_step<1>(acc, l);
-        if (r < n && l < m.NV) pick(m.score, l / m.K)[r * m.K + l % m.K] = acc[0];
-    }
-}
-
-template <int NVC>
-__global__ void __launch_bounds__(256) attn_score_bwd_multi_input_kernel(int64_t n, int d, ScoreMulti m, float *dx, int64_t ld_dx, float beta)
-{
-    const int lane = threadIdx.x & 63, l = lane & 31, half = lane >> 5;
-    float v[NVC][4];
-    load_vectors<NVC>(m, d, l, v);
-    const int64_t wave = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6), n_waves = static_cast<int64_t>(gridDim.x) * 4;
-    for (int64_t r0 = wave * 2; r0 < n; r0 += n_waves * 2) {
-        const int64_t r = r0 + half;
-        float ds = 0.f;
-        if (r < n && l < m.NV) ds = pick(m.score, l / m.K)[r * m.K + l % m.K];
-        float o[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int vi = 0; vi < NVC; ++vi) {
-            const float sv = __shfl(ds, (lane & 32) | vi, 64);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) o[c] = fmaf(sv, v[vi][c], o[c]);
-        }
-        if (r < n && 4 * l < d) {
-            float4 *dst = reinterpret_cast<float4 *>(dx + r * ld_dx + 4 * l);
-            float4 w4 = make_float4(o[0], o[1], o[2], o[3]);
-            if (beta != 0.f) {
-                const float4 old = *dst;
-                w4.x += old.x; w4.y += old.y; w4.z += old.z; w4.w += old.w;
+        for (int i = 0; i < 4; ++i) {
+            if (((c + 1) >> i & 1) != 0) {
+                level[i] = s;
+                break;
             }
-            *dst = w4;
+            s = level[i] + s;
+        }
+    }
+    return level[NC == 8 ? 3 : NC == 4 ? 2 : 1]; // NC is 2, 4 or 8
+}
+
+template <typename T, int NC, int NT, bool VEC>
+__global__ void __launch_bounds__(256, 2) attn_score_multi_kernel(const T *x, int64_t ld_x, int64_t n, int d, ScoreMulti m)
+{
+    __shared__ gf32 *sptr[16 * NT];
+    const int lane = threadIdx.x & 63, l = lane & 15, h = lane >> 4;
+    const int v0 = blockIdx.y * 16 * NT;
+    if (threadIdx.x < 16 * NT) {
+        const int v = v0 + threadIdx.x;
+        sptr[threadIdx.x] = v < m.NV ? (gf32 *)(pick(m.score, v / m.K) + v % m.K) : nullptr;
+    }
+    float a[NT][NC][4];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int v = v0 + 16 * t + l, vc = min(v, m.NV - 1);
+        const float *vec = pick(m.vec, vc / m.K) + static_cast<int64_t>(vc % m.K) * d;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            a[t][c][0] = a[t][c][1] = a[t][c][2] = a[t][c][3] = 0.f;
+            if (v < m.NV && 16 * c + 4 * h < d) load4<float>(vec + 16 * c + 4 * h, a[t][c]);
+        }
+    }
+    __syncthreads();
+    const int64_t wave = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6), step = static_cast<int64_t>(gridDim.x) * 4 * 16;
+    for (int64_t r0 = wave * 16; r0 < n; r0 += step) { // uniform per wavefront
+        const int64_t r = r0 + l;
+        const T *xr = x + min(r, n - 1) * ld_x; // rows past the end repeat the last one and are not stored
+        float xv[NC][4];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            xv[c][0] = xv[c][1] = xv[c][2] = xv[c][3] = 0.f;
+            if (16 * c + 4 * h < d) load4<T>(xr + 16 * c + 4 * h, xv[c]);
+        }
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const f32x4 s = score_sum<NC>(a[t], xv);
+            if (r < n) {
+                if (VEC) {
+                    gf32 *o = sptr[16 * t + 4 * h];
+                    if (o) *(gf32x4 *)(o + r * m.K) = s;
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        gf32 *o = sptr[16 * t + 4 * h + j];
+                        if (o) o[r * m.K] = s[j];
+                    }
+                }
+            }
         }
     }
 }
 
-// part[slab][v][128]: the slab's sum over its rows of dscore_v[i] x[i, :]; the two rows a wavefront has in
-// flight are added first (lane shuffle), then the four wavefronts in wavefront order through LDS
-template <typename T, int NVC>
-__global__ void __launch_bounds__(256) attn_score_bwd_multi_param_kernel(const T *x, int64_t ld_x, int64_t n, int d, ScoreMulti m, float *part)
+// dx[i, :] (+)= sum_v dscore_v[i] vec_v: 32 rows per tile are the first operand, the four columns 4 l .. 4 l + 3 of
+// lane l the second one of four products, so that a row leaves as 16-byte stores of whole cache lines.  The vectors
+// sit in LDS, zero beyond d and up to a multiple of eight vectors; step (c, j) multiplies vector 8 c + 4 h + j.
+template <bool VEC>
+__global__ void __launch_bounds__(256, 3) attn_score_bwd_multi_input_kernel(int64_t n, int d, ScoreMulti m, float *dx, int64_t ld_dx, float beta)
 {
-    __shared__ float buf[NVC][kMultiCols];
-    const int lane = threadIdx.x & 63, l = lane & 31, half = lane >> 5, w = threadIdx.x >> 6;
-    const int64_t slab = blockIdx.x;
-    const int64_t i0 = slab * kSlabRows, i1 = min(n, i0 + kSlabRows);
-    float acc[NVC][4];
+    extern __shared__ __align__(16) float vecs[]; // [8 nc][128], then the pointers
+    const int lane = threadIdx.x & 63, l = lane & 31, h = lane >> 5;
+    const int nc = (m.NV + 7) / 8;
+    const gf32 **sptr = reinterpret_cast<const gf32 **>(vecs + 8 * nc * kMultiCols);
+    for (int t = threadIdx.x; t < 8 * nc * kMultiCols; t += 256) {
+        const int v = t / kMultiCols, c = t % kMultiCols;
+        vecs[t] = v < m.NV && c < d ? pick(m.vec, v / m.K)[static_cast<int64_t>(v % m.K) * d + c] : 0.f;
+    }
+    for (int v = threadIdx.x; v < 8 * nc; v += 256) sptr[v] = v < m.NV ? (const gf32 *)(pick(m.score, v / m.K) + v % m.K) : nullptr;
+    __syncthreads();
+    const int64_t wave = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6), n_waves = static_cast<int64_t>(gridDim.x) * 4;
+    for (int64_t r0 = wave * 32; r0 < n; r0 += n_waves * 32) { // uniform per wavefront
+        const int64_t r = min(r0 + l, n - 1);
+        f32x16 acc[4];
 #pragma unroll
-    for (int vi = 0; vi < NVC; ++vi)
+        for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) acc[vi][c] = 0.f;
-    for (int64_t r0 = i0 + 2 * w; r0 < i1; r0 += 8) {
-        const int64_t r = r0 + half;
-        float xv[4] = {0.f, 0.f, 0.f, 0.f}, ds = 0.f;
-        if (r < i1 && 4 * l < d) load4<T>(x + r * ld_x + 4 * l, xv);
-        if (r < i1 && l < m.NV) ds = pick(m.score, l / m.K)[r * m.K + l % m.K];
+            for (int i = 0; i < 16; ++i) acc[j][i] = 0.f;
+        for (int c0 = 0; c0 < nc; c0 += 4) { // 32 vectors: all their loads before the first product
+            float ds[4][4];
 #pragma unroll
-        for (int vi = 0; vi < NVC; ++vi) {
-            const float sv = __shfl(ds, (lane & 32) | vi, 64);
+            for (int cc = 0; cc < 4; ++cc) {
+                ds[cc][0] = ds[cc][1] = ds[cc][2] = ds[cc][3] = 0.f;
+                if (c0 + cc < nc) {
+                    const int v = 8 * (c0 + cc) + 4 * h;
+                    if (VEC) {
+                        const gf32 *p = sptr[v];
+                        if (p) {
+                            const f32x4 t = *(const gf32x4 *)(p + r * m.K);
+                            ds[cc][0] = t.x; ds[cc][1] = t.y; ds[cc][2] = t.z; ds[cc][3] = t.w;
+                        }
+                    } else {
 #pragma unroll
-            for (int c = 0; c < 4; ++c) acc[vi][c] = fmaf(sv, xv[c], acc[vi][c]);
+                        for (int j = 0; j < 4; ++j) {
+                            const gf32 *p = sptr[v + j];
+                            if (p) ds[cc][j] = p[r * m.K];
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int cc = 0; cc < 4; ++cc) {
+                if (c0 + cc < nc) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float4 b = *reinterpret_cast<const float4 *>(vecs + (8 * (c0 + cc) + 4 * h + j) * kMultiCols + 4 * l);
+                        acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(ds[cc][j], b.x, acc[0], 0, 0, 0);
+                        acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(ds[cc][j], b.y, acc[1], 0, 0, 0);
+                        acc[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(ds[cc][j], b.z, acc[2], 0, 0, 0);
+                        acc[3] = __builtin_amdgcn_mfma_f32_32x32x2f32(ds[cc][j], b.w, acc[3], 0, 0, 0);
+                    }
+                }
+            }
+        }
+        if (4 * l < d) {
+#pragma unroll
+            for (int i0 = 0; i0 < 16; i0 += 8) { // eight rows' loads before their stores
+                float4 old[8];
+                if (beta != 0.f) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const int64_t row = r0 + 8 * ((i0 + i) / 4) + 4 * h + i % 4;
+                        old[i] = *reinterpret_cast<const float4 *>(dx + min(row, n - 1) * ld_dx + 4 * l);
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int64_t row = r0 + 8 * ((i0 + i) / 4) + 4 * h + i % 4;
+                    float4 w4 = make_float4(acc[0][i0 + i], acc[1][i0 + i], acc[2][i0 + i], acc[3][i0 + i]);
+                    if (beta != 0.f) {
+                        w4.x += old[i].x; w4.y += old[i].y; w4.z += old[i].z; w4.w += old[i].w;
+                    }
+                    if (row < n) *reinterpret_cast<float4 *>(dx + row * ld_dx + 4 * l) = w4;
+                }
+            }
         }
     }
+}
+
+// part[slab][v][128]: the slab's sum over its rows of dscore_v[i] x[i, :].  The contraction runs over the rows, two
+// per step (one per wavefront half); a lane's first operand is its vector's dscore, its second the four columns
+// 4 l .. 4 l + 3.  A wavefront takes every fourth group of 2 U rows of the slab, the four wavefronts' sums are added
+// in wavefront order through LDS.
+template <typename T>
+__global__ void __launch_bounds__(256, 3) attn_score_bwd_multi_param_kernel(const T *x, int64_t ld_x, int64_t n, int d, ScoreMulti m, int slab_rows,
+                                                                         float *part)
+{
+    constexpr int U = 8;
+    __shared__ __align__(16) float buf[kVecTile][kMultiCols];
+    const int lane = threadIdx.x & 63, l = lane & 31, h = lane >> 5, w = threadIdx.x >> 6;
+    const int64_t slab = blockIdx.x;
+    const int64_t i0 = slab * slab_rows, i1 = min(n, i0 + slab_rows);
+    const int v = blockIdx.y * kVecTile + l;
+    const bool has_v = v < m.NV, has_c = 4 * l < d;
+    const float *ds = has_v ? pick(m.score, v / m.K) + v % m.K : nullptr;
+    f32x16 acc[4];
 #pragma unroll
-    for (int vi = 0; vi < NVC; ++vi)
+    for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) acc[vi][c] += __shfl_xor(acc[vi][c], 32, 64);
+        for (int i = 0; i < 16; ++i) acc[j][i] = 0.f;
+    for (int64_t rb = i0 + w * (2 * U); rb < i1; rb += 8 * U) { // uniform per wavefront
+        float xv[U][4], sv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t r = rb + 2 * u + h;
+            xv[u][0] = xv[u][1] = xv[u][2] = xv[u][3] = 0.f;
+            sv[u] = 0.f;
+            if (r < i1 && has_c) load4<T>(x + r * ld_x + 4 * l, xv[u]);
+            if (r < i1 && has_v) sv[u] = ds[r * m.K];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(sv[u], xv[u][j], acc[j], 0, 0, 0);
+    }
     for (int q = 0; q < 4; ++q) { // wavefront q adds its sums to the buffer, in order
-        if (w == q && half == 0) {
+        if (w == q) {
 #pragma unroll
-            for (int vi = 0; vi < NVC; ++vi)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) buf[vi][4 * l + c] = (q == 0 ? 0.f : buf[vi][4 * l + c]) + acc[vi][c];
+            for (int i = 0; i < 16; ++i) {
+                float4 *b = reinterpret_cast<float4 *>(&buf[8 * (i / 4) + 4 * h + i % 4][4 * l]);
+                float4 t = make_float4(acc[0][i], acc[1][i], acc[2][i], acc[3][i]);
+                if (q > 0) {
+                    const float4 o = *b;
+                    t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
+                }
+                *b = t;
+            }
         }
         __syncthreads();
     }
-    float *o = part + slab * (NVC * kMultiCols);
-    for (int t = threadIdx.x; t < NVC * kMultiCols; t += 256) o[t] = (&buf[0][0])[t];
+    float *o = part + (slab * gridDim.y + blockIdx.y) * (kVecTile * kMultiCols);
+    for (int t = threadIdx.x * 4; t < kVecTile * kMultiCols; t += 1024)
+        *reinterpret_cast<float4 *>(o + t) = *reinterpret_cast<const float4 *>(&buf[0][0] + t);
 }
 
 // dvec_v[c] = sum over the slabs, in slab order per wavefront and wavefront order through LDS (as attn_slab_sum_kernel)
@@ -1035,7 +1136,7 @@ __global__ void __launch_bounds__(1024) attn_multi_slab_sum_kernel(const float *
     const int64_t t = static_cast<int64_t>(blockIdx.x) * 64 + lane;
     float a = 0.f;
     if (t < elems) {
-#pragma unroll 4
+#pragma unroll 8
         for (int64_t s = w; s < n_slabs; s += 16) a += part[s * elems + t];
     }
     red[w][lane] = a;
@@ -1260,13 +1361,21 @@ heta_status heta_attn_score_multi(const void *x, heta_dtype dt, int64_t ld_x, in
         m.vec[j] = vecs[j];
         m.score[j] = scores[j];
     }
-    const int64_t blocks = std::min<int64_t>((n + 7) / 8, 256 * 8);
+    // a wavefront takes tiles of 16 rows; up to 16 vectors leave registers for four workgroups per CU, 32 for two
+    const int nt = m.NV <= 16 ? 1 : 2;
+    const dim3 grid((unsigned)std::min<int64_t>((n + 63) / 64, nt == 1 ? 1024 : 512), (unsigned)((m.NV + 16 * nt - 1) / (16 * nt)));
+    bool vec4 = heads % 4 == 0;
+    for (int j = 0; j < n_sets; ++j) vec4 = vec4 && aligned16(scores[j]);
     ProfScope prof("attn_score_multi_kernel", st, static_cast<double>(n) * (d * dtype_size(dt) + 4.0 * m.NV), 0);
-#define HETA_SM(TT, NVC) hipLaunchKernelGGL((attn_score_multi_kernel<TT, NVC>), dim3((unsigned)blocks), dim3(256), 0, st, static_cast<const TT *>(x), ld_x, n, (int)d, m)
-#define HETA_SM_T(TT) do { if (m.NV <= 8) HETA_SM(TT, 8); else if (m.NV <= 16) HETA_SM(TT, 16); else if (m.NV <= 24) HETA_SM(TT, 24); else HETA_SM(TT, 32); } while (0)
+#define HETA_SM(TT, NC, NT, V4) hipLaunchKernelGGL((attn_score_multi_kernel<TT, NC, NT, V4>), grid, dim3(256), 0, st, static_cast<const TT *>(x), ld_x, n, (int)d, m)
+#define HETA_SM_V(TT, NC, NT) do { if (vec4) HETA_SM(TT, NC, NT, true); else HETA_SM(TT, NC, NT, false); } while (0)
+#define HETA_SM_N(TT, NC) do { if (nt == 1) HETA_SM_V(TT, NC, 1); else HETA_SM_V(TT, NC, 2); } while (0)
+#define HETA_SM_T(TT) do { if (d <= 32) HETA_SM_N(TT, 2); else if (d <= 64) HETA_SM_N(TT, 4); else HETA_SM_N(TT, 8); } while (0)
     if (dt == HETA_F32) HETA_SM_T(float);
     else HETA_SM_T(bf16_t);
 #undef HETA_SM_T
+#undef HETA_SM_N
+#undef HETA_SM_V
 #undef HETA_SM
     HETA_LAUNCH_CHECK("attn_score_multi_kernel");
     return HETA_OK;
@@ -1307,33 +1416,40 @@ heta_status heta_attn_score_bwd_multi(heta_graph *g, const void *x, heta_dtype d
         m.dvec[j] = dvecs ? dvecs[j] : nullptr;
         any_dvec = any_dvec || m.dvec[j];
     }
-    const int nvc = m.NV <= 8 ? 8 : m.NV <= 16 ? 16 : m.NV <= 24 ? 24 : 32;
+    const int tiles = (m.NV + kVecTile - 1) / kVecTile, nvc = tiles * kVecTile;
     if (dx && n > 0) {
-        const int64_t blocks = std::min<int64_t>((n + 7) / 8, 256 * 8);
+        const int nc8 = (m.NV + 7) / 8 * 8;
+        const size_t lds = static_cast<size_t>(nc8) * (kMultiCols * sizeof(float) + sizeof(float *)); // at most 62,400 bytes
+        const int64_t blocks = std::min<int64_t>((n + 127) / 128, 768);
+        bool vec4 = heads % 4 == 0;
+        for (int j = 0; j < n_sets; ++j) vec4 = vec4 && aligned16(dscores[j]);
         ProfScope prof("attn_score_bwd_input_kernel", st, static_cast<double>(n) * (d * (beta != 0.f ? 8.0 : 4.0) + 4.0 * m.NV), 0);
-#define HETA_SI(NVC) hipLaunchKernelGGL((attn_score_bwd_multi_input_kernel<NVC>), dim3((unsigned)blocks), dim3(256), 0, st, n, (int)d, m, dx, ld_dx, beta)
-        if (nvc == 8) HETA_SI(8); else if (nvc == 16) HETA_SI(16); else if (nvc == 24) HETA_SI(24); else HETA_SI(32);
-#undef HETA_SI
+        if (vec4) hipLaunchKernelGGL((attn_score_bwd_multi_input_kernel<true>), dim3((unsigned)blocks), dim3(256), lds, st, n, (int)d, m, dx, ld_dx, beta);
+        else hipLaunchKernelGGL((attn_score_bwd_multi_input_kernel<false>), dim3((unsigned)blocks), dim3(256), lds, st, n, (int)d, m, dx, ld_dx, beta);
         HETA_LAUNCH_CHECK("attn_score_bwd_multi_input_kernel");
     }
     if (any_dvec) {
-        const int64_t n_slabs = (n + kSlabRows - 1) / kSlabRows;
+        // slabs of a multiple of 64 rows (each wavefront's eight row pairs), at most 1,024 slabs: enough workgroups for
+        // four per CU, and the slab sums (16 KB each) stay small beside the table
+        const int64_t slab_rows = std::max<int64_t>(128, (n + 1024 * 64 - 1) / (1024 * 64) * 64);
+        const int64_t n_slabs = (n + slab_rows - 1) / slab_rows;
         if (n_slabs == 0) {
             for (int j = 0; j < n_sets; ++j)
                 if (m.dvec[j]) HETA_HIP(hipMemsetAsync(m.dvec[j], 0, static_cast<size_t>(heads) * d * sizeof(float), st));
             return HETA_OK;
         }
-        if (n_slabs > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "%s: too many rows", who);
+        if (slab_rows > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "%s: too many rows", who);
         heta_status e = ensure_attn(g, static_cast<size_t>(n_slabs) * nvc * kMultiCols * sizeof(float));
         if (e != HETA_OK) return e;
         float *part = static_cast<float *>(g->d_attn);
         ProfScope prof("attn_score_bwd_param_kernel", st, static_cast<double>(n) * (d * dtype_size(dt) + 4.0 * m.NV), 0);
-#define HETA_SP(TT, NVC) hipLaunchKernelGGL((attn_score_bwd_multi_param_kernel<TT, NVC>), dim3((unsigned)n_slabs), dim3(256), 0, st, static_cast<const TT *>(x), ld_x, n, (int)d, m, part)
-#define HETA_SP_T(TT) do { if (nvc == 8) HETA_SP(TT, 8); else if (nvc == 16) HETA_SP(TT, 16); else if (nvc == 24) HETA_SP(TT, 24); else HETA_SP(TT, 32); } while (0)
-        if (dt == HETA_F32) HETA_SP_T(float);
-        else HETA_SP_T(bf16_t);
-#undef HETA_SP_T
-#undef HETA_SP
+        const dim3 grid((unsigned)n_slabs, (unsigned)tiles);
+        if (dt == HETA_F32)
+            hipLaunchKernelGGL((attn_score_bwd_multi_param_kernel<float>), grid, dim3(256), 0, st, static_cast<const float *>(x), ld_x, n, (int)d, m,
+                               (int)slab_rows, part);
+        else
+            hipLaunchKernelGGL((attn_score_bwd_multi_param_kernel<bf16_t>), grid, dim3(256), 0, st, static_cast<const bf16_t *>(x), ld_x, n, (int)d, m,
+                               (int)slab_rows, part);
         HETA_LAUNCH_CHECK("attn_score_bwd_multi_param_kernel");
         const int64_t elems = static_cast<int64_t>(nvc) * kMultiCols;
         hipLaunchKernelGGL(attn_multi_slab_sum_kernel, dim3((unsigned)((elems + 63) / 64)), dim3(1024), 0, st, part, n_slabs, nvc, (int)d, m);

@@ -112,6 +112,14 @@ def test_scores_of_several_vector_sets_in_one_pass(n, d, heads, n_sets, pad, sto
         graph.destroy()
 
 
+@pytest.mark.parametrize("n,d,heads,n_sets", [(33, 128, 8, 7), (129, 96, 5, 7), (4097, 128, 15, 8), (66000, 32, 2, 5), (127, 4, 1, 8),
+                                              (65, 128, 16, 8)])  # 128 vectors: set by set
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+def test_scores_of_vector_sets_at_tile_edges(n, d, heads, n_sets, storage):
+    """Row tiles of 32, vector tiles of 32, slabs of 128 rows and more: remainders of each."""
+    test_scores_of_several_vector_sets_in_one_pass(n, d, heads, n_sets, 4, storage)
+
+
 # ---- one relation ---------------------------------------------------------------------------------------
 
 def _relation_case(kind, n_src, n_dst, n_edges):
