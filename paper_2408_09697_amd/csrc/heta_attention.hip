@@ -33,18 +33,24 @@ namespace {
 
 using bf16_t = uint16_t;
 constexpr int kMaxHeads = 16;
-constexpr int kShortDegAttn = 32; // same split as the aggregation: below, one thread per (row, head)
+constexpr int kShortDegAttn = 32; // same split as the aggregation: from here on, a wavefront per row
+constexpr int kThreadDegAttn = 4; // up to here, one thread per row
 
 __device__ __forceinline__ float lrelu(float x, float slope) { return x > 0.f ? x : slope * x; }
 
 // ---- row sweeps ------------------------------------------------------------------------------------------
-// One sweep visits every edge slot of a schedule once per phase and touches only scalars: the neighbour's
-// id, KT consecutive heads of its score (one vector load), and the per-slot weights it writes.
-//   rows of fewer than 32 edges: one thread per row; 32..511 edges: one wavefront per row;
+// One sweep touches only scalars: per edge slot of a schedule the neighbour's id, KT consecutive heads of its
+// score (one vector load), and the per-slot weights it writes.  A sweep is bound by the latency of its gathers, so
+// a row gets as many lanes as bring it down to a few loads per lane, all in flight together:
+//   rows of up to 4 edges: one thread per row; 5..31: eight lanes per row; 32..511: one wavefront per row;
 //   hub rows (>= 512 edges): one wavefront per 256-edge chunk writes partial statistics, a second kernel
 //   combines a row's chunks in chunk order, and (forward only) a third writes the weights.
+// The first three and the hub chunks share one launch.  The forward keeps a row's logits in registers from the
+// gather to the weights.  (One thread per row below 32 edges, one gather per phase and a launch per row class:
+// 0.4 M edges into 70,000 rows of a power-law relation, 8 heads: forward 106 us, now 35 us; all sweeps of a 4-head
+// layer over 21 M edges 2.7 ms, now 1.75 ms.)
 enum SweepOp { SWEEP_FWD = 0, SWEEP_BWD_CSR = 1, SWEEP_BWD_CSC = 2 };
-enum Phase { PH_MAX = 0, PH_SUM = 1, PH_ALPHA = 2, PH_BWD_DST = 3, PH_BWD_SRC = 4 };
+enum Phase { PH_ALPHA = 0, PH_BWD_DST = 1, PH_BWD_SRC = 2 };
 
 struct SweepParams {
     const int64_t *sptr;
@@ -53,7 +59,10 @@ struct SweepParams {
     const HubChunk *hub_chunks;
     const int64_t *hub_chunk_ptr;
     int64_t n_hub_rows, n_hub_chunks;
-    int64_t q0, q1;       // schedule positions of this launch
+    // schedule positions [0, q_wave) are hub rows, then one wavefront per row, from q_mid on eight lanes, from
+    // q_short on one thread; first workgroup of each class in the shared launch (hub chunks first)
+    int64_t q_wave, q_mid, q_short, n_rows;
+    unsigned b_wave, b_mid, b_short;
     int K;
     float slope;
     const float *row_a;   // [rows][K]  score half of the row side (er for the CSR, el for the CSC)
@@ -67,7 +76,8 @@ struct SweepParams {
     float *corr;          // [rows][K]  the scalar term subtracted from the row's score gradient (BWD_*)
     const float *nbr_pack; // BWD_CSC: [dst][4][K] = the destination's er, smax, sinv, dot side by side (one cache line
                           // per neighbour instead of four gathers)
-    float *part;          // hub chunks: [n_hub_chunks][K][2] partial statistics
+    float *apos;          // [dst][K]   sum of alpha over the edges with a positive logit (FWD, nullable)
+    float *part;          // hub chunks: [n_hub_chunks][K][3] partial statistics
     float *hub_stat;      // hub rows (FWD): [n_hub_rows][K][2] = shift, 1/denominator
 };
 
@@ -83,6 +93,11 @@ template <> __device__ __forceinline__ void loadk<4>(const float *p, float *v)
     const float4 t = *reinterpret_cast<const float4 *>(p);
     v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
 }
+template <> __device__ __forceinline__ void loadk<8>(const float *p, float *v)
+{
+    loadk<4>(p, v);
+    loadk<4>(p + 4, v + 4);
+}
 template <int KT> __device__ __forceinline__ void storek(float *p, const float *v);
 template <> __device__ __forceinline__ void storek<1>(float *p, const float *v) { *p = v[0]; }
 template <> __device__ __forceinline__ void storek<2>(float *p, const float *v) { *reinterpret_cast<float2 *>(p) = make_float2(v[0], v[1]); }
@@ -91,8 +106,14 @@ template <> __device__ __forceinline__ void storek<4>(float *p, const float *v)
     *reinterpret_cast<float4 *>(p) = make_float4(v[0], v[1], v[2], v[3]);
 }
 
+template <> __device__ __forceinline__ void storek<8>(float *p, const float *v)
+{
+    storek<4>(p, v);
+    storek<4>(p + 4, v + 4);
+}
+
 // One edge slot e, heads k0 .. k0+KT-1.  ar: the row's score half; m, inv: shift and 1/denominator of the
-// row (unused by PH_MAX and PH_BWD_SRC, which reads the neighbour's); acc: running max or sum.
+// row (unused by PH_BWD_SRC, which reads the neighbour's); acc: running sum.
 template <int KT, int PH>
 __device__ __forceinline__ void visit(const SweepParams &p, int64_t e, int k0, const float *ar, const float *m,
                                       const float *inv, float *acc)
@@ -114,11 +135,7 @@ __device__ __forceinline__ void visit(const SweepParams &p, int64_t e, int k0, c
     for (int k = 0; k < KT; ++k) {
         x[k] += ar[k];
         const float sc = lrelu(x[k], p.slope);
-        if (PH == PH_MAX) {
-            acc[k] = fmaxf(acc[k], sc);
-        } else if (PH == PH_SUM) {
-            acc[k] += expf(sc - m[k]);
-        } else if (PH == PH_ALPHA) {
+        if (PH == PH_ALPHA) {
             a[k] = expf(sc - m[k]) * inv[k];
             gt[k] = x[k] > 0.f ? a[k] : 0.f; // the weight restricted to edges with a positive logit
         } else if (PH == PH_BWD_DST) {
@@ -134,102 +151,111 @@ __device__ __forceinline__ void visit(const SweepParams &p, int64_t e, int k0, c
     if (PH == PH_BWD_SRC || ((PH == PH_ALPHA || PH == PH_BWD_DST) && p.gate)) storek<KT>(p.gate + e * p.K + k0, gt);
 }
 
+// the slots e0 + lane, e0 + lane + W, ...
 template <int W, int KT, int PH>
 __device__ __forceinline__ void sweep_range(const SweepParams &p, int64_t e0, int64_t e1, int lane, int k0, const float *ar,
                                             const float *m, const float *inv, float *acc)
 {
-#pragma unroll 4
+#pragma unroll KT >= 8 ? 2 : 4
     for (int64_t e = e0 + lane; e < e1; e += W) visit<KT, PH>(p, e, k0, ar, m, inv, acc);
 }
 
-template <int KT> __device__ __forceinline__ void wave_sum(float *v)
+// over the W lanes of a row's group
+template <int W, int KT> __device__ __forceinline__ void group_sum(float *v)
 {
 #pragma unroll
     for (int k = 0; k < KT; ++k)
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off, 64);
+        for (int off = W / 2; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off, 64);
 }
-template <int KT> __device__ __forceinline__ void wave_max(float *v)
+template <int W, int KT> __device__ __forceinline__ void group_max(float *v)
 {
 #pragma unroll
     for (int k = 0; k < KT; ++k)
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v[k] = fmaxf(v[k], __shfl_xor(v[k], off, 64));
+        for (int off = W / 2; off > 0; off >>= 1) v[k] = fmaxf(v[k], __shfl_xor(v[k], off, 64));
 }
 
-// rows below the hub threshold: W = 1 (one thread per row) or W = 64 (one wavefront per row)
-template <int W, int KT, int OP>
-__global__ void __launch_bounds__(256) attn_rows_kernel(SweepParams p)
+// Forward statistics of up to W NPL edges from slot e0, W lanes, NPL slots per lane: every id and score is loaded
+// once.  Left in x: exp(logit - m), negated where the logit is not positive; m: the largest logit (-inf without
+// edges), den and pos: the sums of all exps and of those of positive logits, in every lane of the group.
+template <int W, int KT, int NPL>
+__device__ __forceinline__ void fwd_stats(const SweepParams &p, int64_t e0, int n, int lane, int k0, const float *ar, float (&x)[NPL][KT],
+                                          float *m, float *den, float *pos)
 {
-    const int lane = W == 1 ? 0 : (threadIdx.x & 63);
-    const int64_t q = p.q0 + (W == 1 ? static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x
-                                     : static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6));
-    if (q >= p.q1) return; // uniform per wavefront when W = 64
-    const int k0 = blockIdx.y * KT;
-    const int64_t row = p.perm[q];
-    const int64_t e0 = p.sptr[q], e1 = p.sptr[q + 1];
-    float ar[KT], acc[KT], m[KT], inv[KT];
-    loadk<KT>(p.row_a + row * p.K + k0, ar);
-    if (OP == SWEEP_FWD && W == 1 && e1 - e0 <= 4 && e1 > e0) {
-        // up to four edges (most rows of a power-law graph): the logits stay in registers, one pass
-        const int n = static_cast<int>(e1 - e0);
-        float sc[4][KT];
+    int64_t id[NPL];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (j < n) {
-                loadk<KT>(p.nbr_a + static_cast<int64_t>(p.sidx[e0 + j]) * p.K + k0, sc[j]);
+    for (int j = 0; j < NPL; ++j) id[j] = lane + j * W < n ? p.sidx[e0 + lane + j * W] : -1;
 #pragma unroll
-                for (int k = 0; k < KT; ++k) sc[j][k] = lrelu(sc[j][k] + ar[k], p.slope);
-            } else {
+    for (int j = 0; j < NPL; ++j) {
 #pragma unroll
-                for (int k = 0; k < KT; ++k) sc[j][k] = -INFINITY;
-            }
-        }
+        for (int k = 0; k < KT; ++k) x[j][k] = 0.f;
+        if (id[j] >= 0) loadk<KT>(p.nbr_a + id[j] * p.K + k0, x[j]);
+    }
+#pragma unroll
+    for (int k = 0; k < KT; ++k) {
+        m[k] = -INFINITY;
+        den[k] = pos[k] = 0.f;
+    }
+#pragma unroll
+    for (int j = 0; j < NPL; ++j)
 #pragma unroll
         for (int k = 0; k < KT; ++k) {
-            m[k] = fmaxf(fmaxf(sc[0][k], sc[1][k]), fmaxf(sc[2][k], sc[3][k]));
-            float den = 0.f;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) den += j < n ? expf(sc[j][k] - m[k]) : 0.f; // same order as the general path
-            inv[k] = 1.f / den;
+            x[j][k] = lrelu(x[j][k] + ar[k], p.slope);
+            if (id[j] >= 0) m[k] = fmaxf(m[k], x[j][k]);
         }
+    group_max<W, KT>(m);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (j < n) {
-                float a[KT], gt[KT];
+    for (int j = 0; j < NPL; ++j)
 #pragma unroll
-                for (int k = 0; k < KT; ++k) {
-                    a[k] = expf(sc[j][k] - m[k]) * inv[k];
-                    gt[k] = sc[j][k] > 0.f ? a[k] : 0.f; // LeakyReLU keeps the sign of the logit
-                }
-                storek<KT>(p.alpha + (e0 + j) * p.K + k0, a);
-                if (p.gate) storek<KT>(p.gate + (e0 + j) * p.K + k0, gt);
-            }
+        for (int k = 0; k < KT; ++k) {
+            const bool up = x[j][k] > 0.f; // LeakyReLU keeps the sign of the logit
+            const float e = id[j] >= 0 ? expf(x[j][k] - m[k]) : 0.f;
+            den[k] += e;
+            pos[k] += up ? e : 0.f;
+            x[j][k] = up ? e : -e;
         }
-        if (p.smax) {
-            storek<KT>(p.smax + row * p.K + k0, m);
-            storek<KT>(p.sinv + row * p.K + k0, inv);
-        }
-    } else if (OP == SWEEP_FWD) {
-#pragma unroll
-        for (int k = 0; k < KT; ++k) m[k] = -INFINITY;
-        sweep_range<W, KT, PH_MAX>(p, e0, e1, lane, k0, ar, nullptr, nullptr, m);
-        if (W == 64) wave_max<KT>(m);
-#pragma unroll
-        for (int k = 0; k < KT; ++k) acc[k] = 0.f;
-        sweep_range<W, KT, PH_SUM>(p, e0, e1, lane, k0, ar, m, nullptr, acc);
-        if (W == 64) wave_sum<KT>(acc);
-        const bool empty = e1 == e0;
+    group_sum<W, KT>(den);
+    group_sum<W, KT>(pos);
+}
+
+// One row: W lanes, at most W NPL edges.
+template <int W, int KT, int NPL, int OP>
+__device__ __forceinline__ void sweep_row(const SweepParams &p, int64_t q, bool live, int lane, int k0)
+{
+    const int64_t row = live ? p.perm[q] : 0;
+    const int64_t e0 = live ? p.sptr[q] : 0, e1 = live ? p.sptr[q + 1] : 0;
+    float ar[KT], acc[KT], m[KT], inv[KT];
+    loadk<KT>(p.row_a + row * p.K + k0, ar);
+    if (OP == SWEEP_FWD) {
+        const int n = static_cast<int>(e1 - e0);
+        float x[NPL][KT], pos[KT];
+        fwd_stats<W, KT, NPL>(p, e0, n, lane, k0, ar, x, m, acc, pos);
+        const bool empty = n == 0;
 #pragma unroll
         for (int k = 0; k < KT; ++k) {
             inv[k] = empty ? 0.f : 1.f / acc[k];
             if (empty) m[k] = 0.f;
+            pos[k] = empty ? 0.f : pos[k] * inv[k];
         }
-        sweep_range<W, KT, PH_ALPHA>(p, e0, e1, lane, k0, ar, m, inv, nullptr);
-        if (lane == 0 && p.smax) {
+#pragma unroll
+        for (int j = 0; j < NPL; ++j) {
+            if (lane + j * W < n) {
+                float a[KT], gt[KT];
+#pragma unroll
+                for (int k = 0; k < KT; ++k) {
+                    a[k] = fabsf(x[j][k]) * inv[k];
+                    gt[k] = x[j][k] > 0.f ? a[k] : 0.f; // the weight restricted to edges with a positive logit
+                }
+                storek<KT>(p.alpha + (e0 + lane + j * W) * p.K + k0, a);
+                if (p.gate) storek<KT>(p.gate + (e0 + lane + j * W) * p.K + k0, gt);
+            }
+        }
+        if (live && lane == 0 && p.smax) {
             storek<KT>(p.smax + row * p.K + k0, m);
             storek<KT>(p.sinv + row * p.K + k0, inv);
         }
+        if (live && lane == 0 && p.apos) storek<KT>(p.apos + row * p.K + k0, pos);
     } else {
 #pragma unroll
         for (int k = 0; k < KT; ++k) acc[k] = 0.f;
@@ -240,8 +266,8 @@ __global__ void __launch_bounds__(256) attn_rows_kernel(SweepParams p)
         } else {
             sweep_range<W, KT, PH_BWD_SRC>(p, e0, e1, lane, k0, ar, nullptr, nullptr, acc);
         }
-        if (W == 64) wave_sum<KT>(acc);
-        if (lane == 0) {
+        group_sum<W, KT>(acc);
+        if (live && lane == 0) {
             if (OP == SWEEP_BWD_CSR) {
                 float d[KT];
                 loadk<KT>(p.dot + row * p.K + k0, d);
@@ -266,33 +292,24 @@ __device__ __forceinline__ int64_t hub_of_chunk(const SweepParams &p, int64_t w)
 }
 
 // hub chunks, first kernel: partial statistics of one chunk (and the backward's weights)
-template <int KT, int OP>
-__global__ void __launch_bounds__(256) attn_hub_partial_kernel(SweepParams p)
+template <int KT, int OP> __device__ __forceinline__ void sweep_hub_chunk(const SweepParams &p, int64_t w, int lane, int k0)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t w = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-    if (w >= p.n_hub_chunks) return; // uniform per wavefront
-    const int k0 = blockIdx.y * KT;
+    static_assert(kHubChunk == 256, "four slots per lane");
     const HubChunk c = p.hub_chunks[w];
     const int64_t row = p.perm[hub_of_chunk(p, w)];
     const int64_t e0 = c.e0, e1 = c.e0 + c.len;
     float ar[KT], acc[KT], m[KT], inv[KT];
     loadk<KT>(p.row_a + row * p.K + k0, ar);
-    float *out = p.part + (w * p.K + k0) * 2;
+    float *out = p.part + (w * p.K + k0) * 3;
     if (OP == SWEEP_FWD) {
-#pragma unroll
-        for (int k = 0; k < KT; ++k) m[k] = -INFINITY;
-        sweep_range<64, KT, PH_MAX>(p, e0, e1, lane, k0, ar, nullptr, nullptr, m);
-        wave_max<KT>(m);
-#pragma unroll
-        for (int k = 0; k < KT; ++k) acc[k] = 0.f;
-        sweep_range<64, KT, PH_SUM>(p, e0, e1, lane, k0, ar, m, nullptr, acc);
-        wave_sum<KT>(acc);
+        float x[4][KT], pos[KT];
+        fwd_stats<64, KT, 4>(p, e0, static_cast<int>(e1 - e0), lane, k0, ar, x, m, acc, pos);
         if (lane == 0) {
 #pragma unroll
             for (int k = 0; k < KT; ++k) {
-                out[2 * k] = m[k];
-                out[2 * k + 1] = acc[k];
+                out[3 * k] = m[k];
+                out[3 * k + 1] = acc[k];
+                out[3 * k + 2] = pos[k];
             }
         }
     } else {
@@ -305,11 +322,33 @@ __global__ void __launch_bounds__(256) attn_hub_partial_kernel(SweepParams p)
         } else {
             sweep_range<64, KT, PH_BWD_SRC>(p, e0, e1, lane, k0, ar, nullptr, nullptr, acc);
         }
-        wave_sum<KT>(acc);
+        group_sum<64, KT>(acc);
         if (lane == 0) {
 #pragma unroll
-            for (int k = 0; k < KT; ++k) out[2 * k] = acc[k];
+            for (int k = 0; k < KT; ++k) out[3 * k] = acc[k];
         }
+    }
+}
+
+// All row classes of a schedule in one launch: the class follows from the workgroup's index (uniform).
+template <int KT, int OP>
+__global__ void __launch_bounds__(256) attn_rows_kernel(SweepParams p)
+{
+    const int lane = threadIdx.x & 63;
+    const int k0 = blockIdx.y * KT;
+    const unsigned b = blockIdx.x;
+    if (b < p.b_wave) {
+        const int64_t w = static_cast<int64_t>(b) * 4 + (threadIdx.x >> 6);
+        if (w < p.n_hub_chunks) sweep_hub_chunk<KT, OP>(p, w, lane, k0); // uniform per wavefront
+    } else if (b < p.b_mid) {
+        const int64_t q = p.q_wave + static_cast<int64_t>(b - p.b_wave) * 4 + (threadIdx.x >> 6);
+        if (q < p.q_mid) sweep_row<64, KT, 8, OP>(p, q, true, lane, k0);
+    } else if (b < p.b_short) {
+        const int64_t q = p.q_mid + static_cast<int64_t>(b - p.b_mid) * 32 + (threadIdx.x >> 3);
+        sweep_row<8, KT, 4, OP>(p, q, q < p.q_short, threadIdx.x & 7, k0); // every lane of the wavefront takes part in the sums
+    } else {
+        const int64_t q = p.q_short + static_cast<int64_t>(b - p.b_short) * 256 + threadIdx.x;
+        if (q < p.n_rows) sweep_row<1, KT, 4, OP>(p, q, true, 0, k0);
     }
 }
 
@@ -325,11 +364,17 @@ __global__ void __launch_bounds__(256) attn_hub_combine_kernel(SweepParams p)
     const int64_t s0 = p.hub_chunk_ptr[h], s1 = p.hub_chunk_ptr[h + 1];
     if (OP == SWEEP_FWD) {
         float m = -INFINITY;
-        for (int64_t s = s0 + lane; s < s1; s += 64) m = fmaxf(m, p.part[(s * p.K + k) * 2]);
-        wave_max<1>(&m);
-        float den = 0.f;
-        for (int64_t s = s0 + lane; s < s1; s += 64) den += p.part[(s * p.K + k) * 2 + 1] * expf(p.part[(s * p.K + k) * 2] - m);
-        wave_sum<1>(&den);
+        for (int64_t s = s0 + lane; s < s1; s += 64) m = fmaxf(m, p.part[(s * p.K + k) * 3]);
+        group_max<64, 1>(&m);
+        float den = 0.f, pos = 0.f;
+        for (int64_t s = s0 + lane; s < s1; s += 64) {
+            const float *t = p.part + (s * p.K + k) * 3;
+            const float e = expf(t[0] - m);
+            den += t[1] * e;
+            pos += t[2] * e;
+        }
+        group_sum<64, 1>(&den);
+        group_sum<64, 1>(&pos);
         if (lane == 0) {
             const float inv = 1.f / den; // a hub row has edges
             p.hub_stat[(h * p.K + k) * 2] = m;
@@ -338,11 +383,12 @@ __global__ void __launch_bounds__(256) attn_hub_combine_kernel(SweepParams p)
                 p.smax[row * p.K + k] = m;
                 p.sinv[row * p.K + k] = inv;
             }
+            if (p.apos) p.apos[row * p.K + k] = pos * inv;
         }
     } else {
         float a = 0.f;
-        for (int64_t s = s0 + lane; s < s1; s += 64) a += p.part[(s * p.K + k) * 2];
-        wave_sum<1>(&a);
+        for (int64_t s = s0 + lane; s < s1; s += 64) a += p.part[(s * p.K + k) * 3];
+        group_sum<64, 1>(&a);
         if (lane == 0) p.corr[row * p.K + k] = OP == SWEEP_BWD_CSR ? (a - p.dot_shift) * p.dot[row * p.K + k] : a;
     }
 }
@@ -385,36 +431,32 @@ __global__ void __launch_bounds__(256) attn_pack_kernel(const float *er, const f
 
 inline size_t hub_scratch_bytes(const Schedule &s, int K)
 {
-    return static_cast<size_t>(s.n_hub_chunks + s.n_hub_rows) * K * 2 * sizeof(float);
+    return static_cast<size_t>(s.n_hub_chunks * 3 + s.n_hub_rows * 2) * K * sizeof(float);
 }
 
 template <int KT, int OP>
 heta_status launch_sweeps_kt(const Schedule &s, SweepParams p, hipStream_t st)
 {
-    const int64_t n_long_or_hub = s.rows_with_deg_ge[kShortDegAttn];
     const unsigned gy = p.K / KT;
+    p.q_wave = s.n_hub_rows;
+    p.q_mid = s.rows_with_deg_ge[kShortDegAttn];
+    p.q_short = s.rows_with_deg_ge[kThreadDegAttn + 1];
+    p.n_rows = s.n_rows;
+    const int64_t cb = (s.n_hub_chunks + 3) / 4;
+    const int64_t wb = (p.q_mid - p.q_wave + 3) / 4, mb = (p.q_short - p.q_mid + 31) / 32, sb = (p.n_rows - p.q_short + 255) / 256;
+    if (cb + wb + mb + sb > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "attention: too many rows");
+    p.b_wave = (unsigned)cb;
+    p.b_mid = (unsigned)(cb + wb);
+    p.b_short = (unsigned)(cb + wb + mb);
+    hipLaunchKernelGGL((attn_rows_kernel<KT, OP>), dim3((unsigned)(cb + wb + mb + sb), gy), dim3(256), 0, st, p);
+    HETA_LAUNCH_CHECK("attn_rows_kernel");
     if (s.n_hub_rows > 0) {
-        const unsigned cb = (unsigned)((s.n_hub_chunks + 3) / 4), rb = (unsigned)((s.n_hub_rows + 3) / 4);
-        hipLaunchKernelGGL((attn_hub_partial_kernel<KT, OP>), dim3(cb, gy), dim3(256), 0, st, p);
-        HETA_LAUNCH_CHECK("attn_hub_partial_kernel");
-        hipLaunchKernelGGL((attn_hub_combine_kernel<OP>), dim3(rb, p.K), dim3(256), 0, st, p);
+        hipLaunchKernelGGL((attn_hub_combine_kernel<OP>), dim3((unsigned)((s.n_hub_rows + 3) / 4), p.K), dim3(256), 0, st, p);
         HETA_LAUNCH_CHECK("attn_hub_combine_kernel");
         if (OP == SWEEP_FWD) {
-            hipLaunchKernelGGL((attn_hub_alpha_kernel<KT>), dim3(cb, gy), dim3(256), 0, st, p);
+            hipLaunchKernelGGL((attn_hub_alpha_kernel<KT>), dim3((unsigned)cb, gy), dim3(256), 0, st, p);
             HETA_LAUNCH_CHECK("attn_hub_alpha_kernel");
         }
-    }
-    if (n_long_or_hub > s.n_hub_rows) {
-        p.q0 = s.n_hub_rows;
-        p.q1 = n_long_or_hub;
-        hipLaunchKernelGGL((attn_rows_kernel<64, KT, OP>), dim3((unsigned)((p.q1 - p.q0 + 3) / 4), gy), dim3(256), 0, st, p);
-        HETA_LAUNCH_CHECK("attn_rows_kernel");
-    }
-    if (s.n_rows > n_long_or_hub) {
-        p.q0 = n_long_or_hub;
-        p.q1 = s.n_rows;
-        hipLaunchKernelGGL((attn_rows_kernel<1, KT, OP>), dim3((unsigned)((p.q1 - p.q0 + 255) / 256), gy), dim3(256), 0, st, p);
-        HETA_LAUNCH_CHECK("attn_rows_kernel");
     }
     return HETA_OK;
 }
@@ -432,7 +474,7 @@ heta_status launch_sweeps(const Schedule &s, SweepParams p, float *hub_scratch, 
     p.n_hub_rows = s.n_hub_rows;
     p.n_hub_chunks = s.n_hub_chunks;
     p.part = hub_scratch;
-    p.hub_stat = hub_scratch + s.n_hub_chunks * p.K * 2;
+    p.hub_stat = hub_scratch + s.n_hub_chunks * p.K * 3;
     // Algorithmic bytes: per edge one 4-byte id, per edge and head the neighbour's 4-byte terms and the
     // 4-byte weights written; per row its offsets and per-head terms.
     const double per_edge = 4.0 + p.K * (OP == SWEEP_BWD_CSC ? 24.0 : 8.0);
@@ -441,7 +483,8 @@ heta_status launch_sweeps(const Schedule &s, SweepParams p, float *hub_scratch, 
     const uintptr_t all = reinterpret_cast<uintptr_t>(p.row_a) | reinterpret_cast<uintptr_t>(p.nbr_a) |
                           reinterpret_cast<uintptr_t>(p.smax) | reinterpret_cast<uintptr_t>(p.sinv) |
                           reinterpret_cast<uintptr_t>(p.dot) | reinterpret_cast<uintptr_t>(p.nbr_pack) | reinterpret_cast<uintptr_t>(p.alpha) |
-                          reinterpret_cast<uintptr_t>(p.gate) | reinterpret_cast<uintptr_t>(p.corr);
+                          reinterpret_cast<uintptr_t>(p.gate) | reinterpret_cast<uintptr_t>(p.corr) | reinterpret_cast<uintptr_t>(p.apos);
+    if (p.K % 8 == 0 && all % 16 == 0) return launch_sweeps_kt<8, OP>(s, p, st);
     if (p.K % 4 == 0 && all % 16 == 0) return launch_sweeps_kt<4, OP>(s, p, st);
     if (p.K % 2 == 0 && all % 8 == 0) return launch_sweeps_kt<2, OP>(s, p, st);
     return launch_sweeps_kt<1, OP>(s, p, st);

@@ -189,6 +189,42 @@ def test_rel_attn_forward_and_backward(kind, n_src, n_dst, n_edges, d, heads, st
     graph.destroy()
 
 
+ROW_CLASS_DEGREES = [0, 1, 3, 4, 5, 8, 9, 31, 32, 33, 64, 65, 511, 512, 513, 768, 769, 1100] + [4, 5, 0, 31, 32] * 9
+
+
+@pytest.mark.parametrize("heads", [1, 2, 3, 4, 8, 16])
+@pytest.mark.parametrize("side", ["dst", "src"])
+def test_sweeps_at_the_edges_of_the_row_classes(heads, side):
+    """Rows of 4 / 5, 31 / 32 and 511 / 512 edges change the kernel that sweeps them, 256 the hub chunk; the
+    forward sweeps the destinations' rows, the backward also the sources'."""
+    deg = np.array(ROW_CLASS_DEGREES)
+    n_many, n_other = deg.size, 300
+    g = rng.stream("tests", f"row_classes{heads}{side}")
+    many = np.repeat(np.arange(n_many), deg)
+    other = g.integers(0, n_other, many.size)
+    dst, src = (many, other) if side == "dst" else (other, many)
+    n_dst, n_src = (n_many, n_other) if side == "dst" else (n_other, n_many)
+    order = np.argsort(dst, kind="stable")
+    src, dst = src[order], dst[order]
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(dst, minlength=n_dst))]).astype(np.int64)
+    d = 8 * heads
+    z, go = g.standard_normal((n_src, d)).astype(np.float32), g.standard_normal((n_dst, d)).astype(np.float32)
+    el, er = (2.0 * g.standard_normal((n_src, heads))).astype(np.float32), (2.0 * g.standard_normal((n_dst, heads))).astype(np.float32)
+    graph = heta.heta_graph_create([(n_src, 4, 0), (n_dst, 4, 0)], [(0, 1, rowptr, src.astype(np.int32))])
+    try:
+        out, pos = (torch.full((n_dst, d), 3.0, device="cuda") for _ in range(2))
+        smax, sinv, d_er = (torch.full((n_dst, heads), 5.0, device="cuda") for _ in range(3))
+        dz, d_el = torch.full((n_src, d), 5.0, device="cuda"), torch.full((n_src, heads), 5.0, device="cuda")
+        heta.heta_rel_attn_fwd(graph, 0, up(z), up(el), up(er), 0.2, out, smax=smax, sinv=sinv, out_pos=pos)
+        heta.heta_rel_attn_bwd(graph, 0, up(z), up(el), up(er), 0.2, smax, sinv, out, up(go), dz, d_el, d_er, o_pos=pos)
+        ref_o, alpha = rgat.gat_aggregate_fwd(src, dst, n_dst, z, el, er, 0.2)
+        rdz, rdel, rder = rgat.gat_aggregate_bwd(src, dst, n_src, n_dst, z, el, er, alpha, go, 0.2)
+        for got, ref, what in ((out, ref_o, "out"), (dz, rdz, "dz"), (d_el, rdel, "del"), (d_er, rder, "der")):
+            assert_rows_close(host(got), ref, 1e-4, what)
+    finally:
+        graph.destroy()
+
+
 def test_attention_argument_checks():
     graph = heta.heta_graph_create([(4, 4, 0)], [(0, 0, np.array([0, 1, 2, 2, 2], dtype=np.int64), np.array([1, 0], dtype=np.int32))])
     z = torch.zeros((4, 12), device="cuda")
