@@ -402,6 +402,28 @@ heta_status heta_rel_attn_bwd(heta_graph *g, int32_t rel, const void *z, heta_dt
                               const float *grad_out, int64_t ld_go, float *dz, int64_t ld_dz, float *del, float *der,
                               void *hip_stream);
 
+/* The same training step in the form that visits no edge on the destination side:
+ * heta_rel_attn_fwd_train is heta_rel_attn_fwd that also writes apos[v, k] = the sum of alpha_e[k] over the in-edges of
+ *   v with a positive logit (device fp32 [n_dst, K]; NULL: heta_rel_attn_fwd).
+ * heta_attn_bwd_dst covers up to 8 relations into one node type in one pass over its rows: grad_in = act'(h) grad_out
+ *   (device fp32; h and grad_in are used for HETA_ACT_RELU only, without an activation grad_out is the gradient itself)
+ *   and per relation der (as heta_rel_attn_bwd) and pack[v][k][0..3] = er, smax, sinv, <grad, o> (16-byte
+ *   aligned).  o / o_pos / er /
+ *   smax / sinv / apos / der / pack: HOST arrays of n_rels device fp32 pointers, o and o_pos [n, ld_o[j]] each.
+ * heta_rel_attn_bwd_src writes dz and del of one relation from its pack and the gradient of its outputs. */
+heta_status heta_rel_attn_fwd_train(heta_graph *g, int32_t rel, const void *z, heta_dtype z_dt, int64_t ld_z, int32_t d,
+                                    int32_t heads, const float *el, const float *er, float slope, void *out,
+                                    heta_dtype out_dt, int64_t ld_out, float beta, float *smax, float *sinv, void *out_pos,
+                                    int64_t ld_pos, float *apos, void *hip_stream);
+heta_status heta_attn_bwd_dst(heta_graph *g, int32_t dst_type, int32_t n_rels, const int32_t *rels, int32_t d, int32_t heads, float slope,
+                              heta_act act, const float *h, int64_t ld_h, const float *grad_out, int64_t ld_go, float *grad_in,
+                              int64_t ld_gi, const float *const *o, const float *const *o_pos, const int64_t *ld_o,
+                              const float *const *er, const float *const *smax, const float *const *sinv, const float *const *apos,
+                              float *const *der, float *const *pack, void *hip_stream);
+heta_status heta_rel_attn_bwd_src(heta_graph *g, int32_t rel, const void *z, heta_dtype z_dt, int64_t ld_z, int32_t d, int32_t heads,
+                                  const float *el, float slope, const float *pack, const float *grad_out, int64_t ld_go, float *dz,
+                                  int64_t ld_dz, float *del, void *hip_stream);
+
 /* ---- k-hop neighbour sampling into blocks (Section 2.2 and the sampling step of Algorithm 1: a fixed
  * number of neighbours per relation is sampled, hop by hop, for the nodes of a mini-batch; fan-outs
  * {25, 20} in Section 8.1).  Rule: all in-edges of a destination if its in-degree is at most `fanout`,

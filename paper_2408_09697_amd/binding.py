@@ -32,7 +32,8 @@ EXPORTS = ["heta_graph_create", "heta_graph_create_batch", "heta_graph_destroy",
            "heta_profile_read", "heta_calibration_copy", "heta_calibration_mfma", "heta_cross_rel_project", "heta_cross_rel_project_bwd",
            "heta_cross_rel_project_wgrad", "heta_sparse_adam", "heta_project_batch",
            "heta_project_sum", "heta_project_wgrad_batch", "heta_attn_score", "heta_attn_score_bwd", "heta_attn_score_multi", "heta_attn_score_bwd_multi",
-           "heta_rel_attn_fwd", "heta_rel_attn_bwd", "heta_sample_neighbors", "heta_unique_relabel",
+           "heta_rel_attn_fwd", "heta_rel_attn_bwd", "heta_rel_attn_fwd_train", "heta_attn_bwd_dst", "heta_rel_attn_bwd_src",
+           "heta_sample_neighbors", "heta_unique_relabel",
            "heta_cross_rel_aggregate_project", "heta_meta_partition", "heta_sample_neighbors_batch",
            "heta_unique_relabel_batch", "heta_rel_aggregate_fwd_noalloc", "heta_attn_fold", "heta_attn_fold_bwd",
            "heta_graph_index_bytes"]
@@ -812,6 +813,14 @@ def heta_rel_attn_fwd(g: Graph, rel: int, z: torch.Tensor, el: torch.Tensor, er:
                       out: torch.Tensor, beta: float = 0.0, smax: Optional[torch.Tensor] = None,
                       sinv: Optional[torch.Tensor] = None, out_pos: Optional[torch.Tensor] = None,
                       d: Optional[int] = None, stream=None) -> torch.Tensor:
+    return heta_rel_attn_fwd_train(g, rel, z, el, er, slope, out, beta, smax, sinv, out_pos, d=d, stream=stream)
+
+
+def heta_rel_attn_fwd_train(g: Graph, rel: int, z: torch.Tensor, el: torch.Tensor, er: torch.Tensor, slope: float,
+                            out: torch.Tensor, beta: float = 0.0, smax: Optional[torch.Tensor] = None,
+                            sinv: Optional[torch.Tensor] = None, out_pos: Optional[torch.Tensor] = None,
+                            apos: Optional[torch.Tensor] = None, d: Optional[int] = None, stream=None) -> torch.Tensor:
+    """heta_rel_attn_fwd that also writes apos[v, k], the attention weight of v's in-edges with a positive logit."""
     d = z.shape[1] if d is None else d
     heads = el.shape[1]
     if z.shape[0] < g.n_src(rel) or out.shape[0] < g.n_dst(rel):
@@ -820,13 +829,14 @@ def heta_rel_attn_fwd(g: Graph, rel: int, z: torch.Tensor, el: torch.Tensor, er:
         raise HetaError(HETA_ERR_SHAPE, "out_pos must match out")
     L = load_library()
     vp, i32, i64, f32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float
-    L.heta_rel_attn_fwd.argtypes = [vp, i32, vp, i32, i64, i32, i32, vp, vp, f32, vp, i32, i64, f32, vp, vp, vp, i64, vp]
-    _check(L.heta_rel_attn_fwd(g.handle, rel, _dev(z, "z"), _dt(z), _ld(z), d, heads,
+    L.heta_rel_attn_fwd_train.argtypes = [vp, i32, vp, i32, i64, i32, i32, vp, vp, f32, vp, i32, i64, f32, vp, vp, vp, i64, vp, vp]
+    _check(L.heta_rel_attn_fwd_train(g.handle, rel, _dev(z, "z"), _dt(z), _ld(z), d, heads,
                                _scores(el, "el", g.n_src(rel), heads), _scores(er, "er", g.n_dst(rel), heads), slope,
                                _dev(out, "out"), _dt(out), _ld(out), beta,
                                None if smax is None else _scores(smax, "smax", g.n_dst(rel), heads),
                                None if sinv is None else _scores(sinv, "sinv", g.n_dst(rel), heads),
-                               _dev(out_pos, "out_pos"), _ld(out_pos) if out_pos is not None else 0, _stream(stream)))
+                               _dev(out_pos, "out_pos"), _ld(out_pos) if out_pos is not None else 0,
+                               None if apos is None else _scores(apos, "apos", g.n_dst(rel), heads), _stream(stream)))
     return out
 
 
@@ -852,6 +862,57 @@ def heta_rel_attn_bwd(g: Graph, rel: int, z: torch.Tensor, el: torch.Tensor, er:
                                _dev(grad_out, "grad_out", torch.float32), _ld(grad_out),
                                _dev(dz, "dz", torch.float32), _ld(dz), _scores(d_el, "del", n_src, heads),
                                _scores(d_er, "der", n_dst, heads), _stream(stream)))
+
+
+def heta_attn_bwd_dst(g: Graph, dst_type: int, rels: Sequence[int], slope: float, act: int, h: Optional[torch.Tensor],
+                      grad_out: torch.Tensor, grad_in: Optional[torch.Tensor], o: Sequence[torch.Tensor], o_pos: Sequence[torch.Tensor],
+                      er: Sequence[torch.Tensor], smax: Sequence[torch.Tensor], sinv: Sequence[torch.Tensor], apos: Sequence[torch.Tensor],
+                      d_er: Sequence[torch.Tensor], pack: Sequence[torch.Tensor], stream=None) -> torch.Tensor:
+    """Destination side of the attention backward of up to 8 relations into one node type; returns the gradient
+    behind the activation (grad_in, or grad_out without one)."""
+    n, heads, d = g.ntypes[dst_type][0], er[0].shape[1], o[0].shape[1]
+    relu = act == HETA_ACT_RELU
+    if relu and (grad_in.shape[0] < grad_out.shape[0] or grad_in.shape[1] < grad_out.shape[1]):
+        raise HetaError(HETA_ERR_SHAPE, "buffers too small")
+    for t in [grad_out, *o, *o_pos] + ([h, grad_in] if relu else []):
+        if t.shape[0] < n or t.shape[1] < d:
+            raise HetaError(HETA_ERR_SHAPE, "a buffer is smaller than the node type needs")
+    for a, b in zip(o, o_pos):
+        if _ld(a) != _ld(b):
+            raise HetaError(HETA_ERR_SHAPE, "o_pos must match o (leading dimension)")
+    k = len(rels)
+    L = load_library()
+    vp, i32, i64, f32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float
+    L.heta_attn_bwd_dst.argtypes = [vp, i32, i32, vp, i32, i32, f32, i32, vp, i64, vp, i64, vp, i64] + [vp] * 10
+
+    def rows(ts, name, width):
+        return (ctypes.c_void_p * k)(*[_scores(t, name, n, width) for t in ts])
+
+    _check(L.heta_attn_bwd_dst(g.handle, dst_type, k, (ctypes.c_int32 * k)(*rels), d, heads, slope, act,
+                               _dev(h, "h", torch.float32) if relu else None, _ld(h) if relu else 0,
+                               _dev(grad_out, "grad_out", torch.float32), _ld(grad_out),
+                               _dev(grad_in, "grad_in", torch.float32) if relu else None, _ld(grad_in) if relu else 0,
+                               _ptr_array(o, "o", torch.float32), _ptr_array(o_pos, "o_pos", torch.float32),
+                               (ctypes.c_int64 * k)(*[_ld(t) for t in o]), rows(er, "er", heads), rows(smax, "smax", heads),
+                               rows(sinv, "sinv", heads), rows(apos, "apos", heads), rows(d_er, "der", heads),
+                               rows(pack, "pack", 4 * heads), _stream(stream)))
+    return grad_in if relu else grad_out
+
+
+def heta_rel_attn_bwd_src(g: Graph, rel: int, z: torch.Tensor, el: torch.Tensor, slope: float, pack: torch.Tensor,
+                          grad_out: torch.Tensor, dz: torch.Tensor, d_el: torch.Tensor, d: Optional[int] = None, stream=None) -> None:
+    """Source side of the attention backward: dz and d_el from the destinations' pack and gradient rows."""
+    d = z.shape[1] if d is None else d
+    heads = el.shape[1]
+    n_src, n_dst = g.n_src(rel), g.n_dst(rel)
+    if z.shape[0] < n_src or dz.shape[0] < n_src or grad_out.shape[0] < n_dst:
+        raise HetaError(HETA_ERR_SHAPE, "a buffer has fewer rows than the relation needs")
+    L = load_library()
+    vp, i32, i64, f32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float
+    L.heta_rel_attn_bwd_src.argtypes = [vp, i32, vp, i32, i64, i32, i32, vp, f32, vp, vp, i64, vp, i64, vp, vp]
+    _check(L.heta_rel_attn_bwd_src(g.handle, rel, _dev(z, "z"), _dt(z), _ld(z), d, heads, _scores(el, "el", n_src, heads), slope,
+                                   _scores(pack, "pack", n_dst, 4 * heads), _dev(grad_out, "grad_out", torch.float32), _ld(grad_out),
+                                   _dev(dz, "dz", torch.float32), _ld(dz), _scores(d_el, "del", n_src, heads), _stream(stream)))
 
 
 def heta_cross_rel_aggregate_project(g: Graph, dst_type: int, rels: List[int], op: int, tables: List[torch.Tensor],

@@ -10,11 +10,12 @@ itself.  Per relation r from source type s to destination type t:
                                             table (narrower than Z_r, and never rounded to the storage type)
     er_r = <H0_t[v], q_r[k]>                a score of the destination type's table; all scores of one table in
                                             one pass (heta_attn_score_multi)
-    O_r  = edge-softmax weighted sum of Z_r heta_rel_attn_fwd
+    O_r  = edge-softmax weighted sum of Z_r heta_rel_attn_fwd_train
     H_t  = ReLU(sum_r O_r)                  heta_cross_rel_reduce
 
-and the backward runs the same chain in reverse (heta_act_bwd, heta_rel_attn_bwd,
-heta_attn_score_bwd_multi, heta_project_wgrad_batch, heta_attn_fold_bwd, heta_project_sum).
+and the backward runs the same chain in reverse (heta_attn_bwd_dst per destination type with the
+activation in it, heta_rel_attn_bwd_src per relation, heta_attn_score_bwd_multi,
+heta_project_wgrad_batch, heta_attn_fold_bwd, heta_project_sum).
 """
 from __future__ import annotations
 
@@ -26,6 +27,7 @@ from . import binding as hb
 
 _MAX_BATCH = 8  # products per batched projection launch
 _MAX_SETS = 8   # score vector sets per one-pass score call
+_MAX_DST = 8    # relations per destination-side pass of the backward
 
 
 class RgatLayer:
@@ -74,6 +76,10 @@ class RgatLayer:
         self.er = {r: torch.empty((n_dst(r), heads), dtype=f32, device=dev) for r in self.rels}
         self.smax = {r: torch.empty((n_dst(r), heads), dtype=f32, device=dev) for r in self.rels}
         self.sinv = {r: torch.empty((n_dst(r), heads), dtype=f32, device=dev) for r in self.rels}
+        # attention weight of the edges with a positive logit, and the terms that the source side of the backward
+        # gathers per destination (er, smax, sinv, <g, o>)
+        self.apos = {r: torch.empty((n_dst(r), heads), dtype=f32, device=dev) for r in self.rels}
+        self.pack = {r: torch.empty((n_dst(r), 4 * heads), dtype=f32, device=dev) for r in self.rels}
         self.O = {r: padded(n_dst(r), d_out, f32) for r in self.rels}
         # the same sums over the edges with a positive logit: saved so that the backward gathers no
         # feature row on the destination side
@@ -111,8 +117,8 @@ class RgatLayer:
                                          [self.el[r] if src else self.er[r] for r, src in part], stream=stream)
         for r in self.rels:
             s, t, _ = g.rels[r]
-            hb.heta_rel_attn_fwd(g, r, self.Z[r], self.el[r], self.er[r], self.slope, self.O[r], beta=0.0,
-                                 smax=self.smax[r], sinv=self.sinv[r], out_pos=self.Opos[r], stream=stream)
+            hb.heta_rel_attn_fwd_train(g, r, self.Z[r], self.el[r], self.er[r], self.slope, self.O[r], beta=0.0,
+                                       smax=self.smax[r], sinv=self.sinv[r], out_pos=self.Opos[r], apos=self.apos[r], stream=stream)
         for t, rs in self.rels_into.items():
             hb.heta_cross_rel_reduce(g, t, [self.O[r] for r in rs], self.H[t], act=self.act, stream=stream)
         return self.H
@@ -122,14 +128,19 @@ class RgatLayer:
         """G[t]: upstream gradient of H_t (fp32).  Fills dW, da, dq per relation and dH0 per node type."""
         g = self.g
         grads = {}
-        for t in self.rels_into:
-            grads[t] = hb.heta_act_bwd(self.act, self.H[t], G[t], self._Gact[t], stream=stream) if self.relu else G[t]
+        for t, rs in self.rels_into.items():  # activation, der and the packed terms of all relations into t: one pass
+            grad = G[t]
+            for i in range(0, len(rs), _MAX_DST):
+                part = rs[i:i + _MAX_DST]
+                of = lambda x: [x[r] for r in part]  # noqa: E731
+                grad = hb.heta_attn_bwd_dst(g, t, part, self.slope, self.act if i == 0 else hb.HETA_ACT_NONE, self.H[t], grad,
+                                            self._Gact.get(t), of(self.O), of(self.Opos), of(self.er), of(self.smax), of(self.sinv),
+                                            of(self.apos), of(self.d_er), of(self.pack), stream=stream)
+            grads[t] = grad
         written = set()
         for r in self.rels:
-            s, t, _ = g.rels[r]
-            hb.heta_rel_attn_bwd(g, r, self.Z[r], self.el[r], self.er[r], self.slope, self.smax[r], self.sinv[r],
-                                 self.O[r], grads[t], self.dZ[r], self.d_el[r], self.d_er[r], o_pos=self.Opos[r],
-                                 stream=stream)
+            hb.heta_rel_attn_bwd_src(g, r, self.Z[r], self.el[r], self.slope, self.pack[r], grads[g.rels[r][1]], self.dZ[r], self.d_el[r],
+                                     stream=stream)
         # el = <H0_s, wa> reaches the source type's table and, through wa, W_r and a_r; er = <H0_t, q> reaches the
         # destination type's table and gives dq: per node type, all of them in one pass over its table
         for t, sets in self._score_sets.items():

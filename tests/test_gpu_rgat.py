@@ -221,6 +221,47 @@ def test_sweeps_at_the_edges_of_the_row_classes(heads, side):
         rdz, rdel, rder = rgat.gat_aggregate_bwd(src, dst, n_src, n_dst, z, el, er, alpha, go, 0.2)
         for got, ref, what in ((out, ref_o, "out"), (dz, rdz, "dz"), (d_el, rdel, "del"), (d_er, rder, "der")):
             assert_rows_close(host(got), ref, 1e-4, what)
+        # the form without a sweep over the destinations' edges
+        apos, pack = torch.full((n_dst, heads), 5.0, device="cuda"), torch.full((n_dst, 4 * heads), 5.0, device="cuda")
+        heta.heta_rel_attn_fwd_train(graph, 0, up(z), up(el), up(er), 0.2, out, smax=smax, sinv=sinv, out_pos=pos, apos=apos)
+        ref_apos = np.zeros((n_dst, heads))
+        np.add.at(ref_apos, dst, alpha * ((el[src] + er[dst]) > 0))
+        assert_rows_close(host(apos), ref_apos, 1e-4, "apos")
+        for t in (d_er, dz, d_el):
+            t.fill_(5.0)
+        heta.heta_attn_bwd_dst(graph, 1, [0], 0.2, heta.HETA_ACT_NONE, None, up(go), None, [out], [pos], [up(er)], [smax], [sinv], [apos],
+                               [d_er], [pack])
+        heta.heta_rel_attn_bwd_src(graph, 0, up(z), up(el), 0.2, pack, up(go), dz, d_el)
+        for got, ref, what in ((dz, rdz, "dz"), (d_el, rdel, "del"), (d_er, rder, "der")):
+            assert_rows_close(host(got), ref, 1e-4, what)
+    finally:
+        graph.destroy()
+
+
+@pytest.mark.parametrize("n,d,heads,n_rels,pad", [(1000, 256, 4, 3, 4), (257, 64, 8, 1, 4), (130, 60, 3, 2, 4), (67, 100, 5, 8, 4), (5, 4, 1, 2, 4),
+                                                  # served row by row: heads of 6 columns, rows of more than 64 chunks, unaligned rows
+                                                  (50, 18, 3, 2, 4), (33, 320, 4, 2, 4), (40, 30, 2, 1, 1)])
+@pytest.mark.parametrize("relu", [True, False])
+def test_destination_side_of_the_backward(n, d, heads, n_rels, pad, relu):
+    g = rng.stream("tests", f"dst_side{n}x{d}x{heads}x{n_rels}")
+    go, h = (g.standard_normal((n, d)).astype(np.float32) for _ in range(2))
+    o, u = ([g.standard_normal((n, d)).astype(np.float32) for _ in range(n_rels)] for _ in range(2))
+    er, smax, sinv, apos = ([g.standard_normal((n, heads)).astype(np.float32) for _ in range(n_rels)] for _ in range(4))
+    graph = heta.heta_graph_create([(3, 4, 0), (n, 4, 0)], [(0, 1, np.zeros(n + 1, dtype=np.int64), np.zeros(0, dtype=np.int32))] * n_rels)
+    try:
+        tab = lambda x: dev_table(x, "f32", pad)  # noqa: E731
+        god, gi = tab(go), tab(np.full((n, d), 7.0, dtype=np.float32))
+        der, pack = [torch.full((n, heads), 5.0, device="cuda") for _ in o], [torch.full((n, 4 * heads), 5.0, device="cuda") for _ in o]
+        got = heta.heta_attn_bwd_dst(graph, 1, list(range(n_rels)), 0.2, heta.HETA_ACT_RELU if relu else heta.HETA_ACT_NONE, tab(h) if relu else None,
+                                     god, gi if relu else None, [tab(x) for x in o], [tab(x) for x in u], [up(x) for x in er],
+                                     [up(x) for x in smax], [up(x) for x in sinv], [up(x) for x in apos], der, pack)
+        ref = np.where(h > 0, go, 0.0).astype(np.float32) if relu else go
+        assert got is (gi if relu else god) and np.array_equal(host(got), ref)
+        dots = lambda x: (ref.astype(np.float64) * x).reshape(n, heads, -1).sum(2)  # noqa: E731
+        for j in range(n_rels):
+            dot = dots(o[j])
+            assert_rows_close(host(der[j]), 0.8 * (dots(u[j]) - apos[j] * dot), 1e-4, "der")
+            assert_rows_close(host(pack[j]), np.stack([er[j], smax[j], sinv[j], dot], axis=2).reshape(n, 4 * heads), 1e-4, "pack")
     finally:
         graph.destroy()
 
