@@ -252,11 +252,11 @@ struct TileLoader {
 // The direct-to-LDS pipeline (heta_gemm_direct.hip).  Sets *handled when it launched the product;
 // otherwise the caller falls back to the register-staged kernel.
 extern bool g_f32_native; // test switch, see heta_test_hooks.h
-// Bytes of the three-term form of a K x N fp32 operand, and the kernel that writes it: B(k, n) = W[k*ldw + n]
-// (trans = 0) or W[n*ldw + k] (trans = 1); x = h + m + l in bf16, zero beyond K and N.  out must be 16-byte aligned.
+// Bytes of the three-term form of a K x N fp32 operand, and the launch that writes it for the B operands of all of p's
+// segments, one after the other into `out` (16-byte aligned): B(k, n) = W[k*ldw + n] (trans = 0) or W[n*ldw + k]
+// (trans = 1); x = h + m + l in bf16, zero beyond K and N.
 size_t split3_weight_bytes(int64_t K, int64_t N);
-heta_status pack_split3_weights(const float *W, int64_t ldw, int64_t K, int64_t N, int trans, void *out, GemmSeg *seg,
-                                hipStream_t st);
+heta_status pack_split3_weights(GemmParams &p, int trans, void *out, hipStream_t st);
 // whether the direct pipeline would give this launch its 64 x 64 tiles (too few 128 x 128 tiles to fill the chip)
 bool gemm_direct_small(const GemmParams &p);
 int wgrad_tile_rows(const GemmParams &p);

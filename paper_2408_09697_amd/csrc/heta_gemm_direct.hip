@@ -418,9 +418,21 @@ __device__ __forceinline__ void x3_step_2x2_presplit(const float *At, const char
 #undef X3_HI
 }
 
-// Writes the three-term form of one B operand: one thread per (k-octet, column).
-__global__ void __launch_bounds__(256) pack_split3_kernel(const float *W, int64_t ldw, int K, int N, int trans, uint4 *out, int ko, int n_pad)
+// Writes the three-term form of the B operands of a product: one thread per (k-octet, column), blockIdx.y picks the
+// operand.  A launch of its own takes 4.5 us however small the matrix; one per operand was 5 % of a layer of 2 M edges.
+struct Split3Segs {
+    const float *W[kMaxSeg];
+    uint4 *out[kMaxSeg];
+    int64_t ldw[kMaxSeg];
+    int K[kMaxSeg], N[kMaxSeg], ko[kMaxSeg], n_pad[kMaxSeg];
+};
+__global__ void __launch_bounds__(256) pack_split3_kernel(Split3Segs q, int trans)
 {
+    const int s = blockIdx.y;
+    const float *W = q.W[s];
+    uint4 *out = q.out[s];
+    const int64_t ldw = q.ldw[s];
+    const int K = q.K[s], N = q.N[s], ko = q.ko[s], n_pad = q.n_pad[s];
     const int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     const int n = static_cast<int>(idx % n_pad), o = static_cast<int>(idx / n_pad);
     if (o >= ko) return;
@@ -924,19 +936,33 @@ bool gemm_direct_small(const GemmParams &p)
 
 static int64_t split3_octets(int64_t K) { return (K + 15) / 16 * 2; }
 static int64_t split3_columns(int64_t N) { return (N + 127) / 128 * 128; }
-size_t split3_weight_bytes(int64_t K, int64_t N) { return static_cast<size_t>(3 * split3_octets(K) * split3_columns(N) * 16); }
+size_t split3_weight_bytes(int64_t K, int64_t N) { return static_cast<size_t>(3 * split3_octets(K) * split3_columns(N) * 16); } // whole KBs
 
-heta_status pack_split3_weights(const float *W, int64_t ldw, int64_t K, int64_t N, int trans, void *out, GemmSeg *seg, hipStream_t st)
+heta_status pack_split3_weights(GemmParams &p, int trans, void *out, hipStream_t st)
 {
-    const int64_t ko = split3_octets(K), n_pad = split3_columns(N);
-    if (K >= (int64_t(1) << 30) || N >= (int64_t(1) << 30) || ko * n_pad >= (int64_t(1) << 31))
-        return fail(HETA_ERR_UNSUPPORTED, "projection: weight matrix too large to pack");
-    hipLaunchKernelGGL(pack_split3_kernel, dim3((unsigned)((ko * n_pad + 255) / 256)), dim3(256), 0, st, W, ldw, static_cast<int>(K),
-                       static_cast<int>(N), trans, static_cast<uint4 *>(out), static_cast<int>(ko), static_cast<int>(n_pad));
+    Split3Segs q{};
+    int64_t chunks = 0;
+    char *dst = static_cast<char *>(out);
+    for (int s = 0; s < p.n_seg; ++s) {
+        GemmSeg &g = p.seg[s];
+        const int64_t ko = split3_octets(g.K), n_pad = split3_columns(g.N);
+        if (g.K >= (int64_t(1) << 30) || g.N >= (int64_t(1) << 30) || ko * n_pad >= (int64_t(1) << 31))
+            return fail(HETA_ERR_UNSUPPORTED, "projection: weight matrix too large to pack");
+        q.W[s] = static_cast<const float *>(g.B);
+        q.out[s] = reinterpret_cast<uint4 *>(dst);
+        q.ldw[s] = g.ldb;
+        q.K[s] = static_cast<int>(g.K);
+        q.N[s] = static_cast<int>(g.N);
+        q.ko[s] = static_cast<int>(ko);
+        q.n_pad[s] = static_cast<int>(n_pad);
+        chunks = std::max(chunks, ko * n_pad);
+        g.B3 = dst;
+        g.ko = static_cast<int32_t>(ko);
+        g.n_pad = static_cast<int32_t>(n_pad);
+        dst += split3_weight_bytes(g.K, g.N);
+    }
+    hipLaunchKernelGGL(pack_split3_kernel, dim3((unsigned)((chunks + 255) / 256), p.n_seg), dim3(256), 0, st, q, trans);
     HETA_LAUNCH_CHECK("pack_split3_kernel");
-    seg->B3 = out;
-    seg->ko = static_cast<int32_t>(ko);
-    seg->n_pad = static_cast<int32_t>(n_pad);
     return HETA_OK;
 }
 

@@ -382,18 +382,11 @@ static heta_status pack_f32_weights(heta_graph *owner, GemmParams &p, int trans,
     for (int s = 0; s < p.n_seg; ++s) {
         const GemmSeg &g = p.seg[s];
         if (!aligned16(g.A) || (g.lda * 4) % 16 || !aligned16(g.B) || (g.ldb * 4) % 16) return HETA_OK;
-        bytes += (split3_weight_bytes(g.K, g.N) + 255) / 256 * 256;
+        bytes += split3_weight_bytes(g.K, g.N);
     }
     heta_status e = ensure_pack(owner, bytes);
     if (e != HETA_OK) return e;
-    char *dst = static_cast<char *>(owner->d_pack);
-    for (int s = 0; s < p.n_seg; ++s) {
-        GemmSeg &g = p.seg[s];
-        e = pack_split3_weights(static_cast<const float *>(g.B), g.ldb, g.K, g.N, trans, dst, &g, st);
-        if (e != HETA_OK) return e;
-        dst += (split3_weight_bytes(g.K, g.N) + 255) / 256 * 256;
-    }
-    return HETA_OK;
+    return pack_split3_weights(p, trans, owner->d_pack, st);
 }
 
 // out = beta*out + row_scale * sum_s in_s . (W_s or W_s^T)
