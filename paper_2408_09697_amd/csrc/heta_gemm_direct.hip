@@ -616,7 +616,7 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
     static_assert(ST >= 2 && (ST - 2) * LD_PER_TILE < 64, "vmcnt range");
     static_assert(!X3 || (A_DIRECT && B_DIRECT && sizeof(SA_T) == 4 && sizeof(SB_T) == 4 && sizeof(CT) == 2 && !B_SPLIT),
                   "three-term feeding: both operands direct fp32, bf16 MFMA");
-    static_assert(!W3 || (BK == 16 && MI == 2 && NJ == 2 && NW == 4 && !A_RC), "pre-split B: 128 x 128 tiles of 16 k-values");
+    static_assert(!W3 || (BK == 16 && MI == 2 && NJ == 2 && !A_RC), "pre-split B: 2 x 2 accumulators, 16 k-values per tile");
     static_assert(A_BYTES % 1024 == 0, "stage addresses stay 1 KB aligned");
     __shared__ __attribute__((aligned(1024))) char ring[A_BYTES + B_BYTES];
     char *const As = ring, *const Bs = ring + A_BYTES;
@@ -1055,6 +1055,9 @@ heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, 
         // half the splitting arithmetic leaves the k loop.  12 KB of B per stage: two workgroups per CU.
         bool packed = true;
         for (int s = 0; s < p.n_seg; ++s) packed = packed && p.seg[s].B3 != nullptr;
+        // up to 64 output columns: 256 x 64 tiles, or half of the matrix work would be done for padding (57 -> 45 us on
+        // 2 x (110 k x 128)(128 x 64))
+        if (packed && n_max <= 64) return launch_direct<bf16_t, float, false, true, float, false, true, 1, 16, 3, 2, false, 2, 2, 4, 2>(p, st, name, bytes, flops);
         if (packed) return launch_direct<bf16_t, float, false, true, float, false, true, 2, 16, 3, 2, false, 2, 2, 2, 2>(p, st, name, bytes, flops);
     }
     if (a_dt == HETA_F32 && b_dt == HETA_F32 && !g_f32_native) {
@@ -1062,6 +1065,10 @@ heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, 
         // 128 x 128 tiles (four wavefronts, three workgroups per CU) also where the output is wider: the
         // 128 x 256 tile's eight wavefronts need more than the 128 registers that two workgroups per CU allow,
         // and with one workgroup per CU nothing runs under its barriers (measured: 0.93 against 1.05 ms)
+        // (a weight gradient of at most 64 output columns: 128 x 64 tiles of two wavefronts, 48 -> 41 us
+        // on 2 x (110 k x 128)^T (110 k x 64))
+        if (p.partial && a_rc && b_rc && n_max <= 64)
+            return launch_direct<bf16_t, float, true, true, float, true, true, 1, 16, 3, 2, false, 2, 2, 2, 1>(p, st, name, bytes, flops);
 #define HETA_X32(ARC, BRC)                                                                                                        \
     return small ? launch_direct<bf16_t, float, ARC, true, float, BRC, true, 2, 16, 3, 4, false, 1, 1, 2, 1>(p, st, name, bytes, flops) \
                  : launch_direct<bf16_t, float, ARC, true, float, BRC, true, 2, 16, 3, 3, false, 2, 2, 2, 1>(p, st, name, bytes, flops)

@@ -1039,6 +1039,14 @@ def test_f32_products_as_six_bf16_terms_are_as_accurate_as_the_fp32_mfma(n, d_in
     assert errw[True] <= 1e-5 and errw[False] <= 2.0 * errw[True] + 1e-7, errw
 
 
+@pytest.mark.parametrize("n,d_in,d_out,trans", [(12545, 128, 64, False), (13001, 100, 63, True), (30000, 17, 33, False), (12800, 300, 65, False),
+                                                (16385, 64, 4, True)])
+def test_f32_products_of_narrow_outputs(n, d_in, d_out, trans):
+    """Up to 64 output columns take tiles of their own (256 x 64, weight gradients 128 x 64); 65 is the first width that
+    does not.  The row counts leave ragged tiles and more than, and fewer than, 128 splits of the contraction."""
+    test_f32_products_as_six_bf16_terms_are_as_accurate_as_the_fp32_mfma(n, d_in, d_out, trans)
+
+
 @pytest.mark.parametrize("on_device", [False, True])
 @pytest.mark.parametrize("mode", [0, 1, 3], ids=["by_size", "host_ingest", "block_ingest"])
 def test_graphs_created_in_one_batch_equal_graphs_created_one_by_one(mode, on_device):
