@@ -374,16 +374,22 @@ template <int BN, int NW> struct Split3Loader {
     }
 };
 
-// One whole k-step (16 k-values, none masked) of a wavefront's 2 x 2 accumulators with B already in three
+// One k-step (16 k-values, kv of them valid) of a wavefront's 2 x 2 accumulators with B already in three
 // terms: only A's two fragments are split (88 vector instructions), and the order is pinned with scheduling
 // barriers so that the splitting runs between the twelve MFMAs that need A's leading term alone; the twelve
 // that need its m and l terms follow.  Terms of one accumulator are added leading term first.
 template <bool A_RC, int BM, int BN, int BK>
-__device__ __forceinline__ void x3_step_2x2_presplit(const float *At, const char *Bt, int ra, int cb, int half, floatx16 (&acc)[2][2])
+__device__ __forceinline__ void x3_step_2x2_presplit(const float *At, const char *Bt, int ra, int cb, int half, int kv, floatx16 (&acc)[2][2])
 {
     X3Frag a[2];
     dfrag_load8<A_RC, BM, BK>(At, ra, 0, half, a[0].x);
     dfrag_load8<A_RC, BM, BK>(At, ra + 32, 0, half, a[1].x);
+    if (kv < BK) { // uniform: the ragged last tile of a segment; k-values from kv on count as zero
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) a[i].x[j] = 8 * half + j < kv ? a[i].x[j] : 0.f;
+    }
     union BF { uint4 u; bf16x8 v; } b[2][3];
 #pragma unroll
     for (int t = 0; t < 3; ++t)
@@ -776,30 +782,7 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
                 }
             } else if constexpr (W3) {
                 // fp32 A split as its fragments are read, B read as the three terms it was packed into
-                if (!ragged) {
-                    x3_step_2x2_presplit<A_RC, BM, BN, BK>(reinterpret_cast<const float *>(At), Bt, wm + l32, wn + l32, half, acc);
-                } else {
-                    union Frag { uint4 u; bf16x8 v; };
-                    uint4 a3[2][3];
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) {
-                        float x[8];
-                        dfrag_load8<A_RC, BM, BK>(reinterpret_cast<const float *>(At), wm + i * 32 + l32, 0, half, x);
-                        split3_frag<true>(x, 8 * half, kv, a3[i]);
-                    }
-                    constexpr int TA[6] = {0, 0, 0, 1, 1, 2}, TB[6] = {0, 1, 2, 0, 1, 0}; // the order of x3_step_2x2_presplit
-#pragma unroll
-                    for (int q = 0; q < 6; ++q)
-#pragma unroll
-                        for (int i = 0; i < 2; ++i)
-#pragma unroll
-                            for (int jj = 0; jj < 2; ++jj) {
-                                Frag fa, fb;
-                                fa.u = a3[i][TA[q]];
-                                fb.u = DB::frag(Bt, TB[q], half, wn + jj * 32 + l32);
-                                acc[i][jj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa.v, fb.v, acc[i][jj], 0, 0, 0);
-                            }
-                }
+                x3_step_2x2_presplit<A_RC, BM, BN, BK>(reinterpret_cast<const float *>(At), Bt, wm + l32, wn + l32, half, kv, acc);
             } else if constexpr (X3 != 0) {
                 // fp32 operands, every product as six bf16 terms (split3_pair)
 #pragma unroll
@@ -1052,13 +1035,17 @@ heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, 
     *handled = true;
     if (a_dt == HETA_F32 && b_dt == HETA_F32 && !g_f32_native && !a_rc && !small && !p.partial) {
         // B already packed as three bf16 terms by the caller (the weights of a forward or input-gradient product):
-        // half the splitting arithmetic leaves the k loop.  12 KB of B per stage: two workgroups per CU.
+        // half the splitting arithmetic leaves the k loop.
         bool packed = true;
         for (int s = 0; s < p.n_seg; ++s) packed = packed && p.seg[s].B3 != nullptr;
         // up to 64 output columns: 256 x 64 tiles, or half of the matrix work would be done for padding (57 -> 45 us on
         // 2 x (110 k x 128)(128 x 64))
-        if (packed && n_max <= 64) return launch_direct<bf16_t, float, false, true, float, false, true, 1, 16, 3, 2, false, 2, 2, 4, 2>(p, st, name, bytes, flops);
-        if (packed) return launch_direct<bf16_t, float, false, true, float, false, true, 2, 16, 3, 2, false, 2, 2, 2, 2>(p, st, name, bytes, flops);
+        if (packed && n_max <= 64) return launch_direct<bf16_t, float, false, true, float, false, true, 1, 16, 2, 3, false, 2, 2, 4, 2>(p, st, name, bytes, flops);
+        // Two stages of 20 KB and at most 168 registers: three workgroups per CU, whose barriers and epilogues overlap
+        // (with three stages, and the ragged tile in a code path of its own, 229 registers and two workgroups: all fp32
+        // projections of a layer over 21 M edges 2.36 -> 2.20 ms; 64 x 128 columns per wavefront, half the splitting per
+        // MFMA but two workgroups per CU: 2.25)
+        if (packed) return launch_direct<bf16_t, float, false, true, float, false, true, 2, 16, 2, 3, false, 2, 2, 2, 2>(p, st, name, bytes, flops);
     }
     if (a_dt == HETA_F32 && b_dt == HETA_F32 && !g_f32_native) {
         // fp32 operands, fp32-exact products as six bf16 MFMA terms each (see split3_pair), fp32 accumulation
