@@ -50,6 +50,30 @@ def test_sample_neighbors_bit_exact(kind, fanout):
     hg.destroy()
 
 
+@pytest.mark.parametrize("limits", [[1, 64, 65], [16383, 16384, 16385, 5], [3_000_000, 40], [67_000_000], [80_000_000, 100_000_000]],
+                         ids=["words", "tiles", "many_tiles", "largest_bitmap", "sorted"])
+@pytest.mark.parametrize("n", [1, 777, 70_000])
+def test_unique_relabel_over_id_ranges(limits, n):
+    """Ranges at the edges of a 64-bit word and of a tile of 16,384 ids, an empty set between two others, the largest
+    ranges that go by bitmap and the first that are sorted; skewed ids (one of them half of all) and both range ends."""
+    g = np.random.default_rng(n + len(limits))
+    groups = []
+    for lim in limits:
+        ids = g.integers(0, lim, n)
+        ids[g.random(n) < 0.5] = lim // 3
+        groups.append([np.concatenate([ids, [lim - 1, 0]]), g.integers(0, min(lim, 100), n // 2)])
+    groups.insert(1, [np.zeros(0, dtype=np.int64)])
+    bounds = [limits[0], 7] + limits[1:]
+    out = heta.heta_unique_relabel_batch([[torch.from_numpy(x.astype(np.int64)).cuda() for x in grp] for grp in groups], bounds)
+    for grp, (u, ls) in zip(groups, out):
+        ref_u, ref_l = osampler.unique_relabel(grp)
+        assert np.array_equal(u.cpu().numpy(), ref_u)
+        for a, b in zip(ls, ref_l):
+            assert np.array_equal(a.cpu().numpy(), b)
+    with pytest.raises(heta.HetaError, match="outside"):
+        heta.heta_unique_relabel_batch([[torch.tensor([0, limits[0]], device="cuda")]], [limits[0]])
+
+
 def test_unique_relabel_bit_exact():
     g = rng.stream("tests", "sampler/unique")
     lists = [g.integers(0, 50000, 30000), np.zeros(0, dtype=np.int64), g.integers(0, 50000, 7), g.integers(49990, 50000, 5000)]
