@@ -50,14 +50,31 @@ __device__ __forceinline__ bf16_t adam_to_bf16(float f)
     return static_cast<bf16_t>((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
 }
 
+// Several tables in one launch (the weight matrices of a model and its learnable tables after one backward pass), their
+// workgroups one after the other: with the table in blockIdx.y and the grid as long as the largest table needs, the
+// surplus workgroups of the others and a 64-bit division per thread were 5 % of an update (1.17 M rows of 128 in three
+// tables: fp32 830 -> 786 us = 5.3 TB/s, bf16 703 -> 663; two and four chunks per thread 788 and 780 / 676 and 678,
+// streaming stores 781 / 659 but nothing at a tenth of the rows).
+constexpr int kAdamMulti = 16;
+struct AdamMulti {
+    int n;
+    unsigned block0[kAdamMulti]; // first workgroup of each table
+    AdamParams p[kAdamMulti];
+};
+static_assert(sizeof(AdamMulti) <= 3584, "kernel arguments are limited to 4 KB");
+
 template <int V> // V = 4: 128-bit accesses on whole, aligned chunks; V = 1: element-wise
-__device__ __forceinline__ void sparse_adam_body(const AdamParams &p)
+__global__ void __launch_bounds__(256) sparse_adam_kernel(AdamMulti q)
 {
-    const int per_row = (p.d + V - 1) / V;
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    const int64_t i = t / per_row;
+    int k = 0;
+    while (k + 1 < q.n && blockIdx.x >= q.block0[k + 1]) ++k; // uniform
+    const AdamParams &p = q.p[k];
+    const uint32_t per_row = static_cast<uint32_t>(p.d / V);
+    const int64_t t = static_cast<int64_t>(blockIdx.x - q.block0[k]) * 256 + threadIdx.x;
+    // below 2^31 chunks (uniform; t is at most 255 past them) row and column come from a 32-bit division
+    const int64_t i = p.n * per_row <= 0x7fffffff ? static_cast<int64_t>(static_cast<uint32_t>(t) / per_row) : t / per_row;
     if (i >= p.n) return;
-    const int c = static_cast<int>(t % per_row) * V;
+    const int c = static_cast<int>(t - i * per_row) * V;
     const int64_t r = p.ids ? p.ids[i] : i;
     if (r < 0 || r >= p.n_table_rows) return; // a row id outside the table: nothing is read or written for it
     const float *gp = p.grad + i * p.ld_grad + c;
@@ -98,17 +115,6 @@ __device__ __forceinline__ void sparse_adam_body(const AdamParams &p)
         *vp = v;
     }
 }
-
-template <int V> __global__ void __launch_bounds__(256) sparse_adam_kernel(AdamParams p) { sparse_adam_body<V>(p); }
-
-// several tables in one launch (the weight matrices of a model and its learnable tables after one backward pass):
-// blockIdx.y picks the table
-constexpr int kAdamMulti = 16;
-struct AdamMulti {
-    AdamParams p[kAdamMulti];
-};
-static_assert(sizeof(AdamMulti) <= 3584, "kernel arguments are limited to 4 KB");
-template <int V> __global__ void __launch_bounds__(256) sparse_adam_multi_kernel(AdamMulti m) { sparse_adam_body<V>(m.p[blockIdx.y]); }
 
 // checks one update's arguments and fills its parameter block; *vec: 128-bit accesses are possible
 static heta_status adam_params(const char *who, void *table, heta_dtype dt, int64_t ld_table, int32_t d, int64_t n_table_rows, float *m,
@@ -154,6 +160,21 @@ static heta_status adam_params(const char *who, void *table, heta_dtype dt, int6
     return HETA_OK;
 }
 
+// One launch for up to kAdamMulti updates that all take 128-bit accesses (vec) or all do not; q.block0 is filled here.
+static heta_status launch_adam(const char *who, AdamMulti &q, bool vec, hipStream_t st)
+{
+    int64_t blocks = 0;
+    for (int k = 0; k < q.n; ++k) {
+        q.block0[k] = static_cast<unsigned>(blocks);
+        blocks += (q.p[k].n * (vec ? q.p[k].d / 4 : q.p[k].d) + 255) / 256;
+        if (blocks > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "%s: too many elements for one launch", who);
+    }
+    if (vec) hipLaunchKernelGGL(sparse_adam_kernel<4>, dim3((unsigned)blocks), dim3(256), 0, st, q);
+    else hipLaunchKernelGGL(sparse_adam_kernel<1>, dim3((unsigned)blocks), dim3(256), 0, st, q);
+    HETA_LAUNCH_CHECK("sparse_adam_kernel");
+    return HETA_OK;
+}
+
 } // namespace heta
 
 using namespace heta;
@@ -184,24 +205,16 @@ extern "C" heta_status heta_sparse_adam_multi(int32_t n_items, const heta_adam_i
             bytes += b;
         }
         if (n_live == 0) continue;
-        // one launch for the items that take 128-bit accesses, one for the rest (blockIdx.y = position in the launch)
+        // one launch for the items that take 128-bit accesses, one for the rest
         for (int pass = 0; pass < 2; ++pass) {
             AdamMulti q{};
-            int k = 0;
-            int64_t threads_max = 0;
             for (int i = 0; i < n_live; ++i)
-                if (vec[i] == (pass == 0)) {
-                    q.p[k++] = m.p[i];
-                    threads_max = std::max<int64_t>(threads_max, m.p[i].n * (pass == 0 ? m.p[i].d / 4 : m.p[i].d));
-                }
-            if (k == 0) continue;
-            if ((threads_max + 255) / 256 > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "%s: too many elements for one launch", who);
+                if (vec[i] == (pass == 0)) q.p[q.n++] = m.p[i];
+            if (q.n == 0) continue;
             ProfScope prof("sparse_adam_kernel", st, bytes, 0);
             bytes = 0; // counted once
-            const dim3 grid((unsigned)((threads_max + 255) / 256), (unsigned)k);
-            if (pass == 0) hipLaunchKernelGGL(sparse_adam_multi_kernel<4>, grid, dim3(256), 0, st, q);
-            else hipLaunchKernelGGL(sparse_adam_multi_kernel<1>, grid, dim3(256), 0, st, q);
-            HETA_LAUNCH_CHECK("sparse_adam_multi_kernel");
+            const heta_status e = launch_adam(who, q, pass == 0, st);
+            if (e != HETA_OK) return e;
         }
     }
     return HETA_OK;
@@ -213,24 +226,15 @@ extern "C" heta_status heta_sparse_adam(void *table, heta_dtype dt, int64_t ld_t
                                         int64_t step, void *hip_stream)
 {
     const char *who = "heta_sparse_adam";
-    AdamParams p{};
+    AdamMulti q{};
+    q.n = 1;
     bool vec = false;
     double bytes = 0;
     heta_status e = adam_params(who, table, dt, ld_table, d, n_table_rows, m, v, ld_state, ids, n, grad, ld_grad, lr, beta1, beta2, eps, step,
-                                &p, &vec, &bytes);
+                                &q.p[0], &vec, &bytes);
     if (e != HETA_OK) return e;
     if (n == 0) return HETA_OK;
     hipStream_t st = as_stream(hip_stream);
     ProfScope prof("sparse_adam_kernel", st, bytes, 0);
-    if (vec) {
-        const int64_t threads = n * (d / 4);
-        if ((threads + 255) / 256 > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "%s: too many elements for one launch", who);
-        hipLaunchKernelGGL(sparse_adam_kernel<4>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, p);
-    } else {
-        const int64_t threads = n * d;
-        if ((threads + 255) / 256 > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "%s: too many elements for one launch", who);
-        hipLaunchKernelGGL(sparse_adam_kernel<1>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, p);
-    }
-    HETA_LAUNCH_CHECK("sparse_adam_kernel");
-    return HETA_OK;
+    return launch_adam(who, q, vec, st);
 }
