@@ -91,6 +91,32 @@ def test_ingest_transpose_at_key_widths_that_take_nine_bit_passes(n_src, mode):
     hg.destroy()
 
 
+@pytest.mark.parametrize("mode", [2, 3], ids=["device_ingest", "block_ingest"])
+@pytest.mark.parametrize("n", [2046, 2047, 2048, 8191, 8192, 16383, 16384, 24577, 32767, 32768])
+def test_ingest_at_the_edges_of_the_one_workgroup_scan(n, mode):
+    """The scans over rows and digit counts run in one workgroup up to 32,768 elements, rounds of 8,192; a scan has one
+    element more than there are rows.  CSC and degrees bit for bit; the schedule through sums of whole numbers, exact."""
+    g = rng.stream("tests", f"ingest-scan/{n}")
+    dst, src = np.sort(g.integers(0, n, size=3 * n)).astype(np.int32), g.integers(0, n, size=3 * n).astype(np.int32)
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(dst, minlength=n))]).astype(np.int64)
+    heta.heta_ingest_force(mode)
+    try:
+        hg = heta.heta_graph_create([(n, 4, 0), (n, 4, 0)], [(0, 1, rowptr, src)])
+    finally:
+        heta.heta_ingest_force(0)
+    colptr, row = heta.heta_graph_get_csc(hg, 0)
+    ref_colptr, ref_row = oracle.csc(src, dst, n)
+    assert np.array_equal(colptr, ref_colptr) and np.array_equal(row, ref_row)
+    assert np.array_equal(heta.heta_graph_get_degrees(hg, 0), np.diff(rowptr))
+    x = g.integers(-50, 50, size=(n, 4)).astype(np.float32)
+    ref = np.zeros((n, 4), dtype=np.float32)
+    np.add.at(ref, dst, x[src])
+    out = torch.full((n, 4), 3.0, device="cuda")
+    heta.heta_rel_aggregate_fwd(hg, 0, heta.HETA_SUM, torch.from_numpy(x).cuda(), out)
+    assert np.array_equal(out.cpu().numpy(), ref)
+    hg.destroy()
+
+
 @pytest.mark.parametrize("mode", [1, 2, 3])
 def test_ingest_config1_and_device_pointers(mode):
     p = workloads.config1()
