@@ -404,7 +404,7 @@ heta_status heta_rel_attn_bwd(heta_graph *g, int32_t rel, const void *z, heta_dt
 
 /* The same training step in the form that visits no edge on the destination side:
  * heta_rel_attn_fwd_train is heta_rel_attn_fwd that also writes apos[v, k] = the sum of alpha_e[k] over the in-edges of
- *   v with a positive logit (device fp32 [n_dst, K]; NULL: heta_rel_attn_fwd).
+ *   v with a positive logit el + er, whatever the sign of slope (device fp32 [n_dst, K]; NULL: heta_rel_attn_fwd).
  * heta_attn_bwd_dst covers up to 8 relations into one node type in one pass over its rows: grad_in = act'(h) grad_out
  *   (device fp32; h and grad_in are used for HETA_ACT_RELU only, without an activation grad_out is the gradient itself)
  *   and per relation der (as heta_rel_attn_bwd) and pack[v][k][0..3] = er, smax, sinv, <grad, o> (16-byte

@@ -178,8 +178,10 @@ template <int W, int KT> __device__ __forceinline__ void group_max(float *v)
 }
 
 // Forward statistics of up to W NPL edges from slot e0, W lanes, NPL slots per lane: every id and score is loaded
-// once.  Left in x: exp(logit - m), negated where the logit is not positive; m: the largest logit (-inf without
-// edges), den and pos: the sums of all exps and of those of positive logits, in every lane of the group.
+// once.  Left in x: exp(LeakyReLU(logit) - m), its sign bit set where the logit itself is not positive (the activation
+// keeps the sign only for a positive slope; a bit, not a product with -1, so that a NaN keeps it as well); m: the largest
+// activated logit (-inf without edges), den and pos: the sums of all exps and of those of positive logits, in every
+// lane of the group.
 template <int W, int KT, int NPL>
 __device__ __forceinline__ void fwd_stats(const SweepParams &p, int64_t e0, int n, int lane, int k0, const float *ar, float (&x)[NPL][KT],
                                           float *m, float *den, float *pos)
@@ -202,19 +204,19 @@ __device__ __forceinline__ void fwd_stats(const SweepParams &p, int64_t e0, int 
     for (int j = 0; j < NPL; ++j)
 #pragma unroll
         for (int k = 0; k < KT; ++k) {
-            x[j][k] = lrelu(x[j][k] + ar[k], p.slope);
-            if (id[j] >= 0) m[k] = fmaxf(m[k], x[j][k]);
+            x[j][k] += ar[k];
+            if (id[j] >= 0) m[k] = fmaxf(m[k], lrelu(x[j][k], p.slope));
         }
     group_max<W, KT>(m);
 #pragma unroll
     for (int j = 0; j < NPL; ++j)
 #pragma unroll
         for (int k = 0; k < KT; ++k) {
-            const bool up = x[j][k] > 0.f; // LeakyReLU keeps the sign of the logit
-            const float e = id[j] >= 0 ? expf(x[j][k] - m[k]) : 0.f;
+            const bool up = x[j][k] > 0.f;
+            const float e = id[j] >= 0 ? expf(lrelu(x[j][k], p.slope) - m[k]) : 0.f;
             den[k] += e;
             pos[k] += up ? e : 0.f;
-            x[j][k] = up ? e : -e;
+            x[j][k] = __uint_as_float((__float_as_uint(e) & 0x7fffffffu) | (up ? 0u : 0x80000000u));
         }
     group_sum<W, KT>(den);
     group_sum<W, KT>(pos);
@@ -246,7 +248,7 @@ __device__ __forceinline__ void sweep_row(const SweepParams &p, int64_t q, bool 
 #pragma unroll
                 for (int k = 0; k < KT; ++k) {
                     a[k] = fabsf(x[j][k]) * inv[k];
-                    gt[k] = x[j][k] > 0.f ? a[k] : 0.f; // the weight restricted to edges with a positive logit
+                    gt[k] = __float_as_uint(x[j][k]) >> 31 ? 0.f : a[k]; // the weight restricted to edges with a positive logit
                 }
                 storek<KT>(p.alpha + (e0 + lane + j * W) * p.K + k0, a);
                 if (p.gate) storek<KT>(p.gate + (e0 + lane + j * W) * p.K + k0, gt);

@@ -238,6 +238,45 @@ def test_sweeps_at_the_edges_of_the_row_classes(heads, side):
         graph.destroy()
 
 
+@pytest.mark.parametrize("heads", [1, 2, 4, 8])
+@pytest.mark.parametrize("slope", [-0.5, 0.0, 1.0])
+def test_positive_logits_are_those_before_the_activation(heads, slope):
+    """With a slope that is not positive the activated logit does not carry the sign any more: out_pos, apos and der of
+    every row class, hub rows included, by the logit itself."""
+    deg = np.array(ROW_CLASS_DEGREES)
+    n_dst, n_src, d = deg.size, 300, 8 * heads
+    g = rng.stream("tests", f"logit_sign{heads}{slope}")
+    dst, src = np.repeat(np.arange(n_dst), deg), g.integers(0, n_src, deg.sum())
+    src[np.unique(dst, return_index=True)[1]] = 0  # every row with edges has one of source 0
+    z, go = g.standard_normal((n_src, d)).astype(np.float32), g.standard_normal((n_dst, d)).astype(np.float32)
+    el, er = (g.standard_normal((n, heads)).astype(np.float32) for n in (n_src, n_dst))
+    graph = heta.heta_graph_create([(n_src, 4, 0), (n_dst, 4, 0)], [(0, 1, np.concatenate([[0], np.cumsum(deg)]).astype(np.int64), src.astype(np.int32))])
+    try:
+        out, pos = (torch.full((n_dst, d), 3.0, device="cuda") for _ in range(2))
+        smax, sinv, apos, d_er = (torch.full((n_dst, heads), 5.0, device="cuda") for _ in range(4))
+        dz, d_el, pack = torch.empty((n_src, d), device="cuda"), torch.empty((n_src, heads), device="cuda"), torch.empty((n_dst, 4 * heads), device="cuda")
+        heta.heta_rel_attn_fwd_train(graph, 0, up(z), up(el), up(er), slope, out, smax=smax, sinv=sinv, out_pos=pos, apos=apos)
+        heta.heta_attn_bwd_dst(graph, 1, [0], slope, heta.HETA_ACT_NONE, None, up(go), None, [out], [pos], [up(er)], [smax], [sinv], [apos],
+                               [d_er], [pack])
+        heta.heta_rel_attn_bwd_src(graph, 0, up(z), up(el), slope, pack, up(go), dz, d_el)
+        ref_o, alpha = rgat.gat_aggregate_fwd(src, dst, n_dst, z, el, er, slope)
+        rdz, rdel, rder = rgat.gat_aggregate_bwd(src, dst, n_src, n_dst, z, el, er, alpha, go, slope)
+        gate = alpha * ((el[src] + er[dst]) > 0)
+        ref_apos, ref_pos = np.zeros((n_dst, heads)), np.zeros((n_dst, heads, d // heads))
+        np.add.at(ref_apos, dst, gate)
+        np.add.at(ref_pos, dst, gate[:, :, None] * z.astype(np.float64)[src].reshape(-1, heads, d // heads))
+        for got, ref, what in ((out, ref_o, "out"), (pos, ref_pos.reshape(n_dst, d), "out_pos"), (apos, ref_apos, "apos"), (dz, rdz, "dz"),
+                               (d_el, rdel, "del"), (d_er, rder, "der")):
+            assert_rows_close(host(got), ref, 1e-4, what)
+        # an infinite positive logit makes the row's weights NaN, those of its positive logits too
+        el[0] = np.inf
+        heta.heta_rel_attn_fwd_train(graph, 0, up(z), up(el), up(er), slope, out, smax=smax, sinv=sinv, out_pos=pos, apos=apos)
+        for t in (out, pos, apos):
+            assert np.isnan(host(t)[deg > 0]).all()
+    finally:
+        graph.destroy()
+
+
 @pytest.mark.parametrize("n,d,heads,n_rels,pad", [(1000, 256, 4, 3, 4), (257, 64, 8, 1, 4), (130, 60, 3, 2, 4), (67, 100, 5, 8, 4), (5, 4, 1, 2, 4),
                                                   # served row by row: heads of 6 columns, rows of more than 64 chunks, unaligned rows
                                                   (50, 18, 3, 2, 4), (33, 320, 4, 2, 4), (40, 30, 2, 1, 1)])
