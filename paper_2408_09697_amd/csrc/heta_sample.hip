@@ -324,6 +324,27 @@ __global__ void __launch_bounds__(256) bit_local_kernel(BitSets f, const unsigne
     f.local[l][i] = static_cast<int32_t>(word_rank[at] + __popcll(bits[at] & ((1ull << (v & 63)) - 1)));
 }
 
+// Whether no output (unique lists, local ids) shares memory with an input list.  The bitmap reads the lists once more after
+// the unique lists are written, and its threads write local ids beside lists that others still read; the sort copies the
+// ids out of the lists before it writes anything.
+static bool outputs_apart(int32_t n_groups, const int32_t *group_ptr, const int64_t *const *lists, const int64_t *lens,
+                          const std::vector<int64_t> &totals, int64_t *const *unique_ids, int32_t *const *local)
+{
+    const auto apart = [&](const void *out, int64_t bytes) {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(out);
+        for (int32_t l = 0; l < group_ptr[n_groups]; ++l) {
+            const uintptr_t b = reinterpret_cast<uintptr_t>(lists[l]);
+            if (bytes > 0 && lens[l] > 0 && a < b + static_cast<uintptr_t>(lens[l]) * 8 && b < a + static_cast<uintptr_t>(bytes)) return false;
+        }
+        return true;
+    };
+    for (int32_t g = 0; g < n_groups; ++g)
+        if (!apart(unique_ids[g], totals[g] * 8)) return false;
+    for (int32_t l = 0; l < group_ptr[n_groups]; ++l)
+        if (!apart(local[l], lens[l] * 4)) return false;
+    return true;
+}
+
 // scratch of one call, from the recycling pool (released idle: every entry point below synchronises its
 // stream before it returns, and the destructor waits for the device in case an error path did not)
 struct Scratch {
@@ -545,7 +566,7 @@ static heta_status heta_unique_relabel_batch_impl(int32_t n_groups, const int32_
     hipStream_t st = as_stream(hip_stream);
     Scratch scratch;
     heta_status e;
-    if (n_groups <= kFusedItems && group_ptr[n_groups] <= kFusedLists) {
+    if (n_groups <= kFusedItems && group_ptr[n_groups] <= kFusedLists && outputs_apart(n_groups, group_ptr, lists, lens, totals, unique_ids, local)) {
         // Id ranges of up to 67 M ids together: by bitmap, whatever the number of ids (its cost is three passes over at
         // most 8 MB; past that the sort, which does not grow with the range, is the faster one).
         BitSets f{};

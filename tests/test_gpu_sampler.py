@@ -2,6 +2,8 @@
 compared bit for bit (block row offsets, sampled global source ids in order, ascending unique source
 sets, local ids), and the blocks the sequencer builds are checked against the oracle's blocks and then
 run through a layer."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -72,6 +74,43 @@ def test_unique_relabel_over_id_ranges(limits, n):
             assert np.array_equal(a.cpu().numpy(), b)
     with pytest.raises(heta.HetaError, match="outside"):
         heta.heta_unique_relabel_batch([[torch.tensor([0, limits[0]], device="cuda")]], [limits[0]])
+
+
+@pytest.mark.parametrize("n", [5, 4000])
+@pytest.mark.parametrize("where", ["unique", "unique_of_another_set", "local"])
+def test_unique_relabel_into_the_memory_of_its_lists(where, n):
+    """The C call may write the unique ids, or the local ids, over the id lists that it was given."""
+    g = np.random.default_rng(n)
+    lists = [g.integers(0, 3000, n), g.integers(500, 3500, n)]
+    buf = torch.from_numpy(np.concatenate(lists).astype(np.int64)).cuda()   # set 0's list, then set 1's
+    src = [buf.data_ptr(), buf.data_ptr() + 8 * n]
+    spare = torch.empty(4 * n, dtype=torch.int64, device="cuda")
+    uniq = [spare.data_ptr(), spare.data_ptr() + 8 * n]
+    local = [spare.data_ptr() + 16 * n, spare.data_ptr() + 24 * n]
+    if where == "local":
+        local = src
+    else:
+        uniq = src if where == "unique" else src[::-1]
+    arr = lambda kind, x: (kind * len(x))(*x)  # noqa: E731
+    count = (ctypes.c_int64 * 2)()
+    lib = heta.binding.load_library()
+    lib.heta_unique_relabel_batch.argtypes = [ctypes.c_int32] + [ctypes.c_void_p] * 8
+    torch.cuda.synchronize()
+    status = lib.heta_unique_relabel_batch(2, arr(ctypes.c_int32, [0, 1, 2]), arr(ctypes.c_void_p, src), arr(ctypes.c_int64, [n, n]),
+                                           arr(ctypes.c_int64, [3500, 3500]), arr(ctypes.c_void_p, uniq), count, arr(ctypes.c_void_p, local), None)
+    assert status == 0
+    both = [buf.cpu().numpy(), spare.cpu().numpy()]
+
+    def at(ptr, dtype, k):
+        of = 0 if buf.data_ptr() <= ptr < buf.data_ptr() + 16 * n else 1
+        off = ptr - (buf, spare)[of].data_ptr()
+        return both[of].view(np.uint8)[off:off + k * np.dtype(dtype).itemsize].view(dtype)
+
+    for j in range(2):
+        ref_u, (ref_l,) = osampler.unique_relabel([lists[j]])
+        assert count[j] == ref_u.size
+        assert np.array_equal(at(uniq[j], np.int64, count[j]), ref_u)
+        assert np.array_equal(at(local[j], np.int32, n), ref_l)
 
 
 def test_unique_relabel_bit_exact():
