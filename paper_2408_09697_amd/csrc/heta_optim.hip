@@ -58,6 +58,7 @@ __device__ __forceinline__ bf16_t adam_to_bf16(float f)
 constexpr int kAdamMulti = 16;
 struct AdamMulti {
     int n;
+    unsigned first;              // first workgroup of this launch
     unsigned block0[kAdamMulti]; // first workgroup of each table
     AdamParams p[kAdamMulti];
 };
@@ -66,11 +67,12 @@ static_assert(sizeof(AdamMulti) <= 3584, "kernel arguments are limited to 4 KB")
 template <int V> // V = 4: 128-bit accesses on whole, aligned chunks; V = 1: element-wise
 __global__ void __launch_bounds__(256) sparse_adam_kernel(AdamMulti q)
 {
+    const unsigned block = q.first + blockIdx.x;
     int k = 0;
-    while (k + 1 < q.n && blockIdx.x >= q.block0[k + 1]) ++k; // uniform
+    while (k + 1 < q.n && block >= q.block0[k + 1]) ++k; // uniform
     const AdamParams &p = q.p[k];
     const uint32_t per_row = static_cast<uint32_t>(p.d / V);
-    const int64_t t = static_cast<int64_t>(blockIdx.x - q.block0[k]) * 256 + threadIdx.x;
+    const int64_t t = static_cast<int64_t>(block - q.block0[k]) * 256 + threadIdx.x;
     // below 2^31 chunks (uniform; t is at most 255 past them) row and column come from a 32-bit division
     const int64_t i = p.n * per_row <= 0x7fffffff ? static_cast<int64_t>(static_cast<uint32_t>(t) / per_row) : t / per_row;
     if (i >= p.n) return;
@@ -160,7 +162,8 @@ static heta_status adam_params(const char *who, void *table, heta_dtype dt, int6
     return HETA_OK;
 }
 
-// One launch for up to kAdamMulti updates that all take 128-bit accesses (vec) or all do not; q.block0 is filled here.
+// One launch for up to kAdamMulti updates that all take 128-bit accesses (vec) or all do not (several only where the tables
+// together have more threads than a grid takes); q.first and q.block0 are filled here.
 static heta_status launch_adam(const char *who, AdamMulti &q, bool vec, hipStream_t st)
 {
     int64_t blocks = 0;
@@ -169,8 +172,11 @@ static heta_status launch_adam(const char *who, AdamMulti &q, bool vec, hipStrea
         blocks += (q.p[k].n * (vec ? q.p[k].d / 4 : q.p[k].d) + 255) / 256;
         if (blocks > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "%s: too many elements for one launch", who);
     }
-    if (vec) hipLaunchKernelGGL(sparse_adam_kernel<4>, dim3((unsigned)blocks), dim3(256), 0, st, q);
-    else hipLaunchKernelGGL(sparse_adam_kernel<1>, dim3((unsigned)blocks), dim3(256), 0, st, q);
+    launch_pieces(blocks, 256, [&](unsigned first, unsigned count) {
+        q.first = first;
+        if (vec) hipLaunchKernelGGL(sparse_adam_kernel<4>, dim3(count), dim3(256), 0, st, q);
+        else hipLaunchKernelGGL(sparse_adam_kernel<1>, dim3(count), dim3(256), 0, st, q);
+    });
     HETA_LAUNCH_CHECK("sparse_adam_kernel");
     return HETA_OK;
 }

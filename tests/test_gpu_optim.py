@@ -139,3 +139,24 @@ def test_sparse_adam_multi_equals_the_single_calls_bit_for_bit():
         t, m, v, grad, ids = bad[3]
         bad[3] = (t, m[: t.shape[0] // 2], v, grad, ids)
         heta.heta_sparse_adam_multi(bad, lr=0.01, step=1)
+
+
+def test_sparse_adam_multi_of_more_elements_than_a_grid_has_threads():
+    """Three tables, each below 2^32 threads at one per element, together above: the update runs in more than one launch.
+    All ids but the first or the last row's lie outside their table, so that nothing else is read."""
+    n, d, rows = 1366, (1 << 20) + 1, 3
+    assert n * d < 1 << 32 < 3 * n * d
+    grad = torch.empty((n, d), device="cuda")
+    grad[[0, n - 1]] = torch.randn((2, d), device="cuda")
+    items = []
+    for k in range(3):
+        ids = torch.full((n,), -1, dtype=torch.int64, device="cuda")
+        ids[0 if k < 2 else n - 1] = k
+        items.append((torch.zeros((rows, d), device="cuda"), torch.zeros((rows, d), device="cuda"), torch.zeros((rows, d), device="cuda"), grad, ids))
+    heta.heta_sparse_adam_multi(items, lr=0.5, step=1)
+    for k, (table, m, v, _, _) in enumerate(items):
+        want = grad[0 if k < 2 else n - 1]
+        # the first step moves a value by lr g / (|g| + eps); some ten 32-bit roundings
+        assert torch.allclose(m[k], 0.1 * want, rtol=1e-5) and torch.allclose(table[k], -0.5 * want / (want.abs() + 1e-8), rtol=1e-5)
+        for x in (table, m, v):
+            assert int((x != 0).any(1).sum()) == 1
