@@ -204,6 +204,7 @@ struct SplitSegs { // passed by value
     const float *part[kMaxSeg];
     float *out[kMaxSeg];
     int64_t M[kMaxSeg], ldo[kMaxSeg];
+    unsigned first; // first workgroup of this launch
 };
 // One workgroup of NW wavefronts per 64 elements: wavefront w adds the splits w, w + NW, ... (eight loads in flight),
 // the NW sums are added in wavefront order through LDS.  16 wavefronts from 128 splits on, 4 below.  (With one thread
@@ -215,7 +216,7 @@ __global__ void __launch_bounds__(64 * NW) splitk_reduce_kernel(SplitSegs g, int
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int seg = blockIdx.y;
     const int64_t total = static_cast<int64_t>(g.M[seg]) * N;
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * 64 + lane;
+    const int64_t t = (static_cast<int64_t>(g.first) + blockIdx.x) * 64 + lane;
     const float *part = g.part[seg];
     float a = 0.f;
     if (t < total) {
@@ -609,11 +610,15 @@ static heta_status wgrad_impl(heta_graph *g, int64_t n_rows, int n_seg, const vo
             bytes += (n_split + 1.0) * total * 4.0;
         }
         ProfScope prof("splitk_reduce_kernel", st, bytes, 0);
-        const dim3 grid((unsigned)((total_max + 63) / 64), (unsigned)n_seg);
-        if (n_split >= 128)
-            hipLaunchKernelGGL(splitk_reduce_kernel<16>, grid, dim3(1024), 0, st, segs, static_cast<int>(n_split), (int64_t)d_out, beta);
-        else
-            hipLaunchKernelGGL(splitk_reduce_kernel<4>, grid, dim3(256), 0, st, segs, static_cast<int>(n_split), (int64_t)d_out, beta);
+        const int nw = n_split >= 128 ? 16 : 4;
+        launch_pieces((total_max + 63) / 64, 64 * nw, [&](unsigned first, unsigned count) {
+            segs.first = first;
+            const dim3 grid(count, (unsigned)n_seg);
+            if (nw == 16)
+                hipLaunchKernelGGL(splitk_reduce_kernel<16>, grid, dim3(1024), 0, st, segs, static_cast<int>(n_split), (int64_t)d_out, beta);
+            else
+                hipLaunchKernelGGL(splitk_reduce_kernel<4>, grid, dim3(256), 0, st, segs, static_cast<int>(n_split), (int64_t)d_out, beta);
+        });
         HETA_LAUNCH_CHECK("splitk_reduce_kernel");
     }
     return HETA_OK;

@@ -490,6 +490,23 @@ def test_project_wgrad(n, d_in, d_out, in_s, gemm_path):
     hg.destroy()
 
 
+def test_project_wgrad_of_more_elements_than_a_grid_has_threads():
+    """Four wavefronts add the splits of 64 elements: from 2^30 elements on, those are 2^32 threads and more."""
+    n, d_in, d_out = 20, 32800, 32768
+    assert d_in * d_out * 4 > 1 << 32
+    hg = heta.heta_graph_create([(n, 8, 0)], [])
+    x, g = torch.randn((n, d_in), device="cuda"), torch.randn((n, d_out), device="cuda")
+    dW = torch.full((d_in, d_out), float("nan"), device="cuda")
+    heta.heta_project_wgrad_batch(hg, [x], [g], [dW])
+    bound = 1e-5 * float(x.abs().sum(0).max() * g.abs().max())
+    for i in range(0, d_in, 1025):
+        ref = x[:, i:i + 1025].double().T @ g.double()
+        assert bool((dW[i:i + 1025] - ref).abs().max() <= bound), f"rows {i} ff."
+    hg.destroy()
+    del dW
+    torch.cuda.empty_cache()
+
+
 # ---- a5: cross-relation sum ---------------------------------------------------------------------------
 
 @pytest.mark.parametrize("d,k,relu", [(256, 3, False), (256, 1, True), (33, 5, True), (32, 16, False)])
