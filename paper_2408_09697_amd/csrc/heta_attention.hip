@@ -63,6 +63,7 @@ struct SweepParams {
     // q_short on one thread; first workgroup of each class in the shared launch (hub chunks first)
     int64_t q_wave, q_mid, q_short, n_rows;
     unsigned b_wave, b_mid, b_short;
+    unsigned b_first;     // first workgroup of this launch
     int K;
     float slope;
     const float *row_a;   // [rows][K]  score half of the row side (er for the CSR, el for the CSC)
@@ -339,7 +340,7 @@ __global__ void __launch_bounds__(256) attn_rows_kernel(SweepParams p)
 {
     const int lane = threadIdx.x & 63;
     const int k0 = blockIdx.y * KT;
-    const unsigned b = blockIdx.x;
+    const unsigned b = p.b_first + blockIdx.x;
     if (b < p.b_wave) {
         const int64_t w = static_cast<int64_t>(b) * 4 + (threadIdx.x >> 6);
         if (w < p.n_hub_chunks) sweep_hub_chunk<KT, OP>(p, w, lane, k0); // uniform per wavefront
@@ -444,7 +445,11 @@ heta_status launch_sweeps_kt(const Schedule &s, SweepParams p, hipStream_t st)
     p.b_wave = (unsigned)cb;
     p.b_mid = (unsigned)(cb + wb);
     p.b_short = (unsigned)(cb + wb + mb);
-    hipLaunchKernelGGL((attn_rows_kernel<KT, OP>), dim3((unsigned)(cb + wb + mb + sb), gy), dim3(256), 0, st, p);
+    // (eight lanes per row: 2^29 rows of 5 to 31 edges are more threads than a grid takes)
+    launch_pieces(cb + wb + mb + sb, 256, [&](unsigned first, unsigned count) {
+        p.b_first = first;
+        hipLaunchKernelGGL((attn_rows_kernel<KT, OP>), dim3(count, gy), dim3(256), 0, st, p);
+    });
     HETA_LAUNCH_CHECK("attn_rows_kernel");
     if (s.n_hub_rows > 0) {
         hipLaunchKernelGGL((attn_hub_combine_kernel<OP>), dim3((unsigned)((s.n_hub_rows + 3) / 4), p.K), dim3(256), 0, st, p);
