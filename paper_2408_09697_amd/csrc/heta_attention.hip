@@ -671,7 +671,11 @@ __global__ void __launch_bounds__(256) attn_sub_kernel(float *a, const float *b,
 // With sum_e alpha_e = 1 and gate_e = alpha_e (slope + (1 - slope) [logit_e > 0]) this der is
 // sum_e gate_e (<grad, z_e> - dot); no edge is visited.  Streaming, bound by its bytes: grad rows are read once for
 // all relations.  (As four launches per relation and one for the activation, with a sweep over the edges for the
-// sums of gates: 4.1 ms for 7 relations into 1.87 M rows of 256, now 2.9 ms = 5.1 TB/s.)
+// sums of gates: 4.1 ms for 7 relations into 1.87 M rows of 256, now 2.9 ms = 5.1 TB/s.)  Rows of up to 1,024 columns
+stay in registers for all relations (200,000 rows, 3 relations: 256 columns 363 us, 512 in 8 heads 748, 1,024 in 4
+heads 1,454 = 5.1 to 5.3 TB/s; served row by row with 4-byte loads, 512 columns took 1,597 us and 1,024 took 2,193).
+Past that, and where a long row's heads are no power of two of chunks, row by row and head by head: 600 columns in 6
+heads 1,375 us, with 4-byte loads 1,802.
 constexpr int kDstRels = 8;
 struct DstItem {
     const float *o, *opos, *er, *smax, *sinv, *apos;
@@ -694,87 +698,133 @@ __device__ __forceinline__ void dst_store(const DstParams &p, const DstItem &t, 
     reinterpret_cast<float4 *>(t.pack)[at] = make_float4(t.er[at], t.smax[at], t.sinv[at], dot);
 }
 
-// Rows of at most 64 16-byte chunks, one chunk per lane, L lanes per row (L a power of two), R rows per lane group;
-// heads of whole chunks.
-template <int R>
+// Rows of 16-byte chunks, T chunks per lane, L lanes per row (L a power of two; 64 if T > 1), R rows per lane group; heads
+// of whole chunks, for T > 1 a power of two of them.
+template <int R, int T>
 __global__ void __launch_bounds__(256) attn_dst_kernel(DstParams p, int L)
 {
     const int lane = threadIdx.x & 63;
     const int G = 64 / L, grp = lane / L, l = lane % L;
     const int64_t first = (static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6)) * R * G + grp;
-    const bool has = 4 * l < p.d;
-    const int cph = p.F / 4, in_head = l % cph;
+    const int n_chunks = p.d / 4, cph = p.F / 4;
     const bool pow2 = (cph & (cph - 1)) == 0;
-    float4 gv[R];
+    float4 gv[R][T];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int64_t i = first + static_cast<int64_t>(r) * G;
-        gv[r] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (i < p.n && has) {
-            gv[r] = *reinterpret_cast<const float4 *>(p.g + i * p.ld_g + 4 * l);
-            if (p.h) {
-                const float4 x = *reinterpret_cast<const float4 *>(p.h + i * p.ld_h + 4 * l);
-                gv[r].x = x.x > 0.f ? gv[r].x : 0.f; gv[r].y = x.y > 0.f ? gv[r].y : 0.f;
-                gv[r].z = x.z > 0.f ? gv[r].z : 0.f; gv[r].w = x.w > 0.f ? gv[r].w : 0.f;
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const int64_t i = first + static_cast<int64_t>(r) * G;
+            const int c = l + L * t;
+            float4 &v = gv[r][t];
+            v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (i < p.n && c < n_chunks) {
+                v = *reinterpret_cast<const float4 *>(p.g + i * p.ld_g + 4 * c);
+                if (p.h) {
+                    const float4 x = *reinterpret_cast<const float4 *>(p.h + i * p.ld_h + 4 * c);
+                    v.x = x.x > 0.f ? v.x : 0.f; v.y = x.y > 0.f ? v.y : 0.f;
+                    v.z = x.z > 0.f ? v.z : 0.f; v.w = x.w > 0.f ? v.w : 0.f;
+                }
             }
         }
-    }
     for (int q = 0; q < p.n_rels; ++q) {
         const DstItem &t = p.it[q];
-        float a[R], b[R];
+        float a[R][T], b[R][T];
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int s = 0; s < T; ++s) {
+                const int64_t i = first + static_cast<int64_t>(r) * G;
+                const int c = l + L * s;
+                const float4 v = gv[r][s];
+                a[r][s] = b[r][s] = 0.f;
+                if (i < p.n && c < n_chunks) {
+                    const float4 o = *reinterpret_cast<const float4 *>(t.o + i * t.ld_o + 4 * c);
+                    const float4 u = *reinterpret_cast<const float4 *>(t.opos + i * t.ld_o + 4 * c);
+                    a[r][s] = v.x * o.x + v.y * o.y + v.z * o.z + v.w * o.w;
+                    b[r][s] = v.x * u.x + v.y * u.y + v.z * u.z + v.w * u.w;
+                }
+            }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int64_t i = first + static_cast<int64_t>(r) * G;
-            a[r] = b[r] = 0.f;
-            if (i < p.n && has) {
-                const float4 o = *reinterpret_cast<const float4 *>(t.o + i * t.ld_o + 4 * l);
-                const float4 u = *reinterpret_cast<const float4 *>(t.opos + i * t.ld_o + 4 * l);
-                a[r] = gv[r].x * o.x + gv[r].y * o.y + gv[r].z * o.z + gv[r].w * o.w;
-                b[r] = gv[r].x * u.x + gv[r].y * u.y + gv[r].z * u.z + gv[r].w * u.w;
-            }
-        }
+            if (T > 1 && cph > 64) { // a head is whole steps of 64 chunks (uniform)
+                float sa = 0.f, sb = 0.f;
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int64_t i = first + static_cast<int64_t>(r) * G;
-            if (pow2) { // uniform
-                for (int off = cph >> 1; off > 0; off >>= 1) {
-                    a[r] += __shfl_xor(a[r], off, 64);
-                    b[r] += __shfl_xor(b[r], off, 64);
+                for (int s = 0; s < T; ++s) {
+                    sa += a[r][s];
+                    sb += b[r][s];
+                    if ((64 * (s + 1)) % cph == 0) {
+                        group_sum<64, 1>(&sa);
+                        group_sum<64, 1>(&sb);
+                        const int k = (64 * (s + 1)) / cph - 1;
+                        if (i < p.n && l == 0 && k < p.K) dst_store(p, t, i, k, sa, sb);
+                        sa = sb = 0.f;
+                    }
                 }
-            } else { // a head's chunks lie in consecutive lanes: its first lane adds the others' in order
-                const float a0 = a[r], b0 = b[r];
-                for (int j = 1; j < cph; ++j) {
-                    a[r] += __shfl(a0, (lane + j) & 63, 64);
-                    b[r] += __shfl(b0, (lane + j) & 63, 64);
-                }
+                continue;
             }
-            if (i < p.n && has && in_head == 0) dst_store(p, t, i, l / cph, a[r], b[r]);
+#pragma unroll
+            for (int s = 0; s < T; ++s) {
+                const int c = l + L * s;
+                if (T > 1 || pow2) { // uniform
+                    for (int off = cph >> 1; off > 0; off >>= 1) {
+                        a[r][s] += __shfl_xor(a[r][s], off, 64);
+                        b[r][s] += __shfl_xor(b[r][s], off, 64);
+                    }
+                } else { // a head's chunks lie in consecutive lanes: its first lane adds the others' in order
+                    const float a0 = a[r][s], b0 = b[r][s];
+                    for (int j = 1; j < cph; ++j) {
+                        a[r][s] += __shfl(a0, (lane + j) & 63, 64);
+                        b[r][s] += __shfl(b0, (lane + j) & 63, 64);
+                    }
+                }
+                if (i < p.n && c < n_chunks && c % cph == 0) dst_store(p, t, i, c / cph, a[r][s], b[r][s]);
+            }
         }
     }
     if (p.ga) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int64_t i = first + static_cast<int64_t>(r) * G;
-            if (i < p.n && has) *reinterpret_cast<float4 *>(p.ga + i * p.ld_ga + 4 * l) = gv[r];
-        }
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const int64_t i = first + static_cast<int64_t>(r) * G;
+                const int c = l + L * t;
+                if (i < p.n && c < n_chunks) *reinterpret_cast<float4 *>(p.ga + i * p.ld_ga + 4 * c) = gv[r][t];
+            }
     }
 }
 
-// any other shape: one wavefront per row, head by head
+// any other shape: one wavefront per row, head by head; EPC = 4: 16-byte loads, heads of whole chunks
+template <int EPC>
 __global__ void __launch_bounds__(256) attn_dst_any_kernel(DstParams p)
 {
     const int lane = threadIdx.x & 63;
     const int64_t i = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (i >= p.n) return; // uniform per wavefront
     const float *g = p.g + i * p.ld_g, *h = p.h ? p.h + i * p.ld_h : nullptr;
+    const auto grad = [&](int j, float (&v)[EPC]) { // the gradient behind the activation, columns j ..
+        ldv<float, EPC>(g + j, v);
+        if (h) {
+            float x[EPC];
+            ldv<float, EPC>(h + j, x);
+#pragma unroll
+            for (int e = 0; e < EPC; ++e) v[e] = x[e] > 0.f ? v[e] : 0.f;
+        }
+    };
     for (int q = 0; q < p.n_rels; ++q) {
         const DstItem &t = p.it[q];
         for (int k = 0; k < p.K; ++k) {
             float a = 0.f, b = 0.f;
-            for (int j = k * p.F + lane; j < (k + 1) * p.F; j += 64) {
-                const float v = h && !(h[j] > 0.f) ? 0.f : g[j];
-                a = fmaf(v, t.o[i * t.ld_o + j], a);
-                b = fmaf(v, t.opos[i * t.ld_o + j], b);
+            for (int j = k * p.F + lane * EPC; j < (k + 1) * p.F; j += 64 * EPC) {
+                float v[EPC], o[EPC], u[EPC];
+                grad(j, v);
+                ldv<float, EPC>(t.o + i * t.ld_o + j, o);
+                ldv<float, EPC>(t.opos + i * t.ld_o + j, u);
+#pragma unroll
+                for (int e = 0; e < EPC; ++e) {
+                    a = fmaf(v[e], o[e], a);
+                    b = fmaf(v[e], u[e], b);
+                }
             }
             group_sum<64, 1>(&a);
             group_sum<64, 1>(&b);
@@ -782,7 +832,12 @@ __global__ void __launch_bounds__(256) attn_dst_any_kernel(DstParams p)
         }
     }
     if (p.ga)
-        for (int j = lane; j < p.d; j += 64) p.ga[i * p.ld_ga + j] = h && !(h[j] > 0.f) ? 0.f : g[j];
+        for (int j = lane * EPC; j < p.d; j += 64 * EPC) {
+            float v[EPC];
+            grad(j, v);
+#pragma unroll
+            for (int e = 0; e < EPC; ++e) p.ga[i * p.ld_ga + j + e] = v[e];
+        }
 }
 
 template <typename TX, typename TY>
@@ -1931,21 +1986,29 @@ heta_status heta_attn_bwd_dst(heta_graph *g, int32_t dst_type, int32_t n_rels, c
     if (p.n == 0) return HETA_OK;
     hipStream_t st = as_stream(hip_stream);
     ProfScope prof("attn_dst_kernel", st, static_cast<double>(p.n) * (4.0 * d * (1 + (relu ? 2 : 0) + 2 * n_rels) + 36.0 * heads * n_rels), 0);
-    const int n_chunks = d / 4;
-    if (d % 4 == 0 && n_chunks <= 64 && p.F % 4 == 0 && all16 % 16 == 0 && lds % 4 == 0) {
-        int L = 1;
-        while (L < n_chunks) L <<= 1;
-        // two rows per lane group once that still leaves eight wavefronts per SIMD, else one
-        const int R = p.n * L >= int64_t(2) * 64 * 8192 ? 2 : 1;
+    const int n_chunks = d / 4, cph = p.F / 4;
+    const bool vec = d % 4 == 0 && p.F % 4 == 0 && all16 % 16 == 0 && lds % 4 == 0;
+    int L = 1, T = 1; // lanes per row, chunks per lane
+    while (L < n_chunks && L < 64) L <<= 1;
+    while (L * T < n_chunks) T <<= 1;
+    if (vec && (T == 1 || (T <= 4 && (cph & (cph - 1)) == 0))) {
+        // two rows per lane group once that still leaves eight wavefronts per SIMD, else one; one of four chunks per lane
+        const int R = T < 4 && p.n * L >= int64_t(2) * 64 * 8192 ? 2 : 1;
         const int64_t rows = static_cast<int64_t>(4) * R * (64 / L);
         const int64_t blocks = (p.n + rows - 1) / rows;
         if (blocks > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "%s: too many rows", who);
-        if (R == 2) hipLaunchKernelGGL(attn_dst_kernel<2>, dim3((unsigned)blocks), dim3(256), 0, st, p, L);
-        else hipLaunchKernelGGL(attn_dst_kernel<1>, dim3((unsigned)blocks), dim3(256), 0, st, p, L);
+#define HETA_DST(RR, TT) hipLaunchKernelGGL((attn_dst_kernel<RR, TT>), dim3((unsigned)blocks), dim3(256), 0, st, p, L)
+        if (T == 4) HETA_DST(1, 4);
+        else if (T == 2 && R == 2) HETA_DST(2, 2);
+        else if (T == 2) HETA_DST(1, 2);
+        else if (R == 2) HETA_DST(2, 1);
+        else HETA_DST(1, 1);
+#undef HETA_DST
     } else {
         const int64_t blocks = (p.n + 3) / 4;
         if (blocks > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "%s: too many rows", who);
-        hipLaunchKernelGGL(attn_dst_any_kernel, dim3((unsigned)blocks), dim3(256), 0, st, p);
+        if (vec) hipLaunchKernelGGL(attn_dst_any_kernel<4>, dim3((unsigned)blocks), dim3(256), 0, st, p);
+        else hipLaunchKernelGGL(attn_dst_any_kernel<1>, dim3((unsigned)blocks), dim3(256), 0, st, p);
     }
     HETA_LAUNCH_CHECK("attn_dst_kernel");
     return HETA_OK;

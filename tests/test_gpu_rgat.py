@@ -278,8 +278,15 @@ def test_positive_logits_are_those_before_the_activation(heads, slope):
 
 
 @pytest.mark.parametrize("n,d,heads,n_rels,pad", [(1000, 256, 4, 3, 4), (257, 64, 8, 1, 4), (130, 60, 3, 2, 4), (67, 100, 5, 8, 4), (5, 4, 1, 2, 4),
-                                                  # served row by row: heads of 6 columns, rows of more than 64 chunks, unaligned rows
-                                                  (50, 18, 3, 2, 4), (33, 320, 4, 2, 4), (40, 30, 2, 1, 1)])
+                                                  # two rows per lane group (from n x lanes = 2^20 on), the last workgroup not full
+                                                  (16389, 256, 4, 2, 4), (16389, 512, 8, 1, 4),
+                                                  # two and four chunks per lane: heads inside a step of 64 chunks, of one and of several steps
+                                                  (33, 320, 5, 1, 4), (50, 512, 8, 2, 4), (33, 512, 1, 2, 4), (21, 768, 12, 1, 4), (21, 1024, 4, 3, 4),
+                                                  (18, 1024, 2, 1, 4), (9, 1024, 1, 1, 4),
+                                                  # served row by row, 16 bytes a load: long rows with heads of 20, 25, 65 and 96 chunks, more than 256 chunks
+                                                  (33, 320, 4, 2, 4), (50, 600, 6, 2, 4), (19, 260, 1, 1, 4), (19, 768, 2, 1, 4), (7, 2048, 16, 1, 4),
+                                                  # row by row, element by element: heads of 6 and 15 columns, unaligned rows
+                                                  (50, 18, 3, 2, 4), (40, 30, 2, 1, 1), (40, 512, 4, 1, 1)])
 @pytest.mark.parametrize("relu", [True, False])
 def test_destination_side_of_the_backward(n, d, heads, n_rels, pad, relu):
     g = rng.stream("tests", f"dst_side{n}x{d}x{heads}x{n_rels}")
@@ -288,7 +295,7 @@ def test_destination_side_of_the_backward(n, d, heads, n_rels, pad, relu):
     er, smax, sinv, apos = ([g.standard_normal((n, heads)).astype(np.float32) for _ in range(n_rels)] for _ in range(4))
     graph = heta.heta_graph_create([(3, 4, 0), (n, 4, 0)], [(0, 1, np.zeros(n + 1, dtype=np.int64), np.zeros(0, dtype=np.int32))] * n_rels)
     try:
-        tab = lambda x: dev_table(x, "f32", pad)  # noqa: E731
+        tab = lambda x: dev_table(x, "f32", pad) if pad > 1 else dev_table(np.pad(x, ((0, 0), (0, 1))), "f32", 1)[:, :d]  # noqa: E731
         god, gi = tab(go), tab(np.full((n, d), 7.0, dtype=np.float32))
         der, pack = [torch.full((n, heads), 5.0, device="cuda") for _ in o], [torch.full((n, 4 * heads), 5.0, device="cuda") for _ in o]
         got = heta.heta_attn_bwd_dst(graph, 1, list(range(n_rels)), 0.2, heta.HETA_ACT_RELU if relu else heta.HETA_ACT_NONE, tab(h) if relu else None,
