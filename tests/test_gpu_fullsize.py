@@ -201,7 +201,8 @@ def test_full_size_rgat_sampled_rows_and_invariants(full_graph):
     oracle computes sampled ones from the row's own in-edges; what needs the whole graph is checked by
     properties that hold at any size: attention weights of a row sum to one (a table of ones aggregates to
     ones), the aggregation is self-adjoint for fixed weights (<dO, O(z)> = <dz(dO), z>), and both score
-    gradients add up the same per-edge terms (sum_v der = sum_u del per head)."""
+    gradients add up the same per-edge terms (sum_v der = sum_u del per head).  The backward both ways: with a sweep
+    over the destinations' edges (heta_rel_attn_bwd) and as RgatLayer runs it, without one."""
     from oracle import rgat
     p, hg = full_graph
     K, d, slope = 4, 256, 0.2
@@ -223,6 +224,13 @@ def test_full_size_rgat_sampled_rows_and_invariants(full_graph):
         d_el = torch.empty((n_s, K), dtype=torch.float32, device="cuda")
         d_er = torch.empty((n_t, K), dtype=torch.float32, device="cuda")
         heta.heta_rel_attn_bwd(hg, i, zd, eld, erd, slope, smax, sinv, out, god, dz, d_el, d_er, o_pos=out_pos)
+        apos = torch.full((n_t, K), float("nan"), dtype=torch.float32, device="cuda")
+        pack = torch.full((n_t, 4 * K), float("nan"), dtype=torch.float32, device="cuda")
+        dz2, d_el2, d_er2 = (torch.full_like(x, float("nan")) for x in (dz, d_el, d_er))
+        heta.heta_rel_attn_fwd_train(hg, i, zd, eld, erd, slope, out, smax=smax, sinv=sinv, out_pos=out_pos, apos=apos)
+        heta.heta_attn_bwd_dst(hg, r.dst_type, [i], slope, heta.HETA_ACT_NONE, None, god, None, [out], [out_pos], [erd], [smax], [sinv], [apos],
+                               [d_er2], [pack])
+        heta.heta_rel_attn_bwd_src(hg, i, zd, eld, slope, pack, god, dz2, d_el2)
         ones = torch.ones((n_s, d), dtype=torch.float32, device="cuda")
         norm = torch.empty((n_t, d), dtype=torch.float32, device="cuda")
         heta.heta_rel_attn_fwd(hg, i, ones, eld, erd, slope, norm)
@@ -232,15 +240,16 @@ def test_full_size_rgat_sampled_rows_and_invariants(full_graph):
         nh = norm.cpu().numpy()
         assert np.abs(nh[deg > 0] - 1.0).max() <= 1e-5 and not nh[deg == 0].any(), r.name
         lhs = float((god.double() * out.double()).sum())
-        rhs = float((dz.double() * zd.double()).sum())
         scale = float((god.double().abs() * out.double().abs()).sum())
-        assert abs(lhs - rhs) <= 1e-6 * scale, (r.name, lhs, rhs)
-        s_er, s_el = d_er.double().sum(0).cpu().numpy(), d_el.double().sum(0).cpu().numpy()
-        mag = d_er.double().abs().sum(0).cpu().numpy()
-        assert np.all(np.abs(s_er - s_el) <= 1e-5 * np.maximum(mag, 1.0)), (r.name, s_er, s_el)
+        for dz_, d_el_, d_er_ in ((dz, d_el, d_er), (dz2, d_el2, d_er2)):
+            rhs = float((dz_.double() * zd.double()).sum())
+            assert abs(lhs - rhs) <= 1e-6 * scale, (r.name, lhs, rhs)
+            s_er, s_el = d_er_.double().sum(0).cpu().numpy(), d_el_.double().sum(0).cpu().numpy()
+            mag = d_er_.double().abs().sum(0).cpu().numpy()
+            assert np.all(np.abs(s_er - s_el) <= 1e-5 * np.maximum(mag, 1.0)), (r.name, s_er, s_el)
         # sampled destination rows against the oracle, from the row's own in-edges
         rows = sample_rows(deg, 12, f"rgat/{r.name}")
-        oh, dh = out.cpu().numpy(), d_er.cpu().numpy()
+        oh, dh, dh2, ah = out.cpu().numpy(), d_er.cpu().numpy(), d_er2.cpu().numpy(), apos.cpu().numpy()
         for v in rows.tolist():
             nb = r.col[r.rowptr[v]:r.rowptr[v + 1]].astype(np.int64)
             src_l = np.arange(nb.size)
@@ -249,7 +258,9 @@ def test_full_size_rgat_sampled_rows_and_invariants(full_graph):
             _, _, rder = rgat.gat_aggregate_bwd(src_l, np.zeros(nb.size, dtype=np.int64), max(nb.size, 1), 1, z[nb], el[nb],
                                                 er[v:v + 1], alpha, go[v:v + 1], slope)
             assert_rows_close(dh[v:v + 1], rder, 1e-4, f"{r.name} der[{v}]")
-        del zd, god, out, out_pos, dz, ones, norm
+            assert_rows_close(dh2[v:v + 1], rder, 1e-4, f"{r.name} der[{v}] without the sweep")
+            assert_rows_close(ah[v:v + 1], (alpha * (el[nb] + er[v] > 0)).sum(0, keepdims=True), 1e-4, f"{r.name} apos[{v}]")
+        del zd, god, out, out_pos, dz, dz2, ones, norm
     torch.cuda.empty_cache()
 
 

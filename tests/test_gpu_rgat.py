@@ -73,8 +73,9 @@ def test_attn_score_and_its_backward(n, d, heads, pad, per_head, storage):
 
 @pytest.mark.parametrize("n,d,heads,n_sets,pad", [(3000, 128, 4, 6, 4), (1001, 128, 4, 8, 4), (700, 64, 1, 3, 4), (513, 100, 3, 5, 4),
                                                   (40, 128, 16, 2, 4), (1, 8, 2, 1, 4),
+                                                  (150, 128, 8, 6, 4),
                                                   # shapes served set by set: wide table, unaligned rows, too many vectors
-                                                  (300, 256, 4, 3, 4), (200, 30, 3, 2, 1), (150, 128, 8, 6, 4)])
+                                                  (300, 256, 4, 3, 4), (200, 30, 3, 2, 1), (150, 128, 16, 8, 4)])
 @pytest.mark.parametrize("storage", ["f32", "bf16"])
 def test_scores_of_several_vector_sets_in_one_pass(n, d, heads, n_sets, pad, storage):
     g = rng.stream("tests", f"multi_score{n}x{d}x{heads}x{n_sets}")
@@ -113,10 +114,13 @@ def test_scores_of_several_vector_sets_in_one_pass(n, d, heads, n_sets, pad, sto
 
 
 @pytest.mark.parametrize("n,d,heads,n_sets", [(33, 128, 8, 7), (129, 96, 5, 7), (4097, 128, 15, 8), (66000, 32, 2, 5), (127, 4, 1, 8),
-                                              (65, 128, 16, 8)])  # 128 vectors: set by set
+                                              (65, 128, 16, 8),  # 128 vectors: set by set
+                                              (131_143, 128, 4, 6), (131_143, 128, 8, 6)])
 @pytest.mark.parametrize("storage", ["f32", "bf16"])
 def test_scores_of_vector_sets_at_tile_edges(n, d, heads, n_sets, storage):
-    """Row tiles of 32, vector tiles of 32, slabs of 128 rows and more: remainders of each."""
+    """Row tiles of 16 and 32, vector tiles of 32 and slabs of 128 rows: remainders of each.  131,143 rows are the launches
+    of large tables: slabs of 192 rows, a ragged last one, and more rows than one pass of the capped grids of the scores
+    (32,768 rows with more than 16 vectors) and of the input gradient (98,304) takes."""
     test_scores_of_several_vector_sets_in_one_pass(n, d, heads, n_sets, 4, storage)
 
 
@@ -374,6 +378,18 @@ def test_rgat_layer_tiny(storage, tol, heads):
     assert max(worst.values()) <= (1.2e-2 if storage == "bf16" else 1e-5)
 
 
+def test_rgat_layer_with_more_relations_into_a_type_than_one_destination_pass_takes():
+    """Ten relations into one type: the destination side runs in two passes, the activation's backward in the first."""
+    nts = [NodeType("A", 700, 24, False), NodeType("B", 300, 16, False)]
+    G = HetGraph(nts)
+    for i in range(10):
+        G.relations.append(uniform_relation(f"r{i}", i % 2, 0, nts[i % 2].num_nodes, 700, 2000 + 100 * i, f"tests/rgat/many/{i}"))
+    tabs = [rng.normal_table(t.num_nodes, t.feat_dim, "tests/rgat/many", t.name) for t in nts]
+    W = [workloads.glorot(nts[r.src_type].feat_dim, 32, "tests/rgat/many", f"W/{r.name}") for r in G.relations]
+    p = workloads.LayerProblem("rgat-many", G, "sum", "f32", tabs, W, 32, {0: rng.normal_table(700, 32, "tests/rgat/many", "G")}, relu=True)
+    assert max(_run_layer(p, workloads.attention_params(p, 4, gain=1.5), 1e-4).values()) <= 1e-5
+
+
 @pytest.mark.parametrize("storage,tol", [("f32", 1e-4), ("bf16", 2e-2)])
 def test_rgat_layer_config3_scaled(storage, tol):
     p = workloads.config3(storage, scale=0.02)
@@ -447,7 +463,14 @@ def test_attention_is_bitwise_reproducible_run_to_run():
         heta.heta_rel_attn_fwd(graph, 0, z, el, er, 0.2, out, smax=smax, sinv=sinv, out_pos=pos)
         heta.heta_rel_attn_bwd(graph, 0, z, el, er, 0.2, smax, sinv, out, go, dz, d_el, d_er, o_pos=pos)
         torch.cuda.synchronize()
-        runs.append((out, pos, smax, sinv, dz, d_el, d_er))
+        # the form that RgatLayer runs
+        apos, pack = torch.empty((3000, heads), device="cuda"), torch.empty((3000, 4 * heads), device="cuda")
+        dz2, d_el2, d_er2 = torch.empty_like(dz), torch.empty_like(d_el), torch.empty_like(d_er)
+        heta.heta_rel_attn_fwd_train(graph, 0, z, el, er, 0.2, out, smax=smax, sinv=sinv, out_pos=pos, apos=apos)
+        heta.heta_attn_bwd_dst(graph, 1, [0], 0.2, heta.HETA_ACT_NONE, None, go, None, [out], [pos], [er], [smax], [sinv], [apos], [d_er2], [pack])
+        heta.heta_rel_attn_bwd_src(graph, 0, z, el, 0.2, pack, go, dz2, d_el2)
+        torch.cuda.synchronize()
+        runs.append((out, pos, smax, sinv, dz, d_el, d_er, apos, pack, dz2, d_el2, d_er2))
     for a, b in zip(*runs):
         assert torch.equal(a, b)
     graph.destroy()
