@@ -672,10 +672,10 @@ __global__ void __launch_bounds__(256) attn_sub_kernel(float *a, const float *b,
 // sum_e gate_e (<grad, z_e> - dot); no edge is visited.  Streaming, bound by its bytes: grad rows are read once for
 // all relations.  (As four launches per relation and one for the activation, with a sweep over the edges for the
 // sums of gates: 4.1 ms for 7 relations into 1.87 M rows of 256, now 2.9 ms = 5.1 TB/s.)  Rows of up to 1,024 columns
-stay in registers for all relations (200,000 rows, 3 relations: 256 columns 363 us, 512 in 8 heads 748, 1,024 in 4
-heads 1,454 = 5.1 to 5.3 TB/s; served row by row with 4-byte loads, 512 columns took 1,597 us and 1,024 took 2,193).
-Past that, and where a long row's heads are no power of two of chunks, row by row and head by head: 600 columns in 6
-heads 1,375 us, with 4-byte loads 1,802.
+// stay in registers for all relations (200,000 rows, 3 relations: 256 columns 363 us, 512 in 8 heads 748, 1,024 in 4
+// heads 1,454 = 5.1 to 5.3 TB/s; served row by row with 4-byte loads, 512 columns took 1,597 us and 1,024 took 2,193).
+// Past that, and where a long row's heads are no power of two of chunks, row by row and head by head: 600 columns in 6
+// heads 1,375 us, with 4-byte loads 1,802.
 constexpr int kDstRels = 8;
 struct DstItem {
     const float *o, *opos, *er, *smax, *sinv, *apos;
