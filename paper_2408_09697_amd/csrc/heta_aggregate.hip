@@ -687,7 +687,8 @@ static heta_status launch_pair(const AggParams *ps, int n, int n_super, hipStrea
         wave_blocks = std::max<int64_t>(wave_blocks, split ? ps[i].n_wave_items : (ps[i].n_wave_items + 3) / 4);
         batch_blocks = std::max<int64_t>(batch_blocks, (ps[i].batch0[kShortDeg] + 3) / 4);
     }
-    if (wave_blocks > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "aggregate: too many long rows");
+    if (wave_blocks > max_blocks(256) - kPairWaveBlocks) return fail(HETA_ERR_UNSUPPORTED, "aggregate: too many long rows");
+    if (batch_blocks > max_blocks(256) - kPairWaveBlocks) return fail(HETA_ERR_UNSUPPORTED, "aggregate: too many short rows");
     AggMulti m{};
     if (n > 1)
         for (int i = 0; i < n; ++i) m.p[i] = ps[i];

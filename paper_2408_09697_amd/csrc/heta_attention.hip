@@ -497,6 +497,7 @@ heta_status launch_sweeps(const Schedule &s, SweepParams p, float *hub_scratch, 
 //                 row shared by every i (ld_y = 0: the attention vector a, laid out [K][F] = [d]).
 //   per_head = 0: j runs over all d columns and y_k = y + k*d (a [K][d] matrix shared by every row).
 struct DotParams {
+    unsigned first; // first workgroup of this launch
     const void *x;
     int64_t ld_x;
     const void *y;
@@ -535,7 +536,7 @@ template <typename TX, typename TY, int EPC>
 __global__ void __launch_bounds__(256) attn_rowdot_kernel(DotParams p)
 {
     const int lane = threadIdx.x & 63;
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+    const int64_t i = (static_cast<int64_t>(p.first) + blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (i >= p.n) return; // uniform per wavefront
     const TX *x = static_cast<const TX *>(p.x) + i * p.ld_x;
     const TY *y = static_cast<const TY *>(p.y) + i * p.ld_y;
@@ -567,7 +568,7 @@ __global__ void __launch_bounds__(256) attn_rowdot_fast_kernel(DotParams p, int 
 {
     const int lane = threadIdx.x & 63;
     const int G = 64 / L, g = lane / L, l = lane % L;
-    const int64_t first = (static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6)) * R * G + g; // rows first, first + G, ...
+    const int64_t first = ((static_cast<int64_t>(p.first) + blockIdx.x) * 4 + (threadIdx.x >> 6)) * R * G + g; // rows first, first + G, ...
     const int n_chunks = p.d / 4;
     float xv[R][T][4];
     bool live[R];
@@ -687,6 +688,7 @@ struct DstParams {
     float *ga;
     int64_t ld_g, ld_h, ld_ga, n;
     int d, K, F, n_rels;
+    unsigned first; // first workgroup of this launch
     float slope;
     DstItem it[kDstRels];
 };
@@ -705,7 +707,7 @@ __global__ void __launch_bounds__(256) attn_dst_kernel(DstParams p, int L)
 {
     const int lane = threadIdx.x & 63;
     const int G = 64 / L, grp = lane / L, l = lane % L;
-    const int64_t first = (static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6)) * R * G + grp;
+    const int64_t first = ((static_cast<int64_t>(p.first) + blockIdx.x) * 4 + (threadIdx.x >> 6)) * R * G + grp;
     const int n_chunks = p.d / 4, cph = p.F / 4;
     const bool pow2 = (cph & (cph - 1)) == 0;
     float4 gv[R][T];
@@ -799,7 +801,7 @@ template <int EPC>
 __global__ void __launch_bounds__(256) attn_dst_any_kernel(DstParams p)
 {
     const int lane = threadIdx.x & 63;
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+    const int64_t i = (static_cast<int64_t>(p.first) + blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (i >= p.n) return; // uniform per wavefront
     const float *g = p.g + i * p.ld_g, *h = p.h ? p.h + i * p.ld_h : nullptr;
     const auto grad = [&](int j, float (&v)[EPC]) { // the gradient behind the activation, columns j ..
@@ -869,33 +871,25 @@ heta_status launch_rowdot_t(const DotParams &p, hipStream_t st)
     const bool vec = (reinterpret_cast<uintptr_t>(p.x) % (4 * sx) == 0) && (p.ld_x % 4 == 0) &&
                      (reinterpret_cast<uintptr_t>(p.y) % (4 * sy) == 0) && (p.ld_y % 4 == 0) && (p.d % 4 == 0) &&
                      (p.F % 4 == 0);
-    const int64_t blocks = (p.n + 3) / 4;
-    if (blocks > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "attention: too many rows");
     const double bytes = static_cast<double>(p.n) * (p.d * (sx + (p.ld_y ? sy : 0) + (p.y2 ? sy : 0)) + 4.0 * p.K * ((p.corr ? 2 : 1) + (p.y2 ? 1 : 0)));
     ProfScope prof("attn_rowdot_kernel", st, bytes, 0);
-    if (vec) {
-        const int n_chunks = p.d / 4;
-        int L = 1;
-        while (L < n_chunks && L < 64) L <<= 1;
-        const int T = (n_chunks + L - 1) / L;
-        const int cph = p.F / 4;
-        const bool pow2 = (cph & (cph - 1)) == 0;
-        if (T <= 4 && (!p.per_head || (pow2 && (cph <= L || T % (cph / L) == 0)))) {
-            const int R = T == 1 ? 4 : (T == 2 ? 2 : 1); // row groups per wavefront, all loads in flight together
-            const int64_t rows_per_block = static_cast<int64_t>(4) * R * (64 / L);
-            const dim3 grid((unsigned)((p.n + rows_per_block - 1) / rows_per_block));
-            switch (T) {
-            case 1: hipLaunchKernelGGL((attn_rowdot_fast_kernel<TX, TY, 1, 4>), grid, dim3(256), 0, st, p, L, cph); break;
-            case 2: hipLaunchKernelGGL((attn_rowdot_fast_kernel<TX, TY, 2, 2>), grid, dim3(256), 0, st, p, L, cph); break;
-            case 3: hipLaunchKernelGGL((attn_rowdot_fast_kernel<TX, TY, 3, 1>), grid, dim3(256), 0, st, p, L, cph); break;
-            default: hipLaunchKernelGGL((attn_rowdot_fast_kernel<TX, TY, 4, 1>), grid, dim3(256), 0, st, p, L, cph); break;
-            }
-        } else {
-            hipLaunchKernelGGL((attn_rowdot_kernel<TX, TY, 4>), dim3((unsigned)blocks), dim3(256), 0, st, p);
-        }
-    } else {
-        hipLaunchKernelGGL((attn_rowdot_kernel<TX, TY, 1>), dim3((unsigned)blocks), dim3(256), 0, st, p);
-    }
+    const int n_chunks = p.d / 4, cph = p.F / 4;
+    int L = 1;
+    while (L < n_chunks && L < 64) L <<= 1;
+    const int T = (n_chunks + L - 1) / L;
+    const bool fast = vec && T <= 4 && (!p.per_head || ((cph & (cph - 1)) == 0 && (cph <= L || T % (cph / L) == 0)));
+    const int R = !fast || T > 2 ? 1 : (T == 1 ? 4 : 2); // row groups per wavefront, all loads in flight together
+    const int64_t rows_per_block = fast ? static_cast<int64_t>(4) * R * (64 / L) : 4;
+    launch_pieces((p.n + rows_per_block - 1) / rows_per_block, 256, [&](unsigned first, unsigned count) {
+        DotParams q = p;
+        q.first = first;
+        if (!vec) hipLaunchKernelGGL((attn_rowdot_kernel<TX, TY, 1>), dim3(count), dim3(256), 0, st, q);
+        else if (!fast) hipLaunchKernelGGL((attn_rowdot_kernel<TX, TY, 4>), dim3(count), dim3(256), 0, st, q);
+        else if (T == 1) hipLaunchKernelGGL((attn_rowdot_fast_kernel<TX, TY, 1, 4>), dim3(count), dim3(256), 0, st, q, L, cph);
+        else if (T == 2) hipLaunchKernelGGL((attn_rowdot_fast_kernel<TX, TY, 2, 2>), dim3(count), dim3(256), 0, st, q, L, cph);
+        else if (T == 3) hipLaunchKernelGGL((attn_rowdot_fast_kernel<TX, TY, 3, 1>), dim3(count), dim3(256), 0, st, q, L, cph);
+        else hipLaunchKernelGGL((attn_rowdot_fast_kernel<TX, TY, 4, 1>), dim3(count), dim3(256), 0, st, q, L, cph);
+    });
     HETA_LAUNCH_CHECK("attn_rowdot_kernel");
     return HETA_OK;
 }
@@ -1523,13 +1517,12 @@ heta_status heta_attn_score_bwd(heta_graph *g, const void *x, heta_dtype dt, int
     hipStream_t st = as_stream(hip_stream);
     const int F = per_head ? d / heads : d;
     if (dx && n > 0) {
-        const int64_t threads = n * d;
-        const int64_t blocks = (threads + 255) / 256;
-        if (blocks > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "heta_attn_score_bwd: too many elements");
         ProfScope prof("attn_score_bwd_input_kernel", st, static_cast<double>(n) * (d * (beta != 0.f ? 8.0 : 4.0) + 4.0 * heads), 0);
         const bool vec4 = d % 4 == 0 && F % 4 == 0 && ld_dx % 4 == 0 && aligned16(dx) && aligned16(vec);
+        const int64_t blocks = (n * (vec4 ? d / 4 : d) + 255) / 256;
+        if (blocks > max_blocks(256)) return fail(HETA_ERR_UNSUPPORTED, "heta_attn_score_bwd: too many elements");
         if (vec4)
-            hipLaunchKernelGGL(attn_score_bwd_input_vec_kernel, dim3((unsigned)((threads / 4 + 255) / 256)), dim3(256), 0, st,
+            hipLaunchKernelGGL(attn_score_bwd_input_vec_kernel, dim3((unsigned)blocks), dim3(256), 0, st,
                                dscore, vec, n, (int)d, (int)heads, F, per_head ? 1 : 0, dx, ld_dx, beta);
         else
             hipLaunchKernelGGL(attn_score_bwd_input_kernel, dim3((unsigned)blocks), dim3(256), 0, st, dscore, vec, n, (int)d,
@@ -1991,25 +1984,20 @@ heta_status heta_attn_bwd_dst(heta_graph *g, int32_t dst_type, int32_t n_rels, c
     int L = 1, T = 1; // lanes per row, chunks per lane
     while (L < n_chunks && L < 64) L <<= 1;
     while (L * T < n_chunks) T <<= 1;
-    if (vec && (T == 1 || (T <= 4 && (cph & (cph - 1)) == 0))) {
-        // two rows per lane group once that still leaves eight wavefronts per SIMD, else one; one of four chunks per lane
-        const int R = T < 4 && p.n * L >= int64_t(2) * 64 * 8192 ? 2 : 1;
-        const int64_t rows = static_cast<int64_t>(4) * R * (64 / L);
-        const int64_t blocks = (p.n + rows - 1) / rows;
-        if (blocks > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "%s: too many rows", who);
-#define HETA_DST(RR, TT) hipLaunchKernelGGL((attn_dst_kernel<RR, TT>), dim3((unsigned)blocks), dim3(256), 0, st, p, L)
-        if (T == 4) HETA_DST(1, 4);
-        else if (T == 2 && R == 2) HETA_DST(2, 2);
-        else if (T == 2) HETA_DST(1, 2);
-        else if (R == 2) HETA_DST(2, 1);
-        else HETA_DST(1, 1);
-#undef HETA_DST
-    } else {
-        const int64_t blocks = (p.n + 3) / 4;
-        if (blocks > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "%s: too many rows", who);
-        if (vec) hipLaunchKernelGGL(attn_dst_any_kernel<4>, dim3((unsigned)blocks), dim3(256), 0, st, p);
-        else hipLaunchKernelGGL(attn_dst_any_kernel<1>, dim3((unsigned)blocks), dim3(256), 0, st, p);
-    }
+    const bool one_pass = vec && (T == 1 || (T <= 4 && (cph & (cph - 1)) == 0));
+    // two rows per lane group once that still leaves eight wavefronts per SIMD, else one; one of four chunks per lane
+    const int R = one_pass && T < 4 && p.n * L >= int64_t(2) * 64 * 8192 ? 2 : 1;
+    const int64_t rows = one_pass ? static_cast<int64_t>(4) * R * (64 / L) : 4;
+    launch_pieces((p.n + rows - 1) / rows, 256, [&](unsigned first, unsigned count) {
+        p.first = first;
+        if (!vec) hipLaunchKernelGGL(attn_dst_any_kernel<1>, dim3(count), dim3(256), 0, st, p);
+        else if (!one_pass) hipLaunchKernelGGL(attn_dst_any_kernel<4>, dim3(count), dim3(256), 0, st, p);
+        else if (T == 4) hipLaunchKernelGGL((attn_dst_kernel<1, 4>), dim3(count), dim3(256), 0, st, p, L);
+        else if (T == 2 && R == 2) hipLaunchKernelGGL((attn_dst_kernel<2, 2>), dim3(count), dim3(256), 0, st, p, L);
+        else if (T == 2) hipLaunchKernelGGL((attn_dst_kernel<1, 2>), dim3(count), dim3(256), 0, st, p, L);
+        else if (R == 2) hipLaunchKernelGGL((attn_dst_kernel<2, 1>), dim3(count), dim3(256), 0, st, p, L);
+        else hipLaunchKernelGGL((attn_dst_kernel<1, 1>), dim3(count), dim3(256), 0, st, p, L);
+    });
     HETA_LAUNCH_CHECK("attn_dst_kernel");
     return HETA_OK;
 }

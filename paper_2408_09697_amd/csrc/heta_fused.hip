@@ -469,7 +469,7 @@ heta_status heta_cross_rel_aggregate_project(heta_graph *g, int32_t dst_type, in
         }
     }
     const int64_t blocks = (n_rows + kFusedRows - 1) / kFusedRows;
-    if (blocks > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "heta_cross_rel_aggregate_project: too many rows");
+    if (blocks > max_blocks(256)) return fail(HETA_ERR_UNSUPPORTED, "heta_cross_rel_aggregate_project: too many rows");
     double bytes = static_cast<double>(n_rows) * d_out * 4.0, flops = 0;
     for (int s = 0; s < n; ++s) {
         const Relation &r = g->rels[rels[s]];

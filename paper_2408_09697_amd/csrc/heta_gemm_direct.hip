@@ -895,7 +895,7 @@ static heta_status launch_direct(GemmParams &p, hipStream_t st, const char *name
     const int64_t outer = p.partial ? std::max(1, p.n_split) : mt;
     const int64_t blocks = (outer + 7) / 8 * 8 * inner;
     if (blocks <= 0) return HETA_OK;
-    if (blocks > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "projection: matrix too large for one launch");
+    if (blocks > max_blocks(64 * WMW * WN)) return fail(HETA_ERR_UNSUPPORTED, "projection: matrix too large for one launch");
     ProfScope prof(name, st, bytes, flops);
     hipLaunchKernelGGL((gemm_direct_kernel<CT, SA_T, A_RC, A_DIRECT, SB_T, B_RC, B_DIRECT, WN, BK, ST, OCC, B_SPLIT, MI, NJ, WMW, X3>),
                        dim3((unsigned)blocks), dim3(64 * WMW * WN), 0, st, p);

@@ -457,7 +457,7 @@ static heta_status differs_from_device(const T *caller, bool on_device, const T 
     }
     if (e != hipSuccess) return done(fail(e == hipErrorOutOfMemory ? HETA_ERR_OOM : HETA_ERR_DEVICE, "heta_graph_create: %s", hipGetErrorString(e)));
     const int64_t blocks = (n + 255) / 256;
-    if (blocks > 0x7fffffff) return done(fail(HETA_ERR_UNSUPPORTED, "heta_graph_create: index array too long to compare"));
+    if (blocks > max_blocks(256)) return done(fail(HETA_ERR_UNSUPPORTED, "heta_graph_create: index array too long to compare"));
     hipLaunchKernelGGL(arrays_differ_kernel<T>, dim3((unsigned)blocks), dim3(256), 0, nullptr, a, dev, n, flag);
     int h = 0;
     e = hipGetLastError();

@@ -33,11 +33,13 @@ heta_status fail(heta_status st, const char *fmt, ...) __attribute__((format(pri
             return ::heta::fail(HETA_ERR_DEVICE, "launch of %s failed: %s", name, hipGetErrorString(e_)); \
     } while (0)
 
-// A grid dimension holds at most 2^32 - 1 threads.  Calls launch(first workgroup, number of workgroups) for the pieces that
-// `blocks` workgroups of `threads` threads are launched in: one, but for grids past that bound.
+// A grid dimension holds at most 2^32 - 1 threads; a longer grid is cut off without an error.
+constexpr int64_t max_blocks(int threads) { return ((int64_t(1) << 32) - 1) / threads; }
+// Calls launch(first workgroup, number of workgroups) for the pieces that `blocks` workgroups of `threads` threads are
+// launched in: one, but for grids past that bound.
 template <typename F> void launch_pieces(int64_t blocks, int threads, F launch)
 {
-    const int64_t most = ((int64_t(1) << 32) - 1) / threads;
+    const int64_t most = max_blocks(threads);
     for (int64_t first = 0; first < blocks; first += most)
         launch(static_cast<unsigned>(first), static_cast<unsigned>(blocks - first < most ? blocks - first : most));
 }

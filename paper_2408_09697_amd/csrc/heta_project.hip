@@ -289,7 +289,7 @@ static heta_status launch_gemm(GemmParams &p, hipStream_t st, int bk)
     const int64_t n_outer = p.partial ? std::max(1, p.n_split) : mt;
     const int64_t blocks = (n_outer + 7) / 8 * 8 * inner;
     if (blocks <= 0) return HETA_OK;
-    if (blocks > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "projection: matrix too large for one launch");
+    if (blocks > max_blocks(128 * WN)) return fail(HETA_ERR_UNSUPPORTED, "projection: matrix too large for one launch");
     ProfScope prof(sizeof(CT) == 4 ? (p.partial ? "gemm_wgrad_f32" : "gemm_f32") : (p.partial ? "gemm_wgrad_bf16" : "gemm_bf16"),
                    st, bytes, flops);
     if constexpr (sizeof(CT) == 2 && A_RC && B_RC && sizeof(SB_T) == 4) {

@@ -11,6 +11,7 @@ constexpr int kMaxPartials = 16;
 struct ReduceParams {
     const float *part[kMaxPartials];
     int n_partials;
+    unsigned first; // first workgroup of this launch
     int64_t ld, ld_out;
     int64_t n_rows;
     int d;
@@ -22,7 +23,7 @@ template <int V> // V floats per thread (4: vector path, 1: scalar path)
 __global__ void __launch_bounds__(256) cross_rel_reduce_kernel(ReduceParams p)
 {
     const int per_row = (p.d + V - 1) / V;
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    const int64_t t = (static_cast<int64_t>(p.first) + blockIdx.x) * 256 + threadIdx.x;
     const int64_t i = t / per_row;
     const int c = static_cast<int>(t % per_row) * V;
     if (i >= p.n_rows) return;
@@ -43,11 +44,11 @@ __global__ void __launch_bounds__(256) cross_rel_reduce_kernel(ReduceParams p)
 }
 
 template <int V>
-__global__ void __launch_bounds__(256) act_bwd_kernel(int64_t n_rows, int d, int relu, const float *h, int64_t ld_h,
+__global__ void __launch_bounds__(256) act_bwd_kernel(unsigned first, int64_t n_rows, int d, int relu, const float *h, int64_t ld_h,
                                                       const float *go, int64_t ld_go, float *gi, int64_t ld_gi)
 {
     const int per_row = (d + V - 1) / V;
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    const int64_t t = (static_cast<int64_t>(first) + blockIdx.x) * 256 + threadIdx.x;
     const int64_t i = t / per_row;
     const int c = static_cast<int>(t % per_row) * V;
     if (i >= n_rows) return;
@@ -160,10 +161,11 @@ heta_status heta_cross_rel_reduce(const heta_graph *g, int32_t dst_type, const f
     if (blocks > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "heta_cross_rel_reduce: too large");
     ProfScope prof("cross_rel_reduce_kernel", as_stream(hip_stream),
                    (n_partials + 1.0) * static_cast<double>(p.n_rows) * d_out * 4.0, 0);
-    if (vec)
-        hipLaunchKernelGGL(cross_rel_reduce_kernel<4>, dim3((unsigned)blocks), dim3(256), 0, as_stream(hip_stream), p);
-    else
-        hipLaunchKernelGGL(cross_rel_reduce_kernel<1>, dim3((unsigned)blocks), dim3(256), 0, as_stream(hip_stream), p);
+    launch_pieces(blocks, 256, [&](unsigned first, unsigned count) {
+        p.first = first;
+        if (vec) hipLaunchKernelGGL(cross_rel_reduce_kernel<4>, dim3(count), dim3(256), 0, as_stream(hip_stream), p);
+        else hipLaunchKernelGGL(cross_rel_reduce_kernel<1>, dim3(count), dim3(256), 0, as_stream(hip_stream), p);
+    });
     HETA_LAUNCH_CHECK("cross_rel_reduce_kernel");
     return HETA_OK;
 }
@@ -187,12 +189,14 @@ heta_status heta_act_bwd(int64_t n_rows, int32_t d, heta_act act, const float *h
     const int64_t blocks = (threads + 255) / 256;
     if (blocks > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "heta_act_bwd: too large");
     ProfScope prof("act_bwd_kernel", as_stream(hip_stream), (relu ? 3.0 : 2.0) * static_cast<double>(n_rows) * d * 4.0, 0);
-    if (vec)
-        hipLaunchKernelGGL(act_bwd_kernel<4>, dim3((unsigned)blocks), dim3(256), 0, as_stream(hip_stream), n_rows, (int)d,
-                           relu, h, ld_h, grad_out, ld_go, grad_in, ld_gi);
-    else
-        hipLaunchKernelGGL(act_bwd_kernel<1>, dim3((unsigned)blocks), dim3(256), 0, as_stream(hip_stream), n_rows, (int)d,
-                           relu, h, ld_h, grad_out, ld_go, grad_in, ld_gi);
+    launch_pieces(blocks, 256, [&](unsigned first, unsigned count) {
+        if (vec)
+            hipLaunchKernelGGL(act_bwd_kernel<4>, dim3(count), dim3(256), 0, as_stream(hip_stream), first, n_rows, (int)d, relu, h, ld_h,
+                               grad_out, ld_go, grad_in, ld_gi);
+        else
+            hipLaunchKernelGGL(act_bwd_kernel<1>, dim3(count), dim3(256), 0, as_stream(hip_stream), first, n_rows, (int)d, relu, h, ld_h,
+                               grad_out, ld_go, grad_in, ld_gi);
+    });
     HETA_LAUNCH_CHECK("act_bwd_kernel");
     return HETA_OK;
 }
@@ -204,7 +208,7 @@ heta_status heta_calibration_copy(void *dst, const void *src, int64_t n_bytes, v
     if (n_bytes == 0) return HETA_OK;
     const int64_t n = n_bytes / 16;
     const int64_t blocks = (n + 255) / 256;
-    if (blocks > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "heta_calibration_copy: too large");
+    if (blocks > max_blocks(256)) return fail(HETA_ERR_UNSUPPORTED, "heta_calibration_copy: too large");
     ProfScope prof("calibration_copy_kernel", as_stream(hip_stream), 2.0 * static_cast<double>(n_bytes), 0);
     hipLaunchKernelGGL(calibration_copy_kernel, dim3((unsigned)blocks), dim3(256), 0, as_stream(hip_stream),
                        static_cast<const uint4 *>(src), static_cast<uint4 *>(dst), n);

@@ -187,3 +187,11 @@ def test_csc_and_reverse_arguments_are_checked_on_the_host():
     # node types that are not swapped
     st, msg, h = create([base, hb._Relation(0, 1, 2, rp.ctypes.data, col.ctypes.data, None, None, 0)])
     assert st == hb.HETA_ERR_BAD_CSR and "node types or edge counts" in msg and h is None
+
+
+def test_a_copy_longer_than_a_grid_is_refused():
+    """16 bytes per thread: 2^36 bytes are 2^32 threads, one more than a grid dimension takes.  Nothing is read."""
+    import ctypes
+    lib = hb.load_library()
+    lib.heta_calibration_copy.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p]
+    assert lib.heta_calibration_copy(1 << 20, 1 << 20, 1 << 36, None) == hb.HETA_ERR_UNSUPPORTED

@@ -509,6 +509,26 @@ def test_project_wgrad_of_more_elements_than_a_grid_has_threads():
 
 # ---- a5: cross-relation sum ---------------------------------------------------------------------------
 
+def test_elementwise_calls_of_more_elements_than_a_grid_has_threads():
+    """One element per thread (odd width), 2^32 elements and some: the rows past the bound are computed like the others."""
+    n, d = 1_048_000, 4099
+    assert n * d > 1 << 32
+    hg = heta.heta_graph_create([(n, 8, 0)], [])
+    x = torch.empty((n, d), device="cuda")
+    for i in range(0, n, 65_500):
+        x[i:i + 65_500] = torch.randn((min(65_500, n - i), d), device="cuda")
+    out = torch.full((n, d), float("nan"), device="cuda")
+    for call in (lambda: heta.heta_act_bwd(heta.HETA_ACT_RELU, x, x, out),
+                 lambda: heta.heta_cross_rel_reduce(hg, 0, [x], out, act=heta.HETA_ACT_RELU)):
+        out.fill_(float("nan"))
+        call()
+        for i in range(0, n, 65_500):
+            assert torch.equal(out[i:i + 65_500], x[i:i + 65_500].clamp(min=0.0)), f"rows {i} ff."
+    hg.destroy()
+    del x, out
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("d,k,relu", [(256, 3, False), (256, 1, True), (33, 5, True), (32, 16, False)])
 def test_cross_rel_reduce_and_act_bwd(d, k, relu):
     n = 1237

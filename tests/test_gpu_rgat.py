@@ -71,6 +71,16 @@ def test_attn_score_and_its_backward(n, d, heads, pad, per_head, storage):
     graph.destroy()
 
 
+def test_attn_score_of_more_rows_than_a_grid_has_wavefronts():
+    """Six columns go row by row, a wavefront each: 2^26 rows and some are more than 2^32 threads."""
+    n = 67_200_000
+    x, vec = torch.randn((n, 6), device="cuda"), torch.randn((1, 6), device="cuda")
+    score = torch.full((n, 1), float("nan"), device="cuda")
+    heta.heta_attn_score(x, vec, False, score)
+    ref = (x * vec).sum(1, keepdim=True)
+    assert bool(((score - ref).abs() <= 1e-5 * (x * vec).abs().sum(1, keepdim=True)).all())
+
+
 @pytest.mark.parametrize("n,d,heads,n_sets,pad", [(3000, 128, 4, 6, 4), (1001, 128, 4, 8, 4), (700, 64, 1, 3, 4), (513, 100, 3, 5, 4),
                                                   (40, 128, 16, 2, 4), (1, 8, 2, 1, 4),
                                                   (150, 128, 8, 6, 4),
