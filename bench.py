@@ -9,7 +9,8 @@ input-gradient projections and the CSC backward aggregation into every source ty
 Inputs are resident in HBM before the timed region; the graph handle (CSC, degree schedules:
 built by device kernels) is created once before it and its build time is reported separately.  The headline run uses fp32
 tables; the same layer with bf16 tables (fp32 accumulation) is measured afterwards and reported
-under "bf16_storage".  Prints ONE JSON line.
+under "bf16_storage", and so are the other workloads.  Prints ONE JSON line: the headline, and value and
+time of every other leg; with --full-record everything that was measured.
 """
 from __future__ import annotations
 
@@ -762,6 +763,23 @@ def measure_sustained_mfma():
     return out
 
 
+def short_line(out):
+    """The record as it is printed: the headline whole, of every other leg its value and time.  It stays below 2,000
+    characters, so that whoever keeps only the end of the output still has all of it."""
+    pick = lambda rec, keys: {k: rec[k] for k in keys if k in rec}  # noqa: E731
+    line = pick(out, ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline",
+                      "dtype", "data"))
+    line["config"] = pick(out["config"], ("workload", "edges", "edge_features_per_pass"))
+    if out.get("roofline"):
+        line["roofline"] = pick(out["roofline"], ("kernel", "bound", "achieved", "peak", "unit", "frac", "traffic", "traffic_source"))
+    if out.get("cpu_baseline"):
+        line["cpu_baseline"] = pick(out["cpu_baseline"], ("value", "unit", "cores", "kind"))
+    legs = {k: out[k] for k in ("bf16_storage", "f32_storage", "minibatch_config2", "config4", "config5") if k in out}
+    legs.update({f"rgat_{k}": rec for k, rec in out.get("rgat", {}).items()})
+    line["legs"] = {k: pick(rec, ("value", "ms_per_step")) for k, rec in legs.items()}
+    return line
+
+
 def main() -> int:
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -786,6 +804,9 @@ def main() -> int:
                     help="also time the fused inference forward (heta_cross_rel_aggregate_project); slower than the unfused "
                          "forward on this hardware, so no default path uses it and the default line leaves it out")
     ap.add_argument("--no-large-block", action="store_true", help="config5: skip the sweep over larger sampled blocks")
+    ap.add_argument("--full-record", action="store_true",
+                    help="print everything that was measured (kernel tables, counters, per-relation rates; some 30 KB) instead of "
+                         "the short line")
     args = ap.parse_args()
     if args.gpus != 1:
         print("bench.py: this build runs on one GPU only (one GPU's share of the layer); "
@@ -870,7 +891,7 @@ def main() -> int:
         out, _, problem = full_graph_record("config4", "bf16")
         if want_cpu:
             out["cpu_baseline"] = oracle_leg(problem, "config4")
-        print(json.dumps(out))
+        print(json.dumps(out if args.full_record else short_line(out)))
         return 0
 
     out, _, problem = full_graph_record("config3", args.dtype)
@@ -915,7 +936,7 @@ def main() -> int:
         "average_speedup_per_model": {"R-GCN": 2.8, "R-GAT": 2.6, "HGT": 2.4},
         "learnable_feature_update_share_of_a_DGL_epoch": "24%-35%",
         "note": "end-to-end distributed training on other hardware: context, not a target for this one-GPU kernel metric"}
-    print(json.dumps(out))
+    print(json.dumps(out if args.full_record else short_line(out)))
     return 0
 
 
