@@ -764,7 +764,7 @@ def heta_attn_score_bwd(g: Graph, x: torch.Tensor, vec: torch.Tensor, per_head: 
 
 def heta_attn_score_multi(x: torch.Tensor, vecs: Sequence[torch.Tensor], scores: Sequence[torch.Tensor],
                           d: Optional[int] = None, stream=None) -> None:
-    """scores[s] = x @ vecs[s]^T for every set s in one pass over x (vecs[s]: [heads, d] fp32)."""
+    """scores[s] = x @ vecs[s]^T for every set s in one launch (vecs[s]: [heads, d] fp32)."""
     if not vecs:
         return
     d = x.shape[1] if d is None else d
@@ -784,7 +784,7 @@ def heta_attn_score_bwd_multi(g: Graph, x: torch.Tensor, vecs: Sequence[torch.Te
                               dx: Optional[torch.Tensor] = None, beta: float = 0.0,
                               dvecs: Optional[Sequence[Optional[torch.Tensor]]] = None, d: Optional[int] = None,
                               stream=None) -> None:
-    """dx = beta dx + sum_s dscores[s] @ vecs[s];  dvecs[s] = dscores[s]^T @ x, all in one pass over x."""
+    """dx = beta dx + sum_s dscores[s] @ vecs[s];  dvecs[s] = dscores[s]^T @ x, all sets together."""
     if not vecs:
         return
     d = x.shape[1] if d is None else d
