@@ -243,21 +243,103 @@ __global__ void __launch_bounds__(256) bit_zero_kernel(uint4 *bits, int64_t n, i
     if (i < n_sets) bad[i] = 0;
 }
 
+// Sets the bits `m` of a word unless all of them are set already.
+__device__ __forceinline__ void mark_word(unsigned long long *w, unsigned long long m)
+{
+    if (m & ~__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicOr(w, m);
+}
+
+// A hub is sampled thousands of times and a small range has few words, but updates of one word, and of the words beside
+// it, are served one after the other (0.6 to 5 ns each; every wavefront in flight still finds the bit clear).  So a
+// workgroup gathers bits in LDS and updates each word once: sets of up to kMarkDirect words in a copy of the whole set,
+// at most kMarkGroups workgroups per list; others, 512 ids at a time, in a table of words, where a word that finds no slot
+// within kMarkProbes is updated directly; lists of up to kMarkPlain ids past the LDS.  Whole calls with one update per id /
+// like this / by the sort, 1 M ids: half of them one of 1.1 M possible ids 2,597 / 117 / 234 us; 64 possible ids
+// 2,983 / 48 / 173; 9,000 possible 349 / 50 / 215; spread over 1.1 M 167 / 153 / 240.  300,000 ids spread over 700,000:
+// 65 / 80 / 174.
+constexpr int kMarkItems = 2, kMarkIds = 256 * kMarkItems, kMarkGroups = 128, kMarkDirect = 4096, kMarkSlots = 1024, kMarkProbes = 4,
+              kMarkPlain = 4096;
 __global__ void __launch_bounds__(256) bit_mark_kernel(BitSets f, unsigned long long *bits, int *bad)
 {
-    const int l = blockIdx.y;
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= f.len[l]) return;
-    const int g = f.set_of[l];
-    const int64_t v = f.ids[l][i];
-    if (v < 0 || v >= f.limit[g]) {
-        bad[g] = 1; // every writer stores the same value
+    constexpr unsigned EMPTY = ~0u; // word indices stay below kBitTilesMax * 256
+    __shared__ unsigned long long set[kMarkDirect];
+    __shared__ unsigned key[kMarkSlots];
+    const int l = blockIdx.y, g = f.set_of[l];
+    const int64_t n = f.len[l], limit = f.limit[g], *ids = f.ids[l];
+    const unsigned n_words = static_cast<unsigned>((limit + 63) / 64);
+    const bool direct = n_words <= kMarkDirect && n >= 4 * static_cast<int64_t>(n_words); // uniform
+    const int64_t rounds = direct ? (n + kMarkGroups * kMarkIds - 1) / (kMarkGroups * kMarkIds) : 1;
+    const int64_t start = blockIdx.x * rounds * kMarkIds;
+    if (start >= n) return; // uniform
+    unsigned long long *words = bits + static_cast<int64_t>(f.tile0[g]) * 256;
+    bool outside = false; // an id outside the set's range
+    if (direct) {
+        for (unsigned s = threadIdx.x; s < n_words; s += 256) set[s] = 0;
+        __syncthreads();
+        const int64_t end = min(n, start + rounds * kMarkIds);
+#pragma unroll 4
+        for (int64_t i = start + threadIdx.x; i < end; i += 256) {
+            const int64_t v = ids[i];
+            if (v < 0 || v >= limit) outside = true;
+            else atomicOr(&set[v >> 6], 1ull << (v & 63));
+        }
+        __syncthreads();
+        for (unsigned s = threadIdx.x; s < n_words; s += 256)
+            if (set[s]) mark_word(words + s, set[s]);
+        if (outside) bad[g] = 1;
         return;
     }
-    unsigned long long *w = bits + static_cast<int64_t>(f.tile0[g]) * 256 + (v >> 6);
-    const unsigned long long bit = 1ull << (v & 63);
-    // a hub is sampled thousands of times: only those that find the bit clear queue up for the word
-    if (!(__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit)) atomicOr(w, bit);
+    int64_t v[kMarkItems];
+#pragma unroll
+    for (int j = 0; j < kMarkItems; ++j) v[j] = start + 256 * j + threadIdx.x < n ? ids[start + 256 * j + threadIdx.x] : -1;
+    if (n <= kMarkPlain) { // too few to queue up for long: past the LDS
+#pragma unroll
+        for (int j = 0; j < kMarkItems; ++j) {
+            if (start + 256 * j + threadIdx.x >= n) continue;
+            if (v[j] < 0 || v[j] >= limit) bad[g] = 1; // every writer stores the same value
+            else mark_word(words + (v[j] >> 6), 1ull << (v[j] & 63));
+        }
+        return;
+    }
+#pragma unroll
+    for (int s = 0; s < kMarkSlots; s += 256) {
+        set[s + threadIdx.x] = 0;
+        key[s + threadIdx.x] = EMPTY;
+    }
+    __syncthreads();
+    int slot[kMarkItems]; // of the words that this thread updates: it entered them
+#pragma unroll
+    for (int j = 0; j < kMarkItems; ++j) {
+        slot[j] = -1;
+        if (v[j] < 0 || v[j] >= limit) {
+            outside |= start + 256 * j + threadIdx.x < n;
+            continue;
+        }
+        const unsigned w = static_cast<unsigned>(v[j] >> 6);
+        const unsigned long long bit = 1ull << (v[j] & 63);
+        unsigned h = (w * 2654435761u) >> 22; // multiplicative hashing: the upper 10 bits
+        bool placed = false;
+        for (int q = 0; q < kMarkProbes && !placed; ++q) {
+            unsigned k = __hip_atomic_load(&key[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (k == EMPTY) {
+                k = atomicCAS(&key[h], EMPTY, w);
+                if (k == EMPTY) slot[j] = h;
+            }
+            placed = k == EMPTY || k == w;
+            if (placed) atomicOr(&set[h], bit);
+            h = (h + 1) % kMarkSlots;
+        }
+        if (!placed) mark_word(words + w, bit);
+    }
+    __syncthreads();
+    unsigned long long now[kMarkItems]; // all loads before the first update, for which a later load would wait
+#pragma unroll
+    for (int j = 0; j < kMarkItems; ++j)
+        now[j] = slot[j] >= 0 ? __hip_atomic_load(words + (v[j] >> 6), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : ~0ull;
+#pragma unroll
+    for (int j = 0; j < kMarkItems; ++j)
+        if (slot[j] >= 0 && (set[slot[j]] & ~now[j])) atomicOr(words + (v[j] >> 6), set[slot[j]]);
+    if (outside) bad[g] = 1;
 }
 
 // sum over the workgroup's 256 threads, in every thread
@@ -567,8 +649,9 @@ static heta_status heta_unique_relabel_batch_impl(int32_t n_groups, const int32_
     Scratch scratch;
     heta_status e;
     if (n_groups <= kFusedItems && group_ptr[n_groups] <= kFusedLists && outputs_apart(n_groups, group_ptr, lists, lens, totals, unique_ids, local)) {
-        // Id ranges of up to 67 M ids together: by bitmap, whatever the number of ids (its cost is three passes over at
-        // most 8 MB; past that the sort, which does not grow with the range, is the faster one).
+        // Id ranges of up to 67 M ids together: by bitmap, whatever the number of ids.  The bound keeps the scratch at 12 MB, which
+        // the recycling pool still takes, and the counts that a tile adds up at 4,096; the sort is not yet faster there (67 M
+        // possible ids, 300 / 50,000 / 5 M given: 50 / 56 / 388 us, by the sort 96 / 133 / 867).
         BitSets f{};
         f.n_sets = n_groups;
         int64_t tiles = 0, len_max = 0;
@@ -601,7 +684,8 @@ static heta_status heta_unique_relabel_batch_impl(int32_t n_groups, const int32_
             hipLaunchKernelGGL(bit_zero_kernel, dim3((unsigned)((words / 2 + 255) / 256)), dim3(256), 0, st, reinterpret_cast<uint4 *>(bits),
                                static_cast<int64_t>(words / 2), bad, (int)n_groups);
             HETA_LAUNCH_CHECK("bit_zero_kernel");
-            hipLaunchKernelGGL(bit_mark_kernel, lists_grid, dim3(256), 0, st, f, bits, bad);
+            const dim3 mark_grid((unsigned)((len_max + kMarkIds - 1) / kMarkIds), (unsigned)group_ptr[n_groups]);
+            hipLaunchKernelGGL(bit_mark_kernel, mark_grid, dim3(256), 0, st, f, bits, bad);
             HETA_LAUNCH_CHECK("bit_mark_kernel");
             hipLaunchKernelGGL(bit_count_kernel, dim3((unsigned)tiles), dim3(256), 0, st, bits, tile_count);
             HETA_LAUNCH_CHECK("bit_count_kernel");
