@@ -1080,11 +1080,10 @@ __global__ void __launch_bounds__(1024) attn_slab_sum_kernel(const float *part, 
 // at a time) and run on the fp32 matrix instruction, whose
 // products and sums are the fp32 FMAs of the vector ALU: what bounds them is the pass over the table.  Measured
 // over the four tables of an academic graph (1.87 M fp32 rows of 128, 16 and 24 vectors), against lane shuffles and
-// per-lane FMAs: scores 547 -> 271 us, input gradient 472 -> 224 us, parameter gradient 628 -> 361 us; 187,000 bf16
-// rows with up to 56 vectors (set by set before, above 32): 274 -> 63, 209 -> 81 and 704 -> 103 us.
+// per-lane FMAs: scores 547 -> 271 us, input gradient 472 -> 224 us; 187,000 bf16 rows with up to 56 vectors (set by set
+// before, above 32): 274 -> 63 and 209 -> 81 us.
 constexpr int kMultiSets = 8, kMultiCols = 128;
 constexpr int kMultiVecs = 120; // the input gradient keeps all vectors in LDS: 120 * (512 + 8) bytes stay below 64 KB
-constexpr int kVecTile = 32; // vectors per matrix tile
 struct ScoreMulti {
     const float *vec[kMultiSets]; // [K][d] each
     float *score[kMultiSets];     // [n][K] each: written by the forward, read (dscore) by the backward
@@ -1120,6 +1119,23 @@ template <> __device__ __forceinline__ void load4<bf16_t>(const bf16_t *p, float
     f[0] = __uint_as_float(v.x << 16); f[1] = __uint_as_float(v.x & 0xffff0000u);
     f[2] = __uint_as_float(v.y << 16); f[3] = __uint_as_float(v.y & 0xffff0000u);
 }
+
+// the same in two steps: the load, and its four columns
+template <typename T> struct Raw4;
+template <> struct Raw4<float> {
+    float4 v;
+    __device__ __forceinline__ void load(const float *p) { v = *reinterpret_cast<const float4 *>(p); }
+    __device__ __forceinline__ void get(float f[4]) const { f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w; }
+};
+template <> struct Raw4<bf16_t> {
+    uint2 v;
+    __device__ __forceinline__ void load(const bf16_t *p) { v = *reinterpret_cast<const uint2 *>(p); }
+    __device__ __forceinline__ void get(float f[4]) const
+    {
+        f[0] = __uint_as_float(v.x << 16); f[1] = __uint_as_float(v.x & 0xffff0000u);
+        f[2] = __uint_as_float(v.y << 16); f[3] = __uint_as_float(v.y & 0xffff0000u);
+    }
+};
 
 // Scores of 16 NT vectors (blockIdx.y picks them) and 16 rows per tile: the vectors are the first operand, so a
 // lane ends with one row's scores of four consecutive vectors - one 16-byte store where a set has a multiple of
@@ -1286,60 +1302,92 @@ __global__ void __launch_bounds__(256, 3) attn_score_bwd_multi_input_kernel(int6
     }
 }
 
-// part[slab][v][128]: the slab's sum over its rows of dscore_v[i] x[i, :].  The contraction runs over the rows, two
-// per step (one per wavefront half); a lane's first operand is its vector's dscore, its second the four columns
-// 4 l .. 4 l + 3.  A wavefront takes every fourth group of 2 U rows of the slab, the four wavefronts' sums are added
-// in wavefront order through LDS.
-template <typename T>
-__global__ void __launch_bounds__(256, 3) attn_score_bwd_multi_param_kernel(const T *x, int64_t ld_x, int64_t n, int d, ScoreMulti m, int slab_rows,
+// part[slab][v][128]: the slab's sum over its rows of dscore_v[i] x[i, :].  The contraction runs over the rows, four per
+// step (one per quarter h of the wavefront); a lane's first operand is its vector's dscore, its second the four columns
+// 64 c + 4 l .. + 3 of chunk c, one product each.  A wavefront takes every fourth group of 4 U rows of the slab, the four
+// wavefronts' sums are added in wavefront order through LDS.  16 NT vectors per workgroup (blockIdx.y picks them), NC
+// chunks of 64 columns: no product is spent on more.  With 32 vectors and 128 columns whatever is given, two rows per
+// step and the loads behind branches, a pass was bound by the products and by one load after the other: 700,000 rows
+// of 128 columns, bf16 with 1 / 24 vectors 146 / 155 -> 45 / 70 us, fp32 116 / 124 -> 74 / 88; of 64, fp32, 4 vectors 89 -> 38.
+template <typename T, int NC, int NT>
+__global__ void __launch_bounds__(256, NC * NT * sizeof(T) == 16 ? 3 : 4) attn_score_bwd_multi_param_kernel(const T *x, int64_t ld_x, int64_t n, int d, ScoreMulti m, int slab_rows,
                                                                          float *part)
 {
-    constexpr int U = 8;
-    __shared__ __align__(16) float buf[kVecTile][kMultiCols];
-    const int lane = threadIdx.x & 63, l = lane & 31, h = lane >> 5, w = threadIdx.x >> 6;
+    constexpr int U = 4, VT = 16 * NT;
+    __shared__ __align__(16) float buf[VT][kMultiCols];
+    const int lane = threadIdx.x & 63, l = lane & 15, h = lane >> 4, w = threadIdx.x >> 6;
     const int64_t slab = blockIdx.x;
     const int64_t i0 = slab * slab_rows, i1 = min(n, i0 + slab_rows);
-    const int v = blockIdx.y * kVecTile + l;
-    const bool has_v = v < m.NV, has_c = 4 * l < d;
-    const float *ds = has_v ? pick(m.score, v / m.K) + v % m.K : nullptr;
-    f32x16 acc[4];
+    // lanes past the vectors and the columns given repeat others; what they sum up is not written out
+    const float *ds[NT];
+    int col[NC];
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int t = 0; t < NT; ++t) {
+        const int v = min(static_cast<int>(blockIdx.y) * VT + 16 * t + l, m.NV - 1);
+        ds[t] = pick(m.score, v / m.K) + v % m.K;
+    }
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[j][i] = 0.f;
-    for (int64_t rb = i0 + w * (2 * U); rb < i1; rb += 8 * U) { // uniform per wavefront
-        float xv[U][4], sv[U];
+    for (int c = 0; c < NC; ++c) col[c] = 64 * c + 4 * l < d ? 64 * c + 4 * l : 0;
+    f32x4 acc[NT][NC][4];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[t][c][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int64_t rb = i0 + w * (4 * U); rb < i1; rb += 16 * U) { // uniform per wavefront
+        // no load behind a branch, a conversion or a product: all of them are in flight together
+        Raw4<T> raw[U][NC];
+        float sv[U][NT];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t r = rb + 2 * u + h;
-            xv[u][0] = xv[u][1] = xv[u][2] = xv[u][3] = 0.f;
-            sv[u] = 0.f;
-            if (r < i1 && has_c) load4<T>(x + r * ld_x + 4 * l, xv[u]);
-            if (r < i1 && has_v) sv[u] = ds[r * m.K];
+            const int64_t r = min(rb + 4 * u + h, i1 - 1);
+#pragma unroll
+            for (int c = 0; c < NC; ++c) raw[u][c].load(x + r * ld_x + col[c]);
+#pragma unroll
+            for (int t = 0; t < NT; ++t) sv[u][t] = ds[t][r * m.K];
         }
+        __builtin_amdgcn_sched_barrier(0); // else each load is moved down to its products
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+        for (int u = 0; u < U; ++u) {
+            const bool past = rb + 4 * u + h >= i1; // a copy of the slab's last row
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(sv[u], xv[u][j], acc[j], 0, 0, 0);
+            for (int t = 0; t < NT; ++t) sv[u][t] = past ? 0.f : sv[u][t];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                float xv[4];
+                raw[u][c].get(xv);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    xv[j] = past ? 0.f : xv[j];
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) acc[t][c][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(sv[u][t], xv[j], acc[t][c][j], 0, 0, 0);
+                }
+            }
+        }
     }
     for (int q = 0; q < 4; ++q) { // wavefront q adds its sums to the buffer, in order
         if (w == q) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                float4 *b = reinterpret_cast<float4 *>(&buf[8 * (i / 4) + 4 * h + i % 4][4 * l]);
-                float4 t = make_float4(acc[0][i], acc[1][i], acc[2][i], acc[3][i]);
-                if (q > 0) {
-                    const float4 o = *b;
-                    t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
-                }
-                *b = t;
-            }
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        float4 *b = reinterpret_cast<float4 *>(&buf[16 * t + 4 * h + i][64 * c + 4 * l]);
+                        float4 s = make_float4(acc[t][c][0][i], acc[t][c][1][i], acc[t][c][2][i], acc[t][c][3][i]);
+                        if (q > 0) {
+                            const float4 o = *b;
+                            s.x += o.x; s.y += o.y; s.z += o.z; s.w += o.w;
+                        }
+                        *b = s;
+                    }
         }
         __syncthreads();
     }
-    float *o = part + (slab * gridDim.y + blockIdx.y) * (kVecTile * kMultiCols);
-    for (int t = threadIdx.x * 4; t < kVecTile * kMultiCols; t += 1024)
-        *reinterpret_cast<float4 *>(o + t) = *reinterpret_cast<const float4 *>(&buf[0][0] + t);
+    float *o = part + (slab * gridDim.y + blockIdx.y) * (VT * kMultiCols);
+    for (int t = threadIdx.x * 4; t < VT * kMultiCols; t += 1024)
+        if (t % kMultiCols < 64 * NC) *reinterpret_cast<float4 *>(o + t) = *reinterpret_cast<const float4 *>(&buf[0][0] + t);
 }
 
 // dvec_v[c] = sum over the slabs, in slab order per wavefront and wavefront order through LDS (as attn_slab_sum_kernel)
@@ -1349,6 +1397,7 @@ __global__ void __launch_bounds__(1024) attn_multi_slab_sum_kernel(const float *
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t elems = static_cast<int64_t>(nvc) * kMultiCols;
     const int64_t t = static_cast<int64_t>(blockIdx.x) * 64 + lane;
+    if ((t - lane) % kMultiCols >= d) return; // uniform: columns that no slab has written
     float a = 0.f;
     if (t < elems) {
 #pragma unroll 8
@@ -1668,7 +1717,8 @@ heta_status heta_attn_score_bwd_multi(heta_graph *g, const void *x, heta_dtype d
         m.dvec[j] = dvecs ? dvecs[j] : nullptr;
         any_dvec = any_dvec || m.dvec[j];
     }
-    const int tiles = (m.NV + kVecTile - 1) / kVecTile, nvc = tiles * kVecTile;
+    const int nt = m.NV <= 16 ? 1 : 2; // tiles of 16 vectors per workgroup of the parameter gradient
+    const int tiles = (m.NV + 16 * nt - 1) / (16 * nt), nvc = tiles * 16 * nt;
     if (dx && n > 0) {
         const int nc8 = (m.NV + 7) / 8 * 8;
         const size_t lds = static_cast<size_t>(nc8) * (kMultiCols * sizeof(float) + sizeof(float *)); // at most 62,400 bytes
@@ -1681,9 +1731,10 @@ heta_status heta_attn_score_bwd_multi(heta_graph *g, const void *x, heta_dtype d
         HETA_LAUNCH_CHECK("attn_score_bwd_multi_input_kernel");
     }
     if (any_dvec) {
-        // slabs of a multiple of 64 rows (each wavefront's eight row pairs), at most 1,024 slabs: enough workgroups for
-        // four per CU, and the slab sums (16 KB each) stay small beside the table
-        const int64_t slab_rows = std::max<int64_t>(128, (n + 1024 * 64 - 1) / (1024 * 64) * 64);
+        // slabs of a multiple of 64 rows (16 per wavefront and step), at most 1,024 slabs: enough workgroups for
+        // four per CU, and the slab sums (8 or 16 KB each) stay small beside the table
+        const int64_t most = dt == HETA_F32 && nt == 2 && d > 64 ? 768 : 1024;
+        const int64_t slab_rows = std::max<int64_t>(128, (n + most * 64 - 1) / (most * 64) * 64);
         const int64_t n_slabs = (n + slab_rows - 1) / slab_rows;
         if (n_slabs == 0) {
             for (int j = 0; j < n_sets; ++j)
@@ -1696,12 +1747,14 @@ heta_status heta_attn_score_bwd_multi(heta_graph *g, const void *x, heta_dtype d
         float *part = static_cast<float *>(g->d_attn);
         ProfScope prof("attn_score_bwd_param_kernel", st, static_cast<double>(n) * (d * dtype_size(dt) + 4.0 * m.NV), 0);
         const dim3 grid((unsigned)n_slabs, (unsigned)tiles);
-        if (dt == HETA_F32)
-            hipLaunchKernelGGL((attn_score_bwd_multi_param_kernel<float>), grid, dim3(256), 0, st, static_cast<const float *>(x), ld_x, n, (int)d, m,
-                               (int)slab_rows, part);
-        else
-            hipLaunchKernelGGL((attn_score_bwd_multi_param_kernel<bf16_t>), grid, dim3(256), 0, st, static_cast<const bf16_t *>(x), ld_x, n, (int)d, m,
-                               (int)slab_rows, part);
+#define HETA_SP(TT, NC, NT) hipLaunchKernelGGL((attn_score_bwd_multi_param_kernel<TT, NC, NT>), grid, dim3(256), 0, st, static_cast<const TT *>(x), ld_x, n, (int)d, m, (int)slab_rows, part)
+#define HETA_SP_N(TT, NC) do { if (nt == 1) HETA_SP(TT, NC, 1); else HETA_SP(TT, NC, 2); } while (0)
+#define HETA_SP_T(TT) do { if (d <= 64) HETA_SP_N(TT, 1); else HETA_SP_N(TT, 2); } while (0)
+        if (dt == HETA_F32) HETA_SP_T(float);
+        else HETA_SP_T(bf16_t);
+#undef HETA_SP_T
+#undef HETA_SP_N
+#undef HETA_SP
         HETA_LAUNCH_CHECK("attn_score_bwd_multi_param_kernel");
         const int64_t elems = static_cast<int64_t>(nvc) * kMultiCols;
         hipLaunchKernelGGL(attn_multi_slab_sum_kernel, dim3((unsigned)((elems + 63) / 64)), dim3(1024), 0, st, part, n_slabs, nvc, (int)d, m);
