@@ -206,29 +206,37 @@ struct SplitSegs { // passed by value
     int64_t M[kMaxSeg], ldo[kMaxSeg];
     unsigned first; // first workgroup of this launch
 };
-// One workgroup of NW wavefronts per 64 elements: wavefront w adds the splits w, w + NW, ... (eight loads in flight),
-// the NW sums are added in wavefront order through LDS.  16 wavefronts from 128 splits on, 4 below.  (With one thread
-// per element, a serial chain on a few dozen workgroups, 8,192 elements x 688 splits took 17.4 us, now 8.)
+// NW wavefronts per 64 elements: wavefront w adds the splits w, w + NW, ... (eight loads in flight), the NW sums are
+// added in wavefront order through LDS.  16 wavefronts from 128 splits on, else 4 (with one thread per element, a serial
+// chain on a few dozen workgroups, 8,192 elements x 688 splits took 17.4 us, now 8); one, four of them in a workgroup,
+// below 32 splits of 196,608 elements and more, which are three wavefronts per SIMD by themselves (whole weight
+// gradients with four and with one: three of 2,000 rows, 768 x 1,024, bf16 65.7 / 57.5 us; one of 9,000 rows 49.0 / 45.0,
+// of 110,000 rows, 789 x 256, 107.8 / 100.4; of 500 rows, 128 x 256, fp32 17.3 / 18.2).
 template <int NW>
-__global__ void __launch_bounds__(64 * NW) splitk_reduce_kernel(SplitSegs g, int n_split, int64_t N, float beta)
+__global__ void __launch_bounds__(NW == 1 ? 256 : 64 * NW) splitk_reduce_kernel(SplitSegs g, int n_split, int64_t N, float beta)
 {
     __shared__ float red[NW][64];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, w = NW == 1 ? 0 : threadIdx.x >> 6;
     const int seg = blockIdx.y;
     const int64_t total = static_cast<int64_t>(g.M[seg]) * N;
-    const int64_t t = (static_cast<int64_t>(g.first) + blockIdx.x) * 64 + lane;
+    const int64_t block = static_cast<int64_t>(g.first) + blockIdx.x;
+    const int64_t t = NW == 1 ? block * 256 + threadIdx.x : block * 64 + lane;
     const float *part = g.part[seg];
     float a = 0.f;
     if (t < total) {
 #pragma unroll 8
         for (int s = w; s < n_split; s += NW) a += part[static_cast<int64_t>(s) * total + t];
     }
-    red[w][lane] = a;
-    __syncthreads();
+    if (NW > 1) {
+        red[w][lane] = a;
+        __syncthreads();
+    }
     if (w != 0 || t >= total) return;
-    a = 0.f;
+    if (NW > 1) {
+        a = 0.f;
 #pragma unroll
-    for (int i = 0; i < NW; ++i) a += red[i][lane];
+        for (int i = 0; i < NW; ++i) a += red[i][lane];
+    }
     const int64_t m = t / N, n = t % N;
     float *o = g.out[seg] + m * g.ldo[seg] + n;
     *o = (beta != 0.f) ? beta * *o + a : a;
@@ -610,14 +618,17 @@ static heta_status wgrad_impl(heta_graph *g, int64_t n_rows, int n_seg, const vo
             bytes += (n_split + 1.0) * total * 4.0;
         }
         ProfScope prof("splitk_reduce_kernel", st, bytes, 0);
-        const int nw = n_split >= 128 ? 16 : 4;
-        launch_pieces((total_max + 63) / 64, 64 * nw, [&](unsigned first, unsigned count) {
+        const int nw = n_split >= 128 ? 16 : n_split >= 32 || out_elems < 196608 ? 4 : 1;
+        const int64_t per_block = nw == 1 ? 256 : 64;
+        launch_pieces((total_max + per_block - 1) / per_block, nw == 1 ? 256 : 64 * nw, [&](unsigned first, unsigned count) {
             segs.first = first;
             const dim3 grid(count, (unsigned)n_seg);
-            if (nw == 16)
-                hipLaunchKernelGGL(splitk_reduce_kernel<16>, grid, dim3(1024), 0, st, segs, static_cast<int>(n_split), (int64_t)d_out, beta);
-            else
-                hipLaunchKernelGGL(splitk_reduce_kernel<4>, grid, dim3(256), 0, st, segs, static_cast<int>(n_split), (int64_t)d_out, beta);
+            const auto launch = [&](auto kernel, int threads) {
+                hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, st, segs, static_cast<int>(n_split), (int64_t)d_out, beta);
+            };
+            if (nw == 16) launch(splitk_reduce_kernel<16>, 1024);
+            else if (nw == 4) launch(splitk_reduce_kernel<4>, 256);
+            else launch(splitk_reduce_kernel<1>, 256);
         });
         HETA_LAUNCH_CHECK("splitk_reduce_kernel");
     }

@@ -471,7 +471,9 @@ def test_project_row_scale_beta_and_odd_strides(pad, gemm_path):
 
 
 @pytest.mark.parametrize("n,d_in,d_out", [(2000, 32, 32), (5000, 128, 256), (3000, 7, 256), (1500, 300, 256),
-                                          (700, 789, 256), (40, 16, 8), (5000, 768, 1024)])
+                                          (700, 789, 256), (40, 16, 8), (5000, 768, 1024),
+                                          # splits summed by four wavefronts and by one: 196,400 and 196,608 elements, one split
+                                          (500, 491, 400), (500, 768, 256), (100, 1000, 333)])
 @pytest.mark.parametrize("in_s", ["f32", "bf16"])
 def test_project_wgrad(n, d_in, d_out, in_s, gemm_path):
     rel = Relation("w", 0, 1, np.zeros(n + 1, dtype=np.int64), np.zeros(0, dtype=np.int32))
