@@ -223,6 +223,39 @@ __device__ __forceinline__ void fwd_stats(const SweepParams &p, int64_t e0, int 
     group_sum<W, KT>(pos);
 }
 
+// Forward of one row: W lanes, at most W NPL edges.
+template <int W, int KT, int NPL>
+__device__ __forceinline__ void fwd_row(const SweepParams &p, int64_t row, int64_t e0, int n, bool live, int lane, int k0, const float *ar)
+{
+    float x[NPL][KT], m[KT], inv[KT], den[KT], pos[KT];
+    fwd_stats<W, KT, NPL>(p, e0, n, lane, k0, ar, x, m, den, pos);
+    const bool empty = n == 0;
+#pragma unroll
+    for (int k = 0; k < KT; ++k) {
+        inv[k] = empty ? 0.f : 1.f / den[k];
+        if (empty) m[k] = 0.f;
+        pos[k] = empty ? 0.f : pos[k] * inv[k];
+    }
+#pragma unroll
+    for (int j = 0; j < NPL; ++j) {
+        if (lane + j * W < n) {
+            float a[KT], gt[KT];
+#pragma unroll
+            for (int k = 0; k < KT; ++k) {
+                a[k] = fabsf(x[j][k]) * inv[k];
+                gt[k] = __float_as_uint(x[j][k]) >> 31 ? 0.f : a[k]; // the weight restricted to edges with a positive logit
+            }
+            storek<KT>(p.alpha + (e0 + lane + j * W) * p.K + k0, a);
+            if (p.gate) storek<KT>(p.gate + (e0 + lane + j * W) * p.K + k0, gt);
+        }
+    }
+    if (live && lane == 0 && p.smax) {
+        storek<KT>(p.smax + row * p.K + k0, m);
+        storek<KT>(p.sinv + row * p.K + k0, inv);
+    }
+    if (live && lane == 0 && p.apos) storek<KT>(p.apos + row * p.K + k0, pos);
+}
+
 // One row: W lanes, at most W NPL edges.
 template <int W, int KT, int NPL, int OP>
 __device__ __forceinline__ void sweep_row(const SweepParams &p, int64_t q, bool live, int lane, int k0)
@@ -232,34 +265,15 @@ __device__ __forceinline__ void sweep_row(const SweepParams &p, int64_t q, bool 
     float ar[KT], acc[KT], m[KT], inv[KT];
     loadk<KT>(p.row_a + row * p.K + k0, ar);
     if (OP == SWEEP_FWD) {
+        // Only as many slots per lane as the row needs (uniform per wavefront), the same bits whichever runs: an empty slot
+        // costs its exponentials all the same (whole forwards of 20,000 rows of 40 edges, 8 heads 103 -> 69 us, 16 heads
+        // 200 -> 136; 100,000 rows of one edge, 8 heads 23.0 -> 21.0).
         const int n = static_cast<int>(e1 - e0);
-        float x[NPL][KT], pos[KT];
-        fwd_stats<W, KT, NPL>(p, e0, n, lane, k0, ar, x, m, acc, pos);
-        const bool empty = n == 0;
-#pragma unroll
-        for (int k = 0; k < KT; ++k) {
-            inv[k] = empty ? 0.f : 1.f / acc[k];
-            if (empty) m[k] = 0.f;
-            pos[k] = empty ? 0.f : pos[k] * inv[k];
-        }
-#pragma unroll
-        for (int j = 0; j < NPL; ++j) {
-            if (lane + j * W < n) {
-                float a[KT], gt[KT];
-#pragma unroll
-                for (int k = 0; k < KT; ++k) {
-                    a[k] = fabsf(x[j][k]) * inv[k];
-                    gt[k] = __float_as_uint(x[j][k]) >> 31 ? 0.f : a[k]; // the weight restricted to edges with a positive logit
-                }
-                storek<KT>(p.alpha + (e0 + lane + j * W) * p.K + k0, a);
-                if (p.gate) storek<KT>(p.gate + (e0 + lane + j * W) * p.K + k0, gt);
-            }
-        }
-        if (live && lane == 0 && p.smax) {
-            storek<KT>(p.smax + row * p.K + k0, m);
-            storek<KT>(p.sinv + row * p.K + k0, inv);
-        }
-        if (live && lane == 0 && p.apos) storek<KT>(p.apos + row * p.K + k0, pos);
+        if (W == 64 && n <= 64) fwd_row<W, KT, 1>(p, row, e0, n, live, lane, k0, ar);
+        else if (W == 64 && n <= 128) fwd_row<W, KT, 2>(p, row, e0, n, live, lane, k0, ar);
+        else if (W == 64 && n <= 256) fwd_row<W, KT, 4>(p, row, e0, n, live, lane, k0, ar);
+        else if (W == 1 && !__any(n > 1)) fwd_row<W, KT, 1>(p, row, e0, n, live, lane, k0, ar);
+        else fwd_row<W, KT, NPL>(p, row, e0, n, live, lane, k0, ar);
     } else {
 #pragma unroll
         for (int k = 0; k < KT; ++k) acc[k] = 0.f;

@@ -273,6 +273,54 @@ def test_sweeps_at_the_edges_of_the_row_classes(heads, side):
         graph.destroy()
 
 
+@pytest.mark.parametrize("heads", [1, 2, 4, 8, 16])
+@pytest.mark.parametrize("degrees", [[63, 64, 65, 127, 128, 129, 255, 256, 257, 510], [1] * 200 + [0] * 100, [2, 1] * 150])
+def test_forward_at_the_edges_of_the_slots_per_lane(heads, degrees):
+    """Rows of one wavefront take 1, 2, 4 or 8 slots per lane, wavefronts of single rows per thread 1 or 4."""
+    deg = np.array(degrees)
+    n_dst, n_src, d = deg.size, 300, 8 * heads
+    g = rng.stream("tests", f"slots{heads}x{deg.max()}")
+    dst, src = np.repeat(np.arange(n_dst), deg), g.integers(0, n_src, deg.sum())
+    z = g.standard_normal((n_src, d)).astype(np.float32)
+    el, er = ((2.0 * g.standard_normal((n, heads))).astype(np.float32) for n in (n_src, n_dst))
+    graph = heta.heta_graph_create([(n_src, 4, 0), (n_dst, 4, 0)], [(0, 1, np.concatenate([[0], np.cumsum(deg)]).astype(np.int64), src.astype(np.int32))])
+    try:
+        out, pos = (torch.full((n_dst, d), 3.0, device="cuda") for _ in range(2))
+        smax, sinv, apos = (torch.full((n_dst, heads), 5.0, device="cuda") for _ in range(3))
+        heta.heta_rel_attn_fwd_train(graph, 0, up(z), up(el), up(er), 0.2, out, smax=smax, sinv=sinv, out_pos=pos, apos=apos)
+        ref_o, alpha = rgat.gat_aggregate_fwd(src, dst, n_dst, z, el, er, 0.2)
+        gate = alpha * ((el[src] + er[dst]) > 0)
+        ref_apos, ref_pos = np.zeros((n_dst, heads)), np.zeros((n_dst, heads, 8))
+        np.add.at(ref_apos, dst, gate)
+        np.add.at(ref_pos, dst, gate[:, :, None] * z.astype(np.float64)[src].reshape(-1, heads, 8))
+        for got, ref, what in ((out, ref_o, "out"), (pos, ref_pos.reshape(n_dst, d), "out_pos"), (apos, ref_apos, "apos")):
+            assert_rows_close(host(got), ref, 1e-4, what)
+    finally:
+        graph.destroy()
+
+
+def test_forward_of_short_wavefront_rows_costs_about_what_its_edges_do():
+    """Rows of 40 edges do not pay for the slots of rows of 511: 1.9 times the time of as many edges in rows of 300 when
+    they did, 1.3 times without."""
+    heads, d, best = 8, 64, {}
+    z, el = torch.randn((50_000, d), device="cuda"), torch.randn((50_000, heads), device="cuda")
+    for rows, degree in ((20_000, 40), (2_667, 300)):
+        col = rng.stream("tests", f"short_rows{degree}").integers(0, 50_000, rows * degree).astype(np.int32)
+        graph = heta.heta_graph_create([(50_000, 4, 0), (rows, 4, 0)], [(0, 1, np.arange(rows + 1, dtype=np.int64) * degree, col)])
+        er, out = torch.randn((rows, heads), device="cuda"), torch.empty((rows, d), device="cuda")
+        start, end, times = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True), []
+        for _ in range(8):
+            start.record()
+            for _ in range(20):
+                heta.heta_rel_attn_fwd(graph, 0, z, el, er, 0.2, out)
+            end.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(end))
+        best[degree] = min(times)
+        graph.destroy()
+    assert best[40] <= 1.6 * best[300]
+
+
 @pytest.mark.parametrize("heads", [1, 2, 4, 8])
 @pytest.mark.parametrize("slope", [-0.5, 0.0, 1.0])
 def test_positive_logits_are_those_before_the_activation(heads, slope):
