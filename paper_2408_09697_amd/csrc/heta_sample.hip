@@ -651,7 +651,8 @@ static heta_status heta_unique_relabel_batch_impl(int32_t n_groups, const int32_
     if (n_groups <= kFusedItems && group_ptr[n_groups] <= kFusedLists && outputs_apart(n_groups, group_ptr, lists, lens, totals, unique_ids, local)) {
         // Id ranges of up to 67 M ids together: by bitmap, whatever the number of ids.  The bound keeps the scratch at 12 MB, which
         // the recycling pool still takes, and the counts that a tile adds up at 4,096; the sort is not yet faster there (67 M
-        // possible ids, 300 / 50,000 / 5 M given: 50 / 56 / 388 us, by the sort 96 / 133 / 867).
+        // possible ids, 300 / 50,000 / 5 M given: 50 / 56 / 388 us, by the sort 96 / 133 / 867), but for many ids of few words
+        // (400,000 of the lowest 67,000: 161 us, by the sort 145).
         BitSets f{};
         f.n_sets = n_groups;
         int64_t tiles = 0, len_max = 0;
