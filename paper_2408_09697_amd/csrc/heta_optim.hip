@@ -52,9 +52,9 @@ __device__ __forceinline__ bf16_t adam_to_bf16(float f)
 
 // Several tables in one launch (the weight matrices of a model and its learnable tables after one backward pass), their
 // workgroups one after the other: with the table in blockIdx.y and the grid as long as the largest table needs, the
-// surplus workgroups of the others and a 64-bit division per thread were 5 % of an update (1.17 M rows of 128 in three
-// tables: fp32 830 -> 786 us = 5.3 TB/s, bf16 703 -> 663; two and four chunks per thread 788 and 780 / 676 and 678,
-// streaming stores 781 / 659 but nothing at a tenth of the rows).
+// surplus workgroups of the others and a 64-bit division per thread were 4 % of an update (1.17 M rows of 128 in three
+// tables, both run in turn: fp32 802 -> 770 us = 5.4 TB/s; in a run of their own 830 -> 786, bf16 703 -> 663, where two and
+// four chunks per thread took 788 and 780 / 676 and 678, streaming stores 781 / 659 but nothing at a tenth of the rows).
 constexpr int kAdamMulti = 16;
 struct AdamMulti {
     int n;
