@@ -1201,3 +1201,66 @@ def test_graphs_created_in_one_batch_equal_graphs_created_one_by_one(mode, on_de
         heta.heta_graph_create_batch(list(bad))
     assert ei.value.status == heta.HETA_ERR_BAD_CSR
     assert heta.heta_graph_create_batch([]) == []
+
+
+@pytest.mark.parametrize("kind", ["growing", "late", "compensated", "specials"])
+@pytest.mark.parametrize("n,k,d_out,trans,segments", [(300, 70, 40, False, 1), (12900, 100, 64, True, 2), (17001, 72, 130, False, 3), (33001, 129, 256, True, 1), (20000, 20, 100, False, 2)])
+def test_f32_products_over_a_wide_range(n, k, d_out, trans, segments, kind):
+    """fp32 products are fed as fp16 terms scaled by a power of two per row and column.  growing: every 16 columns (and
+    every 16 rows, for the weight gradient) 2^6 larger than those before, so that scales are set anew all along; late: rows
+    that start with zeros; compensated: features spread over 2^40 (small launches: 2^24) whose weights make up for it;
+    specials: rows with an infinity or a NaN, which stay alone.  Small launches, tiles of 64, 128 and 256 columns, sums and independent products.
+
+    Bound per element, in units of 2^-24 sum |a b|: one for each operand's representation, one for the term left out, and
+    two for each of the 3 ceil(K / 16) additions to the accumulator."""
+    g = rng.stream("tests", f"range_{kind}_{n}_{k}")
+    xs = [g.standard_normal((n, k)).astype(np.float32) for _ in range(segments)]
+    ws = [g.standard_normal((k, d_out)).astype(np.float32) for _ in range(segments)]
+    gout = g.standard_normal((n, d_out)).astype(np.float32)
+    bad = np.array([5, n // 2, n - 1])
+    for x, w in zip(xs, ws):
+        if kind == "growing":
+            x *= np.exp2(6.0 * (np.arange(k) // 16) + np.arange(n)[:, None] // 16 % 13 * 6.0 - 60.0).astype(np.float32)
+        if kind == "late":
+            x[:, : k // 2] *= (np.arange(n)[:, None] % 3 == 0)
+            x[n // 3: n // 2] = 0.0
+        if kind == "compensated":
+            span = 20.0 if n > 96 * 128 else 12.0  # packed weights are levelled; small launches have the range of their terms
+            r = np.exp2(np.linspace(-span, span, k)[g.permutation(k)]).astype(np.float32)
+            x *= r
+            w /= r[:, None]
+            w[k // 2] = 0.0
+        if kind == "specials":
+            x[bad, [0, k // 2, k - 1]] = [np.inf, np.nan, -np.inf]
+    good = np.setdiff1d(np.arange(n), bad) if kind == "specials" else np.arange(n)
+    unit = 2.0 ** -24
+
+    def check(got, a, b, terms):
+        ref, size = np.zeros((a[0].shape[0], b[0].shape[1])), np.zeros((a[0].shape[0], b[0].shape[1]))
+        for x, w in zip(a, b):
+            ref += x.astype(np.float64) @ w.astype(np.float64)
+            size += np.abs(x.astype(np.float64)) @ np.abs(w.astype(np.float64))
+        err = np.abs(got.cpu().numpy().astype(np.float64) - ref)
+        bound = (3 + 6 * terms) * unit * size + 1e-37
+        assert np.all(err <= bound), float((err / bound).max())
+
+    up = [dev_table(x, "f32", 4) for x in xs]
+    wd = [dev_table(w.T.copy() if trans else w, "f32", 4) for w in ws]
+    hg = heta.heta_graph_create([(n, 8, 0)], [])
+    try:
+        steps = (k + 15) // 16
+        out = torch.full((n, d_out), float("nan"), dtype=torch.float32, device="cuda")
+        heta.heta_project_sum(up, wd, out, trans_w=trans, graph=hg)
+        check(out[torch.from_numpy(good).cuda()], [x[good] for x in xs], ws, steps * segments)
+        assert kind != "specials" or not torch.isfinite(out[torch.from_numpy(bad).cuda()]).any()
+        outs = [torch.full((n, d_out), float("nan"), dtype=torch.float32, device="cuda") for _ in xs]
+        heta.heta_project_batch(up, wd, outs, trans_w=trans, graph=hg)
+        for o, x, w in zip(outs, xs, ws):
+            check(o[torch.from_numpy(good).cuda()], [x[good]], [w], steps)
+        if kind != "specials":
+            dws = [torch.full((k, d_out), float("nan"), dtype=torch.float32, device="cuda") for _ in xs]
+            heta.heta_project_wgrad_batch(hg, up, [dev_table(gout, "f32", 4) for _ in xs], dws, n_rows=n)
+            for o, x in zip(dws, xs):
+                check(o, [x.T], [gout], (n + 15) // 16)
+    finally:
+        hg.destroy()
