@@ -257,8 +257,8 @@ extern bool g_f32_native; // test switch, see heta_test_hooks.h
 // (trans = 1); zero beyond K and N.
 size_t split_weight_bytes(int64_t K, int64_t N);
 heta_status pack_split_weights(GemmParams &p, int trans, void *out, hipStream_t st);
-// whether the direct pipeline would give this launch its 64 x 64 tiles (too few 128 x 128 tiles to fill the chip)
-bool gemm_direct_small(const GemmParams &p);
+// whether an fp32 product is small enough to split both operands in its kernel instead of packing one beforehand
+bool f32_product_unpacked(const GemmParams &p);
 int wgrad_tile_rows(const GemmParams &p);
 heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, bool a_rc, bool b_rc, hipStream_t st,
                                const char *name, double bytes, double flops, bool *handled);

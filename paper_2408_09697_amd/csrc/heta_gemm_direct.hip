@@ -539,10 +539,10 @@ struct SplitSegs {
     int K[kMaxSeg], N[kMaxSeg], ko[kMaxSeg], n_pad[kMaxSeg];
     int n_seg, common;
 };
-__global__ void __launch_bounds__(512) pack_split_kernel(SplitSegs q, int trans)
+__global__ void __launch_bounds__(1024) pack_split_kernel(SplitSegs q, int trans)
 {
-    __shared__ float part[8][16];
-    __shared__ int los[8], his[8];
+    __shared__ float part[16][16];
+    __shared__ int los[16], his[16];
     __shared__ uint8_t row_exp[kLevelRows]; // biased exponent of every row's size, 0: a row of zeros
     const int s = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n_pad = q.n_pad[s], ko = q.ko[s];
@@ -554,7 +554,7 @@ __global__ void __launch_bounds__(512) pack_split_kernel(SplitSegs q, int trans)
         k_all = min(k_all + min(q.K[t], kLevelRows), 2 * kLevelRows);
     }
     // lanes along whatever is contiguous in W
-    const int c = trans ? tid / 32 : tid % 16, r = trans ? tid % 32 : tid / 16;
+    const int c = trans ? tid / 64 : tid % 16, r = trans ? lane : tid / 16;
     const int n = blockIdx.x * 16 + c;
     // the eight values of octet o of operand t in this thread's column
     auto load = [&](int t, int o, float x[8]) {
@@ -580,7 +580,7 @@ __global__ void __launch_bounds__(512) pack_split_kernel(SplitSegs q, int trans)
     load(s, min(r, ko - 1), own);
     int lo = 255, hi = 0;
     if (k_all <= kLevelRows) { // uniform
-        for (int i = tid; i < k_all; i += 512) {
+        for (int i = tid; i < k_all; i += 1024) {
             int t = t0, k = i;
             while (k >= q.K[t]) k -= q.K[t++];
             const float *W = q.W[t] + (trans ? k : k * q.ldw[t]);
@@ -602,15 +602,15 @@ __global__ void __launch_bounds__(512) pack_split_kernel(SplitSegs q, int trans)
     }
     m = largest(own);
     for (int t = t0; t < t1; ++t)
-        for (int o = t == s ? r + 32 : r; o < q.ko[t]; o += 32) {
+        for (int o = t == s ? r + 64 : r; o < q.ko[t]; o += 64) {
             float x[8];
             load(t, o, x);
             m = fmaxf(m, largest(x));
         }
     // maxima over the workgroup, per column; row sizes over everything
     auto column_max = [&](float v) {
-        for (int off = trans ? 1 : 16; off < (trans ? 32 : 64); off <<= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-        if (trans ? lane % 32 == 0 : lane < 16) part[trans ? 0 : wave][c] = v;
+        for (int off = trans ? 1 : 16; off < 64; off <<= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
+        if (trans ? lane == 0 : lane < 16) part[trans ? 0 : wave][c] = v;
     };
     column_max(m);
     for (int off = 1; off < 64; off <<= 1) {
@@ -622,7 +622,7 @@ __global__ void __launch_bounds__(512) pack_split_kernel(SplitSegs q, int trans)
         his[wave] = hi;
     }
     __syncthreads();
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < 16; ++i) {
         lo = min(lo, los[i]);
         hi = max(hi, his[i]);
     }
@@ -637,7 +637,7 @@ __global__ void __launch_bounds__(512) pack_split_kernel(SplitSegs q, int trans)
         m = 0.f;
         int base = 0;
         for (int t = t0; t < t1; ++t) {
-            for (int o = r; o < q.ko[t]; o += 32) {
+            for (int o = r; o < q.ko[t]; o += 64) {
                 float x[8];
                 load(t, o, x);
                 raise(t, base, o, x);
@@ -650,13 +650,13 @@ __global__ void __launch_bounds__(512) pack_split_kernel(SplitSegs q, int trans)
         __syncthreads();
     }
     m = 0.f;
-    for (int i = 0; i < (trans ? 1 : 8); ++i) m = fmaxf(m, part[i][c]);
+    for (int i = 0; i < (trans ? 1 : 16); ++i) m = fmaxf(m, part[i][c]);
     const int e = m > 0.f ? min(141 - static_cast<int>(__float_as_uint(m) >> 23 & 255u), 126) : 0;
     int *tail = reinterpret_cast<int *>(q.out[s] + 2 * static_cast<int64_t>(ko) * n_pad);
     if (r == 0) tail[n] = e;
     const float scale = ldexpf(1.f, e);
     const int64_t plane = static_cast<int64_t>(ko) * n_pad;
-    for (int o = r; o < ko; o += 32) {
+    for (int o = r; o < ko; o += 64) {
         TermFrag f;
         if (o == r) {
 #pragma unroll
@@ -674,7 +674,7 @@ __global__ void __launch_bounds__(512) pack_split_kernel(SplitSegs q, int trans)
     if (blockIdx.x == 0) {
         float *levels = reinterpret_cast<float *>(tail + n_pad);
         if (levelled)
-            for (int k = tid; k < 8 * ko; k += 512) levels[k] = k < q.K[s] ? ldexpf(1.f, row_level(k_own + k)) : 1.f;
+            for (int k = tid; k < 8 * ko; k += 1024) levels[k] = k < q.K[s] ? ldexpf(1.f, row_level(k_own + k)) : 1.f;
         if (tid == 0) levels[8 * ko] = levelled ? 1.f : 0.f;
     }
 }
@@ -1193,7 +1193,8 @@ static heta_status launch_direct(GemmParams &p, hipStream_t st, const char *name
 // test switch: fp32 products on the fp32 MFMA (32x32x2) instead of as three fp16 terms
 bool g_f32_native = false;
 
-bool gemm_direct_small(const GemmParams &p)
+// fewer than a hundred 128 x 128 tiles
+static bool gemm_direct_small(const GemmParams &p)
 {
     if (p.partial) return false;
     int64_t mt = 0, nt = 0;
@@ -1202,6 +1203,21 @@ bool gemm_direct_small(const GemmParams &p)
         nt = std::max(nt, (p.seg[s].N + 127) / 128);
     }
     return mt * nt * (p.batch ? p.n_seg : 1) <= 96;
+}
+
+// fp32 products (forward, input gradient) of too little work for packed weights: 64 x 64 tiles that split both operands.
+// The packing launch takes 6 us and packed tiles are four times as large, so the line lies where the work fills the chip
+// several times over: at about 28,000 (64 x 64 tile, 16 k-values) steps both take the same (48,000 x 128 x 256 31.7 us
+// packed and 31.9 not, 24,000 x 300 x 256 31.8 / 32.8, 96,000 x 64 x 256 41.5 / 40.2), below it the small tiles win
+// (12,000 x 128 x 128 17.9 / 11.2, three summed products of 24,000 x 128 x 64 32.3 / 18.2), above it packing does
+// (three of 96,000 x 128 x 256 91 / 134).
+bool f32_product_unpacked(const GemmParams &p)
+{
+    if (p.partial) return false;
+    double steps = 0;
+    for (int s = 0; s < p.n_seg; ++s)
+        steps += static_cast<double>((p.seg[s].M + 63) / 64) * static_cast<double>((p.seg[s].N + 63) / 64) * static_cast<double>((p.seg[s].K + 15) / 16);
+    return steps <= 24576;
 }
 
 static int64_t split_octets(int64_t K) { return (K + 15) / 16 * 2; }
@@ -1237,7 +1253,7 @@ heta_status pack_split_weights(GemmParams &p, int trans, void *out, hipStream_t 
     }
     q.n_seg = p.n_seg;
     q.common = !p.batch;
-    hipLaunchKernelGGL(pack_split_kernel, dim3((unsigned)(n_max / 16), p.n_seg), dim3(512), 0, st, q, trans);
+    hipLaunchKernelGGL(pack_split_kernel, dim3((unsigned)(n_max / 16), p.n_seg), dim3(1024), 0, st, q, trans);
     HETA_LAUNCH_CHECK("pack_split_kernel");
     return HETA_OK;
 }
@@ -1324,9 +1340,9 @@ heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, 
     // Fewer than a hundred 128 x 128 tiles (the projections of a sampled mini-batch block: a few thousand rows):
     // every tile is a serial chain of MFMAs on one CU while most CUs idle.  64 x 64 tiles (four wavefronts of one
     // accumulator each) cut the chain to a quarter and put four times as many CUs to work.
-    const bool small = gemm_direct_small(p);
+    const bool small = gemm_direct_small(p), unpacked = f32_product_unpacked(p);
     *handled = true;
-    if (a_dt == HETA_F32 && b_dt == HETA_F32 && !g_f32_native && !a_rc && !small && !p.partial) {
+    if (a_dt == HETA_F32 && b_dt == HETA_F32 && !g_f32_native && !a_rc && !unpacked && !p.partial) {
         // B already packed as two fp16 terms by the caller (the weights of a forward or input-gradient product):
         // half the splitting leaves the k loop.
         bool packed = true;
@@ -1360,9 +1376,19 @@ heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, 
         if (p.partial && a_rc && b_rc && n_max <= 64)
             return launch_direct<bf16_t, float, true, true, float, true, true, 1, 16, 3, 2, false, 2, 2, 2, 1>(p, st, name, bytes, flops);
         if (a_rc && b_rc) return launch_direct<bf16_t, float, true, true, float, true, true, 2, 16, 3, 3, false, 2, 2, 2, 1>(p, st, name, bytes, flops);
-#define HETA_TERMS(ARC, BRC)                                                                                                                       \
-    return small ? launch_direct<bf16_t, float, ARC, true, float, BRC, true, 2, 16, 3, 4, false, 1, 1, 2, kWideTerms>(p, st, name, bytes, flops) \
-                 : launch_direct<bf16_t, float, ARC, true, float, BRC, true, 2, 16, 3, 2, false, 2, 2, 2, kWideTerms>(p, st, name, bytes, flops)
+        int64_t tiles64 = 0;
+        for (int s = 0; s < p.n_seg; ++s) {
+            const int64_t tiles = ((p.seg[s].M + 63) / 64) * ((p.seg[s].N + 63) / 64);
+            tiles64 = p.batch ? tiles64 + tiles : std::max(tiles64, tiles);
+        }
+        // 64 x 64 tiles: up to two per CU the launch is one chain of k-steps, and 32 k-values per barrier shorten it
+        // (1,024 rows, K = 768, 256 columns 25.7 -> 21.9 us, 1,024 columns 25.1 -> 21.3); with more of them 16 let four
+        // workgroups share a CU (24,000 x 300 x 100 18.5 us, 19.8 with 32; its input gradient 21.9 and 25.5)
+        const bool chain = tiles64 <= 512;
+#define HETA_TERMS(ARC, BRC)                                                                                                                          \
+    return !unpacked ? launch_direct<bf16_t, float, ARC, true, float, BRC, true, 2, 16, 3, 2, false, 2, 2, 2, kWideTerms>(p, st, name, bytes, flops) \
+           : chain   ? launch_direct<bf16_t, float, ARC, true, float, BRC, true, 2, 32, 3, 3, false, 1, 1, 2, kWideTerms>(p, st, name, bytes, flops) \
+                     : launch_direct<bf16_t, float, ARC, true, float, BRC, true, 2, 16, 3, 4, false, 1, 1, 2, kWideTerms>(p, st, name, bytes, flops)
         if (!a_rc && b_rc) { HETA_TERMS(false, true); }
         if (!a_rc && !b_rc) { HETA_TERMS(false, false); }
 #undef HETA_TERMS

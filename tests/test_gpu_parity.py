@@ -1204,12 +1204,14 @@ def test_graphs_created_in_one_batch_equal_graphs_created_one_by_one(mode, on_de
 
 
 @pytest.mark.parametrize("kind", ["growing", "late", "compensated", "specials"])
-@pytest.mark.parametrize("n,k,d_out,trans,segments", [(300, 70, 40, False, 1), (12900, 100, 64, True, 2), (17001, 72, 130, False, 3), (33001, 129, 256, True, 1), (20000, 20, 100, False, 2)])
+@pytest.mark.parametrize("n,k,d_out,trans,segments", [(300, 70, 40, False, 1), (33001, 129, 256, True, 1), (120001, 100, 64, True, 2), (70001, 72, 130, False, 3), (50001, 129, 256, True, 1),
+                                                      (200003, 20, 100, False, 2)])
 def test_f32_products_over_a_wide_range(n, k, d_out, trans, segments, kind):
     """fp32 products are fed as fp16 terms scaled by a power of two per row and column.  growing: every 16 columns (and
     every 16 rows, for the weight gradient) 2^6 larger than those before, so that scales are set anew all along; late: rows
     that start with zeros; compensated: features spread over 2^40 (small launches: 2^24) whose weights make up for it;
-    specials: rows with an infinity or a NaN, which stay alone.  Small launches, tiles of 64, 128 and 256 columns, sums and independent products.
+    specials: rows with an infinity or a NaN, which stay alone.  Launches on both sides of 24,576
+    steps of 64 x 64 x 16 and of 512 tiles, packed tiles of 64, 128 and 256 columns, sums and independent products.
 
     Bound per element, in units of 2^-24 sum |a b|: one for each operand's representation, one for the term left out, and
     two for each of the 3 ceil(K / 16) additions to the accumulator."""
@@ -1225,7 +1227,7 @@ def test_f32_products_over_a_wide_range(n, k, d_out, trans, segments, kind):
             x[:, : k // 2] *= (np.arange(n)[:, None] % 3 == 0)
             x[n // 3: n // 2] = 0.0
         if kind == "compensated":
-            span = 20.0 if n > 96 * 128 else 12.0  # packed weights are levelled; small launches have the range of their terms
+            span = 20.0 if n > 40000 else 12.0  # packed weights are levelled; small launches have the range of their terms
             r = np.exp2(np.linspace(-span, span, k)[g.permutation(k)]).astype(np.float32)
             x *= r
             w /= r[:, None]
