@@ -585,44 +585,56 @@ __device__ __forceinline__ void agg_wave_body(const AggParams &p, const unsigned
 }
 
 // ---- hub rows: add the chunk partials in chunk order -------------------------------------------------
-// One workgroup of 16 wavefronts per (hub row, tile of 256 columns); wavefront w adds the partials
-// w, w+16, w+32, ... (four loads in flight) and the sixteen sums are combined through LDS in
-// wavefront order, so the summation order is fixed.
-constexpr int kCombineWaves = 16;
-__device__ __forceinline__ void agg_hub_combine_body(const AggParams &p)
+// One workgroup of 4 wavefronts per (hub row, tile of 4 LPC columns); lane group g of wavefront w (LPC lanes) adds the
+// partials q, q + Q, q + 2 Q, ... with q = w + 4 g, Q the number of lane groups (sixteen loads in flight); the groups' sums
+// are combined by shuffles and the wavefronts' through LDS in wavefront order, so the summation order is fixed.
+// A power-law relation has one hub of up to millions of edges, thousands of partials, and the launch takes as long as
+// that row takes the CUs its tiles are on; the other rows have a few partials each, so the workgroups are small.
+// LPC = 8 (32 columns) unless a dot over wider heads needs the head in one tile.  (16 wavefronts and 256 columns per
+// workgroup: relations of 4 M edges, 467 hub rows of 256 columns 85 us, four of 128 columns in one launch 64; now 27 and
+// 32.  16 wavefronts and 64 columns: 37 and 45, and 26 us instead of 18 on 787 rows of a few partials each.)
+constexpr int kCombineWaves = 4;
+template <int LPC> __device__ __forceinline__ void agg_hub_combine_body(const AggParams &p, int tiles)
 {
-    __shared__ float4 part[kCombineWaves][64];
+    constexpr int G = 64 / LPC, Q = kCombineWaves * G, U = 16;
+    __shared__ float4 part[kCombineWaves][LPC];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t h = blockIdx.x;
+    const int l = lane % LPC, g = lane / LPC;
+    const int64_t h = blockIdx.x / tiles; // the tiles of a row are neighbours: all of the largest row, which is first, start at once
     if (h >= p.n_hub_rows) return; // whole workgroup (a launch over several relations is as wide as the widest)
     const int64_t row = p.hub_only ? h : p.perm[h];
     const int64_t s0 = p.hub_chunk_ptr[h], s1 = p.hub_chunk_ptr[h + 1];
-    const int col0 = (blockIdx.y * 64 + lane) * 4;
+    const int col0 = (static_cast<int>(blockIdx.x % tiles) * LPC + l) * 4;
     float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
     if (col0 < p.ws_ld) {
-        for (int64_t s = s0 + wave; s < s1; s += 4 * kCombineWaves) {
-            float4 v[4];
+        for (int64_t s = s0 + wave + kCombineWaves * g; s < s1; s += U * Q) {
+            float4 v[U];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int64_t t = s + kCombineWaves * u;
+            for (int u = 0; u < U; ++u) {
+                const int64_t t = s + Q * u;
                 if (t < s1) v[u] = *reinterpret_cast<const float4 *>(p.ws + t * p.ws_stride + col0);
                 else v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) { a.x += v[u].x; a.y += v[u].y; a.z += v[u].z; a.w += v[u].w; }
+            for (int u = 0; u < U; ++u) { a.x += v[u].x; a.y += v[u].y; a.z += v[u].z; a.w += v[u].w; }
         }
     }
-    part[wave][lane] = a;
+#pragma unroll
+    for (int off = LPC; off < 64; off <<= 1) {
+        a.x += __shfl_xor(a.x, off, 64); a.y += __shfl_xor(a.y, off, 64);
+        a.z += __shfl_xor(a.z, off, 64); a.w += __shfl_xor(a.w, off, 64);
+    }
+    if (g == 0) part[wave][l] = a;
     __syncthreads();
-    if (wave != 0 || (col0 >= p.d && !p.combine_dot)) return;
+    if (wave != 0 || g != 0 || (col0 >= p.d && !p.combine_dot)) return;
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int k = 0; k < kCombineWaves; ++k) {
-        const float4 v = part[k][lane];
+        const float4 v = part[k][l];
         acc[0] += v.x; acc[1] += v.y; acc[2] += v.z; acc[3] += v.w;
     }
     const float scale = row_scale(p, p.sptr[h + 1] - p.sptr[h]);
-    if (p.combine_dot) dot_store<4>(p, row, col0, acc, scale, lane); // all 64 lanes of wavefront 0 (one 256-column tile)
+    if (p.combine_dot) dot_store<4>(p, row, col0, acc, scale, l); // all lanes of the tile
     else store_out<4>(p, row, col0, acc, scale);
 }
 
@@ -640,7 +652,7 @@ template <typename T, int EPC, int L, int CPL, bool DUAL>
 __global__ void __launch_bounds__(256) agg_batch_kernel(AggParams p) { agg_batch_body<T, EPC, L, CPL, DUAL>(p); }
 template <typename T, int EPC, int L, int CPL, bool DUAL>
 __global__ void __launch_bounds__(256) agg_wave_kernel(AggParams p) { agg_wave_body<T, EPC, L, CPL, DUAL>(p); }
-__global__ void __launch_bounds__(64 * kCombineWaves) agg_hub_combine_kernel(AggParams p) { agg_hub_combine_body(p); }
+template <int LPC> __global__ void __launch_bounds__(64 * kCombineWaves) agg_hub_combine_kernel(AggParams p, int tiles) { agg_hub_combine_body<LPC>(p, tiles); }
 
 template <typename T, int EPC, int L, int CPL, bool DUAL>
 __global__ void __launch_bounds__(256) agg_batch_multi_kernel(AggMulti m) { agg_batch_body<T, EPC, L, CPL, DUAL>(m.p[blockIdx.z]); }
@@ -650,7 +662,7 @@ template <typename T, int EPC, int L, int CPL, bool DUAL>
 __global__ void __launch_bounds__(256) agg_wave_split_kernel(AggParams p) { agg_wave_body<T, EPC, L, CPL, DUAL, true>(p); }
 template <typename T, int EPC, int L, int CPL, bool DUAL>
 __global__ void __launch_bounds__(256) agg_wave_split_multi_kernel(AggMulti m) { agg_wave_body<T, EPC, L, CPL, DUAL, true>(m.p[blockIdx.z]); }
-__global__ void __launch_bounds__(64 * kCombineWaves) agg_hub_combine_multi_kernel(AggMulti m) { agg_hub_combine_body(m.p[blockIdx.z]); }
+__global__ void __launch_bounds__(64 * kCombineWaves) agg_hub_combine_multi_kernel(AggMulti m, int tiles) { agg_hub_combine_body<8>(m.p[blockIdx.y], tiles); }
 // Both row classes of a small launch in one grid: the first `wave_blocks` workgroups along x walk the split long rows,
 // the rest the batches of short rows.  A sampled block has a handful of long rows; as a launch of their own they
 // keep a few CUs busy for a serial walk of several hundred edges while the rest of the chip waits for the next kernel.
@@ -851,10 +863,13 @@ static heta_status launch_plans(const AggPlan *plans, int n, hipStream_t st, boo
         e = f.vec ? launch_vec<bf16_t, 8>(ps, n, f.n_chunks, st, cost) : launch_pair<bf16_t, 1, 64, 2>(ps, n, (f.n_chunks + 127) / 128, st, cost);
     if (e != HETA_OK) return e;
     if (hub_rows > 0) {
-        const int tiles = static_cast<int>((f.p.ws_ld + 255) / 256);
+        const int tiles = static_cast<int>((f.p.ws_ld + 31) / 32);
+        if (hub_rows * tiles > max_blocks(64 * kCombineWaves)) return fail(HETA_ERR_UNSUPPORTED, "aggregate: too many hub rows");
+        const dim3 threads(64 * kCombineWaves);
+        auto blocks = [&](int t) { return static_cast<unsigned>(hub_rows * t); };
         ProfScope prof(timed ? "agg_hub_combine_kernel" : nullptr, st, hub_bytes, 0);
         if (n == 1) {
-            hipLaunchKernelGGL(agg_hub_combine_kernel, dim3((unsigned)hub_rows, tiles), dim3(64 * kCombineWaves), 0, st, ps[0]);
+            hipLaunchKernelGGL(agg_hub_combine_kernel<8>, dim3(blocks(tiles)), threads, 0, st, ps[0], tiles);
             HETA_LAUNCH_CHECK("agg_hub_combine_kernel");
             if (f.dual) {
                 AggParams p2 = ps[0];
@@ -862,13 +877,16 @@ static heta_status launch_plans(const AggPlan *plans, int n, hipStream_t st, boo
                 p2.out = ps[0].out2;
                 p2.ld_out = ps[0].ld_out2;
                 p2.combine_dot = ps[0].dot_out ? 1 : 0;
-                hipLaunchKernelGGL(agg_hub_combine_kernel, dim3((unsigned)hub_rows, tiles), dim3(64 * kCombineWaves), 0, st, p2);
+                const int wide = p2.combine_dot ? p2.head_dim : 0; // the plan's dot form has at most 256 columns
+                if (wide > 64) hipLaunchKernelGGL(agg_hub_combine_kernel<64>, dim3(blocks(1)), threads, 0, st, p2, 1);
+                else if (wide > 32) hipLaunchKernelGGL(agg_hub_combine_kernel<16>, dim3(blocks((tiles + 1) / 2)), threads, 0, st, p2, (tiles + 1) / 2);
+                else hipLaunchKernelGGL(agg_hub_combine_kernel<8>, dim3(blocks(tiles)), threads, 0, st, p2, tiles);
                 HETA_LAUNCH_CHECK("agg_hub_combine_kernel");
             }
         } else {
             AggMulti m{};
             for (int i = 0; i < n; ++i) m.p[i] = ps[i];
-            hipLaunchKernelGGL(agg_hub_combine_multi_kernel, dim3((unsigned)hub_rows, tiles, n), dim3(64 * kCombineWaves), 0, st, m);
+            hipLaunchKernelGGL(agg_hub_combine_multi_kernel, dim3(blocks(tiles), n), threads, 0, st, m, tiles);
             HETA_LAUNCH_CHECK("agg_hub_combine_kernel");
         }
     }
