@@ -63,7 +63,7 @@ struct AggParams {
     int64_t ld_out2;
     int mean;              // divide the row sum by the row's degree
     int hub_only;          // reduce the hub rows only, into out[h] for the h-th hub row of the schedule
-    int wave_split;        // few long rows / hub chunks: four wavefronts per item (agg_wave_split_kernel)
+    int wave_split;        // few long rows / hub chunks: four wavefronts per item (SPLIT of agg_wave_body)
     // With slot_w2, instead of storing the second sum: dot_out[row, k] = <second sum of head k, dot_z[row, head k]> -
     // dot_corr[row, k] (the attention backward needs only this dot of the gate-weighted sum, not the sum itself).
     const void *dot_z;     // nullable; rows indexed like out, ld_z elements apart, fp32 or bf16 (dot_z_bf16)
@@ -71,7 +71,6 @@ struct AggParams {
     int dot_z_bf16;
     const float *dot_corr; // nullable
     float *dot_out;        // [n_rows][heads]
-    int combine_dot;       // set on the hub combine launch that finishes dot_out
     void *out;
     int64_t ld_out;
     int out_bf16;
@@ -278,9 +277,14 @@ __host__ __device__ inline int batch_rows(int k, int G)
     return r < 64 ? r : 64;
 }
 
-template <typename T, int EPC, int L, int CPL, bool DUAL>
-__device__ __forceinline__ void agg_batch_body(const AggParams &p, const unsigned bx = blockIdx.x)
+// How the gathered rows are weighted: not at all or by a weight per neighbour id (edge_w; looked up when a row is added,
+// so that a row in flight holds no weight register), by a weight per slot and head, or by two of those into two sums.
+enum AggMode { AGG_PLAIN, AGG_SLOT, AGG_DUAL };
+
+template <typename T, int EPC, int L, int CPL, int MODE>
+__device__ __forceinline__ void agg_batch_body(const AggParams &p, const unsigned bx)
 {
+    constexpr bool DUAL = MODE == AGG_DUAL, SLOT = MODE != AGG_PLAIN;
     constexpr int G = 64 / L;          // lane groups = rows in progress per wavefront
     constexpr int U = CPL == 1 ? 8 : 4; // row loads in flight per lane group
     __shared__ int32_t ids_s[4][kBatchIds];
@@ -345,10 +349,9 @@ __device__ __forceinline__ void agg_batch_body(const AggParams &p, const unsigne
         return;
     }
     const float scale = p.mean ? 1.f / static_cast<float>(k) : 1.f;
-    const bool weighted = p.edge_w || p.slot_w;
     int head[CPL]; // head of each of this lane's chunks (per-head edge weights)
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) head[c] = p.slot_w ? min((ch0 + c * L) * EPC / p.head_dim, p.heads - 1) : 0;
+    for (int c = 0; c < CPL; ++c) head[c] = SLOT ? min((ch0 + c * L) * EPC / p.head_dim, p.heads - 1) : 0;
     float acc[CPL][EPC], acc2[DUAL ? CPL : 1][EPC];
 #pragma unroll
     for (int c = 0; c < CPL; ++c)
@@ -364,7 +367,7 @@ __device__ __forceinline__ void agg_batch_body(const AggParams &p, const unsigne
     const int total = rounds * k;
     for (int s0 = 0; s0 < total; s0 += U) {
         Chunk<T, EPC> v[U][CPL];
-        float ww[U][CPL], ww2[DUAL ? U : 1][CPL];
+        float ww[SLOT ? U : 1][CPL], ww2[DUAL ? U : 1][CPL];
         int rl_u = rl, j_u = j;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -376,13 +379,13 @@ __device__ __forceinline__ void agg_batch_body(const AggParams &p, const unsigne
 #pragma unroll
             for (int c = 0; c < CPL; ++c) {
                 const int ch = ch0 + c * L;
-                ww[u][c] = p.edge_w ? w_s[wave][i] : 1.f;
                 if (ok && ch < n_chunks) {
                     v[u][c].load(rp + static_cast<int64_t>(ch) * EPC);
-                    if (p.slot_w) ww[u][c] = p.slot_w[(e0 + i) * p.heads + head[c]];
+                    if (SLOT) ww[u][c] = p.slot_w[(e0 + i) * p.heads + head[c]];
                     if (DUAL) ww2[u][c] = p.slot_w2[(e0 + i) * p.heads + head[c]];
                 } else {
                     v[u][c].zero();
+                    if (SLOT) ww[u][c] = 0.f;
                     if (DUAL) ww2[u][c] = 0.f;
                 }
             }
@@ -394,9 +397,12 @@ __device__ __forceinline__ void agg_batch_body(const AggParams &p, const unsigne
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (s0 + u < total) {
+                float we = 1.f;
+                if (!SLOT && p.edge_w) we = w_s[wave][g + rl * G < nrows ? (g + rl * G) * k + j : 0];
 #pragma unroll
                 for (int c = 0; c < CPL; ++c) {
-                    if (weighted) v[u][c].add_to(acc[c], ww[u][c]);
+                    if (SLOT) v[u][c].add_to(acc[c], ww[u][c]);
+                    else if (p.edge_w) v[u][c].add_to(acc[c], we);
                     else v[u][c].add_to(acc[c]);
                     if (DUAL) v[u][c].add_to(acc2[c], ww2[u][c]);
                 }
@@ -436,11 +442,12 @@ __device__ __forceinline__ void agg_batch_body(const AggParams &p, const unsigne
 // ...; their sums are added through LDS in wavefront order.  For launches of few items (the long rows of a
 // sampled block), where one wavefront per item leaves most of the chip idle behind a serial walk of up to 511
 // edges.
-template <typename T, int EPC, int L, int CPL, bool DUAL, bool SPLIT = false>
-__device__ __forceinline__ void agg_wave_body(const AggParams &p, const unsigned bx = blockIdx.x)
+template <typename T, int EPC, int L, int CPL, int MODE, bool SPLIT>
+__device__ __forceinline__ void agg_wave_body(const AggParams &p, const unsigned bx)
 {
+    constexpr bool DUAL = MODE == AGG_DUAL, SLOT = MODE != AGG_PLAIN;
     constexpr int G = 64 / L;            // lane groups per wavefront
-    constexpr int U = CPL == 2 ? 4 : ((G >= 16) ? 1 : ((G >= 8) ? 2 : ((G >= 4) ? 4 : 8))); // edges in flight per group and step
+    constexpr int U = G >= 16 ? 1 : G >= 8 ? 2 : G >= 4 || SLOT || EPC == 8 ? 4 : 8; // edges in flight per group and step
     constexpr int NACC = CPL * EPC * (DUAL ? 2 : 1);
     __shared__ float part_s[SPLIT ? 3 : 1][SPLIT ? NACC : 1][SPLIT ? L : 1]; // wavefronts 1..3, one value per (sum element, lane of group 0)
     const int lane = threadIdx.x & 63;
@@ -464,10 +471,9 @@ __device__ __forceinline__ void agg_wave_body(const AggParams &p, const unsigned
     const int n_chunks = (p.d + EPC - 1) / EPC;
     const int ch0 = blockIdx.y * (L * CPL) + l;
     const T *table = static_cast<const T *>(p.table);
-    const bool weighted = p.edge_w || p.slot_w;
     int head[CPL];
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) head[c] = p.slot_w ? min((ch0 + c * L) * EPC / p.head_dim, p.heads - 1) : 0;
+    for (int c = 0; c < CPL; ++c) head[c] = SLOT ? min((ch0 + c * L) * EPC / p.head_dim, p.heads - 1) : 0;
     float acc[CPL][EPC], acc2[DUAL ? CPL : 1][EPC];
 #pragma unroll
     for (int c = 0; c < CPL; ++c)
@@ -488,36 +494,38 @@ __device__ __forceinline__ void agg_wave_body(const AggParams &p, const unsigned
         }
         for (int j = 0; j < cnt; j += G * U) {
             Chunk<T, EPC> v[U][CPL];
-            float ww[U][CPL], ww2[DUAL ? U : 1][CPL];
+            float ww[SLOT ? U : 1][CPL], ww2[DUAL ? U : 1][CPL];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int k = j + u * G + g;
                 const bool ok = k < cnt;
                 const int r = __shfl(rid, k & 63, 64);
-                const float wn = __shfl(wv, k & 63, 64);
                 const T *rp = table + static_cast<int64_t>(r) * p.ld;
 #pragma unroll
                 for (int c = 0; c < CPL; ++c) {
                     const int ch = ch0 + c * L;
-                    ww[u][c] = wn;
                     if (ok && ch < n_chunks) {
                         v[u][c].load(rp + static_cast<int64_t>(ch) * EPC);
-                        if (p.slot_w) ww[u][c] = p.slot_w[(base + k) * p.heads + head[c]];
+                        if (SLOT) ww[u][c] = p.slot_w[(base + k) * p.heads + head[c]];
                         if (DUAL) ww2[u][c] = p.slot_w2[(base + k) * p.heads + head[c]];
                     } else {
                         v[u][c].zero();
+                        if (SLOT) ww[u][c] = 0.f;
                         if (DUAL) ww2[u][c] = 0.f;
                     }
                 }
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u)
+            for (int u = 0; u < U; ++u) {
+                const float we = !SLOT && p.edge_w ? __shfl(wv, (j + u * G + g) & 63, 64) : 1.f;
 #pragma unroll
                 for (int c = 0; c < CPL; ++c) {
-                    if (weighted) v[u][c].add_to(acc[c], ww[u][c]);
+                    if (SLOT) v[u][c].add_to(acc[c], ww[u][c]);
+                    else if (p.edge_w) v[u][c].add_to(acc[c], we);
                     else v[u][c].add_to(acc[c]);
                     if (DUAL) v[u][c].add_to(acc2[c], ww2[u][c]);
                 }
+            }
         }
     }
     // combine the lane groups (fixed butterfly order)
@@ -594,7 +602,7 @@ __device__ __forceinline__ void agg_wave_body(const AggParams &p, const unsigned
 // workgroup: relations of 4 M edges, 467 hub rows of 256 columns 85 us, four of 128 columns in one launch 64; now 27 and
 // 32.  16 wavefronts and 64 columns: 37 and 45, and 26 us instead of 18 on 787 rows of a few partials each.)
 constexpr int kCombineWaves = 4;
-template <int LPC> __device__ __forceinline__ void agg_hub_combine_body(const AggParams &p, int tiles)
+template <int LPC> __device__ __forceinline__ void agg_hub_combine_body(const AggParams &p, int tiles, bool second)
 {
     constexpr int G = 64 / LPC, Q = kCombineWaves * G, U = 16;
     __shared__ float4 part[kCombineWaves][LPC];
@@ -605,6 +613,8 @@ template <int LPC> __device__ __forceinline__ void agg_hub_combine_body(const Ag
     const int64_t row = p.hub_only ? h : p.perm[h];
     const int64_t s0 = p.hub_chunk_ptr[h], s1 = p.hub_chunk_ptr[h + 1];
     const int col0 = (static_cast<int>(blockIdx.x % tiles) * LPC + l) * 4;
+    const float *ws = p.ws + (second ? p.ws_ld : 0);
+    const bool dot = second && p.dot_out;
     float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
     if (col0 < p.ws_ld) {
         for (int64_t s = s0 + wave + kCombineWaves * g; s < s1; s += U * Q) {
@@ -612,7 +622,7 @@ template <int LPC> __device__ __forceinline__ void agg_hub_combine_body(const Ag
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int64_t t = s + Q * u;
-                if (t < s1) v[u] = *reinterpret_cast<const float4 *>(p.ws + t * p.ws_stride + col0);
+                if (t < s1) v[u] = *reinterpret_cast<const float4 *>(ws + t * p.ws_stride + col0);
                 else v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
             }
 #pragma unroll
@@ -626,7 +636,7 @@ template <int LPC> __device__ __forceinline__ void agg_hub_combine_body(const Ag
     }
     if (g == 0) part[wave][l] = a;
     __syncthreads();
-    if (wave != 0 || g != 0 || (col0 >= p.d && !p.combine_dot)) return;
+    if (wave != 0 || g != 0 || (col0 >= p.d && !dot)) return;
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int k = 0; k < kCombineWaves; ++k) {
@@ -634,120 +644,130 @@ template <int LPC> __device__ __forceinline__ void agg_hub_combine_body(const Ag
         acc[0] += v.x; acc[1] += v.y; acc[2] += v.z; acc[3] += v.w;
     }
     const float scale = row_scale(p, p.sptr[h + 1] - p.sptr[h]);
-    if (p.combine_dot) dot_store<4>(p, row, col0, acc, scale, l); // all lanes of the tile
+    if (dot) dot_store<4>(p, row, col0, acc, scale, l); // all lanes of the tile
+    else if (second) store_out<4>(p, p.out2, p.ld_out2, row, col0, acc, scale);
     else store_out<4>(p, row, col0, acc, scale);
 }
 
-// The kernels proper.  The single-relation forms take the parameters of their relation; the multi forms
-// take up to kAggMulti parameter blocks and blockIdx.z picks one, so that the small relations of a
-// sampled mini-batch block share one launch (and one launch latency) instead of queueing behind each
-// other.  Every body guards its own item count, so a grid as wide as the widest relation is safe.
+// All rows of up to N relations in one grid: first the sections of long rows and hub chunks, relation after relation, so
+// that the longest walks start first, then the sections of short rows.  Which section a workgroup belongs to follows from
+// its index (uniform); no workgroup is left without work for being in a launch as wide as the widest relation.
+// A launch of its own for every row class of every relation pays its ramp and its last, half-empty wave each time.
+// What bounds it is the number of rows in flight: random rows arrive at 5 - 6.5 TB/s whether or not the table fits the
+// 256 MB cache, and 4 M edges of 512 bytes take 289 us with 8 wavefronts per SIMD, 295 with 6 and 341 with 5 (8 row
+// loads each).  So the registers are bounded for 8 (bf16: 7); the weights, which have their own kernels, need more.
+// Against two launches per relation with 6 and 4 wavefronts per SIMD (bf16: 4 and 6) and lane groups of 64 for wide
+// rows: one layer of 21 M edges 7.21 -> 7.01 ms (bf16 4.70 -> 4.54), of 2.1 M edges and 64 columns 763 -> 711 us,
+// forward over seven widths 1.27 -> 1.17 ms, R-GAT layer of 21 M edges 22.1 -> 21.2 ms, of 2.1 M edges 1.64 -> 1.55 ms.
 constexpr int kAggMulti = 4;
-struct AggMulti {
-    AggParams p[kAggMulti];
+template <int N> struct AggLaunch {
+    AggParams p[N];
+    unsigned first[2 * N]; // first workgroup of section s: wave items of relation s, or short rows of relation s - N
 };
-static_assert(sizeof(AggMulti) <= 3584, "kernel arguments are limited to 4 KB");
+static_assert(sizeof(AggLaunch<kAggMulti>) <= 3840, "kernel arguments are limited to 4 KB");
 
-template <typename T, int EPC, int L, int CPL, bool DUAL>
-__global__ void __launch_bounds__(256) agg_batch_kernel(AggParams p) { agg_batch_body<T, EPC, L, CPL, DUAL>(p); }
-template <typename T, int EPC, int L, int CPL, bool DUAL>
-__global__ void __launch_bounds__(256) agg_wave_kernel(AggParams p) { agg_wave_body<T, EPC, L, CPL, DUAL>(p); }
-template <int LPC> __global__ void __launch_bounds__(64 * kCombineWaves) agg_hub_combine_kernel(AggParams p, int tiles) { agg_hub_combine_body<LPC>(p, tiles); }
-
-template <typename T, int EPC, int L, int CPL, bool DUAL>
-__global__ void __launch_bounds__(256) agg_batch_multi_kernel(AggMulti m) { agg_batch_body<T, EPC, L, CPL, DUAL>(m.p[blockIdx.z]); }
-template <typename T, int EPC, int L, int CPL, bool DUAL>
-__global__ void __launch_bounds__(256) agg_wave_multi_kernel(AggMulti m) { agg_wave_body<T, EPC, L, CPL, DUAL>(m.p[blockIdx.z]); }
-template <typename T, int EPC, int L, int CPL, bool DUAL>
-__global__ void __launch_bounds__(256) agg_wave_split_kernel(AggParams p) { agg_wave_body<T, EPC, L, CPL, DUAL, true>(p); }
-template <typename T, int EPC, int L, int CPL, bool DUAL>
-__global__ void __launch_bounds__(256) agg_wave_split_multi_kernel(AggMulti m) { agg_wave_body<T, EPC, L, CPL, DUAL, true>(m.p[blockIdx.z]); }
-__global__ void __launch_bounds__(64 * kCombineWaves) agg_hub_combine_multi_kernel(AggMulti m, int tiles) { agg_hub_combine_body<8>(m.p[blockIdx.y], tiles); }
-// Both row classes of a small launch in one grid: the first `wave_blocks` workgroups along x walk the split long rows,
-// the rest the batches of short rows.  A sampled block has a handful of long rows; as a launch of their own they
-// keep a few CUs busy for a serial walk of several hundred edges while the rest of the chip waits for the next kernel.
-template <typename T, int EPC, int L, int CPL, bool DUAL>
-__global__ void __launch_bounds__(256) agg_pair_kernel(AggParams p, unsigned wave_blocks)
+template <typename T, int EPC, int L, int CPL, int MODE, int N>
+__global__ void __launch_bounds__(256, MODE != AGG_PLAIN ? 4 : EPC == 8 ? 7 : 8) agg_rows_kernel(AggLaunch<N> m)
 {
-    if (blockIdx.x < wave_blocks) agg_wave_body<T, EPC, L, CPL, DUAL, true>(p, blockIdx.x);
-    else agg_batch_body<T, EPC, L, CPL, DUAL>(p, blockIdx.x - wave_blocks);
+    int s = 0;
+#pragma unroll
+    for (int i = 1; i < 2 * N; ++i) s += blockIdx.x >= m.first[i] ? 1 : 0;
+    const unsigned bx = blockIdx.x - m.first[s];
+    const AggParams &p = m.p[s % N];
+    if (s >= N) agg_batch_body<T, EPC, L, CPL, MODE>(p, bx);
+    else if (p.wave_split) agg_wave_body<T, EPC, L, CPL, MODE, true>(p, bx);
+    else agg_wave_body<T, EPC, L, CPL, MODE, false>(p, bx);
 }
-template <typename T, int EPC, int L, int CPL, bool DUAL>
-__global__ void __launch_bounds__(256) agg_pair_multi_kernel(AggMulti m, unsigned wave_blocks)
+// Hub rows of up to N relations: blockIdx.y is the relation, or with second sums 2 * relation + (1 for the second).
+template <int LPC, int N> __global__ void __launch_bounds__(64 * kCombineWaves) agg_hub_combine_kernel(AggLaunch<N> m, int tiles, int dual)
 {
-    if (blockIdx.x < wave_blocks) agg_wave_body<T, EPC, L, CPL, DUAL, true>(m.p[blockIdx.z], blockIdx.x);
-    else agg_batch_body<T, EPC, L, CPL, DUAL>(m.p[blockIdx.z], blockIdx.x - wave_blocks);
+    agg_hub_combine_body<LPC>(m.p[dual ? blockIdx.y >> 1 : blockIdx.y], tiles, dual && (blockIdx.y & 1));
 }
 
 // ---- launch ---------------------------------------------------------------------------------------
-constexpr int64_t kPairWaveBlocks = 256; // split long rows up to which both row classes share a launch
-// algorithmic bytes of the two row classes of one call (for the optional profiler)
+constexpr int64_t kMaxSectionBlocks = max_blocks(256) - 256;
+// algorithmic bytes of one call (for the optional profiler)
 struct AggCost {
-    double wave_bytes = 0, group_bytes = 0;
+    double bytes = 0;
     bool timed = true; // false: no event brackets (the entry point that must not allocate)
 };
 
-template <typename T, int EPC, int L, int CPL, bool DUAL = false>
-static heta_status launch_pair(const AggParams *ps, int n, int n_super, hipStream_t st, const AggCost &cost)
+template <typename T, int EPC, int L, int CPL, int MODE, int N>
+static heta_status launch_sections(const AggParams *ps, const int64_t *blocks, int n, int n_super, hipStream_t st, const AggCost &cost)
 {
-    if constexpr (!DUAL && EPC > 1) { // the two-weight form exists for the 128-bit paths
-        if (ps[0].slot_w2) return launch_pair<T, EPC, L, CPL, true>(ps, n, n_super, st, cost);
+    AggLaunch<N> m{};
+    int64_t total = 0;
+    for (int i = 0; i < N; ++i) m.p[i] = ps[i < n ? i : 0];
+    for (int s = 0; s < 2 * N; ++s) {
+        m.first[s] = static_cast<unsigned>(total);
+        if (s % N < n) total += blocks[s / N * n + s % N];
     }
-    const bool split = ps[0].wave_split != 0; // the same for every item of a launch (part of the plan's key)
-    int64_t wave_blocks = 0, batch_blocks = 0;
+    if (total == 0) return HETA_OK;
+    ProfScope prof(cost.timed ? "agg_rows_kernel" : nullptr, st, cost.bytes, 0);
+    hipLaunchKernelGGL((agg_rows_kernel<T, EPC, L, CPL, MODE, N>), dim3((unsigned)total, n_super), dim3(256), 0, st, m);
+    HETA_LAUNCH_CHECK("agg_rows_kernel");
+    return HETA_OK;
+}
+
+template <typename T, int EPC, int L, int CPL, int MODE>
+static heta_status launch_mode(const AggParams *ps, int n, int n_super, hipStream_t st, const AggCost &cost)
+{
+    int64_t blocks[2 * kAggMulti], total = 0; // long rows and hub chunks of each relation, then short rows of each
     for (int i = 0; i < n; ++i) {
-        wave_blocks = std::max<int64_t>(wave_blocks, split ? ps[i].n_wave_items : (ps[i].n_wave_items + 3) / 4);
-        batch_blocks = std::max<int64_t>(batch_blocks, (ps[i].batch0[kShortDeg] + 3) / 4);
+        blocks[i] = ps[i].wave_split ? ps[i].n_wave_items : (ps[i].n_wave_items + 3) / 4;
+        blocks[n + i] = (ps[i].batch0[kShortDeg] + 3) / 4;
+        if (blocks[i] > kMaxSectionBlocks) return fail(HETA_ERR_UNSUPPORTED, "aggregate: too many long rows");
+        if (blocks[n + i] > kMaxSectionBlocks) return fail(HETA_ERR_UNSUPPORTED, "aggregate: too many short rows");
+        total += blocks[i] + blocks[n + i];
     }
-    if (wave_blocks > max_blocks(256) - kPairWaveBlocks) return fail(HETA_ERR_UNSUPPORTED, "aggregate: too many long rows");
-    if (batch_blocks > max_blocks(256) - kPairWaveBlocks) return fail(HETA_ERR_UNSUPPORTED, "aggregate: too many short rows");
-    AggMulti m{};
-    if (n > 1)
-        for (int i = 0; i < n; ++i) m.p[i] = ps[i];
-    if (split && wave_blocks > 0 && wave_blocks <= kPairWaveBlocks && batch_blocks > 0) {
-        ProfScope prof(cost.timed ? "agg_batch_kernel" : nullptr, st, cost.wave_bytes + cost.group_bytes, 0);
-        const unsigned blocks = static_cast<unsigned>(wave_blocks + batch_blocks);
-        if (n == 1)
-            hipLaunchKernelGGL((agg_pair_kernel<T, EPC, L, CPL, DUAL>), dim3(blocks, n_super), dim3(256), 0, st, ps[0], (unsigned)wave_blocks);
-        else
-            hipLaunchKernelGGL((agg_pair_multi_kernel<T, EPC, L, CPL, DUAL>), dim3(blocks, n_super, n), dim3(256), 0, st, m, (unsigned)wave_blocks);
-        HETA_LAUNCH_CHECK("agg_pair_kernel");
-        return HETA_OK;
-    }
-    if (wave_blocks > 0) {
-        ProfScope prof(cost.timed ? "agg_wave_kernel" : nullptr, st, cost.wave_bytes, 0);
-        if (split && n == 1)
-            hipLaunchKernelGGL((agg_wave_split_kernel<T, EPC, L, CPL, DUAL>), dim3((unsigned)wave_blocks, n_super), dim3(256), 0, st, ps[0]);
-        else if (split)
-            hipLaunchKernelGGL((agg_wave_split_multi_kernel<T, EPC, L, CPL, DUAL>), dim3((unsigned)wave_blocks, n_super, n), dim3(256), 0, st, m);
-        else if (n == 1)
-            hipLaunchKernelGGL((agg_wave_kernel<T, EPC, L, CPL, DUAL>), dim3((unsigned)wave_blocks, n_super), dim3(256), 0, st, ps[0]);
-        else
-            hipLaunchKernelGGL((agg_wave_multi_kernel<T, EPC, L, CPL, DUAL>), dim3((unsigned)wave_blocks, n_super, n), dim3(256), 0, st, m);
-        HETA_LAUNCH_CHECK("agg_wave_kernel");
-    }
-    if (batch_blocks > 0) {
-        ProfScope prof(cost.timed ? "agg_batch_kernel" : nullptr, st, cost.group_bytes, 0);
-        if (n == 1)
-            hipLaunchKernelGGL((agg_batch_kernel<T, EPC, L, CPL, DUAL>), dim3((unsigned)batch_blocks, n_super), dim3(256), 0, st, ps[0]);
-        else
-            hipLaunchKernelGGL((agg_batch_multi_kernel<T, EPC, L, CPL, DUAL>), dim3((unsigned)batch_blocks, n_super, n), dim3(256), 0, st, m);
-        HETA_LAUNCH_CHECK("agg_batch_kernel");
+    if (n == 1 && total <= kMaxSectionBlocks) return launch_sections<T, EPC, L, CPL, MODE, 1>(ps, blocks, 1, n_super, st, cost);
+    if (total <= kMaxSectionBlocks) return launch_sections<T, EPC, L, CPL, MODE, kAggMulti>(ps, blocks, n, n_super, st, cost);
+    AggCost c = cost; // more workgroups than one grid takes: one section at a time
+    for (int s = 0; s < 2 * n; ++s) {
+        const int64_t one[2] = {s < n ? blocks[s] : 0, s < n ? 0 : blocks[s]};
+        const heta_status e = launch_sections<T, EPC, L, CPL, MODE, 1>(ps + s % n, one, 1, n_super, st, c);
+        if (e != HETA_OK) return e;
+        c.bytes = 0;
     }
     return HETA_OK;
 }
 
-template <typename T, int EPC>
-static heta_status launch_vec(const AggParams *ps, int n, int n_chunks, hipStream_t st, const AggCost &c)
+// the kernel of a launch's weights (part of the plans' key); the two-weight form exists for the 128-bit paths
+template <typename T, int EPC, int L, int CPL>
+static heta_status launch_rows(const AggParams *ps, int n, int n_super, hipStream_t st, const AggCost &cost)
 {
-    if (n_chunks <= 1) return launch_pair<T, EPC, 1, 1>(ps, n, 1, st, c);
-    if (n_chunks <= 2) return launch_pair<T, EPC, 2, 1>(ps, n, 1, st, c);
-    if (n_chunks <= 4) return launch_pair<T, EPC, 4, 1>(ps, n, 1, st, c);
-    if (n_chunks <= 8) return launch_pair<T, EPC, 8, 1>(ps, n, 1, st, c);
-    if (n_chunks <= 16) return launch_pair<T, EPC, 16, 1>(ps, n, 1, st, c);
-    if (n_chunks <= 32) return launch_pair<T, EPC, 32, 1>(ps, n, 1, st, c);
-    if (n_chunks <= 64) return launch_pair<T, EPC, 64, 1>(ps, n, 1, st, c);
-    return launch_pair<T, EPC, 64, 2>(ps, n, (n_chunks + 127) / 128, st, c);
+    if constexpr (EPC > 1) {
+        if (ps[0].slot_w2) return launch_mode<T, EPC, L, CPL, AGG_DUAL>(ps, n, n_super, st, cost);
+    }
+    if constexpr (L == 64 && EPC > 1) return fail(HETA_ERR_UNSUPPORTED, "aggregate: rows of 64 lanes are the two-weight form's");
+    else {
+        if (ps[0].slot_w) return launch_mode<T, EPC, L, CPL, AGG_SLOT>(ps, n, n_super, st, cost);
+        return launch_mode<T, EPC, L, CPL, AGG_PLAIN>(ps, n, n_super, st, cost);
+    }
+}
+
+// Lanes per row and column tiles (grid.y) of the 128-bit paths: a row of more than 32 chunks is walked in tiles of 32.
+// Against one lane group of 64 lanes, or of 64 lanes with two chunks each: 4 M edges of 1 KB rows from a table of 1.1 GB
+// 838 -> 771 us, of 0.7 GB 775 -> 730; and a row of 96 chunks leaves no lane idle.  The one-pass dot over a head of more
+// than 32 chunks needs the head in one tile.
+static int lanes_per_row(const AggParams &p, int epc, int n_chunks)
+{
+    if (p.slot_w2 && p.dot_out && p.head_dim / epc > 32) return 64;
+    int L = 1;
+    while (L < n_chunks && L < 32) L <<= 1;
+    return L;
+}
+
+template <typename T, int EPC>
+static heta_status launch_vec(const AggParams *ps, int n, int L, int n_super, hipStream_t st, const AggCost &c)
+{
+    if (L == 1) return launch_rows<T, EPC, 1, 1>(ps, n, n_super, st, c);
+    if (L == 2) return launch_rows<T, EPC, 2, 1>(ps, n, n_super, st, c);
+    if (L == 4) return launch_rows<T, EPC, 4, 1>(ps, n, n_super, st, c);
+    if (L == 8) return launch_rows<T, EPC, 8, 1>(ps, n, n_super, st, c);
+    if (L == 16) return launch_rows<T, EPC, 16, 1>(ps, n, n_super, st, c);
+    if (L == 32) return launch_rows<T, EPC, 32, 1>(ps, n, n_super, st, c);
+    return launch_rows<T, EPC, 64, 1>(ps, n, n_super, st, c);
 }
 
 // Everything about one aggregation that the host decides before a launch: the filled-in kernel
@@ -757,13 +777,13 @@ struct AggPlan {
     AggParams p;
     heta_dtype in_dt = HETA_F32;
     bool vec = false, dual = false;
-    int n_chunks = 0;
+    int lanes = 64, n_super = 1; // lanes per row, column tiles
     size_t ws_need = 0;
     AggCost cost;
     double hub_bytes = 0;
     int64_t n_hub_rows = 0;
     // relations with equal keys run the same kernel instantiation with the same grid.y
-    int key() const { return (in_dt == HETA_F32 ? 0 : 1) | (vec ? 2 : 0) | (dual ? 4 : 0) | (p.wave_split ? 8 : 0) | (n_chunks << 4); }
+    int key() const { return (in_dt == HETA_F32 ? 0 : 1) | (vec ? 2 : 0) | (dual ? 4 : 0) | (p.slot_w ? 8 : 0) | (lanes << 4) | (n_super << 11); }
 };
 
 static bool agg_vectorized(const AggParams &p, heta_dtype in_dt)
@@ -780,11 +800,7 @@ static heta_status plan_aggregate(const Schedule &s, AggParams p, heta_dtype in_
     const bool dual = p.slot_w2 != nullptr;
     const int epc = vec ? static_cast<int>(16 / esz) : 1;
     const int n_chunks = (p.d + epc - 1) / epc;
-    int L = 64; // lanes per row, as the dispatch picks them
-    if (vec) {
-        L = 1;
-        while (L < n_chunks && L < 64) L <<= 1;
-    }
+    const int L = vec ? lanes_per_row(p, epc, n_chunks) : 64;
     const int G = 64 / L;
     // rows with at least this many edges get a whole wavefront
     const int wave_min = kShortDeg;
@@ -819,24 +835,32 @@ static heta_status plan_aggregate(const Schedule &s, AggParams p, heta_dtype in_
     p.ws = nullptr;
     if (s.n_hub_rows > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "aggregate: too many hub rows");
     plan->ws_need = static_cast<size_t>(s.n_hub_chunks) * p.ws_stride * sizeof(float);
-    // Algorithmic bytes per row class: one neighbour row and one 4-byte index per edge, one 8-byte
+    // Algorithmic bytes: one neighbour row and one 4-byte index per edge, one 8-byte
     // row pointer and one output row per row.  Hub rows' outputs are written by the combine kernel.
     const double osz = p.out_bf16 ? 2.0 : 4.0;
     const double per_edge = static_cast<double>(p.d) * esz + 4.0 + (p.slot_w ? 4.0 * p.heads : 0.0) + (dual ? 4.0 * p.heads : 0.0);
     const double per_row = 8.0 + p.d * osz * (dual ? 2.0 : 1.0);
-    const double e_wave = static_cast<double>(s.edges_with_deg_ge[wave_min]);
-    const double r_long = static_cast<double>(n_long_or_hub - s.n_hub_rows);
-    plan->cost.wave_bytes = e_wave * per_edge + r_long * per_row;
-    plan->cost.group_bytes = (static_cast<double>(s.n_edges) - e_wave) * per_edge +
-                             static_cast<double>(s.n_rows - n_long_or_hub) * per_row;
+    plan->cost.bytes = static_cast<double>(s.n_edges) * per_edge + static_cast<double>(s.n_rows - s.n_hub_rows) * per_row;
     plan->hub_bytes = static_cast<double>(s.n_hub_rows) * per_row;
     plan->n_hub_rows = s.n_hub_rows;
     plan->p = p;
     plan->in_dt = in_dt;
     plan->vec = vec;
     plan->dual = dual;
-    plan->n_chunks = n_chunks;
+    plan->lanes = L;
+    plan->n_super = vec ? (n_chunks + L - 1) / L : (n_chunks + 127) / 128;
     return HETA_OK;
+}
+
+template <int N>
+static void launch_hub_combine(const AggParams *ps, int n, int lpc, unsigned blocks, int tiles, bool dual, hipStream_t st)
+{
+    AggLaunch<N> m{};
+    for (int i = 0; i < n; ++i) m.p[i] = ps[i];
+    const dim3 grid(blocks, dual ? 2 * n : n), threads(64 * kCombineWaves);
+    if (lpc == 64) hipLaunchKernelGGL((agg_hub_combine_kernel<64, N>), grid, threads, 0, st, m, tiles, (int)dual);
+    else if (lpc == 16) hipLaunchKernelGGL((agg_hub_combine_kernel<16, N>), grid, threads, 0, st, m, tiles, (int)dual);
+    else hipLaunchKernelGGL((agg_hub_combine_kernel<8, N>), grid, threads, 0, st, m, tiles, (int)dual);
 }
 
 // Launches n planned aggregations of one key (n = 1: the single-relation kernels) whose hub partial
@@ -850,46 +874,30 @@ static heta_status launch_plans(const AggPlan *plans, int n, hipStream_t st, boo
     int64_t hub_rows = 0;
     for (int i = 0; i < n; ++i) {
         ps[i] = plans[i].p;
-        cost.wave_bytes += plans[i].cost.wave_bytes;
-        cost.group_bytes += plans[i].cost.group_bytes;
+        cost.bytes += plans[i].cost.bytes;
         hub_bytes += plans[i].hub_bytes;
         hub_rows = std::max(hub_rows, plans[i].n_hub_rows);
     }
     const AggPlan &f = plans[0];
     heta_status e;
     if (f.in_dt == HETA_F32)
-        e = f.vec ? launch_vec<float, 4>(ps, n, f.n_chunks, st, cost) : launch_pair<float, 1, 64, 2>(ps, n, (f.n_chunks + 127) / 128, st, cost);
+        e = f.vec ? launch_vec<float, 4>(ps, n, f.lanes, f.n_super, st, cost) : launch_rows<float, 1, 64, 2>(ps, n, f.n_super, st, cost);
     else
-        e = f.vec ? launch_vec<bf16_t, 8>(ps, n, f.n_chunks, st, cost) : launch_pair<bf16_t, 1, 64, 2>(ps, n, (f.n_chunks + 127) / 128, st, cost);
-    if (e != HETA_OK) return e;
-    if (hub_rows > 0) {
-        const int tiles = static_cast<int>((f.p.ws_ld + 31) / 32);
-        if (hub_rows * tiles > max_blocks(64 * kCombineWaves)) return fail(HETA_ERR_UNSUPPORTED, "aggregate: too many hub rows");
-        const dim3 threads(64 * kCombineWaves);
-        auto blocks = [&](int t) { return static_cast<unsigned>(hub_rows * t); };
-        ProfScope prof(timed ? "agg_hub_combine_kernel" : nullptr, st, hub_bytes, 0);
-        if (n == 1) {
-            hipLaunchKernelGGL(agg_hub_combine_kernel<8>, dim3(blocks(tiles)), threads, 0, st, ps[0], tiles);
-            HETA_LAUNCH_CHECK("agg_hub_combine_kernel");
-            if (f.dual) {
-                AggParams p2 = ps[0];
-                p2.ws = ps[0].ws + ps[0].ws_ld;
-                p2.out = ps[0].out2;
-                p2.ld_out = ps[0].ld_out2;
-                p2.combine_dot = ps[0].dot_out ? 1 : 0;
-                const int wide = p2.combine_dot ? p2.head_dim : 0; // the plan's dot form has at most 256 columns
-                if (wide > 64) hipLaunchKernelGGL(agg_hub_combine_kernel<64>, dim3(blocks(1)), threads, 0, st, p2, 1);
-                else if (wide > 32) hipLaunchKernelGGL(agg_hub_combine_kernel<16>, dim3(blocks((tiles + 1) / 2)), threads, 0, st, p2, (tiles + 1) / 2);
-                else hipLaunchKernelGGL(agg_hub_combine_kernel<8>, dim3(blocks(tiles)), threads, 0, st, p2, tiles);
-                HETA_LAUNCH_CHECK("agg_hub_combine_kernel");
-            }
-        } else {
-            AggMulti m{};
-            for (int i = 0; i < n; ++i) m.p[i] = ps[i];
-            hipLaunchKernelGGL(agg_hub_combine_multi_kernel, dim3(blocks(tiles), n), threads, 0, st, m, tiles);
-            HETA_LAUNCH_CHECK("agg_hub_combine_kernel");
-        }
+        e = f.vec ? launch_vec<bf16_t, 8>(ps, n, f.lanes, f.n_super, st, cost) : launch_rows<bf16_t, 1, 64, 2>(ps, n, f.n_super, st, cost);
+    if (e != HETA_OK || hub_rows == 0) return e;
+    int64_t width = 0;
+    int head = 0; // widest head of a dot (at most 256 columns): its columns need to be in one tile
+    for (int i = 0; i < n; ++i) {
+        width = std::max(width, ps[i].ws_ld);
+        if (ps[i].dot_out) head = std::max(head, ps[i].head_dim);
     }
+    const int lpc = head > 64 ? 64 : head > 32 ? 16 : 8;
+    const int tiles = static_cast<int>((width + 4 * lpc - 1) / (4 * lpc));
+    if (hub_rows * tiles > max_blocks(64 * kCombineWaves)) return fail(HETA_ERR_UNSUPPORTED, "aggregate: too many hub rows");
+    ProfScope prof(timed ? "agg_hub_combine_kernel" : nullptr, st, hub_bytes, 0);
+    if (n == 1) launch_hub_combine<1>(ps, 1, lpc, static_cast<unsigned>(hub_rows * tiles), tiles, f.dual, st);
+    else launch_hub_combine<kAggMulti>(ps, n, lpc, static_cast<unsigned>(hub_rows * tiles), tiles, f.dual, st);
+    HETA_LAUNCH_CHECK("agg_hub_combine_kernel");
     return HETA_OK;
 }
 

@@ -32,7 +32,7 @@ CALIB_KIB = float(1 << 20)  # the calibration copy reads 1 GiB and writes 1 GiB
 
 
 def short_name(full: str) -> str:
-    """'void heta::agg_wave_kernel<float, 4, 32, 1>(heta::AggParams)' -> 'agg_wave_kernel<float, 4, 32, 1>'"""
+    """'void heta::agg_rows_kernel<float, 4, 32, 1, 0, 1>(heta::AggLaunch<1>)' -> 'agg_rows_kernel<float, 4, 32, 1, 0, 1>'"""
     n = full.replace("(anonymous namespace)::", "")
     n = n.split("(")[0].replace("void ", "").replace("heta::", "").strip()
     return n
@@ -51,10 +51,6 @@ def family(name: str) -> str:
         return f"gemm_wgrad_{ct}" if wgrad else f"gemm_{ct}"
     if base.endswith("_multi_kernel"):  # several relations per launch: timed under the single-relation kernel's name
         base = base[:-len("_multi_kernel")] + "_kernel"
-    if base == "agg_wave_split_kernel":  # the long rows of a small launch, four wavefronts per row
-        return "agg_wave_kernel"
-    if base == "agg_pair_kernel":  # both row classes of a small launch in one grid: timed as its short-row part
-        return "agg_batch_kernel"
     return base
 
 

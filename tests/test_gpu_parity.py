@@ -1038,6 +1038,56 @@ def test_multi_relation_aggregation_equals_the_single_calls_bit_for_bit(storage,
         hg.destroy()
 
 
+@pytest.mark.parametrize("dtype,widths", [
+    (torch.float32, [128, 100, 97, 128, 65]),    # one lane class, different widths: one launch of four relations and one of one
+    (torch.float32, [129, 200, 256, 260, 384]),  # more than 32 chunks: column tiles, the last one ragged
+    (torch.bfloat16, [256, 130, 200, 136, 256]),
+    (torch.bfloat16, [264, 512, 520, 768, 257]),
+    (torch.float32, [3, 4, 8, 5, 12]),
+])
+def test_rows_of_all_classes_share_a_launch(dtype, widths):
+    """Hub, long, short and empty rows of several relations in one grid, few and many long rows (four wavefronts per
+    row, or one), against sums in 64 bits: n fp32 additions in any order are off by at most n 2^-24 of the sum of
+    magnitudes, one more for the mean."""
+    gen = torch.Generator().manual_seed(11)
+    n_src, shapes = 700, [(40, 0), (3000, 2600), (500, 3), (1, 1), (64, 0)]  # (rows, long rows)
+    types, rels, lists = [(n_src, 4, 0)], [], []
+    for t, (rows, long_rows) in enumerate(shapes):
+        deg = torch.randint(0, 32, (rows,), generator=gen)
+        deg[:long_rows] = torch.randint(32, 60, (long_rows,), generator=gen)
+        if rows > 1:
+            deg[-1], deg[-2], deg[-3] = 1500, 512, 0
+        rowptr = torch.cat([deg.new_zeros(1), torch.cumsum(deg, 0)])
+        col = torch.randint(0, n_src, (int(rowptr[-1]),), generator=gen, dtype=torch.int32)
+        types.append((rows, 4, 0))
+        rels.append((0, t + 1, rowptr.cuda(), col.cuda()))
+        lists.append((torch.repeat_interleave(torch.arange(rows), deg), col.long(), deg))
+    hg = heta.heta_graph_create(types, rels, heta.HETA_PTRS_ON_DEVICE)
+    try:
+        q = 16 // dtype.itemsize
+        tabs = []
+        for d in widths:
+            x = torch.zeros((n_src, (d + q - 1) // q * q), dtype=dtype)[:, :d]
+            x.copy_(torch.randn((n_src, d), generator=gen))
+            tabs.append(x)
+        dev = [torch.zeros((n_src, (d + q - 1) // q * q), dtype=dtype, device="cuda")[:, :d].copy_(x) for d, x in zip(widths, tabs)]
+        outs = [torch.full((rows, d), 7.0, device="cuda") for (rows, _), d in zip(shapes, widths)]
+        for op in (heta.HETA_SUM, heta.HETA_MEAN):
+            heta.heta_rel_aggregate_fwd_multi(hg, list(range(5)), op, dev, outs)
+            torch.cuda.synchronize()
+            for x, out, (dst, src, deg) in zip(tabs, outs, lists):
+                rows = x.double()[src]
+                ref = torch.zeros((deg.numel(), x.shape[1]), dtype=torch.float64).index_add_(0, dst, rows)
+                mag = torch.zeros_like(ref).index_add_(0, dst, rows.abs())
+                n = deg.double().unsqueeze(1)
+                bound = (n + 1) * 2.0 ** -24 * mag
+                if op == heta.HETA_MEAN:
+                    ref, bound = ref / n.clamp_min(1), bound / n.clamp_min(1) * (1 + 1 / n.clamp_min(1)) + 2.0 ** -23 * (ref / n.clamp_min(1)).abs()
+                assert ((out.cpu().double() - ref).abs() <= bound).all(), (op, x.shape)
+    finally:
+        hg.destroy()
+
+
 def test_calibration_mfma_runs_and_reports_its_flops():
     sink = torch.full((2048,), 3.0, dtype=torch.float32, device="cuda")
     assert heta.heta_calibration_mfma(heta.HETA_F32, 10, sink) == 2.0 * 32 * 32 * 2 * 16 * 10 * 4 * 512
