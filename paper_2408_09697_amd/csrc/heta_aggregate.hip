@@ -45,6 +45,8 @@ constexpr int kShortDeg = 32;      // rows of fewer edges are batched by degree
 constexpr int kBatchIds = 256;     // neighbour ids a batch wavefront parks in LDS
 constexpr int kWaveSplitMaxItems = 2048; // long rows + hub chunks up to which a relation's items get a workgroup each
 
+enum SlotForm { SLOT_RAW, SLOT_FIRST, SLOT_SECOND, SLOT_BOTH };
+
 struct AggParams {
     const int64_t *sptr;   // schedule-ordered row offsets
     const int32_t *sidx;   // schedule-ordered neighbour ids
@@ -58,13 +60,14 @@ struct AggParams {
     const float *slot_w;   // nullable: weight per (edge position in sidx, head): [n_edges][heads]
     int heads;             // with slot_w: number of heads, columns [h*head_dim, (h+1)*head_dim) use weight h
     int head_dim;
-    const float *slot_w2;  // nullable (with slot_w only): a second weight array; the same gathered rows are
-    void *out2;            // reduced a second time with it into out2 (same type and leading dimension rules as out)
+    int slot_form;         // what slot_w holds: the weight (SLOT_RAW), or two weights of which this call wants the first
+    float slot_neg;        // or second alone or BOTH: |w|, and |w| where w's sign bit is clear, slot_neg |w| where it is set
+    void *out2;            // SLOT_BOTH: the same gathered rows, summed with the second weight (type of out)
     int64_t ld_out2;
     int mean;              // divide the row sum by the row's degree
     int hub_only;          // reduce the hub rows only, into out[h] for the h-th hub row of the schedule
     int wave_split;        // few long rows / hub chunks: four wavefronts per item (SPLIT of agg_wave_body)
-    // With slot_w2, instead of storing the second sum: dot_out[row, k] = <second sum of head k, dot_z[row, head k]> -
+    // With SLOT_BOTH, instead of storing the second sum: dot_out[row, k] = <second sum of head k, dot_z[row, head k]> -
     // dot_corr[row, k] (the attention backward needs only this dot of the gate-weighted sum, not the sum itself).
     const void *dot_z;     // nullable; rows indexed like out, ld_z elements apart, fp32 or bf16 (dot_z_bf16)
     int64_t ld_z;
@@ -75,7 +78,7 @@ struct AggParams {
     int64_t ld_out;
     int out_bf16;
     float beta;            // 0 or 1
-    float *ws;             // hub partials [slot][ws_stride]; with slot_w2 the second sum follows at +ws_ld
+    float *ws;             // hub partials [slot][ws_stride]; with SLOT_BOTH the second sum follows at +ws_ld
     int64_t ws_ld;
     int64_t ws_stride;
     int d;
@@ -281,6 +284,18 @@ __host__ __device__ inline int batch_rows(int k, int G)
 // so that a row in flight holds no weight register), by a weight per slot and head, or by two of those into two sums.
 enum AggMode { AGG_PLAIN, AGG_SLOT, AGG_DUAL };
 
+// The second weight of a slot.  A factor of zero gives zero for a NaN weight too: nothing of the edge enters the sum.
+__device__ __forceinline__ float slot_second(const AggParams &p, float w)
+{
+    const float neg = p.slot_neg == 0.f ? 0.f : fabsf(w) * p.slot_neg;
+    return __float_as_uint(w) >> 31 ? neg : fabsf(w);
+}
+// the weight a sum of one kind takes
+__device__ __forceinline__ float slot_single(const AggParams &p, float w)
+{
+    return p.slot_form == SLOT_RAW ? w : p.slot_form == SLOT_FIRST ? fabsf(w) : slot_second(p, w);
+}
+
 template <typename T, int EPC, int L, int CPL, int MODE>
 __device__ __forceinline__ void agg_batch_body(const AggParams &p, const unsigned bx)
 {
@@ -367,7 +382,7 @@ __device__ __forceinline__ void agg_batch_body(const AggParams &p, const unsigne
     const int total = rounds * k;
     for (int s0 = 0; s0 < total; s0 += U) {
         Chunk<T, EPC> v[U][CPL];
-        float ww[SLOT ? U : 1][CPL], ww2[DUAL ? U : 1][CPL];
+        float ww[SLOT ? U : 1][CPL];
         int rl_u = rl, j_u = j;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -382,11 +397,9 @@ __device__ __forceinline__ void agg_batch_body(const AggParams &p, const unsigne
                 if (ok && ch < n_chunks) {
                     v[u][c].load(rp + static_cast<int64_t>(ch) * EPC);
                     if (SLOT) ww[u][c] = p.slot_w[(e0 + i) * p.heads + head[c]];
-                    if (DUAL) ww2[u][c] = p.slot_w2[(e0 + i) * p.heads + head[c]];
                 } else {
                     v[u][c].zero();
                     if (SLOT) ww[u][c] = 0.f;
-                    if (DUAL) ww2[u][c] = 0.f;
                 }
             }
             if (++j_u == k) {
@@ -401,10 +414,10 @@ __device__ __forceinline__ void agg_batch_body(const AggParams &p, const unsigne
                 if (!SLOT && p.edge_w) we = w_s[wave][g + rl * G < nrows ? (g + rl * G) * k + j : 0];
 #pragma unroll
                 for (int c = 0; c < CPL; ++c) {
-                    if (SLOT) v[u][c].add_to(acc[c], ww[u][c]);
+                    if (SLOT) v[u][c].add_to(acc[c], DUAL ? fabsf(ww[u][c]) : slot_single(p, ww[u][c]));
                     else if (p.edge_w) v[u][c].add_to(acc[c], we);
                     else v[u][c].add_to(acc[c]);
-                    if (DUAL) v[u][c].add_to(acc2[c], ww2[u][c]);
+                    if (DUAL) v[u][c].add_to(acc2[c], slot_second(p, ww[u][c]));
                 }
                 if (++j == k) { // last edge of the row: store it, start the next
                     const int r = g + rl * G;
@@ -494,7 +507,7 @@ __device__ __forceinline__ void agg_wave_body(const AggParams &p, const unsigned
         }
         for (int j = 0; j < cnt; j += G * U) {
             Chunk<T, EPC> v[U][CPL];
-            float ww[SLOT ? U : 1][CPL], ww2[DUAL ? U : 1][CPL];
+            float ww[SLOT ? U : 1][CPL];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int k = j + u * G + g;
@@ -507,11 +520,9 @@ __device__ __forceinline__ void agg_wave_body(const AggParams &p, const unsigned
                     if (ok && ch < n_chunks) {
                         v[u][c].load(rp + static_cast<int64_t>(ch) * EPC);
                         if (SLOT) ww[u][c] = p.slot_w[(base + k) * p.heads + head[c]];
-                        if (DUAL) ww2[u][c] = p.slot_w2[(base + k) * p.heads + head[c]];
                     } else {
                         v[u][c].zero();
                         if (SLOT) ww[u][c] = 0.f;
-                        if (DUAL) ww2[u][c] = 0.f;
                     }
                 }
             }
@@ -520,10 +531,10 @@ __device__ __forceinline__ void agg_wave_body(const AggParams &p, const unsigned
                 const float we = !SLOT && p.edge_w ? __shfl(wv, (j + u * G + g) & 63, 64) : 1.f;
 #pragma unroll
                 for (int c = 0; c < CPL; ++c) {
-                    if (SLOT) v[u][c].add_to(acc[c], ww[u][c]);
+                    if (SLOT) v[u][c].add_to(acc[c], DUAL ? fabsf(ww[u][c]) : slot_single(p, ww[u][c]));
                     else if (p.edge_w) v[u][c].add_to(acc[c], we);
                     else v[u][c].add_to(acc[c]);
-                    if (DUAL) v[u][c].add_to(acc2[c], ww2[u][c]);
+                    if (DUAL) v[u][c].add_to(acc2[c], slot_second(p, ww[u][c]));
                 }
             }
         }
@@ -667,7 +678,7 @@ template <int N> struct AggLaunch {
 static_assert(sizeof(AggLaunch<kAggMulti>) <= 3840, "kernel arguments are limited to 4 KB");
 
 template <typename T, int EPC, int L, int CPL, int MODE, int N>
-__global__ void __launch_bounds__(256, MODE != AGG_PLAIN ? 4 : EPC == 8 ? 7 : 8) agg_rows_kernel(AggLaunch<N> m)
+__global__ void __launch_bounds__(256, EPC == 8 ? (MODE == AGG_PLAIN ? 7 : 5) : MODE == AGG_PLAIN ? 8 : MODE == AGG_SLOT ? 7 : 6) agg_rows_kernel(AggLaunch<N> m)
 {
     int s = 0;
 #pragma unroll
@@ -737,7 +748,7 @@ template <typename T, int EPC, int L, int CPL>
 static heta_status launch_rows(const AggParams *ps, int n, int n_super, hipStream_t st, const AggCost &cost)
 {
     if constexpr (EPC > 1) {
-        if (ps[0].slot_w2) return launch_mode<T, EPC, L, CPL, AGG_DUAL>(ps, n, n_super, st, cost);
+        if (ps[0].slot_form == SLOT_BOTH) return launch_mode<T, EPC, L, CPL, AGG_DUAL>(ps, n, n_super, st, cost);
     }
     if constexpr (L == 64 && EPC > 1) return fail(HETA_ERR_UNSUPPORTED, "aggregate: rows of 64 lanes are the two-weight form's");
     else {
@@ -752,7 +763,7 @@ static heta_status launch_rows(const AggParams *ps, int n, int n_super, hipStrea
 // than 32 chunks needs the head in one tile.
 static int lanes_per_row(const AggParams &p, int epc, int n_chunks)
 {
-    if (p.slot_w2 && p.dot_out && p.head_dim / epc > 32) return 64;
+    if (p.slot_form == SLOT_BOTH && p.dot_out && p.head_dim / epc > 32) return 64;
     int L = 1;
     while (L < n_chunks && L < 32) L <<= 1;
     return L;
@@ -797,7 +808,7 @@ static heta_status plan_aggregate(const Schedule &s, AggParams p, heta_dtype in_
 {
     const size_t esz = dtype_size(in_dt);
     const bool vec = agg_vectorized(p, in_dt);
-    const bool dual = p.slot_w2 != nullptr;
+    const bool dual = p.slot_form == SLOT_BOTH;
     const int epc = vec ? static_cast<int>(16 / esz) : 1;
     const int n_chunks = (p.d + epc - 1) / epc;
     const int L = vec ? lanes_per_row(p, epc, n_chunks) : 64;
@@ -838,7 +849,7 @@ static heta_status plan_aggregate(const Schedule &s, AggParams p, heta_dtype in_
     // Algorithmic bytes: one neighbour row and one 4-byte index per edge, one 8-byte
     // row pointer and one output row per row.  Hub rows' outputs are written by the combine kernel.
     const double osz = p.out_bf16 ? 2.0 : 4.0;
-    const double per_edge = static_cast<double>(p.d) * esz + 4.0 + (p.slot_w ? 4.0 * p.heads : 0.0) + (dual ? 4.0 * p.heads : 0.0);
+    const double per_edge = static_cast<double>(p.d) * esz + 4.0 + (p.slot_w ? 4.0 * p.heads : 0.0);
     const double per_row = 8.0 + p.d * osz * (dual ? 2.0 : 1.0);
     plan->cost.bytes = static_cast<double>(s.n_edges) * per_edge + static_cast<double>(s.n_rows - s.n_hub_rows) * per_row;
     plan->hub_bytes = static_cast<double>(s.n_hub_rows) * per_row;
@@ -910,11 +921,10 @@ static heta_status run_aggregate(heta_graph *g, const Schedule &s, AggParams p, 
 {
     (void)table_elems_ld;
     if (s.n_rows == 0) return HETA_OK;
-    if (p.slot_w2 && !agg_vectorized(p, in_dt)) { // the two-weight kernels exist for the 128-bit paths only: two passes otherwise
+    if (p.slot_form == SLOT_BOTH && !agg_vectorized(p, in_dt)) { // the two-weight kernels exist for the 128-bit paths only: two passes otherwise
         AggParams a = p, b = p;
-        a.slot_w2 = nullptr;
-        b.slot_w = p.slot_w2;
-        b.slot_w2 = nullptr;
+        a.slot_form = SLOT_FIRST;
+        b.slot_form = SLOT_SECOND;
         b.out = p.out2;
         b.ld_out = p.ld_out2;
         heta_status e1 = run_aggregate(g, s, a, in_dt, table_elems_ld, st);
@@ -976,14 +986,15 @@ static heta_status run_aggregate_multi(heta_graph *g, std::vector<AggPlan> &plan
 // attention aggregation (heta_attention.hip computes the weights).
 heta_status aggregate_slot_weighted(heta_graph *g, const Schedule &s, const void *table, heta_dtype dt, int64_t ld,
                                     int d, const float *slot_w, int heads, void *out, heta_dtype out_dt,
-                                    int64_t ld_out, float beta, hipStream_t st, const float *slot_w2, void *out2,
+                                    int64_t ld_out, float beta, hipStream_t st, bool two_sums, float neg, void *out2,
                                     int64_t ld_out2, const SecondSumDot *dot, bool *dot_done)
 {
     AggParams p{};
     p.table = table;
     p.ld = ld;
     p.slot_w = slot_w;
-    p.slot_w2 = slot_w2;
+    p.slot_form = two_sums ? SLOT_BOTH : SLOT_RAW;
+    p.slot_neg = neg;
     p.out2 = out2;
     p.ld_out2 = ld_out2;
     p.heads = heads;
@@ -994,7 +1005,7 @@ heta_status aggregate_slot_weighted(heta_graph *g, const Schedule &s, const void
     p.beta = beta;
     p.d = d;
     if (dot_done) *dot_done = false;
-    if (dot && slot_w2 && dot->z && dot->out) {
+    if (dot && two_sums && dot->z && dot->out) {
         // the dot form needs: the 128-bit path, one chunk per lane (a row inside one lane group), heads that are a
         // power-of-two number of chunks wide for both the row kernels' chunk (16 bytes of the gathered type) and the
         // hub combine's (4 columns), z rows whose chunks are aligned, a single 256-column tile in the combine

@@ -71,8 +71,9 @@ struct SweepParams {
     float *smax, *sinv;   // [dst][K]   softmax shift and 1/denominator: written by FWD (nullable), read by the others
     const float *dot;     // [dst][K]   <g, o> per head (backward)
     float *alpha;         // [E][K] by edge slot (FWD, BWD_CSC)
-    float *gate;          // [E][K] by edge slot: alpha * LeakyReLU' (BWD_SRC; BWD_DST if non-null), or alpha on the
-                          // edges with a positive logit (FWD, if non-null)
+    int sign;             // FWD: alpha's sign bit is set where the logit is not positive.  BWD_CSC always sets it.  Weights
+                          // restricted to positive logits, or times LeakyReLU', are then read off the one array
+    float *gate;          // [E][K] by edge slot: alpha * LeakyReLU' (BWD_CSR, if non-null)
     float dot_shift;      // BWD_CSR: corr = dot * (sum of gates - dot_shift)
     float *corr;          // [rows][K]  the scalar term subtracted from the row's score gradient (BWD_*)
     const float *nbr_pack; // BWD_CSC: [dst][K][4] = er, smax, sinv, dot of the destination's head (one cache line per
@@ -113,6 +114,9 @@ template <> __device__ __forceinline__ void storek<8>(float *p, const float *v)
     storek<4>(p + 4, v + 4);
 }
 
+// a weight (>= 0 or NaN) whose sign bit says that its logit is not positive
+__device__ __forceinline__ float signed_weight(float a, bool up) { return __uint_as_float((__float_as_uint(a) & 0x7fffffffu) | (up ? 0u : 0x80000000u)); }
+
 // One edge slot e, heads k0 .. k0+KT-1.  ar: the row's score half; m, inv: shift and 1/denominator of the
 // row (unused by PH_BWD_SRC, which reads the neighbour's); acc: running sum.
 template <int KT, int PH>
@@ -139,7 +143,7 @@ __device__ __forceinline__ void visit(const SweepParams &p, int64_t e, int k0, c
         const float sc = lrelu(x[k], p.slope);
         if (PH == PH_ALPHA) {
             a[k] = expf(sc - m[k]) * inv[k];
-            gt[k] = x[k] > 0.f ? a[k] : 0.f; // the weight restricted to edges with a positive logit
+            if (p.sign) a[k] = signed_weight(a[k], x[k] > 0.f);
         } else if (PH == PH_BWD_DST) {
             gt[k] = expf(sc - m[k]) * inv[k] * (x[k] > 0.f ? 1.f : p.slope);
             acc[k] += gt[k];
@@ -147,10 +151,11 @@ __device__ __forceinline__ void visit(const SweepParams &p, int64_t e, int k0, c
             a[k] = expf(sc - mv[k]) * iv[k];
             gt[k] = a[k] * (x[k] > 0.f ? 1.f : p.slope);
             acc[k] = fmaf(gt[k], dv[k], acc[k]);
+            a[k] = signed_weight(a[k], x[k] > 0.f);
         }
     }
     if (PH == PH_ALPHA || PH == PH_BWD_SRC) storek<KT>(p.alpha + e * p.K + k0, a);
-    if (PH == PH_BWD_SRC || ((PH == PH_ALPHA || PH == PH_BWD_DST) && p.gate)) storek<KT>(p.gate + e * p.K + k0, gt);
+    if (PH == PH_BWD_DST && p.gate) storek<KT>(p.gate + e * p.K + k0, gt);
 }
 
 // the slots e0 + lane, e0 + lane + W, ...
@@ -217,7 +222,7 @@ __device__ __forceinline__ void fwd_stats(const SweepParams &p, int64_t e0, int 
             const float e = id[j] >= 0 ? expf(lrelu(x[j][k], p.slope) - m[k]) : 0.f;
             den[k] += e;
             pos[k] += up ? e : 0.f;
-            x[j][k] = __uint_as_float((__float_as_uint(e) & 0x7fffffffu) | (up ? 0u : 0x80000000u));
+            x[j][k] = signed_weight(e, up);
         }
     group_sum<W, KT>(den);
     group_sum<W, KT>(pos);
@@ -239,14 +244,10 @@ __device__ __forceinline__ void fwd_row(const SweepParams &p, int64_t row, int64
 #pragma unroll
     for (int j = 0; j < NPL; ++j) {
         if (lane + j * W < n) {
-            float a[KT], gt[KT];
+            float a[KT];
 #pragma unroll
-            for (int k = 0; k < KT; ++k) {
-                a[k] = fabsf(x[j][k]) * inv[k];
-                gt[k] = __float_as_uint(x[j][k]) >> 31 ? 0.f : a[k]; // the weight restricted to edges with a positive logit
-            }
+            for (int k = 0; k < KT; ++k) a[k] = signed_weight(fabsf(x[j][k]) * inv[k], !p.sign || __float_as_uint(x[j][k]) >> 31 == 0);
             storek<KT>(p.alpha + (e0 + lane + j * W) * p.K + k0, a);
-            if (p.gate) storek<KT>(p.gate + (e0 + lane + j * W) * p.K + k0, gt);
         }
     }
     if (live && lane == 0 && p.smax) {
@@ -492,7 +493,7 @@ heta_status launch_sweeps(const Schedule &s, SweepParams p, float *hub_scratch, 
     p.hub_stat = hub_scratch + s.n_hub_chunks * p.K * 3;
     // Algorithmic bytes: per edge one 4-byte id, per edge and head the neighbour's 4-byte terms and the
     // 4-byte weights written; per row its offsets and per-head terms.
-    const double per_edge = 4.0 + p.K * (OP == SWEEP_BWD_CSC ? 24.0 : 8.0);
+    const double per_edge = 4.0 + p.K * (OP == SWEEP_BWD_CSC ? 20.0 : 8.0);
     ProfScope prof(name, st, per_edge * static_cast<double>(s.n_edges) + static_cast<double>(s.n_rows) * (12.0 + 12.0 * p.K), 0);
     // KT consecutive heads per thread need 4*KT-byte aligned score rows
     const uintptr_t all = reinterpret_cast<uintptr_t>(p.row_a) | reinterpret_cast<uintptr_t>(p.nbr_a) |
@@ -1501,7 +1502,7 @@ heta_status check_attn_args(const char *fn, heta_graph *g, int32_t rel, int32_t 
 // dz[u] = sum_e alpha_e g[v_e] and R[u] = sum_e gate_e g[v_e]; del = <z, R> - sum_e gate_e dot[v_e].
 heta_status attn_source_side(heta_graph *g, const Relation &r, const void *z, heta_dtype z_dt, int64_t ld_z, int d, int K, const float *el,
                              float slope, const float *nbr_pack, const float *grad_out, int64_t ld_go, float *dz, int64_t ld_dz, float *del,
-                             float *w_alpha, float *w_gate, float *corr_s, float *R, int64_t ld_r, float *hub_scratch, hipStream_t st)
+                             float *w_alpha, float *corr_s, float *R, int64_t ld_r, float *hub_scratch, hipStream_t st)
 {
     SweepParams sp{};
     sp.K = K;
@@ -1509,14 +1510,13 @@ heta_status attn_source_side(heta_graph *g, const Relation &r, const void *z, he
     sp.row_a = el;
     sp.nbr_pack = nbr_pack;
     sp.alpha = w_alpha;
-    sp.gate = w_gate;
     sp.corr = corr_s;
     heta_status e = launch_sweeps<SWEEP_BWD_CSC>(r.csc, sp, hub_scratch, st, "attn_sweep_bwd_src");
     if (e != HETA_OK) return e;
     // del = <z, R> - corr_s is taken inside the aggregation when the shapes allow it (R is then never written)
     const SecondSumDot zr{z, z_dt, ld_z, corr_s, del};
     bool dot_done = false;
-    e = aggregate_slot_weighted(g, r.csc, grad_out, HETA_F32, ld_go, d, w_alpha, K, dz, HETA_F32, ld_dz, 0.f, st, w_gate, R, ld_r,
+    e = aggregate_slot_weighted(g, r.csc, grad_out, HETA_F32, ld_go, d, w_alpha, K, dz, HETA_F32, ld_dz, 0.f, st, true, slope, R, ld_r,
                                 &zr, &dot_done);
     if (e != HETA_OK || dot_done) return e;
     DotParams dp{};
@@ -1862,12 +1862,11 @@ heta_status heta_rel_attn_fwd_train(heta_graph *g, int32_t rel, const void *z, h
     const Relation &r = g->rels[rel];
     hipStream_t st = as_stream(hip_stream);
     const size_t a_bytes = std::max<size_t>(256, round256(static_cast<size_t>(r.n_edges) * heads * sizeof(float)));
-    e = ensure_attn(g, (out_pos ? 2 : 1) * a_bytes + hub_scratch_bytes(r.csr, heads));
+    e = ensure_attn(g, a_bytes + hub_scratch_bytes(r.csr, heads));
     if (e != HETA_OK) return e;
     char *base = static_cast<char *>(g->d_attn);
     float *alpha = reinterpret_cast<float *>(base);
-    float *alpha_pos = out_pos ? reinterpret_cast<float *>(base + a_bytes) : nullptr;
-    float *hub_scratch = reinterpret_cast<float *>(base + (out_pos ? 2 : 1) * a_bytes);
+    float *hub_scratch = reinterpret_cast<float *>(base + a_bytes);
     SweepParams sp{};
     sp.K = heads;
     sp.slope = slope;
@@ -1876,11 +1875,11 @@ heta_status heta_rel_attn_fwd_train(heta_graph *g, int32_t rel, const void *z, h
     sp.smax = smax;
     sp.sinv = sinv;
     sp.alpha = alpha;
-    sp.gate = alpha_pos;
+    sp.sign = out_pos != nullptr;
     sp.apos = apos;
     e = launch_sweeps<SWEEP_FWD>(r.csr, sp, hub_scratch, st, "attn_sweep_fwd");
     if (e != HETA_OK) return e;
-    return aggregate_slot_weighted(g, r.csr, z, z_dt, ld_z, d, alpha, heads, out, out_dt, ld_out, beta, st, alpha_pos, out_pos,
+    return aggregate_slot_weighted(g, r.csr, z, z_dt, ld_z, d, alpha, heads, out, out_dt, ld_out, beta, st, out_pos != nullptr, 0.f, out_pos,
                                    ld_pos);
 }
 
@@ -1991,7 +1990,7 @@ heta_status heta_rel_attn_bwd(heta_graph *g, int32_t rel, const void *z, heta_dt
                            reinterpret_cast<float4 *>(nbr_pack));
         HETA_LAUNCH_CHECK("attn_pack_kernel");
     }
-    return attn_source_side(g, r, z, z_dt, ld_z, d, K, el, slope, nbr_pack, grad_out, ld_go, dz, ld_dz, del, w_alpha, w_gate, corr_s, R, ld_r,
+    return attn_source_side(g, r, z, z_dt, ld_z, d, K, el, slope, nbr_pack, grad_out, ld_go, dz, ld_dz, del, w_alpha, corr_s, R, ld_r,
                             hub_scratch, st);
 }
 
@@ -2087,13 +2086,13 @@ heta_status heta_rel_attn_bwd_src(heta_graph *g, int32_t rel, const void *z, het
     const size_t src_bytes = round256(static_cast<size_t>(r.n_src) * heads * sizeof(float));
     const int64_t ld_r = (static_cast<int64_t>(d) + 3) / 4 * 4;
     const size_t r_bytes = round256(static_cast<size_t>(r.n_src) * ld_r * sizeof(float));
-    e = ensure_attn(g, 2 * w_bytes + src_bytes + r_bytes + round256(hub_scratch_bytes(r.csc, heads)));
+    e = ensure_attn(g, w_bytes + src_bytes + r_bytes + round256(hub_scratch_bytes(r.csc, heads)));
     if (e != HETA_OK) return e;
     char *base = static_cast<char *>(g->d_attn);
-    float *w_alpha = reinterpret_cast<float *>(base), *w_gate = reinterpret_cast<float *>(base + w_bytes);
-    float *corr_s = reinterpret_cast<float *>(base + 2 * w_bytes), *R = reinterpret_cast<float *>(base + 2 * w_bytes + src_bytes);
-    float *hub_scratch = reinterpret_cast<float *>(base + 2 * w_bytes + src_bytes + r_bytes);
-    return attn_source_side(g, r, z, z_dt, ld_z, d, heads, el, slope, pack, grad_out, ld_go, dz, ld_dz, del, w_alpha, w_gate, corr_s, R, ld_r,
+    float *w_alpha = reinterpret_cast<float *>(base);
+    float *corr_s = reinterpret_cast<float *>(base + w_bytes), *R = reinterpret_cast<float *>(base + w_bytes + src_bytes);
+    float *hub_scratch = reinterpret_cast<float *>(base + w_bytes + src_bytes + r_bytes);
+    return attn_source_side(g, r, z, z_dt, ld_z, d, heads, el, slope, pack, grad_out, ld_go, dz, ld_dz, del, w_alpha, corr_s, R, ld_r,
                             hub_scratch, as_stream(hip_stream));
 }
 
