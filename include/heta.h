@@ -209,6 +209,10 @@ typedef struct heta_agg_item {
 } heta_agg_item;
 heta_status heta_rel_aggregate_fwd_multi(heta_graph *g, int32_t n, const heta_agg_item *items, heta_reduce op,
                                          heta_dtype in_dt, heta_dtype out_dt, void *hip_stream);
+/* The same with an activation per item (host array of n; NULL: none) on the rows as they are stored, behind the
+ * accumulation: out = act(beta * out + sum).  For the last of the relations that are summed into one buffer. */
+heta_status heta_rel_aggregate_fwd_multi_act(heta_graph *g, int32_t n, const heta_agg_item *items, const heta_act *acts,
+                                             heta_reduce op, heta_dtype in_dt, heta_dtype out_dt, void *hip_stream);
 heta_status heta_rel_aggregate_bwd_multi(heta_graph *g, int32_t n, const heta_agg_item *items, heta_reduce op,
                                          heta_dtype in_dt, void *hip_stream);
 

@@ -26,7 +26,7 @@ HETA_PTRS_ON_DEVICE = 1
 
 EXPORTS = ["heta_graph_create", "heta_graph_create_batch", "heta_graph_destroy", "heta_graph_get_csc", "heta_graph_get_degrees",
            "heta_feature_gather", "heta_check_ids", "heta_rel_aggregate_fwd", "heta_rel_aggregate_bwd",
-           "heta_rel_aggregate_fwd_multi", "heta_rel_aggregate_bwd_multi",
+           "heta_rel_aggregate_fwd_multi", "heta_rel_aggregate_fwd_multi_act", "heta_rel_aggregate_bwd_multi",
            "heta_project", "heta_rel_project", "heta_rel_project_wgrad", "heta_cross_rel_reduce",
            "heta_act_bwd", "heta_sparse_adam_multi", "heta_last_error", "heta_version", "heta_profile_enable", "heta_profile_reset",
            "heta_profile_read", "heta_calibration_copy", "heta_calibration_mfma", "heta_cross_rel_project", "heta_cross_rel_project_bwd",
@@ -94,6 +94,7 @@ def load_library() -> ctypes.CDLL:
     L.heta_rel_aggregate_fwd_noalloc.argtypes = L.heta_rel_aggregate_fwd.argtypes
     L.heta_rel_aggregate_bwd.argtypes = [vp, i32, i32, vp, i32, i64, i32, vp, i64, f32, vp]
     L.heta_rel_aggregate_fwd_multi.argtypes = [vp, i32, ctypes.POINTER(_AggItem), i32, i32, i32, vp]
+    L.heta_rel_aggregate_fwd_multi_act.argtypes = [vp, i32, ctypes.POINTER(_AggItem), ctypes.POINTER(i32), i32, i32, i32, vp]
     L.heta_rel_aggregate_bwd_multi.argtypes = [vp, i32, ctypes.POINTER(_AggItem), i32, i32, vp]
     L.heta_project.argtypes = [i64, vp, i32, i64, i32, vp, i32, i64, i32, i32, vp, vp, i32, i64, f32, vp]
     L.heta_rel_project.argtypes = [vp, i32, vp, i32, i64, i32, vp, i32, i64, i32, i32, vp, vp, i32, i64, f32, vp]
@@ -356,6 +357,15 @@ def heta_rel_aggregate_fwd_multi(g: Graph, rels: Sequence[int], op: int, src_tab
                                  src_gids: Optional[Sequence[Optional[torch.Tensor]]] = None,
                                  betas: Optional[Sequence[float]] = None, stream=None) -> None:
     """heta_rel_aggregate_fwd for several relations at once (relations of equal shape class share launches)."""
+    heta_rel_aggregate_fwd_multi_act(g, rels, None, op, src_tables, outs, d, src_gids, betas, stream)
+
+
+def heta_rel_aggregate_fwd_multi_act(g: Graph, rels: Sequence[int], acts: Optional[Sequence[int]], op: int,
+                                     src_tables: Sequence[torch.Tensor], outs: Sequence[torch.Tensor],
+                                     d: Optional[Sequence[int]] = None,
+                                     src_gids: Optional[Sequence[Optional[torch.Tensor]]] = None,
+                                     betas: Optional[Sequence[float]] = None, stream=None) -> None:
+    """heta_rel_aggregate_fwd_multi with an activation per item on the rows as they are stored."""
     n = len(rels)
     if n == 0:
         return
@@ -375,8 +385,8 @@ def heta_rel_aggregate_fwd_multi(g: Graph, rels: Sequence[int], op: int, src_tab
         it.src_gid = _dev(gid, "src_gid", torch.int64)
         it.out, it.ld_out = _dev(o, "out"), _ld(o)
         it.beta = 0.0 if betas is None else betas[i]
-    _check(load_library().heta_rel_aggregate_fwd_multi(g.handle, n, items, op, _dt(src_tables[0]), _dt(outs[0]),
-                                                       _stream(stream)))
+    _check(load_library().heta_rel_aggregate_fwd_multi_act(g.handle, n, items, None if acts is None else (ctypes.c_int32 * n)(*acts), op,
+                                                           _dt(src_tables[0]), _dt(outs[0]), _stream(stream)))
 
 
 def heta_rel_aggregate_bwd_multi(g: Graph, rels: Sequence[int], op: int, grad_outs: Sequence[torch.Tensor],

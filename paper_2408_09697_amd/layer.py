@@ -189,6 +189,7 @@ class RafLayer:
         # the relation-specific aggregations of a layer do not depend on each other: one call for all of them
         # (relations of one shape class share launches, which is what a sampled block's small relations need)
         self._aggregate_all([r for r in self.rels if r not in self.pf], stream)
+        into = []
         for t, all_rs in self.rels_into.items():
             rs = [r for r in all_rs if r not in self.pf]
             pfs = [r for r in all_rs if r in self.pf]
@@ -200,12 +201,16 @@ class RafLayer:
                                           act=self.act if last else hb.HETA_ACT_NONE, beta=0.0 if c == 0 else 1.0,
                                           stream=stream)
                 wrote = True
-            for r in pfs:  # projected over the source rows above; aggregate at the output width into H_t
-                hb.heta_rel_aggregate_fwd(self.g, r, self.op, self.Zp[r], self.H[t], d=self.d_out,
-                                          beta=1.0 if wrote else 0.0, stream=stream)
-                wrote = True
-            if pfs and self.relu:
-                hb.heta_cross_rel_reduce(self.g, t, [self.H[t]], self.H[t], act=hb.HETA_ACT_RELU, stream=stream)
+            if pfs:
+                into.append((t, pfs, wrote))
+        # Projected over the source rows above; aggregated at the output width into H_t.  Round k takes the k-th such
+        # relation of every type (distinct outputs: one call), the rounds keep the order of each sum, and the last
+        # relation of a type stores activated rows.
+        for k in range(max((len(pfs) for _, pfs, _ in into), default=0)):
+            part = [(t, pfs[k], k + 1 == len(pfs), wrote or k > 0) for t, pfs, wrote in into if k < len(pfs)]
+            hb.heta_rel_aggregate_fwd_multi_act(self.g, [r for _, r, _, _ in part], [self.act if last else hb.HETA_ACT_NONE for _, _, last, _ in part],
+                                                self.op, [self.Zp[r] for _, r, _, _ in part], [self.H[t] for t, _, _, _ in part],
+                                                d=[self.d_out] * len(part), betas=[1.0 if add else 0.0 for _, _, _, add in part], stream=stream)
         return self.H
 
     def forward_per_relation(self, stream=None) -> Dict[int, torch.Tensor]:
@@ -257,6 +262,7 @@ class RafLayer:
     # ---- backward: dZ = G; dW = M^T dZ; dM = dZ W^T; dH0 += CSC gather of dM ---------------------------
     def backward(self, G: Dict[int, torch.Tensor], stream=None, per_relation: bool = False):
         first_for_src = {s: True for s in self.rels_from}
+        pf_grads = []  # (project-first relation, its destination's gradient)
         per_src: Dict[int, list] = {}  # source type -> [(relation, dM_r)] in the order of the sum
         for t, all_rs in self.rels_into.items():
             rs = [r for r in all_rs if r not in self._pf_active]
@@ -282,8 +288,11 @@ class RafLayer:
                                                   [self.dM[r] for r in part], stream=stream)
             for r in rs:
                 per_src.setdefault(self.g.rels[r][0], []).append((r, dM[r]))
-            for r in pfs:  # dZ'_r = CSC gather of G_t over the source rows
-                hb.heta_rel_aggregate_bwd(self.g, r, self.op, g, self.Ghat[r], d=self.d_out, stream=stream)
+            pf_grads += [(r, g) for r in pfs]
+        for dtype in dict.fromkeys(g.dtype for _, g in pf_grads):  # dZ'_r = CSC gather of G_t over the source rows
+            part = [(r, g) for r, g in pf_grads if g.dtype == dtype]
+            hb.heta_rel_aggregate_bwd_multi(self.g, [r for r, _ in part], self.op, [g for _, g in part],
+                                            [self.Ghat[r] for r, _ in part], d=[self.d_out] * len(part), stream=stream)
         # dH0_s = sum over the relations leaving s of the CSC gather of dM_r.  Round k takes the k-th relation
         # of every source type (their outputs are distinct, so one call covers them); the rounds follow each
         # other on the stream, which keeps the order of the sum over the relations of a type fixed.

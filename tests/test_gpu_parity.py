@@ -1084,6 +1084,18 @@ def test_rows_of_all_classes_share_a_launch(dtype, widths):
                 if op == heta.HETA_MEAN:
                     ref, bound = ref / n.clamp_min(1), bound / n.clamp_min(1) * (1 + 1 / n.clamp_min(1)) + 2.0 ** -23 * (ref / n.clamp_min(1)).abs()
                 assert ((out.cpu().double() - ref).abs() <= bound).all(), (op, x.shape)
+        # behind the accumulation, an activation on every second relation: the rows are bitwise those of the two steps
+        for beta in (0.0, 1.0):
+            start = [torch.randn(o.shape, generator=gen).cuda() for o in outs]
+            plain, act = [x.clone() for x in start], [x.clone() for x in start]
+            heta.heta_rel_aggregate_fwd_multi(hg, list(range(5)), heta.HETA_SUM, dev, plain, betas=[beta] * 5)
+            heta.heta_rel_aggregate_fwd_multi_act(hg, list(range(5)), [heta.HETA_ACT_RELU if i % 2 == 0 else heta.HETA_ACT_NONE for i in range(5)],
+                                                  heta.HETA_SUM, dev, act, betas=[beta] * 5)
+            torch.cuda.synchronize()
+            for i in range(5):
+                assert torch.equal(act[i], plain[i].relu() if i % 2 == 0 else plain[i]), (beta, i)
+        with pytest.raises(heta.HetaError):
+            heta.heta_rel_aggregate_fwd_multi_act(hg, [0], [7], heta.HETA_SUM, dev[:1], outs[:1])
     finally:
         hg.destroy()
 
