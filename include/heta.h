@@ -429,6 +429,38 @@ heta_status heta_rel_attn_bwd_src(heta_graph *g, int32_t rel, const void *z, het
                                   const float *el, float slope, const float *pack, const float *grad_out, int64_t ld_go, float *dz,
                                   int64_t ld_dz, float *del, void *hip_stream);
 
+/* heta_rel_attn_fwd_train and heta_rel_attn_bwd_src for several relations of one call (same d, heads and element types):
+ * relations whose edges fill the chip only together share their launches.  Items run concurrently, so no two may write
+ * overlapping outputs (checked for out and out_pos, and dz); out_pos goes with every item or with none.  items: host
+ * array, read before the call returns.  n = 0 is a no-op.  Errors as the single calls, detected before anything is
+ * launched. */
+typedef struct heta_attn_fwd_item {
+    int32_t rel;
+    const void *z;           /* device, z_dt */
+    int64_t ld_z;
+    const float *el, *er;    /* device */
+    void *out;               /* device, out_dt */
+    int64_t ld_out;
+    float *smax, *sinv;      /* device or both NULL */
+    void *out_pos;           /* device, out_dt, or NULL */
+    int64_t ld_pos;
+    float *apos;             /* device or NULL */
+} heta_attn_fwd_item;
+typedef struct heta_attn_src_item {
+    int32_t rel;
+    const void *z;           /* device, z_dt */
+    int64_t ld_z;
+    const float *el, *pack, *grad_out; /* device */
+    int64_t ld_go;
+    float *dz;               /* device */
+    int64_t ld_dz;
+    float *del;              /* device */
+} heta_attn_src_item;
+heta_status heta_rel_attn_fwd_train_multi(heta_graph *g, int32_t n, const heta_attn_fwd_item *items, heta_dtype z_dt, int32_t d,
+                                          int32_t heads, float slope, heta_dtype out_dt, float beta, void *hip_stream);
+heta_status heta_rel_attn_bwd_src_multi(heta_graph *g, int32_t n, const heta_attn_src_item *items, heta_dtype z_dt, int32_t d,
+                                        int32_t heads, float slope, void *hip_stream);
+
 /* ---- k-hop neighbour sampling into blocks (Section 2.2 and the sampling step of Algorithm 1: a fixed
  * number of neighbours per relation is sampled, hop by hop, for the nodes of a mini-batch; fan-outs
  * {25, 20} in Section 8.1).  Rule: all in-edges of a destination if its in-degree is at most `fanout`,

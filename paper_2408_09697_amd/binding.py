@@ -32,7 +32,7 @@ EXPORTS = ["heta_graph_create", "heta_graph_create_batch", "heta_graph_destroy",
            "heta_profile_read", "heta_calibration_copy", "heta_calibration_mfma", "heta_cross_rel_project", "heta_cross_rel_project_bwd",
            "heta_cross_rel_project_wgrad", "heta_sparse_adam", "heta_project_batch",
            "heta_project_sum", "heta_project_wgrad_batch", "heta_attn_score", "heta_attn_score_bwd", "heta_attn_score_multi", "heta_attn_score_bwd_multi",
-           "heta_rel_attn_fwd", "heta_rel_attn_bwd", "heta_rel_attn_fwd_train", "heta_attn_bwd_dst", "heta_rel_attn_bwd_src",
+           "heta_rel_attn_fwd", "heta_rel_attn_bwd", "heta_rel_attn_fwd_train", "heta_rel_attn_fwd_train_multi", "heta_rel_attn_bwd_src_multi", "heta_attn_bwd_dst", "heta_rel_attn_bwd_src",
            "heta_sample_neighbors", "heta_unique_relabel",
            "heta_cross_rel_aggregate_project", "heta_meta_partition", "heta_sample_neighbors_batch",
            "heta_unique_relabel_batch", "heta_rel_aggregate_fwd_noalloc", "heta_attn_fold", "heta_attn_fold_bwd",
@@ -69,6 +69,18 @@ class _AggItem(ctypes.Structure):
     _fields_ = [("rel", ctypes.c_int32), ("d", ctypes.c_int32), ("inp", ctypes.c_void_p), ("ld_in", ctypes.c_int64),
                 ("n_table_rows", ctypes.c_int64), ("src_gid", ctypes.c_void_p), ("out", ctypes.c_void_p),
                 ("ld_out", ctypes.c_int64), ("beta", ctypes.c_float)]
+
+
+class _AttnFwdItem(ctypes.Structure):
+    _fields_ = [("rel", ctypes.c_int32), ("z", ctypes.c_void_p), ("ld_z", ctypes.c_int64), ("el", ctypes.c_void_p), ("er", ctypes.c_void_p),
+                ("out", ctypes.c_void_p), ("ld_out", ctypes.c_int64), ("smax", ctypes.c_void_p), ("sinv", ctypes.c_void_p),
+                ("out_pos", ctypes.c_void_p), ("ld_pos", ctypes.c_int64), ("apos", ctypes.c_void_p)]
+
+
+class _AttnSrcItem(ctypes.Structure):
+    _fields_ = [("rel", ctypes.c_int32), ("z", ctypes.c_void_p), ("ld_z", ctypes.c_int64), ("el", ctypes.c_void_p), ("pack", ctypes.c_void_p),
+                ("grad_out", ctypes.c_void_p), ("ld_go", ctypes.c_int64), ("dz", ctypes.c_void_p), ("ld_dz", ctypes.c_int64),
+                ("d_el", ctypes.c_void_p)]
 
 
 _lib = None
@@ -923,6 +935,60 @@ def heta_rel_attn_bwd_src(g: Graph, rel: int, z: torch.Tensor, el: torch.Tensor,
     _check(L.heta_rel_attn_bwd_src(g.handle, rel, _dev(z, "z"), _dt(z), _ld(z), d, heads, _scores(el, "el", n_src, heads), slope,
                                    _scores(pack, "pack", n_dst, 4 * heads), _dev(grad_out, "grad_out", torch.float32), _ld(grad_out),
                                    _dev(dz, "dz", torch.float32), _ld(dz), _scores(d_el, "del", n_src, heads), _stream(stream)))
+
+
+def heta_rel_attn_fwd_train_multi(g: Graph, rels: Sequence[int], z: Sequence[torch.Tensor], el: Sequence[torch.Tensor],
+                                  er: Sequence[torch.Tensor], slope: float, outs: Sequence[torch.Tensor], smax: Sequence[torch.Tensor],
+                                  sinv: Sequence[torch.Tensor], out_pos: Sequence[torch.Tensor], apos: Sequence[torch.Tensor],
+                                  stream=None) -> None:
+    """heta_rel_attn_fwd_train (beta = 0) for several relations at once; their outputs are distinct."""
+    n = len(rels)
+    if n == 0:
+        return
+    d, heads = z[0].shape[1], el[0].shape[1]
+    items = (_AttnFwdItem * n)()
+    for i, r in enumerate(rels):
+        n_src, n_dst = g.n_src(r), g.n_dst(r)
+        if z[i].shape[0] < n_src or outs[i].shape[0] < n_dst or out_pos[i].shape[0] < n_dst:
+            raise HetaError(HETA_ERR_SHAPE, "z / out / out_pos have fewer rows than the relation needs")
+        if z[i].dtype != z[0].dtype or z[i].shape[1] != d or any(o.dtype != outs[0].dtype for o in (outs[i], out_pos[i])):
+            raise HetaError(HETA_ERR_INVALID_ARG, "the items of one call share their width and element types")
+        it = items[i]
+        it.rel, it.z, it.ld_z = r, _dev(z[i], "z"), _ld(z[i])
+        it.el, it.er = _scores(el[i], "el", n_src, heads), _scores(er[i], "er", n_dst, heads)
+        it.out, it.ld_out, it.out_pos, it.ld_pos = _dev(outs[i], "out"), _ld(outs[i]), _dev(out_pos[i], "out_pos"), _ld(out_pos[i])
+        it.smax, it.sinv = _scores(smax[i], "smax", n_dst, heads), _scores(sinv[i], "sinv", n_dst, heads)
+        it.apos = _scores(apos[i], "apos", n_dst, heads)
+    L = load_library()
+    vp, i32, f32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_float
+    L.heta_rel_attn_fwd_train_multi.argtypes = [vp, i32, ctypes.POINTER(_AttnFwdItem), i32, i32, i32, f32, i32, f32, vp]
+    _check(L.heta_rel_attn_fwd_train_multi(g.handle, n, items, _dt(z[0]), d, heads, slope, _dt(outs[0]), 0.0, _stream(stream)))
+
+
+def heta_rel_attn_bwd_src_multi(g: Graph, rels: Sequence[int], z: Sequence[torch.Tensor], el: Sequence[torch.Tensor], slope: float,
+                                pack: Sequence[torch.Tensor], grad_outs: Sequence[torch.Tensor], dz: Sequence[torch.Tensor],
+                                d_el: Sequence[torch.Tensor], stream=None) -> None:
+    """heta_rel_attn_bwd_src for several relations at once; their outputs are distinct."""
+    n = len(rels)
+    if n == 0:
+        return
+    d, heads = z[0].shape[1], el[0].shape[1]
+    items = (_AttnSrcItem * n)()
+    for i, r in enumerate(rels):
+        n_src, n_dst = g.n_src(r), g.n_dst(r)
+        if z[i].shape[0] < n_src or dz[i].shape[0] < n_src or grad_outs[i].shape[0] < n_dst:
+            raise HetaError(HETA_ERR_SHAPE, "a buffer has fewer rows than the relation needs")
+        if z[i].dtype != z[0].dtype or z[i].shape[1] != d:
+            raise HetaError(HETA_ERR_INVALID_ARG, "the items of one call share their width and element types")
+        it = items[i]
+        it.rel, it.z, it.ld_z, it.el = r, _dev(z[i], "z"), _ld(z[i]), _scores(el[i], "el", n_src, heads)
+        it.pack = _scores(pack[i], "pack", n_dst, 4 * heads)
+        it.grad_out, it.ld_go = _dev(grad_outs[i], "grad_out", torch.float32), _ld(grad_outs[i])
+        it.dz, it.ld_dz, it.d_el = _dev(dz[i], "dz", torch.float32), _ld(dz[i]), _scores(d_el[i], "del", n_src, heads)
+    L = load_library()
+    vp, i32, f32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_float
+    L.heta_rel_attn_bwd_src_multi.argtypes = [vp, i32, ctypes.POINTER(_AttnSrcItem), i32, i32, i32, f32, vp]
+    _check(L.heta_rel_attn_bwd_src_multi(g.handle, n, items, _dt(z[0]), d, heads, slope, _stream(stream)))
 
 
 def heta_cross_rel_aggregate_project(g: Graph, dst_type: int, rels: List[int], op: int, tables: List[torch.Tensor],

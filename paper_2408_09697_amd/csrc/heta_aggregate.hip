@@ -930,15 +930,6 @@ static heta_status run_aggregate(heta_graph *g, const Schedule &s, AggParams p, 
 {
     (void)table_elems_ld;
     if (s.n_rows == 0) return HETA_OK;
-    if (p.slot_form == SLOT_BOTH && !agg_vectorized(p, in_dt)) { // the two-weight kernels exist for the 128-bit paths only: two passes otherwise
-        AggParams a = p, b = p;
-        a.slot_form = SLOT_FIRST;
-        b.slot_form = SLOT_SECOND;
-        b.out = p.out2;
-        b.ld_out = p.ld_out2;
-        heta_status e1 = run_aggregate(g, s, a, in_dt, table_elems_ld, st);
-        return e1 != HETA_OK ? e1 : run_aggregate(g, s, b, in_dt, table_elems_ld, st);
-    }
     AggPlan plan;
     heta_status e = plan_aggregate(s, p, in_dt, &plan);
     if (e != HETA_OK) return e;
@@ -991,49 +982,79 @@ static heta_status run_aggregate_multi(heta_graph *g, std::vector<AggPlan> &plan
     return HETA_OK;
 }
 
-// Weighted aggregation with one weight per (edge slot of the schedule, head): the second half of the
+// Weighted aggregations with one weight per (edge slot of the schedule, head): the second half of the
 // attention aggregation (heta_attention.hip computes the weights).
+heta_status aggregate_slot_weighted_multi(heta_graph *g, std::vector<SlotAggregation> &calls, heta_dtype dt, int d, int heads,
+                                          heta_dtype out_dt, float beta, bool two_sums, float neg, hipStream_t st)
+{
+    std::vector<AggPlan> plans;
+    for (SlotAggregation &c : calls) {
+        AggParams p{};
+        p.table = c.table;
+        p.ld = c.ld;
+        p.slot_w = c.slot_w;
+        p.slot_form = two_sums ? SLOT_BOTH : SLOT_RAW;
+        p.slot_neg = neg;
+        p.out2 = c.out2;
+        p.ld_out2 = c.ld_out2;
+        p.heads = heads;
+        p.head_dim = d / heads;
+        p.out = c.out;
+        p.ld_out = c.ld_out;
+        p.out_bf16 = (out_dt == HETA_BF16);
+        p.beta = beta;
+        p.d = d;
+        c.dot_done = false;
+        const SecondSumDot &dot = c.dot;
+        if (two_sums && dot.z && dot.out) {
+            // the dot form needs: the 128-bit path, one chunk per lane (a row inside one lane group), heads that are a
+            // power-of-two number of chunks wide for both the row kernels' chunk (16 bytes of the gathered type) and the
+            // hub combine's (4 columns), z rows whose chunks are aligned, a single 256-column tile in the combine
+            const int epc = static_cast<int>(16 / dtype_size(dt));
+            const int hd = p.head_dim, lph = hd / epc, lph4 = hd / 4;
+            const size_t zsz = dtype_size(dot.z_dt);
+            const bool ok = agg_vectorized(p, dt) && d % epc == 0 && d / epc <= 64 && d <= 256 && hd % epc == 0 && hd % 4 == 0 &&
+                            lph > 0 && (lph & (lph - 1)) == 0 && (lph4 & (lph4 - 1)) == 0 &&
+                            reinterpret_cast<uintptr_t>(dot.z) % (epc * zsz) == 0 && dot.ld_z % epc == 0;
+            if (ok) {
+                p.dot_z = dot.z;
+                p.ld_z = dot.ld_z;
+                p.dot_z_bf16 = dot.z_dt == HETA_BF16;
+                p.dot_corr = dot.corr;
+                p.dot_out = dot.out;
+                c.dot_done = true;
+            }
+        }
+        if (c.s->n_rows == 0) continue;
+        if (two_sums && !agg_vectorized(p, dt)) { // the two-weight kernels exist for the 128-bit paths only: two passes otherwise
+            for (const SlotForm form : {SLOT_FIRST, SLOT_SECOND}) {
+                AggParams one = p;
+                one.slot_form = form;
+                if (form == SLOT_SECOND) {
+                    one.out = p.out2;
+                    one.ld_out = p.ld_out2;
+                }
+                AggPlan pl;
+                const heta_status e = plan_aggregate(*c.s, one, dt, &pl);
+                if (e != HETA_OK) return e;
+                plans.push_back(pl);
+            }
+            continue;
+        }
+        AggPlan pl;
+        const heta_status e = plan_aggregate(*c.s, p, dt, &pl);
+        if (e != HETA_OK) return e;
+        plans.push_back(pl);
+    }
+    return run_aggregate_multi(g, plans, st);
+}
+
 heta_status aggregate_slot_weighted(heta_graph *g, const Schedule &s, const void *table, heta_dtype dt, int64_t ld,
                                     int d, const float *slot_w, int heads, void *out, heta_dtype out_dt,
-                                    int64_t ld_out, float beta, hipStream_t st, bool two_sums, float neg, void *out2,
-                                    int64_t ld_out2, const SecondSumDot *dot, bool *dot_done)
+                                    int64_t ld_out, float beta, hipStream_t st)
 {
-    AggParams p{};
-    p.table = table;
-    p.ld = ld;
-    p.slot_w = slot_w;
-    p.slot_form = two_sums ? SLOT_BOTH : SLOT_RAW;
-    p.slot_neg = neg;
-    p.out2 = out2;
-    p.ld_out2 = ld_out2;
-    p.heads = heads;
-    p.head_dim = d / heads;
-    p.out = out;
-    p.ld_out = ld_out;
-    p.out_bf16 = (out_dt == HETA_BF16);
-    p.beta = beta;
-    p.d = d;
-    if (dot_done) *dot_done = false;
-    if (dot && two_sums && dot->z && dot->out) {
-        // the dot form needs: the 128-bit path, one chunk per lane (a row inside one lane group), heads that are a
-        // power-of-two number of chunks wide for both the row kernels' chunk (16 bytes of the gathered type) and the
-        // hub combine's (4 columns), z rows whose chunks are aligned, a single 256-column tile in the combine
-        const int epc = static_cast<int>(16 / dtype_size(dt));
-        const int hd = p.head_dim, lph = hd / epc, lph4 = hd / 4;
-        const size_t zsz = dtype_size(dot->z_dt);
-        const bool ok = agg_vectorized(p, dt) && d % epc == 0 && d / epc <= 64 && d <= 256 && hd % epc == 0 && hd % 4 == 0 &&
-                        lph > 0 && (lph & (lph - 1)) == 0 && (lph4 & (lph4 - 1)) == 0 &&
-                        reinterpret_cast<uintptr_t>(dot->z) % (epc * zsz) == 0 && dot->ld_z % epc == 0;
-        if (ok) {
-            p.dot_z = dot->z;
-            p.ld_z = dot->ld_z;
-            p.dot_z_bf16 = dot->z_dt == HETA_BF16;
-            p.dot_corr = dot->corr;
-            p.dot_out = dot->out;
-            if (dot_done) *dot_done = true;
-        }
-    }
-    return run_aggregate(g, s, p, dt, ld, st);
+    std::vector<SlotAggregation> one(1, SlotAggregation{&s, table, ld, slot_w, out, ld_out, nullptr, 0, {}, false});
+    return aggregate_slot_weighted_multi(g, one, dt, d, heads, out_dt, beta, false, 0.f, st);
 }
 
 // The hub rows of a schedule only (rows of at least kHubMinDeg edges), reduced into a compact fp32

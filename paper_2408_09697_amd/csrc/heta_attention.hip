@@ -24,6 +24,8 @@
 // i.e. the per-edge dot products of the softmax backward collapse, by linearity, into weighted
 // aggregations followed by one per-row, per-head dot product.  No atomics anywhere.
 #include <algorithm>
+#include <new>
+#include <vector>
 
 #include "heta_internal.h"
 
@@ -349,13 +351,25 @@ template <int KT, int OP> __device__ __forceinline__ void sweep_hub_chunk(const 
     }
 }
 
-// All row classes of a schedule in one launch: the class follows from the workgroup's index (uniform).
-template <int KT, int OP>
-__global__ void __launch_bounds__(256) attn_rows_kernel(SweepParams p)
+// Up to N relations of one call; first: the first workgroup of each in a launch over all of them.
+constexpr int kSweepMulti = 8;
+template <int N> struct SweepMulti {
+    SweepParams p[N];
+    unsigned first[N];
+};
+static_assert(sizeof(SweepMulti<kSweepMulti>) <= 3840, "kernel arguments are limited to 4 KB");
+
+// All row classes of all schedules in one launch: relation and class follow from the workgroup's index (uniform).
+template <int KT, int OP, int N>
+__global__ void __launch_bounds__(256) attn_rows_kernel(SweepMulti<N> m)
 {
+    int i = 0;
+#pragma unroll
+    for (int j = 1; j < N; ++j) i += blockIdx.x >= m.first[j] ? 1 : 0;
+    const SweepParams &p = m.p[i];
     const int lane = threadIdx.x & 63;
     const int k0 = blockIdx.y * KT;
-    const unsigned b = p.b_first + blockIdx.x;
+    const unsigned b = p.b_first + (blockIdx.x - m.first[i]);
     if (b < p.b_wave) {
         const int64_t w = static_cast<int64_t>(b) * 4 + (threadIdx.x >> 6);
         if (w < p.n_hub_chunks) sweep_hub_chunk<KT, OP>(p, w, lane, k0); // uniform per wavefront
@@ -372,9 +386,11 @@ __global__ void __launch_bounds__(256) attn_rows_kernel(SweepParams p)
 }
 
 // hub rows, second kernel: one wavefront per (hub row, head) combines the row's chunks in chunk order
-template <int OP>
-__global__ void __launch_bounds__(256) attn_hub_combine_kernel(SweepParams p)
+// (blockIdx.z: the relation)
+template <int OP, int N>
+__global__ void __launch_bounds__(256) attn_hub_combine_kernel(SweepMulti<N> m)
 {
+    const SweepParams &p = m.p[blockIdx.z];
     const int lane = threadIdx.x & 63;
     const int64_t h = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (h >= p.n_hub_rows) return;
@@ -413,9 +429,10 @@ __global__ void __launch_bounds__(256) attn_hub_combine_kernel(SweepParams p)
 }
 
 // hub chunks, third kernel (forward): the weights, from the combined statistics
-template <int KT>
-__global__ void __launch_bounds__(256) attn_hub_alpha_kernel(SweepParams p)
+template <int KT, int N>
+__global__ void __launch_bounds__(256) attn_hub_alpha_kernel(SweepMulti<N> all)
 {
+    const SweepParams &p = all.p[blockIdx.z];
     const int lane = threadIdx.x & 63;
     const int64_t w = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (w >= p.n_hub_chunks) return;
@@ -446,64 +463,118 @@ inline size_t hub_scratch_bytes(const Schedule &s, int K)
     return static_cast<size_t>(s.n_hub_chunks * 3 + s.n_hub_rows * 2) * K * sizeof(float);
 }
 
-template <int KT, int OP>
-heta_status launch_sweeps_kt(const Schedule &s, SweepParams p, hipStream_t st)
+// One sweep of a call: the schedule, its parameters, and hub_scratch_bytes of device memory for the hub rows' statistics.
+struct Sweep {
+    const Schedule *s;
+    SweepParams p;
+    float *hub_scratch;
+    int64_t blocks; // filled in below
+};
+
+template <int KT, int OP, int N>
+heta_status launch_sweeps_n(const Sweep *sw, int n, hipStream_t st)
 {
-    const unsigned gy = p.K / KT;
-    p.q_wave = s.n_hub_rows;
-    p.q_mid = s.rows_with_deg_ge[kShortDegAttn];
-    p.q_short = s.rows_with_deg_ge[kThreadDegAttn + 1];
-    p.n_rows = s.n_rows;
-    const int64_t cb = (s.n_hub_chunks + 3) / 4;
-    const int64_t wb = (p.q_mid - p.q_wave + 3) / 4, mb = (p.q_short - p.q_mid + 31) / 32, sb = (p.n_rows - p.q_short + 255) / 256;
-    if (cb + wb + mb + sb > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "attention: too many rows");
-    p.b_wave = (unsigned)cb;
-    p.b_mid = (unsigned)(cb + wb);
-    p.b_short = (unsigned)(cb + wb + mb);
-    // (eight lanes per row: 2^29 rows of 5 to 31 edges are more threads than a grid takes)
-    launch_pieces(cb + wb + mb + sb, 256, [&](unsigned first, unsigned count) {
-        p.b_first = first;
-        hipLaunchKernelGGL((attn_rows_kernel<KT, OP>), dim3(count, gy), dim3(256), 0, st, p);
-    });
+    SweepMulti<N> m{};
+    int64_t total = 0, hub_rows = 0, hub_blocks = 0;
+    for (int i = 0; i < N; ++i) {
+        m.first[i] = static_cast<unsigned>(total);
+        if (i >= n) {
+            m.first[i] = 0xffffffffu; // no workgroup reaches it
+            continue;
+        }
+        m.p[i] = sw[i].p;
+        total += sw[i].blocks;
+        hub_rows = std::max(hub_rows, sw[i].s->n_hub_rows);
+        hub_blocks = std::max(hub_blocks, (sw[i].s->n_hub_chunks + 3) / 4);
+    }
+    const unsigned K = sw[0].p.K, gy = K / KT;
+    if (N == 1) {
+        // (eight lanes per row: 2^29 rows of 5 to 31 edges are more threads than a grid takes)
+        launch_pieces(total, 256, [&](unsigned first, unsigned count) {
+            m.p[0].b_first = first;
+            hipLaunchKernelGGL((attn_rows_kernel<KT, OP, N>), dim3(count, gy), dim3(256), 0, st, m);
+        });
+    } else {
+        hipLaunchKernelGGL((attn_rows_kernel<KT, OP, N>), dim3((unsigned)total, gy), dim3(256), 0, st, m);
+    }
     HETA_LAUNCH_CHECK("attn_rows_kernel");
-    if (s.n_hub_rows > 0) {
-        hipLaunchKernelGGL((attn_hub_combine_kernel<OP>), dim3((unsigned)((s.n_hub_rows + 3) / 4), p.K), dim3(256), 0, st, p);
+    if (hub_rows > 0) {
+        hipLaunchKernelGGL((attn_hub_combine_kernel<OP, N>), dim3((unsigned)((hub_rows + 3) / 4), K, n), dim3(256), 0, st, m);
         HETA_LAUNCH_CHECK("attn_hub_combine_kernel");
         if (OP == SWEEP_FWD) {
-            hipLaunchKernelGGL((attn_hub_alpha_kernel<KT>), dim3((unsigned)cb, gy), dim3(256), 0, st, p);
+            hipLaunchKernelGGL((attn_hub_alpha_kernel<KT, N>), dim3((unsigned)hub_blocks, gy, n), dim3(256), 0, st, m);
             HETA_LAUNCH_CHECK("attn_hub_alpha_kernel");
         }
     }
     return HETA_OK;
 }
 
-// `hub_scratch`: hub_scratch_bytes(s, K) bytes of device memory for the hub rows' partial statistics
-template <int OP>
-heta_status launch_sweeps(const Schedule &s, SweepParams p, float *hub_scratch, hipStream_t st, const char *name)
+template <int KT, int OP>
+heta_status launch_sweeps_kt(Sweep *sw, int n, hipStream_t st)
 {
-    if (s.n_rows == 0) return HETA_OK;
-    p.sptr = s.d_sptr;
-    p.sidx = s.d_sidx;
-    p.perm = s.d_perm;
-    p.hub_chunks = s.d_hub_chunks;
-    p.hub_chunk_ptr = s.d_hub_chunk_ptr;
-    p.n_hub_rows = s.n_hub_rows;
-    p.n_hub_chunks = s.n_hub_chunks;
-    p.part = hub_scratch;
-    p.hub_stat = hub_scratch + s.n_hub_chunks * p.K * 3;
-    // Algorithmic bytes: per edge one 4-byte id, per edge and head the neighbour's 4-byte terms and the
-    // 4-byte weights written; per row its offsets and per-head terms.
-    const double per_edge = 4.0 + p.K * (OP == SWEEP_BWD_CSC ? 20.0 : 8.0);
-    ProfScope prof(name, st, per_edge * static_cast<double>(s.n_edges) + static_cast<double>(s.n_rows) * (12.0 + 12.0 * p.K), 0);
-    // KT consecutive heads per thread need 4*KT-byte aligned score rows
-    const uintptr_t all = reinterpret_cast<uintptr_t>(p.row_a) | reinterpret_cast<uintptr_t>(p.nbr_a) |
-                          reinterpret_cast<uintptr_t>(p.smax) | reinterpret_cast<uintptr_t>(p.sinv) |
-                          reinterpret_cast<uintptr_t>(p.dot) | reinterpret_cast<uintptr_t>(p.nbr_pack) | reinterpret_cast<uintptr_t>(p.alpha) |
-                          reinterpret_cast<uintptr_t>(p.gate) | reinterpret_cast<uintptr_t>(p.corr) | reinterpret_cast<uintptr_t>(p.apos);
-    if (p.K % 8 == 0 && all % 16 == 0) return launch_sweeps_kt<8, OP>(s, p, st);
-    if (p.K % 4 == 0 && all % 16 == 0) return launch_sweeps_kt<4, OP>(s, p, st);
-    if (p.K % 2 == 0 && all % 8 == 0) return launch_sweeps_kt<2, OP>(s, p, st);
-    return launch_sweeps_kt<1, OP>(s, p, st);
+    int64_t total = 0;
+    for (int i = 0; i < n; ++i) {
+        const Schedule &s = *sw[i].s;
+        SweepParams &p = sw[i].p;
+        p.q_wave = s.n_hub_rows;
+        p.q_mid = s.rows_with_deg_ge[kShortDegAttn];
+        p.q_short = s.rows_with_deg_ge[kThreadDegAttn + 1];
+        p.n_rows = s.n_rows;
+        const int64_t cb = (s.n_hub_chunks + 3) / 4;
+        const int64_t wb = (p.q_mid - p.q_wave + 3) / 4, mb = (p.q_short - p.q_mid + 31) / 32, sb = (p.n_rows - p.q_short + 255) / 256;
+        if (cb + wb + mb + sb > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "attention: too many rows");
+        p.b_wave = (unsigned)cb;
+        p.b_mid = (unsigned)(cb + wb);
+        p.b_short = (unsigned)(cb + wb + mb);
+        p.b_first = 0;
+        sw[i].blocks = cb + wb + mb + sb;
+        total += sw[i].blocks;
+    }
+    if (n > 1 && n <= kSweepMulti && total <= max_blocks(256)) return launch_sweeps_n<KT, OP, kSweepMulti>(sw, n, st);
+    for (int i = 0; i < n; ++i) {
+        const heta_status e = launch_sweeps_n<KT, OP, 1>(sw + i, 1, st);
+        if (e != HETA_OK) return e;
+    }
+    return HETA_OK;
+}
+
+// One kind of sweep over several relations of one head count.
+template <int OP>
+heta_status launch_sweeps(std::vector<Sweep> &sw, hipStream_t st, const char *name)
+{
+    sw.erase(std::remove_if(sw.begin(), sw.end(), [](const Sweep &x) { return x.s->n_rows == 0; }), sw.end());
+    if (sw.empty()) return HETA_OK;
+    const int K = sw[0].p.K;
+    double bytes = 0;
+    uintptr_t all = 0;
+    for (Sweep &x : sw) {
+        const Schedule &s = *x.s;
+        SweepParams &p = x.p;
+        p.sptr = s.d_sptr;
+        p.sidx = s.d_sidx;
+        p.perm = s.d_perm;
+        p.hub_chunks = s.d_hub_chunks;
+        p.hub_chunk_ptr = s.d_hub_chunk_ptr;
+        p.n_hub_rows = s.n_hub_rows;
+        p.n_hub_chunks = s.n_hub_chunks;
+        p.part = x.hub_scratch;
+        p.hub_stat = x.hub_scratch + s.n_hub_chunks * p.K * 3;
+        // Algorithmic bytes: per edge one 4-byte id, per edge and head the neighbour's 4-byte terms and the
+        // 4-byte weight written; per row its offsets and per-head terms.
+        const double per_edge = 4.0 + K * (OP == SWEEP_BWD_CSC ? 20.0 : 8.0);
+        bytes += per_edge * static_cast<double>(s.n_edges) + static_cast<double>(s.n_rows) * (12.0 + 12.0 * K);
+        // KT consecutive heads per thread need 4*KT-byte aligned score rows
+        all |= reinterpret_cast<uintptr_t>(p.row_a) | reinterpret_cast<uintptr_t>(p.nbr_a) | reinterpret_cast<uintptr_t>(p.smax) |
+               reinterpret_cast<uintptr_t>(p.sinv) | reinterpret_cast<uintptr_t>(p.dot) | reinterpret_cast<uintptr_t>(p.nbr_pack) |
+               reinterpret_cast<uintptr_t>(p.alpha) | reinterpret_cast<uintptr_t>(p.gate) | reinterpret_cast<uintptr_t>(p.corr) |
+               reinterpret_cast<uintptr_t>(p.apos);
+    }
+    ProfScope prof(name, st, bytes, 0);
+    const int n = static_cast<int>(sw.size());
+    if (K % 8 == 0 && all % 16 == 0) return launch_sweeps_kt<8, OP>(sw.data(), n, st);
+    if (K % 4 == 0 && all % 16 == 0) return launch_sweeps_kt<4, OP>(sw.data(), n, st);
+    if (K % 2 == 0 && all % 8 == 0) return launch_sweeps_kt<2, OP>(sw.data(), n, st);
+    return launch_sweeps_kt<1, OP>(sw.data(), n, st);
 }
 
 // ---- per-row, per-head dot products -------------------------------------------------------------------
@@ -1498,42 +1569,76 @@ heta_status check_attn_args(const char *fn, heta_graph *g, int32_t rel, int32_t 
     return HETA_OK;
 }
 
-// Source side of the backward: alpha and gate per CSC slot; one pass over the gathered gradient rows gives both
-// dz[u] = sum_e alpha_e g[v_e] and R[u] = sum_e gate_e g[v_e]; del = <z, R> - sum_e gate_e dot[v_e].
-heta_status attn_source_side(heta_graph *g, const Relation &r, const void *z, heta_dtype z_dt, int64_t ld_z, int d, int K, const float *el,
-                             float slope, const float *nbr_pack, const float *grad_out, int64_t ld_go, float *dz, int64_t ld_dz, float *del,
-                             float *w_alpha, float *corr_s, float *R, int64_t ld_r, float *hub_scratch, hipStream_t st)
+// Source side of one relation's backward, checked and with its workspace assigned.
+struct SourceSide {
+    const Relation *r;
+    const void *z;
+    heta_dtype z_dt;
+    int64_t ld_z;
+    const float *el, *nbr_pack, *grad_out;
+    int64_t ld_go;
+    float *dz;
+    int64_t ld_dz;
+    float *del;
+    float *w_alpha, *corr_s, *R, *hub_scratch; // workspace
+    int64_t ld_r;
+};
+
+// alpha per CSC slot, its sign bit set where the logit is not positive; one pass over the gathered gradient rows gives both
+// dz[u] = sum_e alpha_e g[v_e] and R[u] = sum_e gate_e g[v_e], gate_e = alpha_e LeakyReLU'; del = <z, R> - sum_e gate_e dot[v_e].
+heta_status attn_source_side(heta_graph *g, const SourceSide *it, int n, int d, int K, float slope, hipStream_t st)
 {
-    SweepParams sp{};
-    sp.K = K;
-    sp.slope = slope;
-    sp.row_a = el;
-    sp.nbr_pack = nbr_pack;
-    sp.alpha = w_alpha;
-    sp.corr = corr_s;
-    heta_status e = launch_sweeps<SWEEP_BWD_CSC>(r.csc, sp, hub_scratch, st, "attn_sweep_bwd_src");
+    std::vector<Sweep> sw;
+    for (int i = 0; i < n; ++i) {
+        SweepParams sp{};
+        sp.K = K;
+        sp.slope = slope;
+        sp.row_a = it[i].el;
+        sp.nbr_pack = it[i].nbr_pack;
+        sp.alpha = it[i].w_alpha;
+        sp.corr = it[i].corr_s;
+        sw.push_back({&it[i].r->csc, sp, it[i].hub_scratch, 0});
+    }
+    heta_status e = launch_sweeps<SWEEP_BWD_CSC>(sw, st, "attn_sweep_bwd_src");
     if (e != HETA_OK) return e;
     // del = <z, R> - corr_s is taken inside the aggregation when the shapes allow it (R is then never written)
-    const SecondSumDot zr{z, z_dt, ld_z, corr_s, del};
-    bool dot_done = false;
-    e = aggregate_slot_weighted(g, r.csc, grad_out, HETA_F32, ld_go, d, w_alpha, K, dz, HETA_F32, ld_dz, 0.f, st, true, slope, R, ld_r,
-                                &zr, &dot_done);
-    if (e != HETA_OK || dot_done) return e;
-    DotParams dp{};
-    dp.x = z;
-    dp.ld_x = ld_z;
-    dp.y = R;
-    dp.ld_y = ld_r;
-    dp.n = r.n_src;
-    dp.d = d;
-    dp.K = K;
-    dp.F = d / K;
-    dp.per_head = 1;
-    dp.scale = 1.f;
-    dp.corr = corr_s;
-    dp.out = del;
-    return launch_rowdot(dp, z_dt, HETA_F32, st);
+    std::vector<SlotAggregation> calls;
+    for (int i = 0; i < n; ++i)
+        calls.push_back({&it[i].r->csc, it[i].grad_out, it[i].ld_go, it[i].w_alpha, it[i].dz, it[i].ld_dz, it[i].R, it[i].ld_r,
+                         {it[i].z, it[i].z_dt, it[i].ld_z, it[i].corr_s, it[i].del}, false});
+    e = aggregate_slot_weighted_multi(g, calls, HETA_F32, d, K, HETA_F32, 0.f, true, slope, st);
+    for (int i = 0; e == HETA_OK && i < n; ++i) {
+        if (calls[i].dot_done) continue;
+        DotParams dp{};
+        dp.x = it[i].z;
+        dp.ld_x = it[i].ld_z;
+        dp.y = it[i].R;
+        dp.ld_y = it[i].ld_r;
+        dp.n = it[i].r->n_src;
+        dp.d = d;
+        dp.K = K;
+        dp.F = d / K;
+        dp.per_head = 1;
+        dp.scale = 1.f;
+        dp.corr = it[i].corr_s;
+        dp.out = it[i].del;
+        e = launch_rowdot(dp, it[i].z_dt, HETA_F32, st);
+    }
+    return e;
 }
+
+// Relations of one call share their launches while their workspace stays below this: larger ones fill the chip by
+// themselves (seven relations of 0.06 - 0.4 M edges, 64 columns and 8 heads together: 0.2 GB; one of 4 M edges and 256
+// columns alone: 1.2 GB).
+constexpr size_t kAttnGroupBytes = size_t(256) << 20;
+
+// an output of one item of a multi call, as a byte range
+struct OutRange {
+    uintptr_t lo, hi;
+    OutRange(const void *p, int64_t rows, int64_t ld, int d, size_t esz)
+        : lo(reinterpret_cast<uintptr_t>(p)), hi(p && rows > 0 ? lo + static_cast<uintptr_t>((rows - 1) * ld + d) * esz : lo) {}
+    bool overlaps(const OutRange &o) const { return lo < o.hi && o.lo < hi; }
+};
 
 } // namespace
 
@@ -1848,39 +1953,85 @@ heta_status heta_rel_attn_fwd_train(heta_graph *g, int32_t rel, const void *z, h
                                     heta_dtype out_dt, int64_t ld_out, float beta, float *smax, float *sinv, void *out_pos,
                                     int64_t ld_pos, float *apos, void *hip_stream)
 {
-    heta_status e = check_attn_args("heta_rel_attn_fwd", g, rel, d, heads);
-    if (e != HETA_OK) return e;
-    if (!z || !el || !er || !out || ((smax == nullptr) != (sinv == nullptr)))
-        return fail(HETA_ERR_INVALID_ARG, "heta_rel_attn_fwd: null argument (smax and sinv go together)");
-    if (!valid_dtype(z_dt) || !valid_dtype(out_dt)) return fail(HETA_ERR_INVALID_ARG, "heta_rel_attn_fwd: bad dtype");
-    if (ld_z < d || ld_out < d || (out_pos && ld_pos < d)) return fail(HETA_ERR_SHAPE, "heta_rel_attn_fwd: need d <= ld");
-    if (beta != 0.f && beta != 1.f) return fail(HETA_ERR_SHAPE, "heta_rel_attn_fwd: beta must be 0 or 1");
-    if (out_pos && beta != 0.f) return fail(HETA_ERR_SHAPE, "heta_rel_attn_fwd: out_pos needs beta = 0");
-    if (reinterpret_cast<uintptr_t>(z) % dtype_size(z_dt) || reinterpret_cast<uintptr_t>(out) % dtype_size(out_dt) ||
-        reinterpret_cast<uintptr_t>(out_pos) % dtype_size(out_dt))
-        return fail(HETA_ERR_INVALID_ARG, "heta_rel_attn_fwd: pointer not aligned to its element size");
-    const Relation &r = g->rels[rel];
+    const heta_attn_fwd_item it = {rel, z, ld_z, el, er, out, ld_out, smax, sinv, out_pos, ld_pos, apos};
+    return heta_rel_attn_fwd_train_multi(g, 1, &it, z_dt, d, heads, slope, out_dt, beta, hip_stream);
+}
+
+heta_status heta_rel_attn_fwd_train_multi(heta_graph *g, int32_t n, const heta_attn_fwd_item *items, heta_dtype z_dt, int32_t d, int32_t heads,
+                                          float slope, heta_dtype out_dt, float beta, void *hip_stream)
+{
+    if (n < 0 || (n > 0 && !items)) return fail(HETA_ERR_INVALID_ARG, "heta_rel_attn_fwd: bad item array");
+    heta_status e = HETA_OK;
+    for (int32_t i = 0; i < n; ++i) {
+        const heta_attn_fwd_item &it = items[i];
+        e = check_attn_args("heta_rel_attn_fwd", g, it.rel, d, heads);
+        if (e != HETA_OK) return e;
+        if (!it.z || !it.el || !it.er || !it.out || ((it.smax == nullptr) != (it.sinv == nullptr)))
+            return fail(HETA_ERR_INVALID_ARG, "heta_rel_attn_fwd: null argument (smax and sinv go together)");
+        if ((it.out_pos == nullptr) != (items[0].out_pos == nullptr))
+            return fail(HETA_ERR_INVALID_ARG, "heta_rel_attn_fwd: out_pos goes with every item or with none");
+        if (!valid_dtype(z_dt) || !valid_dtype(out_dt)) return fail(HETA_ERR_INVALID_ARG, "heta_rel_attn_fwd: bad dtype");
+        if (it.ld_z < d || it.ld_out < d || (it.out_pos && it.ld_pos < d)) return fail(HETA_ERR_SHAPE, "heta_rel_attn_fwd: need d <= ld");
+        if (beta != 0.f && beta != 1.f) return fail(HETA_ERR_SHAPE, "heta_rel_attn_fwd: beta must be 0 or 1");
+        if (it.out_pos && beta != 0.f) return fail(HETA_ERR_SHAPE, "heta_rel_attn_fwd: out_pos needs beta = 0");
+        if (reinterpret_cast<uintptr_t>(it.z) % dtype_size(z_dt) || reinterpret_cast<uintptr_t>(it.out) % dtype_size(out_dt) ||
+            reinterpret_cast<uintptr_t>(it.out_pos) % dtype_size(out_dt))
+            return fail(HETA_ERR_INVALID_ARG, "heta_rel_attn_fwd: pointer not aligned to its element size");
+    }
+    const size_t osz = dtype_size(out_dt);
+    const auto range = [&](int32_t i, bool pos) {
+        const heta_attn_fwd_item &it = items[i];
+        return OutRange(pos ? it.out_pos : it.out, g->rels[it.rel].n_dst, pos ? it.ld_pos : it.ld_out, d, osz);
+    };
+    for (int32_t i = 0; i < n; ++i)
+        for (int32_t j = 0; j < i; ++j)
+            for (int k = 0; k < 4; ++k)
+                if (range(i, k & 1).overlaps(range(j, k >> 1)))
+                    return fail(HETA_ERR_INVALID_ARG, "heta_rel_attn_fwd: the outputs of items %d and %d overlap", j, i);
     hipStream_t st = as_stream(hip_stream);
-    const size_t a_bytes = std::max<size_t>(256, round256(static_cast<size_t>(r.n_edges) * heads * sizeof(float)));
-    e = ensure_attn(g, a_bytes + hub_scratch_bytes(r.csr, heads));
-    if (e != HETA_OK) return e;
-    char *base = static_cast<char *>(g->d_attn);
-    float *alpha = reinterpret_cast<float *>(base);
-    float *hub_scratch = reinterpret_cast<float *>(base + a_bytes);
-    SweepParams sp{};
-    sp.K = heads;
-    sp.slope = slope;
-    sp.row_a = er;
-    sp.nbr_a = el;
-    sp.smax = smax;
-    sp.sinv = sinv;
-    sp.alpha = alpha;
-    sp.sign = out_pos != nullptr;
-    sp.apos = apos;
-    e = launch_sweeps<SWEEP_FWD>(r.csr, sp, hub_scratch, st, "attn_sweep_fwd");
-    if (e != HETA_OK) return e;
-    return aggregate_slot_weighted(g, r.csr, z, z_dt, ld_z, d, alpha, heads, out, out_dt, ld_out, beta, st, out_pos != nullptr, 0.f, out_pos,
-                                   ld_pos);
+    const auto need = [&](int32_t i) {
+        const Relation &r = g->rels[items[i].rel];
+        return std::max<size_t>(256, round256(static_cast<size_t>(r.n_edges) * heads * sizeof(float))) + round256(hub_scratch_bytes(r.csr, heads));
+    };
+    try {
+        for (int32_t i0 = 0; i0 < n;) {
+            int32_t i1 = i0;
+            size_t bytes = 0;
+            while (i1 < n && (i1 == i0 || bytes + need(i1) <= kAttnGroupBytes)) bytes += need(i1++);
+            e = ensure_attn(g, bytes);
+            if (e != HETA_OK) return e;
+            char *base = static_cast<char *>(g->d_attn);
+            std::vector<Sweep> sw;
+            std::vector<SlotAggregation> calls;
+            for (int32_t i = i0; i < i1; ++i) {
+                const heta_attn_fwd_item &it = items[i];
+                const Relation &r = g->rels[it.rel];
+                SweepParams sp{};
+                sp.K = heads;
+                sp.slope = slope;
+                sp.row_a = it.er;
+                sp.nbr_a = it.el;
+                sp.smax = it.smax;
+                sp.sinv = it.sinv;
+                sp.alpha = reinterpret_cast<float *>(base);
+                sp.sign = it.out_pos != nullptr;
+                sp.apos = it.apos;
+                float *hub_scratch = reinterpret_cast<float *>(base + need(i) - round256(hub_scratch_bytes(r.csr, heads)));
+                sw.push_back({&r.csr, sp, hub_scratch, 0});
+                calls.push_back({&r.csr, it.z, it.ld_z, sp.alpha, it.out, it.ld_out, it.out_pos, it.ld_pos, {}, false});
+                base += need(i);
+            }
+            e = launch_sweeps<SWEEP_FWD>(sw, st, "attn_sweep_fwd");
+            if (e == HETA_OK) e = aggregate_slot_weighted_multi(g, calls, z_dt, d, heads, out_dt, beta, items[0].out_pos != nullptr, 0.f, st);
+            if (e != HETA_OK) return e;
+            i0 = i1;
+        }
+        return HETA_OK;
+    } catch (const std::bad_alloc &) {
+        return fail(HETA_ERR_OOM, "heta_rel_attn_fwd: host allocation failed");
+    } catch (...) {
+        return fail(HETA_ERR_DEVICE, "heta_rel_attn_fwd: unexpected exception");
+    }
 }
 
 heta_status heta_rel_attn_bwd(heta_graph *g, int32_t rel, const void *z, heta_dtype z_dt, int64_t ld_z, int32_t d,
@@ -1945,6 +2096,7 @@ heta_status heta_rel_attn_bwd(heta_graph *g, int32_t rel, const void *z, heta_dt
     if (e != HETA_OK) return e;
     dp.y2 = nullptr;
 
+    try {
     // Destination side: der = sum_e gate_e <g, z[u_e]> - dot * sum_e gate_e, gate_e = alpha_e * LeakyReLU'.
     SweepParams sp{};
     sp.K = K;
@@ -1961,7 +2113,8 @@ heta_status heta_rel_attn_bwd(heta_graph *g, int32_t rel, const void *z, heta_dt
         // and no feature row is gathered on this side.
         sp.gate = nullptr;
         sp.dot_shift = slope;
-        e = launch_sweeps<SWEEP_BWD_CSR>(r.csr, sp, hub_scratch, st, "attn_sweep_bwd_dst");
+        std::vector<Sweep> sw(1, Sweep{&r.csr, sp, hub_scratch, 0});
+        e = launch_sweeps<SWEEP_BWD_CSR>(sw, st, "attn_sweep_bwd_dst");
         if (e != HETA_OK) return e;
         const int64_t total = r.n_dst * K;
         if (total > 0) {
@@ -1972,7 +2125,8 @@ heta_status heta_rel_attn_bwd(heta_graph *g, int32_t rel, const void *z, heta_dt
         // without it: R[v] = sum_e gate_e z[u_e] by one more weighted aggregation over the CSR
         sp.gate = w_gate;
         sp.dot_shift = 0.f;
-        e = launch_sweeps<SWEEP_BWD_CSR>(r.csr, sp, hub_scratch, st, "attn_sweep_bwd_dst");
+        std::vector<Sweep> sw(1, Sweep{&r.csr, sp, hub_scratch, 0});
+        e = launch_sweeps<SWEEP_BWD_CSR>(sw, st, "attn_sweep_bwd_dst");
         if (e != HETA_OK) return e;
         e = aggregate_slot_weighted(g, r.csr, z, z_dt, ld_z, d, w_gate, K, R, HETA_F32, ld_r, 0.f, st);
         if (e != HETA_OK) return e;
@@ -1990,8 +2144,13 @@ heta_status heta_rel_attn_bwd(heta_graph *g, int32_t rel, const void *z, heta_dt
                            reinterpret_cast<float4 *>(nbr_pack));
         HETA_LAUNCH_CHECK("attn_pack_kernel");
     }
-    return attn_source_side(g, r, z, z_dt, ld_z, d, K, el, slope, nbr_pack, grad_out, ld_go, dz, ld_dz, del, w_alpha, corr_s, R, ld_r,
-                            hub_scratch, st);
+    const SourceSide side = {&r, z, z_dt, ld_z, el, nbr_pack, grad_out, ld_go, dz, ld_dz, del, w_alpha, corr_s, R, hub_scratch, ld_r};
+    return attn_source_side(g, &side, 1, d, K, slope, st);
+    } catch (const std::bad_alloc &) {
+        return fail(HETA_ERR_OOM, "heta_rel_attn_bwd: host allocation failed");
+    } catch (...) {
+        return fail(HETA_ERR_DEVICE, "heta_rel_attn_bwd: unexpected exception");
+    }
 }
 
 heta_status heta_attn_bwd_dst(heta_graph *g, int32_t dst_type, int32_t n_rels, const int32_t *rels, int32_t d, int32_t heads, float slope,
@@ -2073,27 +2232,70 @@ heta_status heta_rel_attn_bwd_src(heta_graph *g, int32_t rel, const void *z, het
                                   const float *el, float slope, const float *pack, const float *grad_out, int64_t ld_go, float *dz,
                                   int64_t ld_dz, float *del, void *hip_stream)
 {
-    heta_status e = check_attn_args("heta_rel_attn_bwd_src", g, rel, d, heads);
-    if (e != HETA_OK) return e;
-    if (!z || !el || !pack || !grad_out || !dz || !del) return fail(HETA_ERR_INVALID_ARG, "heta_rel_attn_bwd_src: null argument");
-    if (!aligned16(pack)) return fail(HETA_ERR_INVALID_ARG, "heta_rel_attn_bwd_src: pack not 16-byte aligned");
-    if (!valid_dtype(z_dt)) return fail(HETA_ERR_INVALID_ARG, "heta_rel_attn_bwd_src: bad dtype");
-    if (ld_z < d || ld_go < d || ld_dz < d) return fail(HETA_ERR_SHAPE, "heta_rel_attn_bwd_src: need d <= ld");
-    if (reinterpret_cast<uintptr_t>(z) % dtype_size(z_dt) || reinterpret_cast<uintptr_t>(grad_out) % 4 || reinterpret_cast<uintptr_t>(dz) % 4)
-        return fail(HETA_ERR_INVALID_ARG, "heta_rel_attn_bwd_src: pointer not aligned to its element size");
-    const Relation &r = g->rels[rel];
-    const size_t w_bytes = std::max<size_t>(256, round256(static_cast<size_t>(r.n_edges) * heads * sizeof(float)));
-    const size_t src_bytes = round256(static_cast<size_t>(r.n_src) * heads * sizeof(float));
+    const heta_attn_src_item it = {rel, z, ld_z, el, pack, grad_out, ld_go, dz, ld_dz, del};
+    return heta_rel_attn_bwd_src_multi(g, 1, &it, z_dt, d, heads, slope, hip_stream);
+}
+
+heta_status heta_rel_attn_bwd_src_multi(heta_graph *g, int32_t n, const heta_attn_src_item *items, heta_dtype z_dt, int32_t d, int32_t heads,
+                                        float slope, void *hip_stream)
+{
+    const char *fn = "heta_rel_attn_bwd_src";
+    if (n < 0 || (n > 0 && !items)) return fail(HETA_ERR_INVALID_ARG, "%s: bad item array", fn);
+    heta_status e = HETA_OK;
+    for (int32_t i = 0; i < n; ++i) {
+        const heta_attn_src_item &it = items[i];
+        e = check_attn_args(fn, g, it.rel, d, heads);
+        if (e != HETA_OK) return e;
+        if (!it.z || !it.el || !it.pack || !it.grad_out || !it.dz || !it.del) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", fn);
+        if (!aligned16(it.pack)) return fail(HETA_ERR_INVALID_ARG, "%s: pack not 16-byte aligned", fn);
+        if (!valid_dtype(z_dt)) return fail(HETA_ERR_INVALID_ARG, "%s: bad dtype", fn);
+        if (it.ld_z < d || it.ld_go < d || it.ld_dz < d) return fail(HETA_ERR_SHAPE, "%s: need d <= ld", fn);
+        if (reinterpret_cast<uintptr_t>(it.z) % dtype_size(z_dt) || reinterpret_cast<uintptr_t>(it.grad_out) % 4 ||
+            reinterpret_cast<uintptr_t>(it.dz) % 4)
+            return fail(HETA_ERR_INVALID_ARG, "%s: pointer not aligned to its element size", fn);
+        for (int32_t j = 0; j < i; ++j)
+            if (OutRange(it.dz, g->rels[it.rel].n_src, it.ld_dz, d, 4)
+                    .overlaps(OutRange(items[j].dz, g->rels[items[j].rel].n_src, items[j].ld_dz, d, 4)))
+                return fail(HETA_ERR_INVALID_ARG, "%s: the outputs of items %d and %d overlap", fn, j, i);
+    }
     const int64_t ld_r = (static_cast<int64_t>(d) + 3) / 4 * 4;
-    const size_t r_bytes = round256(static_cast<size_t>(r.n_src) * ld_r * sizeof(float));
-    e = ensure_attn(g, w_bytes + src_bytes + r_bytes + round256(hub_scratch_bytes(r.csc, heads)));
-    if (e != HETA_OK) return e;
-    char *base = static_cast<char *>(g->d_attn);
-    float *w_alpha = reinterpret_cast<float *>(base);
-    float *corr_s = reinterpret_cast<float *>(base + w_bytes), *R = reinterpret_cast<float *>(base + w_bytes + src_bytes);
-    float *hub_scratch = reinterpret_cast<float *>(base + w_bytes + src_bytes + r_bytes);
-    return attn_source_side(g, r, z, z_dt, ld_z, d, heads, el, slope, pack, grad_out, ld_go, dz, ld_dz, del, w_alpha, corr_s, R, ld_r,
-                            hub_scratch, as_stream(hip_stream));
+    struct Bytes {
+        size_t w, corr, R, hub;
+        size_t all() const { return w + corr + R + hub; }
+    };
+    const auto need = [&](int32_t i) {
+        const Relation &r = g->rels[items[i].rel];
+        return Bytes{std::max<size_t>(256, round256(static_cast<size_t>(r.n_edges) * heads * sizeof(float))),
+                     round256(static_cast<size_t>(r.n_src) * heads * sizeof(float)), round256(static_cast<size_t>(r.n_src) * ld_r * sizeof(float)),
+                     round256(hub_scratch_bytes(r.csc, heads))};
+    };
+    try {
+        for (int32_t i0 = 0; i0 < n;) {
+            int32_t i1 = i0;
+            size_t bytes = 0;
+            while (i1 < n && (i1 == i0 || bytes + need(i1).all() <= kAttnGroupBytes)) bytes += need(i1++).all();
+            e = ensure_attn(g, bytes);
+            if (e != HETA_OK) return e;
+            char *base = static_cast<char *>(g->d_attn);
+            std::vector<SourceSide> sides;
+            for (int32_t i = i0; i < i1; ++i) {
+                const heta_attn_src_item &it = items[i];
+                const Bytes b = need(i);
+                const auto at = [&](size_t off) { return reinterpret_cast<float *>(base + off); };
+                sides.push_back({&g->rels[it.rel], it.z, z_dt, it.ld_z, it.el, it.pack, it.grad_out, it.ld_go, it.dz, it.ld_dz, it.del, at(0),
+                                 at(b.w), at(b.w + b.corr), at(b.w + b.corr + b.R), ld_r});
+                base += b.all();
+            }
+            e = attn_source_side(g, sides.data(), static_cast<int>(sides.size()), d, heads, slope, as_stream(hip_stream));
+            if (e != HETA_OK) return e;
+            i0 = i1;
+        }
+        return HETA_OK;
+    } catch (const std::bad_alloc &) {
+        return fail(HETA_ERR_OOM, "%s: host allocation failed", fn);
+    } catch (...) {
+        return fail(HETA_ERR_DEVICE, "%s: unexpected exception", fn);
+    }
 }
 
 } // extern "C"

@@ -177,7 +177,7 @@ heta_status ensure_workspace(heta_graph *g, size_t bytes);
 // |w| is the first weight and the second is |w|, or neg |w| where the bit is set; the same gathered rows are reduced with it
 // into out2 (same element type as out).  Uses g's workspace for hub rows.
 // dot: instead of storing the second sum, dot->out[row, k] = <second sum of head k, dot->z[row, head k]> - dot->corr[row, k];
-// *dot_done tells whether the shapes allowed it (else out2 was written as usual and the caller takes the dot itself).
+// dot_done tells whether the shapes allowed it (else out2 was written as usual and the caller takes the dot itself).
 struct SecondSumDot {
     const void *z;
     heta_dtype z_dt;
@@ -187,9 +187,22 @@ struct SecondSumDot {
 };
 heta_status aggregate_slot_weighted(heta_graph *g, const Schedule &s, const void *table, heta_dtype dt, int64_t ld,
                                     int d, const float *slot_w, int heads, void *out, heta_dtype out_dt,
-                                    int64_t ld_out, float beta, hipStream_t st, bool two_sums = false, float neg = 0.f,
-                                    void *out2 = nullptr, int64_t ld_out2 = 0, const SecondSumDot *dot = nullptr,
-                                    bool *dot_done = nullptr);
+                                    int64_t ld_out, float beta, hipStream_t st);
+// Several of them (distinct outputs) in as few launches as their kernels allow.
+struct SlotAggregation {
+    const Schedule *s;
+    const void *table;
+    int64_t ld;
+    const float *slot_w;
+    void *out;
+    int64_t ld_out;
+    void *out2;
+    int64_t ld_out2;
+    SecondSumDot dot; // with dot.out
+    bool dot_done;
+};
+heta_status aggregate_slot_weighted_multi(heta_graph *g, std::vector<SlotAggregation> &calls, heta_dtype dt, int d, int heads,
+                                          heta_dtype out_dt, float beta, bool two_sums, float neg, hipStream_t st);
 // out[h] (fp32, compact) = sum or mean of the h-th hub row of s (rows of >= kHubMinDeg edges lead the schedule)
 heta_status aggregate_hub_rows(heta_graph *g, const Schedule &s, const void *table, heta_dtype dt, int64_t ld, int d,
                                const int64_t *gid, int mean, float *out, int64_t ld_out, hipStream_t st);

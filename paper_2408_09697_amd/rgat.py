@@ -115,10 +115,9 @@ class RgatLayer:
                 part = sets[i:i + _MAX_SETS]
                 hb.heta_attn_score_multi(self.tables[t], [self.wa[r] if src else self.q[r] for r, src in part],
                                          [self.el[r] if src else self.er[r] for r, src in part], stream=stream)
-        for r in self.rels:
-            s, t, _ = g.rels[r]
-            hb.heta_rel_attn_fwd_train(g, r, self.Z[r], self.el[r], self.er[r], self.slope, self.O[r], beta=0.0,
-                                       smax=self.smax[r], sinv=self.sinv[r], out_pos=self.Opos[r], apos=self.apos[r], stream=stream)
+        every = lambda x: [x[r] for r in self.rels]  # noqa: E731
+        hb.heta_rel_attn_fwd_train_multi(g, self.rels, every(self.Z), every(self.el), every(self.er), self.slope, every(self.O),
+                                         every(self.smax), every(self.sinv), every(self.Opos), every(self.apos), stream=stream)
         for t, rs in self.rels_into.items():
             hb.heta_cross_rel_reduce(g, t, [self.O[r] for r in rs], self.H[t], act=self.act, stream=stream)
         return self.H
@@ -138,9 +137,9 @@ class RgatLayer:
                                             of(self.apos), of(self.d_er), of(self.pack), stream=stream)
             grads[t] = grad
         written = set()
-        for r in self.rels:
-            hb.heta_rel_attn_bwd_src(g, r, self.Z[r], self.el[r], self.slope, self.pack[r], grads[g.rels[r][1]], self.dZ[r], self.d_el[r],
-                                     stream=stream)
+        every = lambda x: [x[r] for r in self.rels]  # noqa: E731
+        hb.heta_rel_attn_bwd_src_multi(g, self.rels, every(self.Z), every(self.el), self.slope, every(self.pack),
+                                       [grads[g.rels[r][1]] for r in self.rels], every(self.dZ), every(self.d_el), stream=stream)
         # el = <H0_s, wa> reaches the source type's table and, through wa, W_r and a_r; er = <H0_t, q> reaches the
         # destination type's table and gives dq: per node type, all of them in one pass over its table
         for t, sets in self._score_sets.items():

@@ -395,6 +395,56 @@ def test_destination_side_of_the_backward(n, d, heads, n_rels, pad, relu):
         graph.destroy()
 
 
+@pytest.mark.parametrize("d,heads", [(64, 8), (256, 4), (30, 3), (256, 1)])
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+def test_attention_of_several_relations_in_one_call(d, heads, storage):
+    """Ten relations (more than a sweep launch or a gather launch takes), one of them empty, with hub, long and short rows:
+    bitwise what one call per relation gives, forward and source side of the backward."""
+    gen = torch.Generator().manual_seed(d + heads)
+    n_src, n_dst, graph_rels = 300, 400, []
+    for r in range(10):
+        deg = torch.randint(0, 6, (n_dst,), generator=gen)
+        if r % 3 == 0:
+            deg[7], deg[8], deg[9] = 1300, 512, 40
+        if r == 4:
+            deg.zero_()
+        rowptr = torch.cat([deg.new_zeros(1), torch.cumsum(deg, 0)])
+        graph_rels.append((0, 1, rowptr.numpy(), torch.randint(0, n_src, (int(rowptr[-1]),), generator=gen, dtype=torch.int32).numpy()))
+    hg = heta.heta_graph_create([(n_src, 4, 0), (n_dst, 4, 0)], graph_rels)
+    dt = torch.float32 if storage == "f32" else torch.bfloat16
+    rels = list(range(10))
+
+    def rand(n, w, dtype=torch.float32):
+        return [torch.randn((n, w), generator=gen).to(dtype).cuda() for _ in rels]
+
+    def buffers(n, w):
+        return [[torch.full((n, w), 7.0, device="cuda") for _ in rels] for _ in range(2)]
+
+    try:
+        z, el, er, grad = rand(n_src, d, dt), rand(n_src, heads), rand(n_dst, heads), rand(n_dst, d)
+        out, pos, smax, sinv, apos = (buffers(n_dst, w) for w in (d, d, heads, heads, heads))
+        dz, del_ = buffers(n_src, d), buffers(n_src, heads)
+        for r in rels:
+            heta.heta_rel_attn_fwd_train(hg, r, z[r], el[r], er[r], 0.2, out[0][r], smax=smax[0][r], sinv=sinv[0][r], out_pos=pos[0][r], apos=apos[0][r])
+        heta.heta_rel_attn_fwd_train_multi(hg, rels, z, el, er, 0.2, out[1], smax[1], sinv[1], pos[1], apos[1])
+        pack = [torch.stack([er[r], smax[0][r], sinv[0][r], torch.randn((n_dst, heads), generator=gen).cuda()], 2).reshape(n_dst, 4 * heads).contiguous()
+                for r in rels]
+        for r in rels:
+            heta.heta_rel_attn_bwd_src(hg, r, z[r], el[r], 0.2, pack[r], grad[r], dz[0][r], del_[0][r])
+        heta.heta_rel_attn_bwd_src_multi(hg, rels, z, el, 0.2, pack, grad, dz[1], del_[1])
+        torch.cuda.synchronize()
+        for one, all_ in (out, pos, smax, sinv, apos, dz, del_):
+            for r in rels:
+                assert torch.equal(one[r].view(torch.int32), all_[r].view(torch.int32)), r
+        with pytest.raises(heta.HetaError, match="overlap"):
+            heta.heta_rel_attn_bwd_src_multi(hg, [0, 1], z[:2], el[:2], 0.2, pack[:2], grad[:2], [dz[0][0], dz[0][0]], del_[0][:2])
+        with pytest.raises(heta.HetaError, match="overlap"):
+            heta.heta_rel_attn_fwd_train_multi(hg, [0, 1], z[:2], el[:2], er[:2], 0.2, out[0][:2], smax[0][:2], sinv[0][:2],
+                                               [pos[0][0], out[0][0]], apos[0][:2])
+    finally:
+        hg.destroy()
+
+
 def test_attention_argument_checks():
     graph = heta.heta_graph_create([(4, 4, 0)], [(0, 0, np.array([0, 1, 2, 2, 2], dtype=np.int64), np.array([1, 0], dtype=np.int32))])
     z = torch.zeros((4, 12), device="cuda")
