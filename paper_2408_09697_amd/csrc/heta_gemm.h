@@ -24,9 +24,9 @@ struct GemmSeg {
     float *C;           // output of this segment (batch mode) - segment 0's is used in sum mode
     int64_t ldc;
     int64_t M, N, K;
-    // optional: B rewritten as two fp16 terms (pack_split_weights), [term][k / 8][n_pad][8 k-values], then int32 [n_pad] exponents
-    const void *B2;
-    int32_t ko, n_pad;  // k-octets (K rounded up to 16, over 8) and columns (N rounded up to 128) of B2
+    // optional: B rewritten as three bf16 terms (pack_split3_weights), [term][k / 8][n_pad][8 k-values]
+    const void *B3;
+    int32_t ko, n_pad;  // k-octets (K rounded up to 16, over 8) and columns (N rounded up to 128) of B3
 };
 
 struct GemmParams {
@@ -252,13 +252,13 @@ struct TileLoader {
 // The direct-to-LDS pipeline (heta_gemm_direct.hip).  Sets *handled when it launched the product;
 // otherwise the caller falls back to the register-staged kernel.
 extern bool g_f32_native; // test switch, see heta_test_hooks.h
-// Bytes of the two-term form of a K x N fp32 operand, and the launch that writes it for the B operands of all of p's
+// Bytes of the three-term form of a K x N fp32 operand, and the launch that writes it for the B operands of all of p's
 // segments, one after the other into `out` (16-byte aligned): B(k, n) = W[k*ldw + n] (trans = 0) or W[n*ldw + k]
-// (trans = 1); zero beyond K and N.
-size_t split_weight_bytes(int64_t K, int64_t N);
-heta_status pack_split_weights(GemmParams &p, int trans, void *out, hipStream_t st);
-// whether an fp32 product is small enough to split both operands in its kernel instead of packing one beforehand
-bool f32_product_unpacked(const GemmParams &p);
+// (trans = 1); x = h + m + l in bf16, zero beyond K and N.
+size_t split3_weight_bytes(int64_t K, int64_t N);
+heta_status pack_split3_weights(GemmParams &p, int trans, void *out, hipStream_t st);
+// whether the direct pipeline would give this launch its 64 x 64 tiles (too few 128 x 128 tiles to fill the chip)
+bool gemm_direct_small(const GemmParams &p);
 int wgrad_tile_rows(const GemmParams &p);
 heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, bool a_rc, bool b_rc, hipStream_t st,
                                const char *name, double bytes, double flops, bool *handled);

@@ -246,35 +246,20 @@ __device__ __forceinline__ uint4 dfrag_bf16_rc_from_f32(const float *tile, int r
     return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// fp32 products on the fp16 matrix pipe.  A value times a power of two is x = h + l with two fp16 terms
-// (h = fp16(x), l = fp16(x - h); the difference is exact in fp32): h and l hold 11 significant bits each and l a
-// sign, so |x - (h + l)| <= 2^-24 |x| while l is a normal number, i.e. |x| >= 2^-2, and <= 2^-25 below that.  A product
-// a b is fed as the three terms ah bh, ah bl, al bh (each exact in the fp32 accumulator's input); the one left out is
-// below 2^-24 |a b|, the rounding of one fp32 multiplication.  What the powers of two have to provide is the range
-// (fp16 ends at 2^16 - 2^5): every row of A and every column of B has its own, taken off again by the epilogue
-// (accumulator element (i, j) times 2^-(e_i + e_j), exact).  Data get theirs as they come (TermScale), weights that
-// a launch packs beforehand from their largest element.  An element 2^13 below the largest of its row still has 24
-// bits; a smaller one is held to 2^-36 of the largest, which only matters where its partners are that much larger than
-// the others'.  Packed weights of that kind are levelled (pack_split_kernel); products of two data operands with
-// accumulators to spare (kWideTerms) scale the remainders up by 2^11 and sum them on their own, which moves both bounds
-// by 2^11 or more; the weight gradient, whose rows would have to make up for each other one by one, does neither.
-// Three MFMAs and 24 vector instructions per fragment of eight values; with three bf16 terms, which need no scaling, it
-// is six and 44.  Forward and input gradient of three products 700 k x 128 x 256 920 -> 660 and 865 -> 640 us, their
-// weight gradients 860 -> 600; and fewer roundings of the accumulator: the error against 64 bits falls from 3.0e-7 to
-// 2.3e-7, 2.5e-7 to 2.0e-7 and 3.4e-6 to 1.7e-6 (norm).  (The remainders' own accumulators on the large tiles: two
-// workgroups per CU instead of three, 776, 728 and 732 us.)
-constexpr int kPackedTerms = 2, kWideTerms = 3; // values of the kernel's TERMS beside 0 (none) and 1
-constexpr float kRestUp = 2048.f;
-typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-__device__ __forceinline__ uint32_t pack_f16(float lo, float hi)
+// fp32 products on the bf16 matrix pipe.  x = h + m + l with three bf16 terms (h = bf16(x), m = bf16(x - h),
+// l = bf16(x - h - m); both differences are exact in fp32), so |x - (h + m + l)| <= 2^-27 |x|.  A product a b
+// is fed as the six terms ah bh, ah bm, am bh, am bm, ah bl, al bh (each a product of two 8-bit significands,
+// exact in the fp32 accumulator's input); the three terms left out are below 2^-25 |a b|, less than the
+// rounding of one fp32 multiplication.  Six bf16 MFMAs of 16 k-values cost 6 x 8 passes where the fp32 MFMA
+// needs 8 x 16 for the same 16 k-values.
+__device__ __forceinline__ void split3_pair(float x0, float x1, uint32_t &h, uint32_t &m, uint32_t &l)
 {
-    const floatx2_t f = {lo, hi};
-    const f16x2_t h = __builtin_convertvector(f, f16x2_t);
-    return *reinterpret_cast<const uint32_t *>(&h);
+    h = pack_bf16(x0, x1);
+    const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);
+    m = pack_bf16(r0, r1);
+    const float s0 = r0 - __uint_as_float(m << 16), s1 = r1 - __uint_as_float(m & 0xffff0000u);
+    l = pack_bf16(s0, s1);
 }
-__device__ __forceinline__ float f16_lo(uint32_t w) { return static_cast<float>((*reinterpret_cast<const f16x2_t *>(&w))[0]); }
-__device__ __forceinline__ float f16_hi(uint32_t w) { return static_cast<float>((*reinterpret_cast<const f16x2_t *>(&w))[1]); }
 
 // The lane's eight k-values kk + 8*half + 0..7 of row r of an fp32 operand lying in LDS (k-contiguous with
 // swizzled chunks, or r-contiguous as in memory): the LDS reads only.
@@ -294,6 +279,25 @@ __device__ __forceinline__ void dfrag_load8(const float *tile, int r, int kk, in
     }
 }
 
+// Eight k-values (the first is k0 of its tile) as three bf16 fragments; with MASKED, k-values from kv on
+// count as zero (branch-free: the caller's code stays one scheduling region).
+template <bool MASKED> __device__ __forceinline__ void split3_frag(const float x[8], int k0, int kv, uint4 out[3])
+{
+    uint32_t h[4], m[4], l[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        float x0 = x[2 * j], x1 = x[2 * j + 1];
+        if constexpr (MASKED) {
+            x0 = k0 + 2 * j < kv ? x0 : 0.f;
+            x1 = k0 + 2 * j + 1 < kv ? x1 : 0.f;
+        }
+        split3_pair(x0, x1, h[j], m[j], l[j]);
+    }
+    out[0] = make_uint4(h[0], h[1], h[2], h[3]);
+    out[1] = make_uint4(m[0], m[1], m[2], m[3]);
+    out[2] = make_uint4(l[0], l[1], l[2], l[3]);
+}
+
 // zeroes the k-values of a bf16 fragment (8 consecutive k from k_first) that are >= kv
 __device__ __forceinline__ uint4 mask_bf16(uint4 v, int k_first, int kv)
 {
@@ -308,117 +312,49 @@ __device__ __forceinline__ uint4 mask_bf16(uint4 v, int k_first, int kv)
 }
 
 // The splitting of one fragment (8 k-values of a lane) in pieces, so that a k-step can place them between its
-// MFMAs: hp scales a pair of values and packs their leading terms, lp their remainders.
-struct TermFrag {
-    float x[8];
-    uint32_t h[4], l[4];
-    __device__ __forceinline__ void mask(int k0, int kv) // k-values from kv on count as zero (the first is k0)
+// MFMAs: hp / mp / lp pack the leading, middle and last term of a pair of values, r1 / r2 leave the residuals.
+struct X3Frag {
+    float x[8];      // the values, then their residuals
+    uint32_t h[4], m[4], l[4];
+    __device__ __forceinline__ void hp(int j) { h[j] = pack_bf16(x[2 * j], x[2 * j + 1]); }
+    __device__ __forceinline__ void r1(int j)
     {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = k0 + j < kv ? x[j] : 0.f;
+        x[2 * j] -= __uint_as_float(h[j] << 16);
+        x[2 * j + 1] -= __uint_as_float(h[j] & 0xffff0000u);
     }
-    // the largest magnitude; a NaN only hides values of a row that is NaN in any case
-    __device__ __forceinline__ float largest() const
+    __device__ __forceinline__ void mp(int j) { m[j] = pack_bf16(x[2 * j], x[2 * j + 1]); }
+    __device__ __forceinline__ void r2(int j)
     {
-        float m;
-        asm("v_max3_f32 %0, |%1|, |%2|, |%3|" : "=v"(m) : "v"(x[0]), "v"(x[1]), "v"(x[2]));
-        asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(m) : "v"(m), "v"(x[3]), "v"(x[4]));
-        asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(m) : "v"(m), "v"(x[5]), "v"(x[6]));
-        asm("v_max_f32 %0, %1, |%2|" : "=v"(m) : "v"(m), "v"(x[7]));
-        return m;
+        x[2 * j] -= __uint_as_float(m[j] << 16);
+        x[2 * j + 1] -= __uint_as_float(m[j] & 0xffff0000u);
     }
-    __device__ __forceinline__ void hp(int j, float s)
+    __device__ __forceinline__ void lp(int j) { l[j] = pack_bf16(x[2 * j], x[2 * j + 1]); }
+    __device__ __forceinline__ bf16x8 term(int t) const
     {
-        x[2 * j] *= s;
-        x[2 * j + 1] *= s;
-        h[j] = pack_f16(x[2 * j], x[2 * j + 1]);
-    }
-    template <bool UP = false> __device__ __forceinline__ void lp(int j)
-    {
-        const float r0 = x[2 * j] - f16_lo(h[j]), r1 = x[2 * j + 1] - f16_hi(h[j]);
-        l[j] = UP ? pack_f16(r0 * kRestUp, r1 * kRestUp) : pack_f16(r0, r1);
-    }
-    __device__ __forceinline__ f16x8 lead() const
-    {
-        union { uint4 u; f16x8 v; } f;
-        f.u = make_uint4(h[0], h[1], h[2], h[3]);
-        return f.v;
-    }
-    __device__ __forceinline__ f16x8 rest() const
-    {
-        union { uint4 u; f16x8 v; } f;
-        f.u = make_uint4(l[0], l[1], l[2], l[3]);
+        union { uint4 u; bf16x8 v; } f;
+        const uint32_t *w = t == 0 ? h : (t == 1 ? m : l);
+        f.u = make_uint4(w[0], w[1], w[2], w[3]);
         return f.v;
     }
 };
 
-// The power of two one lane's row (or column) of an operand is scaled by.  It is chosen when the first value other
-// than zero comes by, so that the largest of that tile lands in [2^11, 2^12), and kept while |value| <= limit, i.e.
-// while scaled values stay at or below 2^15; a larger one sets it anew and the accumulators follow.  Both lanes of a
-// row (the two halves of its k-values) always hold the same.
-struct TermScale {
-    float s, limit; // 2^e ; 2^(15 - e), or 0 while every value was zero
-    int e;
-};
-
-// Called when a row's largest value in this tile (m, per lane: of its eight k-values) is beyond its limit: that row gets
-// a new scale, and so do those of the wavefront that are within a factor of eight of theirs, which saves them the next
-// call.  Returns whether accumulators have to follow, by 2^delta of their row: not where the row was zero so far.
-template <int N> __device__ __forceinline__ bool rescale(TermScale (&t)[N], const float (&m)[N], int (&delta)[N])
-{
-    bool follow = false;
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        const float mm = fmaxf(m[i], __shfl_xor(m[i], 32, 64));
-        const bool over = mm > t[i].limit * 0.125f;
-        const int e = min(138 - static_cast<int>(__float_as_uint(mm) >> 23 & 255u), 126); // mm in [2^(11-e), 2^(12-e))
-        follow = follow || (over && t[i].limit > 0.f);
-        delta[i] = over ? e - t[i].e : 0;
-        if (over) t[i] = {ldexpf(1.f, e), ldexpf(1.f, 15 - e), e};
-    }
-    return __any(follow);
-}
-
-// accumulators times 2^d of their row: register v of block (i, .) belongs to row 8*(v/4) + 4*half + v%4, whose
-// lane holds d[i]
-template <int MI, int NJ> __device__ __forceinline__ void scale_rows(floatx16 (&acc)[MI][NJ], const int (&d)[MI], int half)
-{
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int dv = __shfl(d[i], 8 * (v / 4) + 4 * half + v % 4, 64);
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) acc[i][j][v] = ldexpf(acc[i][j][v], dv);
-        }
-}
-template <int MI, int NJ> __device__ __forceinline__ void scale_columns(floatx16 (&acc)[MI][NJ], const int (&d)[NJ])
-{
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = ldexpf(acc[i][j][v], d[j]);
-}
-
-// Loader of an operand that lies in memory as two fp16 terms (pack_split_weights): a stage holds, for each
-// term and each of the tile's k-octets, the BN columns' 16-byte chunks (8 k-values) side by side, so a
+// Loader of an operand that lies in memory as three bf16 terms (pack_split3_weights): a stage holds, for each
+// term and each of the tile's two k-octets, the BN columns' 16-byte chunks (8 k-values) side by side, so a
 // fragment read (lane = column, half = octet) is one conflict-free 128-bit load per term and a wavefront load
 // instruction copies 64 neighbouring columns' chunks, 1 KB that is contiguous in memory too.  The packed
 // operand is zero beyond K and N, so no tile needs clamping or masking on this side.
-template <int BN, int BK, int NW> struct SplitLoader {
-    static constexpr int OCT = BK / 8, SLOTS = 2 * OCT * (BN / 64);
+template <int BN, int NW> struct Split3Loader {
+    static constexpr int SLOTS = 3 * 2 * (BN / 64);
     static constexpr int NI = (SLOTS + NW - 1) / NW;
     static constexpr int STAGE_BYTES = SLOTS * 1024;
     const char *tile;    // uniform: the chunk of term 0, the next tile's first octet, column n0
     uint32_t off;        // per lane
     int64_t plane, oct;  // uniform: bytes from term to term, from octet to octet
-    __device__ __forceinline__ void init(const void *b2, int ko, int n_pad, int64_t n0, int64_t k0, int lane)
+    __device__ __forceinline__ void init(const void *b3, int ko, int n_pad, int64_t n0, int64_t k0, int lane)
     {
         oct = static_cast<int64_t>(n_pad) * 16;
         plane = ko * oct;
-        tile = static_cast<const char *>(b2) + (k0 / 8) * oct + n0 * 16;
+        tile = static_cast<const char *>(b3) + (k0 / 8) * oct + n0 * 16;
         off = static_cast<uint32_t>(lane) * 16u;
     }
     __device__ __forceinline__ void issue(uint32_t lds, int wave)
@@ -426,257 +362,101 @@ template <int BN, int BK, int NW> struct SplitLoader {
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             const int slot = (i * NW + wave) % SLOTS; // surplus slots repeat earlier ones (same bytes, same place)
-            const int t = slot / (OCT * (BN / 64)), o = (slot / (BN / 64)) % OCT, hn = slot % (BN / 64);
+            const int t = slot / (2 * (BN / 64)), o = (slot / (BN / 64)) % 2, hn = slot % (BN / 64);
             load_chunk_to_lds(tile + t * plane + o * oct + hn * 1024, off, lds + slot * 1024);
         }
-        tile += OCT * oct;
+        tile += 2 * oct;
     }
-    // term t of the 8 k-values of octet o of column c, of the stage at `stage`
-    __device__ __forceinline__ static f16x8 frag(const char *stage, int t, int o, int c)
+    // term t of the 8 k-values of octet `half` of column c, of the stage at `stage`
+    __device__ __forceinline__ static uint4 frag(const char *stage, int t, int half, int c)
     {
-        union { uint4 u; f16x8 v; } f;
-        f.u = *reinterpret_cast<const uint4 *>(stage + ((t * OCT + o) * BN + c) * 16);
-        return f.v;
+        return *reinterpret_cast<const uint4 *>(stage + ((t * 2 + half) * BN + c) * 16);
     }
 };
 
-// One k-step (16 k-values from kk on) of a wavefront's 2 x NJ accumulators with B already in two terms: only A's two
-// fragments are split, and the order is pinned with scheduling barriers so that their remainders are formed between
-// the 4 NJ MFMAs that need A's leading terms alone; the 2 NJ that need the remainders follow.
-template <bool A_RC, int BM, int BN, int BK, int NJ>
-__device__ __forceinline__ void step_packed(const float *At, const char *Bt, const float *level, int ra, int cb, int kk, int half, int kv, TermScale (&ts)[2],
-                                            floatx16 (&acc)[2][NJ])
+// One k-step (16 k-values, kv of them valid) of a wavefront's 2 x 2 accumulators with B already in three
+// terms: only A's two fragments are split (88 vector instructions), and the order is pinned with scheduling
+// barriers so that the splitting runs between the twelve MFMAs that need A's leading term alone; the twelve
+// that need its m and l terms follow.  Terms of one accumulator are added leading term first.
+template <bool A_RC, int BM, int BN, int BK>
+__device__ __forceinline__ void x3_step_2x2_presplit(const float *At, const char *Bt, int ra, int cb, int half, int kv, floatx16 (&acc)[2][2])
 {
-    TermFrag a[2];
-    dfrag_load8<A_RC, BM, BK>(At, ra, kk, half, a[0].x);
-    dfrag_load8<A_RC, BM, BK>(At, ra + 32, kk, half, a[1].x);
-    f16x8 b[2][NJ];
+    X3Frag a[2];
+    dfrag_load8<A_RC, BM, BK>(At, ra, 0, half, a[0].x);
+    dfrag_load8<A_RC, BM, BK>(At, ra + 32, 0, half, a[1].x);
+    if (kv < BK) { // uniform: the ragged last tile of a segment; k-values from kv on count as zero
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) b[t][j] = SplitLoader<BN, BK, 4>::frag(Bt, t, kk / 8 + half, cb + 32 * j);
-    if (kv < BK) { // uniform: the ragged last tile of a segment
-        a[0].mask(kk + 8 * half, kv);
-        a[1].mask(kk + 8 * half, kv);
+            for (int j = 0; j < 8; ++j) a[i].x[j] = 8 * half + j < kv ? a[i].x[j] : 0.f;
     }
-    if (level) { // uniform: levelled weights
+    union BF { uint4 u; bf16x8 v; } b[2][3];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const float f = level[kk + 8 * half + j];
-            a[0].x[j] *= f;
-            a[1].x[j] *= f;
-        }
-    }
-    const float m[2] = {a[0].largest(), a[1].largest()};
-    if (__any(m[0] > ts[0].limit || m[1] > ts[1].limit)) {
-        int d[2];
-        if (rescale(ts, m, d)) scale_rows(acc, d, half);
-    }
-#define HETA_PIN __builtin_amdgcn_sched_barrier(0)
-#define HETA_MM(PART_, I_, T_, J_)                                                                                     \
-    HETA_PIN;                                                                                                          \
-    acc[I_][J_] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[I_].PART_(), b[T_][J_], acc[I_][J_], 0, 0, 0);             \
-    HETA_PIN
+    for (int t = 0; t < 3; ++t)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) a[0].hp(j, ts[0].s);
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-        HETA_MM(lead, 0, 0, j);
-        if (j < 2) {
-            a[1].hp(2 * j, ts[1].s);
-            a[1].hp(2 * j + 1, ts[1].s);
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-        HETA_MM(lead, 1, 0, j);
-        if (j < 2) {
-            a[0].lp(2 * j);
-            a[0].lp(2 * j + 1);
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-        HETA_MM(lead, 0, 1, j);
-        if (j < 2) {
-            a[1].lp(2 * j);
-            a[1].lp(2 * j + 1);
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) { HETA_MM(lead, 1, 1, j); }
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) { HETA_MM(rest, 0, 0, j); }
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) { HETA_MM(rest, 1, 0, j); }
-#undef HETA_PIN
-#undef HETA_MM
+        for (int j = 0; j < 2; ++j) b[j][t].u = Split3Loader<BN, 4>::frag(Bt, t, half, cb + 32 * j);
+#define X3_PIN __builtin_amdgcn_sched_barrier(0)
+#define X3_MM(TA_, I_, TB_, J_)                                                                                        \
+    X3_PIN;                                                                                                            \
+    acc[I_][J_] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[I_].term(TA_), b[J_][TB_].v, acc[I_][J_], 0, 0, 0);       \
+    X3_PIN
+#define X3_ALL(F_, OP_) F_.OP_(0); F_.OP_(1); F_.OP_(2); F_.OP_(3)
+#define X3_LO(F_, OP_) F_.OP_(0); F_.OP_(1)
+#define X3_HI(F_, OP_) F_.OP_(2); F_.OP_(3)
+    X3_ALL(a[0], hp); X3_ALL(a[1], hp);
+    X3_MM(0, 0, 0, 0); X3_LO(a[0], r1);
+    X3_MM(0, 0, 0, 1); X3_HI(a[0], r1);
+    X3_MM(0, 1, 0, 0); X3_ALL(a[0], mp); X3_LO(a[1], r1);
+    X3_MM(0, 1, 0, 1); X3_HI(a[1], r1);
+    X3_MM(0, 0, 1, 0); X3_ALL(a[1], mp); X3_LO(a[0], r2);
+    X3_MM(0, 0, 1, 1); X3_HI(a[0], r2);
+    X3_MM(0, 1, 1, 0); X3_ALL(a[0], lp); X3_LO(a[1], r2);
+    X3_MM(0, 1, 1, 1); X3_HI(a[1], r2);
+    X3_MM(0, 0, 2, 0); X3_ALL(a[1], lp);
+    X3_MM(0, 0, 2, 1); X3_MM(0, 1, 2, 0); X3_MM(0, 1, 2, 1);
+    X3_MM(1, 0, 0, 0); X3_MM(1, 0, 0, 1); X3_MM(1, 1, 0, 0); X3_MM(1, 1, 0, 1);
+    X3_MM(1, 0, 1, 0); X3_MM(1, 0, 1, 1); X3_MM(1, 1, 1, 0); X3_MM(1, 1, 1, 1);
+    X3_MM(2, 0, 0, 0); X3_MM(2, 0, 0, 1); X3_MM(2, 1, 0, 0); X3_MM(2, 1, 0, 1);
+#undef X3_PIN
+#undef X3_MM
+#undef X3_ALL
+#undef X3_LO
+#undef X3_HI
 }
 
-// What pack_split_kernel leaves of one operand: two planes [ko][n_pad] of 16-byte chunks, the columns' exponents
-// int32 [n_pad], the rows' levels float [8 ko], and whether they are in use.
-__device__ __forceinline__ const int *packed_exponents(const GemmSeg &g)
-{
-    return reinterpret_cast<const int *>(static_cast<const char *>(g.B2) + static_cast<int64_t>(g.ko) * g.n_pad * 32);
-}
-__device__ __forceinline__ const float *packed_levels(const GemmSeg &g) { return reinterpret_cast<const float *>(packed_exponents(g) + g.n_pad); }
-__device__ __forceinline__ bool packed_levelled(const GemmSeg &g) { return packed_levels(g)[8 * g.ko] != 0.f; }
-
-// Writes the two-term form of the B operands of a product, blockIdx.y picks the operand: a workgroup takes 16 columns,
-// finds each one's largest element (over all operands where they add up to one output: the columns of one accumulator
-// share a scale), which lands in [2^14, 2^15), and packs them by k-octets.
-// Weights whose rows differ in size by more than 2^8 are levelled: row k is packed 2^-c times larger, c <= 0, so that the
-// rows are alike, and the product multiplies column k of A by 2^c.  Where features of very different scale meet weights
-// that make up for it, A's small elements are then no longer small beside the others (features and weights spread over
-// 2^24 against each other: error 1.2e-5 without, 1.5e-7 with).  A row's size is the largest of up to 16 of its
-// elements, the same ones in every workgroup; beyond kLevelRows rows the weights stay as they are.
-// A launch of its own takes 4.5 us however small the matrix; one per operand was 5 % of a layer of 2 M edges.
-constexpr int kLevelRows = 8192;
-struct SplitSegs {
+// Writes the three-term form of the B operands of a product: one thread per (k-octet, column), blockIdx.y picks the
+// operand.  A launch of its own takes 4.5 us however small the matrix; one per operand was 5 % of a layer of 2 M edges.
+struct Split3Segs {
     const float *W[kMaxSeg];
     uint4 *out[kMaxSeg];
     int64_t ldw[kMaxSeg];
     int K[kMaxSeg], N[kMaxSeg], ko[kMaxSeg], n_pad[kMaxSeg];
-    int n_seg, common;
 };
-__global__ void __launch_bounds__(1024) pack_split_kernel(SplitSegs q, int trans)
+__global__ void __launch_bounds__(256) pack_split3_kernel(Split3Segs q, int trans)
 {
-    __shared__ float part[16][16];
-    __shared__ int los[16], his[16];
-    __shared__ uint8_t row_exp[kLevelRows]; // biased exponent of every row's size, 0: a row of zeros
-    const int s = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int n_pad = q.n_pad[s], ko = q.ko[s];
-    if (blockIdx.x * 16 >= static_cast<unsigned>(n_pad)) return; // uniform: a narrower operand of the launch
-    const int t0 = q.common ? 0 : s, t1 = q.common ? q.n_seg : s + 1;
-    int k_all = 0, k_own = 0; // rows of all operands that share a scale; of those before this one
-    for (int t = t0; t < t1; ++t) {
-        if (t == s) k_own = k_all;
-        k_all = min(k_all + min(q.K[t], kLevelRows), 2 * kLevelRows);
-    }
-    // lanes along whatever is contiguous in W
-    const int c = trans ? tid / 64 : tid % 16, r = trans ? lane : tid / 16;
-    const int n = blockIdx.x * 16 + c;
-    // the eight values of octet o of operand t in this thread's column
-    auto load = [&](int t, int o, float x[8]) {
-        const float *W = q.W[t];
-        const int64_t ldw = q.ldw[t];
-        const bool in = n < q.N[t];
+    const int s = blockIdx.y;
+    const float *W = q.W[s];
+    uint4 *out = q.out[s];
+    const int64_t ldw = q.ldw[s];
+    const int K = q.K[s], N = q.N[s], ko = q.ko[s], n_pad = q.n_pad[s];
+    const int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    const int n = static_cast<int>(idx % n_pad), o = static_cast<int>(idx / n_pad);
+    if (o >= ko) return;
+    uint32_t h[4], m[4], l[4];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int k = o * 8 + j;
-            x[j] = in && k < q.K[t] ? (trans ? W[n * ldw + k] : W[k * ldw + n]) : 0.f;
+    for (int j = 0; j < 4; ++j) {
+        float x[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int k = o * 8 + 2 * j + e;
+            x[e] = (k < K && n < N) ? (trans ? W[static_cast<int64_t>(n) * ldw + k] : W[static_cast<int64_t>(k) * ldw + n]) : 0.f;
         }
-    };
-    auto largest = [](const float x[8]) {
-        float m = 0.f;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) m = fmaxf(m, fabsf(x[j]));
-        return m;
-    };
-    // One round of loads wherever the matrix is small enough: the thread's first octet, which stays in registers, and
-    // one row's sample (three dependent rounds and as many barriers
-    // took 11-12 us on 128 x 256, this 6.4)
-    float own[8], m = 0.f;
-    load(s, min(r, ko - 1), own);
-    int lo = 255, hi = 0;
-    if (k_all <= kLevelRows) { // uniform
-        for (int i = tid; i < k_all; i += 1024) {
-            int t = t0, k = i;
-            while (k >= q.K[t]) k -= q.K[t++];
-            const float *W = q.W[t] + (trans ? k : k * q.ldw[t]);
-            const int64_t step = trans ? q.ldw[t] : 1;
-            const int N = q.N[t];
-            float x[16];
-#pragma unroll
-            for (int j = 0; j < 16; ++j) x[j] = W[static_cast<int>(static_cast<int64_t>(j) * N / 16) * step];
-            float size = 0.f;
-#pragma unroll
-            for (int j = 0; j < 16; ++j) size = fmaxf(size, fabsf(x[j]));
-            const int e = static_cast<int>(__float_as_uint(size) >> 23 & 255u);
-            row_exp[i] = static_cast<uint8_t>(e);
-            if (e) {
-                lo = min(lo, e);
-                hi = max(hi, e);
-            }
-        }
+        split3_pair(x[0], x[1], h[j], m[j], l[j]);
     }
-    m = largest(own);
-    for (int t = t0; t < t1; ++t)
-        for (int o = t == s ? r + 64 : r; o < q.ko[t]; o += 64) {
-            float x[8];
-            load(t, o, x);
-            m = fmaxf(m, largest(x));
-        }
-    // maxima over the workgroup, per column; row sizes over everything
-    auto column_max = [&](float v) {
-        for (int off = trans ? 1 : 16; off < 64; off <<= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-        if (trans ? lane == 0 : lane < 16) part[trans ? 0 : wave][c] = v;
-    };
-    column_max(m);
-    for (int off = 1; off < 64; off <<= 1) {
-        lo = min(lo, __shfl_xor(lo, off, 64));
-        hi = max(hi, __shfl_xor(hi, off, 64));
-    }
-    if (lane == 0) {
-        los[wave] = lo;
-        his[wave] = hi;
-    }
-    __syncthreads();
-    for (int i = 0; i < 16; ++i) {
-        lo = min(lo, los[i]);
-        hi = max(hi, his[i]);
-    }
-    const bool levelled = hi - lo > 8; // the same in every workgroup of operands that share a scale
-    auto row_level = [&](int row) { return (row_exp[row] ? row_exp[row] : lo) - hi; };
-    auto raise = [&](int t, int base, int o, float x[8]) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            if (o * 8 + j < q.K[t]) x[j] *= ldexpf(1.f, -row_level(base + o * 8 + j));
-    };
-    if (levelled) {
-        m = 0.f;
-        int base = 0;
-        for (int t = t0; t < t1; ++t) {
-            for (int o = r; o < q.ko[t]; o += 64) {
-                float x[8];
-                load(t, o, x);
-                raise(t, base, o, x);
-                m = fmaxf(m, largest(x));
-            }
-            base += q.K[t];
-        }
-        __syncthreads(); // every thread has read los and his, none has yet read part
-        column_max(m);
-        __syncthreads();
-    }
-    m = 0.f;
-    for (int i = 0; i < (trans ? 1 : 16); ++i) m = fmaxf(m, part[i][c]);
-    const int e = m > 0.f ? min(141 - static_cast<int>(__float_as_uint(m) >> 23 & 255u), 126) : 0;
-    int *tail = reinterpret_cast<int *>(q.out[s] + 2 * static_cast<int64_t>(ko) * n_pad);
-    if (r == 0) tail[n] = e;
-    const float scale = ldexpf(1.f, e);
-    const int64_t plane = static_cast<int64_t>(ko) * n_pad;
-    for (int o = r; o < ko; o += 64) {
-        TermFrag f;
-        if (o == r) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) f.x[j] = own[j];
-        } else load(s, o, f.x);
-        if (levelled) raise(s, k_own, o, f.x);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            f.hp(j, scale);
-            f.lp(j);
-        }
-        q.out[s][o * static_cast<int64_t>(n_pad) + n] = make_uint4(f.h[0], f.h[1], f.h[2], f.h[3]);
-        q.out[s][plane + o * static_cast<int64_t>(n_pad) + n] = make_uint4(f.l[0], f.l[1], f.l[2], f.l[3]);
-    }
-    if (blockIdx.x == 0) {
-        float *levels = reinterpret_cast<float *>(tail + n_pad);
-        if (levelled)
-            for (int k = tid; k < 8 * ko; k += 1024) levels[k] = k < q.K[s] ? ldexpf(1.f, row_level(k_own + k)) : 1.f;
-        if (tid == 0) levels[8 * ko] = levelled ? 1.f : 0.f;
-    }
+    const int64_t plane = static_cast<int64_t>(ko) * n_pad, at = static_cast<int64_t>(o) * n_pad + n;
+    out[at] = make_uint4(h[0], h[1], h[2], h[3]);
+    out[plane + at] = make_uint4(m[0], m[1], m[2], m[3]);
+    out[2 * plane + at] = make_uint4(l[0], l[1], l[2], l[3]);
 }
 
 // The sequence of k-tiles a workgroup walks: the k range of its split in every segment it owns.
@@ -804,9 +584,9 @@ __device__ __forceinline__ void store_tile(const GemmParams &p, const GemmSeg &o
         }
 }
 
-template <bool PACKED, bool B_DIRECT, typename DB, typename SB_T, typename Staged, typename CT> constexpr int b_stage_bytes()
+template <bool W3, bool B_DIRECT, typename DB, typename SB_T, typename Staged, typename CT> constexpr int b_stage_bytes()
 {
-    if constexpr (PACKED) return DB::STAGE_BYTES;
+    if constexpr (W3) return DB::STAGE_BYTES;
     else if constexpr (B_DIRECT) return DB::STAGE_ELEMS * (int)sizeof(SB_T);
     else return Staged::elems * (int)sizeof(CT);
 }
@@ -819,31 +599,30 @@ template <bool PACKED, bool B_DIRECT, typename DB, typename SB_T, typename Stage
 // second side too (MI x NJ = 5 x 2 or 4 x 2: 320 x 256 / 256 x 256; 2 x 5: 256 x 320), one workgroup per CU: fewer
 // operand bytes loaded per MFMA.
 template <typename CT, typename SA_T, bool A_RC, bool A_DIRECT, typename SB_T, bool B_RC, bool B_DIRECT, int WN, int BK,
-          int ST, int OCC, bool B_SPLIT = false, int MI = 2, int NJ = 2, int WMW = 2, int TERMS = 0>
+          int ST, int OCC, bool B_SPLIT = false, int MI = 2, int NJ = 2, int WMW = 2, int X3 = 0>
 __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmParams p)
 {
     constexpr int NW = WMW * WN, NT = 64 * NW, BN = 32 * NJ * WN, BM = 32 * MI * WMW; // BM shadows the default tile height
     // a direct operand lies in LDS in its storage type (fp32 storage under bf16 compute is converted
     // when fragments are read); a staged operand lies there in the compute type
     using DA = std::conditional_t<A_DIRECT, DirectLoader<SA_T, A_RC && A_DIRECT, BM, BK, NW>, NoLoader>;
-    // TERMS: fp32 operands as two fp16 terms each - 1: both split when their fragments are read, kWideTerms: with the
-    // remainders' products summed on their own, kPackedTerms: B comes packed
-    constexpr bool PACKED = TERMS == kPackedTerms, WIDE = TERMS == kWideTerms;
-    using DB = std::conditional_t<PACKED, SplitLoader<BN, BK, NW>, std::conditional_t<B_DIRECT, DirectLoader<SB_T, B_RC && B_DIRECT, BN, BK, NW>, NoLoader>>;
+    // X3: fp32 operands as three bf16 terms each - 1: both split when their fragments are read, 2: B comes pre-split
+    constexpr bool W3 = X3 == 2;
+    using DB = std::conditional_t<W3, Split3Loader<BN, NW>, std::conditional_t<B_DIRECT, DirectLoader<SB_T, B_RC && B_DIRECT, BN, BK, NW>, NoLoader>>;
     using SA = std::conditional_t<A_DIRECT, NoLoader, TileLoader<SA_T, CT, A_RC, BM, NT, true, BK>>;
     using SB = std::conditional_t<B_DIRECT, NoLoader, TileLoader<SB_T, CT, B_RC, BN, NT, true, BK>>;
     constexpr bool ANY_STAGED = !A_DIRECT || !B_DIRECT;
     // bytes of one LDS stage / buffer of each operand
     constexpr int A_STRIDE = A_DIRECT ? DA::STAGE_ELEMS * (int)sizeof(SA_T) : LdsTile<CT, A_RC, BM, BK>::elems * (int)sizeof(CT);
-    constexpr int B_STRIDE = b_stage_bytes<PACKED, B_DIRECT, DB, SB_T, LdsTile<CT, B_RC, BN, BK>, CT>();
+    constexpr int B_STRIDE = b_stage_bytes<W3, B_DIRECT, DB, SB_T, LdsTile<CT, B_RC, BN, BK>, CT>();
     constexpr int A_BYTES = (A_DIRECT ? ST : 2) * A_STRIDE, B_BYTES = (B_DIRECT ? ST : 2) * B_STRIDE;
     constexpr int LD_PER_TILE = (A_DIRECT ? DA::NI : 0) + (B_DIRECT ? DB::NI : 0);
     static_assert(A_DIRECT || B_DIRECT, "at least one operand is loaded directly");
     static_assert(!B_SPLIT || (B_DIRECT && B_RC && sizeof(SB_T) == 4 && sizeof(CT) == 2), "two-term feeding: direct r-contiguous fp32 B");
     static_assert(ST >= 2 && (ST - 2) * LD_PER_TILE < 64, "vmcnt range");
-    static_assert(!TERMS || (A_DIRECT && B_DIRECT && sizeof(SA_T) == 4 && sizeof(SB_T) == 4 && sizeof(CT) == 2 && !B_SPLIT),
-                  "two-term feeding: both operands direct fp32, 16-bit MFMA");
-    static_assert(!PACKED || (MI == 2 && !A_RC), "packed B: 2 x NJ accumulators");
+    static_assert(!X3 || (A_DIRECT && B_DIRECT && sizeof(SA_T) == 4 && sizeof(SB_T) == 4 && sizeof(CT) == 2 && !B_SPLIT),
+                  "three-term feeding: both operands direct fp32, bf16 MFMA");
+    static_assert(!W3 || (BK == 16 && MI == 2 && NJ == 2 && !A_RC), "pre-split B: 2 x 2 accumulators, 16 k-values per tile");
     static_assert(A_BYTES % 1024 == 0, "stage addresses stay 1 KB aligned");
     __shared__ __attribute__((aligned(1024))) char ring[A_BYTES + B_BYTES];
     char *const As = ring, *const Bs = ring + A_BYTES;
@@ -883,14 +662,6 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][jj][v] = 0.f;
 
-    floatx16 acc_r[WIDE ? MI : 1][WIDE ? NJ : 1]; // the products with a remainder, kRestUp times too large
-    if constexpr (WIDE) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int jj = 0; jj < NJ; ++jj) acc_r[i][jj] = acc[i][jj];
-    }
-
     DA da;
     DB db;
     SA sa;
@@ -903,7 +674,7 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
     auto init_direct = [&]() {
         const GemmSeg &g = p.seg[I.s];
         if constexpr (A_DIRECT) da.init(static_cast<const SA_T *>(g.A), g.lda, m0, g.M, I.k, wave, lane);
-        if constexpr (PACKED) db.init(g.B2, g.ko, g.n_pad, n0, I.k, lane);
+        if constexpr (W3) db.init(g.B3, g.ko, g.n_pad, n0, I.k, lane);
         else if constexpr (B_DIRECT) db.init(static_cast<const SB_T *>(g.B), g.ldb, n0, g.N, I.k, wave, lane);
     };
     auto init_staged = [&]() {
@@ -927,7 +698,7 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
         } else {
             const GemmSeg &g = p.seg[I.s];
             if constexpr (A_DIRECT) da.issue_ragged(a_lds + st * A_STRIDE, wave, lane, kv, g.lda - I.k);
-            if constexpr (PACKED) db.issue(b_lds + st * B_STRIDE, wave);
+            if constexpr (W3) db.issue(b_lds + st * B_STRIDE, wave);
             else if constexpr (B_DIRECT) db.issue_ragged(b_lds + st * B_STRIDE, wave, lane, kv, g.ldb - I.k);
         }
         ++ahead;
@@ -954,16 +725,6 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
 #pragma unroll
     for (int q = 0; q < ST - 1; ++q)
         if (i_ok) issue_direct(q);
-
-    // TERMS: the powers of two that the rows of A and (unless packed) the columns of B are scaled by
-    TermScale ts_a[MI], ts_b[NJ];
-#pragma unroll
-    for (int i = 0; i < MI; ++i) ts_a[i] = {1.f, 0.f, 0};
-#pragma unroll
-    for (int jj = 0; jj < NJ; ++jj) ts_b[jj] = {1.f, 0.f, 0};
-
-    bool levelled = false;
-    if constexpr (PACKED) levelled = packed_levelled(p.seg[s0]); // the same in all segments of a sum
 
     int sbuf = 0; // LDS buffer of the staged operand's current tile
     while (c_ok) {
@@ -1019,66 +780,40 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
                             for (int jj = 0; jj < NJ; ++jj)
                                 acc[i][jj] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][t], b[jj][t], acc[i][jj], 0, 0, 0);
                 }
-            } else if constexpr (PACKED) {
-                // fp32 A split as its fragments are read, B read as the two terms it was packed into
-#pragma unroll
-                for (int kk = 0; kk < BK; kk += 16)
-                    step_packed<A_RC, BM, BN, BK, NJ>(reinterpret_cast<const float *>(At), Bt, levelled ? packed_levels(p.seg[C.s]) + C.k : nullptr,
-                                                      wm + l32, wn + l32, kk, half, kv, ts_a, acc);
-            } else if constexpr (TERMS != 0) {
-                // fp32 operands, both split as their fragments are read
+            } else if constexpr (W3) {
+                // fp32 A split as its fragments are read, B read as the three terms it was packed into
+                x3_step_2x2_presplit<A_RC, BM, BN, BK>(reinterpret_cast<const float *>(At), Bt, wm + l32, wn + l32, half, kv, acc);
+            } else if constexpr (X3 != 0) {
+                // fp32 operands, every product as six bf16 terms (split3_pair)
 #pragma unroll
                 for (int kk = 0; kk < BK; kk += 16) {
-                    TermFrag a[MI], b[NJ];
-                    float ma[MI], mb[NJ];
-                    bool over = false;
+                    union Frag { uint4 u; bf16x8 v; };
+                    uint4 a3[MI][3], b3[NJ][3];
 #pragma unroll
                     for (int i = 0; i < MI; ++i) {
-                        dfrag_load8<A_RC, BM, BK>(reinterpret_cast<const float *>(At), wm + i * 32 + l32, kk, half, a[i].x);
-                        if (ragged) a[i].mask(kk + 8 * half, kv);
-                        ma[i] = a[i].largest();
-                        over = over || ma[i] > ts_a[i].limit;
+                        float x[8];
+                        dfrag_load8<A_RC, BM, BK>(reinterpret_cast<const float *>(At), wm + i * 32 + l32, kk, half, x);
+                        if (ragged) split3_frag<true>(x, kk + 8 * half, kv, a3[i]);
+                        else split3_frag<false>(x, kk + 8 * half, kv, a3[i]);
                     }
 #pragma unroll
                     for (int jj = 0; jj < NJ; ++jj) {
-                        dfrag_load8<B_RC, BN, BK>(reinterpret_cast<const float *>(Bt), wn + jj * 32 + l32, kk, half, b[jj].x);
-                        if (ragged) b[jj].mask(kk + 8 * half, kv);
-                        mb[jj] = b[jj].largest();
-                        over = over || mb[jj] > ts_b[jj].limit;
+                        float x[8];
+                        dfrag_load8<B_RC, BN, BK>(reinterpret_cast<const float *>(Bt), wn + jj * 32 + l32, kk, half, x);
+                        if (ragged) split3_frag<true>(x, kk + 8 * half, kv, b3[jj]);
+                        else split3_frag<false>(x, kk + 8 * half, kv, b3[jj]);
                     }
-                    if (__any(over)) {
-                        int da_[MI], db_[NJ];
-                        if (rescale(ts_a, ma, da_)) {
-                            scale_rows(acc, da_, half);
-                            if constexpr (WIDE) scale_rows(acc_r, da_, half);
-                        }
-                        if (rescale(ts_b, mb, db_)) {
-                            scale_columns(acc, db_);
-                            if constexpr (WIDE) scale_columns(acc_r, db_);
-                        }
-                    }
+                    constexpr int TA[6] = {2, 0, 1, 1, 0, 0}, TB[6] = {0, 2, 1, 0, 1, 0}; // smallest products first
 #pragma unroll
-                    for (int i = 0; i < MI; ++i)
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) {
-                            a[i].hp(t, ts_a[i].s);
-                            a[i].template lp<WIDE>(t);
-                        }
-#pragma unroll
-                    for (int jj = 0; jj < NJ; ++jj)
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) {
-                            b[jj].hp(t, ts_b[jj].s);
-                            b[jj].template lp<WIDE>(t);
-                        }
-#pragma unroll
-                    for (int q = 0; q < 3; ++q)
+                    for (int q = 0; q < 6; ++q)
 #pragma unroll
                         for (int i = 0; i < MI; ++i)
 #pragma unroll
                             for (int jj = 0; jj < NJ; ++jj) {
-                                floatx16 &to = WIDE && q ? acc_r[WIDE ? i : 0][WIDE ? jj : 0] : acc[i][jj];
-                                to = __builtin_amdgcn_mfma_f32_32x32x16_f16(q == 2 ? a[i].rest() : a[i].lead(), q == 1 ? b[jj].rest() : b[jj].lead(), to, 0, 0, 0);
+                                Frag fa, fb;
+                                fa.u = a3[i][TA[q]];
+                                fb.u = b3[jj][TB[q]];
+                                acc[i][jj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa.v, fb.v, acc[i][jj], 0, 0, 0);
                             }
                 }
             } else {
@@ -1138,28 +873,6 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
     }
 
     barrier_no_drain();     // every wavefront's last fragment reads are done (they fed its last MFMAs)
-    if constexpr (TERMS != 0) { // the scales come off again
-        int er[MI], ec[NJ];
-#pragma unroll
-        for (int i = 0; i < MI; ++i) er[i] = -ts_a[i].e;
-#pragma unroll
-        for (int jj = 0; jj < NJ; ++jj) {
-            if constexpr (PACKED) {
-                ec[jj] = -packed_exponents(p.seg[s0])[n0 + wn + jj * 32 + l32]; // segments of a sum share their columns' exponents
-            } else ec[jj] = -ts_b[jj].e;
-        }
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int e = __shfl(er[i], 8 * (v / 4) + 4 * half + v % 4, 64);
-#pragma unroll
-                for (int jj = 0; jj < NJ; ++jj) {
-                    if constexpr (WIDE) acc[i][jj][v] = fmaf(acc_r[i][jj][v], 1.f / kRestUp, acc[i][jj][v]);
-                    acc[i][jj][v] = ldexpf(acc[i][jj][v], e + ec[jj]);
-                }
-            }
-    }
     static_assert(A_BYTES + B_BYTES >= NW * 8 * (32 * NJ + 4) * 4, "the epilogue strips overlay the ring");
     store_tile<MI, NJ>(p, out_seg, reinterpret_cast<float *>(ring), acc, wave, lane, wm, wn, m0, n0, rows_a, rows_b, split);
 }
@@ -1167,7 +880,7 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
 // ---- host side -------------------------------------------------------------------------------------
 
 template <typename CT, typename SA_T, bool A_RC, bool A_DIRECT, typename SB_T, bool B_RC, bool B_DIRECT, int WN, int BK,
-          int ST, int OCC, bool B_SPLIT = false, int MI = 2, int NJ = 2, int WMW = 2, int TERMS = 0>
+          int ST, int OCC, bool B_SPLIT = false, int MI = 2, int NJ = 2, int WMW = 2, int X3 = 0>
 static heta_status launch_direct(GemmParams &p, hipStream_t st, const char *name, double bytes, double flops)
 {
     constexpr int BN = 32 * NJ * WN, BM = 32 * MI * WMW;
@@ -1184,17 +897,16 @@ static heta_status launch_direct(GemmParams &p, hipStream_t st, const char *name
     if (blocks <= 0) return HETA_OK;
     if (blocks > max_blocks(64 * WMW * WN)) return fail(HETA_ERR_UNSUPPORTED, "projection: matrix too large for one launch");
     ProfScope prof(name, st, bytes, flops);
-    hipLaunchKernelGGL((gemm_direct_kernel<CT, SA_T, A_RC, A_DIRECT, SB_T, B_RC, B_DIRECT, WN, BK, ST, OCC, B_SPLIT, MI, NJ, WMW, TERMS>),
+    hipLaunchKernelGGL((gemm_direct_kernel<CT, SA_T, A_RC, A_DIRECT, SB_T, B_RC, B_DIRECT, WN, BK, ST, OCC, B_SPLIT, MI, NJ, WMW, X3>),
                        dim3((unsigned)blocks), dim3(64 * WMW * WN), 0, st, p);
     HETA_LAUNCH_CHECK("gemm_direct_kernel");
     return HETA_OK;
 }
 
-// test switch: fp32 products on the fp32 MFMA (32x32x2) instead of as three fp16 terms
+// test switch: fp32 products on the fp32 MFMA (32x32x2) instead of as six bf16 terms
 bool g_f32_native = false;
 
-// fewer than a hundred 128 x 128 tiles
-static bool gemm_direct_small(const GemmParams &p)
+bool gemm_direct_small(const GemmParams &p)
 {
     if (p.partial) return false;
     int64_t mt = 0, nt = 0;
@@ -1205,37 +917,18 @@ static bool gemm_direct_small(const GemmParams &p)
     return mt * nt * (p.batch ? p.n_seg : 1) <= 96;
 }
 
-// fp32 products (forward, input gradient) of too little work for packed weights: 64 x 64 tiles that split both operands.
-// The packing launch takes 6 us and packed tiles are four times as large, so the line lies where the work fills the chip
-// several times over: at about 28,000 (64 x 64 tile, 16 k-values) steps both take the same (48,000 x 128 x 256 31.7 us
-// packed and 31.9 not, 24,000 x 300 x 256 31.8 / 32.8, 96,000 x 64 x 256 41.5 / 40.2), below it the small tiles win
-// (12,000 x 128 x 128 17.9 / 11.2, three summed products of 24,000 x 128 x 64 32.3 / 18.2), above it packing does
-// (three of 96,000 x 128 x 256 91 / 134).
-bool f32_product_unpacked(const GemmParams &p)
-{
-    if (p.partial) return false;
-    double steps = 0;
-    for (int s = 0; s < p.n_seg; ++s)
-        steps += static_cast<double>((p.seg[s].M + 63) / 64) * static_cast<double>((p.seg[s].N + 63) / 64) * static_cast<double>((p.seg[s].K + 15) / 16);
-    return steps <= 24576;
-}
+static int64_t split3_octets(int64_t K) { return (K + 15) / 16 * 2; }
+static int64_t split3_columns(int64_t N) { return (N + 127) / 128 * 128; }
+size_t split3_weight_bytes(int64_t K, int64_t N) { return static_cast<size_t>(3 * split3_octets(K) * split3_columns(N) * 16); } // whole KBs
 
-static int64_t split_octets(int64_t K) { return (K + 15) / 16 * 2; }
-static int64_t split_columns(int64_t N) { return (N + 127) / 128 * 128; }
-// see pack_split_kernel, whole KBs
-size_t split_weight_bytes(int64_t K, int64_t N)
+heta_status pack_split3_weights(GemmParams &p, int trans, void *out, hipStream_t st)
 {
-    return static_cast<size_t>((2 * split_octets(K) * 16 + 4) * split_columns(N) + 32 * split_octets(K) + 4 + 1023) / 1024 * 1024;
-}
-
-heta_status pack_split_weights(GemmParams &p, int trans, void *out, hipStream_t st)
-{
-    SplitSegs q{};
-    int64_t n_max = 0;
+    Split3Segs q{};
+    int64_t chunks = 0;
     char *dst = static_cast<char *>(out);
     for (int s = 0; s < p.n_seg; ++s) {
         GemmSeg &g = p.seg[s];
-        const int64_t ko = split_octets(g.K), n_pad = split_columns(g.N);
+        const int64_t ko = split3_octets(g.K), n_pad = split3_columns(g.N);
         if (g.K >= (int64_t(1) << 30) || g.N >= (int64_t(1) << 30) || ko * n_pad >= (int64_t(1) << 31))
             return fail(HETA_ERR_UNSUPPORTED, "projection: weight matrix too large to pack");
         q.W[s] = static_cast<const float *>(g.B);
@@ -1245,16 +938,14 @@ heta_status pack_split_weights(GemmParams &p, int trans, void *out, hipStream_t 
         q.N[s] = static_cast<int>(g.N);
         q.ko[s] = static_cast<int>(ko);
         q.n_pad[s] = static_cast<int>(n_pad);
-        n_max = std::max(n_max, n_pad);
-        g.B2 = dst;
+        chunks = std::max(chunks, ko * n_pad);
+        g.B3 = dst;
         g.ko = static_cast<int32_t>(ko);
         g.n_pad = static_cast<int32_t>(n_pad);
-        dst += split_weight_bytes(g.K, g.N);
+        dst += split3_weight_bytes(g.K, g.N);
     }
-    q.n_seg = p.n_seg;
-    q.common = !p.batch;
-    hipLaunchKernelGGL(pack_split_kernel, dim3((unsigned)(n_max / 16), p.n_seg), dim3(1024), 0, st, q, trans);
-    HETA_LAUNCH_CHECK("pack_split_kernel");
+    hipLaunchKernelGGL(pack_split3_kernel, dim3((unsigned)((chunks + 255) / 256), p.n_seg), dim3(256), 0, st, q, trans);
+    HETA_LAUNCH_CHECK("pack_split3_kernel");
     return HETA_OK;
 }
 
@@ -1340,34 +1031,24 @@ heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, 
     // Fewer than a hundred 128 x 128 tiles (the projections of a sampled mini-batch block: a few thousand rows):
     // every tile is a serial chain of MFMAs on one CU while most CUs idle.  64 x 64 tiles (four wavefronts of one
     // accumulator each) cut the chain to a quarter and put four times as many CUs to work.
-    const bool small = gemm_direct_small(p), unpacked = f32_product_unpacked(p);
+    const bool small = gemm_direct_small(p);
     *handled = true;
-    if (a_dt == HETA_F32 && b_dt == HETA_F32 && !g_f32_native && !a_rc && !unpacked && !p.partial) {
-        // B already packed as two fp16 terms by the caller (the weights of a forward or input-gradient product):
-        // half the splitting leaves the k loop.
+    if (a_dt == HETA_F32 && b_dt == HETA_F32 && !g_f32_native && !a_rc && !small && !p.partial) {
+        // B already packed as three bf16 terms by the caller (the weights of a forward or input-gradient product):
+        // half the splitting arithmetic leaves the k loop.
         bool packed = true;
-        for (int s = 0; s < p.n_seg; ++s) packed = packed && p.seg[s].B2 != nullptr;
+        for (int s = 0; s < p.n_seg; ++s) packed = packed && p.seg[s].B3 != nullptr;
         // up to 64 output columns: 256 x 64 tiles, or half of the matrix work would be done for padding (57 -> 45 us on
         // 2 x (110 k x 128)(128 x 64))
-        if (packed && n_max <= 64) return launch_direct<bf16_t, float, false, true, float, false, true, 1, 16, 2, 3, false, 2, 2, 4, kPackedTerms>(p, st, name, bytes, flops);
-        // Where that pads no more columns than 128 x 128 tiles and gives every CU a tile, 128 x 256 tiles of 64 x 128 per
-        // wavefront (256 registers, two workgroups per CU): a row of A is loaded once and split once per 256 columns
-        // instead of twice (700 k x 128 x 256: three products of one input 893 -> 859 us; one of 1.1 M rows 455 -> 436).
-        if (packed && (n_max + 255) / 256 * 256 <= (n_max + 127) / 128 * 128) {
-            int64_t mt = 0;
-            for (int s = 0; s < p.n_seg; ++s) mt = std::max(mt, (p.seg[s].M + 127) / 128);
-            if (mt * ((n_max + 255) / 256) * (p.batch ? p.n_seg : 1) >= 256)
-                return launch_direct<bf16_t, float, false, true, float, false, true, 2, 16, 3, 2, false, 2, 4, 2, kPackedTerms>(p, st, name, bytes, flops);
-        }
-        // Two stages of 16 KB and at most 168 registers: three workgroups per CU, whose barriers and epilogues overlap.
-        // Three stages, four workgroups (128 registers, spilling), 256 x 128 tiles, 32 k-values per stage and an epilogue
-        // through strips of 32 rows take the same time within 4 % or longer: the kernel is bound by none of what these
-        // change, but by the clock that the chip grants it (leaving out stores, splitting or half of the MFMAs each takes
-        // its own share off the time, in any combination).
-        if (packed) return launch_direct<bf16_t, float, false, true, float, false, true, 2, 16, 2, 3, false, 2, 2, 2, kPackedTerms>(p, st, name, bytes, flops);
+        if (packed && n_max <= 64) return launch_direct<bf16_t, float, false, true, float, false, true, 1, 16, 2, 3, false, 2, 2, 4, 2>(p, st, name, bytes, flops);
+        // Two stages of 20 KB and at most 168 registers: three workgroups per CU, whose barriers and epilogues overlap
+        // (with three stages, and the ragged tile in a code path of its own, 229 registers and two workgroups: all fp32
+        // projections of a layer over 21 M edges 2.36 -> 2.20 ms; 64 x 128 columns per wavefront, half the splitting per
+        // MFMA but two workgroups per CU: 2.25)
+        if (packed) return launch_direct<bf16_t, float, false, true, float, false, true, 2, 16, 2, 3, false, 2, 2, 2, 2>(p, st, name, bytes, flops);
     }
     if (a_dt == HETA_F32 && b_dt == HETA_F32 && !g_f32_native) {
-        // fp32 operands, products as three fp16 MFMA terms each (see TermFrag), fp32 accumulation
+        // fp32 operands, fp32-exact products as six bf16 MFMA terms each (see split3_pair), fp32 accumulation
         // 128 x 128 tiles (four wavefronts, three workgroups per CU) also where the output is wider: the
         // 128 x 256 tile's eight wavefronts need more than the 128 registers that two workgroups per CU allow,
         // and with one workgroup per CU nothing runs under its barriers (measured: 0.93 against 1.05 ms)
@@ -1375,23 +1056,13 @@ heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, 
         // on 2 x (110 k x 128)^T (110 k x 64))
         if (p.partial && a_rc && b_rc && n_max <= 64)
             return launch_direct<bf16_t, float, true, true, float, true, true, 1, 16, 3, 2, false, 2, 2, 2, 1>(p, st, name, bytes, flops);
-        if (a_rc && b_rc) return launch_direct<bf16_t, float, true, true, float, true, true, 2, 16, 3, 3, false, 2, 2, 2, 1>(p, st, name, bytes, flops);
-        int64_t tiles64 = 0;
-        for (int s = 0; s < p.n_seg; ++s) {
-            const int64_t tiles = ((p.seg[s].M + 63) / 64) * ((p.seg[s].N + 63) / 64);
-            tiles64 = p.batch ? tiles64 + tiles : std::max(tiles64, tiles);
-        }
-        // 64 x 64 tiles: up to two per CU the launch is one chain of k-steps, and 32 k-values per barrier shorten it
-        // (1,024 rows, K = 768, 256 columns 25.7 -> 21.9 us, 1,024 columns 25.1 -> 21.3); with more of them 16 let four
-        // workgroups share a CU (24,000 x 300 x 100 18.5 us, 19.8 with 32; its input gradient 21.9 and 25.5)
-        const bool chain = tiles64 <= 512;
-#define HETA_TERMS(ARC, BRC)                                                                                                                          \
-    return !unpacked ? launch_direct<bf16_t, float, ARC, true, float, BRC, true, 2, 16, 3, 2, false, 2, 2, 2, kWideTerms>(p, st, name, bytes, flops) \
-           : chain   ? launch_direct<bf16_t, float, ARC, true, float, BRC, true, 2, 32, 3, 3, false, 1, 1, 2, kWideTerms>(p, st, name, bytes, flops) \
-                     : launch_direct<bf16_t, float, ARC, true, float, BRC, true, 2, 16, 3, 4, false, 1, 1, 2, kWideTerms>(p, st, name, bytes, flops)
-        if (!a_rc && b_rc) { HETA_TERMS(false, true); }
-        if (!a_rc && !b_rc) { HETA_TERMS(false, false); }
-#undef HETA_TERMS
+#define HETA_X32(ARC, BRC)                                                                                                        \
+    return small ? launch_direct<bf16_t, float, ARC, true, float, BRC, true, 2, 16, 3, 4, false, 1, 1, 2, 1>(p, st, name, bytes, flops) \
+                 : launch_direct<bf16_t, float, ARC, true, float, BRC, true, 2, 16, 3, 3, false, 2, 2, 2, 1>(p, st, name, bytes, flops)
+        if (!a_rc && b_rc) { HETA_X32(false, true); }
+        if (!a_rc && !b_rc) { HETA_X32(false, false); }
+        if (a_rc && b_rc) { HETA_X32(true, true); }
+#undef HETA_X32
     }
     if (small) {
         if (a_dt == HETA_F32 && b_dt == HETA_F32 && !a_rc)

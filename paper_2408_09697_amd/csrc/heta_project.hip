@@ -387,21 +387,21 @@ static heta_status ensure_pack(heta_graph *owner, size_t bytes)
 }
 
 // fp32 x fp32 products through a graph handle whose B operands are weight matrices (forward, input gradient):
-// the weights are rewritten once per launch as the two fp16 terms the product is fed with, into the handle's
-// packing buffer, and the k loop splits only A.  Launches the direct pipeline would not take, or would give tiles that
-// split both operands, are left as they are.  trans: B(k, n) = W[n*ldb + k].
+// the weights are rewritten once per launch as the three bf16 terms the product is fed with, into the handle's
+// packing buffer, and the k loop splits only A.  Launches the direct pipeline would not take, or would give its
+// small tiles, are left as they are.  trans: B(k, n) = W[n*ldb + k].
 static heta_status pack_f32_weights(heta_graph *owner, GemmParams &p, int trans, hipStream_t st)
 {
-    if (!owner || g_force_staged || g_f32_native || p.partial || f32_product_unpacked(p)) return HETA_OK;
+    if (!owner || g_force_staged || g_f32_native || p.partial || gemm_direct_small(p)) return HETA_OK;
     size_t bytes = 0;
     for (int s = 0; s < p.n_seg; ++s) {
         const GemmSeg &g = p.seg[s];
         if (!aligned16(g.A) || (g.lda * 4) % 16 || !aligned16(g.B) || (g.ldb * 4) % 16) return HETA_OK;
-        bytes += split_weight_bytes(g.K, g.N);
+        bytes += split3_weight_bytes(g.K, g.N);
     }
     heta_status e = ensure_pack(owner, bytes);
     if (e != HETA_OK) return e;
-    return pack_split_weights(p, trans, owner->d_pack, st);
+    return pack_split3_weights(p, trans, owner->d_pack, st);
 }
 
 // out = beta*out + row_scale * sum_s in_s . (W_s or W_s^T)
@@ -532,7 +532,7 @@ static heta_status wgrad_impl(heta_graph *g, int64_t n_rows, int n_seg, const vo
     bool bf16_direct = in_dt == HETA_BF16 && !g_force_staged;
     for (int s = 0; s < n_seg && bf16_direct; ++s)
         bf16_direct = ins[s] && vec_ok(ins[s], ld_in[s], in_dt) && vec_ok(gouts ? gouts[s] : gout, gouts ? ld_gos[s] : ld_go, HETA_F32);
-    // fp32 inputs on the direct pipeline (three fp16 terms per product): 128 x 128 tiles, three workgroups per CU
+    // fp32 inputs on the direct pipeline (six bf16 terms per product): 128 x 128 tiles, three workgroups per CU
     bool f32_terms = in_dt == HETA_F32 && !g_force_staged && !g_f32_native;
     for (int s = 0; s < n_seg && f32_terms; ++s)
         f32_terms = ins[s] && vec_ok(ins[s], ld_in[s], in_dt) && vec_ok(gouts ? gouts[s] : gout, gouts ? ld_gos[s] : ld_go, HETA_F32);

@@ -231,3 +231,48 @@ def compare_minibatch(mb, layers, grads, ref_fwd, ref_bwd, tol):
             if g.shape[0] == 0:
                 continue
             assert_rows_close(g.cpu().numpy(), dH0_ref[s], tol, f"layer {l + 1} dH0[{s}]")
+
+
+def assert_product(got: np.ndarray, a, b, what=""):
+    """got = sum of the products a[s] @ b[s] of fp32 operands, fed to the matrix unit as bf16 terms (three per operand, six
+    products of 16 k-values each).  Unit u = 2^-24.
+
+    Per element: representing both operands and leaving out three of the nine products costs less than one u of
+    sum |a b|; each of the 6 ceil(K / 16) additions to the accumulator at most two u of it.
+    Per column (2-norm): these errors fall on either side, and the accumulator they are relative to is the sum so far,
+    about R = sqrt(sum a^2 b^2) where the signs are mixed: 1 + 2 sqrt(additions) u of R."""
+    ref, mag, sq, additions = 0.0, 0.0, 0.0, 0
+    for x, w in zip(a, b):
+        x, w = x.astype(np.float64), w.astype(np.float64)
+        ref, mag, sq = ref + x @ w, mag + np.abs(x) @ np.abs(w), sq + np.square(x) @ np.square(w)
+        additions += 6 * ((x.shape[1] + 15) // 16)
+    err, u = np.abs(np.asarray(got, dtype=np.float64) - ref), 2.0 ** -24
+    worst = float((err / ((1 + 2 * additions) * u * mag + 1e-37)).max())
+    column = float((np.linalg.norm(err, axis=0) / ((1 + 2 * np.sqrt(additions)) * u * np.linalg.norm(np.sqrt(sq), axis=0) + 1e-37)).max())
+    assert worst <= 1.0 and column <= 1.0, f"{what}: {worst:.3g} of the bound of an element, {column:.3g} of a column's"
+
+
+def patterned_weights(pattern: str, k: int, d_out: int, g) -> np.ndarray:
+    """Weights whose size depends on where they stand."""
+    w = g.standard_normal((k, d_out))
+    row, col = np.arange(k)[:, None], np.arange(d_out)
+    if pattern == "diagonal":       # ordinary entries but for one
+        w = np.where(row == col, 1.0 + np.abs(w), 0.0)
+        w[0, 0] = 2.0 ** -40
+    if pattern == "blocks":         # one of the 8 x 8 blocks decayed
+        w = np.where(row // 8 == col // 8, w, 0.0)
+        w[:8] *= 2.0 ** -30
+    if pattern == "pruned":         # 2 % left, one row of them decayed
+        w = np.where(g.random((k, d_out)) < 0.02, w, 0.0)
+        w[3, :: d_out // 3] = 1e-8
+        w[3] *= 1e-8
+    if pattern == "comb":           # every 16th column tiny in half of the rows
+        w[: k // 2, ::16] *= 2.0 ** -30
+    if pattern == "decayed":        # a row at the end of the range, a row of zeros
+        w[1], w[2] = w[1] * 2.0 ** -125, 0.0
+    if pattern == "late":           # one large weight beside ordinary ones, in one column
+        w[k // 2, d_out // 2] *= 2.0 ** 60
+    return w.astype(np.float32)
+
+
+WEIGHT_PATTERNS = ["diagonal", "blocks", "pruned", "comb", "decayed", "late"]

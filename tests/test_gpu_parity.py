@@ -12,8 +12,8 @@ import oracle
 import paper_2408_09697_amd as heta
 from gen import rng, workloads
 from gen.graphs import HetGraph, NodeType, Relation, power_law_degrees
-from tests.harness import (assert_rows_close, compare_layer, dev_table, make_graph, make_layer,
-                           run_layer_on_gpu)
+from tests.harness import (WEIGHT_PATTERNS, assert_product, assert_rows_close, compare_layer, dev_table, make_graph, make_layer,
+                           patterned_weights, run_layer_on_gpu)
 
 pytestmark = pytest.mark.gpu
 
@@ -1269,19 +1269,16 @@ def test_graphs_created_in_one_batch_equal_graphs_created_one_by_one(mode, on_de
 @pytest.mark.parametrize("n,k,d_out,trans,segments", [(300, 70, 40, False, 1), (33001, 129, 256, True, 1), (120001, 100, 64, True, 2), (70001, 72, 130, False, 3), (50001, 129, 256, True, 1),
                                                       (200003, 20, 100, False, 2)])
 def test_f32_products_over_a_wide_range(n, k, d_out, trans, segments, kind):
-    """fp32 products are fed as fp16 terms scaled by a power of two per row and column.  growing: every 16 columns (and
-    every 16 rows, for the weight gradient) 2^6 larger than those before, so that scales are set anew all along; late: rows
-    that start with zeros; compensated: features spread over 2^40 (small launches: 2^24) whose weights make up for it;
-    specials: rows with an infinity or a NaN, which stay alone.  Launches on both sides of 24,576
-    steps of 64 x 64 x 16 and of 512 tiles, packed tiles of 64, 128 and 256 columns, sums and independent products.
-
-    Bound per element, in units of 2^-24 sum |a b|: one for each operand's representation, one for the term left out, and
-    two for each of the 3 ceil(K / 16) additions to the accumulator."""
+    """Every element of an fp32 operand keeps its own 24 bits, whatever stands beside it.  growing: every 16 columns (and
+    every 16 rows, for the weight gradient) 2^6 larger than those before; late: rows that start with zeros; compensated:
+    features spread over 2^40 whose weights make up for it; specials: rows with an infinity or a NaN, which stay alone, and
+    so do the columns of the weight gradient that belong to them.  Launches of small and of packed tiles of 64 and 128
+    columns, sums and independent products."""
     g = rng.stream("tests", f"range_{kind}_{n}_{k}")
     xs = [g.standard_normal((n, k)).astype(np.float32) for _ in range(segments)]
     ws = [g.standard_normal((k, d_out)).astype(np.float32) for _ in range(segments)]
     gout = g.standard_normal((n, d_out)).astype(np.float32)
-    bad = np.array([5, n // 2, n - 1])
+    bad, bad_col = np.array([5, n // 2, n - 1]), [0, k // 2, k - 1]
     for x, w in zip(xs, ws):
         if kind == "growing":
             x *= np.exp2(6.0 * (np.arange(k) // 16) + np.arange(n)[:, None] // 16 % 13 * 6.0 - 60.0).astype(np.float32)
@@ -1289,42 +1286,116 @@ def test_f32_products_over_a_wide_range(n, k, d_out, trans, segments, kind):
             x[:, : k // 2] *= (np.arange(n)[:, None] % 3 == 0)
             x[n // 3: n // 2] = 0.0
         if kind == "compensated":
-            span = 20.0 if n > 40000 else 12.0  # packed weights are levelled; small launches have the range of their terms
-            r = np.exp2(np.linspace(-span, span, k)[g.permutation(k)]).astype(np.float32)
+            r = np.exp2(np.linspace(-20.0, 20.0, k)[g.permutation(k)]).astype(np.float32)
             x *= r
             w /= r[:, None]
             w[k // 2] = 0.0
         if kind == "specials":
-            x[bad, [0, k // 2, k - 1]] = [np.inf, np.nan, -np.inf]
-    good = np.setdiff1d(np.arange(n), bad) if kind == "specials" else np.arange(n)
-    unit = 2.0 ** -24
-
-    def check(got, a, b, terms):
-        ref, size = np.zeros((a[0].shape[0], b[0].shape[1])), np.zeros((a[0].shape[0], b[0].shape[1]))
-        for x, w in zip(a, b):
-            ref += x.astype(np.float64) @ w.astype(np.float64)
-            size += np.abs(x.astype(np.float64)) @ np.abs(w.astype(np.float64))
-        err = np.abs(got.cpu().numpy().astype(np.float64) - ref)
-        bound = (3 + 6 * terms) * unit * size + 1e-37
-        assert np.all(err <= bound), float((err / bound).max())
-
+            x[bad, bad_col] = [np.inf, np.nan, -np.inf]
+    specials = kind == "specials"
+    good = np.setdiff1d(np.arange(n), bad) if specials else np.arange(n)
+    good_col = np.setdiff1d(np.arange(k), bad_col) if specials else np.arange(k)
     up = [dev_table(x, "f32", 4) for x in xs]
     wd = [dev_table(w.T.copy() if trans else w, "f32", 4) for w in ws]
     hg = heta.heta_graph_create([(n, 8, 0)], [])
     try:
-        steps = (k + 15) // 16
         out = torch.full((n, d_out), float("nan"), dtype=torch.float32, device="cuda")
         heta.heta_project_sum(up, wd, out, trans_w=trans, graph=hg)
-        check(out[torch.from_numpy(good).cuda()], [x[good] for x in xs], ws, steps * segments)
-        assert kind != "specials" or not torch.isfinite(out[torch.from_numpy(bad).cuda()]).any()
+        out = out.cpu().numpy()
+        assert_product(out[good], [x[good] for x in xs], ws, "sum")
+        assert not specials or not np.isfinite(out[bad]).any()
         outs = [torch.full((n, d_out), float("nan"), dtype=torch.float32, device="cuda") for _ in xs]
         heta.heta_project_batch(up, wd, outs, trans_w=trans, graph=hg)
         for o, x, w in zip(outs, xs, ws):
-            check(o[torch.from_numpy(good).cuda()], [x[good]], [w], steps)
-        if kind != "specials":
-            dws = [torch.full((k, d_out), float("nan"), dtype=torch.float32, device="cuda") for _ in xs]
-            heta.heta_project_wgrad_batch(hg, up, [dev_table(gout, "f32", 4) for _ in xs], dws, n_rows=n)
-            for o, x in zip(dws, xs):
-                check(o, [x.T], [gout], (n + 15) // 16)
+            assert_product(o.cpu().numpy()[good], [x[good]], [w], "batch")
+        dws = [torch.full((k, d_out), float("nan"), dtype=torch.float32, device="cuda") for _ in xs]
+        heta.heta_project_wgrad_batch(hg, up, [dev_table(gout, "f32", 4) for _ in xs], dws, n_rows=n)
+        for o, x in zip(dws, xs):
+            o = o.cpu().numpy()
+            assert_product(o[good_col], [x.T[good_col]], [gout], "weight gradient")
+            assert not specials or not np.isfinite(o[bad_col]).any()
+    finally:
+        hg.destroy()
+
+
+@pytest.mark.parametrize("pattern", WEIGHT_PATTERNS)
+@pytest.mark.parametrize("n,k,d_out,segments", [(500, 128, 128, 1), (60001, 128, 256, 1), (70001, 128, 64, 3), (40001, 256, 128, 2)])
+@pytest.mark.parametrize("trans", [False, True])
+def test_f32_products_with_weights_of_any_pattern(n, k, d_out, segments, trans, pattern):
+    """Diagonal, block-diagonal, pruned and partly decayed weights: every output column by itself, small launches and packed
+    weights, sums and independent products; the other segments' weights are ordinary."""
+    g = rng.stream("tests", f"pattern_{pattern}_{n}_{d_out}")
+    xs = [g.standard_normal((n, k)).astype(np.float32) for _ in range(segments)]
+    ws = [patterned_weights(pattern if s == 0 else "", k, d_out, g) for s in range(segments)]
+    up = [dev_table(x, "f32", 4) for x in xs]
+    wd = [dev_table(w.T.copy() if trans else w, "f32", 4) for w in ws]
+    hg = heta.heta_graph_create([(n, 8, 0)], [])
+    try:
+        out = torch.full((n, d_out), float("nan"), dtype=torch.float32, device="cuda")
+        heta.heta_project_sum(up, wd, out, trans_w=trans, graph=hg)
+        assert_product(out.cpu().numpy(), xs, ws, "sum")
+        outs = [torch.full((n, d_out), float("nan"), dtype=torch.float32, device="cuda") for _ in xs]
+        heta.heta_project_batch(up, wd, outs, trans_w=trans, graph=hg)
+        for o, x, w in zip(outs, xs, ws):
+            assert_product(o.cpu().numpy(), [x], [w], "batch")
+    finally:
+        hg.destroy()
+
+
+@pytest.mark.parametrize("n", [500, 60001])
+@pytest.mark.parametrize("trans", [False, True])
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+def test_an_infinite_weight_stays_in_its_column(n, trans, value):
+    k, d_out = 128, 256
+    g = rng.stream("tests", f"infinite_{n}")
+    x, w = g.standard_normal((n, k)).astype(np.float32), g.standard_normal((k, d_out)).astype(np.float32)
+    bad = [0, 101]  # the first and an odd column
+    w[[17, 90], bad] = value
+    good = np.setdiff1d(np.arange(d_out), bad)
+    hg = heta.heta_graph_create([(n, 8, 0)], [])
+    try:
+        out = torch.full((n, d_out), 7.0, dtype=torch.float32, device="cuda")
+        heta.heta_project_sum([dev_table(x, "f32", 4)], [dev_table(w.T.copy() if trans else w, "f32", 4)], out, trans_w=trans, graph=hg)
+        out = out.cpu().numpy()
+        assert not np.isfinite(out[:, bad]).any()
+        assert_product(out[:, good], [x], [w[:, good]])
+    finally:
+        hg.destroy()
+
+
+@pytest.mark.parametrize("n", [3000, 40001])
+@pytest.mark.parametrize("power", [20, 40, 100])
+def test_f32_weight_gradients_beside_rows_without_gradient(n, power):
+    """Rows 2^power larger than the others whose gradient is zero (a masked hub of a sum) leave nothing behind, and neither
+    does a gradient 2^power larger than the others where the features are zero; the products of both are exact zeros."""
+    k, d_out = 128, 64
+    g = rng.stream("tests", f"masked_{n}_{power}")
+    x, go = np.abs(g.standard_normal((n, k))).astype(np.float32), g.standard_normal((n, d_out)).astype(np.float32)
+    hubs, masked = [3, n // 2], [n // 3, n - 2]
+    x[hubs], go[hubs] = x[hubs] * np.float32(2.0 ** power), 0.0
+    go[masked], x[masked] = go[masked] * np.float32(2.0 ** power), 0.0
+    hg = heta.heta_graph_create([(n, 8, 0)], [])
+    try:
+        dw = torch.full((k, d_out), float("nan"), dtype=torch.float32, device="cuda")
+        heta.heta_project_wgrad_batch(hg, [dev_table(x, "f32", 4)], [dev_table(go, "f32", 4)], [dw], n_rows=n)
+        assert_product(dw.cpu().numpy(), [x.T], [go])
+    finally:
+        hg.destroy()
+
+
+@pytest.mark.parametrize("k", [8192, 8193, 9000])
+@pytest.mark.parametrize("n", [200, 12700])
+def test_f32_products_with_many_rows_of_weights(n, k):
+    """More rows of weights, spread over 2^40, than a workgroup has threads for by far; small tiles and packed weights."""
+    d_out = 16
+    g = rng.stream("tests", f"tall_{k}")
+    w = (g.standard_normal((k, d_out)) * np.exp2(np.linspace(-20.0, 20.0, k))[g.permutation(k), None]).astype(np.float32)
+    x = torch.randn((n, (k + 3) // 4 * 4), generator=torch.Generator(device="cuda").manual_seed(k), device="cuda")[:, :k]
+    hg = heta.heta_graph_create([(n, 8, 0)], [])
+    try:
+        out = torch.full((n, d_out), float("nan"), dtype=torch.float32, device="cuda")
+        heta.heta_project_batch([x], [dev_table(w, "f32", 4)], [out], graph=hg)
+        rows = torch.arange(0, n, max(1, n // 150))
+        assert_product(out[rows.cuda()].cpu().numpy(), [x[rows.cuda()].cpu().numpy()], [w])
     finally:
         hg.destroy()
