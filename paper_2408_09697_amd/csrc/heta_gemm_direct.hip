@@ -247,11 +247,12 @@ __device__ __forceinline__ uint4 dfrag_bf16_rc_from_f32(const float *tile, int r
 }
 
 // fp32 products on the bf16 matrix pipe.  x = h + m + l with three bf16 terms (h = bf16(x), m = bf16(x - h),
-// l = bf16(x - h - m); both differences are exact in fp32), so |x - (h + m + l)| <= 2^-27 |x|.  A product a b
+// l = bf16(x - h - m); both differences are exact in fp32) is exact: eight bits each, a remainder's sign its ninth.
+// Only below 2^-110, where l leaves bf16's range, does x lose bits.  A product a b
 // is fed as the six terms ah bh, ah bm, am bh, am bm, ah bl, al bh (each a product of two 8-bit significands,
-// exact in the fp32 accumulator's input); the three terms left out are below 2^-25 |a b|, less than the
-// rounding of one fp32 multiplication.  Six bf16 MFMAs of 16 k-values cost 6 x 8 passes where the fp32 MFMA
-// needs 8 x 16 for the same 16 k-values.
+// exact in the fp32 accumulator's input); |m| <= 2^-8 |x|, |l| <= 2^-17 |x|, so the three terms left out are at most
+// 2^-24 |a b|, the rounding of one fp32 multiplication (over random significands 2^-27.5 rms).  Six bf16 MFMAs of
+// 16 k-values cost 6 x 8 passes where the fp32 MFMA needs 8 x 16 for the same 16 k-values.
 __device__ __forceinline__ void split3_pair(float x0, float x1, uint32_t &h, uint32_t &m, uint32_t &l)
 {
     h = pack_bf16(x0, x1);

@@ -237,8 +237,8 @@ def assert_product(got: np.ndarray, a, b, what=""):
     """got = sum of the products a[s] @ b[s] of fp32 operands, fed to the matrix unit as bf16 terms (three per operand, six
     products of 16 k-values each).  Unit u = 2^-24.
 
-    Per element: representing both operands and leaving out three of the nine products costs less than one u of
-    sum |a b|; each of the 6 ceil(K / 16) additions to the accumulator at most two u of it.
+    Per element: three bf16 terms are an fp32 value exactly, leaving out three of their nine products costs at most one u of
+    |a b|; each of the 6 ceil(K / 16) additions to the accumulator at most two u of sum |a b|.
     Per column (2-norm): these errors fall on either side, and the accumulator they are relative to is the sum so far,
     about R = sqrt(sum a^2 b^2) where the signs are mixed: 1 + 2 sqrt(additions) u of R."""
     ref, mag, sq, additions = 0.0, 0.0, 0.0, 0

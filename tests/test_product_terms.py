@@ -38,6 +38,16 @@ def product(a, b, pairs, form="bf16"):
     return acc * np.exp2(-ea - eb)
 
 
+def test_three_bf16_terms_are_the_value_and_six_products_all_but_2_to_the_minus_24_of_theirs():
+    """Over every significand; the extremes of |m| and |l| bound what three of the nine products can hold."""
+    x = (np.arange(1 << 23, dtype=np.uint32) | np.uint32(127 << 23)).view(np.float32)
+    h, m, l = terms(x, 3, "bf16")
+    assert np.array_equal(h.astype(np.float64) + m + l, x.astype(np.float64))
+    m, l = np.abs(m / x), np.abs(l / x)
+    assert m.max() <= 2.0 ** -8 and l.max() <= 2.0 ** -17
+    assert 2 * m.max() * l.max() + l.max() ** 2 <= 2.0 ** -24
+
+
 SIX = [(0, 0), (0, 1), (0, 2), (1, 0), (1, 1), (2, 0)]  # three bf16 terms per operand
 THREE = [(0, 0), (0, 1), (1, 0)]                        # two terms per operand
 
