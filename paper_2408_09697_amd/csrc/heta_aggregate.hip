@@ -612,19 +612,19 @@ __device__ __forceinline__ void agg_wave_body(const AggParams &p, const unsigned
 }
 
 // ---- hub rows: add the chunk partials in chunk order -------------------------------------------------
-// One workgroup of 4 wavefronts per (hub row, tile of 4 LPC columns); lane group g of wavefront w (LPC lanes) adds the
-// partials q, q + Q, q + 2 Q, ... with q = w + 4 g, Q the number of lane groups (sixteen loads in flight); the groups' sums
-// are combined by shuffles and the wavefronts' through LDS in wavefront order, so the summation order is fixed.
+// Sixteen lane groups of LPC lanes per (hub row, tile of 4 LPC columns): group q adds the partials q, q + 16, q + 32, ...
+// (sixteen loads in flight) and the groups' sums are added through LDS in the order of q.  That order is what the sums
+// are made of, whatever the tile, so it does not move with the tiling (gradients behind a ReLU show its last bits).
 // A power-law relation has one hub of up to millions of edges, thousands of partials, and the launch takes as long as
-// that row takes the CUs its tiles are on; the other rows have a few partials each, so the workgroups are small.
-// LPC = 8 (32 columns) unless a dot over wider heads needs the head in one tile.  (16 wavefronts and 256 columns per
-// workgroup: relations of 4 M edges, 467 hub rows of 256 columns 85 us, four of 128 columns in one launch 64; now 27 and
-// 32.  16 wavefronts and 64 columns: 37 and 45, and 26 us instead of 18 on 787 rows of a few partials each.)
-constexpr int kCombineWaves = 4;
+// that row takes the CUs its tiles are on; the other rows have a few partials each, so the workgroups are small:
+// LPC = 8 (32 columns, two wavefronts) unless a dot over wider heads needs the head in one tile.  All hub sums of an
+// R-GAT layer of 21 M edges and 256 columns: one workgroup of 16 wavefronts per 256 columns 238 us, four wavefronts per
+// 32 columns with 32 groups 129, this 92; of a layer of 128 columns 75, 66 and 48.
+constexpr int kCombineChains = 16;
 template <int LPC> __device__ __forceinline__ void agg_hub_combine_body(const AggParams &p, int tiles, bool second)
 {
-    constexpr int G = 64 / LPC, Q = kCombineWaves * G, U = 16;
-    __shared__ float4 part[kCombineWaves][LPC];
+    constexpr int G = 64 / LPC, W = kCombineChains / G, Q = kCombineChains, U = 16;
+    __shared__ float4 part[Q][LPC];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l = lane % LPC, g = lane / LPC;
     const int64_t h = blockIdx.x / tiles; // the tiles of a row are neighbours: all of the largest row, which is first, start at once
@@ -636,7 +636,7 @@ template <int LPC> __device__ __forceinline__ void agg_hub_combine_body(const Ag
     const bool dot = second && p.dot_out;
     float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
     if (col0 < p.ws_ld) {
-        for (int64_t s = s0 + wave + kCombineWaves * g; s < s1; s += U * Q) {
+        for (int64_t s = s0 + wave + W * g; s < s1; s += U * Q) {
             float4 v[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -648,17 +648,12 @@ template <int LPC> __device__ __forceinline__ void agg_hub_combine_body(const Ag
             for (int u = 0; u < U; ++u) { a.x += v[u].x; a.y += v[u].y; a.z += v[u].z; a.w += v[u].w; }
         }
     }
-#pragma unroll
-    for (int off = LPC; off < 64; off <<= 1) {
-        a.x += __shfl_xor(a.x, off, 64); a.y += __shfl_xor(a.y, off, 64);
-        a.z += __shfl_xor(a.z, off, 64); a.w += __shfl_xor(a.w, off, 64);
-    }
-    if (g == 0) part[wave][l] = a;
+    part[wave + W * g][l] = a;
     __syncthreads();
     if (wave != 0 || g != 0 || (col0 >= p.d && !dot)) return;
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int k = 0; k < kCombineWaves; ++k) {
+    for (int k = 0; k < Q; ++k) {
         const float4 v = part[k][l];
         acc[0] += v.x; acc[1] += v.y; acc[2] += v.z; acc[3] += v.w;
     }
@@ -699,7 +694,7 @@ __global__ void __launch_bounds__(256, EPC == 8 ? (MODE == AGG_PLAIN ? 7 : 5) : 
     else agg_wave_body<T, EPC, L, CPL, MODE, false>(p, bx);
 }
 // Hub rows of up to N relations: blockIdx.y is the relation, or with second sums 2 * relation + (1 for the second).
-template <int LPC, int N> __global__ void __launch_bounds__(64 * kCombineWaves) agg_hub_combine_kernel(AggLaunch<N> m, int tiles, int dual)
+template <int LPC, int N> __global__ void __launch_bounds__(kCombineChains * LPC) agg_hub_combine_kernel(AggLaunch<N> m, int tiles, int dual)
 {
     agg_hub_combine_body<LPC>(m.p[dual ? blockIdx.y >> 1 : blockIdx.y], tiles, dual && (blockIdx.y & 1));
 }
@@ -877,7 +872,7 @@ static void launch_hub_combine(const AggParams *ps, int n, int lpc, unsigned blo
 {
     AggLaunch<N> m{};
     for (int i = 0; i < n; ++i) m.p[i] = ps[i];
-    const dim3 grid(blocks, dual ? 2 * n : n), threads(64 * kCombineWaves);
+    const dim3 grid(blocks, dual ? 2 * n : n), threads(kCombineChains * lpc);
     if (lpc == 64) hipLaunchKernelGGL((agg_hub_combine_kernel<64, N>), grid, threads, 0, st, m, tiles, (int)dual);
     else if (lpc == 16) hipLaunchKernelGGL((agg_hub_combine_kernel<16, N>), grid, threads, 0, st, m, tiles, (int)dual);
     else hipLaunchKernelGGL((agg_hub_combine_kernel<8, N>), grid, threads, 0, st, m, tiles, (int)dual);
@@ -913,7 +908,7 @@ static heta_status launch_plans(const AggPlan *plans, int n, hipStream_t st, boo
     }
     const int lpc = head > 64 ? 64 : head > 32 ? 16 : 8;
     const int tiles = static_cast<int>((width + 4 * lpc - 1) / (4 * lpc));
-    if (hub_rows * tiles > max_blocks(64 * kCombineWaves)) return fail(HETA_ERR_UNSUPPORTED, "aggregate: too many hub rows");
+    if (hub_rows * tiles > max_blocks(kCombineChains * lpc)) return fail(HETA_ERR_UNSUPPORTED, "aggregate: too many hub rows");
     ProfScope prof(timed ? "agg_hub_combine_kernel" : nullptr, st, hub_bytes, 0);
     if (n == 1) launch_hub_combine<1>(ps, 1, lpc, static_cast<unsigned>(hub_rows * tiles), tiles, f.dual, st);
     else launch_hub_combine<kAggMulti>(ps, n, lpc, static_cast<unsigned>(hub_rows * tiles), tiles, f.dual, st);

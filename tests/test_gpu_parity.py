@@ -1399,3 +1399,33 @@ def test_f32_products_with_many_rows_of_weights(n, k):
         assert_product(out[rows.cuda()].cpu().numpy(), [x[rows.cuda()].cpu().numpy()], [w])
     finally:
         hg.destroy()
+
+
+@pytest.mark.parametrize("d,storage", [(40, "f32"), (200, "f32"), (257, "f32"), (256, "bf16")])
+def test_hub_rows_are_summed_in_sixteen_chains(d, storage):
+    """The order of a hub row's sum does not depend on its tiling: partials of 256 edges, the q-th of sixteen chains takes
+    every 16th from q on, the chains are added in order.  Whole numbers make the partials exact, so only that order rounds."""
+    g = rng.stream("tests", f"hub_{d}")
+    degs, n_src = [25_700, 513, 8192, 9000 + d], 500
+    table = g.integers(1 << 14, 1 << 15, size=(n_src, d)) * 2 + 1
+    if storage == "bf16":
+        table = g.integers(128, 256, size=(n_src, d)) << g.integers(0, 9, size=(n_src, d))
+    table = table.astype(np.float32)
+    rowptr = np.concatenate([[0], np.cumsum(degs)]).astype(np.int64)
+    col = g.integers(0, n_src, size=int(rowptr[-1]), dtype=np.int32)
+    hg = heta.heta_graph_create([(n_src, 8, 0), (len(degs), 8, 0)], [(0, 1, rowptr, col)])
+    try:
+        out = torch.full((len(degs), d), 7.0, device="cuda")
+        heta.heta_rel_aggregate_fwd(hg, 0, heta.HETA_SUM, dev_table(table, storage, 8), out)
+        for row, (e0, e1) in enumerate(zip(rowptr[:-1], rowptr[1:])):
+            chains = np.zeros((16, d), dtype=np.float32)
+            for i, e in enumerate(range(e0, e1, 256)):
+                partial = table[col[e:min(e + 256, e1)]].astype(np.float64).sum(0)
+                assert partial.max() < 2.0 ** 24
+                chains[i % 16] += partial.astype(np.float32)
+            want = np.zeros(d, dtype=np.float32)
+            for c in chains:
+                want += c
+            assert np.array_equal(out[row].cpu().numpy(), want), (row, d)
+    finally:
+        hg.destroy()

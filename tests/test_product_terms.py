@@ -27,7 +27,7 @@ def product(a, b, pairs, form="bf16"):
     of b puts its largest element below 2^15."""
     ea = eb = np.zeros(1)
     if form == "fp16":
-        ea, eb = (14 - np.floor(np.log2(np.abs(x).max(axis=axis, keepdims=True) + 1e-37)) for x, axis in ((a, 1), (b, 0)))
+        ea, eb = (14 - np.floor(np.log2(np.maximum(np.abs(x).max(axis=axis, keepdims=True), 2.0 ** -100))) for x, axis in ((a, 1), (b, 0)))
         a, b = (a * np.exp2(ea)).astype(np.float32), (b * np.exp2(eb)).astype(np.float32)
     n = max(max(p) for p in pairs) + 1
     ta, tb = terms(a, n, form), terms(b, n, form)
