@@ -754,22 +754,22 @@ static heta_status launch_rows(const AggParams *ps, int n, int n_super, hipStrea
     if constexpr (EPC > 1) {
         if (ps[0].slot_form == SLOT_BOTH) return launch_mode<T, EPC, L, CPL, AGG_DUAL>(ps, n, n_super, st, cost);
     }
-    if constexpr (L == 64 && EPC > 1) return fail(HETA_ERR_UNSUPPORTED, "aggregate: rows of 64 lanes are the two-weight form's");
-    else {
-        if (ps[0].slot_w) return launch_mode<T, EPC, L, CPL, AGG_SLOT>(ps, n, n_super, st, cost);
-        return launch_mode<T, EPC, L, CPL, AGG_PLAIN>(ps, n, n_super, st, cost);
-    }
+    if (ps[0].slot_w) return launch_mode<T, EPC, L, CPL, AGG_SLOT>(ps, n, n_super, st, cost);
+    if constexpr (L == 64 && EPC > 1) return fail(HETA_ERR_UNSUPPORTED, "aggregate: rows of 64 lanes are the weighted forms'");
+    else return launch_mode<T, EPC, L, CPL, AGG_PLAIN>(ps, n, n_super, st, cost);
 }
 
 // Lanes per row and column tiles (grid.y) of the 128-bit paths: a row of more than 32 chunks is walked in tiles of 32.
 // Against one lane group of 64 lanes, or of 64 lanes with two chunks each: 4 M edges of 1 KB rows from a table of 1.1 GB
-// 838 -> 771 us, of 0.7 GB 775 -> 730; and a row of 96 chunks leaves no lane idle.  The one-pass dot over a head of more
-// than 32 chunks needs the head in one tile.
-static int lanes_per_row(const AggParams &p, int epc, int n_chunks)
+// 838 -> 771 us, of 0.7 GB 775 -> 730; and a row of 96 chunks leaves no lane idle.  Rows weighted per slot keep one group
+// up to 64 chunks: their kernels are bound by registers, not by lanes (all weighted gathers of an R-GAT layer of 21 M edges
+// and 256 columns 9.64 ms, 9.56 in tiles of 32), a long row's edges are added one after the other, not in two halves, and
+// the one-pass dot needs a head's columns in one tile (it is taken up to 64 chunks).
+static int lanes_per_row(const AggParams &p, int n_chunks)
 {
-    if (p.slot_form == SLOT_BOTH && p.dot_out && p.head_dim / epc > 32) return 64;
+    const int most = p.slot_w && n_chunks <= 64 ? 64 : 32;
     int L = 1;
-    while (L < n_chunks && L < 32) L <<= 1;
+    while (L < n_chunks && L < most) L <<= 1;
     return L;
 }
 
@@ -815,7 +815,7 @@ static heta_status plan_aggregate(const Schedule &s, AggParams p, heta_dtype in_
     const bool dual = p.slot_form == SLOT_BOTH;
     const int epc = vec ? static_cast<int>(16 / esz) : 1;
     const int n_chunks = (p.d + epc - 1) / epc;
-    const int L = vec ? lanes_per_row(p, epc, n_chunks) : 64;
+    const int L = vec ? lanes_per_row(p, n_chunks) : 64;
     const int G = 64 / L;
     // rows with at least this many edges get a whole wavefront
     const int wave_min = kShortDeg;

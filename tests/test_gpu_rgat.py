@@ -445,6 +445,28 @@ def test_attention_of_several_relations_in_one_call(d, heads, storage):
         hg.destroy()
 
 
+@pytest.mark.parametrize("d,storage,train", [(256, "f32", False), (256, "f32", True), (200, "f32", True), (512, "bf16", False), (512, "bf16", True)])
+def test_edges_of_a_long_row_are_added_in_order(d, storage, train):
+    """Rows of up to 64 chunks have one lane group: 64 edges of one weight (2^-6 exactly, since all scores are equal) are
+    added one after the other, whether one sum or two are taken."""
+    gen = torch.Generator().manual_seed(d)
+    n_src, n_dst, heads = 300, 5, 4
+    col = torch.randint(0, n_src, (64 * n_dst,), generator=gen, dtype=torch.int32)
+    hg = heta.heta_graph_create([(n_src, 4, 0), (n_dst, 4, 0)], [(0, 1, np.arange(n_dst + 1, dtype=np.int64) * 64, col.numpy())])
+    try:
+        z = torch.randn((n_src, d), generator=gen).to(torch.float32 if storage == "f32" else torch.bfloat16)
+        el, er = torch.ones((n_src, heads), device="cuda"), torch.ones((n_dst, heads), device="cuda")
+        out, pos = torch.full((n_dst, d), 7.0, device="cuda"), torch.full((n_dst, d), 7.0, device="cuda")
+        heta.heta_rel_attn_fwd(hg, 0, z.cuda(), el, er, 0.2, out, out_pos=pos if train else None)
+        want = torch.zeros((n_dst, d))
+        for e in range(64):
+            want += z.float()[col.view(n_dst, 64)[:, e].long()] * 2.0 ** -6
+        assert torch.equal(out.cpu(), want)
+        assert not train or torch.equal(pos.cpu(), want)  # every logit is positive
+    finally:
+        hg.destroy()
+
+
 def test_attention_argument_checks():
     graph = heta.heta_graph_create([(4, 4, 0)], [(0, 0, np.array([0, 1, 2, 2, 2], dtype=np.int64), np.array([1, 0], dtype=np.int32))])
     z = torch.zeros((4, 12), device="cuda")
