@@ -1504,21 +1504,28 @@ __global__ void __launch_bounds__(1024) attn_multi_slab_sum_kernel(const float *
 // ---- the source score taken off the input table ------------------------------------------------------
 // el[u, k] = <z_u[k, :], a[k, :]> with z_u = W^T h_u equals <h_u, wa[k, :]> with wa[k, j] = sum_f W[j, kF + f] a[k, f]:
 // the scores then come from the (narrower, never rounded) input table instead of the stored projection.
-// Eight lanes per (k, j) take f round-robin and are combined by a fixed butterfly: the matrix is small, and what counts is
-// the chain of loads of one lane (128 x 256, 4 heads: one lane per element 11.5 us, eight 4.7).
+// One lane per (k, j), so that the sum over f runs in order; the matrix is small, and what counts is the chain of loads of
+// one lane, so sixteen are in flight, on workgroups of one wavefront (128 x 256, 4 heads: 9.5 us one by one, now 3.0, eight
+// lanes per element 2.8; 768 x 1,024 34.0, 5.7 and 5.0).
 template <typename T>
-__global__ void __launch_bounds__(256) attn_fold_kernel(const T *W, int64_t ld_w, int d_in, int K, int F, const float *a, float *wa)
+__global__ void __launch_bounds__(64) attn_fold_kernel(const T *W, int64_t ld_w, int d_in, int K, int F, const float *a, float *wa)
 {
-    const int t = blockIdx.x * 32 + (threadIdx.x >> 3), l = threadIdx.x & 7;
+    const int t = blockIdx.x * 64 + threadIdx.x;
+    if (t >= K * d_in) return;
+    const int k = t / d_in, j = t - k * d_in;
+    const T *w = W + static_cast<int64_t>(j) * ld_w + k * F;
+    a += k * F;
     float acc = 0.f;
-    if (t < K * d_in) {
-        const int k = t / d_in, j = t - k * d_in;
-        const T *w = W + static_cast<int64_t>(j) * ld_w + k * F;
-        for (int f = l; f < F; f += 8) acc = fmaf(ld1(w + f), a[k * F + f], acc);
-    }
+    int f = 0;
+    for (; f + 16 <= F; f += 16) {
+        float x[16];
 #pragma unroll
-    for (int off = 4; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64); // every lane of the wavefront takes part
-    if (l == 0 && t < K * d_in) wa[t] = acc;
+        for (int i = 0; i < 16; ++i) x[i] = ld1(w + f + i);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc = fmaf(x[i], a[f + i], acc);
+    }
+    for (; f < F; ++f) acc = fmaf(ld1(w + f), a[f], acc);
+    wa[t] = acc;
 }
 
 // Its backward, both halves in one launch (two of 4.9 us before, one of 4.9 now at 128 x 256):
@@ -1899,12 +1906,12 @@ heta_status heta_attn_fold(const void *W, heta_dtype w_dt, int64_t ld_w, int32_t
         return fail(HETA_ERR_INVALID_ARG, "heta_attn_fold: pointer not aligned to its element size");
     hipStream_t st = as_stream(hip_stream);
     const int F = d_out / heads;
-    const unsigned blocks = static_cast<unsigned>((static_cast<int64_t>(heads) * d_in + 31) / 32);
+    const unsigned blocks = static_cast<unsigned>((static_cast<int64_t>(heads) * d_in + 63) / 64);
     if (w_dt == HETA_F32)
-        hipLaunchKernelGGL(attn_fold_kernel<float>, dim3(blocks), dim3(256), 0, st, static_cast<const float *>(W), ld_w, (int)d_in,
+        hipLaunchKernelGGL(attn_fold_kernel<float>, dim3(blocks), dim3(64), 0, st, static_cast<const float *>(W), ld_w, (int)d_in,
                            (int)heads, F, a, wa);
     else
-        hipLaunchKernelGGL(attn_fold_kernel<bf16_t>, dim3(blocks), dim3(256), 0, st, static_cast<const bf16_t *>(W), ld_w, (int)d_in,
+        hipLaunchKernelGGL(attn_fold_kernel<bf16_t>, dim3(blocks), dim3(64), 0, st, static_cast<const bf16_t *>(W), ld_w, (int)d_in,
                            (int)heads, F, a, wa);
     HETA_LAUNCH_CHECK("attn_fold_kernel");
     return HETA_OK;

@@ -467,6 +467,26 @@ def test_edges_of_a_long_row_are_added_in_order(d, storage, train):
         hg.destroy()
 
 
+@pytest.mark.parametrize("d_in,heads,F", [(128, 4, 64), (70, 3, 20), (1, 1, 5), (33, 2, 16), (768, 8, 33)])
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+def test_folded_score_vector_is_summed_in_order(d_in, heads, F, storage):
+    """wa[k, j] = sum_f W[j, k F + f] a[k, f], f = 0, 1, ...: factors of 12 bits make the products exact, and every sum of two
+    fp32 values of these sizes is exact in 64 bits, so each step rounds once, as the fused multiply-add does."""
+    gen = torch.Generator().manual_seed(F)
+
+    def factors(shape, bits):
+        return torch.randint(1 << (bits - 1), 1 << bits, shape, generator=gen) * torch.randint(0, 2, shape, generator=gen).mul(2).sub(1) / float(1 << bits)
+
+    W, a = factors((d_in, heads * F), 12 if storage == "f32" else 8), factors((heads, F), 12)
+    W = W.to(torch.float32 if storage == "f32" else torch.bfloat16)
+    wa = torch.full((heads, d_in), 7.0, device="cuda")
+    heta.heta_attn_fold(W.cuda(), a.float().cuda(), wa)
+    want = torch.zeros((heads, d_in), dtype=torch.float64)
+    for f in range(F):
+        want = (want + W.double().view(d_in, heads, F)[:, :, f].T * a.double()[:, f:f + 1]).float().double()
+    assert torch.equal(wa.cpu(), want.float())
+
+
 def test_attention_argument_checks():
     graph = heta.heta_graph_create([(4, 4, 0)], [(0, 0, np.array([0, 1, 2, 2, 2], dtype=np.int64), np.array([1, 0], dtype=np.int32))])
     z = torch.zeros((4, 12), device="cuda")
