@@ -40,6 +40,7 @@ struct GemmParams {
     int out_bf16;        // outputs are bf16 [M][ldc] (plain stores only: no beta, scale, activation, split)
     int64_t k_per_split; // multiple of BK
     int n_split;
+    int both_signs;      // B3 holds the terms of B and, behind them, those of -B (input gradients)
     int partial;         // write raw partial products [split][M][ldc] (ldc = N) instead of the output
     int64_t mt, nt;      // tile counts (maximum over the segments in batch mode)
 };
@@ -254,8 +255,8 @@ struct TileLoader {
 extern bool g_f32_native; // test switch, see heta_test_hooks.h
 // Bytes of the three-term form of a K x N fp32 operand, and the launch that writes it for the B operands of all of p's
 // segments, one after the other into `out` (16-byte aligned): B(k, n) = W[k*ldw + n] (trans = 0) or W[n*ldw + k]
-// (trans = 1); x = h + m + l in bf16, zero beyond K and N.
-size_t split3_weight_bytes(int64_t K, int64_t N);
+// (trans = 1, an input gradient: the terms of B and behind them those of -B, see flip_signs); zero beyond K and N.
+size_t split3_weight_bytes(int64_t K, int64_t N, int trans);
 heta_status pack_split3_weights(GemmParams &p, int trans, void *out, hipStream_t st);
 // whether the direct pipeline would give this launch its 64 x 64 tiles (too few 128 x 128 tiles to fill the chip)
 bool gemm_direct_small(const GemmParams &p);

@@ -280,6 +280,19 @@ __device__ __forceinline__ void dfrag_load8(const float *tile, int r, int kk, in
     }
 }
 
+// The bf16 matrix instruction's accumulator loses more downwards than upwards: its error leans to one side by 0.04 of its
+// size over 128 k-values, 0.06 over 256 (the fp32 instruction's does not).  Where products are summed on, over the splits of
+// a weight gradient or over the rows that a hub gathers, that part adds up while the rest averages out.  So every other
+// split, and every other row tile of an input gradient, forms the negative product: A with its signs flipped as it is
+// split (weight gradient: both operands are data), or weights that are packed in both signs, and the epilogue turns the
+// accumulator around.  Weight gradients of 700 k rows and more 2.8e-6 -> 9e-7 off 64 bits, gradients of gathered rows
+// 1.9e-6 -> 2.8e-7 (layer of 21 M edges).
+__device__ __forceinline__ void flip_signs(float x[8], uint32_t flip)
+{
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = __uint_as_float(__float_as_uint(x[j]) ^ flip);
+}
+
 // Eight k-values (the first is k0 of its tile) as three bf16 fragments; with MASKED, k-values from kv on
 // count as zero (branch-free: the caller's code stays one scheduling region).
 template <bool MASKED> __device__ __forceinline__ void split3_frag(const float x[8], int k0, int kv, uint4 out[3])
@@ -426,12 +439,14 @@ __device__ __forceinline__ void x3_step_2x2_presplit(const float *At, const char
 }
 
 // Writes the three-term form of the B operands of a product: one thread per (k-octet, column), blockIdx.y picks the
-// operand.  A launch of its own takes 4.5 us however small the matrix; one per operand was 5 % of a layer of 2 M edges.
+// operand; with `both`, that of -B behind it.  A launch of its own takes 4.5 us however small the matrix; one per operand
+// was 5 % of a layer of 2 M edges.
 struct Split3Segs {
     const float *W[kMaxSeg];
     uint4 *out[kMaxSeg];
     int64_t ldw[kMaxSeg];
     int K[kMaxSeg], N[kMaxSeg], ko[kMaxSeg], n_pad[kMaxSeg];
+    int both;
 };
 __global__ void __launch_bounds__(256) pack_split3_kernel(Split3Segs q, int trans)
 {
@@ -458,6 +473,11 @@ __global__ void __launch_bounds__(256) pack_split3_kernel(Split3Segs q, int tran
     out[at] = make_uint4(h[0], h[1], h[2], h[3]);
     out[plane + at] = make_uint4(m[0], m[1], m[2], m[3]);
     out[2 * plane + at] = make_uint4(l[0], l[1], l[2], l[3]);
+    if (!q.both) return;
+    constexpr uint32_t S = 0x80008000u;
+    out[3 * plane + at] = make_uint4(h[0] ^ S, h[1] ^ S, h[2] ^ S, h[3] ^ S);
+    out[4 * plane + at] = make_uint4(m[0] ^ S, m[1] ^ S, m[2] ^ S, m[3] ^ S);
+    out[5 * plane + at] = make_uint4(l[0] ^ S, l[1] ^ S, l[2] ^ S, l[3] ^ S);
 }
 
 // The sequence of k-tiles a workgroup walks: the k range of its split in every segment it owns.
@@ -608,7 +628,7 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
     // when fragments are read); a staged operand lies there in the compute type
     using DA = std::conditional_t<A_DIRECT, DirectLoader<SA_T, A_RC && A_DIRECT, BM, BK, NW>, NoLoader>;
     // X3: fp32 operands as three bf16 terms each - 1: both split when their fragments are read, 2: B comes pre-split
-    constexpr bool W3 = X3 == 2;
+    constexpr bool W3 = X3 == 2, X3_WGRAD = X3 == 1 && A_RC && B_RC;
     using DB = std::conditional_t<W3, Split3Loader<BN, NW>, std::conditional_t<B_DIRECT, DirectLoader<SB_T, B_RC && B_DIRECT, BN, BK, NW>, NoLoader>>;
     using SA = std::conditional_t<A_DIRECT, NoLoader, TileLoader<SA_T, CT, A_RC, BM, NT, true, BK>>;
     using SB = std::conditional_t<B_DIRECT, NoLoader, TileLoader<SB_T, CT, B_RC, BN, NT, true, BK>>;
@@ -650,6 +670,8 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
     const int64_t n0 = (rest % p.nt) * BN;
     const int64_t m0 = (p.partial ? rest / p.nt : outer) * BM;
     const int64_t split = p.partial ? outer : 0;
+    const bool negated = X3_WGRAD ? (outer & 1) : W3 && p.both_signs && (outer & 1); // uniform: see flip_signs
+    const uint32_t flip = negated ? 0x80000000u : 0u;
     const GemmSeg &out_seg = p.seg[s0];
     if (m0 >= out_seg.M || n0 >= out_seg.N) return; // uniform per workgroup
     const int rows_a = static_cast<int>(min(out_seg.M - m0, static_cast<int64_t>(BM)));
@@ -675,7 +697,7 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
     auto init_direct = [&]() {
         const GemmSeg &g = p.seg[I.s];
         if constexpr (A_DIRECT) da.init(static_cast<const SA_T *>(g.A), g.lda, m0, g.M, I.k, wave, lane);
-        if constexpr (W3) db.init(g.B3, g.ko, g.n_pad, n0, I.k, lane);
+        if constexpr (W3) db.init(static_cast<const char *>(g.B3) + (negated ? static_cast<int64_t>(g.ko) * g.n_pad * 48 : 0), g.ko, g.n_pad, n0, I.k, lane);
         else if constexpr (B_DIRECT) db.init(static_cast<const SB_T *>(g.B), g.ldb, n0, g.N, I.k, wave, lane);
     };
     auto init_staged = [&]() {
@@ -794,6 +816,7 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
                     for (int i = 0; i < MI; ++i) {
                         float x[8];
                         dfrag_load8<A_RC, BM, BK>(reinterpret_cast<const float *>(At), wm + i * 32 + l32, kk, half, x);
+                        if constexpr (X3_WGRAD) flip_signs(x, flip);
                         if (ragged) split3_frag<true>(x, kk + 8 * half, kv, a3[i]);
                         else split3_frag<false>(x, kk + 8 * half, kv, a3[i]);
                     }
@@ -874,6 +897,14 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
     }
 
     barrier_no_drain();     // every wavefront's last fragment reads are done (they fed its last MFMAs)
+    if ((W3 || X3_WGRAD) && negated) {
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int jj = 0; jj < NJ; ++jj)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[i][jj][v] = 0.f - acc[i][jj][v]; // zero stays +0
+    }
     static_assert(A_BYTES + B_BYTES >= NW * 8 * (32 * NJ + 4) * 4, "the epilogue strips overlay the ring");
     store_tile<MI, NJ>(p, out_seg, reinterpret_cast<float *>(ring), acc, wave, lane, wm, wn, m0, n0, rows_a, rows_b, split);
 }
@@ -920,11 +951,12 @@ bool gemm_direct_small(const GemmParams &p)
 
 static int64_t split3_octets(int64_t K) { return (K + 15) / 16 * 2; }
 static int64_t split3_columns(int64_t N) { return (N + 127) / 128 * 128; }
-size_t split3_weight_bytes(int64_t K, int64_t N) { return static_cast<size_t>(3 * split3_octets(K) * split3_columns(N) * 16); } // whole KBs
+size_t split3_weight_bytes(int64_t K, int64_t N, int trans) { return static_cast<size_t>((trans ? 6 : 3) * split3_octets(K) * split3_columns(N) * 16); } // whole KBs
 
 heta_status pack_split3_weights(GemmParams &p, int trans, void *out, hipStream_t st)
 {
     Split3Segs q{};
+    q.both = p.both_signs = trans;
     int64_t chunks = 0;
     char *dst = static_cast<char *>(out);
     for (int s = 0; s < p.n_seg; ++s) {
@@ -943,7 +975,7 @@ heta_status pack_split3_weights(GemmParams &p, int trans, void *out, hipStream_t
         g.B3 = dst;
         g.ko = static_cast<int32_t>(ko);
         g.n_pad = static_cast<int32_t>(n_pad);
-        dst += split3_weight_bytes(g.K, g.N);
+        dst += split3_weight_bytes(g.K, g.N, trans);
     }
     hipLaunchKernelGGL(pack_split3_kernel, dim3((unsigned)((chunks + 255) / 256), p.n_seg), dim3(256), 0, st, q, trans);
     HETA_LAUNCH_CHECK("pack_split3_kernel");

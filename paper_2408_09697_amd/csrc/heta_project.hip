@@ -397,7 +397,7 @@ static heta_status pack_f32_weights(heta_graph *owner, GemmParams &p, int trans,
     for (int s = 0; s < p.n_seg; ++s) {
         const GemmSeg &g = p.seg[s];
         if (!aligned16(g.A) || (g.lda * 4) % 16 || !aligned16(g.B) || (g.ldb * 4) % 16) return HETA_OK;
-        bytes += split3_weight_bytes(g.K, g.N);
+        bytes += split3_weight_bytes(g.K, g.N, trans);
     }
     heta_status e = ensure_pack(owner, bytes);
     if (e != HETA_OK) return e;

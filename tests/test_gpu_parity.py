@@ -1383,6 +1383,28 @@ def test_f32_weight_gradients_beside_rows_without_gradient(n, power):
         hg.destroy()
 
 
+@pytest.mark.parametrize("d_in,d_out", [(128, 256), (64, 128), (100, 40)])
+def test_errors_of_f32_gradients_do_not_lean_to_one_side(d_in, d_out):
+    """Gradients are summed on, over splits or over the rows that a hub gathers: an error that leans to one side adds up there.
+    Independent errors have a mean of 1 / sqrt(number) of their size: 0.0006 here for input gradients, at most 0.02 for weight
+    gradients; an accumulator that loses more downwards shows 0.02 to 0.06 and about 0.5.  Zero rows stay positive zeros."""
+    n = 65_536
+    gen = torch.Generator(device="cuda").manual_seed(d_in)
+    x, go, w = (torch.randn(shape, generator=gen, device="cuda") for shape in ((n, d_in), (n, d_out), (d_in, d_out)))
+    go[128:400] = 0.0
+    hg = heta.heta_graph_create([(n, 8, 0)], [])
+    try:
+        out, dw = torch.full((n, d_in), 7.0, device="cuda"), torch.full((d_in, d_out), 7.0, device="cuda")
+        heta.heta_project_batch([go], [w], [out], trans_w=True, graph=hg)
+        heta.heta_project_wgrad_batch(hg, [x], [go], [dw], n_rows=n)
+        assert not out[128:400].view(torch.int32).any()
+        for got, ref, most in ((out, go.double() @ w.double().t().contiguous(), 0.005), (dw, x.double().t().contiguous() @ go.double(), 0.1)):
+            err = got.double() - ref
+            assert abs(float(err.mean() / err.square().mean().sqrt())) <= most, (d_in, d_out, most)
+    finally:
+        hg.destroy()
+
+
 @pytest.mark.parametrize("k", [8192, 8193, 9000])
 @pytest.mark.parametrize("n", [200, 12700])
 def test_f32_products_with_many_rows_of_weights(n, k):
