@@ -671,6 +671,9 @@ template <int LPC> __device__ __forceinline__ void agg_hub_combine_body(const Ag
 // What bounds it is the number of rows in flight: random rows arrive at 5 - 6.5 TB/s whether or not the table fits the
 // 256 MB cache, and 4 M edges of 512 bytes take 289 us with 8 wavefronts per SIMD, 295 with 6 and 341 with 5 (8 row
 // loads each).  So the registers are bounded for 8 (bf16: 7); the weights, which have their own kernels, need more.
+// At these bounds only the bf16 two-sum kernels of one relation keep anything in scratch (6 registers at 5 wavefronts; none
+// at 4, or with the parameters read as in the four-relation kernel): an R-GAT forward of 19 M edges takes 6.42 ms with 256
+// columns and 2.80 with 64, 6.39 and 2.81 at 4 wavefronts, 6.43 and 2.80 with the other parameters.
 // Against two launches per relation with 6 and 4 wavefronts per SIMD (bf16: 4 and 6) and lane groups of 64 for wide
 // rows: one layer of 21 M edges 7.21 -> 7.01 ms (bf16 4.70 -> 4.54), of 2.1 M edges and 64 columns 763 -> 711 us,
 // forward over seven widths 1.27 -> 1.17 ms, R-GAT layer of 21 M edges 22.1 -> 21.2 ms, of 2.1 M edges 1.64 -> 1.55 ms.
