@@ -13,7 +13,8 @@
 // Mapping to the machine (wave64, HBM-bound):
 //   - A row of d elements is cut into 16-byte chunks; a "lane group" of L lanes (L = the
 //     power of two covering the chunks, at most 32, one chunk per lane; wider rows in column
-//     tiles) reads a neighbour row with one 128-bit load per lane, fully coalesced.
+//     tiles, or on 64 lanes where they are weighted per slot) reads a neighbour row with one
+//     128-bit load per lane, fully coalesced.
 //   - Rows are scheduled by degree (perm = rows by descending degree) and the kernels walk the
 //     schedule-ordered copy of the adjacency (sptr / sidx), so what a wavefront needs before
 //     its first feature load is consecutive in memory:

@@ -286,7 +286,7 @@ __device__ __forceinline__ void dfrag_load8(const float *tile, int r, int kk, in
 // split, and every other row tile of an input gradient, forms the negative product: A with its signs flipped as it is
 // split (weight gradient: both operands are data), or weights that are packed in both signs, and the epilogue turns the
 // accumulator around.  Weight gradients of 700 k rows and more 2.8e-6 -> 9e-7 off 64 bits, gradients of gathered rows
-// 1.9e-6 -> 2.8e-7 (layer of 21 M edges).
+// 1.9e-6 -> 2.8e-7 (layer of 21 M edges; its weight gradients 1,105 -> 1,128 us, its other products the same).
 __device__ __forceinline__ void flip_signs(float x[8], uint32_t flip)
 {
 #pragma unroll
