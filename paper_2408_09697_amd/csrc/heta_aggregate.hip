@@ -12,14 +12,14 @@
 //
 // Mapping to the machine (wave64, HBM-bound):
 //   - A row of d elements is cut into 16-byte chunks; a "lane group" of L lanes (L = the
-//     power of two covering the chunks, at most 32, one chunk per lane; wider rows in column
-//     tiles, or on 64 lanes where they are weighted per slot) reads a neighbour row with one
+//     power of two covering the chunks, one chunk per lane, at most 64; wider rows, and short
+//     rows of more than 32 chunks, in column tiles: row_lanes) reads a neighbour row with one
 //     128-bit load per lane, fully coalesced.
 //   - Rows are scheduled by degree (perm = rows by descending degree) and the kernels walk the
 //     schedule-ordered copy of the adjacency (sptr / sidx), so what a wavefront needs before
 //     its first feature load is consecutive in memory:
 //       hub rows   (>= 512 edges): cut into 256-edge chunks, one wavefront per chunk, partial
-//                  sums to a workspace, a second kernel adds the partials in chunk order;
+//                  sums to a workspace, a second kernel adds the partials in a fixed order;
 //       long rows  (32 .. 511 edges): one wavefront per row; its 64/L lane groups take the
 //                  row's edges round-robin, several loads in flight each, and are combined at
 //                  the end with cross-lane shuffles;
@@ -465,7 +465,7 @@ __device__ __forceinline__ void agg_batch_body(const AggParams &p, const unsigne
 // sampled block), where one wavefront per item leaves most of the chip idle behind a serial walk of up to 511
 // edges.
 template <typename T, int EPC, int L, int CPL, int MODE, bool SPLIT>
-__device__ __forceinline__ void agg_wave_body(const AggParams &p, const unsigned bx)
+__device__ __forceinline__ void agg_wave_body(const AggParams &p, const unsigned bx, const unsigned by)
 {
     constexpr bool DUAL = MODE == AGG_DUAL, SLOT = MODE != AGG_PLAIN;
     constexpr int G = 64 / L;            // lane groups per wavefront
@@ -491,7 +491,7 @@ __device__ __forceinline__ void agg_wave_body(const AggParams &p, const unsigned
     }
     const int g = lane / L, l = lane % L;
     const int n_chunks = (p.d + EPC - 1) / EPC;
-    const int ch0 = blockIdx.y * (L * CPL) + l;
+    const int ch0 = by * (L * CPL) + l;
     const T *table = static_cast<const T *>(p.table);
     int head[CPL];
 #pragma unroll
@@ -685,7 +685,8 @@ template <int N> struct AggLaunch {
 };
 static_assert(sizeof(AggLaunch<kAggMulti>) <= 3840, "kernel arguments are limited to 4 KB");
 
-template <typename T, int EPC, int L, int CPL, int MODE, int N>
+// BL: lanes of a short row and chunks of a column tile (see row_lanes).
+template <typename T, int EPC, int L, int CPL, int MODE, int N, int BL>
 __global__ void __launch_bounds__(256, EPC == 8 ? (MODE == AGG_PLAIN ? 7 : 5) : MODE == AGG_PLAIN ? 8 : MODE == AGG_SLOT ? 7 : 5) agg_rows_kernel(AggLaunch<N> m)
 {
     int s = 0;
@@ -693,9 +694,13 @@ __global__ void __launch_bounds__(256, EPC == 8 ? (MODE == AGG_PLAIN ? 7 : 5) : 
     for (int i = 1; i < 2 * N; ++i) s += blockIdx.x >= m.first[i] ? 1 : 0;
     const unsigned bx = blockIdx.x - m.first[s];
     const AggParams &p = m.p[s % N];
-    if (s >= N) agg_batch_body<T, EPC, L, CPL, MODE>(p, bx);
-    else if (p.wave_split) agg_wave_body<T, EPC, L, CPL, MODE, true>(p, bx);
-    else agg_wave_body<T, EPC, L, CPL, MODE, false>(p, bx);
+    if (s >= N) {
+        agg_batch_body<T, EPC, BL, CPL, MODE>(p, bx);
+        return;
+    }
+    if (blockIdx.y % (L / BL)) return; // a long row's tile is L / BL tiles of short rows wide
+    if (p.wave_split) agg_wave_body<T, EPC, L, CPL, MODE, true>(p, bx, blockIdx.y / (L / BL));
+    else agg_wave_body<T, EPC, L, CPL, MODE, false>(p, bx, blockIdx.y / (L / BL));
 }
 // Hub rows of up to N relations: blockIdx.y is the relation, or with second sums 2 * relation + (1 for the second).
 template <int LPC, int N> __global__ void __launch_bounds__(kCombineChains * LPC) agg_hub_combine_kernel(AggLaunch<N> m, int tiles, int dual)
@@ -711,7 +716,7 @@ struct AggCost {
     bool timed = true; // false: no event brackets (the entry point that must not allocate)
 };
 
-template <typename T, int EPC, int L, int CPL, int MODE, int N>
+template <typename T, int EPC, int L, int CPL, int BL, int MODE, int N>
 static heta_status launch_sections(const AggParams *ps, const int64_t *blocks, int n, int n_super, hipStream_t st, const AggCost &cost)
 {
     AggLaunch<N> m{};
@@ -723,12 +728,12 @@ static heta_status launch_sections(const AggParams *ps, const int64_t *blocks, i
     }
     if (total == 0) return HETA_OK;
     ProfScope prof(cost.timed ? "agg_rows_kernel" : nullptr, st, cost.bytes, 0);
-    hipLaunchKernelGGL((agg_rows_kernel<T, EPC, L, CPL, MODE, N>), dim3((unsigned)total, n_super), dim3(256), 0, st, m);
+    hipLaunchKernelGGL((agg_rows_kernel<T, EPC, L, CPL, MODE, N, BL>), dim3((unsigned)total, n_super), dim3(256), 0, st, m);
     HETA_LAUNCH_CHECK("agg_rows_kernel");
     return HETA_OK;
 }
 
-template <typename T, int EPC, int L, int CPL, int MODE>
+template <typename T, int EPC, int L, int CPL, int BL, int MODE>
 static heta_status launch_mode(const AggParams *ps, int n, int n_super, hipStream_t st, const AggCost &cost)
 {
     int64_t blocks[2 * kAggMulti], total = 0; // long rows and hub chunks of each relation, then short rows of each
@@ -739,12 +744,12 @@ static heta_status launch_mode(const AggParams *ps, int n, int n_super, hipStrea
         if (blocks[n + i] > kMaxSectionBlocks) return fail(HETA_ERR_UNSUPPORTED, "aggregate: too many short rows");
         total += blocks[i] + blocks[n + i];
     }
-    if (n == 1 && total <= kMaxSectionBlocks) return launch_sections<T, EPC, L, CPL, MODE, 1>(ps, blocks, 1, n_super, st, cost);
-    if (total <= kMaxSectionBlocks) return launch_sections<T, EPC, L, CPL, MODE, kAggMulti>(ps, blocks, n, n_super, st, cost);
+    if (n == 1 && total <= kMaxSectionBlocks) return launch_sections<T, EPC, L, CPL, BL, MODE, 1>(ps, blocks, 1, n_super, st, cost);
+    if (total <= kMaxSectionBlocks) return launch_sections<T, EPC, L, CPL, BL, MODE, kAggMulti>(ps, blocks, n, n_super, st, cost);
     AggCost c = cost; // more workgroups than one grid takes: one section at a time
     for (int s = 0; s < 2 * n; ++s) {
         const int64_t one[2] = {s < n ? blocks[s] : 0, s < n ? 0 : blocks[s]};
-        const heta_status e = launch_sections<T, EPC, L, CPL, MODE, 1>(ps + s % n, one, 1, n_super, st, c);
+        const heta_status e = launch_sections<T, EPC, L, CPL, BL, MODE, 1>(ps + s % n, one, 1, n_super, st, c);
         if (e != HETA_OK) return e;
         c.bytes = 0;
     }
@@ -752,40 +757,46 @@ static heta_status launch_mode(const AggParams *ps, int n, int n_super, hipStrea
 }
 
 // the kernel of a launch's weights (part of the plans' key); the two-weight form exists for the 128-bit paths
-template <typename T, int EPC, int L, int CPL>
+template <typename T, int EPC, int L, int CPL, int BL = L>
 static heta_status launch_rows(const AggParams *ps, int n, int n_super, hipStream_t st, const AggCost &cost)
 {
     if constexpr (EPC > 1) {
-        if (ps[0].slot_form == SLOT_BOTH) return launch_mode<T, EPC, L, CPL, AGG_DUAL>(ps, n, n_super, st, cost);
+        if (ps[0].slot_form == SLOT_BOTH) return launch_mode<T, EPC, L, CPL, BL, AGG_DUAL>(ps, n, n_super, st, cost);
     }
-    if (ps[0].slot_w) return launch_mode<T, EPC, L, CPL, AGG_SLOT>(ps, n, n_super, st, cost);
-    if constexpr (L == 64 && EPC > 1) return fail(HETA_ERR_UNSUPPORTED, "aggregate: rows of 64 lanes are the weighted forms'");
-    else return launch_mode<T, EPC, L, CPL, AGG_PLAIN>(ps, n, n_super, st, cost);
+    if (ps[0].slot_w) return launch_mode<T, EPC, L, CPL, BL, AGG_SLOT>(ps, n, n_super, st, cost);
+    if constexpr (BL == 64 && EPC > 1) return fail(HETA_ERR_UNSUPPORTED, "aggregate: short rows of 64 lanes are the weighted forms'");
+    else return launch_mode<T, EPC, L, CPL, BL, AGG_PLAIN>(ps, n, n_super, st, cost);
 }
 
-// Lanes per row and column tiles (grid.y) of the 128-bit paths: a row of more than 32 chunks is walked in tiles of 32.
-// Against one lane group of 64 lanes, or of 64 lanes with two chunks each: 4 M edges of 1 KB rows from a table of 1.1 GB
-// 838 -> 771 us, of 0.7 GB 775 -> 730; and a row of 96 chunks leaves no lane idle.  Rows weighted per slot keep one group
-// up to 64 chunks: their kernels are bound by registers, not by lanes (all weighted gathers of an R-GAT layer of 21 M edges
-// and 256 columns 9.64 ms, 9.56 in tiles of 32), a long row's edges are added one after the other, not in two halves, and
-// the one-pass dot needs a head's columns in one tile (it is taken up to 64 chunks).
-static int lanes_per_row(const AggParams &p, int n_chunks)
+// Lanes of a long row and of a short one, whose number of chunks is also the width of a column tile (grid.y), on the
+// 128-bit paths.  Short rows of more than 32 chunks are walked in tiles of 32: against 64 lanes, or 64 with two chunks each,
+// 4 M edges of 1 KB rows from a table of 1.1 GB 838 -> 771 us, of 0.7 GB 775 -> 730; and a row of 96 chunks leaves no lane
+// idle.  A long row has one group of 64 lanes and tiles of 64, so that its
+// edges are added one after the other whatever the tile of the short ones, not in two halves (a ReLU or LeakyReLU behind
+// the sum turns its last bits into whole gradient rows).  Rows weighted per slot are short rows of 64 lanes up to 64 chunks:
+// their kernels are bound by registers, not by lanes (all weighted gathers of an R-GAT layer of 21 M edges and 256
+// columns 9.64 ms, 9.56 in tiles of 32), and the one-pass dot needs a head's columns in one tile.
+struct RowLanes {
+    int long_row, short_row;
+};
+static RowLanes row_lanes(const AggParams &p, int n_chunks)
 {
-    const int most = p.slot_w && n_chunks <= 64 ? 64 : 32;
     int L = 1;
-    while (L < n_chunks && L < most) L <<= 1;
-    return L;
+    while (L < n_chunks && L < 64) L <<= 1;
+    return {L, p.slot_w && n_chunks <= 64 ? L : std::min(L, 32)};
 }
 
 template <typename T, int EPC>
-static heta_status launch_vec(const AggParams *ps, int n, int L, int n_super, hipStream_t st, const AggCost &c)
+static heta_status launch_vec(const AggParams *ps, int n, RowLanes lanes, int n_super, hipStream_t st, const AggCost &c)
 {
+    const int L = lanes.long_row;
     if (L == 1) return launch_rows<T, EPC, 1, 1>(ps, n, n_super, st, c);
     if (L == 2) return launch_rows<T, EPC, 2, 1>(ps, n, n_super, st, c);
     if (L == 4) return launch_rows<T, EPC, 4, 1>(ps, n, n_super, st, c);
     if (L == 8) return launch_rows<T, EPC, 8, 1>(ps, n, n_super, st, c);
     if (L == 16) return launch_rows<T, EPC, 16, 1>(ps, n, n_super, st, c);
     if (L == 32) return launch_rows<T, EPC, 32, 1>(ps, n, n_super, st, c);
+    if (lanes.short_row == 32) return launch_rows<T, EPC, 64, 1, 32>(ps, n, n_super, st, c);
     return launch_rows<T, EPC, 64, 1>(ps, n, n_super, st, c);
 }
 
@@ -796,13 +807,15 @@ struct AggPlan {
     AggParams p;
     heta_dtype in_dt = HETA_F32;
     bool vec = false, dual = false;
-    int lanes = 64, n_super = 1; // lanes per row, column tiles
+    RowLanes lanes = {64, 64};
+    int n_super = 1; // column tiles
     size_t ws_need = 0;
     AggCost cost;
     double hub_bytes = 0;
     int64_t n_hub_rows = 0;
-    // relations with equal keys run the same kernel instantiation with the same grid.y
-    int key() const { return (in_dt == HETA_F32 ? 0 : 1) | (vec ? 2 : 0) | (dual ? 4 : 0) | (p.slot_w ? 8 : 0) | (lanes << 4) | (n_super << 11); }
+    // relations with equal keys run the same kernel instantiation with the same grid.y (the lanes of short rows follow from
+    // those of long ones, the weights and the number of tiles)
+    int key() const { return (in_dt == HETA_F32 ? 0 : 1) | (vec ? 2 : 0) | (dual ? 4 : 0) | (p.slot_w ? 8 : 0) | (lanes.long_row << 4) | (n_super << 11); }
 };
 
 static bool agg_vectorized(const AggParams &p, heta_dtype in_dt)
@@ -819,8 +832,8 @@ static heta_status plan_aggregate(const Schedule &s, AggParams p, heta_dtype in_
     const bool dual = p.slot_form == SLOT_BOTH;
     const int epc = vec ? static_cast<int>(16 / esz) : 1;
     const int n_chunks = (p.d + epc - 1) / epc;
-    const int L = vec ? lanes_per_row(p, n_chunks) : 64;
-    const int G = 64 / L;
+    const RowLanes lanes = vec ? row_lanes(p, n_chunks) : RowLanes{64, 64};
+    const int G = 64 / lanes.short_row;
     // rows with at least this many edges get a whole wavefront
     const int wave_min = kShortDeg;
     const int64_t n_long_or_hub = s.rows_with_deg_ge[wave_min];
@@ -866,8 +879,8 @@ static heta_status plan_aggregate(const Schedule &s, AggParams p, heta_dtype in_
     plan->in_dt = in_dt;
     plan->vec = vec;
     plan->dual = dual;
-    plan->lanes = L;
-    plan->n_super = vec ? (n_chunks + L - 1) / L : (n_chunks + 127) / 128;
+    plan->lanes = lanes;
+    plan->n_super = vec ? (n_chunks + lanes.short_row - 1) / lanes.short_row : (n_chunks + 127) / 128;
     return HETA_OK;
 }
 

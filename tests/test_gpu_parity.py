@@ -1451,3 +1451,26 @@ def test_hub_rows_are_summed_in_sixteen_chains(d, storage):
             assert np.array_equal(out[row].cpu().numpy(), want), (row, d)
     finally:
         hg.destroy()
+
+
+@pytest.mark.parametrize("d,storage", [(132, "f32"), (256, "f32"), (260, "f32"), (392, "f32"), (520, "f32"), (264, "bf16"), (512, "bf16"), (520, "bf16"), (1032, "bf16")])
+def test_edges_of_a_long_row_of_many_chunks_are_added_in_order(d, storage):
+    """More than 32 chunks: short rows are walked in tiles of 32 chunks, long rows in tiles of 64, so that their edges are added
+    one after the other.  Rows of 1 to 64 edges, the first and last chunk of every tile."""
+    gen = torch.Generator().manual_seed(d)
+    n_src, degs = 300, [64, 33, 32, 31, 5, 1, 0, 64, 50]
+    rowptr = np.concatenate([[0], np.cumsum(degs)]).astype(np.int64)
+    col = torch.randint(0, n_src, (int(rowptr[-1]),), generator=gen, dtype=torch.int32)
+    dt = torch.float32 if storage == "f32" else torch.bfloat16
+    x = torch.randn((n_src, d), generator=gen).to(dt)
+    hg = heta.heta_graph_create([(n_src, 4, 0), (len(degs), 4, 0)], [(0, 1, rowptr, col.numpy())])
+    try:
+        out = torch.full((len(degs), d), 7.0, device="cuda")
+        heta.heta_rel_aggregate_fwd(hg, 0, heta.HETA_SUM, x.cuda(), out)
+        for row, (e0, e1) in enumerate(zip(rowptr[:-1], rowptr[1:])):
+            want = torch.zeros(d)
+            for e in range(e0, e1):
+                want += x[int(col[e])].float()
+            assert torch.equal(out[row].cpu(), want), (row, d)
+    finally:
+        hg.destroy()

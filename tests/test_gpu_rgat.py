@@ -445,9 +445,10 @@ def test_attention_of_several_relations_in_one_call(d, heads, storage):
         hg.destroy()
 
 
-@pytest.mark.parametrize("d,storage,train", [(256, "f32", False), (256, "f32", True), (200, "f32", True), (512, "bf16", False), (512, "bf16", True)])
+@pytest.mark.parametrize("d,storage,train", [(256, "f32", False), (256, "f32", True), (200, "f32", True), (512, "bf16", False), (512, "bf16", True),
+                                             (384, "f32", False), (384, "f32", True), (768, "bf16", True)])
 def test_edges_of_a_long_row_are_added_in_order(d, storage, train):
-    """Rows of up to 64 chunks have one lane group: 64 edges of one weight (2^-6 exactly, since all scores are equal) are
+    """Long rows have one lane group of up to 64 lanes: 64 edges of one weight (2^-6 exactly, since all scores are equal) are
     added one after the other, whether one sum or two are taken."""
     gen = torch.Generator().manual_seed(d)
     n_src, n_dst, heads = 300, 5, 4
