@@ -40,6 +40,7 @@ struct GemmParams {
     int out_bf16;        // outputs are bf16 [M][ldc] (plain stores only: no beta, scale, activation, split)
     int64_t k_per_split; // multiple of BK
     int n_split;
+    int as_packed;       // fp32 product of a call whose larger launches pack B: the same order of sums where this one does not
     int both_signs;      // B3 holds the terms of B and, behind them, those of -B (input gradients)
     int partial;         // write raw partial products [split][M][ldc] (ldc = N) instead of the output
     int64_t mt, nt;      // tile counts (maximum over the segments in batch mode)
@@ -258,8 +259,8 @@ extern bool g_f32_native; // test switch, see heta_test_hooks.h
 // (trans = 1, an input gradient: the terms of B and behind them those of -B, see flip_signs); zero beyond K and N.
 size_t split3_weight_bytes(int64_t K, int64_t N, int trans);
 heta_status pack_split3_weights(GemmParams &p, int trans, void *out, hipStream_t st);
-// whether the direct pipeline would give this launch its 64 x 64 tiles (too few 128 x 128 tiles to fill the chip)
-bool gemm_direct_small(const GemmParams &p);
+// whether an fp32 product is small enough to split both operands in its kernel instead of packing one beforehand
+bool f32_product_unpacked(const GemmParams &p);
 int wgrad_tile_rows(const GemmParams &p);
 heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, bool a_rc, bool b_rc, hipStream_t st,
                                const char *name, double bytes, double flops, bool *handled);

@@ -284,8 +284,7 @@ __device__ __forceinline__ void dfrag_load8(const float *tile, int r, int kk, in
 // size over 128 k-values, 0.06 over 256 (the fp32 instruction's does not).  Where products are summed on, over the splits of
 // a weight gradient or over the rows that a hub gathers, that part adds up while the rest averages out.  So every other
 // split, and every other row tile of an input gradient, forms the negative product: A with its signs flipped as it is
-// split (weight gradient: both operands are data), or weights that are packed in both signs, and the epilogue turns the
-// accumulator around.  Weight gradients of 700 k rows and more 2.8e-6 -> 9e-7 off 64 bits, gradients of gathered rows
+// split, or weights that are packed in both signs, and the epilogue turns the accumulator around.  Weight gradients of 700 k rows and more 2.8e-6 -> 9e-7 off 64 bits, gradients of gathered rows
 // 1.9e-6 -> 2.8e-7 (layer of 21 M edges; its weight gradients 1,105 -> 1,128 us, its other products the same).
 __device__ __forceinline__ void flip_signs(float x[8], uint32_t flip)
 {
@@ -627,8 +626,11 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
     // a direct operand lies in LDS in its storage type (fp32 storage under bf16 compute is converted
     // when fragments are read); a staged operand lies there in the compute type
     using DA = std::conditional_t<A_DIRECT, DirectLoader<SA_T, A_RC && A_DIRECT, BM, BK, NW>, NoLoader>;
-    // X3: fp32 operands as three bf16 terms each - 1: both split when their fragments are read, 2: B comes pre-split
-    constexpr bool W3 = X3 == 2, X3_WGRAD = X3 == 1 && A_RC && B_RC;
+    // X3: fp32 operands as three bf16 terms each - 1: both split when their fragments are read, 2: B comes pre-split, 3: both
+    // split, the products added in the order of 2 (bitwise the same sums)
+    constexpr bool X3_AS_PACKED = X3 == 3;
+    // A is flipped where its product's sign alternates (packed weights come in both signs instead): see flip_signs
+    constexpr bool W3 = X3 == 2, X3_FLIP = X3 == 1 ? A_RC && B_RC : X3 == 3 && !B_RC;
     using DB = std::conditional_t<W3, Split3Loader<BN, NW>, std::conditional_t<B_DIRECT, DirectLoader<SB_T, B_RC && B_DIRECT, BN, BK, NW>, NoLoader>>;
     using SA = std::conditional_t<A_DIRECT, NoLoader, TileLoader<SA_T, CT, A_RC, BM, NT, true, BK>>;
     using SB = std::conditional_t<B_DIRECT, NoLoader, TileLoader<SB_T, CT, B_RC, BN, NT, true, BK>>;
@@ -670,7 +672,7 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
     const int64_t n0 = (rest % p.nt) * BN;
     const int64_t m0 = (p.partial ? rest / p.nt : outer) * BM;
     const int64_t split = p.partial ? outer : 0;
-    const bool negated = X3_WGRAD ? (outer & 1) : W3 && p.both_signs && (outer & 1); // uniform: see flip_signs
+    const bool negated = (X3_FLIP || (W3 && p.both_signs)) && (outer & 1); // uniform
     const uint32_t flip = negated ? 0x80000000u : 0u;
     const GemmSeg &out_seg = p.seg[s0];
     if (m0 >= out_seg.M || n0 >= out_seg.N) return; // uniform per workgroup
@@ -816,7 +818,7 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
                     for (int i = 0; i < MI; ++i) {
                         float x[8];
                         dfrag_load8<A_RC, BM, BK>(reinterpret_cast<const float *>(At), wm + i * 32 + l32, kk, half, x);
-                        if constexpr (X3_WGRAD) flip_signs(x, flip);
+                        if constexpr (X3_FLIP) flip_signs(x, flip);
                         if (ragged) split3_frag<true>(x, kk + 8 * half, kv, a3[i]);
                         else split3_frag<false>(x, kk + 8 * half, kv, a3[i]);
                     }
@@ -827,7 +829,9 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
                         if (ragged) split3_frag<true>(x, kk + 8 * half, kv, b3[jj]);
                         else split3_frag<false>(x, kk + 8 * half, kv, b3[jj]);
                     }
-                    constexpr int TA[6] = {2, 0, 1, 1, 0, 0}, TB[6] = {0, 2, 1, 0, 1, 0}; // smallest products first
+                    // smallest products first, or in the order of the packed kernel
+                    constexpr int TA[6] = {X3_AS_PACKED ? 0 : 2, 0, X3_AS_PACKED ? 0 : 1, 1, X3_AS_PACKED ? 1 : 0, X3_AS_PACKED ? 2 : 0};
+                    constexpr int TB[6] = {0, X3_AS_PACKED ? 1 : 2, X3_AS_PACKED ? 2 : 1, 0, 1, 0};
 #pragma unroll
                     for (int q = 0; q < 6; ++q)
 #pragma unroll
@@ -897,7 +901,7 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
     }
 
     barrier_no_drain();     // every wavefront's last fragment reads are done (they fed its last MFMAs)
-    if ((W3 || X3_WGRAD) && negated) {
+    if ((W3 || X3_FLIP) && negated) {
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -938,7 +942,8 @@ static heta_status launch_direct(GemmParams &p, hipStream_t st, const char *name
 // test switch: fp32 products on the fp32 MFMA (32x32x2) instead of as six bf16 terms
 bool g_f32_native = false;
 
-bool gemm_direct_small(const GemmParams &p)
+// fewer than a hundred 128 x 128 tiles
+static bool gemm_direct_small(const GemmParams &p)
 {
     if (p.partial) return false;
     int64_t mt = 0, nt = 0;
@@ -947,6 +952,20 @@ bool gemm_direct_small(const GemmParams &p)
         nt = std::max(nt, (p.seg[s].N + 127) / 128);
     }
     return mt * nt * (p.batch ? p.n_seg : 1) <= 96;
+}
+
+// fp32 products (forward, input gradient) of too little work for packed weights: 64 x 64 tiles that split both operands.
+// The packing launch takes 5 us and packed tiles are four times as large; packed and not, in us: 48,000 x 128 x 64 17.9 and
+// 13.1 (6,000 steps of 64 x 64 x 16), three of 24,000 x 128 x 64 21.9 and 18.0 (9,000), 100,000 x 64 x 100 27.7 and 24.0
+// (12,500), two of 60,000 x 128 x 64 27.0 and 24.1 (15,000), two of 70,000 30.9 and 27.5 (17,500), 20,000 x 512 x 100 33.4
+// and 32.9 (20,000), two of 160,000 x 24 x 100 40.5 and 46.4 (20,000), 48,000 x 128 x 256 29.7 and 33.4 (24,000).
+bool f32_product_unpacked(const GemmParams &p)
+{
+    if (p.partial) return false;
+    double steps = 0;
+    for (int s = 0; s < p.n_seg; ++s)
+        steps += static_cast<double>((p.seg[s].M + 63) / 64) * static_cast<double>((p.seg[s].N + 63) / 64) * static_cast<double>((p.seg[s].K + 15) / 16);
+    return steps <= 16384 || gemm_direct_small(p);
 }
 
 static int64_t split3_octets(int64_t K) { return (K + 15) / 16 * 2; }
@@ -1064,9 +1083,9 @@ heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, 
     // Fewer than a hundred 128 x 128 tiles (the projections of a sampled mini-batch block: a few thousand rows):
     // every tile is a serial chain of MFMAs on one CU while most CUs idle.  64 x 64 tiles (four wavefronts of one
     // accumulator each) cut the chain to a quarter and put four times as many CUs to work.
-    const bool small = gemm_direct_small(p);
+    const bool small = gemm_direct_small(p), unpacked = f32_product_unpacked(p);
     *handled = true;
-    if (a_dt == HETA_F32 && b_dt == HETA_F32 && !g_f32_native && !a_rc && !small && !p.partial) {
+    if (a_dt == HETA_F32 && b_dt == HETA_F32 && !g_f32_native && !a_rc && !unpacked && !p.partial) {
         // B already packed as three bf16 terms by the caller (the weights of a forward or input-gradient product):
         // half the splitting arithmetic leaves the k loop.
         bool packed = true;
@@ -1089,12 +1108,23 @@ heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, 
         // on 2 x (110 k x 128)^T (110 k x 64))
         if (p.partial && a_rc && b_rc && n_max <= 64)
             return launch_direct<bf16_t, float, true, true, float, true, true, 1, 16, 3, 2, false, 2, 2, 2, 1>(p, st, name, bytes, flops);
-#define HETA_X32(ARC, BRC)                                                                                                        \
-    return small ? launch_direct<bf16_t, float, ARC, true, float, BRC, true, 2, 16, 3, 4, false, 1, 1, 2, 1>(p, st, name, bytes, flops) \
-                 : launch_direct<bf16_t, float, ARC, true, float, BRC, true, 2, 16, 3, 3, false, 2, 2, 2, 1>(p, st, name, bytes, flops)
-        if (!a_rc && b_rc) { HETA_X32(false, true); }
-        if (!a_rc && !b_rc) { HETA_X32(false, false); }
-        if (a_rc && b_rc) { HETA_X32(true, true); }
+        if (a_rc && b_rc) return launch_direct<bf16_t, float, true, true, float, true, true, 2, 16, 3, 3, false, 2, 2, 2, 1>(p, st, name, bytes, flops);
+        int64_t tiles64 = 0;
+        for (int s = 0; s < p.n_seg; ++s) {
+            const int64_t tiles = ((p.seg[s].M + 63) / 64) * ((p.seg[s].N + 63) / 64);
+            tiles64 = p.batch ? tiles64 + tiles : std::max(tiles64, tiles);
+        }
+        // 64 x 64 tiles: up to two per CU the launch is one chain of k-steps, and 32 k-values per barrier shorten it
+        // (1,024 rows, K = 768, 256 columns 28.0 -> 24.3 us, 1,024 columns 30.1 -> 25.9)
+        const bool chain = tiles64 <= 512;
+#define HETA_X32(BRC)                                                                                                                                \
+    return !unpacked        ? launch_direct<bf16_t, float, false, true, float, BRC, true, 2, 16, 3, 3, false, 2, 2, 2, 1>(p, st, name, bytes, flops) \
+           : small && chain ? launch_direct<bf16_t, float, false, true, float, BRC, true, 2, 32, 3, 3, false, 1, 1, 2, 1>(p, st, name, bytes, flops) \
+           : small || !p.as_packed                                                                                                                 \
+               ? launch_direct<bf16_t, float, false, true, float, BRC, true, 2, 16, 3, 4, false, 1, 1, 2, 1>(p, st, name, bytes, flops)             \
+               : launch_direct<bf16_t, float, false, true, float, BRC, true, 2, 16, 3, 4, false, 1, 1, 2, 3>(p, st, name, bytes, flops)
+        if (!a_rc && b_rc) { HETA_X32(true); }
+        if (!a_rc && !b_rc) { HETA_X32(false); }
 #undef HETA_X32
     }
     if (small) {

@@ -388,11 +388,13 @@ static heta_status ensure_pack(heta_graph *owner, size_t bytes)
 
 // fp32 x fp32 products through a graph handle whose B operands are weight matrices (forward, input gradient):
 // the weights are rewritten once per launch as the three bf16 terms the product is fed with, into the handle's
-// packing buffer, and the k loop splits only A.  Launches the direct pipeline would not take, or would give its
-// small tiles, are left as they are.  trans: B(k, n) = W[n*ldb + k].
+// packing buffer, and the k loop splits only A.  Launches the direct pipeline would not take, or would give tiles that
+// split both operands, are left as they are.  trans: B(k, n) = W[n*ldb + k].
 static heta_status pack_f32_weights(heta_graph *owner, GemmParams &p, int trans, hipStream_t st)
 {
-    if (!owner || g_force_staged || g_f32_native || p.partial || gemm_direct_small(p)) return HETA_OK;
+    if (!owner || g_force_staged || g_f32_native || p.partial) return HETA_OK;
+    p.as_packed = 1;
+    if (f32_product_unpacked(p)) return HETA_OK;
     size_t bytes = 0;
     for (int s = 0; s < p.n_seg; ++s) {
         const GemmSeg &g = p.seg[s];

@@ -1405,6 +1405,25 @@ def test_errors_of_f32_gradients_do_not_lean_to_one_side(d_in, d_out):
         hg.destroy()
 
 
+@pytest.mark.parametrize("n,k,d_out", [(12801, 128, 128), (60000, 128, 64), (33001, 100, 40), (13000, 300, 65)])
+def test_f32_products_of_any_launch_size_have_the_same_bits(n, k, d_out):
+    """Launches of moderate size split both operands, larger ones pack the weights: a row's product is the same in both."""
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn((n, (k + 3) // 4 * 4), generator=gen, device="cuda")[:, :k]
+    w = torch.randn((k, (d_out + 3) // 4 * 4), generator=gen, device="cuda")[:, :d_out]
+    steps = -(-n // 64) * -(-d_out // 64) * -(-k // 16)
+    assert -(-n // 128) * -(-d_out // 128) > 96 and steps <= 16384 < 8 * steps  # alone: moderate; eight times: packed
+    hg = heta.heta_graph_create([(n, 8, 0)], [])
+    try:
+        one, many = torch.full((n, d_out), 7.0, device="cuda"), [torch.full((n, d_out), 8.0, device="cuda") for _ in range(8)]
+        heta.heta_project_batch([x], [w], [one], graph=hg)
+        heta.heta_project_batch([x] * 8, [w] * 8, many, graph=hg)
+        for o in many:
+            assert torch.equal(o, one)
+    finally:
+        hg.destroy()
+
+
 @pytest.mark.parametrize("k", [8192, 8193, 9000])
 @pytest.mark.parametrize("n", [200, 12700])
 def test_f32_products_with_many_rows_of_weights(n, k):
