@@ -279,7 +279,7 @@ heta_status heta_project_wgrad_batch(heta_graph *g, int64_t n_rows, int32_t n, c
  * On a subset of a type's relations with beta = 0 it yields the partial aggregation of that subset.
  * With bf16 inputs and weights the call first rewrites the weights k-contiguous into a buffer of the
  * handle (grown on demand: the first call for a larger shape synchronises); with fp32 inputs and weights
- * and enough rows for full-size tiles it rewrites the weights there as the three bf16 terms the product is
+ * and enough work for full-size tiles it rewrites the weights there as the three bf16 terms the product is
  * fed with (so does heta_cross_rel_project_bwd).  Calls on one handle that do so must be stream-ordered,
  * like the calls that use its workspace. */
 heta_status heta_cross_rel_project(heta_graph *g, int32_t dst_type, int32_t n, const void *const *ins,
