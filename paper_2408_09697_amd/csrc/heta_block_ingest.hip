@@ -3,24 +3,27 @@
 // A mini-batch block (Section 2.2 of the paper: the sampled k-hop neighbourhood, one bipartite graph per
 // relation and hop) has a handful of relations of 10^3 .. 10^5 edges each.  The per-relation device
 // pipeline costs twenty launches per relation, the host path a few hundred microseconds of CPU work and
-// an upload (plus a download when the block was sampled on the device).  Here the relations of a block
-// are treated as ONE block-diagonal bipartite graph over the concatenated destination rows, source nodes
-// and edges, so that every step is one launch (or one sort / one scan) for the whole block:
+// an upload (plus a download when the block was sampled on the device).  Here four launches build every
+// relation of the block, from the caller's CSR to both schedules:
 //
-//   rows kernel     degrees, 1/deg, validation, degree histograms, sort keys (relation, 512 - min(deg, 512))
-//   edges kernel    validation, the CSR's neighbour ids copied, (global source id, global edge id) pairs
-//   sort            stable LSD radix sort of those pairs = the transpose of every relation at once
-//   colptr, rows    column offsets by binary search in the sorted keys; the CSC's degrees, keys, histograms
-//   sort            one stable sort of all CSR and CSC rows by (schedule, capped degree) = every schedule's
-//                   row order (a relation's rows stay contiguous because the schedule id leads the key)
-//   scan, fill      schedule-ordered offsets and neighbour ids, hub chunk lists
+//   prep     rows: validation, offsets, 1/deg, degree counts; edges: validation, neighbour ids, the row of
+//            every edge, counts per bucket of sources
+//   spread   CSR rows placed by descending degree, their neighbours copied in that order; edges moved, stably,
+//            to their buckets of sources
+//   columns  a bucket's edges sorted, stably, by source in LDS: column offsets, the transpose's rows, degree counts
+//   place    CSC rows placed like the CSR's
 //
-// Values are written relation-local (row ids, neighbour ids, offsets) into per-relation slices of one
-// arena, so the aggregation kernels see exactly what the other ingest paths produce; the results are
-// bit-identical to theirs.  Everything is deterministic: integer atomics only count, every placement is
-// by rank.  Inputs are sanitised as they are read (offsets clamped into [0, E], ids into [0, n_src)), so
-// a malformed CSR cannot send any later access out of bounds; it is reported after the one
-// synchronisation at the end.
+// What bounds it is latency: a launch is 4 to 8 us of a few dependent L2 accesses, whatever the block's size, and each
+// launch after the first costs as much again in submission and gap.  So nothing is scanned over the whole block in a
+// launch of its own: a relation has at most 64 or 128 workgroups a side, and each of them adds up the counts of all of
+// them itself.  (The chain of two radix sorts and two scans that it replaces was 22 launches and two fills: whole calls
+// for 14 relations of 2,000 / 5,000 / 40,000 edges 202 / 216 / 445 us, now 99 / 100 / 162; by the host path, with device
+// arrays, 304 / 593 / 2,186.)
+//
+// A relation's slice of every array is what the other ingest paths produce, bit for bit.  Everything is deterministic:
+// integer atomics only count, every placement is by rank.  Where a workgroup of the first launch finds the caller's
+// arrays malformed, the later launches leave that relation alone, and the fault is reported after the one
+// synchronisation at the end; the first launch follows no offset or id that it has not clamped.
 #include <algorithm>
 #include <cstring>
 #include <vector>
@@ -32,24 +35,57 @@ namespace heta {
 namespace {
 
 constexpr int kMaxBlockRels = 32;
+constexpr int kThreads = 256, kWaves = kThreads / 64;
+constexpr int kMaxRowBlocks = 64;             // workgroups per relation over its destination rows, over its edges
+constexpr int kMaxBuckets = 128;              // buckets of sources per relation
+constexpr int kMaxRowsPer = 4096;             // rows per workgroup
+constexpr int kMaxLow = 11;                   // a bucket holds 2^10 or 2^11 sources
+constexpr int64_t kMaxElems = int64_t(1) << 18; // edges + rows of both sides of a relation: fewer (the caller's bound)
+constexpr int kMaxHubs = kMaxElems / kHubMinDeg;
+static_assert(kMaxElems <= int64_t(kMaxRowBlocks) * kMaxRowsPer && kMaxElems <= int64_t(kMaxBuckets) << kMaxLow, "a relation fits its workgroups");
+static_assert(kMaxHubs <= 2 * kThreads, "hub rows of a workgroup: two per thread");
+static_assert(kHubMinDeg == 2 * kThreads, "two degree buckets per thread beside the hubs'");
 
-struct BlockTables { // passed by value
+struct BlockPlan { // passed by value
     int n_rel;
-    int64_t dst_off[kMaxBlockRels + 1];  // destination rows of relation i are global rows [dst_off[i], dst_off[i+1])
-    int64_t src_off[kMaxBlockRels + 1];  // its source nodes
-    int64_t edge_off[kMaxBlockRels + 1]; // its edges
-    int64_t hub_off[2 * kMaxBlockRels + 1];    // chunk descriptors of schedule s (s < n_rel: CSR of relation s; else CSC of s - n_rel)
-    int64_t hubptr_off[2 * kMaxBlockRels + 1]; // its chunk range array
-};
-
-struct BlockInputs { // passed by value
+    int32_t dst_off[kMaxBlockRels + 1], src_off[kMaxBlockRels + 1], edge_off[kMaxBlockRels + 1]; // a relation's rows and edges
+    int32_t hub_off[2 * kMaxBlockRels + 1];    // chunk descriptors of schedule s (s < n_rel: CSR of relation s; else CSC of s - n_rel)
+    int32_t hubptr_off[2 * kMaxBlockRels + 1]; // its chunk range array
+    int32_t row_blk[kMaxBlockRels + 1], edge_blk[kMaxBlockRels + 1], src_blk[kMaxBlockRels + 1]; // a relation's workgroups
+    int32_t rows_per[kMaxBlockRels], edges_per[kMaxBlockRels], low[kMaxBlockRels];               // elements of a workgroup; 2^low sources
     const int64_t *rowptr[kMaxBlockRels];
     const int32_t *col[kMaxBlockRels];
 };
 
-// largest i < n with off[i] <= x (off non-decreasing, off[0] <= x): the segment that owns x; among segments
-// starting at the same offset the last one, which is the non-empty one
-__device__ __forceinline__ int seg_of(const int64_t *off, int n, int64_t x)
+struct BlockBack { // per schedule, in page-locked host memory
+    unsigned long long err; // CSR schedules
+    uint32_t hub_edges, n_chunks;
+    uint32_t rows[kDegHist + 1]; // rows of every capped degree
+};
+
+struct DegCounts { // of one workgroup's rows
+    uint16_t rows[kHubMinDeg];
+    uint32_t hub_rows, hub_edges, hub_chunks, pad;
+};
+
+struct BlockArrays { // passed by value
+    // the arena; a relation's slice of an offset array has one more entry than rows
+    int64_t *csr_ptr, *csr_sptr, *csc_ptr, *csc_sptr, *hub_chunk_ptr;
+    HubChunk *hub_chunks;
+    int32_t *csr_idx, *csr_sidx, *csc_idx, *csc_sidx, *csr_perm, *csc_perm;
+    float *inv_deg;
+    // scratch
+    DegCounts *row_counts, *src_counts;   // per workgroup over rows / bucket
+    uint16_t *bucket_counts;              // per workgroup over edges: kMaxBuckets
+    uint32_t *bucket_start;               // per relation: kMaxBuckets + 1
+    unsigned long long *err;              // per workgroup of the first launch
+    uint32_t *row_of, *src_of;            // row of every CSR edge, source of every CSC edge
+    uint2 *spread;                        // (source, row) by bucket
+    BlockBack *back;
+};
+
+// largest i < n with off[i] <= x (off increasing, off[0] <= x)
+__device__ __forceinline__ int seg_of(const int32_t *off, int n, int x)
 {
     int lo = 0, hi = n;
     while (hi - lo > 1) {
@@ -60,12 +96,12 @@ __device__ __forceinline__ int seg_of(const int64_t *off, int n, int64_t x)
     return lo;
 }
 
-__device__ __forceinline__ int64_t last_le64(const int64_t *a, int64_t n, int64_t x)
+// the last v in [lo, hi) with rp[v] <= x, lo if there is none
+__device__ __forceinline__ int row_at(const int64_t *rp, int lo, int hi, int64_t x)
 {
-    int64_t lo = 0, hi = n;
     while (hi - lo > 1) {
-        const int64_t mid = lo + (hi - lo) / 2;
-        if (a[mid] <= x) lo = mid;
+        const int mid = (lo + hi) >> 1;
+        if (rp[mid] <= x) lo = mid;
         else hi = mid;
     }
     return lo;
@@ -73,282 +109,509 @@ __device__ __forceinline__ int64_t last_le64(const int64_t *a, int64_t n, int64_
 
 enum : unsigned long long { kBadPtr0 = 1, kBadDecrease = 2, kBadTotal = 3, kBadCol = 4 };
 
-// The error word holds the complement of the smallest (kind, relation, position) reported, 0 while nothing is:
-// it is cleared by the same fill as the counters beside it.
+// An error word holds the complement of the smallest (kind, relation, position) reported, 0 while nothing is.
 __device__ __forceinline__ void report(unsigned long long *err, unsigned long long kind, int rel, int64_t at)
 {
     atomicMax(err, ~((kind << 56) | (static_cast<unsigned long long>(rel) << 48) | static_cast<unsigned long long>(at)));
 }
 
-__device__ __forceinline__ int64_t clamp64(int64_t x, int64_t lo, int64_t hi) { return x < lo ? lo : (x > hi ? hi : x); }
-
-// One thread per global row of one direction.  CSR (CSC = 0): offsets come from the caller's rowptr, sanitised;
-// CSC (CSC = 1): from the global column offsets found in the sorted keys.  Writes the relation-local offsets,
-// the global offsets (CSR only; the CSC's are an input), 1/deg (CSR only), the schedule sort pair and the
-// degree histograms of the row's schedule.
-constexpr int kBlkRowsThreads = 1024; // rows per workgroup of blk_rows_kernel
-constexpr int kBlkLocalSched = 4;     // schedules whose histograms a workgroup keeps in LDS
-template <int CSC>
-__device__ __forceinline__ void blk_rows_body(const unsigned bx, const BlockTables &t, const BlockInputs &in, int64_t n_rows_total,
-                                              int64_t sched_pos0, int64_t *ptr_local, int64_t *ptr_global, float *inv_deg, uint32_t *key,
-                                              uint32_t *val, unsigned long long *hist, unsigned long long *err)
+// Inclusive sum over a wavefront by the vector ALU's data-parallel moves (a shuffle goes through the LDS): steps of 1, 2, 4
+// and 8 within a row of 16 lanes, then the last lane of row 0 (2) into row 1 (3), and of row 1 into rows 2 and 3.
+template <int CTRL, int ROWS> __device__ __forceinline__ uint32_t dpp_or_zero(uint32_t x)
 {
-    // degree histograms of the workgroup's rows: the schedule of its first row and the three after it (a workgroup's
-    // 1,024 consecutive rows rarely span more) are counted in LDS and reach the global counters once per workgroup and
-    // bin; counted per wavefront, the few thousand wavefronts of a block queued up on the counters of degrees 1 and 2
-    __shared__ unsigned int rows_s[kBlkLocalSched][kDegHist];
-    __shared__ unsigned long long edges_s[kBlkLocalSched][kDegHist];
-    __shared__ int sched0_s;
-    for (int k = threadIdx.x; k < kBlkLocalSched * kDegHist; k += kBlkRowsThreads) {
-        (&rows_s[0][0])[k] = 0;
-        (&edges_s[0][0])[k] = 0;
-    }
-    if (threadIdx.x == 0) {
-        const int64_t R0 = static_cast<int64_t>(bx) * kBlkRowsThreads;
-        const int rel0 = R0 < n_rows_total ? seg_of(CSC ? t.src_off : t.dst_off, t.n_rel, R0) : 0;
-        sched0_s = CSC ? t.n_rel + rel0 : rel0;
+    return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), CTRL, ROWS, 0xf, false));
+}
+__device__ __forceinline__ uint32_t wave_sum(uint32_t x)
+{
+    x += dpp_or_zero<0x111, 0xf>(x);
+    x += dpp_or_zero<0x112, 0xf>(x);
+    x += dpp_or_zero<0x114, 0xf>(x);
+    x += dpp_or_zero<0x118, 0xf>(x);
+    x += dpp_or_zero<0x142, 0xa>(x);
+    return x + dpp_or_zero<0x143, 0xc>(x);
+}
+
+// exclusive sums over the workgroup's threads of two values; lds: [2][kWaves]; every thread calls it
+__device__ __forceinline__ uint2 block_scan2(uint32_t (*lds)[kWaves], uint32_t a, uint32_t b)
+{
+    const int w = threadIdx.x >> 6;
+    uint32_t x = wave_sum(a), y = wave_sum(b);
+    __syncthreads(); // earlier readers of lds
+    if ((threadIdx.x & 63) == 63) {
+        lds[0][w] = x;
+        lds[1][w] = y;
     }
     __syncthreads();
-    const int sched0 = sched0_s;
-    const int64_t R = static_cast<int64_t>(bx) * kBlkRowsThreads + threadIdx.x;
-    const bool live = R < n_rows_total;
-    uint32_t hkey = 0xffffffffu; // (schedule, capped degree) of this lane's row, for the histogram at the end
-    int64_t hdeg = 0;
-    if (live) {
-    const int64_t *off = CSC ? t.src_off : t.dst_off;
-    const int rel = seg_of(off, t.n_rel, R);
-    const int64_t v = R - off[rel], n_local = off[rel + 1] - off[rel];
-    const int64_t E = t.edge_off[rel + 1] - t.edge_off[rel];
-    int64_t p0, p1;
-    if (CSC) {
-        p0 = ptr_global[R] - t.edge_off[rel];
-        p1 = ptr_global[R + 1] - t.edge_off[rel];
-    } else {
-        const int64_t *rp = in.rowptr[rel];
-        const int64_t r0 = rp[v], r1 = rp[v + 1];
-        if (v == 0 && r0 != 0) report(err, kBadPtr0, rel, 0);
-        if (r1 < r0) report(err, kBadDecrease, rel, v);
-        if (v == n_local - 1 && r1 != E) report(err, kBadTotal, rel, 0);
-        p0 = v == 0 ? 0 : clamp64(r0, 0, E);
-        p1 = v == n_local - 1 ? E : clamp64(r1, p0, E);
-        ptr_global[R] = t.edge_off[rel] + p0;
-        if (R == n_rows_total - 1) ptr_global[n_rows_total] = t.edge_off[t.n_rel];
-        inv_deg[R] = p1 > p0 ? 1.0f / static_cast<float>(p1 - p0) : 0.0f;
+    x -= a;
+    y -= b;
+    for (int q = 0; q < w; ++q) {
+        x += lds[0][q];
+        y += lds[1][q];
     }
-    int64_t *pl = ptr_local + off[rel] + rel; // each relation's slice has one more entry than rows
-    pl[v] = p0;
-    if (v == n_local - 1) pl[n_local] = E;
-    const int64_t deg = p1 - p0;
-    const int capped = static_cast<int>(min(deg, static_cast<int64_t>(kHubMinDeg)));
-    const int sched = CSC ? t.n_rel + rel : rel;
-    key[sched_pos0 + R] = (static_cast<uint32_t>(sched) << 10) | static_cast<uint32_t>(kHubMinDeg - capped);
-    val[sched_pos0 + R] = static_cast<uint32_t>(sched_pos0 + R);
-    hkey = (static_cast<uint32_t>(sched) << 10) | static_cast<uint32_t>(capped);
-    hdeg = deg;
-    }
-    if (live) {
-        const int sched = static_cast<int>(hkey >> 10), capped = static_cast<int>(hkey & 1023u);
-        const int ls = sched - sched0;
-        if (ls >= 0 && ls < kBlkLocalSched) {
-            atomicAdd(&rows_s[ls][capped], 1u);
-            atomicAdd(&edges_s[ls][capped], static_cast<unsigned long long>(hdeg));
-        } else { // a workgroup that spans more than four schedules: straight to the global counters
-            unsigned long long *h = hist + static_cast<int64_t>(sched) * 2 * kDegHist;
-            atomicAdd(&h[capped], 1ull);
-            atomicAdd(&h[kDegHist + capped], static_cast<unsigned long long>(hdeg));
+    return make_uint2(x, y);
+}
+
+// Positions of this lane's elements of kRounds consecutive rounds among those of their buckets: the wavefront's counter of
+// the bucket, plus the lanes below with the same bucket; advances the counters, whose updates a wavefront's LDS accesses
+// take in order.  Whole wavefront.
+constexpr int kRounds = 4;
+__device__ __forceinline__ void stable_slots(uint32_t *cnt, const uint32_t (&bucket)[kRounds], const bool (&live)[kRounds], int bits,
+                                             uint32_t (&at)[kRounds])
+{
+    unsigned long long same[kRounds];
+    const unsigned long long lower = (1ull << (threadIdx.x & 63)) - 1;
+#pragma unroll
+    for (int u = 0; u < kRounds; ++u) same[u] = __ballot(live[u]);
+    for (int b = 0; b < bits; ++b)
+#pragma unroll
+        for (int u = 0; u < kRounds; ++u) {
+            const bool one = (bucket[u] >> b) & 1u;
+            const unsigned long long ones = __ballot(one);
+            same[u] &= one ? ones : ~ones;
         }
+#pragma unroll
+    for (int u = 0; u < kRounds; ++u) {
+        at[u] = 0;
+        if (live[u] && (same[u] & lower) == 0) at[u] = atomicAdd(&cnt[bucket[u]], static_cast<uint32_t>(__popcll(same[u])));
     }
-    __syncthreads();
-    for (int k = threadIdx.x; k < kBlkLocalSched * kDegHist; k += kBlkRowsThreads) {
-        const unsigned int n = (&rows_s[0][0])[k];
-        if (n) {
-            unsigned long long *h = hist + static_cast<int64_t>(sched0 + k / kDegHist) * 2 * kDegHist;
-            atomicAdd(&h[k % kDegHist], static_cast<unsigned long long>(n));
-            atomicAdd(&h[kDegHist + k % kDegHist], (&edges_s[0][0])[k]);
-        }
-    }
+#pragma unroll
+    for (int u = 0; u < kRounds; ++u)
+        at[u] = __shfl(at[u], live[u] ? __ffsll(same[u]) - 1 : 0, 64) + static_cast<uint32_t>(__popcll(same[u] & lower));
 }
 
-// One thread per global edge: the caller's neighbour id, checked and sanitised, goes to the CSR's own copy and,
-// as a global source id, into the transpose's sort key; the value is the global edge id.
-__device__ __forceinline__ void blk_edges_body(const int64_t e, const BlockTables &t, const BlockInputs &in, int64_t n_edges_total,
-                                               int32_t *csr_idx, uint32_t *key, uint32_t *val, unsigned long long *err)
+struct HistLds {
+    uint32_t rows[kDegHist + 3];
+    uint32_t hub_edges, hub_chunks;
+};
+__device__ __forceinline__ void hist_clear(HistLds &h)
 {
-    if (e >= n_edges_total) return;
-    const int rel = seg_of(t.edge_off, t.n_rel, e);
-    const int64_t le = e - t.edge_off[rel], n_src = t.src_off[rel + 1] - t.src_off[rel];
-    int64_t c = in.col[rel][le];
-    if (c < 0 || c >= n_src) {
-        report(err, kBadCol, rel, le);
-        c = clamp64(c, 0, max(n_src - 1, static_cast<int64_t>(0)));
-    }
-    csr_idx[e] = static_cast<int32_t>(c);
-    key[e] = static_cast<uint32_t>(t.src_off[rel] + c);
-    val[e] = static_cast<uint32_t>(e);
+    for (int k = threadIdx.x; k < kDegHist; k += kThreads) h.rows[k] = 0;
+    if (threadIdx.x == 0) h.hub_edges = h.hub_chunks = 0;
 }
-
-template <int CSC>
-__global__ void __launch_bounds__(kBlkRowsThreads) blk_rows_kernel(BlockTables t, BlockInputs in, int64_t n_rows_total, int64_t sched_pos0,
-                                                                   int64_t *ptr_local, int64_t *ptr_global, float *inv_deg, uint32_t *key,
-                                                                   uint32_t *val, unsigned long long *hist, unsigned long long *err)
+__device__ __forceinline__ void hist_add(HistLds &h, uint32_t deg)
 {
-    blk_rows_body<CSC>(blockIdx.x, t, in, n_rows_total, sched_pos0, ptr_local, ptr_global, inv_deg, key, val, hist, err);
-}
-// The two kernels that read the caller's arrays in one grid (they depend on nothing and on each other not at all):
-// the first row_blocks workgroups take the CSR rows, the rest 1,024 edges each.
-__global__ void __launch_bounds__(kBlkRowsThreads) blk_rows_edges_kernel(BlockTables t, BlockInputs in, unsigned row_blocks, int64_t n_rows_total,
-                                                                         int64_t *ptr_local, int64_t *ptr_global, float *inv_deg, uint32_t *row_key,
-                                                                         uint32_t *row_val, unsigned long long *hist, int64_t n_edges_total,
-                                                                         int32_t *csr_idx, uint32_t *edge_key, uint32_t *edge_val,
-                                                                         unsigned long long *err)
-{
-    if (blockIdx.x < row_blocks)
-        blk_rows_body<0>(blockIdx.x, t, in, n_rows_total, 0, ptr_local, ptr_global, inv_deg, row_key, row_val, hist, err);
-    else
-        blk_edges_body(static_cast<int64_t>(blockIdx.x - row_blocks) * kBlkRowsThreads + threadIdx.x, t, in, n_edges_total, csr_idx, edge_key,
-                       edge_val, err);
-}
-
-// global column offsets: colG[U] = number of sorted keys below U, U in [0, n_src_total]
-__device__ __forceinline__ void blk_colptr_body(const int64_t U, const uint32_t *sorted_keys, int64_t n_edges, int64_t n_src_total, int64_t *colG)
-{
-    if (U > n_src_total) return;
-    int64_t lo = 0, hi = n_edges;
-    while (lo < hi) {
-        const int64_t mid = lo + (hi - lo) / 2;
-        if (sorted_keys[mid] < static_cast<uint32_t>(U)) lo = mid + 1;
-        else hi = mid;
-    }
-    colG[U] = lo;
-}
-
-// csc_idx[p] = relation-local destination row of the edge at sorted position p (the block-diagonal structure
-// keeps a relation's columns, and so its CSC slots, contiguous: p is already the slot's global position)
-__device__ __forceinline__ void blk_csc_idx_body(const int64_t p, const BlockTables &t, const uint32_t *sorted_edge, int64_t n_edges_total,
-                                                 const int64_t *ptrG_csr, int64_t n_dst_total, int32_t *csc_idx)
-{
-    if (p >= n_edges_total) return;
-    const int64_t e = sorted_edge[p];
-    const int64_t R = last_le64(ptrG_csr, n_dst_total, e); // the last row starting at or before e owns it (empty rows share offsets)
-    const int rel = seg_of(t.edge_off, t.n_rel, e);
-    csc_idx[p] = static_cast<int32_t>(R - t.dst_off[rel]);
-}
-
-// both readers of the transpose sort's result in one grid: the first col_blocks workgroups the column offsets
-__global__ void __launch_bounds__(256) blk_colptr_csc_idx_kernel(BlockTables t, unsigned col_blocks, const uint32_t *sorted_keys,
-                                                                 const uint32_t *sorted_edge, int64_t n_edges_total, int64_t n_src_total,
-                                                                 int64_t *colG, const int64_t *ptrG_csr, int64_t n_dst_total, int32_t *csc_idx)
-{
-    if (blockIdx.x < col_blocks)
-        blk_colptr_body(static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x, sorted_keys, n_edges_total, n_src_total, colG);
-    else
-        blk_csc_idx_body(static_cast<int64_t>(blockIdx.x - col_blocks) * 256 + threadIdx.x, t, sorted_edge, n_edges_total, ptrG_csr, n_dst_total,
-                         csc_idx);
-}
-
-// Sorted position Q of the schedule sort -> that row's place in its schedule: the row order (relation-local
-// ids), its degree, and the number of 256-edge chunks if it is a hub row.
-__global__ void __launch_bounds__(256) blk_perm_kernel(BlockTables t, const uint32_t *sorted_row, int64_t n_dst_total, int64_t n_total,
-                                                       const int64_t *ptrG_csr, const int64_t *ptrG_csc, int32_t *csr_perm,
-                                                       int32_t *csc_perm, int64_t *sdeg, int64_t *cnt)
-{
-    const int64_t Q = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (Q >= n_total) return;
-    const int64_t g = sorted_row[Q]; // global row: CSR rows first, then CSC rows; the sort keeps the two sides apart
-    int64_t deg;
-    if (Q < n_dst_total) {
-        const int rel = seg_of(t.dst_off, t.n_rel, g);
-        csr_perm[Q] = static_cast<int32_t>(g - t.dst_off[rel]);
-        deg = ptrG_csr[g + 1] - ptrG_csr[g];
-    } else {
-        const int64_t U = g - n_dst_total;
-        const int rel = seg_of(t.src_off, t.n_rel, U);
-        csc_perm[Q - n_dst_total] = static_cast<int32_t>(U - t.src_off[rel]);
-        deg = ptrG_csc[U + 1] - ptrG_csc[U];
-    }
-    sdeg[Q] = deg;
-    cnt[Q] = deg >= kHubMinDeg ? (deg + kHubChunk - 1) / kHubChunk : 0;
-}
-
-// Relation-local schedule offsets, hub chunk ranges and hub chunk descriptors from the two global scans.
-// sptrG: exclusive scan of sdeg over all Q (CSR side counts from 0, CSC side continues from the edge total);
-// chunkG: exclusive scan of cnt.
-__device__ __forceinline__ void blk_sptr_body(const int64_t Q, const BlockTables &t, int64_t n_dst_total, int64_t n_total, const int64_t *sptrG,
-                                              const int64_t *chunkG, const int64_t *sdeg, int64_t *csr_sptr, int64_t *csc_sptr,
-                                              int64_t *hub_chunk_ptr, HubChunk *hub_chunks, int64_t *n_chunks_out)
-{
-    if (Q >= n_total) return;
-    const bool csc = Q >= n_dst_total;
-    const int64_t *off = csc ? t.src_off : t.dst_off;
-    const int64_t P = csc ? Q - n_dst_total : Q;       // position within its side
-    const int rel = seg_of(off, t.n_rel, P);
-    const int sched = csc ? t.n_rel + rel : rel;
-    const int64_t q = P - off[rel], n_local = off[rel + 1] - off[rel];
-    const int64_t start = (csc ? n_dst_total : 0) + off[rel];              // first Q of this schedule
-    const int64_t e_base = sptrG[start], c_base = chunkG[start];
-    int64_t *sp = (csc ? csc_sptr : csr_sptr) + off[rel] + rel;
-    const int64_t s0 = sptrG[Q] - e_base;
-    sp[q] = s0;
-    if (q == n_local - 1) sp[n_local] = sptrG[Q + 1] - e_base;
-    // chunk ranges: entry h for every hub row h and the one after the last (non-hub rows add no chunks, so the
-    // running count simply stays); the slice holds E / 512 + 2 entries, more than hub rows + 1
-    const int64_t E = t.edge_off[rel + 1] - t.edge_off[rel];
-    const int64_t cap = E / kHubMinDeg + 2;
-    int64_t *cp = hub_chunk_ptr + t.hubptr_off[sched];
-    if (q < cap) cp[q] = chunkG[Q] - c_base;
-    if (q == n_local - 1) {
-        if (q + 1 < cap) cp[q + 1] = chunkG[Q + 1] - c_base;
-        n_chunks_out[sched] = chunkG[Q + 1] - c_base;
-    }
-    const int64_t deg = sdeg[Q];
+    atomicAdd(&h.rows[min(deg, static_cast<uint32_t>(kHubMinDeg))], 1u);
     if (deg >= kHubMinDeg) {
-        HubChunk *hc = hub_chunks + t.hub_off[sched];
-        const int64_t room = t.hub_off[sched + 1] - t.hub_off[sched]; // never exceeded by a well-formed CSR
-        const int64_t c0 = chunkG[Q] - c_base, nc = (deg + kHubChunk - 1) / kHubChunk;
-        for (int64_t c = 0; c < nc && c0 + c < room; ++c) { // a hub row's chunks: at most a few thousand, written by its one thread
-            HubChunk d;
-            d.e0 = s0 + c * kHubChunk;
-            d.len = static_cast<int32_t>(min(static_cast<int64_t>(kHubChunk), s0 + deg - d.e0));
-            d.slot = static_cast<int32_t>(c0 + c);
-            hc[c0 + c] = d;
+        atomicAdd(&h.hub_edges, deg);
+        atomicAdd(&h.hub_chunks, (deg + kHubChunk - 1) / kHubChunk);
+    }
+}
+__device__ __forceinline__ void hist_store(const HistLds &h, DegCounts *out)
+{
+    reinterpret_cast<uint32_t *>(out->rows)[threadIdx.x] = h.rows[2 * threadIdx.x] | (h.rows[2 * threadIdx.x + 1] << 16);
+    if (threadIdx.x == 0) {
+        out->hub_rows = h.rows[kHubMinDeg];
+        out->hub_edges = h.hub_edges;
+        out->hub_chunks = h.hub_chunks;
+    }
+}
+
+// ---- first launch ---------------------------------------------------------------------------------------------------
+__global__ void __launch_bounds__(kThreads) blk_prep_kernel(BlockPlan p, BlockArrays a)
+{
+    __shared__ HistLds hist;
+    __shared__ uint32_t buckets[kMaxBuckets];
+    __shared__ unsigned long long err;
+    __shared__ int first_row, last_row;
+    const int tid = threadIdx.x, row_blocks = p.row_blk[p.n_rel];
+    const bool rows = static_cast<int>(blockIdx.x) < row_blocks;
+    const int blk = rows ? blockIdx.x : blockIdx.x - row_blocks;
+    const int rel = seg_of(rows ? p.row_blk : p.edge_blk, p.n_rel, blk);
+    const int n_dst = p.dst_off[rel + 1] - p.dst_off[rel], n_src = p.src_off[rel + 1] - p.src_off[rel], E = p.edge_off[rel + 1] - p.edge_off[rel];
+    const int64_t *rp = p.rowptr[rel];
+    if (tid == 0) err = 0;
+    if (rows) {
+        const int lo = (blk - p.row_blk[rel]) * p.rows_per[rel], hi = min(n_dst, lo + p.rows_per[rel]);
+        int64_t *ptr = a.csr_ptr + p.dst_off[rel] + rel;
+        float *inv_deg = a.inv_deg + p.dst_off[rel];
+        hist_clear(hist);
+        __syncthreads();
+        for (int v = lo + tid; v < hi; v += kThreads) {
+            const int64_t r0 = rp[v], r1 = rp[v + 1], deg = r1 - r0;
+            if (v == 0 && r0 != 0) report(&err, kBadPtr0, rel, 0);
+            if (r1 < r0) report(&err, kBadDecrease, rel, v);
+            if (v == n_dst - 1 && r1 != E) report(&err, kBadTotal, rel, 0);
+            ptr[v] = r0;
+            inv_deg[v] = deg > 0 ? 1.0f / static_cast<float>(deg) : 0.0f;
+            hist_add(hist, static_cast<uint32_t>(min(max(deg, static_cast<int64_t>(0)), static_cast<int64_t>(E))));
+        }
+        if (tid == 0 && hi == n_dst) ptr[n_dst] = E;
+        __syncthreads();
+        hist_store(hist, a.row_counts + blk);
+    } else {
+        const int lo = (blk - p.edge_blk[rel]) * p.edges_per[rel], hi = min(E, lo + p.edges_per[rel]), low = p.low[rel];
+        const int32_t *col = p.col[rel];
+        int32_t *idx = a.csr_idx + p.edge_off[rel];
+        uint32_t *row_of = a.row_of + p.edge_off[rel];
+        if (tid < kMaxBuckets) buckets[tid] = 0;
+        if (lo < hi) { // uniform; n_dst > 0
+            if (tid == 0) first_row = row_at(rp, 0, n_dst, lo);
+            if (tid == 64) last_row = row_at(rp, 0, n_dst, hi - 1);
+        }
+        __syncthreads();
+        for (int e = lo + tid; e < hi; e += kThreads) {
+            int32_t c = col[e];
+            if (c < 0 || c >= n_src) {
+                report(&err, kBadCol, rel, e);
+                c = 0;
+            }
+            idx[e] = c;
+            row_of[e] = static_cast<uint32_t>(row_at(rp, first_row, last_row + 1, e));
+            atomicAdd(&buckets[c >> low], 1u);
+        }
+        __syncthreads();
+        if (tid < kMaxBuckets) a.bucket_counts[static_cast<int64_t>(blk) * kMaxBuckets + tid] = static_cast<uint16_t>(buckets[tid]);
+    }
+    if (tid == 0) a.err[blockIdx.x] = err;
+}
+
+// Whether the first launch found relation `rel` malformed; `word` (one workgroup's pointer, else null) takes the fault or 0.
+__device__ __forceinline__ bool faulty(const BlockPlan &p, const BlockArrays &a, int rel, unsigned long long *word)
+{
+    const int row_blocks = p.row_blk[p.n_rel], nr = p.row_blk[rel + 1] - p.row_blk[rel], ne = p.edge_blk[rel + 1] - p.edge_blk[rel];
+    unsigned long long mine = 0; // nr + ne <= 2 kMaxRowBlocks <= kThreads
+    if (static_cast<int>(threadIdx.x) < nr + ne)
+        mine = a.err[static_cast<int>(threadIdx.x) < nr ? p.row_blk[rel] + threadIdx.x : row_blocks + p.edge_blk[rel] + threadIdx.x - nr];
+    const bool bad = __syncthreads_or(mine != 0);
+    if (word && threadIdx.x == 0) {
+        unsigned long long all = 0;
+        if (bad)
+            for (int i = 0; i < nr + ne; ++i) all = max(all, a.err[i < nr ? p.row_blk[rel] + i : row_blocks + p.edge_blk[rel] + i - nr]);
+        *word = all;
+    }
+    return bad;
+}
+
+struct PlaceLds {
+    uint32_t cnt[kWaves][kDegHist + 3];
+    uint32_t rows_ge[kDegHist + 1], edges_ge[kDegHist + 1]; // rows / edges of degree >= k in the relation
+    uint32_t delta[kMaxRowsPer]; // schedule position of a row's first edge minus its position by row id
+    uint32_t hub_row[kMaxHubs];
+    uint32_t scan[2][kWaves];
+    uint32_t hub[2][3]; // rows, edges, chunks of hub rows: of the relation, of the workgroups before this one
+    uint32_t max_deg;
+};
+
+// The rows [lo, hi) of one direction of a relation, placed in its schedule: rows by descending capped degree (stable),
+// schedule-ordered offsets and neighbours, hub chunks.  counts: of the relation's nb workgroups, this one is the b-th;
+// per: rows per workgroup.  Below the hub degree a row's offset follows from its degree's start and its position.
+__device__ __forceinline__ void place_rows(PlaceLds &L, int n, int lo, int hi, int per, int E, const int64_t *ptr, const int32_t *idx,
+                                           const uint32_t *row_of, int32_t *perm, int64_t *sptr, int32_t *sidx, int64_t *hub_chunk_ptr,
+                                           HubChunk *hub_chunks, const DegCounts *counts, int nb, int b, BlockBack *back)
+{
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int share = per / kWaves; // a multiple of 64
+    const int wlo = lo + w * share, whi = min(hi, wlo + share);
+    for (int i = tid; i < kWaves * (kDegHist + 3); i += kThreads) (&L.cnt[0][0])[i] = 0;
+    if (tid < 6) L.hub[tid / 3][tid % 3] = 0;
+    if (tid == 6) L.max_deg = 0;
+    // thread t: degrees 2 j and 2 j + 1 with j = 255 - t, over all workgroups and over those before this one
+    const int j = kThreads - 1 - tid;
+    uint32_t total0 = 0, total1 = 0, before0 = 0, before1 = 0;
+    uint32_t rows = 0, edges = 0, chunks = 0;
+    if (tid < nb) { // nb <= kThreads
+        rows = counts[tid].hub_rows;
+        edges = counts[tid].hub_edges;
+        chunks = counts[tid].hub_chunks;
+    }
+#pragma unroll 16
+    for (int q = 0; q < nb; ++q) {
+        const uint32_t c = reinterpret_cast<const uint32_t *>(counts[q].rows)[j];
+        total0 += c & 0xffffu;
+        total1 += c >> 16;
+        before0 += q < b ? c & 0xffffu : 0;
+        before1 += q < b ? c >> 16 : 0;
+    }
+    __syncthreads();
+    if (rows > 0) {
+        for (int i = 0; i < (tid < b ? 2 : 1); ++i) {
+            atomicAdd(&L.hub[i][0], rows);
+            atomicAdd(&L.hub[i][1], edges);
+            atomicAdd(&L.hub[i][2], chunks);
         }
     }
+    uint32_t most = 0;
+#pragma unroll 4
+    for (int v = wlo + lane; v < whi; v += 64) {
+        const uint32_t deg = static_cast<uint32_t>(ptr[v + 1] - ptr[v]);
+        atomicAdd(&L.cnt[w][min(deg, static_cast<uint32_t>(kHubMinDeg))], 1u);
+        most = max(most, min(deg, static_cast<uint32_t>(kHubMinDeg)));
+    }
+    atomicMax(&L.max_deg, most);
+    const uint32_t k0 = 2 * j, k1 = k0 + 1;
+    const uint2 above = block_scan2(L.scan, total0 + total1, total0 * k0 + total1 * k1); // its barriers come after the last count
+    const uint32_t hub_rows = L.hub[0][0], hub_edges = L.hub[0][1], hubs_before = L.hub[1][0], hub_edges_before = L.hub[1][1], chunks_before = L.hub[1][2];
+    const uint32_t rows1 = hub_rows + above.x, edges1 = hub_edges + above.y; // of degrees above k1
+    L.rows_ge[k1] = rows1 + total1;
+    L.edges_ge[k1] = edges1 + total1 * k1;
+    L.rows_ge[k0] = rows1 + total1 + total0;
+    L.edges_ge[k0] = edges1 + total1 * k1 + total0 * k0;
+    uint32_t run0 = rows1 + total1 + before0, run1 = rows1 + before1;
+    for (int q = 0; q < kWaves; ++q) {
+        const uint32_t c0 = L.cnt[q][k0], c1 = L.cnt[q][k1];
+        L.cnt[q][k0] = run0;
+        L.cnt[q][k1] = run1;
+        run0 += c0;
+        run1 += c1;
+    }
+    if (tid == 0) {
+        L.rows_ge[kHubMinDeg] = hub_rows;
+        L.edges_ge[kHubMinDeg] = hub_edges;
+        uint32_t run = hubs_before;
+        for (int q = 0; q < kWaves; ++q) {
+            const uint32_t c = L.cnt[q][kHubMinDeg];
+            L.cnt[q][kHubMinDeg] = run;
+            run += c;
+        }
+    }
+    if (b == 0) { // uniform
+        back->rows[k0] = total0;
+        back->rows[k1] = total1;
+        if (tid == 0) {
+            back->rows[kHubMinDeg] = hub_rows;
+            back->hub_edges = hub_edges;
+            back->n_chunks = L.hub[0][2];
+            hub_chunk_ptr[hub_rows] = L.hub[0][2];
+            sptr[n] = E;
+        }
+    }
+    __syncthreads();
+    const int bits = 32 - __clz(static_cast<int>(L.max_deg)); // 0 where every row is empty
+    for (int i0 = wlo; i0 < whi; i0 += 64 * kRounds) { // uniform per wavefront
+        uint32_t k[kRounds], at[kRounds], p0[kRounds];
+        bool live[kRounds];
+#pragma unroll
+        for (int u = 0; u < kRounds; ++u) {
+            const int v = i0 + 64 * u + lane;
+            live[u] = v < whi;
+            p0[u] = live[u] ? static_cast<uint32_t>(ptr[v]) : 0;
+            k[u] = live[u] ? min(static_cast<uint32_t>(ptr[v + 1]) - p0[u], static_cast<uint32_t>(kHubMinDeg)) : 0;
+        }
+        stable_slots(L.cnt[w], k, live, bits, at);
+#pragma unroll
+        for (int u = 0; u < kRounds; ++u) {
+            if (!live[u]) continue;
+            const int v = i0 + 64 * u + lane;
+            perm[at[u]] = v;
+            if (k[u] < kHubMinDeg) {
+                const uint32_t s = L.edges_ge[k[u] + 1] + (at[u] - L.rows_ge[k[u] + 1]) * k[u];
+                sptr[at[u]] = s;
+                L.delta[v - lo] = s - p0[u];
+            } else {
+                L.hub_row[at[u] - hubs_before] = static_cast<uint32_t>(v);
+            }
+        }
+    }
+    __syncthreads();
+    const int n_hubs = static_cast<int>(counts[b].hub_rows);
+    if (n_hubs > 0) { // uniform; two hub rows per thread
+        uint32_t v[2] = {0, 0}, deg[2] = {0, 0}, nc[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            if (2 * tid + i < n_hubs) {
+                v[i] = L.hub_row[2 * tid + i];
+                deg[i] = static_cast<uint32_t>(ptr[v[i] + 1] - ptr[v[i]]);
+            }
+            nc[i] = (deg[i] + kHubChunk - 1) / kHubChunk;
+        }
+        const uint2 first = block_scan2(L.scan, deg[0] + deg[1], nc[0] + nc[1]);
+        uint32_t s = hub_edges_before + first.x, c0 = chunks_before + first.y;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            if (2 * tid + i < n_hubs) {
+                const uint32_t q = hubs_before + 2 * tid + i;
+                sptr[q] = s;
+                hub_chunk_ptr[q] = c0;
+                L.delta[v[i] - lo] = s - static_cast<uint32_t>(ptr[v[i]]);
+                for (uint32_t c = 0; c < nc[i]; ++c) {
+                    HubChunk d;
+                    d.e0 = s + c * kHubChunk;
+                    d.len = static_cast<int32_t>(min(static_cast<uint32_t>(kHubChunk), deg[i] - c * kHubChunk));
+                    d.slot = static_cast<int32_t>(c0 + c);
+                    hub_chunks[c0 + c] = d;
+                }
+            }
+            s += deg[i];
+            c0 += nc[i];
+        }
+        __syncthreads();
+    }
+    if (lo >= hi) return;
+    const int e1 = static_cast<int>(ptr[hi]);
+#pragma unroll 4
+    for (int e = static_cast<int>(ptr[lo]) + tid; e < e1; e += kThreads) sidx[e + L.delta[row_of[e] - lo]] = idx[e];
 }
 
-// sidx of both directions: slot e' of the concatenated schedule-ordered adjacency (CSR slots first, then CSC
-// slots) takes the neighbour id of its row's (e' - row start)-th edge
-__device__ __forceinline__ void blk_sidx_body(const int64_t x, int64_t n_edges_total, int64_t n_dst_total, int64_t n_src_total,
-                                              const int64_t *sptrG, const uint32_t *sorted_row, const int64_t *ptrG_csr,
-                                              const int64_t *ptrG_csc, const int32_t *csr_idx, const int32_t *csc_idx,
-                                              int32_t *csr_sidx, int32_t *csc_sidx)
+// ---- second launch --------------------------------------------------------------------------------------------------
+// A workgroup's edges moved to their buckets of sources: position = start of the bucket + edges of it in earlier
+// workgroups, wavefronts, rounds and lanes.
+struct SpreadLds {
+    uint32_t cnt[kWaves][kMaxBuckets];
+    uint32_t scan[2][kWaves];
+};
+
+__device__ __forceinline__ void spread_edges(SpreadLds &L, const BlockPlan &p, const BlockArrays &a, int rel, int b)
 {
-    if (x >= 2 * n_edges_total) return;
-    if (x < n_edges_total) {
-        const int64_t Q = last_le64(sptrG, n_dst_total, x);
-        const int64_t g = sorted_row[Q];
-        // (the clamp only matters for a malformed CSR, whose offsets need not add up: it is reported, never followed out of bounds)
-        csr_sidx[x] = csr_idx[clamp64(ptrG_csr[g] + (x - sptrG[Q]), 0, n_edges_total - 1)];
-    } else {
-        const int64_t Q = n_dst_total + last_le64(sptrG + n_dst_total, n_src_total, x);
-        const int64_t U = static_cast<int64_t>(sorted_row[Q]) - n_dst_total;
-        csc_sidx[x - n_edges_total] = csc_idx[clamp64(ptrG_csc[U] + (x - sptrG[Q]), 0, n_edges_total - 1)];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int E = p.edge_off[rel + 1] - p.edge_off[rel], n_src = p.src_off[rel + 1] - p.src_off[rel], low = p.low[rel];
+    const int nb = p.edge_blk[rel + 1] - p.edge_blk[rel], per = p.edges_per[rel], share = per / kWaves;
+    const int lo = b * per, hi = min(E, lo + per), wlo = lo + w * share, whi = min(hi, wlo + share);
+    const int32_t *idx = a.csr_idx + p.edge_off[rel];
+    const uint32_t *row_of = a.row_of + p.edge_off[rel];
+    uint2 *out = a.spread + p.edge_off[rel];
+    const uint16_t *counts = a.bucket_counts + static_cast<int64_t>(p.edge_blk[rel]) * kMaxBuckets;
+    for (int i = tid; i < kWaves * kMaxBuckets; i += kThreads) (&L.cnt[0][0])[i] = 0;
+    uint32_t total = 0, before = 0;
+    if (tid < kMaxBuckets) {
+#pragma unroll 16
+        for (int q = 0; q < nb; ++q) {
+            const uint32_t c = counts[q * kMaxBuckets + tid];
+            total += c;
+            before += q < b ? c : 0;
+        }
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (int e = wlo + lane; e < whi; e += 64) atomicAdd(&L.cnt[w][idx[e] >> low], 1u);
+    const uint32_t start = block_scan2(L.scan, total, 0).x; // its barriers come after the last count
+    if (tid < kMaxBuckets) {
+        uint32_t run = start + before;
+        for (int q = 0; q < kWaves; ++q) {
+            const uint32_t c = L.cnt[q][tid];
+            L.cnt[q][tid] = run;
+            run += c;
+        }
+        if (b == 0) {
+            uint32_t *bs = a.bucket_start + rel * (kMaxBuckets + 1);
+            bs[tid] = start;
+            if (tid == kMaxBuckets - 1) bs[kMaxBuckets] = E;
+        }
+    }
+    __syncthreads();
+    int bits = 0;
+    while ((n_src - 1) >> (low + bits) > 0) ++bits;
+    for (int i0 = wlo; i0 < whi; i0 += 64 * kRounds) { // uniform per wavefront
+        uint32_t c[kRounds], row[kRounds], bucket[kRounds], at[kRounds];
+        bool live[kRounds];
+#pragma unroll
+        for (int u = 0; u < kRounds; ++u) {
+            const int e = i0 + 64 * u + lane;
+            live[u] = e < whi;
+            c[u] = live[u] ? static_cast<uint32_t>(idx[e]) : 0;
+            row[u] = live[u] ? row_of[e] : 0;
+            bucket[u] = c[u] >> low;
+        }
+        stable_slots(L.cnt[w], bucket, live, bits, at);
+#pragma unroll
+        for (int u = 0; u < kRounds; ++u)
+            if (live[u]) out[at[u]] = make_uint2(c[u], row[u]);
     }
 }
 
-// both consumers of the two row scans in one grid: the first sptr_blocks workgroups the schedule offsets and hub chunks
-__global__ void __launch_bounds__(256) blk_sptr_sidx_kernel(BlockTables t, unsigned sptr_blocks, int64_t n_dst_total, int64_t n_src_total,
-                                                            int64_t n_total, int64_t n_edges_total, const int64_t *sptrG, const int64_t *chunkG,
-                                                            const int64_t *sdeg, int64_t *csr_sptr, int64_t *csc_sptr, int64_t *hub_chunk_ptr,
-                                                            HubChunk *hub_chunks, int64_t *n_chunks_out, const uint32_t *sorted_row,
-                                                            const int64_t *ptrG_csr, const int64_t *ptrG_csc, const int32_t *csr_idx,
-                                                            const int32_t *csc_idx, int32_t *csr_sidx, int32_t *csc_sidx)
+__global__ void __launch_bounds__(kThreads) blk_spread_kernel(BlockPlan p, BlockArrays a)
 {
-    if (blockIdx.x < sptr_blocks)
-        blk_sptr_body(static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x, t, n_dst_total, n_total, sptrG, chunkG, sdeg, csr_sptr, csc_sptr,
-                      hub_chunk_ptr, hub_chunks, n_chunks_out);
-    else
-        blk_sidx_body(static_cast<int64_t>(blockIdx.x - sptr_blocks) * 256 + threadIdx.x, n_edges_total, n_dst_total, n_src_total, sptrG,
-                      sorted_row, ptrG_csr, ptrG_csc, csr_idx, csc_idx, csr_sidx, csc_sidx);
+    __shared__ union {
+        PlaceLds place;
+        SpreadLds spread;
+    } L;
+    const int row_blocks = p.row_blk[p.n_rel];
+    const bool rows = static_cast<int>(blockIdx.x) < row_blocks;
+    const int blk = rows ? blockIdx.x : blockIdx.x - row_blocks;
+    const int rel = seg_of(rows ? p.row_blk : p.edge_blk, p.n_rel, blk);
+    const int b = blk - (rows ? p.row_blk : p.edge_blk)[rel];
+    if (faulty(p, a, rel, rows && b == 0 ? &a.back[rel].err : nullptr)) return; // uniform
+    if (!rows) {
+        spread_edges(L.spread, p, a, rel, b);
+        return;
+    }
+    const int n = p.dst_off[rel + 1] - p.dst_off[rel], per = p.rows_per[rel], lo = b * per;
+    place_rows(L.place, n, lo, min(n, lo + per), per, p.edge_off[rel + 1] - p.edge_off[rel], a.csr_ptr + p.dst_off[rel] + rel, a.csr_idx + p.edge_off[rel],
+               a.row_of + p.edge_off[rel], a.csr_perm + p.dst_off[rel], a.csr_sptr + p.dst_off[rel] + rel, a.csr_sidx + p.edge_off[rel],
+               a.hub_chunk_ptr + p.hubptr_off[rel], a.hub_chunks + p.hub_off[rel], a.row_counts + p.row_blk[rel], p.row_blk[rel + 1] - p.row_blk[rel], b,
+               a.back + rel);
+}
+
+// ---- third launch: one workgroup per bucket of sources -----------------------------------------------------------------
+__global__ void __launch_bounds__(kThreads) blk_columns_kernel(BlockPlan p, BlockArrays a)
+{
+    constexpr int SRC = 1 << kMaxLow, PER = SRC / kThreads;
+    __shared__ uint32_t cnt[kWaves][SRC];
+    __shared__ uint32_t scan[2][kWaves];
+    __shared__ HistLds hist;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int rel = seg_of(p.src_blk, p.n_rel, blockIdx.x), b = blockIdx.x - p.src_blk[rel];
+    if (faulty(p, a, rel, nullptr)) return; // uniform
+    const int n_src = p.src_off[rel + 1] - p.src_off[rel], low = p.low[rel], u0 = b << low, n = min(n_src - u0, 1 << low);
+    const uint32_t *bs = a.bucket_start + rel * (kMaxBuckets + 1);
+    const int e0 = static_cast<int>(bs[b]), m = static_cast<int>(bs[b + 1]) - e0;
+    const int share = (m + kThreads - 1) / kThreads * 64, wlo = w * share, whi = min(m, wlo + share);
+    const uint2 *in = a.spread + p.edge_off[rel] + e0;
+    int64_t *ptr = a.csc_ptr + p.src_off[rel] + rel;
+    int32_t *idx = a.csc_idx + p.edge_off[rel] + e0;
+    uint32_t *src_of = a.src_of + p.edge_off[rel] + e0;
+    for (int i = tid; i < kWaves * SRC; i += kThreads) (&cnt[0][0])[i] = 0;
+    hist_clear(hist);
+    __syncthreads();
+#pragma unroll 4
+    for (int i = wlo + lane; i < whi; i += 64) atomicAdd(&cnt[w][in[i].x - u0], 1u);
+    __syncthreads();
+    uint32_t deg[PER], sum = 0; // PER consecutive sources per thread
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int u = tid * PER + k;
+        deg[k] = 0;
+        for (int q = 0; q < kWaves; ++q) deg[k] += cnt[q][u];
+        sum += deg[k];
+        if (u < n) hist_add(hist, deg[k]);
+    }
+    uint32_t at0 = block_scan2(scan, sum, 0).x;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int u = tid * PER + k;
+        if (u < n) ptr[u0 + u] = e0 + at0;
+        uint32_t run = at0;
+        for (int q = 0; q < kWaves; ++q) {
+            const uint32_t c = cnt[q][u];
+            cnt[q][u] = run;
+            run += c;
+        }
+        at0 = run;
+    }
+    if (tid == 0 && u0 + n == n_src) ptr[n_src] = p.edge_off[rel + 1] - p.edge_off[rel];
+    __syncthreads();
+    hist_store(hist, a.src_counts + blockIdx.x);
+    for (int i0 = wlo; i0 < whi; i0 += 64 * kRounds) { // uniform per wavefront
+        uint2 pair[kRounds];
+        uint32_t u[kRounds], at[kRounds];
+        bool live[kRounds];
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) {
+            const int i = i0 + 64 * r + lane;
+            live[r] = i < whi;
+            pair[r] = live[r] ? in[i] : make_uint2(u0, 0);
+            u[r] = pair[r].x - u0;
+        }
+        stable_slots(cnt[w], u, live, low, at);
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r)
+            if (live[r]) {
+                idx[at[r]] = static_cast<int32_t>(pair[r].y);
+                src_of[at[r]] = pair[r].x;
+            }
+    }
+}
+
+// ---- fourth launch ------------------------------------------------------------------------------------------------------
+__global__ void __launch_bounds__(kThreads) blk_place_kernel(BlockPlan p, BlockArrays a)
+{
+    __shared__ PlaceLds L;
+    const int rel = seg_of(p.src_blk, p.n_rel, blockIdx.x), b = blockIdx.x - p.src_blk[rel], sched = p.n_rel + rel;
+    if (faulty(p, a, rel, nullptr)) return; // uniform
+    const int n = p.src_off[rel + 1] - p.src_off[rel], per = 1 << p.low[rel], lo = b * per;
+    place_rows(L, n, lo, min(n, lo + per), per, p.edge_off[rel + 1] - p.edge_off[rel], a.csc_ptr + p.src_off[rel] + rel, a.csc_idx + p.edge_off[rel],
+               a.src_of + p.edge_off[rel], a.csc_perm + p.src_off[rel], a.csc_sptr + p.src_off[rel] + rel, a.csc_sidx + p.edge_off[rel],
+               a.hub_chunk_ptr + p.hubptr_off[sched], a.hub_chunks + p.hub_off[sched], a.src_counts + p.src_blk[rel],
+               p.src_blk[rel + 1] - p.src_blk[rel], b, a.back + sched);
 }
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -361,6 +624,19 @@ template <typename T> T *carve(char *&cursor, size_t n)
 }
 
 template <typename T> size_t carve_size(size_t n) { return align_up(std::max<size_t>(n, 1) * sizeof(T), 256); }
+
+// the message of an error word left by `report`
+heta_status malformed(unsigned long long word, const std::vector<Relation *> &rels, const std::vector<std::string> &names)
+{
+    const unsigned long long bad = ~word, kind = bad >> 56, at = bad & ((1ull << 48) - 1);
+    const int which = static_cast<int>((bad >> 48) & 0xff);
+    const Relation &r = *rels[which];
+    const char *name = names[which].c_str();
+    if (kind == kBadPtr0) return fail(HETA_ERR_BAD_CSR, "%s: rowptr[0] is not 0", name);
+    if (kind == kBadDecrease) return fail(HETA_ERR_BAD_CSR, "%s: rowptr decreases at row %llu", name, at);
+    if (kind == kBadTotal) return fail(HETA_ERR_BAD_CSR, "%s: rowptr[n_dst] differs from num_edges = %lld", name, (long long)r.n_edges);
+    return fail(HETA_ERR_BAD_CSR, "%s: col[%llu] outside [0, %lld)", name, at, (long long)r.n_src);
+}
 
 } // namespace
 
@@ -378,211 +654,144 @@ heta_status build_block_on_device(const std::vector<Relation *> &rels, const std
     const int n_rel = static_cast<int>(rels.size());
     if (n_rel == 0) return HETA_OK;
     if (n_rel > kMaxBlockRels) return fail(HETA_ERR_UNSUPPORTED, "block ingest takes at most %d relations at once", kMaxBlockRels);
-    BlockTables t{};
-    BlockInputs in{};
-    t.n_rel = n_rel;
-    size_t hub_total = 0, hubptr_total = 0;
-    for (int i = 0; i < n_rel; ++i) {
-        const Relation &r = *rels[i];
-        t.dst_off[i + 1] = t.dst_off[i] + r.n_dst;
-        t.src_off[i + 1] = t.src_off[i] + r.n_src;
-        t.edge_off[i + 1] = t.edge_off[i] + r.n_edges;
-        in.rowptr[i] = rowptr[i];
-        in.col[i] = col[i];
-    }
-    for (int s = 0; s < 2 * n_rel; ++s) { // chunk descriptors / chunk ranges per schedule: the same bounds as the host path's
-        const int64_t E = rels[s % n_rel]->n_edges;
-        t.hub_off[s] = static_cast<int64_t>(hub_total);
-        t.hubptr_off[s] = static_cast<int64_t>(hubptr_total);
-        hub_total += static_cast<size_t>(E / kHubChunk + E / kHubMinDeg + 1);
-        hubptr_total += static_cast<size_t>(E / kHubMinDeg + 2);
-    }
-    t.hub_off[2 * n_rel] = static_cast<int64_t>(hub_total);
-    t.hubptr_off[2 * n_rel] = static_cast<int64_t>(hubptr_total);
+    BlockPlan p{};
+    p.n_rel = n_rel;
     for (int i = 0; i < n_rel; ++i) { // what needs no look at the arrays is rejected before anything is launched
         const Relation &r = *rels[i];
         if (r.n_edges > 0 && r.n_dst == 0)
             return fail(HETA_ERR_BAD_CSR, "%s: rowptr[n_dst] differs from num_edges = %lld", names[i].c_str(), (long long)r.n_edges);
         if (r.n_edges > 0 && r.n_src == 0) return fail(HETA_ERR_BAD_CSR, "%s: col[0] outside [0, 0)", names[i].c_str());
+        if (r.n_edges + r.n_dst + r.n_src >= kMaxElems) return fail(HETA_ERR_UNSUPPORTED, "%s: too large for the block ingest", names[i].c_str());
+        p.dst_off[i + 1] = p.dst_off[i] + static_cast<int32_t>(r.n_dst);
+        p.src_off[i + 1] = p.src_off[i] + static_cast<int32_t>(r.n_src);
+        p.edge_off[i + 1] = p.edge_off[i] + static_cast<int32_t>(r.n_edges);
+        // one workgroup at least on every side: it writes what a relation without rows has, too
+        const auto per = [](int64_t n, int64_t least) { return static_cast<int32_t>(std::max<int64_t>(least, ((n + kMaxRowBlocks - 1) / kMaxRowBlocks + 255) / 256 * 256)); };
+        const auto blocks = [](int64_t n, int64_t each) { return static_cast<int32_t>(std::max<int64_t>(1, (n + each - 1) / each)); };
+        p.rows_per[i] = per(r.n_dst, 256);
+        p.edges_per[i] = per(r.n_edges, 1024);
+        p.low[i] = r.n_src <= (int64_t(kMaxBuckets) << 9) ? 10 : kMaxLow;
+        p.row_blk[i + 1] = p.row_blk[i] + blocks(r.n_dst, p.rows_per[i]);
+        p.edge_blk[i + 1] = p.edge_blk[i] + blocks(r.n_edges, p.edges_per[i]);
+        p.src_blk[i + 1] = p.src_blk[i] + blocks(r.n_src, int64_t(1) << p.low[i]);
+        p.rowptr[i] = rowptr[i];
+        p.col[i] = col[i];
     }
-    const int64_t nR = t.dst_off[n_rel], nS = t.src_off[n_rel], nE = t.edge_off[n_rel], nQ = nR + nS;
-    if (nQ >= (int64_t(1) << 31) || nE >= (int64_t(1) << 31)) return fail(HETA_ERR_UNSUPPORTED, "block too large for the block ingest");
+    for (int s = 0; s < 2 * n_rel; ++s) { // chunk descriptors / chunk ranges per schedule: the same bounds as the host path's
+        const int32_t E = static_cast<int32_t>(rels[s % n_rel]->n_edges);
+        p.hub_off[s + 1] = p.hub_off[s] + E / kHubChunk + E / kHubMinDeg + 1;
+        p.hubptr_off[s + 1] = p.hubptr_off[s] + E / kHubMinDeg + 2;
+    }
+    const int64_t nR = p.dst_off[n_rel], nS = p.src_off[n_rel], nE = p.edge_off[n_rel];
 
     // ---- the arena: everything the relations keep ------------------------------------------------------
-    const size_t arena_bytes = 2 * carve_size<int64_t>(nR + n_rel) + 2 * carve_size<int64_t>(nS + n_rel) + carve_size<int64_t>(hubptr_total) +
-                               carve_size<HubChunk>(hub_total) + 4 * carve_size<int32_t>(nE) + carve_size<int32_t>(nR) +
+    const size_t n_hub = p.hub_off[2 * n_rel], n_hubptr = p.hubptr_off[2 * n_rel];
+    const size_t arena_bytes = 2 * carve_size<int64_t>(nR + n_rel) + 2 * carve_size<int64_t>(nS + n_rel) + carve_size<int64_t>(n_hubptr) +
+                               carve_size<HubChunk>(n_hub) + 4 * carve_size<int32_t>(nE) + carve_size<int32_t>(nR) +
                                carve_size<int32_t>(nS) + carve_size<float>(nR);
     void *arena = nullptr;
     HETA_HIP(scratch_alloc(&arena, arena_bytes));
+    BlockArrays a{};
     char *cur = static_cast<char *>(arena);
-    int64_t *csr_ptr = carve<int64_t>(cur, nR + n_rel), *csr_sptr = carve<int64_t>(cur, nR + n_rel);
-    int64_t *csc_ptr = carve<int64_t>(cur, nS + n_rel), *csc_sptr = carve<int64_t>(cur, nS + n_rel);
-    int64_t *hub_chunk_ptr = carve<int64_t>(cur, hubptr_total);
-    HubChunk *hub_chunks = carve<HubChunk>(cur, hub_total);
-    int32_t *csr_idx = carve<int32_t>(cur, nE), *csr_sidx = carve<int32_t>(cur, nE);
-    int32_t *csc_idx = carve<int32_t>(cur, nE), *csc_sidx = carve<int32_t>(cur, nE);
-    int32_t *csr_perm = carve<int32_t>(cur, nR), *csc_perm = carve<int32_t>(cur, nS);
-    float *inv_deg = carve<float>(cur, nR);
+    a.csr_ptr = carve<int64_t>(cur, nR + n_rel);
+    a.csr_sptr = carve<int64_t>(cur, nR + n_rel);
+    a.csc_ptr = carve<int64_t>(cur, nS + n_rel);
+    a.csc_sptr = carve<int64_t>(cur, nS + n_rel);
+    a.hub_chunk_ptr = carve<int64_t>(cur, n_hubptr);
+    a.hub_chunks = carve<HubChunk>(cur, n_hub);
+    a.csr_idx = carve<int32_t>(cur, nE);
+    a.csr_sidx = carve<int32_t>(cur, nE);
+    a.csc_idx = carve<int32_t>(cur, nE);
+    a.csc_sidx = carve<int32_t>(cur, nE);
+    a.csr_perm = carve<int32_t>(cur, nR);
+    a.csc_perm = carve<int32_t>(cur, nS);
+    a.inv_deg = carve<float>(cur, nR);
 
-    // ---- scratch: one pool block ---------------------------------------------------------------------------
-    const int64_t n_sort = std::max(nE, nQ);
-    const int64_t hist_elems = sort_hist_elems(std::max<int64_t>(n_sort, 1));
-    const size_t n_hist = static_cast<size_t>(2 * n_rel) * 2 * kDegHist;
-    const size_t scratch_bytes = carve_size<int64_t>(nR + 1) + carve_size<int64_t>(nS + 1) + 2 * carve_size<int64_t>(nQ) +
-                                 2 * carve_size<int64_t>(nQ + 1) + carve_size<int64_t>(2 * scan_scratch_elems(nQ + 1)) +
-                                 4 * carve_size<uint32_t>(n_sort) + 2 * carve_size<uint32_t>(hist_elems) +
-                                 carve_size<uint32_t>(scan_scratch_elems(hist_elems)) + carve_size<unsigned long long>(n_hist + 1) +
-                                 carve_size<int64_t>(2 * n_rel);
-    void *scratch = nullptr;
-    hipError_t he = scratch_alloc(&scratch, scratch_bytes);
-    if (he != hipSuccess) {
+    // ---- scratch: one pool block, and the page-locked results of this thread (written by the kernels: no copy) ----
+    const size_t row_blocks = p.row_blk[n_rel], edge_blocks = p.edge_blk[n_rel], src_blocks = p.src_blk[n_rel];
+    const size_t scratch_bytes = carve_size<DegCounts>(row_blocks) + carve_size<DegCounts>(src_blocks) +
+                                 carve_size<uint16_t>(edge_blocks * kMaxBuckets) + carve_size<uint32_t>(n_rel * (kMaxBuckets + 1)) +
+                                 carve_size<unsigned long long>(row_blocks + edge_blocks) + 2 * carve_size<uint32_t>(nE) + carve_size<uint2>(nE);
+    static thread_local BlockBack *t_back = nullptr; // never freed: it lives as long as the thread builds graphs
+    void *scratch = nullptr, *back = nullptr;
+    hipError_t e = t_back ? hipSuccess : hipHostMalloc(&back, 2 * kMaxBlockRels * sizeof(BlockBack), hipHostMallocPortable | hipHostMallocMapped);
+    if (back) t_back = static_cast<BlockBack *>(back);
+    if (e == hipSuccess) e = scratch_alloc(&scratch, scratch_bytes);
+    if (e != hipSuccess) {
         scratch_free(arena);
-        return fail(he == hipErrorOutOfMemory ? HETA_ERR_OOM : HETA_ERR_DEVICE, "block ingest: %s", hipGetErrorString(he));
+        return fail(e == hipErrorOutOfMemory ? HETA_ERR_OOM : HETA_ERR_DEVICE, "block ingest: %s", hipGetErrorString(e));
     }
     cur = static_cast<char *>(scratch);
-    int64_t *ptrG_csr = carve<int64_t>(cur, nR + 1), *ptrG_csc = carve<int64_t>(cur, nS + 1);
-    int64_t *sdeg = carve<int64_t>(cur, nQ), *cnt = carve<int64_t>(cur, nQ);
-    int64_t *sptrG = carve<int64_t>(cur, nQ + 1), *chunkG = carve<int64_t>(cur, nQ + 1);
-    int64_t *tile_sums = carve<int64_t>(cur, 2 * scan_scratch_elems(nQ + 1)); // two scans share a launch set
-    uint32_t *keyA = carve<uint32_t>(cur, n_sort), *valA = carve<uint32_t>(cur, n_sort);
-    uint32_t *keyB = carve<uint32_t>(cur, n_sort), *valB = carve<uint32_t>(cur, n_sort);
-    uint32_t *shist = carve<uint32_t>(cur, hist_elems), *soffs = carve<uint32_t>(cur, hist_elems);
-    uint32_t *stile = carve<uint32_t>(cur, scan_scratch_elems(hist_elems));
-    unsigned long long *hist = carve<unsigned long long>(cur, n_hist + 1); // the last entry is the error word
-    int64_t *n_chunks_dev = carve<int64_t>(cur, 2 * n_rel);
-    unsigned long long *err = hist + n_hist;
+    a.row_counts = carve<DegCounts>(cur, row_blocks);
+    a.src_counts = carve<DegCounts>(cur, src_blocks);
+    a.bucket_counts = carve<uint16_t>(cur, edge_blocks * kMaxBuckets);
+    a.bucket_start = carve<uint32_t>(cur, n_rel * (kMaxBuckets + 1));
+    a.err = carve<unsigned long long>(cur, row_blocks + edge_blocks);
+    a.row_of = carve<uint32_t>(cur, nE);
+    a.src_of = carve<uint32_t>(cur, nE);
+    a.spread = carve<uint2>(cur, nE);
+    a.back = t_back;
 
-    heta_status e = HETA_OK;
-    auto finish = [&](heta_status s) { // the pool wants idle blocks
-        (void)hipStreamSynchronize(st);
-        scratch_free(scratch);
-        if (s != HETA_OK) scratch_free(arena);
-        return s;
-    };
-#define HETA_BLK(call)                                                                                             \
-    do {                                                                                                           \
-        hipError_t e_ = (call);                                                                                    \
-        if (e_ != hipSuccess) return finish(fail(HETA_ERR_DEVICE, "%s failed: %s", #call, hipGetErrorString(e_))); \
-    } while (0)
-#define HETA_BLK_LAUNCHED(name)                                                                                    \
-    do {                                                                                                           \
-        hipError_t e_ = hipGetLastError();                                                                         \
-        if (e_ != hipSuccess) return finish(fail(HETA_ERR_DEVICE, "launch of %s failed: %s", name, hipGetErrorString(e_))); \
-    } while (0)
-    auto blocks_for = [](int64_t n) { return dim3(static_cast<unsigned>((std::max<int64_t>(n, 1) + 255) / 256)); };
-
-    // offsets of relations without rows, chunk ranges of schedules without hub rows: zero unless written
-    HETA_BLK(hipMemsetAsync(arena, 0, reinterpret_cast<char *>(hub_chunks) - static_cast<char *>(arena), st));
-    // one fill for the histograms, the error word and the chunk counts (consecutive pieces)
-    HETA_BLK(hipMemsetAsync(hist, 0, reinterpret_cast<char *>(n_chunks_dev + 2 * n_rel) - reinterpret_cast<char *>(hist), st));
-    // the schedule sort's pairs: CSR rows at [0, nR), CSC rows at [nR, nQ) of keyB / valB (keyA / valA serve the transpose first)
-    auto blocks_of = [](int64_t n, int64_t per) { return static_cast<unsigned>((n + per - 1) / per); };
-    if (nR == 0) HETA_BLK(hipMemsetAsync(ptrG_csr, 0, sizeof(int64_t), st));
-    uint32_t *ks = keyA, *vs = valA;
-    if (nR > 0 || nE > 0) { // CSR rows and edges, both straight from the caller's arrays, in one launch
-        const unsigned rb = blocks_of(nR, kBlkRowsThreads), eb = blocks_of(nE, kBlkRowsThreads);
-        hipLaunchKernelGGL(blk_rows_edges_kernel, dim3(rb + eb), dim3(kBlkRowsThreads), 0, st, t, in, rb, nR, csr_ptr, ptrG_csr, inv_deg, keyB,
-                           valB, hist, nE, csr_idx, keyA, valA, err);
-        HETA_BLK_LAUNCHED("blk_rows_edges_kernel");
+    const char *name = "blk_prep_kernel";
+    hipLaunchKernelGGL(blk_prep_kernel, dim3(row_blocks + edge_blocks), dim3(kThreads), 0, st, p, a);
+    if ((e = hipGetLastError()) == hipSuccess) {
+        name = "blk_spread_kernel";
+        hipLaunchKernelGGL(blk_spread_kernel, dim3(row_blocks + edge_blocks), dim3(kThreads), 0, st, p, a);
+        e = hipGetLastError();
     }
-    // The transpose sort's ping-pong partner: keyB / valB already hold the CSR rows' schedule pairs, so the partner is the
-    // arena's two sidx arrays (nE 32-bit words each), which nothing touches before the final fill.
-    uint32_t *keyT = reinterpret_cast<uint32_t *>(csr_sidx), *valT = reinterpret_cast<uint32_t *>(csc_sidx);
-    if (nE > 0) {
-        int bits = 1;
-        while ((int64_t(1) << bits) < std::max<int64_t>(nS, 2)) ++bits;
-        if ((e = device_sort_pairs_u32_async(keyA, valA, keyT, valT, nE, int64_t(1) << bits, &ks, &vs, shist, soffs, stile, st)) != HETA_OK)
-            return finish(e);
+    if (e == hipSuccess) {
+        name = "blk_columns_kernel";
+        hipLaunchKernelGGL(blk_columns_kernel, dim3(src_blocks), dim3(kThreads), 0, st, p, a);
+        e = hipGetLastError();
     }
-    {
-        const unsigned cb = blocks_of(nS + 1, 256), ib = blocks_of(nE, 256);
-        hipLaunchKernelGGL(blk_colptr_csc_idx_kernel, dim3(cb + ib), dim3(256), 0, st, t, cb, ks, vs, nE, nS, ptrG_csc, ptrG_csr, nR, csc_idx);
-        HETA_BLK_LAUNCHED("blk_colptr_csc_idx_kernel");
+    if (e == hipSuccess) {
+        name = "blk_place_kernel";
+        hipLaunchKernelGGL(blk_place_kernel, dim3(src_blocks), dim3(kThreads), 0, st, p, a);
+        e = hipGetLastError();
     }
-    if (nS > 0) {
-        hipLaunchKernelGGL(blk_rows_kernel<1>, dim3(static_cast<unsigned>((nS + kBlkRowsThreads - 1) / kBlkRowsThreads)), dim3(kBlkRowsThreads), 0, st, t, in, nS, nR, csc_ptr, ptrG_csc, (float *)nullptr, keyB,
-                           valB, hist, err);
-        HETA_BLK_LAUNCHED("blk_rows_kernel");
+    const hipError_t done = hipStreamSynchronize(st);
+    scratch_free(scratch); // idle
+    heta_status status = HETA_OK;
+    if (e != hipSuccess) status = fail(HETA_ERR_DEVICE, "launch of %s failed: %s", name, hipGetErrorString(e));
+    else if (done != hipSuccess) status = fail(HETA_ERR_DEVICE, "block ingest: %s", hipGetErrorString(done));
+    else {
+        unsigned long long err = 0; // complements: the largest is the first fault
+        for (int i = 0; i < n_rel; ++i) err = std::max(err, t_back[i].err);
+        if (err) status = malformed(err, rels, names);
     }
-    // every schedule's row order: one stable sort by (schedule, 512 - capped degree); 2 n_rel <= 64 schedules: 16 bits
-    uint32_t *ks2 = keyB, *vs2 = valB;
-    if (nQ > 0) {
-        // the transpose's results (ks / vs) are consumed; (keyA, valA) is free as the partner unless the sort ended there
-        uint32_t *pk = keyA, *pv = valA;
-        if ((e = device_sort_pairs_u32_async(keyB, valB, pk, pv, nQ, int64_t(1) << 16, &ks2, &vs2, shist, soffs, stile, st)) != HETA_OK)
-            return finish(e);
-        hipLaunchKernelGGL(blk_perm_kernel, blocks_for(nQ), dim3(256), 0, st, t, vs2, nR, nQ, ptrG_csr, ptrG_csc, csr_perm, csc_perm, sdeg, cnt);
-        HETA_BLK_LAUNCHED("blk_perm_kernel");
-    }
-    if ((e = device_exclusive_scan2_i64_async(sdeg, cnt, nQ, sptrG, chunkG, nQ + 1, tile_sums, st)) != HETA_OK) return finish(e);
-    if (nQ > 0 || nE > 0) {
-        const unsigned sb = blocks_of(nQ, 256), xb = blocks_of(2 * nE, 256);
-        hipLaunchKernelGGL(blk_sptr_sidx_kernel, dim3(sb + xb), dim3(256), 0, st, t, sb, nR, nS, nQ, nE, sptrG, chunkG, sdeg, csr_sptr, csc_sptr,
-                           hub_chunk_ptr, hub_chunks, n_chunks_dev, vs2, ptrG_csr, ptrG_csc, csr_idx, csc_idx, csr_sidx, csc_sidx);
-        HETA_BLK_LAUNCHED("blk_sptr_sidx_kernel");
-    }
-    // histograms, the error word and the chunk counts come back through a page-locked buffer of the thread's own
-    // (hist, err and n_chunks_dev are consecutive in the scratch block: 256-byte aligned pieces)
-    static thread_local void *t_back = nullptr;
-    static thread_local size_t t_back_cap = 0;
-    // one copy: the host buffer mirrors the device layout from hist to the end of the chunk counts
-    const size_t back_hist = reinterpret_cast<char *>(n_chunks_dev) - reinterpret_cast<char *>(hist);
-    const size_t back_total = back_hist + 2 * n_rel * sizeof(int64_t);
-    if (back_total > t_back_cap) {
-        if (t_back) (void)hipHostFree(t_back);
-        t_back = nullptr;
-        t_back_cap = 0;
-        const size_t cap = std::max<size_t>(back_total, (size_t(2) * kMaxBlockRels * 2 * kDegHist + 1) * 8 + 2 * kMaxBlockRels * 8 + 512);
-        HETA_BLK(hipHostMalloc(&t_back, cap, hipHostMallocDefault));
-        t_back_cap = cap;
-    }
-    unsigned long long *h = static_cast<unsigned long long *>(t_back);
-    int64_t *n_chunks = reinterpret_cast<int64_t *>(static_cast<char *>(t_back) + back_hist);
-    HETA_BLK(hipMemcpyAsync(h, hist, back_total, hipMemcpyDeviceToHost, st));
-    HETA_BLK(hipStreamSynchronize(st));
-#undef HETA_BLK
-#undef HETA_BLK_LAUNCHED
-    if (h[n_hist] != 0) {
-        const unsigned long long bad = ~h[n_hist];
-        const unsigned long long kind = bad >> 56, at = bad & ((1ull << 48) - 1);
-        const int which = static_cast<int>((bad >> 48) & 0xff);
-        const Relation &r = *rels[which];
-        const char *name = names[which].c_str();
-        if (kind == kBadPtr0) e = fail(HETA_ERR_BAD_CSR, "%s: rowptr[0] is not 0", name);
-        else if (kind == kBadDecrease) e = fail(HETA_ERR_BAD_CSR, "%s: rowptr decreases at row %llu", name, at);
-        else if (kind == kBadTotal) e = fail(HETA_ERR_BAD_CSR, "%s: rowptr[n_dst] differs from num_edges = %lld", name, (long long)r.n_edges);
-        else e = fail(HETA_ERR_BAD_CSR, "%s: col[%llu] outside [0, %lld)", name, at, (long long)r.n_src);
-        return finish(e);
+    if (status != HETA_OK) {
+        scratch_free(arena);
+        return status;
     }
     for (int i = 0; i < n_rel; ++i) {
         Relation &r = *rels[i];
         for (int side = 0; side < 2; ++side) {
             Schedule &s = side ? r.csc : r.csr;
             const int sched = side ? n_rel + i : i;
-            const int64_t row0 = side ? t.src_off[i] : t.dst_off[i];
-            s.d_ptr = (side ? csc_ptr : csr_ptr) + row0 + i;
-            s.d_sptr = (side ? csc_sptr : csr_sptr) + row0 + i;
-            s.d_idx = (side ? csc_idx : csr_idx) + t.edge_off[i];
-            s.d_sidx = (side ? csc_sidx : csr_sidx) + t.edge_off[i];
-            s.d_perm = (side ? csc_perm : csr_perm) + row0;
-            s.d_hub_chunks = hub_chunks + t.hub_off[sched];
-            s.d_hub_chunk_ptr = hub_chunk_ptr + t.hubptr_off[sched];
-            const unsigned long long *hh = h + static_cast<size_t>(sched) * 2 * kDegHist;
+            const int32_t row0 = side ? p.src_off[i] : p.dst_off[i];
+            s.d_ptr = (side ? a.csc_ptr : a.csr_ptr) + row0 + i;
+            s.d_sptr = (side ? a.csc_sptr : a.csr_sptr) + row0 + i;
+            s.d_idx = (side ? a.csc_idx : a.csr_idx) + p.edge_off[i];
+            s.d_sidx = (side ? a.csc_sidx : a.csr_sidx) + p.edge_off[i];
+            s.d_perm = (side ? a.csc_perm : a.csr_perm) + row0;
+            s.d_hub_chunks = a.hub_chunks + p.hub_off[sched];
+            s.d_hub_chunk_ptr = a.hub_chunk_ptr + p.hubptr_off[sched];
+            const BlockBack &h = t_back[sched];
             int64_t rows = 0, edges = 0;
             for (int k = kHubMinDeg; k >= 0; --k) {
-                rows += static_cast<int64_t>(hh[k]);
-                edges += static_cast<int64_t>(hh[kDegHist + k]);
+                rows += h.rows[k];
+                edges += k == kHubMinDeg ? static_cast<int64_t>(h.hub_edges) : static_cast<int64_t>(h.rows[k]) * k;
                 s.rows_with_deg_ge[k] = rows;
                 s.edges_with_deg_ge[k] = edges;
             }
             s.n_hub_rows = s.rows_with_deg_ge[kHubMinDeg];
-            s.n_hub_chunks = n_chunks[sched];
+            s.n_hub_chunks = h.n_chunks;
         }
-        r.d_inv_deg = inv_deg + t.dst_off[i];
+        r.d_inv_deg = a.inv_deg + p.dst_off[i];
         r.host_built = true; // its arrays are slices of an arena of the graph, not allocations of its own
     }
     *arena_out = arena;
-    return finish(HETA_OK);
+    return HETA_OK;
 }
 
 } // namespace heta

@@ -471,8 +471,9 @@ static heta_status differs_from_device(const T *caller, bool on_device, const T 
 // beat the launch latencies of the device pipeline (sampled mini-batch blocks); everything larger
 // is built by the kernels of heta_ingest.hip.  heta_ingest_force() overrides the choice.
 constexpr int64_t kDeviceIngestMin = 1 << 18;
-// The small relations of one graph together (a sampled block) go through the whole-block device ingest when they
-// add up to this many edges + rows (and are at most 32); below it the host builds them faster than ~40 launches run.
+// The small relations of one call together (a sampled block) go through the whole-block device ingest when their arrays lie
+// on the device already, or add up to this many edges + rows (and are at most 32 relations).  Host arrays below it are
+// built on the host, which needs one copy.
 constexpr int64_t kBlockIngestMin = 1 << 16;
 static int g_ingest_mode = 0; // 0 = by size, 1 = host, 2 = per-relation device kernels, 3 = small relations by the whole-block device ingest
 
@@ -489,20 +490,31 @@ static bool takes_device_path(int64_t E, int64_t n_dst, int64_t n_src)
     return g_ingest_mode == 2 || ((g_ingest_mode == 0 || g_ingest_mode == 3) && E + n_dst + n_src >= kDeviceIngestMin);
 }
 
-// whether the small relations of a graph (those that do not take the per-relation device path) are built together on the device
-static bool takes_block_path(const std::vector<heta_ntype> &nts, const heta_relation *rels, int32_t n_rels)
-{
-    if (g_ingest_mode == 1 || g_ingest_mode == 2) return false;
-    int64_t work = 0;
-    int32_t n_small = 0;
-    for (int32_t i = 0; i < n_rels; ++i) {
-        const int64_t n_dst = nts[rels[i].dst_type].num_nodes, n_src = nts[rels[i].src_type].num_nodes, E = rels[i].num_edges;
-        if (takes_device_path(E, n_dst, n_src)) continue;
-        work += E + n_dst + n_src;
-        ++n_small;
+// Whether the small relations of a call (those that do not take the per-relation device path) are built together on the
+// device, counted graph by graph.
+struct SmallCount {
+    int64_t work = 0, n = 0;
+    void add(const heta_ntype *nts, const heta_relation *rels, int32_t n_rels)
+    {
+        for (int32_t i = 0; i < n_rels; ++i) {
+            const int64_t n_dst = nts[rels[i].dst_type].num_nodes, n_src = nts[rels[i].src_type].num_nodes, E = rels[i].num_edges;
+            if (takes_device_path(E, n_dst, n_src)) continue;
+            work += E + n_dst + n_src;
+            ++n;
+        }
     }
-    if (n_small == 0 || n_small > block_ingest_max_relations()) return false;
-    return g_ingest_mode == 3 || work >= kBlockIngestMin;
+    bool together(bool on_device) const
+    {
+        if (g_ingest_mode == 1 || g_ingest_mode == 2 || n == 0 || n > block_ingest_max_relations()) return false;
+        return g_ingest_mode == 3 || on_device || work >= kBlockIngestMin;
+    }
+};
+
+static bool takes_block_path(const std::vector<heta_ntype> &nts, const heta_relation *rels, int32_t n_rels, bool on_device)
+{
+    SmallCount c;
+    c.add(nts.data(), rels, n_rels);
+    return c.together(on_device);
 }
 
 // One small relation of a graph about to be built: relation `index` of `rels`, registered in g; graph_no is the
@@ -566,14 +578,20 @@ static heta_status build_small_relations_on_device(const std::vector<SmallRef> &
     }
     // The build runs on a stream of the library's own (per thread and device, default priority, non-blocking): its inputs
     // are complete (host arrays; device arrays the caller has finished, as for every synchronous call) and it is complete
-    // when the call returns.  On the legacy default stream every one of its ~45 launches would first be ordered against
+    // when the call returns.  On the legacy default stream every one of its launches would first be ordered against
     // all other streams of the process, which costs more than the kernels run.
     static thread_local hipStream_t t_stream[64] = {};
     int dev = 0;
     HETA_HIP(hipGetDevice(&dev));
     if (dev < 0 || dev >= 64) return fail(HETA_ERR_UNSUPPORTED, "device index %d beyond 64", dev);
     if (!t_stream[dev]) HETA_HIP(hipStreamCreateWithFlags(&t_stream[dev], hipStreamNonBlocking));
-    if (staging) HETA_HIP(hipStreamSynchronize(nullptr)); // the staged arrays have arrived
+    // The staged arrays have arrived; what the caller left on the default stream has run, as on the other paths, whose
+    // copies go there.
+    const hipError_t arrived = hipStreamSynchronize(nullptr);
+    if (arrived != hipSuccess) {
+        scratch_free(staging);
+        return fail(HETA_ERR_DEVICE, "heta_graph_create: %s", hipGetErrorString(arrived));
+    }
     void *arena = nullptr;
     heta_status st = build_block_on_device(built, names, ptrs.data(), cols.data(), &arena, t_stream[dev]); // synchronous
     scratch_free(staging);
@@ -933,7 +951,7 @@ heta_status heta_graph_create(const heta_ntype *ntypes, int32_t n_ntypes, const 
     if (st0 != HETA_OK) return st0;
     if (!(flags & HETA_PTRS_ON_DEVICE)) {
         const std::vector<heta_ntype> nts(ntypes, ntypes + n_ntypes);
-        st0 = validate_host_arrays(ntypes, n_ntypes, rels, n_rels, takes_block_path(nts, rels, n_rels));
+        st0 = validate_host_arrays(ntypes, n_ntypes, rels, n_rels, takes_block_path(nts, rels, n_rels, false));
         if (st0 != HETA_OK) return st0;
     }
     const bool on_device = (flags & HETA_PTRS_ON_DEVICE) != 0;
@@ -945,7 +963,7 @@ heta_status heta_graph_create(const heta_ntype *ntypes, int32_t n_ntypes, const 
         HostPack pack;
         std::vector<PendingRelation> pending;
         std::vector<StagedCsr> staged(n_rels);
-        const bool block_path = takes_block_path(g->ntypes, rels, n_rels);
+        const bool block_path = takes_block_path(g->ntypes, rels, n_rels, on_device);
         if (on_device && !block_path) {
             heta_status st = download_small_relations(g->ntypes, rels, n_rels, staged);
             if (st != HETA_OK) {
@@ -996,20 +1014,10 @@ heta_status heta_graph_create_batch(int32_t n_graphs, const heta_ntype *const *n
     }
     const bool on_device = (flags & HETA_PTRS_ON_DEVICE) != 0;
     // The small relations of all graphs go through one whole-block build when together they qualify for it; otherwise
-    // (too few edges for the device to pay, too many relations for one build, or a forced path) graph by graph.
-    bool together = g_ingest_mode == 0 || g_ingest_mode == 3;
-    if (together) {
-        int64_t work = 0, n_small = 0;
-        for (int32_t q = 0; q < n_graphs; ++q)
-            for (int32_t i = 0; i < n_rels[q]; ++i) {
-                const heta_relation &r = rels[q][i];
-                const int64_t n_dst = ntypes[q][r.dst_type].num_nodes, n_src = ntypes[q][r.src_type].num_nodes;
-                if (takes_device_path(r.num_edges, n_dst, n_src)) continue;
-                work += r.num_edges + n_dst + n_src;
-                ++n_small;
-            }
-        together = n_small > 0 && n_small <= block_ingest_max_relations() && (g_ingest_mode == 3 || work >= kBlockIngestMin);
-    }
+    // (host arrays of too few edges for the device to pay, too many relations for one build, or a forced path) graph by graph.
+    SmallCount small;
+    for (int32_t q = 0; q < n_graphs; ++q) small.add(ntypes[q], rels[q], n_rels[q]);
+    const bool together = small.together(on_device);
     if (together && !on_device)
         for (int32_t q = 0; q < n_graphs; ++q) {
             heta_status st = validate_host_arrays(ntypes[q], n_ntypes[q], rels[q], n_rels[q], true);

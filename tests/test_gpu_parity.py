@@ -192,6 +192,52 @@ def test_device_ingest_edge_cases(mode):
         heta.heta_ingest_force(0)
 
 
+@pytest.mark.parametrize("n_src,n_dst,n_e,hubs", [
+    (1, 1, 1, 0), (3, 5, 0, 0), (0, 4, 0, 0), (4, 0, 0, 0), (1, 700, 5000, 0), (700, 1, 5000, 0), (63, 64, 65, 0), (1023, 255, 1023, 0),
+    (1024, 256, 1024, 0), (1025, 257, 1025, 2), (2049, 513, 4097, 3), (9000, 40, 40000, 5), (31, 15000, 33333, 2), (65536, 16384, 65536, 4),
+    (65537, 16385, 65537, 1), (130000, 132000, 143, 0), (2000, 200000, 60000, 9), (200000, 2000, 60143, 9), (1, 1, 262141, 0)])
+def test_block_ingest_at_the_edges_of_its_workgroups(n_src, n_dst, n_e, hubs):
+    """The whole-block build at the edges of its workgroups' shares (256 rows, 1,024 edges, 1,024 or 2,048 sources; 64 or 128
+    workgroups), with no, some and only hub rows, up to just below 2^18 edges + rows: CSC, degrees and both schedules
+    (through exact integer sums) of three relations built together, from host and device arrays."""
+    g = rng.stream("tests", f"ingest-one/{n_src}/{n_dst}/{n_e}")
+    made = []
+    for k in range(3):
+        dst = np.sort(g.integers(0, max(n_dst, 1), size=n_e)).astype(np.int32)
+        src = g.integers(0, max(n_src, 1), size=n_e).astype(np.int32)
+        for h in range(hubs):  # hub rows of 512, 513, ... edges and a hub column
+            at = np.arange(h * (512 + h), min(n_e, (h + 1) * (512 + h)))
+            dst[at] = min(n_dst - 1, 7 * h)
+            src[at[::2]] = n_src - 1
+        dst = np.sort(dst)
+        if k == 2:
+            dst, src = dst[:n_e // 2], src[:n_e // 2]
+        made.append((dst, src, np.concatenate([[0], np.cumsum(np.bincount(dst, minlength=n_dst))]).astype(np.int64)))
+    for device in (False, True):
+        rels = [(0, 1, torch.from_numpy(p).cuda(), torch.from_numpy(s).cuda()) if device else (0, 1, p, s) for _, s, p in made]
+        heta.heta_ingest_force(3)
+        try:
+            hg = heta.heta_graph_create([(n_src, 4, 0), (n_dst, 4, 0)], rels, flags=heta.HETA_PTRS_ON_DEVICE if device else 0)
+        finally:
+            heta.heta_ingest_force(0)
+        for r, (dst, src, rowptr) in enumerate(made):
+            colptr, row = heta.heta_graph_get_csc(hg, r)
+            ref_colptr, ref_row = oracle.csc(src, dst, n_src)
+            assert np.array_equal(colptr, ref_colptr) and np.array_equal(row, ref_row)
+            assert np.array_equal(heta.heta_graph_get_degrees(hg, r), np.diff(rowptr))
+            if n_src == 0 or n_dst == 0:
+                continue
+            x, y = (g.integers(-50, 50, size=(n, 4)).astype(np.float32) for n in (n_src, n_dst))
+            fwd, bwd = np.zeros((n_dst, 4), dtype=np.float32), np.zeros((n_src, 4), dtype=np.float32)
+            np.add.at(fwd, dst, x[src])
+            np.add.at(bwd, src, y[dst])
+            out, back = torch.full((n_dst, 4), 3.0, device="cuda"), torch.full((n_src, 4), 3.0, device="cuda")
+            heta.heta_rel_aggregate_fwd(hg, r, heta.HETA_SUM, torch.from_numpy(x).cuda(), out)
+            heta.heta_rel_aggregate_bwd(hg, r, heta.HETA_SUM, torch.from_numpy(y).cuda(), back)
+            assert np.array_equal(out.cpu().numpy(), fwd) and np.array_equal(back.cpu().numpy(), bwd)
+        hg.destroy()
+
+
 # ---- a2: heterogeneous gather ----------------------------------------------------------------------
 
 @pytest.mark.parametrize("d,storage,pad", [(128, "f32", 4), (7, "bf16", 8), (7, "bf16", 1), (300, "f32", 1), (789, "bf16", 8)])
