@@ -494,6 +494,15 @@ heta_status heta_sample_neighbors_batch(const heta_graph *g, int32_t n, const in
 heta_status heta_unique_relabel_batch(int32_t n_groups, const int32_t *group_ptr, const int64_t *const *lists,
                                       const int64_t *lens, const int64_t *id_limit, int64_t *const *unique_ids,
                                       int64_t *n_unique, int32_t *const *local, void *hip_stream);
+/* One hop of a mini-batch: heta_sample_neighbors_batch, and heta_unique_relabel_batch over the sampled ids with one set per
+ * node type (the relations leaving it, in the order of the items), queued together and awaited once.  rowptr[i] and
+ * src_ids[i] as there, local[i] (device int32, capacity n_dst[i] * fanout) the position of each sampled id in the set of
+ * its relation's source type; unique_ids[t] (device, one entry per node type of g; may be NULL where no relation leaves t)
+ * with capacity min(number of nodes of t, sum of n_dst[i] * fanout over those relations), n_unique[t] (host) its length.
+ * Every array is a HOST array.  Results and errors are those of the two calls. */
+heta_status heta_sample_hop(const heta_graph *g, int32_t n, const int32_t *rels, const int64_t *const *dst_ids, const int64_t *n_dst,
+                            int32_t fanout, const uint64_t *seeds, int64_t *const *rowptr, int64_t *const *src_ids, int32_t *const *local,
+                            int64_t *n_sampled, int64_t *const *unique_ids, int64_t *n_unique, void *hip_stream);
 
 /* ---- sparse update of a learnable feature table (Sections 2.2 and 6: the learnable vectors of
  * featureless node types and their optimizer states, Adam's moment and variance, are updated after

@@ -35,7 +35,7 @@ EXPORTS = ["heta_graph_create", "heta_graph_create_batch", "heta_graph_destroy",
            "heta_rel_attn_fwd", "heta_rel_attn_bwd", "heta_rel_attn_fwd_train", "heta_rel_attn_fwd_train_multi", "heta_rel_attn_bwd_src_multi", "heta_attn_bwd_dst", "heta_rel_attn_bwd_src",
            "heta_sample_neighbors", "heta_unique_relabel",
            "heta_cross_rel_aggregate_project", "heta_meta_partition", "heta_sample_neighbors_batch",
-           "heta_unique_relabel_batch", "heta_rel_aggregate_fwd_noalloc", "heta_attn_fold", "heta_attn_fold_bwd",
+           "heta_unique_relabel_batch", "heta_sample_hop", "heta_rel_aggregate_fwd_noalloc", "heta_attn_fold", "heta_attn_fold_bwd",
            "heta_graph_index_bytes"]
 # process-wide switches for tests and measurements, declared in csrc/heta_test_hooks.h (not in the public header)
 TEST_HOOKS = ["heta_projection_force_staged", "heta_ingest_force", "heta_projection_f32_native"]
@@ -1106,6 +1106,57 @@ def heta_unique_relabel_batch(groups: Sequence[Sequence[torch.Tensor]], id_limit
                                        ctypes.addressof(a_lim), ctypes.addressof(a_uniq), ctypes.addressof(a_cnt),
                                        ctypes.addressof(a_local), _stream(stream)))
     return [(uniq[j][:a_cnt[j]], local[j]) for j in range(n)]
+
+
+def heta_sample_hop(g: Graph, rels: Sequence[int], dst_ids: Sequence[torch.Tensor], fanout: int, seeds: Sequence[int], stream=None):
+    """One hop of a mini-batch: heta_sample_neighbors_batch and, per node type, heta_unique_relabel of the relations leaving
+    it, in one call (one synchronisation).  Returns (rowptr per item, local source ids per item, unique ids per node type)."""
+    n, n_types = len(rels), len(g.ntypes)
+    dev = dst_ids[0].device if n else torch.device("cuda")
+    sizes = [int(d.numel()) for d in dst_ids]
+    caps = [k * fanout for k in sizes]
+    uniq_caps = [0] * n_types
+    for r, c in zip(rels, caps):
+        uniq_caps[g.rels[r][0]] += c
+    uniq_caps = [min(c, g.ntypes[t][0]) for t, c in enumerate(uniq_caps)]
+    n_ptr, n_uniq, n_cap = sum(sizes) + n, sum(uniq_caps), sum(caps)
+    # row offsets and unique ids in one allocation, local ids in one, the global source ids in a third that goes on return
+    kept = torch.empty(n_ptr + n_uniq, dtype=torch.int64, device=dev)
+    local = torch.empty(max(1, n_cap), dtype=torch.int32, device=dev)
+    src = torch.empty(max(1, n_cap), dtype=torch.int64, device=dev)
+    at, a_rp, a_src, a_local, a_uniq = kept.data_ptr(), [], [], [], []
+    at_s, at_l = src.data_ptr(), local.data_ptr()
+    for k, c in zip(sizes, caps):
+        a_rp.append(at)
+        a_src.append(at_s if c else None)
+        a_local.append(at_l if c else None)
+        at += 8 * (k + 1)
+        at_s += 8 * c
+        at_l += 4 * c
+    for c in uniq_caps:
+        a_uniq.append(at if c else None)
+        at += 8 * c
+    vp, i32, i64, u64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_uint64
+    m = max(1, n)
+    counts, n_unique = (i64 * m)(), (i64 * n_types)()
+    L = load_library()
+    L.heta_sample_hop.argtypes = [vp, i32, vp, vp, vp, i32, vp, vp, vp, vp, vp, vp, vp, vp]
+    _check(L.heta_sample_hop(g.handle, n, (i32 * m)(*[int(r) for r in rels]), (vp * m)(*[_dev(d, "dst_ids", torch.int64) if k else None for d, k in zip(dst_ids, sizes)]),
+                             (i64 * m)(*sizes), int(fanout), (u64 * m)(*[int(x) & ((1 << 64) - 1) for x in seeds]), (vp * m)(*a_rp), (vp * m)(*a_src),
+                             (vp * m)(*a_local), counts, (vp * n_types)(*a_uniq), n_unique, _stream(stream)))
+    # views of the written parts, in one call per buffer
+    parts = [k + 1 for k in sizes]
+    for c, used in zip(uniq_caps, n_unique):
+        parts += [used, c - used]
+    cut = kept.split_with_sizes(parts)
+    parts = []
+    for c, used in zip(caps, counts):
+        parts += [used, c - used]
+    cut_local = local[:n_cap].split_with_sizes(parts) if n else ()
+    cols = list(cut_local[::2])
+    if n_cap - sum(counts) > 1 << 22:  # more than 16 MB of capacity behind the local ids: not kept with the block
+        cols = [c.clone() for c in cols]
+    return list(cut[:n]), cols, list(cut[n::2])
 
 
 def heta_unique_relabel(lists: List[torch.Tensor], id_limit: int, stream=None):

@@ -9,9 +9,10 @@
 // number is mapped below n by the high half of (its high 32 bits) * n.  The result therefore depends
 // on (seed, v) only - not on the launch shape or on which other destinations are sampled.
 //
-// One wavefront per destination: lane i holds the i-th chosen slot, membership is one ballot, and the
-// ascending order of the output is each lane's rank among the chosen slots.  The unique source ids of a
-// node type and the local ids of the sampled edges come from one radix sort of all sampled ids.
+// One wavefront per destination: lane i draws the i-th number and holds the i-th chosen slot, membership is one ballot,
+// and the ascending order of the output is each lane's rank among the chosen slots.  The unique source ids of a node type
+// and the local ids of the sampled edges come from a bitmap of the type's ids, or one radix sort of all sampled ids.  A
+// whole hop is five launches and one synchronisation (heta_sample_hop).
 #include <algorithm>
 #include <vector>
 
@@ -36,68 +37,16 @@ __host__ __device__ inline unsigned long long mix(unsigned long long x)
 
 __device__ __forceinline__ bool id_ok(int64_t v, int64_t n_rows) { return v >= 0 && v < n_rows; }
 
-__device__ __forceinline__ void count_one(const int64_t *ptr, int64_t n_rows, const int64_t *dst_ids, int64_t i, int fanout,
-                                          int64_t *cnt, int *bad)
-{
-    const int64_t v = dst_ids[i];
-    if (!id_ok(v, n_rows)) {
-        *bad = 1; // every writer stores the same value
-        cnt[i] = 0;
-        return;
-    }
-    const int64_t deg = ptr[v + 1] - ptr[v];
-    cnt[i] = deg < fanout ? deg : fanout;
-}
-
-// one wavefront: the sampled in-edges of destination i, ascending edge slot, at out[rowptr[i] ...]
-__device__ __forceinline__ void fill_one(const int64_t *ptr, const int32_t *idx, int64_t n_rows, const int64_t *dst_ids, int64_t i,
-                                         int fanout, unsigned long long seed, const int64_t *rowptr, int64_t *out, int lane)
-{
-    const int64_t v = dst_ids[i];
-    if (!id_ok(v, n_rows)) return;
-    const int64_t start = ptr[v], deg = ptr[v + 1] - start;
-    const int64_t base = rowptr[i];
-    if (deg <= fanout) {
-        if (lane < deg) out[base + lane] = idx[start + lane];
-        return;
-    }
-    const unsigned long long key = mix(seed ^ mix(static_cast<unsigned long long>(v)));
-    int64_t mine = -1; // lane c holds the c-th chosen slot
-    for (int step = 0; step < fanout; ++step) {
-        const int64_t j = deg - fanout + step;
-        const unsigned long long r = mix(key + static_cast<unsigned long long>(step));
-        const int64_t t = static_cast<int64_t>(((r >> 32) * static_cast<unsigned long long>(j + 1)) >> 32);
-        const bool present = __ballot(mine == t) != 0ull;
-        if (lane == step) mine = present ? j : t;
-    }
-    int rank = 0;
-    for (int c = 0; c < fanout; ++c) {
-        const int64_t other = __shfl(mine, c, 64);
-        rank += other < mine ? 1 : 0;
-    }
-    if (lane < fanout) out[base + rank] = idx[start + mine];
-}
-
-__global__ void __launch_bounds__(256) sample_count_kernel(const int64_t *ptr, int64_t n_rows, const int64_t *dst_ids,
-                                                           int64_t n, int fanout, int64_t *cnt, int *bad)
-{
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= n) return;
-    count_one(ptr, n_rows, dst_ids, i, fanout, cnt, bad);
-}
-
-__global__ void __launch_bounds__(256) sample_fill_kernel(const int64_t *ptr, const int32_t *idx, int64_t n_rows,
-                                                          const int64_t *dst_ids, int64_t n, int fanout,
-                                                          unsigned long long seed, const int64_t *rowptr, int64_t *out)
-{
-    const int lane = threadIdx.x & 63;
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-    if (i >= n) return; // uniform per wavefront
-    fill_one(ptr, idx, n_rows, dst_ids, i, fanout, seed, rowptr, out, lane);
-}
-
-// ---- several relations per launch (a hop of a mini-batch): blockIdx.y = item ------------------------------------
+// ---- sampling: up to 32 relations of a hop in two launches --------------------------------------------------------
+// The first counts (destinations in chunks of 256), the second adds up what lies before its 16 destinations, writes their
+// row offsets and samples them, one wavefront per destination.  A launch of a few us costs as much again in submission and
+// gap, so the sum over the chunks before is taken by every workgroup itself while they are at most kChunksAdded; beyond
+// that by a scan (10 M destinations: the workgroups would read 50 GB of sums).  Counts, scan, row offsets and samples in a
+// launch each, with two fills and two copies, took 72 to 93 us a hop where this takes 77 to 116 with the source sets, which
+// had taken another 59 to 68 (64 / 1,024 seeds of a graph of 21 M edges, seven relations).
 constexpr int kFusedItems = 32;
+constexpr int kChunk = 256, kFillPer = 16, kFillSubs = kChunk / kFillPer;
+constexpr int64_t kChunksAdded = 4096;
 struct FusedSample { // passed by value
     int n, fanout;
     const int64_t *ptr[kFusedItems];
@@ -105,38 +54,140 @@ struct FusedSample { // passed by value
     int64_t n_rows[kFusedItems];
     const int64_t *dst[kFusedItems];
     int64_t n_dst[kFusedItems];
-    int64_t off[kFusedItems + 1]; // item r's counts sit at cnt_all[off[r] ...]; off[n] = total
+    int32_t chunk0[kFusedItems + 1]; // first chunk of each item, one at least
     unsigned long long seed[kFusedItems];
     int64_t *rowptr[kFusedItems];
     int64_t *out[kFusedItems];
 };
-
-__global__ void __launch_bounds__(256) sample_count_multi_kernel(FusedSample f, int64_t *cnt_all, int *bad)
+__device__ __forceinline__ int item_of(const FusedSample &f, int chunk)
 {
-    const int r = blockIdx.y;
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= f.n_dst[r]) return;
-    count_one(f.ptr[r], f.n_rows[r], f.dst[r], i, f.fanout, cnt_all + f.off[r], bad + r);
+    int r = 0;
+    while (chunk >= f.chunk0[r + 1]) ++r; // uniform; chunk < chunk0[n]
+    return r;
 }
 
-// scan_all = exclusive scan of all items' counts laid end to end; an item's row offsets restart at 0
-__global__ void __launch_bounds__(256) sample_rowptr_multi_kernel(FusedSample f, const int64_t *scan_all, int64_t *counts)
+// Results of one call, in page-locked host memory that the kernels write: no copies to wait for.
+struct SampleBack {
+    int64_t count[kFusedItems];
+    int32_t bad[kFusedItems]; // set where a destination id is out of range; cleared by the host
+};
+
+// The workgroups past the last chunk clear n_zero pieces of 16 bytes (the bitmap of the same hop's source sets).
+__global__ void __launch_bounds__(kChunk) sample_count_kernel(FusedSample f, uint8_t *cnt, int64_t *chunk_sum, SampleBack *back, uint4 *zero,
+                                                              int64_t n_zero)
 {
-    const int r = blockIdx.y;
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (i > f.n_dst[r]) return;
-    const int64_t first = scan_all[f.off[r]];
-    f.rowptr[r][i] = scan_all[f.off[r] + i] - first;
-    if (i == f.n_dst[r]) counts[r] = scan_all[f.off[r] + i] - first;
+    const int chunk = blockIdx.x;
+    if (chunk >= f.chunk0[f.n]) {
+        const int64_t i = static_cast<int64_t>(chunk - f.chunk0[f.n]) * kChunk + threadIdx.x;
+        if (i < n_zero) zero[i] = make_uint4(0u, 0u, 0u, 0u);
+        return;
+    }
+    __shared__ int total;
+    if (threadIdx.x == 0) total = 0;
+    __syncthreads();
+    const int r = item_of(f, chunk);
+    const int64_t i = static_cast<int64_t>(chunk - f.chunk0[r]) * kChunk + threadIdx.x;
+    int c = 0;
+    if (i < f.n_dst[r]) {
+        const int64_t v = f.dst[r][i];
+        if (!id_ok(v, f.n_rows[r])) back->bad[r] = 1; // every writer stores the same value
+        else c = static_cast<int>(min(f.ptr[r][v + 1] - f.ptr[r][v], static_cast<int64_t>(f.fanout)));
+    }
+    cnt[static_cast<int64_t>(chunk) * kChunk + threadIdx.x] = static_cast<uint8_t>(c); // at most kMaxFanout
+    atomicAdd(&total, c);
+    __syncthreads();
+    if (threadIdx.x == 0) chunk_sum[chunk] = total;
 }
 
-__global__ void __launch_bounds__(256) sample_fill_multi_kernel(FusedSample f)
+__device__ __forceinline__ int64_t readlane64(int64_t x, int lane)
 {
-    const int r = blockIdx.y;
-    const int lane = threadIdx.x & 63;
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-    if (i >= f.n_dst[r]) return; // uniform per wavefront
-    fill_one(f.ptr[r], f.idx[r], f.n_rows[r], f.dst[r], i, f.fanout, f.seed[r], f.rowptr[r], f.out[r], lane);
+    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(x), lane), hi = __builtin_amdgcn_readlane(static_cast<int>(x >> 32), lane);
+    return static_cast<int64_t>((static_cast<unsigned long long>(hi) << 32) | lo);
+}
+
+// one wavefront: the sampled in-edges of destination v, whose `deg` edges start at `start`, ascending edge slot, at out[0 ...]
+__device__ __forceinline__ void fill_one(const int32_t *idx, int64_t v, int64_t start, int64_t deg, int fanout, unsigned long long seed,
+                                         int64_t *out, int lane)
+{
+    if (deg <= fanout) {
+        if (lane < deg) out[lane] = idx[start + lane];
+        return;
+    }
+    // lane c draws the c-th number and holds the c-th chosen slot
+    const unsigned long long key = mix(seed ^ mix(static_cast<unsigned long long>(v)));
+    const int64_t j = deg - fanout + lane;
+    const int64_t drawn = static_cast<int64_t>(((mix(key + static_cast<unsigned long long>(lane)) >> 32) * static_cast<unsigned long long>(j + 1)) >> 32);
+    int64_t mine = -1;
+    for (int step = 0; step < fanout; ++step) {
+        const int64_t t = readlane64(drawn, step);
+        const bool present = __ballot(mine == t) != 0ull;
+        if (lane == step) mine = present ? j : t;
+    }
+    int rank = 0;
+    for (int c = 0; c < fanout; ++c) rank += readlane64(mine, c) < mine ? 1 : 0;
+    if (lane < fanout) out[rank] = idx[start + mine];
+}
+
+// SCANNED: chunk_sum holds the exclusive sums over all chunks; first_blk: see launch_pieces
+template <bool SCANNED>
+__global__ void __launch_bounds__(256) sample_fill_kernel(FusedSample f, int64_t first_blk, const uint8_t *cnt, const int64_t *chunk_sum, SampleBack *back)
+{
+    __shared__ unsigned long long before_s;
+    __shared__ int64_t at[kFillPer], node[kFillPer], first[kFillPer], degree[kFillPer];
+    __shared__ int own[kFillPer];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t blk = first_blk + blockIdx.x;
+    const int chunk = static_cast<int>(blk / kFillSubs), sub = static_cast<int>(blk % kFillSubs), r = item_of(f, chunk), chunk0 = f.chunk0[r];
+    const int64_t n = f.n_dst[r], i0 = static_cast<int64_t>(chunk - chunk0) * kChunk + sub * kFillPer;
+    if (i0 >= n) { // uniform
+        if (i0 == 0 && tid == 0) {
+            f.rowptr[r][0] = 0;
+            back->count[r] = 0;
+        }
+        return;
+    }
+    if (tid == 0) before_s = 0;
+    if (tid < kFillPer && i0 + tid < n) {
+        const int64_t v = f.dst[r][i0 + tid];
+        node[tid] = v;
+        if (id_ok(v, f.n_rows[r])) {
+            first[tid] = f.ptr[r][v];
+            degree[tid] = f.ptr[r][v + 1] - first[tid];
+        } else {
+            degree[tid] = 0;
+        }
+    }
+    unsigned long long before = 0;
+    if (SCANNED) {
+        if (tid == 0) before = static_cast<unsigned long long>(chunk_sum[chunk] - chunk_sum[chunk0]);
+    } else {
+#pragma unroll 4
+        for (int q = chunk0 + tid; q < chunk; q += 256) before += static_cast<unsigned long long>(chunk_sum[q]);
+    }
+    const int c = cnt[static_cast<int64_t>(chunk) * kChunk + tid];
+    if (tid < sub * kFillPer) before += static_cast<unsigned long long>(c);
+    else if (tid < (sub + 1) * kFillPer) own[tid - sub * kFillPer] = c;
+    __syncthreads();
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off, 64);
+    if (lane == 0 && before) atomicAdd(&before_s, before);
+    __syncthreads();
+    if (tid < kFillPer && i0 + tid < n) {
+        int64_t p = static_cast<int64_t>(before_s);
+        for (int q = 0; q < tid; ++q) p += own[q];
+        at[tid] = p;
+        f.rowptr[r][i0 + tid] = p;
+        if (i0 + tid == n - 1) {
+            f.rowptr[r][n] = p + own[tid];
+            back->count[r] = p + own[tid];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kFillPer / 4; ++q) {
+        const int t = wave + 4 * q;
+        if (i0 + t < n) fill_one(f.idx[r], node[t], first[t], degree[t], f.fanout, f.seed[r], f.out[r] + at[t], lane);
+    }
 }
 
 // ---- unique + relabel ----------------------------------------------------------------------------------------
@@ -230,17 +281,19 @@ struct BitSets { // passed by value
     const int64_t *ids[kFusedLists];
     int32_t *local[kFusedLists];
     int64_t len[kFusedLists];
+    const int64_t *len_at[kFusedLists]; // where the length stands on the device, if the host does not know it
     uint8_t set_of[kFusedLists];
     int64_t limit[kFusedItems];
     int64_t *uniq[kFusedItems];
     int32_t tile0[kFusedItems + 1]; // first tile of each set
 };
 
-__global__ void __launch_bounds__(256) bit_zero_kernel(uint4 *bits, int64_t n, int *bad, int n_sets)
+__device__ __forceinline__ int64_t list_len(const BitSets &f, int l) { return f.len_at[l] ? *f.len_at[l] : f.len[l]; }
+
+__global__ void __launch_bounds__(256) bit_zero_kernel(uint4 *bits, int64_t n)
 {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     if (i < n) bits[i] = make_uint4(0u, 0u, 0u, 0u);
-    if (i < n_sets) bad[i] = 0;
 }
 
 // Sets the bits `m` of a word unless all of them are set already.
@@ -265,7 +318,7 @@ __global__ void __launch_bounds__(256) bit_mark_kernel(BitSets f, unsigned long 
     __shared__ unsigned long long set[kMarkDirect];
     __shared__ unsigned key[kMarkSlots];
     const int l = blockIdx.y, g = f.set_of[l];
-    const int64_t n = f.len[l], limit = f.limit[g], *ids = f.ids[l];
+    const int64_t n = list_len(f, l), limit = f.limit[g], *ids = f.ids[l];
     const unsigned n_words = static_cast<unsigned>((limit + 63) / 64);
     const bool direct = n_words <= kMarkDirect && n >= 4 * static_cast<int64_t>(n_words); // uniform
     const int64_t rounds = direct ? (n + kMarkGroups * kMarkIds - 1) / (kMarkGroups * kMarkIds) : 1;
@@ -360,6 +413,10 @@ __global__ void __launch_bounds__(256) bit_count_kernel(const unsigned long long
     if (threadIdx.x == 0) tile_count[blockIdx.x] = n;
 }
 
+// tile_count null: the bits of the tiles before are counted here.  Up to kBitTilesCounted tiles that is shorter than the
+// launch of bit_count_kernel.
+// (115 tiles: 7 us; with the other launch 2 + 4 us and the gap between them.)
+constexpr int kBitTilesCounted = 256;
 __global__ void __launch_bounds__(256) bit_emit_kernel(BitSets f, const unsigned long long *bits, const uint32_t *tile_count,
                                                        uint32_t *word_rank, int64_t *counts)
 {
@@ -368,7 +425,14 @@ __global__ void __launch_bounds__(256) bit_emit_kernel(BitSets f, const unsigned
     int g = 0;
     while (tile >= f.tile0[g + 1]) ++g; // uniform; tile < tile0[n_sets]
     uint32_t before = 0;
-    for (int t = f.tile0[g] + threadIdx.x; t < tile; t += 256) before += tile_count[t];
+    if (tile_count) {
+        for (int t = f.tile0[g] + threadIdx.x; t < tile; t += 256) before += tile_count[t];
+    } else {
+        const ulonglong2 *pairs = reinterpret_cast<const ulonglong2 *>(bits);
+#pragma unroll 8
+        for (int64_t i = static_cast<int64_t>(f.tile0[g]) * 128 + threadIdx.x; i < static_cast<int64_t>(tile) * 128; i += 256)
+            before += __popcll(pairs[i].x) + __popcll(pairs[i].y);
+    }
     before = block_sum(before, lds);
     const int64_t at = static_cast<int64_t>(tile) * 256 + threadIdx.x;
     unsigned long long w = bits[at];
@@ -398,7 +462,7 @@ __global__ void __launch_bounds__(256) bit_local_kernel(BitSets f, const unsigne
 {
     const int l = blockIdx.y;
     const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= f.len[l]) return;
+    if (i >= list_len(f, l)) return;
     const int g = f.set_of[l];
     const int64_t v = f.ids[l][i];
     if (v < 0 || v >= f.limit[g]) return; // reported after the synchronisation
@@ -432,10 +496,11 @@ static bool outputs_apart(int32_t n_groups, const int32_t *group_ptr, const int6
 struct Scratch {
     char *p = nullptr;
     size_t cursor = 0;
+    bool idle = false; // the entry point has synchronised its stream after the last use
     ~Scratch()
     {
         if (!p) return;
-        (void)hipDeviceSynchronize(); // a no-op wait after the entry point's own synchronisation; covers error paths
+        if (!idle) (void)hipDeviceSynchronize(); // error paths
         scratch_free(p);
     }
     static size_t padded(size_t bytes) { return (std::max<size_t>(bytes, 1) + 255) / 256 * 256; }
@@ -473,11 +538,95 @@ static heta_status slots_reserve(size_t n)
     if (n <= t_slots.cap) return HETA_OK;
     const size_t cap = std::max<size_t>(n, 64);
     void *q = nullptr;
-    if (hipHostMalloc(&q, cap * sizeof(Slot), hipHostMallocDefault) != hipSuccess)
+    if (hipHostMalloc(&q, cap * sizeof(Slot), hipHostMallocPortable | hipHostMallocMapped) != hipSuccess)
         return fail(HETA_ERR_OOM, "page-locked host allocation of %zu result slots failed", cap);
     if (t_slots.p) (void)hipHostFree(t_slots.p);
     t_slots.p = static_cast<Slot *>(q);
     t_slots.cap = cap;
+    return HETA_OK;
+}
+
+// Fills in the items' arguments.
+static void sample_plan(FusedSample &f, const heta_graph *g, int32_t n, const int32_t *rels, const int64_t *const *dst_ids, const int64_t *n_dst,
+                           int32_t fanout, const uint64_t *seeds, int64_t *const *rowptr, int64_t *const *src_ids)
+{
+    f.n = n;
+    f.fanout = fanout;
+    int64_t chunks = 0; // at most kFusedItems + 2^31 / kChunk: the callers bound the destinations
+    for (int32_t i = 0; i < n; ++i) {
+        const Relation &r = g->rels[rels[i]];
+        f.ptr[i] = r.csr.d_ptr;
+        f.idx[i] = r.csr.d_idx;
+        f.n_rows[i] = r.n_dst;
+        f.dst[i] = dst_ids[i];
+        f.n_dst[i] = n_dst[i];
+        f.seed[i] = seeds[i];
+        f.rowptr[i] = rowptr[i];
+        f.out[i] = src_ids[i];
+        f.chunk0[i] = static_cast<int32_t>(chunks);
+        chunks += std::max<int64_t>(1, (n_dst[i] + kChunk - 1) / kChunk);
+    }
+    f.chunk0[n] = static_cast<int32_t>(chunks);
+}
+static size_t sample_scratch_bytes(int64_t chunks)
+{
+    const size_t c = static_cast<size_t>(chunks);
+    return Scratch::padded(c * kChunk) + 2 * Scratch::padded((c + 1) * sizeof(int64_t)) +
+           Scratch::padded(static_cast<size_t>(scan_scratch_elems(chunks + 1)) * sizeof(int64_t));
+}
+static heta_status sample_launch(const FusedSample &f, Scratch &scratch, SampleBack *back, uint4 *zero, int64_t n_zero, hipStream_t st)
+{
+    const int64_t chunks = f.chunk0[f.n];
+    uint8_t *cnt = scratch.take<uint8_t>(static_cast<size_t>(chunks) * kChunk);
+    int64_t *sums = scratch.take<int64_t>(static_cast<size_t>(chunks) + 1), *scanned = scratch.take<int64_t>(static_cast<size_t>(chunks) + 1);
+    int64_t *tsum = scratch.take<int64_t>(static_cast<size_t>(scan_scratch_elems(chunks + 1)));
+    for (int r = 0; r < f.n; ++r) back->bad[r] = 0;
+    hipLaunchKernelGGL(sample_count_kernel, dim3((unsigned)(chunks + (n_zero + kChunk - 1) / kChunk)), dim3(kChunk), 0, st, f, cnt, sums, back, zero, n_zero);
+    HETA_LAUNCH_CHECK("sample_count_kernel");
+    if (chunks > kChunksAdded) {
+        heta_status e = device_exclusive_scan_i64_async(sums, chunks, scanned, chunks + 1, tsum, st);
+        if (e != HETA_OK) return e;
+    }
+    launch_pieces(chunks * kFillSubs, 256, [&](int64_t first, unsigned blocks) {
+        if (chunks > kChunksAdded)
+            hipLaunchKernelGGL(sample_fill_kernel<true>, dim3(blocks), dim3(256), 0, st, f, first, cnt, scanned, back);
+        else
+            hipLaunchKernelGGL(sample_fill_kernel<false>, dim3(blocks), dim3(256), 0, st, f, first, cnt, sums, back);
+    });
+    HETA_LAUNCH_CHECK("sample_fill_kernel");
+    return HETA_OK;
+}
+// after the synchronisation: the counts, or the fault
+static heta_status sample_results(const heta_graph *g, const SampleBack *back, int32_t n, const int32_t *rels, int64_t *n_sampled)
+{
+    for (int32_t i = 0; i < n; ++i)
+        if (back->bad[i])
+            return fail(HETA_ERR_INVALID_ARG, "heta_sample_neighbors: a destination id of relation %d lies outside [0, %lld)", rels[i],
+                        (long long)g->rels[rels[i]].n_dst);
+    for (int32_t i = 0; i < n; ++i) n_sampled[i] = back->count[i];
+    return HETA_OK;
+}
+constexpr size_t kBackSlots = (sizeof(SampleBack) + sizeof(Slot) - 1) / sizeof(Slot);
+
+// The bitmap form of unique + relabel from the mark on, for sets whose bits are clear; counts and bad (cleared) may be
+// page-locked host memory.  cap: the longest list's length or a bound of it.
+static heta_status bits_launch(const BitSets &f, int32_t n_lists, int64_t cap, unsigned long long *bits, uint32_t *word_rank, uint32_t *tile_count,
+                               int64_t *counts, int *bad, hipStream_t st)
+{
+    const int tiles = f.tile0[f.n_sets];
+    if (cap == 0) return HETA_OK;
+    const dim3 mark_grid((unsigned)((cap + kMarkIds - 1) / kMarkIds), (unsigned)n_lists);
+    hipLaunchKernelGGL(bit_mark_kernel, mark_grid, dim3(256), 0, st, f, bits, bad);
+    HETA_LAUNCH_CHECK("bit_mark_kernel");
+    if (tiles > kBitTilesCounted) {
+        hipLaunchKernelGGL(bit_count_kernel, dim3((unsigned)tiles), dim3(256), 0, st, bits, tile_count);
+        HETA_LAUNCH_CHECK("bit_count_kernel");
+    }
+    hipLaunchKernelGGL(bit_emit_kernel, dim3((unsigned)tiles), dim3(256), 0, st, f, bits, tiles > kBitTilesCounted ? tile_count : (uint32_t *)nullptr,
+                       word_rank, counts);
+    HETA_LAUNCH_CHECK("bit_emit_kernel");
+    hipLaunchKernelGGL(bit_local_kernel, dim3((unsigned)((cap + 255) / 256), (unsigned)n_lists), dim3(256), 0, st, f, bits, word_rank);
+    HETA_LAUNCH_CHECK("bit_local_kernel");
     return HETA_OK;
 }
 
@@ -497,7 +646,7 @@ heta_status heta_sample_neighbors_batch(const heta_graph *g, int32_t n, const in
         return fail(HETA_ERR_INVALID_ARG, "heta_sample_neighbors: null argument");
     if (fanout < 1 || fanout > kMaxFanout)
         return fail(HETA_ERR_SHAPE, "heta_sample_neighbors: need 1 <= fanout <= %d", kMaxFanout);
-    size_t bytes = 0;
+    int64_t all_dst = 0;
     for (int32_t i = 0; i < n; ++i) {
         if (rels[i] < 0 || rels[i] >= (int32_t)g->rels.size())
             return fail(HETA_ERR_INVALID_ARG, "heta_sample_neighbors: relation %d out of range", rels[i]);
@@ -505,102 +654,42 @@ heta_status heta_sample_neighbors_batch(const heta_graph *g, int32_t n, const in
         if (!rowptr[i] || (n_dst[i] > 0 && (!dst_ids[i] || !src_ids[i])))
             return fail(HETA_ERR_INVALID_ARG, "heta_sample_neighbors: null argument");
         n_sampled[i] = 0;
-        if (n_dst[i] == 0) continue;
-        bytes += Scratch::padded(static_cast<size_t>(n_dst[i]) * sizeof(int64_t)) +
-                 Scratch::padded(static_cast<size_t>(scan_scratch_elems(n_dst[i] + 1)) * sizeof(int64_t));
+        if (n_dst[i] >= (int64_t(1) << 31)) return fail(HETA_ERR_UNSUPPORTED, "heta_sample_neighbors: more than 2^31 destinations");
+        all_dst += n_dst[i];
     }
     if (n == 0) return HETA_OK;
     hipStream_t st = as_stream(hip_stream);
-    Scratch scratch;
     heta_status e;
-    int64_t all_dst = 0;
-    for (int32_t i = 0; i < n; ++i) all_dst += n_dst[i];
-    if (n <= kFusedItems && all_dst > 0) {
-        // every item in the same launches: counts of all items end to end, one scan, row offsets per item
+    if (n <= kFusedItems && all_dst >= (int64_t(1) << 31)) return fail(HETA_ERR_UNSUPPORTED, "heta_sample_neighbors: more than 2^31 destinations");
+    // Up to kFusedItems items of fewer than 2^31 destinations together share their launches; one synchronisation for all.
+    const auto group_end = [&](int32_t i) {
+        int64_t total = n_dst[i];
+        int32_t j = i + 1;
+        while (j < n && j - i < kFusedItems && total + n_dst[j] < (int64_t(1) << 31)) total += n_dst[j++];
+        return j;
+    };
+    size_t bytes = 0, groups = 0;
+    for (int32_t i = 0; i < n; ++i) bytes += sample_scratch_bytes(std::max<int64_t>(1, (n_dst[i] + kChunk - 1) / kChunk));
+    for (int32_t i = 0; i < n; i = group_end(i)) ++groups;
+    Scratch scratch;
+    if ((e = scratch.alloc(bytes)) != HETA_OK || (e = slots_reserve(kBackSlots * groups)) != HETA_OK) return e;
+    Slot *slot = t_slots.p;
+    for (int32_t i = 0, j; i < n; i = j, slot += kBackSlots) {
+        j = group_end(i);
         FusedSample f{};
-        f.n = n;
-        f.fanout = fanout;
-        int64_t total = 0, n_max = 0;
-        for (int32_t i = 0; i < n; ++i) {
-            const Relation &r = g->rels[rels[i]];
-            f.ptr[i] = r.csr.d_ptr;
-            f.idx[i] = r.csr.d_idx;
-            f.n_rows[i] = r.n_dst;
-            f.dst[i] = dst_ids[i];
-            f.n_dst[i] = n_dst[i];
-            f.off[i] = total;
-            f.seed[i] = seeds[i];
-            f.rowptr[i] = rowptr[i];
-            f.out[i] = src_ids[i];
-            total += n_dst[i];
-            n_max = std::max(n_max, n_dst[i]);
-        }
-        f.off[n] = total;
-        if (total >= (int64_t(1) << 31)) return fail(HETA_ERR_UNSUPPORTED, "heta_sample_neighbors: more than 2^31 destinations");
-        const size_t T = static_cast<size_t>(total);
-        const size_t fused_bytes = Scratch::padded(static_cast<size_t>(n) * sizeof(int)) + Scratch::padded(T * sizeof(int64_t)) +
-                                   Scratch::padded((T + 1) * sizeof(int64_t)) +
-                                   Scratch::padded(static_cast<size_t>(scan_scratch_elems(total + 1)) * sizeof(int64_t)) +
-                                   Scratch::padded(static_cast<size_t>(n) * sizeof(int64_t));
-        if ((e = scratch.alloc(fused_bytes)) != HETA_OK || (e = slots_reserve(2 * static_cast<size_t>(n))) != HETA_OK) return e;
-        int *bad = scratch.take<int>(static_cast<size_t>(n));
-        int64_t *cnt_all = scratch.take<int64_t>(T), *scan_all = scratch.take<int64_t>(T + 1);
-        int64_t *tsum = scratch.take<int64_t>(static_cast<size_t>(scan_scratch_elems(total + 1)));
-        int64_t *counts = scratch.take<int64_t>(static_cast<size_t>(n));
-        HETA_HIP(hipMemsetAsync(bad, 0, static_cast<size_t>(n) * sizeof(int), st));
-        hipLaunchKernelGGL(sample_count_multi_kernel, dim3((unsigned)((n_max + 255) / 256), (unsigned)n), dim3(256), 0, st, f,
-                           cnt_all, bad);
-        HETA_LAUNCH_CHECK("sample_count_multi_kernel");
-        if ((e = device_exclusive_scan_i64_async(cnt_all, total, scan_all, total + 1, tsum, st)) != HETA_OK) return e;
-        hipLaunchKernelGGL(sample_rowptr_multi_kernel, dim3((unsigned)((n_max + 1 + 255) / 256), (unsigned)n), dim3(256), 0, st, f,
-                           scan_all, counts);
-        HETA_LAUNCH_CHECK("sample_rowptr_multi_kernel");
-        hipLaunchKernelGGL(sample_fill_multi_kernel, dim3((unsigned)((n_max + 3) / 4), (unsigned)n), dim3(256), 0, st, f);
-        HETA_LAUNCH_CHECK("sample_fill_multi_kernel");
-        // counts in slots [0, n), flags in slots [n, 2n) (their .bad fields), one copy each
-        int64_t *h_counts = reinterpret_cast<int64_t *>(t_slots.p);
-        int *h_bad = reinterpret_cast<int *>(t_slots.p + n);
-        HETA_HIP(hipMemcpyAsync(h_counts, counts, static_cast<size_t>(n) * sizeof(int64_t), hipMemcpyDeviceToHost, st));
-        HETA_HIP(hipMemcpyAsync(h_bad, bad, static_cast<size_t>(n) * sizeof(int), hipMemcpyDeviceToHost, st));
-        HETA_HIP(hipStreamSynchronize(st));
-        for (int32_t i = 0; i < n; ++i)
-            if (h_bad[i])
-                return fail(HETA_ERR_INVALID_ARG, "heta_sample_neighbors: a destination id of relation %d lies outside [0, %lld)",
-                            rels[i], (long long)g->rels[rels[i]].n_dst);
-        for (int32_t i = 0; i < n; ++i) n_sampled[i] = h_counts[i];
-        return HETA_OK;
-    }
-    bytes += Scratch::padded(static_cast<size_t>(n) * sizeof(int));
-    if ((e = scratch.alloc(bytes)) != HETA_OK || (e = slots_reserve(static_cast<size_t>(n))) != HETA_OK) return e;
-    int *bad = scratch.take<int>(static_cast<size_t>(n));
-    HETA_HIP(hipMemsetAsync(bad, 0, static_cast<size_t>(n) * sizeof(int), st));
-    // per relation count -> scan -> fill -> count and flag to the host, all asynchronous; one synchronisation for the batch
-    for (int32_t i = 0; i < n; ++i) {
-        const Relation &r = g->rels[rels[i]];
-        t_slots.p[i].count = 0;
-        t_slots.p[i].bad = 0;
-        if (n_dst[i] == 0) {
-            HETA_HIP(hipMemsetAsync(rowptr[i], 0, sizeof(int64_t), st));
-            continue;
-        }
-        int64_t *cnt = scratch.take<int64_t>(static_cast<size_t>(n_dst[i]));
-        int64_t *tsum = scratch.take<int64_t>(static_cast<size_t>(scan_scratch_elems(n_dst[i] + 1)));
-        hipLaunchKernelGGL(sample_count_kernel, dim3((unsigned)((n_dst[i] + 255) / 256)), dim3(256), 0, st, r.csr.d_ptr, r.n_dst,
-                           dst_ids[i], n_dst[i], (int)fanout, cnt, bad + i);
-        HETA_LAUNCH_CHECK("sample_count_kernel");
-        if ((e = device_exclusive_scan_i64_async(cnt, n_dst[i], rowptr[i], n_dst[i] + 1, tsum, st)) != HETA_OK) return e;
-        hipLaunchKernelGGL(sample_fill_kernel, dim3((unsigned)((n_dst[i] + 3) / 4)), dim3(256), 0, st, r.csr.d_ptr, r.csr.d_idx,
-                           r.n_dst, dst_ids[i], n_dst[i], (int)fanout, (unsigned long long)seeds[i], rowptr[i], src_ids[i]);
-        HETA_LAUNCH_CHECK("sample_fill_kernel");
-        HETA_HIP(hipMemcpyAsync(&t_slots.p[i].bad, bad + i, sizeof(int), hipMemcpyDeviceToHost, st));
-        HETA_HIP(hipMemcpyAsync(&t_slots.p[i].count, rowptr[i] + n_dst[i], sizeof(int64_t), hipMemcpyDeviceToHost, st));
+        sample_plan(f, g, j - i, rels + i, dst_ids + i, n_dst + i, fanout, seeds + i, rowptr + i, src_ids + i);
+        if ((e = sample_launch(f, scratch, reinterpret_cast<SampleBack *>(slot), nullptr, 0, st)) != HETA_OK) return e;
     }
     HETA_HIP(hipStreamSynchronize(st));
-    for (int32_t i = 0; i < n; ++i)
-        if (t_slots.p[i].bad)
-            return fail(HETA_ERR_INVALID_ARG, "heta_sample_neighbors: a destination id of relation %d lies outside [0, %lld)",
-                        rels[i], (long long)g->rels[rels[i]].n_dst);
-    for (int32_t i = 0; i < n; ++i) n_sampled[i] = t_slots.p[i].count;
+    scratch.idle = true;
+    slot = t_slots.p;
+    for (int32_t i = 0, j; i < n; i = j, slot += kBackSlots) {
+        j = group_end(i);
+        if ((e = sample_results(g, reinterpret_cast<const SampleBack *>(slot), j - i, rels + i, n_sampled + i)) != HETA_OK) {
+            std::fill(n_sampled, n_sampled + n, int64_t(0));
+            return e;
+        }
+    }
     return HETA_OK;
 }
 
@@ -672,32 +761,20 @@ static heta_status heta_unique_relabel_batch_impl(int32_t n_groups, const int32_
         if (tiles <= kBitTilesMax) {
             f.tile0[n_groups] = static_cast<int32_t>(tiles);
             const size_t words = static_cast<size_t>(tiles) * 256, ns = static_cast<size_t>(n_groups);
-            const size_t result_bytes = ns * (sizeof(int64_t) + sizeof(int)); // counts, then error flags: one copy back
-            if ((e = scratch.alloc(Scratch::padded(result_bytes) + Scratch::padded(words * 8) + Scratch::padded(words * 4) +
-                                   Scratch::padded(static_cast<size_t>(tiles) * 4))) != HETA_OK ||
-                (e = slots_reserve(ns)) != HETA_OK)
+            if ((e = scratch.alloc(Scratch::padded(words * 8) + Scratch::padded(words * 4) + Scratch::padded(static_cast<size_t>(tiles) * 4))) != HETA_OK ||
+                (e = slots_reserve(ns)) != HETA_OK) // a slot holds a count and a flag
                 return e;
-            int64_t *counts = reinterpret_cast<int64_t *>(scratch.take<char>(result_bytes));
-            int *bad = reinterpret_cast<int *>(counts + n_groups);
+            int64_t *h_counts = reinterpret_cast<int64_t *>(t_slots.p); // written by the kernels
+            int *h_bad = reinterpret_cast<int *>(h_counts + n_groups);
+            for (int32_t gidx = 0; gidx < n_groups; ++gidx) h_bad[gidx] = 0;
             unsigned long long *bits = scratch.take<unsigned long long>(words);
             uint32_t *word_rank = scratch.take<uint32_t>(words), *tile_count = scratch.take<uint32_t>(static_cast<size_t>(tiles));
-            const dim3 lists_grid((unsigned)((len_max + 255) / 256), (unsigned)group_ptr[n_groups]);
             hipLaunchKernelGGL(bit_zero_kernel, dim3((unsigned)((words / 2 + 255) / 256)), dim3(256), 0, st, reinterpret_cast<uint4 *>(bits),
-                               static_cast<int64_t>(words / 2), bad, (int)n_groups);
+                               static_cast<int64_t>(words / 2));
             HETA_LAUNCH_CHECK("bit_zero_kernel");
-            const dim3 mark_grid((unsigned)((len_max + kMarkIds - 1) / kMarkIds), (unsigned)group_ptr[n_groups]);
-            hipLaunchKernelGGL(bit_mark_kernel, mark_grid, dim3(256), 0, st, f, bits, bad);
-            HETA_LAUNCH_CHECK("bit_mark_kernel");
-            hipLaunchKernelGGL(bit_count_kernel, dim3((unsigned)tiles), dim3(256), 0, st, bits, tile_count);
-            HETA_LAUNCH_CHECK("bit_count_kernel");
-            hipLaunchKernelGGL(bit_emit_kernel, dim3((unsigned)tiles), dim3(256), 0, st, f, bits, tile_count, word_rank, counts);
-            HETA_LAUNCH_CHECK("bit_emit_kernel");
-            hipLaunchKernelGGL(bit_local_kernel, lists_grid, dim3(256), 0, st, f, bits, word_rank);
-            HETA_LAUNCH_CHECK("bit_local_kernel");
-            int64_t *h_counts = reinterpret_cast<int64_t *>(t_slots.p); // a slot is larger than a count and a flag
-            const int *h_bad = reinterpret_cast<const int *>(h_counts + n_groups);
-            HETA_HIP(hipMemcpyAsync(h_counts, counts, result_bytes, hipMemcpyDeviceToHost, st));
+            if ((e = bits_launch(f, group_ptr[n_groups], len_max, bits, word_rank, tile_count, h_counts, h_bad, st)) != HETA_OK) return e;
             HETA_HIP(hipStreamSynchronize(st));
+            scratch.idle = true;
             for (int32_t gidx = 0; gidx < n_groups; ++gidx)
                 if (h_bad[gidx])
                     return fail(HETA_ERR_INVALID_ARG, "heta_unique_relabel: an id lies outside [0, %lld)", (long long)id_limit[gidx]);
@@ -857,6 +934,106 @@ heta_status heta_unique_relabel_batch(int32_t n_groups, const int32_t *group_ptr
         return fail(HETA_ERR_OOM, "heta_unique_relabel_batch: host allocation failed");
     } catch (...) {
         return fail(HETA_ERR_DEVICE, "heta_unique_relabel_batch: unexpected exception");
+    }
+}
+
+static heta_status heta_sample_hop_impl(const heta_graph *g, int32_t n, const int32_t *rels, const int64_t *const *dst_ids, const int64_t *n_dst,
+                                        int32_t fanout, const uint64_t *seeds, int64_t *const *rowptr, int64_t *const *src_ids,
+                                        int32_t *const *local, int64_t *n_sampled, int64_t *const *unique_ids, int64_t *n_unique, void *hip_stream)
+{
+    if (!g || n < 0 || (n > 0 && (!rels || !dst_ids || !n_dst || !seeds || !rowptr || !src_ids || !local || !n_sampled || !unique_ids || !n_unique)))
+        return fail(HETA_ERR_INVALID_ARG, "heta_sample_hop: null argument");
+    if (fanout < 1 || fanout > kMaxFanout) return fail(HETA_ERR_SHAPE, "heta_sample_hop: need 1 <= fanout <= %d", kMaxFanout);
+    const int32_t n_types = static_cast<int32_t>(g->ntypes.size());
+    std::vector<int64_t> cap(n_types, 0); // sampled edges per source type, at most
+    int64_t all_dst = 0, cap_max = 0;
+    for (int32_t i = 0; i < n; ++i) {
+        if (rels[i] < 0 || rels[i] >= (int32_t)g->rels.size()) return fail(HETA_ERR_INVALID_ARG, "heta_sample_hop: relation %d out of range", rels[i]);
+        if (n_dst[i] < 0) return fail(HETA_ERR_SHAPE, "heta_sample_hop: need n_dst >= 0");
+        if (!rowptr[i] || (n_dst[i] > 0 && (!dst_ids[i] || !src_ids[i] || !local[i]))) return fail(HETA_ERR_INVALID_ARG, "heta_sample_hop: null argument");
+        if (n_dst[i] >= (int64_t(1) << 31)) return fail(HETA_ERR_UNSUPPORTED, "heta_sample_hop: more than 2^31 destinations");
+        all_dst += n_dst[i];
+        cap[g->rels[rels[i]].src_type] += n_dst[i] * fanout;
+        cap_max = std::max(cap_max, n_dst[i] * fanout);
+    }
+    if (n == 0) return HETA_OK;
+    int64_t tiles = 0;
+    for (int32_t t = 0; t < n_types; ++t) {
+        if (cap[t] > 0 && !unique_ids[t]) return fail(HETA_ERR_INVALID_ARG, "heta_sample_hop: null unique_ids");
+        if (cap[t] > 0) tiles += std::max<int64_t>(1, (g->ntypes[t].num_nodes + kBitTile - 1) / kBitTile);
+        n_unique[t] = 0;
+    }
+    for (int32_t i = 0; i < n; ++i) n_sampled[i] = 0;
+    heta_status e;
+    if (n > kFusedItems || n_types > kFusedItems || tiles > kBitTilesMax || all_dst >= (int64_t(1) << 31) / kMaxFanout) {
+        // as the two calls that this one stands for
+        if ((e = heta_sample_neighbors_batch(g, n, rels, dst_ids, n_dst, fanout, seeds, rowptr, src_ids, n_sampled, hip_stream)) != HETA_OK) return e;
+        std::vector<int32_t> first(1, 0);
+        std::vector<const int64_t *> lists;
+        std::vector<int64_t> lens, limit;
+        std::vector<int32_t *> loc;
+        for (int32_t t = 0; t < n_types; ++t) {
+            for (int32_t i = 0; i < n; ++i)
+                if (g->rels[rels[i]].src_type == t) {
+                    lists.push_back(src_ids[i]);
+                    lens.push_back(n_sampled[i]);
+                    loc.push_back(local[i]);
+                }
+            first.push_back(static_cast<int32_t>(lists.size()));
+            limit.push_back(g->ntypes[t].num_nodes);
+        }
+        return heta_unique_relabel_batch_impl(n_types, first.data(), lists.data(), lens.data(), limit.data(), unique_ids, n_unique, loc.data(), hip_stream);
+    }
+    hipStream_t st = as_stream(hip_stream);
+    FusedSample f{};
+    sample_plan(f, g, n, rels, dst_ids, n_dst, fanout, seeds, rowptr, src_ids);
+    const size_t words = static_cast<size_t>(tiles) * 256;
+    Scratch scratch;
+    if ((e = scratch.alloc(sample_scratch_bytes(f.chunk0[n]) + Scratch::padded(words * 8) + Scratch::padded(words * 4) +
+                           Scratch::padded(static_cast<size_t>(tiles) * 4))) != HETA_OK ||
+        (e = slots_reserve(kBackSlots + static_cast<size_t>(n_types))) != HETA_OK)
+        return e;
+    unsigned long long *bits = scratch.take<unsigned long long>(words);
+    uint32_t *word_rank = scratch.take<uint32_t>(words), *tile_count = scratch.take<uint32_t>(static_cast<size_t>(tiles));
+    SampleBack *back = reinterpret_cast<SampleBack *>(t_slots.p);
+    int64_t *h_counts = reinterpret_cast<int64_t *>(t_slots.p + kBackSlots);
+    int *h_bad = reinterpret_cast<int *>(h_counts + n_types); // the ids are the graph's own, in range
+    BitSets b{};
+    b.n_sets = n_types;
+    tiles = 0;
+    for (int32_t t = 0; t < n_types; ++t) {
+        h_bad[t] = 0;
+        b.tile0[t] = static_cast<int32_t>(tiles);
+        if (cap[t] > 0) tiles += std::max<int64_t>(1, (g->ntypes[t].num_nodes + kBitTile - 1) / kBitTile);
+        b.limit[t] = g->ntypes[t].num_nodes;
+        b.uniq[t] = unique_ids[t];
+    }
+    b.tile0[n_types] = static_cast<int32_t>(tiles);
+    for (int32_t i = 0; i < n; ++i) {
+        b.ids[i] = src_ids[i];
+        b.local[i] = local[i];
+        b.len_at[i] = rowptr[i] + n_dst[i];
+        b.set_of[i] = static_cast<uint8_t>(g->rels[rels[i]].src_type);
+    }
+    if ((e = sample_launch(f, scratch, back, reinterpret_cast<uint4 *>(bits), static_cast<int64_t>(words / 2), st)) != HETA_OK) return e;
+    if ((e = bits_launch(b, n, cap_max, bits, word_rank, tile_count, h_counts, h_bad, st)) != HETA_OK) return e;
+    HETA_HIP(hipStreamSynchronize(st));
+    scratch.idle = true;
+    if ((e = sample_results(g, back, n, rels, n_sampled)) != HETA_OK) return e;
+    for (int32_t t = 0; t < n_types; ++t) n_unique[t] = cap[t] > 0 ? h_counts[t] : 0;
+    return HETA_OK;
+}
+
+heta_status heta_sample_hop(const heta_graph *g, int32_t n, const int32_t *rels, const int64_t *const *dst_ids, const int64_t *n_dst, int32_t fanout,
+                            const uint64_t *seeds, int64_t *const *rowptr, int64_t *const *src_ids, int32_t *const *local, int64_t *n_sampled,
+                            int64_t *const *unique_ids, int64_t *n_unique, void *hip_stream)
+{
+    try {
+        return heta_sample_hop_impl(g, n, rels, dst_ids, n_dst, fanout, seeds, rowptr, src_ids, local, n_sampled, unique_ids, n_unique, hip_stream);
+    } catch (const std::bad_alloc &) {
+        return fail(HETA_ERR_OOM, "heta_sample_hop: host allocation failed");
+    } catch (...) {
+        return fail(HETA_ERR_DEVICE, "heta_sample_hop: unexpected exception");
     }
 }
 

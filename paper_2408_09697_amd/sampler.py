@@ -1,8 +1,7 @@
 """Sequencing of the device sampler for a k-hop mini-batch (Section 2.2 and the sampling step of
-Algorithm 1 of the paper): hop by hop from the seeds outwards, per relation a call of
-`heta_sample_neighbors` on the current frontier of its destination type, then per source type one
-`heta_unique_relabel` over the relations leaving it (each hop issues them as one batched call of each
-kind, synchronising twice); the handles of all hops' blocks are then built by one `heta_graph_create_batch` on
+Algorithm 1 of the paper): hop by hop from the seeds outwards, per relation the sampling of the current
+frontier of its destination type, then per source type the unique ids of the relations leaving it and the
+edges' positions among them (a hop is one `heta_sample_hop`, which synchronises once); the handles of all hops' blocks are then built by one `heta_graph_create_batch` on
 the hops' device arrays.  No arithmetic here beyond the seed given to each (hop, relation) pair.
 """
 from __future__ import annotations
@@ -44,20 +43,9 @@ def sample_blocks(base: hb.Graph, seed_type: int, seeds: torch.Tensor, fanouts: 
     parts = []
     for hop, fanout in enumerate(reversed(list(fanouts))):
         n_rels = len(base.rels)
-        sampled = hb.heta_sample_neighbors_batch(
+        rowptrs, cols, src_ids = hb.heta_sample_hop(
             base, list(range(n_rels)), [frontier[t] if frontier[t] is not None else empty for _, t, _ in base.rels], fanout,
             [relation_seed(seed, hop, i) for i in range(n_rels)], stream=stream)
-        rowptrs = [rp for rp, _ in sampled]
-        srcs = [src for _, src in sampled]
-        by_type = [[i for i, r in enumerate(base.rels) if r[0] == s] for s in range(T)]
-        relabelled = hb.heta_unique_relabel_batch([[srcs[i] for i in rs] for rs in by_type],
-                                                  [base.ntypes[s][0] for s in range(T)], stream=stream)
-        src_ids: List[torch.Tensor] = []
-        cols: List[Optional[torch.Tensor]] = [None] * n_rels
-        for rs, (uniq, local) in zip(by_type, relabelled):
-            src_ids.append(uniq)
-            for i, l in zip(rs, local):
-                cols[i] = l
         nts = [(int(src_ids[k].numel()), base.ntypes[k][1], base.ntypes[k][2]) for k in range(T)]
         nts += [(0 if frontier[k] is None else int(frontier[k].numel()), base.ntypes[k][1], base.ntypes[k][2]) for k in range(T)]
         rels = [(s, T + t, rowptrs[i], cols[i]) for i, (s, t, _) in enumerate(base.rels)]

@@ -269,3 +269,45 @@ def test_batches_beyond_the_fused_limits_take_the_per_item_path():
         ref_u, ref_l = osampler.unique_relabel([x])
         assert np.array_equal(uniq.cpu().numpy(), ref_u) and np.array_equal(local[0].cpu().numpy(), ref_l[0])
     hg.destroy()
+
+
+@pytest.mark.parametrize("n_types,rels,n_nodes,n_dst,fanout", [
+    (3, [(0, 1), (1, 0), (2, 0), (0, 2), (2, 2)], [3000, 2500, 40], [700, 255, 16], 5),      # a hop of a small graph
+    (2, [(0, 1), (1, 1), (0, 0)], [5_000_000, 70_000], [1, 257], 64),                            # more than 256 tiles of ids: counted in a launch
+    (2, [(0, 1), (1, 0)], [1_100_000, 1_100_000], [1_050_000, 0], 2),                            # more than 4,096 chunks of destinations; an item without any
+    (1, [(0, 0)] * 33, [900], [300], 3),                                                          # more items than one launch takes
+    (2, [(0, 1)], [70_000_000, 50], [0, 50], 7)])                                                # id ranges past the bitmap
+def test_sample_hop_equals_its_two_calls(n_types, rels, n_nodes, n_dst, fanout):
+    """A hop in one call against the batched sampling and the batched unique / relabel, bit for bit, and against the oracle
+    where it is quick; out-of-range destinations are refused alike."""
+    g = rng.stream("tests", f"hop/{n_types}/{len(rels)}/{n_nodes[0]}")
+    made = []
+    for s, t in rels:
+        deg = np.minimum(g.zipf(1.6, size=n_nodes[t]), 300) * (g.random(n_nodes[t]) < 0.7)
+        rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+        made.append((s, t, rowptr, g.integers(0, n_nodes[s], size=int(rowptr[-1]), dtype=np.int32)))
+    hg = heta.heta_graph_create([(n, 4, 0) for n in n_nodes], made)
+    fr = [np.sort(g.choice(n_nodes[t], size=n_dst[t], replace=False)).astype(np.int64) for t in range(n_types)]
+    dst = [torch.from_numpy(fr[t]).cuda() for _, t in rels]
+    seeds = [77 + 13 * i for i in range(len(rels))]
+    sampled = heta.heta_sample_neighbors_batch(hg, list(range(len(rels))), dst, fanout, seeds)
+    by_type = [[i for i, (s, _) in enumerate(rels) if s == k] for k in range(n_types)]
+    relabelled = heta.heta_unique_relabel_batch([[sampled[i][1] for i in rs] for rs in by_type], n_nodes)
+    for _ in range(2):
+        rowptr, local, uniq = heta.heta_sample_hop(hg, list(range(len(rels))), dst, fanout, seeds)
+        for k, rs in enumerate(by_type):
+            assert torch.equal(uniq[k], relabelled[k][0])
+            for i, l in zip(rs, relabelled[k][1]):
+                assert torch.equal(rowptr[i], sampled[i][0]) and torch.equal(local[i], l)
+    if sum(n_dst) < 2000:
+        for i, (_, t, ptr, col) in enumerate(made):
+            ref_ptr, ref_src = osampler.sample_neighbors(ptr, col, fr[t], fanout, seeds[i])
+            assert np.array_equal(rowptr[i].cpu().numpy(), ref_ptr)
+            assert np.array_equal(uniq[rels[i][0]].cpu().numpy()[local[i].cpu().numpy()], ref_src)
+    bad = [d.clone() for d in dst]
+    k = max(range(len(rels)), key=lambda i: bad[i].numel())
+    bad[k][-1] = n_nodes[rels[k][1]]
+    with pytest.raises(heta.HetaError) as e:
+        heta.heta_sample_hop(hg, list(range(len(rels))), bad, fanout, seeds)
+    assert e.value.status == heta.HETA_ERR_INVALID_ARG
+    hg.destroy()
