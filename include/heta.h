@@ -269,6 +269,24 @@ heta_status heta_project_wgrad_batch(heta_graph *g, int64_t n_rows, int32_t n, c
                                      const int64_t *ld_in, const int32_t *d_in, const float *const *gouts,
                                      const int64_t *ld_go, int32_t d_out, float *const *dW, const int64_t *ld_dw,
                                      float beta, int32_t gout_two_terms, void *hip_stream);
+/* The products of several node types of a layer in one call: item i takes n_rows[i] rows and the products first[i] ..
+ * first[i+1]-1 (1..8 of them; first: n + 1 entries from 0) of ins / ld_in / depth / Ws / ld_w / width, product s being
+ * ins[s] [n_rows, depth[s]] . (Ws[s] [depth, width], or Ws[s] [width, depth] transposed).
+ * heta_project_multi, sum = 0: outs[s] = product s (products of one item share their depth); sum = 1: outs[i] = act_i(beta_i
+ *   outs[i] + the sum of item i's products) (which share their width).  acts, betas: per item, or NULL for none and 0; a
+ *   bf16 output takes neither.
+ * heta_project_wgrad_multi: dW[s] = ins[s]^T . gouts[s] (d_in[s] x d_out[i]) over n_rows[i] rows; workspace and
+ *   gout_two_terms as in heta_cross_rel_project_wgrad.
+ * Items that a launch of their own would leave part of the chip idle share one: they run concurrently, so no two outputs may
+ * overlap (checked).  g: handle whose packing buffer (and workspace) the call uses.  All arrays are HOST arrays; shapes,
+ * dtypes and errors as in the calls above, detected before anything is launched.  n = 0 is a no-op. */
+heta_status heta_project_multi(heta_graph *g, int32_t n, const int32_t *first, const int64_t *n_rows, int32_t sum, const void *const *ins,
+                               heta_dtype in_dt, const int64_t *ld_in, const int32_t *depth, const void *const *Ws, heta_dtype w_dt,
+                               const int64_t *ld_w, const int32_t *width, int32_t transW, void *const *outs, heta_dtype out_dt,
+                               const int64_t *ld_out, const heta_act *acts, const float *betas, void *hip_stream);
+heta_status heta_project_wgrad_multi(heta_graph *g, int32_t n, const int32_t *first, const int64_t *n_rows, const void *const *ins,
+                                     heta_dtype in_dt, const int64_t *ld_in, const int32_t *d_in, const float *const *gouts, const int64_t *ld_go,
+                                     const int32_t *d_out, float *const *dW, const int64_t *ld_dw, int32_t gout_two_terms, void *hip_stream);
 
 /* ---- projection of all relations into one destination type, fused with the cross-relation sum --
  * (Eq. 1, both lines in one pass; Algorithm 1, relation-specific aggregation followed by AGG_all.)
@@ -334,6 +352,9 @@ heta_status heta_cross_rel_reduce(const heta_graph *g, int32_t dst_type, const f
 heta_status heta_act_bwd(int64_t n_rows, int32_t d, heta_act act, const float *h, int64_t ld_h,
                          const float *grad_out, int64_t ld_go, float *grad_in, int64_t ld_gi,
                          void *hip_stream);
+/* The same for n gradients in one launch (up to 16); HOST arrays of n entries, h and ld_h may be NULL without an activation. */
+heta_status heta_act_bwd_multi(int32_t n, const int64_t *n_rows, const int32_t *d, heta_act act, const float *const *h, const int64_t *ld_h,
+                               const float *const *grad_out, const int64_t *ld_go, float *const *grad_in, const int64_t *ld_gi, void *hip_stream);
 
 /* ---- graph attention as the relation-specific aggregation (Section 2.1: R-GAT applies GAT for
  * AGG_r, sums the relations' outputs and activates the sum with ReLU; the paper prints no formula for

@@ -31,7 +31,7 @@ EXPORTS = ["heta_graph_create", "heta_graph_create_batch", "heta_graph_destroy",
            "heta_act_bwd", "heta_sparse_adam_multi", "heta_last_error", "heta_version", "heta_profile_enable", "heta_profile_reset",
            "heta_profile_read", "heta_calibration_copy", "heta_calibration_mfma", "heta_cross_rel_project", "heta_cross_rel_project_bwd",
            "heta_cross_rel_project_wgrad", "heta_sparse_adam", "heta_project_batch",
-           "heta_project_sum", "heta_project_wgrad_batch", "heta_attn_score", "heta_attn_score_bwd", "heta_attn_score_multi", "heta_attn_score_bwd_multi",
+           "heta_project_sum", "heta_project_wgrad_batch", "heta_project_multi", "heta_project_wgrad_multi", "heta_act_bwd_multi", "heta_attn_score", "heta_attn_score_bwd", "heta_attn_score_multi", "heta_attn_score_bwd_multi",
            "heta_rel_attn_fwd", "heta_rel_attn_bwd", "heta_rel_attn_fwd_train", "heta_rel_attn_fwd_train_multi", "heta_rel_attn_bwd_src_multi", "heta_attn_bwd_dst", "heta_rel_attn_bwd_src",
            "heta_sample_neighbors", "heta_unique_relabel",
            "heta_cross_rel_aggregate_project", "heta_meta_partition", "heta_sample_neighbors_batch",
@@ -583,6 +583,79 @@ def heta_project_wgrad_batch(g: Graph, ins: List[torch.Tensor], gouts: List[torc
     return dW
 
 
+def heta_project_multi(g: Graph, items: Sequence[Sequence], trans_w: bool = False, sum: bool = False, stream=None) -> None:
+    """The products of several node types in one call.  items: (n_rows, ins, Ws, outs[, act, beta]); sum: outs is the one
+    output act(beta*outs + sum_p ins[p] @ W_p), else outs[p] = ins[p] @ W_p, W_p = Ws[p]^T if trans_w else Ws[p]."""
+    by_dtype: dict = {}  # items of other element types go in a call of their own
+    for it in items:
+        if it[1]:
+            by_dtype.setdefault((it[1][0].dtype, it[2][0].dtype, (it[3] if sum else it[3][0]).dtype), []).append(it)
+    if len(by_dtype) != 1:
+        for part in by_dtype.values():
+            heta_project_multi(g, part, trans_w, sum, stream)
+        return
+    (dtypes, items), = by_dtype.items()
+    first, rows, outs, acts, betas, x_all, w_all = [0], [], [], [], [], [], []
+    for it in items:
+        n_rows, ins, Ws, out = it[:4]
+        mine = [out] if sum else out
+        if len(ins) != len(Ws) or (not sum and len(ins) != len(mine)):
+            raise HetaError(HETA_ERR_SHAPE, "bad arguments")
+        for x, w, o in zip(ins, Ws, mine * len(ins) if sum else mine):
+            k, n = (w.shape[1], w.shape[0]) if trans_w else w.shape
+            if k != x.shape[1] or x.shape[0] < n_rows or o.shape[0] < n_rows or o.shape[1] < n or (x.dtype, w.dtype, o.dtype) != dtypes:
+                raise HetaError(HETA_ERR_SHAPE, "inputs / weights / outputs do not match")
+        x_all += ins
+        w_all += Ws
+        outs += mine
+        rows.append(n_rows)
+        acts.append(it[4] if len(it) > 4 else HETA_ACT_NONE)
+        betas.append(it[5] if len(it) > 5 else 0.0)
+        first.append(len(x_all))
+    in_dt, w_dt, out_dt = dtypes
+    vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
+    L = load_library()
+    L.heta_project_multi.argtypes = [vp, i32, vp, vp, i32, vp, i32, vp, vp, vp, i32, vp, vp, i32, vp, i32, vp, vp, vp, vp]
+    _check(L.heta_project_multi(g.handle, len(items), _i32_array(first), _i64_array(rows), int(sum), _ptr_array(x_all, "in", in_dt), _dt(x_all[0]),
+                                _i64_array([_ld(x) for x in x_all]), _i32_array([x.shape[1] for x in x_all]), _ptr_array(w_all, "W", w_dt), _dt(w_all[0]),
+                                _i64_array([w.stride(0) for w in w_all]), _i32_array([w.shape[0 if trans_w else 1] for w in w_all]), int(trans_w),
+                                _ptr_array(outs, "out", out_dt), _dt(outs[0]), _i64_array([_ld(o) for o in outs]),
+                                _i32_array(acts) if sum else None, (ctypes.c_float * len(betas))(*betas) if sum else None, _stream(stream)))
+
+
+def heta_project_wgrad_multi(g: Graph, items: Sequence[Sequence], gout_two_terms: bool = False, stream=None) -> None:
+    """Weight gradients of several node types in one call.  items: (n_rows, ins, gouts, dW): dW[p] = ins[p]^T @ gouts[p]."""
+    by_dtype: dict = {}
+    for it in items:
+        if it[1]:
+            by_dtype.setdefault(it[1][0].dtype, []).append(it)
+    if len(by_dtype) != 1:
+        for part in by_dtype.values():
+            heta_project_wgrad_multi(g, part, gout_two_terms, stream)
+        return
+    (dtype, items), = by_dtype.items()
+    first, x_all, g_all, w_all = [0], [], [], []
+    for n_rows, ins, gouts, dW in items:
+        if len(ins) != len(gouts) or len(ins) != len(dW):
+            raise HetaError(HETA_ERR_SHAPE, "bad arguments")
+        d_out = gouts[0].shape[1]
+        for x, go, w in zip(ins, gouts, dW):
+            if x.shape[0] < n_rows or go.shape[0] < n_rows or go.shape[1] != d_out or w.shape[0] < x.shape[1] or w.shape[1] < d_out or x.dtype != dtype:
+                raise HetaError(HETA_ERR_SHAPE, "inputs / gradients do not match")
+        x_all += ins
+        g_all += gouts
+        w_all += dW
+        first.append(len(x_all))
+    vp, i32 = ctypes.c_void_p, ctypes.c_int32
+    L = load_library()
+    L.heta_project_wgrad_multi.argtypes = [vp, i32, vp, vp, vp, i32, vp, vp, vp, vp, vp, vp, vp, i32, vp]
+    _check(L.heta_project_wgrad_multi(g.handle, len(items), _i32_array(first), _i64_array([it[0] for it in items]), _ptr_array(x_all, "in", x_all[0].dtype),
+                                      _dt(x_all[0]), _i64_array([_ld(x) for x in x_all]), _i32_array([x.shape[1] for x in x_all]),
+                                      _ptr_array(g_all, "gout", torch.float32), _i64_array([_ld(x) for x in g_all]),
+                                      _i32_array([it[2][0].shape[1] for it in items]), _ptr_array(w_all, "dW", torch.float32),
+                                      _i64_array([_ld(w) for w in w_all]), int(gout_two_terms), _stream(stream)))
+
+
 def heta_cross_rel_project_bwd(g: Graph, dst_type: int, gout: torch.Tensor, Ws: List[torch.Tensor],
                                dM: List[torch.Tensor], stream=None) -> List[torch.Tensor]:
     """dM[p] = gout @ Ws[p]^T for every relation p into dst_type, one launch."""
@@ -654,6 +727,23 @@ def heta_act_bwd(act: int, h: Optional[torch.Tensor], grad_out: torch.Tensor, gr
                                        _dev(grad_out, "grad_out", torch.float32), _ld(grad_out),
                                        _dev(grad_in, "grad_in", torch.float32), _ld(grad_in), _stream(stream)))
     return grad_in
+
+
+def heta_act_bwd_multi(act: int, hs: Sequence[torch.Tensor], grads_out: Sequence[torch.Tensor], grads_in: Sequence[torch.Tensor], stream=None) -> None:
+    """heta_act_bwd for several gradients (one launch for up to 16)."""
+    n = len(grads_out)
+    if n == 0:
+        return
+    for h, go, gi in zip(hs, grads_out, grads_in):
+        if gi.shape[0] < go.shape[0] or gi.shape[1] < go.shape[1] or h.shape[0] < go.shape[0] or h.shape[1] < go.shape[1]:
+            raise HetaError(HETA_ERR_SHAPE, "buffers too small")
+    vp, i32 = ctypes.c_void_p, ctypes.c_int32
+    L = load_library()
+    L.heta_act_bwd_multi.argtypes = [i32, vp, vp, i32, vp, vp, vp, vp, vp, vp, vp]
+    _check(L.heta_act_bwd_multi(n, _i64_array([x.shape[0] for x in grads_out]), _i32_array([x.shape[1] for x in grads_out]), act,
+                                _ptr_array(hs, "h", torch.float32), _i64_array([_ld(x) for x in hs]), _ptr_array(grads_out, "grad_out", torch.float32),
+                                _i64_array([_ld(x) for x in grads_out]), _ptr_array(grads_in, "grad_in", torch.float32),
+                                _i64_array([_ld(x) for x in grads_in]), _stream(stream)))
 
 
 class _KernelStat(ctypes.Structure):

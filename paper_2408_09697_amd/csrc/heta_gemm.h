@@ -14,7 +14,9 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 constexpr int BM = 128;
 // BK, the k-values per tile, is a template parameter: 32, or 64 for the bf16 weight gradient,
 // whose long k loop is bound by per-tile overhead rather than by MFMA work.
-constexpr int kMaxSeg = 8;
+constexpr int kMaxSeg = 8;        // segments of a call
+constexpr int kMaxLaunchSeg = 16; // segments of a launch: several calls of one shape class can share it
+constexpr int kMaxCalls = 8;
 
 struct GemmSeg {
     const void *A;
@@ -29,10 +31,24 @@ struct GemmSeg {
     int32_t ko, n_pad;  // k-octets (K rounded up to 16, over 8) and columns (N rounded up to 128) of B3
 };
 
+// One of the calls that share a launch of the direct kernel: segments [first, first + n_seg).
+struct GemmCall {
+    int32_t first, n_seg;
+    int32_t mt, nt;      // tile counts (maximum over the segments in batch mode)
+    int32_t outer0;      // row blocks (weight gradients: splits) of the calls before it
+    int32_t n_split, k_per_split; // multiple of BK
+    int relu;
+    float beta;
+    const float *row_scale;
+};
+
 struct GemmParams {
-    GemmSeg seg[kMaxSeg];
+    GemmSeg seg[kMaxLaunchSeg];
     int n_seg;
-    int batch;           // 0: C_0 (+)= sum_s A_s B_s ; 1: C_s (+)= A_s B_s for every s
+    int n_call;          // 0: one call, described by the fields below; else by call[]
+    int32_t inner, n_outer; // workgroups per row block or split (the largest call's), row blocks or splits of all calls
+    GemmCall call[kMaxCalls];
+    int batch;           // 0: C_0 (+)= sum_s A_s B_s ; 1: C_s (+)= A_s B_s for every s (s over a call's segments)
     const float *row_scale;
     float beta;
     int relu;
@@ -262,6 +278,8 @@ heta_status pack_split3_weights(GemmParams &p, int trans, void *out, hipStream_t
 // whether an fp32 product is small enough to split both operands in its kernel instead of packing one beforehand
 bool f32_product_unpacked(const GemmParams &p);
 int wgrad_tile_rows(const GemmParams &p);
+// whether the direct pipeline takes the launch (alignment, extents)
+bool gemm_direct_takes(const GemmParams &p, heta_dtype a_dt, heta_dtype b_dt);
 heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, bool a_rc, bool b_rc, hipStream_t st,
                                const char *name, double bytes, double flops, bool *handled);
 

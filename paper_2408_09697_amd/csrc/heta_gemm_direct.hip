@@ -441,10 +441,10 @@ __device__ __forceinline__ void x3_step_2x2_presplit(const float *At, const char
 // operand; with `both`, that of -B behind it.  A launch of its own takes 4.5 us however small the matrix; one per operand
 // was 5 % of a layer of 2 M edges.
 struct Split3Segs {
-    const float *W[kMaxSeg];
-    uint4 *out[kMaxSeg];
-    int64_t ldw[kMaxSeg];
-    int K[kMaxSeg], N[kMaxSeg], ko[kMaxSeg], n_pad[kMaxSeg];
+    const float *W[kMaxLaunchSeg];
+    uint4 *out[kMaxLaunchSeg];
+    int64_t ldw[kMaxLaunchSeg];
+    int K[kMaxLaunchSeg], N[kMaxLaunchSeg], ko[kMaxLaunchSeg], n_pad[kMaxLaunchSeg];
     int both;
 };
 __global__ void __launch_bounds__(256) pack_split3_kernel(Split3Segs q, int trans)
@@ -507,7 +507,7 @@ template <int BK> struct TileSeq {
 
 // ---- epilogue ---------------------------------------------------------------------------------------
 template <int MI, int NJ>
-__device__ __forceinline__ void store_tile(const GemmParams &p, const GemmSeg &out_seg, float *strips, floatx16 (&acc)[MI][NJ],
+__device__ __forceinline__ void store_tile(const GemmParams &p, const GemmCall &call, const GemmSeg &out_seg, float *strips, floatx16 (&acc)[MI][NJ],
                                            int wave, int lane, int wm, int wn, int64_t m0, int64_t n0, int rows_a, int rows_b,
                                            int64_t split)
 {
@@ -526,7 +526,7 @@ __device__ __forceinline__ void store_tile(const GemmParams &p, const GemmSeg &o
     float *Cp = out_seg.C + (p.partial ? split * out_seg.M * out_seg.ldc : 0);
     bf16_t *Hp = reinterpret_cast<bf16_t *>(out_seg.C);
     const bool direct = !p.partial;
-    const bool fused = direct && (p.row_scale || p.beta != 0.f || p.relu);
+    const bool fused = direct && (call.row_scale || call.beta != 0.f || call.relu);
     // 16-byte pieces (4 fp32 or 8 bf16 columns) need rows that keep that alignment
     const bool vec_out = p.out_bf16 ? ((out_seg.ldc & 7) == 0 && (reinterpret_cast<uintptr_t>(Hp) & 15u) == 0)
                                     : ((out_seg.ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(Cp) & 15u) == 0);
@@ -573,9 +573,9 @@ __device__ __forceinline__ void store_tile(const GemmParams &p, const GemmSeg &o
                 float *o = Cp + off;
                 const bool whole = vec_out && nl + 4 <= rows_b;
                 if (fused) {
-                    const float sc = p.row_scale ? p.row_scale[m0 + ml] : 1.f;
+                    const float sc = call.row_scale ? call.row_scale[m0 + ml] : 1.f;
                     float old[4] = {0.f, 0.f, 0.f, 0.f};
-                    if (p.beta != 0.f) {
+                    if (call.beta != 0.f) {
                         if (whole) {
                             const float4 o4 = *reinterpret_cast<const float4 *>(o);
                             old[0] = o4.x; old[1] = o4.y; old[2] = o4.z; old[3] = o4.w;
@@ -588,8 +588,8 @@ __device__ __forceinline__ void store_tile(const GemmParams &p, const GemmSeg &o
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         float x = v[e] * sc;
-                        if (p.beta != 0.f) x += p.beta * old[e];
-                        if (p.relu) x = fmaxf(x, 0.f);
+                        if (call.beta != 0.f) x += call.beta * old[e];
+                        if (call.relu) x = fmaxf(x, 0.f);
                         v[e] = x;
                     }
                 }
@@ -661,16 +661,19 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
     // segments of a row block (inner), one row block per outer step; for a split contraction
     // (weight gradient) every tile and segment of one split (they share that split's rows of both
     // operands), one split per outer step.
-    const int n_batch = p.batch ? p.n_seg : 1;
-    const int64_t inner = p.nt * n_batch * (p.partial ? p.mt : 1);
-    const int64_t n_outer = p.partial ? p.n_split : p.mt;
-    const int64_t xcd = blockIdx.x % 8, j = blockIdx.x / 8;
-    const int64_t in_idx = j % inner, outer = (j / inner) * 8 + xcd;
-    if (outer >= n_outer) return;
-    const int s0 = p.batch ? static_cast<int>(in_idx % n_batch) : 0;
-    const int64_t rest = in_idx / n_batch;
-    const int64_t n0 = (rest % p.nt) * BN;
-    const int64_t m0 = (p.partial ? rest / p.nt : outer) * BM;
+    // The calls of a launch follow one another in the outer index.
+    const uint32_t xcd = blockIdx.x % 8, j = blockIdx.x / 8;
+    const int in_idx = static_cast<int>(j % static_cast<uint32_t>(p.inner)), outer_all = static_cast<int>(j / static_cast<uint32_t>(p.inner) * 8 + xcd);
+    if (outer_all >= p.n_outer) return;
+    int c = 0;
+    while (c + 1 < p.n_call && outer_all >= p.call[c + 1].outer0) ++c;
+    const GemmCall &call = p.call[c];
+    const int outer = outer_all - call.outer0, n_batch = p.batch ? call.n_seg : 1;
+    if (in_idx >= call.nt * n_batch * (p.partial ? call.mt : 1)) return; // a call of fewer tiles per row block
+    const int s0 = call.first + (p.batch ? in_idx % n_batch : 0);
+    const int rest = in_idx / n_batch;
+    const int64_t n0 = static_cast<int64_t>(rest % call.nt) * BN;
+    const int64_t m0 = static_cast<int64_t>(p.partial ? rest / call.nt : outer) * BM;
     const int64_t split = p.partial ? outer : 0;
     const bool negated = (X3_FLIP || (W3 && p.both_signs)) && (outer & 1); // uniform
     const uint32_t flip = negated ? 0x80000000u : 0u;
@@ -693,8 +696,7 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
     SB sb;
 
     // issue side (direct loads, ST-1 tiles ahead), staged side (one tile ahead), consume side
-    TileSeq<BK> I{s0, p.batch ? s0 + 1 : p.n_seg, 0, 0, static_cast<int>(split * p.k_per_split),
-                  static_cast<int>(min(p.k_per_split, static_cast<int64_t>(0x7fffffff)))};
+    TileSeq<BK> I{s0, p.batch ? s0 + 1 : call.first + call.n_seg, 0, 0, static_cast<int>(split) * call.k_per_split, call.k_per_split};
     TileSeq<BK> L = I, C = I;
     auto init_direct = [&]() {
         const GemmSeg &g = p.seg[I.s];
@@ -910,7 +912,7 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
                 for (int v = 0; v < 16; ++v) acc[i][jj][v] = 0.f - acc[i][jj][v]; // zero stays +0
     }
     static_assert(A_BYTES + B_BYTES >= NW * 8 * (32 * NJ + 4) * 4, "the epilogue strips overlay the ring");
-    store_tile<MI, NJ>(p, out_seg, reinterpret_cast<float *>(ring), acc, wave, lane, wm, wn, m0, n0, rows_a, rows_b, split);
+    store_tile<MI, NJ>(p, call, out_seg, reinterpret_cast<float *>(ring), acc, wave, lane, wm, wn, m0, n0, rows_a, rows_b, split);
 }
 
 // ---- host side -------------------------------------------------------------------------------------
@@ -920,18 +922,27 @@ template <typename CT, typename SA_T, bool A_RC, bool A_DIRECT, typename SB_T, b
 static heta_status launch_direct(GemmParams &p, hipStream_t st, const char *name, double bytes, double flops)
 {
     constexpr int BN = 32 * NJ * WN, BM = 32 * MI * WMW;
-    int64_t mt = 0, nt = 0;
-    for (int s = 0; s < p.n_seg; ++s) {
-        mt = std::max(mt, (p.seg[s].M + BM - 1) / BM);
-        nt = std::max(nt, (p.seg[s].N + BN - 1) / BN);
+    int64_t inner = 0, outer = 0;
+    for (int c = 0; c < p.n_call; ++c) {
+        GemmCall &call = p.call[c];
+        int64_t mt = 0, nt = 0;
+        for (int s = call.first; s < call.first + call.n_seg; ++s) {
+            mt = std::max(mt, (p.seg[s].M + BM - 1) / BM);
+            nt = std::max(nt, (p.seg[s].N + BN - 1) / BN);
+        }
+        inner = std::max(inner, nt * (p.batch ? call.n_seg : 1) * (p.partial ? mt : 1));
+        if (mt >= (int64_t(1) << 31) || nt >= (int64_t(1) << 31)) return fail(HETA_ERR_UNSUPPORTED, "projection: matrix too large for one launch");
+        call.mt = static_cast<int32_t>(mt);
+        call.nt = static_cast<int32_t>(nt);
+        call.outer0 = static_cast<int32_t>(std::min<int64_t>(outer, 0x7fffffff));
+        outer += p.partial ? std::max(1, call.n_split) : mt;
     }
-    p.mt = mt;
-    p.nt = nt;
-    const int64_t inner = nt * (p.batch ? p.n_seg : 1) * (p.partial ? mt : 1);
-    const int64_t outer = p.partial ? std::max(1, p.n_split) : mt;
     const int64_t blocks = (outer + 7) / 8 * 8 * inner;
     if (blocks <= 0) return HETA_OK;
-    if (blocks > max_blocks(64 * WMW * WN)) return fail(HETA_ERR_UNSUPPORTED, "projection: matrix too large for one launch");
+    if (inner >= (int64_t(1) << 31) || outer >= (int64_t(1) << 31) - 8 || blocks > max_blocks(64 * WMW * WN))
+        return fail(HETA_ERR_UNSUPPORTED, "projection: matrix too large for one launch");
+    p.inner = static_cast<int32_t>(inner);
+    p.n_outer = static_cast<int32_t>(outer);
     ProfScope prof(name, st, bytes, flops);
     hipLaunchKernelGGL((gemm_direct_kernel<CT, SA_T, A_RC, A_DIRECT, SB_T, B_RC, B_DIRECT, WN, BK, ST, OCC, B_SPLIT, MI, NJ, WMW, X3>),
                        dim3((unsigned)blocks), dim3(64 * WMW * WN), 0, st, p);
@@ -946,12 +957,18 @@ bool g_f32_native = false;
 static bool gemm_direct_small(const GemmParams &p)
 {
     if (p.partial) return false;
-    int64_t mt = 0, nt = 0;
-    for (int s = 0; s < p.n_seg; ++s) {
-        mt = std::max(mt, (p.seg[s].M + 127) / 128);
-        nt = std::max(nt, (p.seg[s].N + 127) / 128);
+    int64_t tiles = 0;
+    const int n_call = std::max(1, p.n_call);
+    for (int c = 0; c < n_call; ++c) {
+        const int first = p.n_call ? p.call[c].first : 0, n_seg = p.n_call ? p.call[c].n_seg : p.n_seg;
+        int64_t mt = 0, nt = 0;
+        for (int s = first; s < first + n_seg; ++s) {
+            mt = std::max(mt, (p.seg[s].M + 127) / 128);
+            nt = std::max(nt, (p.seg[s].N + 127) / 128);
+        }
+        tiles += mt * nt * (p.batch ? n_seg : 1);
     }
-    return mt * nt * (p.batch ? p.n_seg : 1) <= 96;
+    return tiles <= 96;
 }
 
 // fp32 products (forward, input gradient) of too little work for packed weights: 64 x 64 tiles that split both operands.
@@ -1013,25 +1030,35 @@ int wgrad_tile_rows(const GemmParams &p)
     return pad256 < pad320 ? 256 : 320;
 }
 
+bool gemm_direct_takes(const GemmParams &p, heta_dtype a_dt, heta_dtype b_dt)
+{
+    for (int s = 0; s < p.n_seg; ++s) {
+        const GemmSeg &g = p.seg[s];
+        // 16-byte rows on both operands; r-contiguous operands are read in whole chunks along r
+        if (!aligned16(g.A) || !aligned16(g.B)) return false;
+        const int64_t a_row = g.lda * (int64_t)dtype_size(a_dt), b_row = g.ldb * (int64_t)dtype_size(b_dt);
+        if (a_row % 16 || b_row % 16) return false;
+        if (g.M < 1 || g.N < 1 || g.K < 1) return false;
+        // per-lane offsets within a tile are 32-bit; k extents are walked in 32-bit arithmetic
+        if (a_row * 256 >= (int64_t(1) << 31) || b_row * 256 >= (int64_t(1) << 31) || g.K >= (int64_t(1) << 31) - 256) return false;
+    }
+    for (int c = 0; c < p.n_call; ++c)
+        if (p.call[c].n_split > 1 && static_cast<int64_t>(p.call[c].k_per_split) * p.call[c].n_split >= (int64_t(1) << 31) - 256) return false;
+    return p.n_call > 0 || !(p.n_split > 1 && p.k_per_split * p.n_split >= (int64_t(1) << 31) - 256);
+}
+
 heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, bool a_rc, bool b_rc, hipStream_t st,
                                const char *name, double bytes, double flops, bool *handled)
 {
     *handled = false;
     if (p.n_split < 1) p.n_split = 1;
-    int64_t n_max = 0;
-    for (int s = 0; s < p.n_seg; ++s) {
-        const GemmSeg &g = p.seg[s];
-        // 16-byte rows on both operands; r-contiguous operands are read in whole chunks along r
-        if (!aligned16(g.A) || !aligned16(g.B)) return HETA_OK;
-        const int64_t a_row = g.lda * (int64_t)dtype_size(a_dt), b_row = g.ldb * (int64_t)dtype_size(b_dt);
-        if (a_row % 16 || b_row % 16) return HETA_OK;
-        if (g.M < 1 || g.N < 1 || g.K < 1) return HETA_OK;
-        // per-lane offsets within a tile are 32-bit; k extents are walked in 32-bit arithmetic
-        if (a_row * 256 >= (int64_t(1) << 31) || b_row * 256 >= (int64_t(1) << 31) || g.K >= (int64_t(1) << 31) - 256)
-            return HETA_OK;
-        n_max = std::max(n_max, g.N);
+    if (!gemm_direct_takes(p, a_dt, b_dt)) return HETA_OK;
+    if (p.n_call == 0) {
+        p.n_call = 1;
+        p.call[0] = GemmCall{0, p.n_seg, 0, 0, 0, p.n_split, static_cast<int32_t>(std::min<int64_t>(p.k_per_split, 0x7fffffff)), p.relu, p.beta, p.row_scale};
     }
-    if (p.n_split > 1 && p.k_per_split * p.n_split >= (int64_t(1) << 31) - 256) return HETA_OK;
+    int64_t n_max = 0;
+    for (int s = 0; s < p.n_seg; ++s) n_max = std::max(n_max, p.seg[s].N);
     if (a_dt == HETA_BF16 && b_dt == HETA_F32 && a_rc && b_rc) {
         // The weight gradient with bf16 inputs: both operands lie with the graph rows (the contraction index)
         // outermost and stream into LDS as they are, 16 graph rows per stage, four stages; 128 x 128 output tiles
@@ -1071,14 +1098,17 @@ heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, 
         // A launch of at most one and a half 128 x 256 tiles per CU (the projections of a sampled mini-batch
         // block) runs as one uneven round of workgroups, each a serial chain of k-steps with nothing beside it
         // on its CU: 128 x 128 tiles put the same work on twice the workgroups, two or three to a CU.
-        int64_t mt = 0, nt = 0;
-        for (int s = 0; s < p.n_seg; ++s) {
-            mt = std::max(mt, (p.seg[s].M + BM - 1) / BM);
-            nt = std::max(nt, (p.seg[s].N + 255) / 256);
+        int64_t tiles = 0;
+        for (int c = 0; c < p.n_call; ++c) {
+            const GemmCall &call = p.call[c];
+            int64_t mt = 0, nt = 0;
+            for (int s = call.first; s < call.first + call.n_seg; ++s) {
+                mt = std::max(mt, (p.seg[s].M + BM - 1) / BM);
+                nt = std::max(nt, (p.seg[s].N + 255) / 256);
+            }
+            tiles += nt * (p.batch ? call.n_seg : 1) * mt * (p.partial ? std::max(1, call.n_split) : 1);
         }
-        const int64_t inner = nt * (p.batch ? p.n_seg : 1) * (p.partial ? mt : 1);
-        const int64_t outer = p.partial ? std::max(1, p.n_split) : mt;
-        if (outer * inner <= 384) wide = false;
+        if (tiles <= 384) wide = false;
     }
     // Fewer than a hundred 128 x 128 tiles (the projections of a sampled mini-batch block: a few thousand rows):
     // every tile is a serial chain of MFMAs on one CU while most CUs idle.  64 x 64 tiles (four wavefronts of one
@@ -1110,9 +1140,14 @@ heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, 
             return launch_direct<bf16_t, float, true, true, float, true, true, 1, 16, 3, 2, false, 2, 2, 2, 1>(p, st, name, bytes, flops);
         if (a_rc && b_rc) return launch_direct<bf16_t, float, true, true, float, true, true, 2, 16, 3, 3, false, 2, 2, 2, 1>(p, st, name, bytes, flops);
         int64_t tiles64 = 0;
-        for (int s = 0; s < p.n_seg; ++s) {
-            const int64_t tiles = ((p.seg[s].M + 63) / 64) * ((p.seg[s].N + 63) / 64);
-            tiles64 = p.batch ? tiles64 + tiles : std::max(tiles64, tiles);
+        for (int c = 0; c < p.n_call; ++c) {
+            const GemmCall &call = p.call[c];
+            int64_t most = 0;
+            for (int s = call.first; s < call.first + call.n_seg; ++s) {
+                const int64_t tiles = ((p.seg[s].M + 63) / 64) * ((p.seg[s].N + 63) / 64);
+                most = p.batch ? most + tiles : std::max(most, tiles);
+            }
+            tiles64 += most;
         }
         // 64 x 64 tiles: up to two per CU the launch is one chain of k-steps, and 32 k-values per barrier shorten it
         // (1,024 rows, K = 768, 256 columns 28.0 -> 24.3 us, 1,024 columns 30.1 -> 25.9)

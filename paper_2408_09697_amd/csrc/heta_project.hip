@@ -27,6 +27,8 @@
 //   - the weight gradient contracts over graph rows: the row range is split over workgroups,
 //     partial products go to the workspace and are added in split order (no atomics).
 #include <algorithm>
+#include <new>
+#include <vector>
 
 #include "heta_gemm.h"
 #include "heta_test_hooks.h"
@@ -201,9 +203,11 @@ __global__ void __launch_bounds__(128 * WN) gemm_kernel(GemmParams p)
 // out[m, n] = beta * out[m, n] + sum over splits (in split order) of part[s][m][n], for every segment of
 // a batched weight gradient in one launch (blockIdx.y = segment)
 struct SplitSegs { // passed by value
-    const float *part[kMaxSeg];
-    float *out[kMaxSeg];
-    int64_t M[kMaxSeg], ldo[kMaxSeg];
+    const float *part[kMaxLaunchSeg];
+    float *out[kMaxLaunchSeg];
+    int64_t M[kMaxLaunchSeg], ldo[kMaxLaunchSeg];
+    int32_t N[kMaxLaunchSeg], n_split[kMaxLaunchSeg];
+    float beta[kMaxLaunchSeg];
     unsigned first; // first workgroup of this launch
 };
 // NW wavefronts per 64 elements: wavefront w adds the splits w, w + NW, ... (eight loads in flight), the NW sums are
@@ -213,12 +217,13 @@ struct SplitSegs { // passed by value
 // gradients with four and with one: three of 2,000 rows, 768 x 1,024, bf16 65.7 / 57.5 us; one of 9,000 rows 49.0 / 45.0,
 // of 110,000 rows, 789 x 256, 107.8 / 100.4; of 500 rows, 128 x 256, fp32 17.3 / 18.2).
 template <int NW>
-__global__ void __launch_bounds__(NW == 1 ? 256 : 64 * NW) splitk_reduce_kernel(SplitSegs g, int n_split, int64_t N, float beta)
+__global__ void __launch_bounds__(NW == 1 ? 256 : 64 * NW) splitk_reduce_kernel(SplitSegs g)
 {
     __shared__ float red[NW][64];
     const int lane = threadIdx.x & 63, w = NW == 1 ? 0 : threadIdx.x >> 6;
-    const int seg = blockIdx.y;
-    const int64_t total = static_cast<int64_t>(g.M[seg]) * N;
+    const int seg = blockIdx.y, n_split = g.n_split[seg];
+    const int64_t N = g.N[seg], total = g.M[seg] * N;
+    const float beta = g.beta[seg];
     const int64_t block = static_cast<int64_t>(g.first) + blockIdx.x;
     const int64_t t = NW == 1 ? block * 256 + threadIdx.x : block * 64 + lane;
     const float *part = g.part[seg];
@@ -246,22 +251,22 @@ __global__ void __launch_bounds__(NW == 1 ? 256 : 64 * NW) splitk_reduce_kernel(
 // pipeline can copy into LDS as is (an n-contiguous bf16 operand would need pair interleaving).
 // blockIdx.z picks the matrix: the weights of every segment of a product in one launch.
 struct PackSegs {
-    const bf16_t *W[kMaxSeg];
-    bf16_t *out[kMaxSeg];
-    int64_t ldw[kMaxSeg];
-    int K[kMaxSeg], ld_out[kMaxSeg];
+    const bf16_t *W[kMaxLaunchSeg];
+    bf16_t *out[kMaxLaunchSeg];
+    int64_t ldw[kMaxLaunchSeg];
+    int K[kMaxLaunchSeg], N[kMaxLaunchSeg], ld_out[kMaxLaunchSeg];
 };
-__global__ void __launch_bounds__(256) pack_weight_kernel(PackSegs q, int N)
+__global__ void __launch_bounds__(256) pack_weight_kernel(PackSegs q)
 {
     __shared__ bf16_t tile[32][33];
     const int s = blockIdx.z;
     const bf16_t *W = q.W[s];
     bf16_t *out = q.out[s];
     const int64_t ldw = q.ldw[s];
-    const int K = q.K[s], ld_out = q.ld_out[s];
+    const int K = q.K[s], N = q.N[s], ld_out = q.ld_out[s];
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5; // 32 x 8
     const int k0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
-    if (k0 >= ld_out) return; // uniform per workgroup: a narrower matrix of the launch
+    if (k0 >= ld_out || n0 >= N) return; // uniform per workgroup: a smaller matrix of the launch
     for (int r = ty; r < 32; r += 8)
         tile[r][tx] = (k0 + r < K && n0 + tx < N) ? W[static_cast<int64_t>(k0 + r) * ldw + n0 + tx] : bf16_t(0);
     __syncthreads();
@@ -322,9 +327,15 @@ static void gemm_cost(const GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, dou
 {
     *bytes = 0;
     *flops = 0;
-    const int n_out = p.batch ? p.n_seg : 1;
     for (int s = 0; s < p.n_seg; ++s) {
         const GemmSeg &g = p.seg[s];
+        bool first = p.n_call == 0 && s == 0; // of its call
+        float beta = p.beta;
+        for (int c = 0; c < p.n_call; ++c)
+            if (s >= p.call[c].first) {
+                first = s == p.call[c].first;
+                beta = p.call[c].beta;
+            }
         *flops += 2.0 * g.M * g.N * g.K;
         bool a_seen = false, b_seen = false;
         for (int q = 0; q < s; ++q) {
@@ -333,7 +344,7 @@ static void gemm_cost(const GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, dou
         }
         if (!a_seen) *bytes += static_cast<double>(g.M) * g.K * dtype_size(a_dt);
         if (!b_seen) *bytes += static_cast<double>(g.K) * g.N * dtype_size(b_dt);
-        if (s < n_out) *bytes += static_cast<double>(g.M) * g.N * (p.out_bf16 ? 2.0 : 4.0) * ((p.beta != 0.f && !p.partial) ? 2.0 : 1.0);
+        if (p.batch || first) *bytes += static_cast<double>(g.M) * g.N * (p.out_bf16 ? 2.0 : 4.0) * ((beta != 0.f && !p.partial) ? 2.0 : 1.0);
     }
 }
 
@@ -406,12 +417,11 @@ static heta_status pack_f32_weights(heta_graph *owner, GemmParams &p, int trans,
     return pack_split3_weights(p, trans, owner->d_pack, st);
 }
 
-// out = beta*out + row_scale * sum_s in_s . (W_s or W_s^T)
-static heta_status project_impl(int64_t n_rows, int n_seg, const void *const *ins, heta_dtype in_dt, const int64_t *ld_in,
-                                const int32_t *d_in, const void *const *Ws, heta_dtype w_dt, const int64_t *ld_w,
-                                int32_t d_out, int32_t transW, const float *row_scale, int relu, void *out,
-                                int64_t ld_out, float beta, hipStream_t st, const char *who, heta_graph *pack_owner = nullptr,
-                                heta_dtype out_dt = HETA_F32, void *const *outs = nullptr, const int64_t *ld_outs = nullptr)
+// out = beta*out + row_scale * sum_s in_s . (W_s or W_s^T): the checked arguments as launch parameters (n_seg 0: no rows)
+static heta_status project_plan(GemmParams &p, int64_t n_rows, int n_seg, const void *const *ins, heta_dtype in_dt, const int64_t *ld_in,
+                                const int32_t *d_in, const void *const *Ws, heta_dtype w_dt, const int64_t *ld_w, int32_t d_out, int32_t transW,
+                                const float *row_scale, int relu, void *out, int64_t ld_out, float beta, const char *who, heta_dtype out_dt,
+                                void *const *outs, const int64_t *ld_outs)
 {
     // outs != nullptr: n_seg independent products, one output each (out / ld_out unused); else one summed output
     if (outs && n_seg >= 1) {
@@ -435,7 +445,7 @@ static heta_status project_impl(int64_t n_rows, int n_seg, const void *const *in
     if (misaligned(out, dtype_size(out_dt))) return fail(HETA_ERR_INVALID_ARG, "%s: out not aligned to its element size", who);
     if (out_dt == HETA_BF16 && (beta != 0.f || row_scale || relu))
         return fail(HETA_ERR_UNSUPPORTED, "%s: a bf16 output takes no beta, row_scale or activation", who);
-    GemmParams p{};
+    p = GemmParams{};
     p.out_bf16 = out_dt == HETA_BF16;
     for (int s = 0; s < n_seg; ++s) {
         if (d_in[s] <= 0 || ld_in[s] < d_in[s] || ld_w[s] < (transW ? d_in[s] : d_out))
@@ -462,6 +472,13 @@ static heta_status project_impl(int64_t n_rows, int n_seg, const void *const *in
     p.k_per_split = int64_t(1) << 40;
     p.n_split = 1;
     p.partial = 0;
+    return HETA_OK;
+}
+
+// the planned call, or the calls merged into one plan
+static heta_status project_run(GemmParams &p, heta_dtype in_dt, heta_dtype w_dt, int32_t transW, heta_graph *pack_owner, hipStream_t st)
+{
+    if (p.n_seg == 0) return HETA_OK;
     if (in_dt == HETA_F32 && w_dt == HETA_F32) {
         heta_status pe = pack_f32_weights(pack_owner, p, transW, st);
         if (pe != HETA_OK) return pe;
@@ -475,29 +492,33 @@ static heta_status project_impl(int64_t n_rows, int n_seg, const void *const *in
         // register-staged kernel rounds them when it stages them)
         bool ok = true;
         size_t bytes = 0;
-        for (int s = 0; s < n_seg; ++s) {
-            ok = ok && aligned16(ins[s]) && (ld_in[s] * static_cast<int64_t>(dtype_size(in_dt))) % 16 == 0;
-            bytes += static_cast<size_t>(d_out) * ((d_in[s] + 7) / 8 * 8) * 2 + 256;
+        for (int s = 0; s < p.n_seg; ++s) {
+            const GemmSeg &g = p.seg[s];
+            ok = ok && aligned16(g.A) && (g.lda * static_cast<int64_t>(dtype_size(in_dt))) % 16 == 0;
+            bytes += static_cast<size_t>(g.N) * ((g.K + 7) / 8 * 8) * 2 + 256;
         }
         if (ok) {
             heta_status pe = ensure_pack(pack_owner, bytes);
             if (pe != HETA_OK) return pe;
             char *dst = static_cast<char *>(pack_owner->d_pack);
             PackSegs q{};
-            int ldp_max = 0;
-            for (int s = 0; s < n_seg; ++s) {
-                const int ldp = (d_in[s] + 7) / 8 * 8;
-                q.W[s] = static_cast<const bf16_t *>(Ws[s]);
+            int ldp_max = 0, n_max = 0;
+            for (int s = 0; s < p.n_seg; ++s) {
+                GemmSeg &g = p.seg[s];
+                const int ldp = static_cast<int>((g.K + 7) / 8 * 8);
+                q.W[s] = static_cast<const bf16_t *>(g.B);
                 q.out[s] = reinterpret_cast<bf16_t *>(dst);
-                q.ldw[s] = ld_w[s];
-                q.K[s] = d_in[s];
+                q.ldw[s] = g.ldb;
+                q.K[s] = static_cast<int>(g.K);
+                q.N[s] = static_cast<int>(g.N);
                 q.ld_out[s] = ldp;
                 ldp_max = std::max(ldp_max, ldp);
-                p.seg[s].B = dst;
-                p.seg[s].ldb = ldp;
-                dst += (static_cast<size_t>(d_out) * ldp * 2 + 255) / 256 * 256;
+                n_max = std::max(n_max, q.N[s]);
+                g.B = dst;
+                g.ldb = ldp;
+                dst += (static_cast<size_t>(g.N) * ldp * 2 + 255) / 256 * 256;
             }
-            hipLaunchKernelGGL(pack_weight_kernel, dim3((d_out + 31) / 32, (ldp_max + 31) / 32, n_seg), dim3(256), 0, st, q, d_out);
+            hipLaunchKernelGGL(pack_weight_kernel, dim3((n_max + 31) / 32, (ldp_max + 31) / 32, p.n_seg), dim3(256), 0, st, q);
             HETA_LAUNCH_CHECK("pack_weight_kernel");
             return dispatch_gemm<false, false>(p, in_dt, w_dt, st);
         }
@@ -505,134 +526,407 @@ static heta_status project_impl(int64_t n_rows, int n_seg, const void *const *in
     return dispatch_gemm<false, true>(p, in_dt, w_dt, st);
 }
 
-// dW_s = beta*dW_s + in_s^T . gout over n_rows graph rows, all s in one launch
-static heta_status wgrad_impl(heta_graph *g, int64_t n_rows, int n_seg, const void *const *ins, heta_dtype in_dt,
-                              const int64_t *ld_in, const int32_t *d_in, const float *gout, int64_t ld_go, int32_t d_out,
-                              float *const *dW, const int64_t *ld_dw, float beta, hipStream_t st, const char *who,
-                              int gout_two_terms = 0, const float *const *gouts = nullptr, const int64_t *ld_gos = nullptr)
+static heta_status project_impl(int64_t n_rows, int n_seg, const void *const *ins, heta_dtype in_dt, const int64_t *ld_in,
+                                const int32_t *d_in, const void *const *Ws, heta_dtype w_dt, const int64_t *ld_w,
+                                int32_t d_out, int32_t transW, const float *row_scale, int relu, void *out,
+                                int64_t ld_out, float beta, hipStream_t st, const char *who, heta_graph *pack_owner = nullptr,
+                                heta_dtype out_dt = HETA_F32, void *const *outs = nullptr, const int64_t *ld_outs = nullptr)
 {
-    // gouts != nullptr: every segment has its own gradient operand (gout / ld_go unused)
-    if (gouts && n_seg >= 1) {
-        if (!ld_gos) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
-        for (int s = 0; s < n_seg && s < kMaxSeg; ++s) {
-            if (!gouts[s]) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
-            if (ld_gos[s] < d_out) return fail(HETA_ERR_SHAPE, "%s: bad sizes", who);
-            if (misaligned(gouts[s], 4)) return fail(HETA_ERR_INVALID_ARG, "%s: gout not 4-byte aligned", who);
-        }
-        gout = gouts[0];
-        ld_go = ld_gos[0];
+    GemmParams p;
+    heta_status e = project_plan(p, n_rows, n_seg, ins, in_dt, ld_in, d_in, Ws, w_dt, ld_w, d_out, transW, row_scale, relu, out, ld_out, beta, who,
+                                 out_dt, outs, ld_outs);
+    return e == HETA_OK ? project_run(p, in_dt, w_dt, transW, pack_owner, st) : e;
+}
+
+// ---- several calls in one launch -------------------------------------------------------------------------------------
+// A launch of a few hundred workgroups leaves the chip idle at its end, and one of a few dozen from the start; calls of
+// one layer that do not depend on each other (one per node type) run side by side in one launch instead.  Calls of more
+// than kMergeTiles tiles of 128 x 128 (three to four rounds of workgroups) have the chip to themselves anyway and keep
+// the tiles that suit them; calls whose widest outputs take different tiles do not meet.
+constexpr int64_t kMergeTiles = 2048;
+static int width_class(const GemmParams &p)
+{
+    int64_t n = 0;
+    for (int s = 0; s < p.n_seg; ++s) n = std::max(n, p.seg[s].N);
+    return n <= 64 ? 0 : n <= 128 ? 1 : n <= 256 ? 2 : n <= 320 ? 3 : 4;
+}
+static bool merges(const GemmParams &p, heta_dtype a_dt, heta_dtype b_dt)
+{
+    if (g_force_staged || !gemm_direct_takes(p, a_dt, b_dt)) return false;
+    int64_t tiles = 0;
+    for (int s = 0; s < p.n_seg; ++s) {
+        const int64_t t = ((p.seg[s].M + 127) / 128) * ((p.seg[s].N + 127) / 128);
+        tiles = p.batch ? tiles + t : std::max(tiles, t);
     }
-    if (!g || !ins || !gout || !dW || !ld_in || !d_in || !ld_dw) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
-    if (n_seg < 1 || n_seg > kMaxSeg) return fail(HETA_ERR_INVALID_ARG, "%s: between 1 and %d inputs", who, kMaxSeg);
-    if (!valid_dtype(in_dt)) return fail(HETA_ERR_INVALID_ARG, "%s: bad dtype", who);
-    if (d_out <= 0 || ld_go < d_out) return fail(HETA_ERR_SHAPE, "%s: bad sizes", who);
-    if (misaligned(gout, 4)) return fail(HETA_ERR_INVALID_ARG, "%s: gout not 4-byte aligned", who);
-    GemmParams p{};
-    int64_t out_elems = 0, tiles = 0;
-    // bf16 inputs with 16-byte rows take the all-direct kernel: 128 x 128 tiles, three workgroups per CU (wider and
-    // taller tiles below)
-    bool bf16_direct = in_dt == HETA_BF16 && !g_force_staged;
-    for (int s = 0; s < n_seg && bf16_direct; ++s)
-        bf16_direct = ins[s] && vec_ok(ins[s], ld_in[s], in_dt) && vec_ok(gouts ? gouts[s] : gout, gouts ? ld_gos[s] : ld_go, HETA_F32);
-    // fp32 inputs on the direct pipeline (six bf16 terms per product): 128 x 128 tiles, three workgroups per CU
-    bool f32_terms = in_dt == HETA_F32 && !g_force_staged && !g_f32_native;
-    for (int s = 0; s < n_seg && f32_terms; ++s)
-        f32_terms = ins[s] && vec_ok(ins[s], ld_in[s], in_dt) && vec_ok(gouts ? gouts[s] : gout, gouts ? ld_gos[s] : ld_go, HETA_F32);
-    int d_in_max = 0;
-    for (int s = 0; s < n_seg; ++s) d_in_max = std::max(d_in_max, d_in[s]);
-    const bool tall = bf16_direct && d_in_max > 128; // 320 x 128 tiles, one 512-thread workgroup per CU
-    const bool wide_direct = bf16_direct && !tall && d_out > 128; // 128 x 256 tiles, two 512-thread workgroups per CU
-    const bool tall_wide = tall && d_out > 128;                   // 320 x 256 or 256 x 256 tiles, one workgroup per CU
-    const int BN = (d_out > 128 && (!bf16_direct || wide_direct || tall_wide) && !f32_terms) ? 256 : 128;
-    int BMt = tall ? 320 : BM;
-    if (tall_wide) { // the tile height the launch will choose (wgrad_tile_rows): the one that pads the input columns less
-        int64_t pad320 = 0, pad256 = 0;
-        for (int s = 0; s < n_seg; ++s) {
-            pad320 += (static_cast<int64_t>(d_in[s]) + 319) / 320 * 320;
-            pad256 += (static_cast<int64_t>(d_in[s]) + 255) / 256 * 256;
-        }
-        if (pad256 < pad320) BMt = 256;
-    }
-    for (int s = 0; s < n_seg; ++s) {
-        if (!ins[s] || !dW[s]) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
-        if (d_in[s] <= 0 || ld_in[s] < d_in[s] || ld_dw[s] < d_out) return fail(HETA_ERR_SHAPE, "%s: bad sizes", who);
-        if (misaligned(ins[s], dtype_size(in_dt)) || misaligned(dW[s], 4))
+    return tiles <= kMergeTiles;
+}
+// whether call `q` (both `merges`) joins the calls in `p`
+static bool joins(const GemmParams &p, const GemmParams &q)
+{
+    return std::max(1, p.n_call) < kMaxCalls && p.n_seg + q.n_seg <= kMaxLaunchSeg && p.batch == q.batch && p.out_bf16 == q.out_bf16 &&
+           width_class(p) == width_class(q);
+}
+static void join(GemmParams &p, const GemmParams &q)
+{
+    const auto call_of = [](const GemmParams &x, int first) { return GemmCall{first, x.n_seg, 0, 0, 0, 1, 0x7fffffff, x.relu, x.beta, x.row_scale}; };
+    if (p.n_call == 0) p.call[p.n_call++] = call_of(p, 0);
+    p.call[p.n_call++] = call_of(q, p.n_seg);
+    for (int s = 0; s < q.n_seg; ++s) p.seg[p.n_seg++] = q.seg[s];
+}
+
+// dM_s = gout . W_s^T for every s: products of one depth whose outputs differ in width
+static heta_status bwd_plan(GemmParams &p, int64_t n_rows, int n, const void *const *ins, const int64_t *ld_in, int32_t d_out, const void *const *Ws,
+                            heta_dtype w_dt, const int64_t *ld_w, const int32_t *d_in, void *const *dM, heta_dtype dm_dt, const int64_t *ld_dm,
+                            const char *who)
+{
+    p = GemmParams{};
+    for (int s = 0; s < n; ++s) {
+        if (!ins[s] || !Ws[s] || !dM[s]) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
+        if (d_in[s] <= 0 || ld_in[s] < d_out || ld_w[s] < d_out || ld_dm[s] < d_in[s]) return fail(HETA_ERR_SHAPE, "%s: bad sizes", who);
+        if (misaligned(ins[s], 4) || misaligned(Ws[s], dtype_size(w_dt)) || misaligned(dM[s], dtype_size(dm_dt)))
             return fail(HETA_ERR_INVALID_ARG, "%s: pointer not aligned to its element size", who);
         GemmSeg &q = p.seg[s];
-        q.A = ins[s];      // A[m = column of `in`][k = graph row] : r-contiguous
+        q.A = ins[s];
         q.lda = ld_in[s];
-        q.B = gouts ? gouts[s] : gout; // B[k = graph row][n] : r-contiguous
-        q.ldb = gouts ? ld_gos[s] : ld_go;
-        q.M = d_in[s];
-        q.N = d_out;
-        q.K = n_rows;
-        q.ldc = d_out;
-        out_elems += static_cast<int64_t>(d_in[s]) * d_out;
-        tiles += ((d_in[s] + BMt - 1) / BMt) * ((d_out + BN - 1) / BN);
+        q.B = Ws[s];   // B[k][n] = W[n][k]: W is [d_in, d_out] row-major, k-contiguous
+        q.ldb = ld_w[s];
+        q.C = static_cast<float *>(dM[s]); // typed by p.out_bf16 in the kernels' epilogue
+        q.ldc = ld_dm[s];
+        q.M = n_rows;
+        q.N = d_in[s];
+        q.K = d_out;
     }
-    // Split the graph rows so that the workgroups fill the chip exactly once and never spill into a
-    // second, nearly empty round.  Workgroups are dealt round-robin to the 8 XCDs (32 CUs each) and
-    // the kernel keeps the `tiles` output tiles of one split on one XCD, so a split costs `tiles`
-    // workgroup slots of its XCD: 2 resident 512-thread workgroups per CU (3 or 4 of 256 threads).
-    // Each split keeps at least 4 k-tiles (a few thousand graph rows still spread over the chip: a
-    // workgroup's k-tiles are latency-bound when few workgroups run).
-    const int64_t BK = in_dt == HETA_F32 ? 32 : 64;
-    const int64_t k_tiles = (n_rows + BK - 1) / BK;
-    const int64_t slots_per_xcd = 32 * (tall ? 1 : wide_direct ? 2 : (bf16_direct || f32_terms) ? 3 : (d_out > 128 ? 2 : (in_dt == HETA_F32 ? 3 : 4)));
-    // a split's workgroups are (largest segment's row tiles) x (column tiles) x (segments), all on one XCD
-    int64_t mt_max = 1;
-    for (int s = 0; s < n_seg; ++s) mt_max = std::max<int64_t>(mt_max, (d_in[s] + BMt - 1) / BMt);
-    const int64_t slots_per_split = std::max<int64_t>(tiles, mt_max * ((d_out + BN - 1) / BN) * n_seg);
-    const int64_t splits_per_xcd = std::max<int64_t>(1, slots_per_xcd / std::max<int64_t>(1, slots_per_split));
-    int64_t n_split = std::max<int64_t>(1, std::min<int64_t>((k_tiles + 3) / 4, 8 * splits_per_xcd));
-    const int64_t tiles_per_split = std::max<int64_t>(1, (k_tiles + n_split - 1) / n_split);
-    n_split = std::max<int64_t>(1, (k_tiles + tiles_per_split - 1) / tiles_per_split);
-    heta_status e = ensure_workspace(g, static_cast<size_t>(n_split) * out_elems * sizeof(float));
-    if (e != HETA_OK) return e;
-    float *ws = static_cast<float *>(g->d_ws);
-    int64_t off = 0;
-    for (int s = 0; s < n_seg; ++s) {
-        p.seg[s].C = ws + off;
-        off += n_split * static_cast<int64_t>(d_in[s]) * d_out;
-    }
-    p.n_seg = n_seg;
+    if (n_rows == 0) return HETA_OK;
+    p.n_seg = n;
     p.batch = 1;
-    p.row_scale = nullptr;
-    p.beta = 0.f;
-    p.relu = 0;
-    p.k_per_split = tiles_per_split * BK;
-    p.n_split = static_cast<int>(n_split);
+    p.k_per_split = int64_t(1) << 40;
+    p.n_split = 1;
+    p.out_bf16 = dm_dt == HETA_BF16;
+    return HETA_OK;
+}
+
+// A weight gradient dW_s = beta*dW_s + in_s^T . gout_s over n_rows graph rows, all s of one width d_out.
+struct Wgrad {
+    int64_t n_rows;
+    int n_seg;
+    const void *const *ins;
+    const int64_t *ld_in;
+    const int32_t *d_in;
+    const float *const *gouts;
+    const int64_t *ld_go;
+    int32_t d_out;
+    float *const *dW;
+    const int64_t *ld_dw;
+};
+// Which kernel and tiles it takes (wgrad_run): calls of one kind can share a launch.
+struct WgradKind {
+    bool bf16_direct, f32_terms; // neither: the register-staged kernel
+    bool tall, wide_direct;
+    int BM, BN, width;
+    bool operator==(const WgradKind &o) const
+    {
+        return bf16_direct == o.bf16_direct && f32_terms == o.f32_terms && tall == o.tall && wide_direct == o.wide_direct && BM == o.BM && BN == o.BN &&
+               width == o.width;
+    }
+};
+
+static heta_status wgrad_check(const Wgrad &c, heta_dtype in_dt, const char *who)
+{
+    if (!c.ins || !c.gouts || !c.dW || !c.ld_in || !c.ld_go || !c.d_in || !c.ld_dw) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
+    if (c.n_seg < 1 || c.n_seg > kMaxSeg) return fail(HETA_ERR_INVALID_ARG, "%s: between 1 and %d inputs", who, kMaxSeg);
+    for (int s = 0; s < c.n_seg; ++s) {
+        if (!c.gouts[s]) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
+        if (c.ld_go[s] < c.d_out) return fail(HETA_ERR_SHAPE, "%s: bad sizes", who);
+        if (misaligned(c.gouts[s], 4)) return fail(HETA_ERR_INVALID_ARG, "%s: gout not 4-byte aligned", who);
+    }
+    if (!valid_dtype(in_dt)) return fail(HETA_ERR_INVALID_ARG, "%s: bad dtype", who);
+    if (c.n_rows < 0 || c.d_out <= 0) return fail(HETA_ERR_SHAPE, "%s: bad sizes", who);
+    for (int s = 0; s < c.n_seg; ++s) {
+        if (!c.ins[s] || !c.dW[s]) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
+        if (c.d_in[s] <= 0 || c.ld_in[s] < c.d_in[s] || c.ld_dw[s] < c.d_out) return fail(HETA_ERR_SHAPE, "%s: bad sizes", who);
+        if (misaligned(c.ins[s], dtype_size(in_dt)) || misaligned(c.dW[s], 4))
+            return fail(HETA_ERR_INVALID_ARG, "%s: pointer not aligned to its element size", who);
+    }
+    return HETA_OK;
+}
+
+static WgradKind wgrad_kind(const Wgrad &c, heta_dtype in_dt)
+{
+    WgradKind k{};
+    bool vec = !g_force_staged;
+    int d_in_max = 0;
+    for (int s = 0; s < c.n_seg; ++s) {
+        vec = vec && vec_ok(c.ins[s], c.ld_in[s], in_dt) && vec_ok(c.gouts[s], c.ld_go[s], HETA_F32);
+        d_in_max = std::max(d_in_max, c.d_in[s]);
+    }
+    // bf16 inputs with 16-byte rows take the all-direct kernel: 128 x 128 tiles, three workgroups per CU (wider and
+    // taller tiles below)
+    k.bf16_direct = in_dt == HETA_BF16 && vec;
+    // fp32 inputs on the direct pipeline (six bf16 terms per product): 128 x 128 tiles, three workgroups per CU
+    k.f32_terms = in_dt == HETA_F32 && vec && !g_f32_native;
+    k.tall = k.bf16_direct && d_in_max > 128;                     // 320 x 128 tiles, one 512-thread workgroup per CU
+    k.wide_direct = k.bf16_direct && !k.tall && c.d_out > 128;    // 128 x 256 tiles, two 512-thread workgroups per CU
+    const bool tall_wide = k.tall && c.d_out > 128;               // 320 x 256 or 256 x 256 tiles, one workgroup per CU
+    k.BN = (c.d_out > 128 && (!k.bf16_direct || k.wide_direct || tall_wide) && !k.f32_terms) ? 256 : 128;
+    k.BM = k.tall ? 320 : BM;
+    if (tall_wide) { // the tile height the launch will choose (wgrad_tile_rows): the one that pads the input columns less
+        int64_t pad320 = 0, pad256 = 0;
+        for (int s = 0; s < c.n_seg; ++s) {
+            pad320 += (static_cast<int64_t>(c.d_in[s]) + 319) / 320 * 320;
+            pad256 += (static_cast<int64_t>(c.d_in[s]) + 255) / 256 * 256;
+        }
+        if (pad256 < pad320) k.BM = 256;
+    }
+    k.width = c.d_out <= 64 ? 0 : c.d_out <= 128 ? 1 : 2;
+    return k;
+}
+
+// Split the graph rows so that a call's workgroups fill the chip exactly once and never spill into a
+// second, nearly empty round.  Workgroups are dealt round-robin to the 8 XCDs (32 CUs each) and
+// the kernel keeps the `tiles` output tiles of one split on one XCD, so a split costs `tiles`
+// workgroup slots of its XCD: 2 resident 512-thread workgroups per CU (3 or 4 of 256 threads).
+// Each split keeps at least 4 k-tiles (a few thousand graph rows still spread over the chip: a
+// workgroup's k-tiles are latency-bound when few workgroups run).
+struct WgradSplit {
+    int64_t n, k_tiles_each, k_tile; // splits, k-tiles of each, graph rows per k-tile
+};
+static WgradSplit wgrad_split(const Wgrad &c, const WgradKind &kind, heta_dtype in_dt)
+{
+    const int64_t BK = in_dt == HETA_F32 ? 32 : 64, k_tiles = (c.n_rows + BK - 1) / BK, nt = (c.d_out + kind.BN - 1) / kind.BN;
+    const int64_t slots_per_xcd =
+        32 * (kind.tall ? 1 : kind.wide_direct ? 2 : (kind.bf16_direct || kind.f32_terms) ? 3 : (c.d_out > 128 ? 2 : (in_dt == HETA_F32 ? 3 : 4)));
+    int64_t tiles = 0, mt_max = 1;
+    for (int s = 0; s < c.n_seg; ++s) {
+        const int64_t mt = (static_cast<int64_t>(c.d_in[s]) + kind.BM - 1) / kind.BM;
+        tiles += mt * nt;
+        mt_max = std::max(mt_max, mt);
+    }
+    // a split's workgroups are (largest segment's row tiles) x (column tiles) x (segments), all on one XCD
+    const int64_t slots_per_split = std::max<int64_t>(tiles, mt_max * nt * c.n_seg);
+    const int64_t splits_per_xcd = std::max<int64_t>(1, slots_per_xcd / std::max<int64_t>(1, slots_per_split));
+    const int64_t n = std::max<int64_t>(1, std::min<int64_t>((k_tiles + 3) / 4, 8 * splits_per_xcd));
+    const int64_t each = std::max<int64_t>(1, (k_tiles + n - 1) / n);
+    return WgradSplit{std::max<int64_t>(1, (k_tiles + each - 1) / each), each, BK};
+}
+
+// The listed calls (checked; of one kind if there are several) in one launch, their partial sums in another.  Calls that
+// share a launch keep their splits: splits of one length that fill the chip together would be longer, and longer sums are
+// further from 64 bits (9.4e-7 -> 1.3e-6, layer of 21 M edges).
+static heta_status wgrad_run(heta_graph *g, const Wgrad *calls, int n_calls, heta_dtype in_dt, int gout_two_terms, float beta, hipStream_t st)
+{
+    const WgradKind kind = wgrad_kind(calls[0], in_dt);
+    GemmParams p{};
+    int64_t out_elems = 0;
+    int64_t n_split[kMaxCalls], split_max = 1, ws_elems = 0;
+    for (int c = 0; c < n_calls; ++c) {
+        const Wgrad &w = calls[c];
+        int64_t elems = 0;
+        const int first = p.n_seg;
+        for (int s = 0; s < w.n_seg; ++s) {
+            GemmSeg &q = p.seg[p.n_seg++];
+            q.A = w.ins[s];    // A[m = column of `in`][k = graph row] : r-contiguous
+            q.lda = w.ld_in[s];
+            q.B = w.gouts[s];  // B[k = graph row][n] : r-contiguous
+            q.ldb = w.ld_go[s];
+            q.M = w.d_in[s];
+            q.N = w.d_out;
+            q.K = w.n_rows;
+            q.ldc = w.d_out;
+            elems += q.M * q.N;
+        }
+        const WgradSplit split = wgrad_split(w, kind, in_dt);
+        n_split[c] = split.n;
+        out_elems += elems;
+        ws_elems += n_split[c] * elems;
+        split_max = std::max(split_max, n_split[c]);
+        p.k_per_split = split.k_tiles_each * split.k_tile;
+        if (n_calls > 1)
+            p.call[p.n_call++] = GemmCall{first, w.n_seg, 0, 0, 0, static_cast<int32_t>(n_split[c]),
+                                          static_cast<int32_t>(std::min<int64_t>(p.k_per_split, 0x7fffffff)), 0, 0.f, nullptr};
+    }
+    heta_status e = ensure_workspace(g, static_cast<size_t>(ws_elems) * sizeof(float));
+    if (e != HETA_OK) return e;
+    SplitSegs segs{};
+    int64_t total_max = 0;
+    double bytes = 0;
+    float *ws = static_cast<float *>(g->d_ws);
+    for (int c = 0, at = 0; c < n_calls; ++c)
+        for (int s = 0; s < calls[c].n_seg; ++s, ++at) {
+            const int64_t total = static_cast<int64_t>(calls[c].d_in[s]) * calls[c].d_out;
+            p.seg[at].C = ws;
+            ws += n_split[c] * total;
+            segs.part[at] = p.seg[at].C;
+            segs.out[at] = calls[c].dW[s];
+            segs.M[at] = calls[c].d_in[s];
+            segs.ldo[at] = calls[c].ld_dw[s];
+            segs.N[at] = calls[c].d_out;
+            segs.n_split[at] = static_cast<int32_t>(n_split[c]);
+            segs.beta[at] = beta;
+            total_max = std::max(total_max, total);
+            bytes += (n_split[c] + 1.0) * total * 4.0;
+        }
+    p.batch = 1;
+    p.n_split = static_cast<int>(split_max);
     p.partial = 1;
     p.split_b = (gout_two_terms && in_dt == HETA_BF16) ? 1 : 0;
-    e = dispatch_gemm<true, true>(p, in_dt, HETA_F32, st, static_cast<int>(BK));
-    if (e != HETA_OK) return e;
-    {
-        SplitSegs segs{};
-        int64_t total_max = 0;
-        double bytes = 0;
-        for (int s = 0; s < n_seg; ++s) {
-            const int64_t total = static_cast<int64_t>(d_in[s]) * d_out;
-            segs.part[s] = static_cast<const float *>(p.seg[s].C);
-            segs.out[s] = dW[s];
-            segs.M[s] = d_in[s];
-            segs.ldo[s] = ld_dw[s];
-            total_max = std::max(total_max, total);
-            bytes += (n_split + 1.0) * total * 4.0;
+    if ((e = dispatch_gemm<true, true>(p, in_dt, HETA_F32, st, in_dt == HETA_F32 ? 32 : 64)) != HETA_OK) return e;
+    ProfScope prof("splitk_reduce_kernel", st, bytes, 0);
+    const int nw = split_max >= 128 ? 16 : split_max >= 32 || out_elems < 196608 ? 4 : 1;
+    const int64_t per_block = nw == 1 ? 256 : 64;
+    launch_pieces((total_max + per_block - 1) / per_block, nw == 1 ? 256 : 64 * nw, [&](unsigned first, unsigned count) {
+        segs.first = first;
+        const dim3 grid(count, (unsigned)p.n_seg);
+        const auto launch = [&](auto kernel, int threads) { hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, st, segs); };
+        if (nw == 16) launch(splitk_reduce_kernel<16>, 1024);
+        else if (nw == 4) launch(splitk_reduce_kernel<4>, 256);
+        else launch(splitk_reduce_kernel<1>, 256);
+    });
+    HETA_LAUNCH_CHECK("splitk_reduce_kernel");
+    return HETA_OK;
+}
+
+// one call; gouts null: every segment takes gout / ld_go
+static heta_status wgrad_impl(heta_graph *g, int64_t n_rows, int n_seg, const void *const *ins, heta_dtype in_dt, const int64_t *ld_in,
+                              const int32_t *d_in, const float *gout, int64_t ld_go, int32_t d_out, float *const *dW, const int64_t *ld_dw, float beta,
+                              hipStream_t st, const char *who, int gout_two_terms = 0, const float *const *gouts = nullptr,
+                              const int64_t *ld_gos = nullptr)
+{
+    if (!g) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
+    const float *same[kMaxSeg];
+    int64_t ld_same[kMaxSeg];
+    if (!gouts) {
+        std::fill(same, same + kMaxSeg, gout);
+        std::fill(ld_same, ld_same + kMaxSeg, ld_go);
+        gouts = same;
+        ld_gos = ld_same;
+    }
+    const Wgrad call{n_rows, n_seg, ins, ld_in, d_in, gouts, ld_gos, d_out, dW, ld_dw};
+    heta_status e = wgrad_check(call, in_dt, who);
+    return e == HETA_OK ? wgrad_run(g, &call, 1, in_dt, gout_two_terms, beta, st) : e;
+}
+
+// whether the byte ranges of n rows of `bytes` (pitch `pitch`) at a and at b share memory
+static bool rows_overlap(const void *a, int64_t na, int64_t pa, int64_t wa, const void *b, int64_t nb, int64_t pb, int64_t wb)
+{
+    if (na <= 0 || nb <= 0) return false;
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + static_cast<uintptr_t>((nb - 1) * pb + wb) && y < x + static_cast<uintptr_t>((na - 1) * pa + wa);
+}
+
+static heta_status project_multi_impl(heta_graph *g, int32_t n, const int32_t *first, const int64_t *n_rows, int32_t sum, const void *const *ins,
+                                      heta_dtype in_dt, const int64_t *ld_in, const int32_t *depth, const void *const *Ws, heta_dtype w_dt,
+                                      const int64_t *ld_w, const int32_t *width, int32_t transW, void *const *outs, heta_dtype out_dt,
+                                      const int64_t *ld_out, const heta_act *acts, const float *betas, hipStream_t st)
+{
+    const char *who = "heta_project_multi";
+    if (!g || n < 0 || (n > 0 && (!first || !n_rows || !ins || !ld_in || !depth || !Ws || !ld_w || !width || !outs || !ld_out)))
+        return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
+    if (!valid_dtype(in_dt) || !valid_dtype(w_dt) || !valid_dtype(out_dt)) return fail(HETA_ERR_INVALID_ARG, "%s: bad dtype", who);
+    if (n > 0 && first[0] != 0) return fail(HETA_ERR_INVALID_ARG, "%s: first[0] must be 0", who);
+    std::vector<GemmParams> plans(n);
+    for (int32_t i = 0; i < n; ++i) {
+        const int32_t f = first[i], m = first[i + 1] - f;
+        if (m < 1 || m > kMaxSeg) return fail(HETA_ERR_INVALID_ARG, "%s: between 1 and %d products per item", who, kMaxSeg);
+        if (acts && acts[i] != HETA_ACT_NONE && acts[i] != HETA_ACT_RELU) return fail(HETA_ERR_INVALID_ARG, "%s: bad act", who);
+        if (!sum && ((acts && acts[i] != HETA_ACT_NONE) || (betas && betas[i] != 0.f)))
+            return fail(HETA_ERR_UNSUPPORTED, "%s: activation and beta belong to sums", who);
+        for (int32_t s = f + 1; s < f + m; ++s)
+            if (sum ? width[s] != width[f] : depth[s] != depth[f])
+                return fail(HETA_ERR_SHAPE, "%s: a sum's products share their width, independent ones their depth", who);
+        heta_status e = sum ? project_plan(plans[i], n_rows[i], m, ins + f, in_dt, ld_in + f, depth + f, Ws + f, w_dt, ld_w + f, width[f], transW, nullptr,
+                                           acts && acts[i] == HETA_ACT_RELU, outs[i], ld_out[i], betas ? betas[i] : 0.f, who, out_dt, nullptr, nullptr)
+                        : HETA_OK;
+        if (!sum) { // independent products: one depth, any widths
+            if (n_rows[i] < 0 || depth[f] <= 0) return fail(HETA_ERR_SHAPE, "%s: bad sizes", who);
+            GemmParams &p = plans[i];
+            p = GemmParams{};
+            for (int32_t s = f; s < f + m; ++s) {
+                if (!ins[s] || !Ws[s] || !outs[s]) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
+                if (width[s] <= 0 || ld_in[s] < depth[s] || ld_w[s] < (transW ? depth[s] : width[s]) || ld_out[s] < width[s])
+                    return fail(HETA_ERR_SHAPE, "%s: bad sizes", who);
+                if (misaligned(ins[s], dtype_size(in_dt)) || misaligned(Ws[s], dtype_size(w_dt)) || misaligned(outs[s], dtype_size(out_dt)))
+                    return fail(HETA_ERR_INVALID_ARG, "%s: pointer not aligned to its element size", who);
+                p.seg[s - f] = GemmSeg{ins[s], ld_in[s], Ws[s], ld_w[s], static_cast<float *>(outs[s]), ld_out[s], n_rows[i], width[s], depth[s], nullptr, 0, 0};
+            }
+            if (n_rows[i] > 0) {
+                p.n_seg = m;
+                p.batch = 1;
+                p.k_per_split = int64_t(1) << 40;
+                p.n_split = 1;
+                p.out_bf16 = out_dt == HETA_BF16;
+            }
         }
-        ProfScope prof("splitk_reduce_kernel", st, bytes, 0);
-        const int nw = n_split >= 128 ? 16 : n_split >= 32 || out_elems < 196608 ? 4 : 1;
-        const int64_t per_block = nw == 1 ? 256 : 64;
-        launch_pieces((total_max + per_block - 1) / per_block, nw == 1 ? 256 : 64 * nw, [&](unsigned first, unsigned count) {
-            segs.first = first;
-            const dim3 grid(count, (unsigned)n_seg);
-            const auto launch = [&](auto kernel, int threads) {
-                hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, st, segs, static_cast<int>(n_split), (int64_t)d_out, beta);
-            };
-            if (nw == 16) launch(splitk_reduce_kernel<16>, 1024);
-            else if (nw == 4) launch(splitk_reduce_kernel<4>, 256);
-            else launch(splitk_reduce_kernel<1>, 256);
-        });
-        HETA_LAUNCH_CHECK("splitk_reduce_kernel");
+        if (e != HETA_OK) return e;
+    }
+    // the outputs are written side by side
+    const int64_t elt = static_cast<int64_t>(dtype_size(out_dt));
+    std::vector<const GemmSeg *> written;
+    for (const GemmParams &p : plans)
+        for (int s = 0; s < (p.batch ? p.n_seg : std::min(p.n_seg, 1)); ++s) {
+            const GemmSeg &a = p.seg[s];
+            for (const GemmSeg *b : written)
+                if (rows_overlap(a.C, a.M, a.ldc * elt, a.N * elt, b->C, b->M, b->ldc * elt, b->N * elt))
+                    return fail(HETA_ERR_INVALID_ARG, "%s: outputs overlap", who);
+            written.push_back(&a);
+        }
+    for (int32_t i = 0; i < n; ++i) {
+        GemmParams &p = plans[i];
+        if (p.n_seg == 0) continue; // no rows, or joined already
+        if (merges(p, in_dt, w_dt))
+            for (int32_t j = i + 1; j < n; ++j)
+                if (plans[j].n_seg > 0 && merges(plans[j], in_dt, w_dt) && joins(p, plans[j])) {
+                    join(p, plans[j]);
+                    plans[j].n_seg = 0;
+                }
+        heta_status e = project_run(p, in_dt, w_dt, transW, g, st);
+        if (e != HETA_OK) return e;
+    }
+    return HETA_OK;
+}
+
+constexpr int64_t kMergeKTiles = 32;
+static heta_status wgrad_multi_impl(heta_graph *g, int32_t n, const int32_t *first, const int64_t *n_rows, const void *const *ins, heta_dtype in_dt,
+                                    const int64_t *ld_in, const int32_t *d_in, const float *const *gouts, const int64_t *ld_go, const int32_t *d_out,
+                                    float *const *dW, const int64_t *ld_dw, int32_t gout_two_terms, hipStream_t st)
+{
+    const char *who = "heta_project_wgrad_multi";
+    if (!g || n < 0 || (n > 0 && (!first || !n_rows || !ins || !ld_in || !d_in || !gouts || !ld_go || !d_out || !dW || !ld_dw)))
+        return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
+    if (n > 0 && first[0] != 0) return fail(HETA_ERR_INVALID_ARG, "%s: first[0] must be 0", who);
+    std::vector<Wgrad> calls;
+    for (int32_t i = 0; i < n; ++i) {
+        const int32_t f = first[i];
+        calls.push_back(Wgrad{n_rows[i], first[i + 1] - f, ins + f, ld_in + f, d_in + f, gouts + f, ld_go + f, d_out[i], dW + f, ld_dw + f});
+        heta_status e = wgrad_check(calls.back(), in_dt, who);
+        if (e != HETA_OK) return e;
+    }
+    for (int32_t i = 0; i < n; ++i)
+        for (int32_t s = first[i]; s < first[i + 1]; ++s)
+            for (int32_t j = 0; j <= i; ++j)
+                for (int32_t t = first[j]; t < first[j + 1] && t < s; ++t)
+                    if (rows_overlap(dW[s], d_in[s], ld_dw[s] * 4, d_out[i] * 4, dW[t], d_in[t], ld_dw[t] * 4, d_out[j] * 4))
+                        return fail(HETA_ERR_INVALID_ARG, "%s: outputs overlap", who);
+    // Calls of few k-tiles per split share a launch; the others fill the chip for long enough by themselves (kMergeKTiles: five
+    // calls of 10^4 to 10^6 rows, 128 x 256, 1.34 ms together and 1.13 one by one; four of 900 to 110,000 rows, 128 x 64, 76 us
+    // together and 112).  Calls without rows leave zeros and go alone.
+    const auto shares = [&](const Wgrad &c, const WgradKind &kind) {
+        return (kind.bf16_direct || kind.f32_terms) && c.n_rows > 0 && wgrad_split(c, kind, in_dt).k_tiles_each <= kMergeKTiles;
+    };
+    std::vector<char> done(n, 0);
+    for (int32_t i = 0; i < n; ++i) {
+        if (done[i]) continue;
+        const WgradKind kind = wgrad_kind(calls[i], in_dt);
+        Wgrad part[kMaxCalls] = {calls[i]};
+        int count = 1, segs = calls[i].n_seg;
+        if (shares(calls[i], kind))
+            for (int32_t j = i + 1; j < n && count < kMaxCalls; ++j)
+                if (!done[j] && segs + calls[j].n_seg <= kMaxLaunchSeg && wgrad_kind(calls[j], in_dt) == kind && shares(calls[j], kind)) {
+                    part[count++] = calls[j];
+                    segs += calls[j].n_seg;
+                    done[j] = 1;
+                }
+        heta_status e = wgrad_run(g, part, count, in_dt, gout_two_terms, 0.f, st);
+        if (e != HETA_OK) return e;
     }
     return HETA_OK;
 }
@@ -747,39 +1041,14 @@ heta_status heta_cross_rel_project_bwd(const heta_graph *g, int32_t dst_type, in
     if (!valid_dtype(w_dt) || !valid_dtype(dm_dt)) return fail(HETA_ERR_INVALID_ARG, "%s: bad dtype", who);
     if (d_out <= 0 || ld_go < d_out) return fail(HETA_ERR_SHAPE, "%s: bad sizes", who);
     if (misaligned(gout, 4)) return fail(HETA_ERR_INVALID_ARG, "%s: gout not 4-byte aligned", who);
-    const int64_t n_rows = g->ntypes[dst_type].num_nodes;
-    GemmParams p{};
-    for (int s = 0; s < n; ++s) {
-        if (!Ws[s] || !dM[s]) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
-        if (d_in[s] <= 0 || ld_w[s] < d_out || ld_dm[s] < d_in[s]) return fail(HETA_ERR_SHAPE, "%s: bad sizes", who);
-        if (misaligned(Ws[s], dtype_size(w_dt)) || misaligned(dM[s], dtype_size(dm_dt)))
-            return fail(HETA_ERR_INVALID_ARG, "%s: pointer not aligned to its element size", who);
-        GemmSeg &q = p.seg[s];
-        q.A = gout;
-        q.lda = ld_go;
-        q.B = Ws[s];   // B[k][n] = W[n][k]: W is [d_in, d_out] row-major, k-contiguous
-        q.ldb = ld_w[s];
-        q.C = static_cast<float *>(dM[s]); // typed by p.out_bf16 in the kernels' epilogue
-        q.ldc = ld_dm[s];
-        q.M = n_rows;
-        q.N = d_in[s];
-        q.K = d_out;
-    }
-    if (n_rows == 0) return HETA_OK;
-    p.n_seg = n;
-    p.batch = 1;
-    p.row_scale = nullptr;
-    p.beta = 0.f;
-    p.relu = 0;
-    p.k_per_split = int64_t(1) << 40;
-    p.n_split = 1;
-    p.partial = 0;
-    p.out_bf16 = dm_dt == HETA_BF16;
-    if (w_dt == HETA_F32) { // the handle's packing buffer is scratch memory, not part of the graph it describes
-        e = pack_f32_weights(const_cast<heta_graph *>(g), p, 1, as_stream(hip_stream));
-        if (e != HETA_OK) return e;
-    }
-    return dispatch_gemm<false, false>(p, HETA_F32, w_dt, as_stream(hip_stream));
+    const void *ins[kMaxSeg];
+    int64_t ld_in[kMaxSeg];
+    GemmParams p;
+    std::fill(ins, ins + n, gout);
+    std::fill(ld_in, ld_in + n, ld_go);
+    if ((e = bwd_plan(p, g->ntypes[dst_type].num_nodes, n, ins, ld_in, d_out, Ws, w_dt, ld_w, d_in, dM, dm_dt, ld_dm, who)) != HETA_OK) return e;
+    // the handle's packing buffer is scratch memory, not part of the graph it describes
+    return project_run(p, HETA_F32, w_dt, 1, const_cast<heta_graph *>(g), as_stream(hip_stream));
 }
 
 heta_status heta_cross_rel_project_wgrad(heta_graph *g, int32_t dst_type, int32_t n, const void *const *ins,
@@ -791,6 +1060,35 @@ heta_status heta_cross_rel_project_wgrad(heta_graph *g, int32_t dst_type, int32_
     if (e != HETA_OK) return e;
     return wgrad_impl(g, g->ntypes[dst_type].num_nodes, n, ins, in_dt, ld_in, d_in, gout, ld_go, d_out, dW, ld_dw, beta,
                       as_stream(hip_stream), "heta_cross_rel_project_wgrad", gout_two_terms);
+}
+
+// No exception crosses the boundary: host containers may throw std::bad_alloc.
+heta_status heta_project_multi(heta_graph *g, int32_t n, const int32_t *first, const int64_t *n_rows, int32_t sum, const void *const *ins, heta_dtype in_dt,
+                               const int64_t *ld_in, const int32_t *depth, const void *const *Ws, heta_dtype w_dt, const int64_t *ld_w,
+                               const int32_t *width, int32_t transW, void *const *outs, heta_dtype out_dt, const int64_t *ld_out, const heta_act *acts,
+                               const float *betas, void *hip_stream)
+{
+    try {
+        return project_multi_impl(g, n, first, n_rows, sum, ins, in_dt, ld_in, depth, Ws, w_dt, ld_w, width, transW, outs, out_dt, ld_out, acts, betas,
+                                  as_stream(hip_stream));
+    } catch (const std::bad_alloc &) {
+        return fail(HETA_ERR_OOM, "heta_project_multi: host allocation failed");
+    } catch (...) {
+        return fail(HETA_ERR_DEVICE, "heta_project_multi: unexpected exception");
+    }
+}
+
+heta_status heta_project_wgrad_multi(heta_graph *g, int32_t n, const int32_t *first, const int64_t *n_rows, const void *const *ins, heta_dtype in_dt,
+                                     const int64_t *ld_in, const int32_t *d_in, const float *const *gouts, const int64_t *ld_go, const int32_t *d_out,
+                                     float *const *dW, const int64_t *ld_dw, int32_t gout_two_terms, void *hip_stream)
+{
+    try {
+        return wgrad_multi_impl(g, n, first, n_rows, ins, in_dt, ld_in, d_in, gouts, ld_go, d_out, dW, ld_dw, gout_two_terms, as_stream(hip_stream));
+    } catch (const std::bad_alloc &) {
+        return fail(HETA_ERR_OOM, "heta_project_wgrad_multi: host allocation failed");
+    } catch (...) {
+        return fail(HETA_ERR_DEVICE, "heta_project_wgrad_multi: unexpected exception");
+    }
 }
 
 } // extern "C"

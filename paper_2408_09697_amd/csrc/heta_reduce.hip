@@ -67,6 +67,41 @@ __global__ void __launch_bounds__(256) act_bwd_kernel(unsigned first, int64_t n_
     }
 }
 
+// Several of them in one launch, their workgroups end to end: a launch of its own takes 4 to 5 us however few rows a node
+// type has.
+constexpr int kMaxActs = 16;
+struct ActItems { // passed by value
+    const float *h[kMaxActs], *go[kMaxActs];
+    float *gi[kMaxActs];
+    int64_t ld_h[kMaxActs], ld_go[kMaxActs], ld_gi[kMaxActs], n_rows[kMaxActs];
+    uint32_t blk0[kMaxActs + 1]; // first workgroup
+    int32_t d[kMaxActs];
+    int n, relu;
+};
+template <int V> __global__ void __launch_bounds__(256) act_bwd_multi_kernel(ActItems a)
+{
+    int k = 0;
+    while (k + 1 < a.n && blockIdx.x >= a.blk0[k + 1]) ++k; // uniform
+    const int d = a.d[k], per_row = (d + V - 1) / V;
+    const int64_t t = static_cast<int64_t>(blockIdx.x - a.blk0[k]) * 256 + threadIdx.x;
+    const int64_t i = t / per_row;
+    const int c = static_cast<int>(t % per_row) * V;
+    if (i >= a.n_rows[k]) return;
+    if (V == 4) {
+        float4 g = *reinterpret_cast<const float4 *>(a.go[k] + i * a.ld_go[k] + c);
+        if (a.relu) {
+            const float4 x = *reinterpret_cast<const float4 *>(a.h[k] + i * a.ld_h[k] + c);
+            g.x = x.x > 0.f ? g.x : 0.f; g.y = x.y > 0.f ? g.y : 0.f;
+            g.z = x.z > 0.f ? g.z : 0.f; g.w = x.w > 0.f ? g.w : 0.f;
+        }
+        *reinterpret_cast<float4 *>(a.gi[k] + i * a.ld_gi[k] + c) = g;
+    } else {
+        float g = a.go[k][i * a.ld_go[k] + c];
+        if (a.relu && !(a.h[k][i * a.ld_h[k] + c] > 0.f)) g = 0.f;
+        a.gi[k][i * a.ld_gi[k] + c] = g;
+    }
+}
+
 // A plain streaming copy of known size: the reference point against which hardware byte
 // counters are scaled when the library's kernels are profiled.
 __global__ void __launch_bounds__(256) calibration_copy_kernel(const uint4 *src, uint4 *dst, int64_t n)
@@ -198,6 +233,63 @@ heta_status heta_act_bwd(int64_t n_rows, int32_t d, heta_act act, const float *h
                                grad_out, ld_go, grad_in, ld_gi);
     });
     HETA_LAUNCH_CHECK("act_bwd_kernel");
+    return HETA_OK;
+}
+
+heta_status heta_act_bwd_multi(int32_t n, const int64_t *n_rows, const int32_t *d, heta_act act, const float *const *h, const int64_t *ld_h,
+                               const float *const *grad_out, const int64_t *ld_go, float *const *grad_in, const int64_t *ld_gi, void *hip_stream)
+{
+    if (n < 0 || (n > 0 && (!n_rows || !d || !grad_out || !ld_go || !grad_in || !ld_gi || (act == HETA_ACT_RELU && (!h || !ld_h)))))
+        return fail(HETA_ERR_INVALID_ARG, "heta_act_bwd_multi: null argument");
+    if (act != HETA_ACT_NONE && act != HETA_ACT_RELU) return fail(HETA_ERR_INVALID_ARG, "heta_act_bwd_multi: bad act");
+    const int relu = act == HETA_ACT_RELU;
+    bool vec = true;
+    for (int32_t i = 0; i < n; ++i) {
+        if (!grad_out[i] || !grad_in[i] || (relu && !h[i])) return fail(HETA_ERR_INVALID_ARG, "heta_act_bwd_multi: null argument");
+        if (n_rows[i] < 0 || d[i] <= 0 || ld_go[i] < d[i] || ld_gi[i] < d[i] || (relu && ld_h[i] < d[i]))
+            return fail(HETA_ERR_SHAPE, "heta_act_bwd_multi: bad shape");
+        if ((reinterpret_cast<uintptr_t>(grad_out[i]) & 3u) || (reinterpret_cast<uintptr_t>(grad_in[i]) & 3u) ||
+            (relu && (reinterpret_cast<uintptr_t>(h[i]) & 3u)))
+            return fail(HETA_ERR_INVALID_ARG, "heta_act_bwd_multi: pointer not 4-byte aligned");
+        vec = vec && d[i] % 4 == 0 && ld_go[i] % 4 == 0 && ld_gi[i] % 4 == 0 && aligned16(grad_out[i]) && aligned16(grad_in[i]) &&
+              (!relu || (ld_h[i] % 4 == 0 && aligned16(h[i])));
+    }
+    int64_t blocks = 0;
+    double bytes = 0;
+    for (int32_t i = 0; i < n; ++i) {
+        blocks += (n_rows[i] * (vec ? d[i] / 4 : d[i]) + 255) / 256;
+        bytes += (relu ? 3.0 : 2.0) * static_cast<double>(n_rows[i]) * d[i] * 4.0;
+    }
+    if (n > kMaxActs || blocks > max_blocks(256)) { // more than one launch takes: item by item
+        for (int32_t i = 0; i < n; ++i) {
+            heta_status e = heta_act_bwd(n_rows[i], d[i], act, relu ? h[i] : nullptr, relu ? ld_h[i] : d[i], grad_out[i], ld_go[i], grad_in[i], ld_gi[i],
+                                         hip_stream);
+            if (e != HETA_OK) return e;
+        }
+        return HETA_OK;
+    }
+    if (blocks == 0) return HETA_OK;
+    ActItems a{};
+    a.n = n;
+    a.relu = relu;
+    blocks = 0;
+    for (int32_t i = 0; i < n; ++i) {
+        a.h[i] = relu ? h[i] : nullptr;
+        a.ld_h[i] = relu ? ld_h[i] : 0;
+        a.go[i] = grad_out[i];
+        a.ld_go[i] = ld_go[i];
+        a.gi[i] = grad_in[i];
+        a.ld_gi[i] = ld_gi[i];
+        a.n_rows[i] = n_rows[i];
+        a.d[i] = d[i];
+        a.blk0[i] = static_cast<uint32_t>(blocks);
+        blocks += (n_rows[i] * (vec ? d[i] / 4 : d[i]) + 255) / 256;
+    }
+    a.blk0[n] = static_cast<uint32_t>(blocks);
+    ProfScope prof("act_bwd_kernel", as_stream(hip_stream), bytes, 0);
+    if (vec) hipLaunchKernelGGL(act_bwd_multi_kernel<4>, dim3((unsigned)blocks), dim3(256), 0, as_stream(hip_stream), a);
+    else hipLaunchKernelGGL(act_bwd_multi_kernel<1>, dim3((unsigned)blocks), dim3(256), 0, as_stream(hip_stream), a);
+    HETA_LAUNCH_CHECK("act_bwd_multi_kernel");
     return HETA_OK;
 }
 

@@ -148,9 +148,8 @@ class RafLayer:
 
     def _pre_project(self, stream):
         if self.pre_proj is not None:
-            for t, h0 in enumerate(self.H0):
-                if h0 is not None:
-                    hb.heta_project(self.tables[t], self.pre_proj[t], h0, stream=stream)
+            hb.heta_project_multi(self.g, [(h0.shape[0], [self.tables[t]], [self.pre_proj[t]], [h0]) for t, h0 in enumerate(self.H0) if h0 is not None],
+                                  stream=stream)
 
     def _aggregate_first_everywhere(self):
         """The per-relation and unfused call paths aggregate first: give every relation its M_r / dM_r."""
@@ -180,29 +179,31 @@ class RafLayer:
         """aggregate every relation, then one fused projection + cross-relation sum per type."""
         self._pre_project(stream)
         self._pf_active = set(self.pf)
-        for s, rs in self.rels_from.items():  # Z'_r = H0_s W_r for all project-first relations out of s, one launch
+        # Z'_r = H0_s W_r for all project-first relations, item by source type
+        items = []
+        for s, rs in self.rels_from.items():
             pfs = [r for r in rs if r in self.pf]
             for c in range(0, len(pfs), 8):
                 part = pfs[c:c + 8]
-                hb.heta_project_batch([self.source(s)] * len(part), [self.W[r] for r in part], [self.Zp[r] for r in part],
-                                      n_rows=self.g.ntypes[s][0], stream=stream, graph=self.g)
+                items.append((self.g.ntypes[s][0], [self.source(s)] * len(part), [self.W[r] for r in part], [self.Zp[r] for r in part]))
+        hb.heta_project_multi(self.g, items, stream=stream)
         # the relation-specific aggregations of a layer do not depend on each other: one call for all of them
         # (relations of one shape class share launches, which is what a sampled block's small relations need)
         self._aggregate_all([r for r in self.rels if r not in self.pf], stream)
-        into = []
+        # projection and cross-relation sum, item by destination type; a type's relations past the eighth add to it in rounds
+        into, sums = [], {}
         for t, all_rs in self.rels_into.items():
             rs = [r for r in all_rs if r not in self.pf]
             pfs = [r for r in all_rs if r in self.pf]
-            wrote = False
-            for c in range(0, len(rs), 8):  # the library takes up to 8 relations per call
+            for c in range(0, len(rs), 8):
                 part = rs[c:c + 8]
                 last = c + 8 >= len(rs) and not pfs
-                hb.heta_cross_rel_project(self.g, t, [self.M[r] for r in part], [self.W[r] for r in part], self.H[t],
-                                          act=self.act if last else hb.HETA_ACT_NONE, beta=0.0 if c == 0 else 1.0,
-                                          stream=stream)
-                wrote = True
+                sums.setdefault(c, []).append((self.g.ntypes[t][0], [self.M[r] for r in part], [self.W[r] for r in part], self.H[t],
+                                               self.act if last else hb.HETA_ACT_NONE, 0.0 if c == 0 else 1.0))
             if pfs:
-                into.append((t, pfs, wrote))
+                into.append((t, pfs, bool(rs)))
+        for c in sorted(sums):
+            hb.heta_project_multi(self.g, sums[c], sum=True, stream=stream)
         # Projected over the source rows above; aggregated at the output width into H_t.  Round k takes the k-th such
         # relation of every type (distinct outputs: one call), the rounds keep the order of each sum, and the last
         # relation of a type stores activated rows.
@@ -264,12 +265,16 @@ class RafLayer:
         first_for_src = {s: True for s in self.rels_from}
         pf_grads = []  # (project-first relation, its destination's gradient)
         per_src: Dict[int, list] = {}  # source type -> [(relation, dM_r)] in the order of the sum
+        grads = {t: G[t] for t in self.rels_into}
+        if self.relu:
+            ts = list(grads)
+            hb.heta_act_bwd_multi(hb.HETA_ACT_RELU, [self.H[t] for t in ts], [G[t] for t in ts], [self._Gact[t] for t in ts], stream=stream)
+            grads = {t: self._Gact[t] for t in ts}
+        wgrads, bwds = [], []
         for t, all_rs in self.rels_into.items():
             rs = [r for r in all_rs if r not in self._pf_active]
             pfs = [r for r in all_rs if r in self._pf_active]
-            g = G[t]
-            if self.relu:
-                g = hb.heta_act_bwd(hb.HETA_ACT_RELU, self.H[t], G[t], self._Gact[t], stream=stream)
+            g = grads[t]
             dM = self.dM
             if per_relation:
                 if self.m_dtype != torch.float32:
@@ -282,13 +287,13 @@ class RafLayer:
             else:
                 for c in range(0, len(rs), 8):
                     part = rs[c:c + 8]
-                    hb.heta_cross_rel_project_wgrad(self.g, t, [self.M[r] for r in part], g,
-                                                    [self.dW[r] for r in part], stream=stream)
-                    hb.heta_cross_rel_project_bwd(self.g, t, g, [self.W[r] for r in part],
-                                                  [self.dM[r] for r in part], stream=stream)
+                    wgrads.append((self.g.ntypes[t][0], [self.M[r] for r in part], [g] * len(part), [self.dW[r] for r in part]))
+                    bwds.append((self.g.ntypes[t][0], [g] * len(part), [self.W[r] for r in part], [self.dM[r] for r in part]))
             for r in rs:
                 per_src.setdefault(self.g.rels[r][0], []).append((r, dM[r]))
             pf_grads += [(r, g) for r in pfs]
+        hb.heta_project_wgrad_multi(self.g, wgrads, stream=stream)
+        hb.heta_project_multi(self.g, bwds, trans_w=True, stream=stream)
         for dtype in dict.fromkeys(g.dtype for _, g in pf_grads):  # dZ'_r = CSC gather of G_t over the source rows
             part = [(r, g) for r, g in pf_grads if g.dtype == dtype]
             hb.heta_rel_aggregate_bwd_multi(self.g, [r for r, _ in part], self.op, [g for _, g in part],
@@ -307,19 +312,21 @@ class RafLayer:
                                                 stream=stream)
         for s in per_src:
             first_for_src[s] = False
-        for s, rs in self.rels_from.items():  # per source type: dW_r = H0_s^T dZ'_r ; dH0_s += sum_r dZ'_r W_r^T
+        # per source type: dW_r = H0_s^T dZ'_r ; dH0_s += sum_r dZ'_r W_r^T
+        wgrads, sums = [], {}
+        for s, rs in self.rels_from.items():
             pfs = [r for r in rs if r in self._pf_active]
             for c in range(0, len(pfs), 8):
                 part = pfs[c:c + 8]
-                # dZ'_r sums G over a source's out-edges: fed to the bf16 MFMA as two terms so that its size does not show in dW
-                hb.heta_project_wgrad_batch(self.g, [self.source(s)] * len(part), [self.Ghat[r] for r in part],
-                                            [self.dW[r] for r in part], gout_two_terms=True, n_rows=self.g.ntypes[s][0],
-                                            stream=stream)
-                hb.heta_project_sum([self.Ghat[r] for r in part], [self.W[r] for r in part], self.dH0[s], trans_w=True,
-                                    beta=0.0 if first_for_src[s] else 1.0, n_rows=self.g.ntypes[s][0], stream=stream,
-                                    graph=self.g)
+                wgrads.append((self.g.ntypes[s][0], [self.source(s)] * len(part), [self.Ghat[r] for r in part], [self.dW[r] for r in part]))
+                sums.setdefault(c, []).append((self.g.ntypes[s][0], [self.Ghat[r] for r in part], [self.W[r] for r in part], self.dH0[s],
+                                               hb.HETA_ACT_NONE, 0.0 if first_for_src[s] else 1.0))
                 first_for_src[s] = False
+        # dZ'_r sums G over a source's out-edges: fed to the bf16 MFMA as two terms so that its size does not show in dW
+        hb.heta_project_wgrad_multi(self.g, wgrads, gout_two_terms=True, stream=stream)
+        for c in sorted(sums):
+            hb.heta_project_multi(self.g, sums[c], trans_w=True, sum=True, stream=stream)
         if self.pre_proj is not None:
-            for s, gh in self.dH0.items():
-                hb.heta_project(gh, self.pre_proj[s], self.dtable[s], trans_w=True, stream=stream)
+            hb.heta_project_multi(self.g, [(gh.shape[0], [gh], [self.pre_proj[s]], [self.dtable[s]]) for s, gh in self.dH0.items()], trans_w=True,
+                                  stream=stream)
         return self.dW, self.dH0, (self.dtable if self.pre_proj is not None else self.dH0)

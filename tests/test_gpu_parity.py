@@ -1539,3 +1539,96 @@ def test_edges_of_a_long_row_of_many_chunks_are_added_in_order(d, storage):
             assert torch.equal(out[row].cpu(), want), (row, d)
     finally:
         hg.destroy()
+
+
+# ---- the products of several node types in one call ----------------------------------------------------------
+
+def _padded_rand(g, n, d, dtype):
+    q = 16 // torch.empty(0, dtype=dtype).element_size()
+    x = torch.zeros((max(n, 1), (d + q - 1) // q * q), dtype=dtype, device="cuda")[:, :d]  # an address also without rows
+    x.copy_(torch.from_numpy(g.standard_normal((max(n, 1), d)).astype(np.float32)))
+    return x
+
+
+def _close(got, ref, storage):
+    scale = max(1.0, float(ref.abs().max())) if ref.numel() else 1.0
+    err = float((got.double() - ref).abs().max()) / scale if ref.numel() else 0.0
+    assert err <= (1e-5 if storage == "f32" else 1e-2), err  # as the layer tests guard their observed errors
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+@pytest.mark.parametrize("rows", [[0, 1, 63, 64], [65, 129, 1000, 4097], [300_000, 9000, 0, 257], [40, 50, 60, 70, 80, 90, 100, 110, 120]])
+def test_project_multi_against_fp64(rows, storage):
+    """Sums, independent products of several widths and transposed weights, for items that share a launch (by rows, widths and
+    their number: 8 calls and 16 products at most), items too large to, and items without rows."""
+    g = rng.stream("tests", f"project-multi/{storage}/{rows[0]}")
+    hg = heta.heta_graph_create([(1, 1, 0)], [(0, 0, np.zeros(2, dtype=np.int64), np.zeros(0, dtype=np.int32))])
+    dt = torch.float32 if storage == "f32" else torch.bfloat16
+    widths, depths = [7, 64, 65, 128, 200, 256, 300], [16, 24, 100, 128]
+    for trans in (False, True):
+        sums, singles, ref_sums, ref_singles = [], [], [], []
+        for i, n in enumerate(rows):
+            d_out, k = widths[i % len(widths)], 1 + i % 3
+            ins = [_padded_rand(g, n, depths[(i + p) % 4], dt if not trans else torch.float32) for p in range(k)]
+            Ws = [_padded_rand(g, *((d_out, x.shape[1]) if trans else (x.shape[1], d_out)), dt) for x in ins]
+            out = _padded_rand(g, n, d_out, torch.float32)
+            wide = [w.double().t() if trans else w.double() for w in Ws]
+            # the bf16 product rounds its fp32 operand
+            xs = [x.to(torch.bfloat16).double() if storage == "bf16" else x.double() for x in ins]
+            relu, beta = i % 2, float(i % 3 == 1)
+            total = beta * out.double() + sum(x @ w for x, w in zip(xs, wide))
+            ref_sums.append(total.relu() if relu else total)
+            sums.append((n, ins, Ws, out, heta.HETA_ACT_RELU if relu else heta.HETA_ACT_NONE, beta))
+            many = [_padded_rand(g, *((d, depths[0]) if trans else (depths[0], d)), dt) for d in (widths[i % 7], widths[(i + 1) % 7])]
+            x = _padded_rand(g, n, depths[0], dt if not trans else torch.float32)
+            outs = [_padded_rand(g, n, w.shape[0 if trans else 1], dt) for w in many]
+            x64 = x.to(torch.bfloat16).double() if storage == "bf16" else x.double()
+            ref_singles.append([x64 @ (w.double().t() if trans else w.double()) for w in many])
+            singles.append((n, [x, x], many, outs))
+        heta.heta_project_multi(hg, sums, trans_w=trans, sum=True)
+        heta.heta_project_multi(hg, singles, trans_w=trans)
+        for item, ref in zip(sums, ref_sums):
+            _close(item[3][:item[0]], ref[:item[0]], storage)
+        for item, refs in zip(singles, ref_singles):
+            for o, ref in zip(item[3], refs):
+                _close(o[:item[0]], ref[:item[0]], storage)
+    o = torch.zeros((64, 64), device="cuda")
+    w, x = torch.zeros((64, 64), device="cuda"), torch.zeros((64, 64), device="cuda")
+    with pytest.raises(heta.HetaError) as e:
+        heta.heta_project_multi(hg, [(64, [x], [w], [o]), (64, [x], [w], [o])])
+    assert e.value.status == heta.HETA_ERR_INVALID_ARG
+    hg.destroy()
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+@pytest.mark.parametrize("rows", [[1, 0, 31, 33], [127, 1000, 4097, 20_000], [200_000, 129, 64, 5000]])
+def test_wgrad_multi_against_fp64(rows, storage):
+    """Weight gradients of several node types: calls of one kind share a launch, of few and many rows, wide and narrow inputs
+    and outputs; a call without rows leaves zeros."""
+    g = rng.stream("tests", f"wgrad-multi/{storage}/{rows[0]}")
+    hg = heta.heta_graph_create([(1, 1, 0)], [(0, 0, np.zeros(2, dtype=np.int64), np.zeros(0, dtype=np.int32))])
+    dt = torch.float32 if storage == "f32" else torch.bfloat16
+    for d_out in (40, 64, 128, 256):
+        items, refs = [], []
+        for i, n in enumerate(rows):
+            d_ins = [[16], [128, 24], [300, 128], [64, 64, 100]][i % 4]
+            ins, go = [_padded_rand(g, n, d, dt) for d in d_ins], [_padded_rand(g, n, d_out, torch.float32) for _ in d_ins]
+            items.append((n, ins, go, [torch.full((d, d_out), 7.0, device="cuda") for d in d_ins]))
+            refs.append([x[:n].double().t() @ y[:n].double() for x, y in zip(ins, go)])
+        heta.heta_project_wgrad_multi(hg, items, gout_two_terms=True)
+        for item, ref in zip(items, refs):
+            for w, r in zip(item[3], ref):
+                _close(w, r, "f32" if storage == "f32" else "bf16")
+    hg.destroy()
+
+
+@pytest.mark.parametrize("d,n_items", [(64, 4), (7, 3), (100, 17)])
+def test_act_bwd_multi(d, n_items):
+    """Gradients of several node types behind a ReLU, vectorised or not, in one launch or (more than 16) one by one."""
+    g = rng.stream("tests", f"act-multi/{d}")
+    rows = [1 + (97 * i * i) % 1000 for i in range(n_items)]
+    h, go = ([torch.from_numpy(g.standard_normal((n, d)).astype(np.float32)).cuda() for n in rows] for _ in range(2))
+    gi = [torch.full_like(x, 5.0) for x in go]
+    heta.heta_act_bwd_multi(heta.HETA_ACT_RELU, h, go, gi)
+    for a, b, c in zip(h, go, gi):
+        assert torch.equal(c, torch.where(a > 0, b, torch.zeros_like(b)))
