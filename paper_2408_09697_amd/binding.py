@@ -106,13 +106,19 @@ def load_library() -> ctypes.CDLL:
     L.heta_rel_aggregate_fwd_noalloc.argtypes = L.heta_rel_aggregate_fwd.argtypes
     L.heta_rel_aggregate_bwd.argtypes = [vp, i32, i32, vp, i32, i64, i32, vp, i64, f32, vp]
     L.heta_rel_aggregate_fwd_multi.argtypes = [vp, i32, ctypes.POINTER(_AggItem), i32, i32, i32, vp]
-    L.heta_rel_aggregate_fwd_multi_act.argtypes = [vp, i32, ctypes.POINTER(_AggItem), ctypes.POINTER(i32), i32, i32, i32, vp]
-    L.heta_rel_aggregate_bwd_multi.argtypes = [vp, i32, ctypes.POINTER(_AggItem), i32, i32, vp]
     L.heta_project.argtypes = [i64, vp, i32, i64, i32, vp, i32, i64, i32, i32, vp, vp, i32, i64, f32, vp]
     L.heta_rel_project.argtypes = [vp, i32, vp, i32, i64, i32, vp, i32, i64, i32, i32, vp, vp, i32, i64, f32, vp]
     L.heta_rel_project_wgrad.argtypes = [vp, i32, vp, i32, i64, i32, vp, i64, i32, vp, i64, f32, vp]
     L.heta_cross_rel_reduce.argtypes = [vp, i32, vp, i32, i64, i32, i32, vp, i64, vp]
     L.heta_act_bwd.argtypes = [i64, i32, i32, vp, i64, vp, i64, vp, i64, vp]
+    L.heta_project_multi.argtypes = [vp, i32, vp, vp, i32, vp, i32, vp, vp, vp, i32, vp, vp, i32, vp, i32, vp, vp, vp, vp]
+    L.heta_project_wgrad_multi.argtypes = [vp, i32, vp, vp, vp, i32, vp, vp, vp, vp, vp, vp, vp, i32, vp]
+    L.heta_act_bwd_multi.argtypes = [i32, vp, vp, i32, vp, vp, vp, vp, vp, vp, vp]
+    L.heta_rel_aggregate_fwd_multi_act.argtypes = [vp, i32, vp, vp, i32, i32, i32, vp]
+    L.heta_rel_aggregate_bwd_multi.argtypes = [vp, i32, vp, i32, i32, vp]
+    L.heta_sparse_adam_multi.argtypes = [i32, vp, f32, f32, f32, f32, i64, vp]
+    L.heta_sample_hop.argtypes = [vp, i32, vp, vp, vp, i32, vp, vp, vp, vp, vp, vp, vp, vp]
+    L.heta_graph_create_batch.argtypes = [i32, vp, vp, vp, vp, u32, vp]
     for name in EXPORTS + TEST_HOOKS:
         getattr(L, name).restype = ctypes.c_int
     L.heta_last_error.restype = ctypes.c_char_p
@@ -126,6 +132,9 @@ def load_library() -> ctypes.CDLL:
 def _check(st: int) -> None:
     if st != HETA_OK:
         raise HetaError(st, load_library().heta_last_error().decode())
+
+
+_DT = {torch.float32: HETA_F32, torch.bfloat16: HETA_BF16}
 
 
 def _dt(t: torch.Tensor) -> int:
@@ -147,6 +156,36 @@ def _dev(t: Optional[torch.Tensor], name: str, dtype=None) -> Optional[int]:
     if dtype is not None and t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
     return t.data_ptr()
+
+
+def _mat(t: torch.Tensor, name: str, dtype: torch.dtype):
+    """(address, leading dimension, rows, columns) of a device matrix; every attribute is read once (100 to 200 ns each, a
+    dozen matrices per call: a mini-batch's launches wait for this)."""
+    if not t.is_cuda:
+        raise TypeError(f"{name} must be a device tensor")
+    if t.dtype is not dtype:
+        raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
+    rows, cols = t.shape
+    ld, inner = t.stride()
+    if inner != 1 and cols > 1 and rows:
+        raise TypeError(f"{name}: last dimension must be contiguous")
+    return t.data_ptr(), ld, rows, cols
+
+
+def _vec(t: torch.Tensor, name: str, dtype: torch.dtype):
+    """(address, length) of a contiguous device vector."""
+    if not t.is_cuda:
+        raise TypeError(f"{name} must be a device tensor")
+    if t.dtype is not dtype:
+        raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
+    if not t.is_contiguous():
+        raise TypeError(f"{name}: last dimension must be contiguous")
+    return t.data_ptr(), t.numel()
+
+
+def _pack(fmt: str, vals) -> bytes:
+    """Host array argument of a call (the bytes live as long as the call): i 32-bit, q 64-bit, Q addresses, f floats."""
+    return struct.pack("%d%s" % (len(vals), fmt), *vals)
 
 
 def _ld(t: torch.Tensor) -> int:
@@ -208,6 +247,11 @@ _REL_PACK = struct.Struct("=iiqQQQQi4x")     # heta_relation
 assert _NT_PACK.size == ctypes.sizeof(_NType) and _REL_PACK.size == ctypes.sizeof(_Relation)
 
 
+_AGG_PACK = struct.Struct("=iiQqqQQqf4x")    # heta_agg_item
+_ADAM_PACK = struct.Struct("=Qi4xqi4xqQQqQqQq")  # heta_adam_item
+assert _AGG_PACK.size == ctypes.sizeof(_AggItem) and _ADAM_PACK.size == ctypes.sizeof(_AdamItem)
+
+
 def _marshal_graph(ntypes: Sequence[Sequence[int]], relations: Sequence[Sequence], flags: int):
     """The C arrays of one heta_graph_create call (packed byte buffers laid out as heta_ntype[] and
     heta_relation[]), what keeps their memory alive, and the relations' (s, t, E)."""
@@ -224,9 +268,8 @@ def _marshal_graph(ntypes: Sequence[Sequence[int]], relations: Sequence[Sequence
         csc = extras.get("csc") if extras else None
         ccp = crp = 0
         if on_device:
-            rp = _dev(rowptr, "rowptr", torch.int64)
-            cp = _dev(col, "col", torch.int32)
-            n_e = int(col.numel())
+            rp, _ = _vec(rowptr, "rowptr", torch.int64)
+            cp, n_e = _vec(col, "col", torch.int32)
             if csc is not None:
                 ccp, crp = _dev(csc[0], "csc colptr", torch.int64), _dev(csc[1], "csc row", torch.int32)
                 keep += list(csc)
@@ -270,7 +313,6 @@ def heta_graph_create_batch(graphs: Sequence[Sequence], flags: int = 0) -> List[
         return []
     parts = [_marshal_graph(nts, rels, flags) for nts, rels in graphs]
     vp, i32 = ctypes.c_void_p, ctypes.c_int32
-    L.heta_graph_create_batch.argtypes = [i32, vp, vp, vp, vp, ctypes.c_uint32, vp]
     nt_ptrs = (vp * n)(*[ctypes.addressof(p[0]) for p in parts])
     rl_ptrs = (vp * n)(*[ctypes.addressof(p[1]) for p in parts])
     n_nt = (i32 * n)(*[len(g[0]) for g in graphs])
@@ -381,23 +423,22 @@ def heta_rel_aggregate_fwd_multi_act(g: Graph, rels: Sequence[int], acts: Option
     n = len(rels)
     if n == 0:
         return
-    items = (_AggItem * n)()
+    in_dt, out_dt = src_tables[0].dtype, outs[0].dtype
+    items = []
     for i, r in enumerate(rels):
         x, o = src_tables[i], outs[i]
         gid = None if src_gids is None else src_gids[i]
-        if o.shape[0] < g.n_dst(r):
+        if x.dtype is not in_dt or o.dtype is not out_dt:
+            raise HetaError(HETA_ERR_INVALID_ARG, "the items of one call share their element types")
+        px, lx, rx, cx = _mat(x, "src_table", in_dt)
+        po, lo, ro, _ = _mat(o, "out", out_dt)
+        if ro < g.n_dst(r):
             raise HetaError(HETA_ERR_SHAPE, "out has fewer rows than the relation has destinations")
         if gid is not None and gid.numel() < g.n_src(r):
             raise HetaError(HETA_ERR_SHAPE, "src_gid has fewer entries than the relation has sources")
-        if x.dtype != src_tables[0].dtype or o.dtype != outs[0].dtype:
-            raise HetaError(HETA_ERR_INVALID_ARG, "the items of one call share their element types")
-        it = items[i]
-        it.rel, it.d = r, (x.shape[1] if d is None else d[i])
-        it.inp, it.ld_in, it.n_table_rows = _dev(x, "src_table"), _ld(x), x.shape[0]
-        it.src_gid = _dev(gid, "src_gid", torch.int64)
-        it.out, it.ld_out = _dev(o, "out"), _ld(o)
-        it.beta = 0.0 if betas is None else betas[i]
-    _check(load_library().heta_rel_aggregate_fwd_multi_act(g.handle, n, items, None if acts is None else (ctypes.c_int32 * n)(*acts), op,
+        items.append(_AGG_PACK.pack(r, cx if d is None else d[i], px, lx, rx, _dev(gid, "src_gid", torch.int64) or 0, po, lo,
+                                    0.0 if betas is None else betas[i]))
+    _check(load_library().heta_rel_aggregate_fwd_multi_act(g.handle, n, b"".join(items), None if acts is None else _pack("i", acts), op,
                                                            _dt(src_tables[0]), _dt(outs[0]), _stream(stream)))
 
 
@@ -408,19 +449,18 @@ def heta_rel_aggregate_bwd_multi(g: Graph, rels: Sequence[int], op: int, grad_ou
     n = len(rels)
     if n == 0:
         return
-    items = (_AggItem * n)()
+    in_dt = grad_outs[0].dtype
+    items = []
     for i, r in enumerate(rels):
         x, o = grad_outs[i], grad_srcs[i]
-        if x.shape[0] < g.n_dst(r) or o.shape[0] < g.n_src(r):
-            raise HetaError(HETA_ERR_SHAPE, "gradient buffers have fewer rows than the relation needs")
-        if x.dtype != grad_outs[0].dtype:
+        if x.dtype is not in_dt:
             raise HetaError(HETA_ERR_INVALID_ARG, "the items of one call share their element types")
-        it = items[i]
-        it.rel, it.d = r, (x.shape[1] if d is None else d[i])
-        it.inp, it.ld_in, it.n_table_rows, it.src_gid = _dev(x, "grad_out"), _ld(x), 0, None
-        it.out, it.ld_out = _dev(o, "grad_src", torch.float32), _ld(o)
-        it.beta = 0.0 if betas is None else betas[i]
-    _check(load_library().heta_rel_aggregate_bwd_multi(g.handle, n, items, op, _dt(grad_outs[0]), _stream(stream)))
+        px, lx, rx, cx = _mat(x, "grad_out", in_dt)
+        po, lo, ro, _ = _mat(o, "grad_src", torch.float32)
+        if rx < g.n_dst(r) or ro < g.n_src(r):
+            raise HetaError(HETA_ERR_SHAPE, "gradient buffers have fewer rows than the relation needs")
+        items.append(_AGG_PACK.pack(r, cx if d is None else d[i], px, lx, 0, 0, po, lo, 0.0 if betas is None else betas[i]))
+    _check(load_library().heta_rel_aggregate_bwd_multi(g.handle, n, b"".join(items), op, _dt(grad_outs[0]), _stream(stream)))
 
 
 def _w_ld(W: torch.Tensor) -> int:
@@ -595,32 +635,41 @@ def heta_project_multi(g: Graph, items: Sequence[Sequence], trans_w: bool = Fals
             heta_project_multi(g, part, trans_w, sum, stream)
         return
     (dtypes, items), = by_dtype.items()
-    first, rows, outs, acts, betas, x_all, w_all = [0], [], [], [], [], [], []
+    in_dt, w_dt, out_dt = dtypes
+    if any(d not in _DT for d in dtypes):
+        raise TypeError(f"unsupported tensor dtypes {dtypes}")
+    first, rows, acts, betas = [0], [], [], []
+    p_in, ld_in, depth, p_w, ld_w, width, p_out, ld_out = [], [], [], [], [], [], [], []
     for it in items:
         n_rows, ins, Ws, out = it[:4]
         mine = [out] if sum else out
         if len(ins) != len(Ws) or (not sum and len(ins) != len(mine)):
             raise HetaError(HETA_ERR_SHAPE, "bad arguments")
-        for x, w, o in zip(ins, Ws, mine * len(ins) if sum else mine):
-            k, n = (w.shape[1], w.shape[0]) if trans_w else w.shape
-            if k != x.shape[1] or x.shape[0] < n_rows or o.shape[0] < n_rows or o.shape[1] < n or (x.dtype, w.dtype, o.dtype) != dtypes:
+        for x, w in zip(ins, Ws):
+            if x.dtype is not in_dt or w.dtype is not w_dt:
                 raise HetaError(HETA_ERR_SHAPE, "inputs / weights / outputs do not match")
-        x_all += ins
-        w_all += Ws
-        outs += mine
+            px, lx, rx, cx = _mat(x, "in", in_dt)
+            pw, lw, k, n = _mat(w, "W", w_dt)
+            if trans_w:
+                k, n = n, k
+            if k != cx or rx < n_rows:
+                raise HetaError(HETA_ERR_SHAPE, "inputs / weights / outputs do not match")
+            p_in.append(px), ld_in.append(lx), depth.append(k), p_w.append(pw), ld_w.append(lw), width.append(n)
+        for o, n in zip(mine, width[first[-1]:]):
+            if o.dtype is not out_dt:
+                raise HetaError(HETA_ERR_SHAPE, "inputs / weights / outputs do not match")
+            po, lo, ro, co = _mat(o, "out", out_dt)
+            if ro < n_rows or co < n:
+                raise HetaError(HETA_ERR_SHAPE, "inputs / weights / outputs do not match")
+            p_out.append(po), ld_out.append(lo)
         rows.append(n_rows)
         acts.append(it[4] if len(it) > 4 else HETA_ACT_NONE)
         betas.append(it[5] if len(it) > 5 else 0.0)
-        first.append(len(x_all))
-    in_dt, w_dt, out_dt = dtypes
-    vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
-    L = load_library()
-    L.heta_project_multi.argtypes = [vp, i32, vp, vp, i32, vp, i32, vp, vp, vp, i32, vp, vp, i32, vp, i32, vp, vp, vp, vp]
-    _check(L.heta_project_multi(g.handle, len(items), _i32_array(first), _i64_array(rows), int(sum), _ptr_array(x_all, "in", in_dt), _dt(x_all[0]),
-                                _i64_array([_ld(x) for x in x_all]), _i32_array([x.shape[1] for x in x_all]), _ptr_array(w_all, "W", w_dt), _dt(w_all[0]),
-                                _i64_array([w.stride(0) for w in w_all]), _i32_array([w.shape[0 if trans_w else 1] for w in w_all]), int(trans_w),
-                                _ptr_array(outs, "out", out_dt), _dt(outs[0]), _i64_array([_ld(o) for o in outs]),
-                                _i32_array(acts) if sum else None, (ctypes.c_float * len(betas))(*betas) if sum else None, _stream(stream)))
+        first.append(len(p_in))
+    _check(load_library().heta_project_multi(
+        g.handle, len(items), _pack("i", first), _pack("q", rows), int(sum), _pack("Q", p_in), _DT[in_dt], _pack("q", ld_in), _pack("i", depth),
+        _pack("Q", p_w), _DT[w_dt], _pack("q", ld_w), _pack("i", width), int(trans_w), _pack("Q", p_out), _DT[out_dt], _pack("q", ld_out),
+        _pack("i", acts) if sum else None, _pack("f", betas) if sum else None, _stream(stream)))
 
 
 def heta_project_wgrad_multi(g: Graph, items: Sequence[Sequence], gout_two_terms: bool = False, stream=None) -> None:
@@ -634,26 +683,28 @@ def heta_project_wgrad_multi(g: Graph, items: Sequence[Sequence], gout_two_terms
             heta_project_wgrad_multi(g, part, gout_two_terms, stream)
         return
     (dtype, items), = by_dtype.items()
-    first, x_all, g_all, w_all = [0], [], [], []
+    if dtype not in _DT:
+        raise TypeError(f"unsupported tensor dtype {dtype}")
+    first, d_outs = [0], []
+    p_in, ld_in, d_in, p_go, ld_go, p_dw, ld_dw = [], [], [], [], [], [], []
     for n_rows, ins, gouts, dW in items:
         if len(ins) != len(gouts) or len(ins) != len(dW):
             raise HetaError(HETA_ERR_SHAPE, "bad arguments")
         d_out = gouts[0].shape[1]
         for x, go, w in zip(ins, gouts, dW):
-            if x.shape[0] < n_rows or go.shape[0] < n_rows or go.shape[1] != d_out or w.shape[0] < x.shape[1] or w.shape[1] < d_out or x.dtype != dtype:
+            if x.dtype is not dtype:
                 raise HetaError(HETA_ERR_SHAPE, "inputs / gradients do not match")
-        x_all += ins
-        g_all += gouts
-        w_all += dW
-        first.append(len(x_all))
-    vp, i32 = ctypes.c_void_p, ctypes.c_int32
-    L = load_library()
-    L.heta_project_wgrad_multi.argtypes = [vp, i32, vp, vp, vp, i32, vp, vp, vp, vp, vp, vp, vp, i32, vp]
-    _check(L.heta_project_wgrad_multi(g.handle, len(items), _i32_array(first), _i64_array([it[0] for it in items]), _ptr_array(x_all, "in", x_all[0].dtype),
-                                      _dt(x_all[0]), _i64_array([_ld(x) for x in x_all]), _i32_array([x.shape[1] for x in x_all]),
-                                      _ptr_array(g_all, "gout", torch.float32), _i64_array([_ld(x) for x in g_all]),
-                                      _i32_array([it[2][0].shape[1] for it in items]), _ptr_array(w_all, "dW", torch.float32),
-                                      _i64_array([_ld(w) for w in w_all]), int(gout_two_terms), _stream(stream)))
+            px, lx, rx, cx = _mat(x, "in", dtype)
+            pg, lg, rg, cg = _mat(go, "gout", torch.float32)
+            pw, lw, rw, cw = _mat(w, "dW", torch.float32)
+            if rx < n_rows or rg < n_rows or cg != d_out or rw < cx or cw < d_out:
+                raise HetaError(HETA_ERR_SHAPE, "inputs / gradients do not match")
+            p_in.append(px), ld_in.append(lx), d_in.append(cx), p_go.append(pg), ld_go.append(lg), p_dw.append(pw), ld_dw.append(lw)
+        d_outs.append(d_out)
+        first.append(len(p_in))
+    _check(load_library().heta_project_wgrad_multi(
+        g.handle, len(items), _pack("i", first), _pack("q", [it[0] for it in items]), _pack("Q", p_in), _DT[dtype], _pack("q", ld_in), _pack("i", d_in),
+        _pack("Q", p_go), _pack("q", ld_go), _pack("i", d_outs), _pack("Q", p_dw), _pack("q", ld_dw), int(gout_two_terms), _stream(stream)))
 
 
 def heta_cross_rel_project_bwd(g: Graph, dst_type: int, gout: torch.Tensor, Ws: List[torch.Tensor],
@@ -734,16 +785,15 @@ def heta_act_bwd_multi(act: int, hs: Sequence[torch.Tensor], grads_out: Sequence
     n = len(grads_out)
     if n == 0:
         return
-    for h, go, gi in zip(hs, grads_out, grads_in):
-        if gi.shape[0] < go.shape[0] or gi.shape[1] < go.shape[1] or h.shape[0] < go.shape[0] or h.shape[1] < go.shape[1]:
+    f32 = torch.float32
+    mh, mo, mi = [_mat(h, "h", f32) for h in hs], [_mat(x, "grad_out", f32) for x in grads_out], [_mat(x, "grad_in", f32) for x in grads_in]
+    for h, go, gi in zip(mh, mo, mi):
+        if gi[2] < go[2] or gi[3] < go[3] or h[2] < go[2] or h[3] < go[3]:
             raise HetaError(HETA_ERR_SHAPE, "buffers too small")
-    vp, i32 = ctypes.c_void_p, ctypes.c_int32
-    L = load_library()
-    L.heta_act_bwd_multi.argtypes = [i32, vp, vp, i32, vp, vp, vp, vp, vp, vp, vp]
-    _check(L.heta_act_bwd_multi(n, _i64_array([x.shape[0] for x in grads_out]), _i32_array([x.shape[1] for x in grads_out]), act,
-                                _ptr_array(hs, "h", torch.float32), _i64_array([_ld(x) for x in hs]), _ptr_array(grads_out, "grad_out", torch.float32),
-                                _i64_array([_ld(x) for x in grads_out]), _ptr_array(grads_in, "grad_in", torch.float32),
-                                _i64_array([_ld(x) for x in grads_in]), _stream(stream)))
+    col = lambda m, j: [x[j] for x in m]  # noqa: E731
+    _check(load_library().heta_act_bwd_multi(n, _pack("q", col(mo, 2)), _pack("i", col(mo, 3)), act, _pack("Q", col(mh, 0)), _pack("q", col(mh, 1)),
+                                             _pack("Q", col(mo, 0)), _pack("q", col(mo, 1)), _pack("Q", col(mi, 0)), _pack("q", col(mi, 1)),
+                                             _stream(stream)))
 
 
 class _KernelStat(ctypes.Structure):
@@ -784,20 +834,19 @@ def heta_sparse_adam_multi(items: Sequence[Sequence], lr: float = 1e-3, beta1: f
     n = len(items)
     if n == 0:
         return
-    arr = (_AdamItem * n)()
-    for i, (table, m, v, grad, ids) in enumerate(items):
-        rows = grad.shape[0]
+    f32 = torch.float32
+    arr = []
+    for table, m, v, grad, ids in items:
+        pt, lt, rt, d = _mat(table, "table", table.dtype)
+        pm, lm, rm, _ = _mat(m, "m", f32)
+        pv, _, rv, _ = _mat(v, "v", f32)
+        pg, lg, rows, _ = _mat(grad, "grad", f32)
         if ids is not None and ids.numel() < rows:
             raise HetaError(HETA_ERR_SHAPE, "fewer ids than gradient rows")
-        if m.shape[0] < table.shape[0] or v.shape[0] < table.shape[0]:
+        if rm < rt or rv < rt:
             raise HetaError(HETA_ERR_SHAPE, "optimizer states have fewer rows than the table")
-        arr[i] = _AdamItem(_dev(table, "table"), _dt(table), _ld(table), table.shape[1], table.shape[0],
-                           _dev(m, "m", torch.float32), _dev(v, "v", torch.float32), _ld(m), _dev(ids, "ids", torch.int64),
-                           rows, _dev(grad, "grad", torch.float32), _ld(grad))
-    L = load_library()
-    vp, i32, i64, f32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float
-    L.heta_sparse_adam_multi.argtypes = [i32, vp, f32, f32, f32, f32, i64, vp]
-    _check(L.heta_sparse_adam_multi(n, ctypes.addressof(arr), lr, beta1, beta2, eps, int(step), _stream(stream)))
+        arr.append(_ADAM_PACK.pack(pt, _dt(table), lt, d, rt, pm, pv, lm, _dev(ids, "ids", torch.int64) or 0, rows, pg, lg))
+    _check(load_library().heta_sparse_adam_multi(n, b"".join(arr), lr, beta1, beta2, eps, int(step), _stream(stream)))
 
 
 def _scores(t: torch.Tensor, name: str, rows: int, heads: int) -> int:
@@ -1218,22 +1267,19 @@ def heta_sample_hop(g: Graph, rels: Sequence[int], dst_ids: Sequence[torch.Tenso
     at_s, at_l = src.data_ptr(), local.data_ptr()
     for k, c in zip(sizes, caps):
         a_rp.append(at)
-        a_src.append(at_s if c else None)
-        a_local.append(at_l if c else None)
+        a_src.append(at_s if c else 0)
+        a_local.append(at_l if c else 0)
         at += 8 * (k + 1)
         at_s += 8 * c
         at_l += 4 * c
     for c in uniq_caps:
-        a_uniq.append(at if c else None)
+        a_uniq.append(at if c else 0)
         at += 8 * c
-    vp, i32, i64, u64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_uint64
-    m = max(1, n)
-    counts, n_unique = (i64 * m)(), (i64 * n_types)()
-    L = load_library()
-    L.heta_sample_hop.argtypes = [vp, i32, vp, vp, vp, i32, vp, vp, vp, vp, vp, vp, vp, vp]
-    _check(L.heta_sample_hop(g.handle, n, (i32 * m)(*[int(r) for r in rels]), (vp * m)(*[_dev(d, "dst_ids", torch.int64) if k else None for d, k in zip(dst_ids, sizes)]),
-                             (i64 * m)(*sizes), int(fanout), (u64 * m)(*[int(x) & ((1 << 64) - 1) for x in seeds]), (vp * m)(*a_rp), (vp * m)(*a_src),
-                             (vp * m)(*a_local), counts, (vp * n_types)(*a_uniq), n_unique, _stream(stream)))
+    counts, n_unique = (ctypes.c_int64 * max(1, n))(), (ctypes.c_int64 * n_types)()
+    _check(load_library().heta_sample_hop(
+        g.handle, n, _pack("i", rels), _pack("Q", [_dev(d, "dst_ids", torch.int64) if k else 0 for d, k in zip(dst_ids, sizes)]), _pack("q", sizes),
+        int(fanout), _pack("Q", [int(x) & ((1 << 64) - 1) for x in seeds]), _pack("Q", a_rp), _pack("Q", a_src), _pack("Q", a_local),
+        ctypes.addressof(counts), _pack("Q", a_uniq), ctypes.addressof(n_unique), _stream(stream)))
     # views of the written parts, in one call per buffer
     parts = [k + 1 for k in sizes]
     for c, used in zip(uniq_caps, n_unique):

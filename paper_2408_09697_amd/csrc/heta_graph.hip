@@ -47,40 +47,71 @@ heta_status fail(heta_status st, const char *fmt, ...)
 }
 
 // ---- recycled device blocks for short-lived scratch ---------------------------------------------------
-// Sampling a mini-batch and ingesting its blocks makes dozens of small allocations per iteration; each
-// hipMalloc / hipFree pair costs tens of microseconds and hipFree waits for the device.  Blocks of up to
-// 16 MiB are rounded to a power of two and kept on a free list per (device, size) when released, up to
-// 256 MiB in total; larger ones go straight to hipMalloc / hipFree.  A block must be idle when it is
-// released (the callers synchronise first).
+// Sampling a mini-batch, ingesting its blocks and the split sums of its weight gradients make dozens of allocations per
+// iteration; each hipMalloc / hipFree pair costs tens of microseconds, hundreds from some 100 MB on, and hipFree waits for
+// the device.  Blocks of up to 256 MiB (the partial weight gradients of two blocks of 4,096 seeds, 768 x 1,024: 30 to 130 MB)
+// are rounded up to a power of two, above 16 MiB to a quarter of one, and kept on a free list per (device, size) when
+// released, up to 1 GiB in total; larger ones go straight to hipMalloc / hipFree.  The list goes back to the device when
+// an allocation fails.  A block must be idle when it is released (the callers synchronise first).
 namespace {
-constexpr size_t kPoolMaxBlock = size_t(16) << 20, kPoolMaxCached = size_t(256) << 20;
+constexpr size_t kPoolMaxBlock = size_t(256) << 20, kPoolMaxCached = size_t(1) << 30;
 std::mutex g_pool_mu;
 std::unordered_map<void *, std::pair<int, size_t>> g_pool_blocks;     // live pooled block -> (device, size class)
 std::map<std::pair<int, size_t>, std::vector<void *>> g_pool_free;
 size_t g_pool_cached = 0;
+
+size_t pool_class(size_t bytes)
+{
+    size_t cls = 256;
+    while (cls < bytes) cls <<= 1;
+    if (cls <= size_t(16) << 20) return cls;
+    const size_t step = cls / 8; // a quarter of the power of two below
+    return (bytes + step - 1) / step * step;
+}
+
+// everything on the current device's free lists back to the device
+void pool_give_back(int dev)
+{
+    std::vector<void *> blocks;
+    {
+        std::lock_guard<std::mutex> lk(g_pool_mu);
+        for (auto it = g_pool_free.lower_bound({dev, 0}); it != g_pool_free.end() && it->first.first == dev; it = g_pool_free.erase(it))
+            for (void *p : it->second) {
+                blocks.push_back(p);
+                g_pool_blocks.erase(p);
+                g_pool_cached -= it->first.second;
+            }
+    }
+    for (void *p : blocks) (void)hipFree(p);
+}
 } // namespace
 
 hipError_t scratch_alloc(void **out, size_t bytes)
 {
     *out = nullptr;
-    size_t cls = 256;
-    while (cls < bytes) cls <<= 1;
-    if (cls > kPoolMaxBlock) return hipMalloc(out, bytes);
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
-    {
+    const bool pooled = bytes <= kPoolMaxBlock;
+    const size_t cls = pooled ? pool_class(bytes) : bytes;
+    if (pooled) {
         std::lock_guard<std::mutex> lk(g_pool_mu);
-        auto it = g_pool_free.find({dev, cls});
-        if (it != g_pool_free.end() && !it->second.empty()) {
-            *out = it->second.back();
-            it->second.pop_back();
-            g_pool_cached -= cls;
-            return hipSuccess;
-        }
+        // the smallest block that is large enough, but not of twice the size
+        for (auto it = g_pool_free.lower_bound({dev, cls}); it != g_pool_free.end() && it->first.first == dev && it->first.second < 2 * cls; ++it)
+            if (!it->second.empty()) {
+                *out = it->second.back();
+                it->second.pop_back();
+                g_pool_cached -= it->first.second;
+                return hipSuccess;
+            }
     }
     e = hipMalloc(out, cls);
-    if (e != hipSuccess) return e;
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        pool_give_back(dev);
+        e = hipMalloc(out, cls);
+    }
+    if (e != hipSuccess || !pooled) return e;
     std::lock_guard<std::mutex> lk(g_pool_mu);
     g_pool_blocks[*out] = {dev, cls};
     return hipSuccess;

@@ -7,6 +7,7 @@ the local backward.  It computes nothing itself.
 """
 from __future__ import annotations
 
+from functools import cached_property
 from typing import Dict, List, Optional, Sequence
 
 import torch
@@ -100,7 +101,8 @@ class RafLayer:
         # keeps awkward widths (7, 300, 789, ...) on the library's 128-bit paths
         def padded(n, d, dtype):
             q = 16 // dtype.itemsize
-            return torch.empty((n, (d + q - 1) // q * q), dtype=dtype, device=dev)[:, :d]
+            x = torch.empty((n, (d + q - 1) // q * q), dtype=dtype, device=dev)
+            return x[:, :d] if d % q else x
 
         # Aggregation and projection commute (Eq. 1 is linear in H0).  A relation can be projected
         # first: Z'_r = H0_s W_r over the source rows, then aggregated at the output width straight
@@ -125,23 +127,42 @@ class RafLayer:
         self._padded = padded
         self._m_shapes = {r: (graph.n_dst(r), self.d_rel[r]) for r in self.rels}
         self.M = {r: padded(graph.n_dst(r), self.d_rel[r], m_dtype) for r in self.rels if r not in self.pf}
-        # dM_r, like the saved M_r, is an [n x d] intermediate that the backward aggregation re-reads once
-        # per edge: it is kept in the storage type (bf16 tables -> bf16 dM_r, fp32 accumulation around it)
-        self.dM = {r: padded(graph.n_dst(r), self.d_rel[r], m_dtype) for r in self.rels if r not in self.pf}
         self._dM32 = None  # fp32 dM_r for the per-relation call path, whose projection writes fp32
         self.Zp = {r: padded(graph.n_src(r), d_out, m_dtype) for r in self.pf}
-        self.Ghat = {r: padded(graph.n_src(r), d_out, torch.float32) for r in self.pf}
         self.H = {t: torch.empty((graph.ntypes[t][0], d_out), dtype=torch.float32, device=dev)
                   for t in self.rels_into}
-        self.dW = {r: torch.empty((self.d_rel[r], d_out), dtype=torch.float32, device=dev) for r in self.rels}
-        self.dH0 = {s: padded(graph.ntypes[s][0], self.d_rel[rs[0]], torch.float32)
-                    for s, rs in self.rels_from.items()}
-        self.dtable: Dict[int, torch.Tensor] = {}
-        if self.pre_proj is not None:
-            for s in self.rels_from:
-                self.dtable[s] = torch.empty((self.tables[s].shape[0], self.pre_proj[s].shape[0]),
-                                             dtype=torch.float32, device=dev)
-        self._Gact = ({t: torch.empty_like(h) for t, h in self.H.items()} if relu else {})
+        # The backward's buffers: now, so that no pass allocates - but for a sampled block's layer (a row map, a part of the
+        # relations), which lives for one pass, when they are first asked for: one that serves never needs them.
+        if src_gid is None and rels is None:
+            _ = self.dM, self.Ghat, self.dW, self.dH0, self.dtable, self._Gact
+
+    @cached_property
+    def dM(self) -> Dict[int, torch.Tensor]:
+        """dM_r, like the saved M_r, is an [n x d] intermediate that the backward aggregation re-reads once per edge: it is
+        kept in the storage type (bf16 tables -> bf16 dM_r, fp32 accumulation around it)."""
+        return {r: self._padded(self.g.n_dst(r), self.d_rel[r], self.m_dtype) for r in self.M}
+
+    @cached_property
+    def Ghat(self) -> Dict[int, torch.Tensor]:
+        return {r: self._padded(self.g.n_src(r), self.d_out, torch.float32) for r in self.pf}
+
+    @cached_property
+    def dW(self) -> Dict[int, torch.Tensor]:
+        return {r: torch.empty((self.d_rel[r], self.d_out), dtype=torch.float32, device=self.dev) for r in self.rels}
+
+    @cached_property
+    def dH0(self) -> Dict[int, torch.Tensor]:
+        return {s: self._padded(self.g.ntypes[s][0], self.d_rel[rs[0]], torch.float32) for s, rs in self.rels_from.items()}
+
+    @cached_property
+    def dtable(self) -> Dict[int, torch.Tensor]:
+        if self.pre_proj is None:
+            return {}
+        return {s: torch.empty((self.tables[s].shape[0], self.pre_proj[s].shape[0]), dtype=torch.float32, device=self.dev) for s in self.rels_from}
+
+    @cached_property
+    def _Gact(self) -> Dict[int, torch.Tensor]:
+        return {t: torch.empty_like(h) for t, h in self.H.items()} if self.relu else {}
 
     def source(self, s: int) -> torch.Tensor:
         return self.H0[s] if self.pre_proj is not None else self.tables[s]
@@ -157,7 +178,8 @@ class RafLayer:
         for r in self.rels:
             if r not in self.M:
                 self.M[r] = self._padded(*self._m_shapes[r], self.m_dtype)
-                self.dM[r] = self._padded(*self._m_shapes[r], self.m_dtype)
+                if "dM" in self.__dict__:
+                    self.dM[r] = self._padded(*self._m_shapes[r], self.m_dtype)
 
     def _aggregate(self, r: int, stream):
         s = self.g.rels[r][0]
