@@ -347,6 +347,11 @@ heta_status heta_cross_rel_aggregate_project(heta_graph *g, int32_t dst_type, in
 heta_status heta_cross_rel_reduce(const heta_graph *g, int32_t dst_type, const float *const *partials,
                                   int32_t n_partials, int64_t ld, int32_t d_out, heta_act act,
                                   float *out, int64_t ld_out, void *hip_stream);
+/* The same for n node types, launched together: type i adds partials[first[i] .. first[i+1]-1] (first: n + 1 entries from 0)
+ * into outs[i].  HOST arrays; no output may overlap another one, or a partial of another type.  n = 0 is a no-op. */
+heta_status heta_cross_rel_reduce_multi(const heta_graph *g, int32_t n, const int32_t *dst_type, const int32_t *first,
+                                        const float *const *partials, const int64_t *ld, const int32_t *d_out, heta_act act, float *const *outs,
+                                        const int64_t *ld_out, void *hip_stream);
 /* Backward of the activation: grad_in = grad_out * [h > 0] for HETA_ACT_RELU (copy otherwise).
  * All device fp32 [n_rows, ld]; grad_in may alias grad_out. */
 heta_status heta_act_bwd(int64_t n_rows, int32_t d, heta_act act, const float *h, int64_t ld_h,
@@ -391,6 +396,18 @@ heta_status heta_attn_score_multi(const void *x, heta_dtype dt, int64_t ld_x, in
 heta_status heta_attn_score_bwd_multi(heta_graph *g, const void *x, heta_dtype dt, int64_t ld_x, int64_t n, int32_t d,
                                       int32_t n_sets, const float *const *vecs, int32_t heads, const float *const *dscores,
                                       float *dx, int64_t ld_dx, float beta, float *const *dvecs, void *hip_stream);
+/* The two calls above for n tables (same dt and heads) at once: table i (x[i], n_rows[i] rows of d[i] columns) takes the
+ * sets first[i] .. first[i+1]-1 of vecs / scores / dscores / dvecs (first: n + 1 entries from 0).  Tables that take the
+ * same kernel share its launch, so the outputs of two tables must not overlap (the backward checks dx and dvecs); all
+ * partial sums that fit g's attention workspace together are added by one launch.  dx may be NULL, as may its entries.
+ * All arrays are HOST arrays; errors are detected before anything is launched.  n = 0 is a no-op. */
+heta_status heta_attn_score_tables(int32_t n, const int32_t *first, const void *const *x, heta_dtype dt, const int64_t *ld_x,
+                                   const int64_t *n_rows, const int32_t *d, const float *const *vecs, int32_t heads, float *const *scores,
+                                   void *hip_stream);
+heta_status heta_attn_score_bwd_tables(heta_graph *g, int32_t n, const int32_t *first, const void *const *x, heta_dtype dt,
+                                       const int64_t *ld_x, const int64_t *n_rows, const int32_t *d, const float *const *vecs, int32_t heads,
+                                       const float *const *dscores, float *const *dx, const int64_t *ld_dx, const float *beta,
+                                       float *const *dvecs, void *hip_stream);
 /* The source score taken off the input table: since z_u = W^T h_u, el[u, k] = <z_u[k,:], a[k,:]> equals
  * <h_u, wa[k,:]> with wa[k, j] = sum_f W[j, kF + f] a[k, f].  heta_attn_fold writes wa (device fp32
  * [K][d_in]); el is then heta_attn_score(H0_s, wa, per_head = 0) - read from the input table, so in the
@@ -404,6 +421,13 @@ heta_status heta_attn_fold(const void *W, heta_dtype w_dt, int64_t ld_w, int32_t
 heta_status heta_attn_fold_bwd(const void *W, heta_dtype w_dt, int64_t ld_w, int32_t d_in, int32_t d_out, const float *a,
                                int32_t heads, const float *dwa, float *dW, int64_t ld_dw, float beta, float *da,
                                void *hip_stream);
+/* The same for n relations of one element type, heads and beta, launched together (their outputs must not overlap).  HOST
+ * arrays of n entries; dW and da, or single entries of them, may be NULL.  n = 0 is a no-op. */
+heta_status heta_attn_fold_multi(int32_t n, const void *const *W, heta_dtype w_dt, const int64_t *ld_w, const int32_t *d_in,
+                                 const int32_t *d_out, const float *const *a, int32_t heads, float *const *wa, void *hip_stream);
+heta_status heta_attn_fold_bwd_multi(int32_t n, const void *const *W, heta_dtype w_dt, const int64_t *ld_w, const int32_t *d_in,
+                                     const int32_t *d_out, const float *const *a, int32_t heads, const float *const *dwa, float *const *dW,
+                                     const int64_t *ld_dw, float beta, float *const *da, void *hip_stream);
 /* z: device [n_src, ld_z] of z_dt; el: device fp32 [n_src, K]; er: device fp32 [n_dst, K]; out: device
  * [n_dst, ld_out] of out_dt; smax, sinv: device fp32 [n_dst, K], receive the softmax shift and the
  * reciprocal denominator that heta_rel_attn_bwd needs (both NULL for inference).  out_pos (nullable;
@@ -446,6 +470,15 @@ heta_status heta_attn_bwd_dst(heta_graph *g, int32_t dst_type, int32_t n_rels, c
                               int64_t ld_gi, const float *const *o, const float *const *o_pos, const int64_t *ld_o,
                               const float *const *er, const float *const *smax, const float *const *sinv, const float *const *apos,
                               float *const *der, float *const *pack, void *hip_stream);
+/* heta_attn_bwd_dst for n node types, launched together: type i takes the relations first[i] .. first[i+1]-1 (first: n + 1
+ * entries from 0) of rels / o / ... / pack, and h[i], grad_out[i], grad_in[i].  The outputs of two types must not overlap
+ * (checked).  n = 0 is a no-op. */
+heta_status heta_attn_bwd_dst_multi(heta_graph *g, int32_t n, const int32_t *dst_type, const int32_t *first, const int32_t *rels, int32_t d,
+                                    int32_t heads, float slope, heta_act act, const float *const *h, const int64_t *ld_h,
+                                    const float *const *grad_out, const int64_t *ld_go, float *const *grad_in, const int64_t *ld_gi,
+                                    const float *const *o, const float *const *o_pos, const int64_t *ld_o, const float *const *er,
+                                    const float *const *smax, const float *const *sinv, const float *const *apos, float *const *der,
+                                    float *const *pack, void *hip_stream);
 heta_status heta_rel_attn_bwd_src(heta_graph *g, int32_t rel, const void *z, heta_dtype z_dt, int64_t ld_z, int32_t d, int32_t heads,
                                   const float *el, float slope, const float *pack, const float *grad_out, int64_t ld_go, float *dz,
                                   int64_t ld_dz, float *del, void *hip_stream);

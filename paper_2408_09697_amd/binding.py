@@ -32,6 +32,8 @@ EXPORTS = ["heta_graph_create", "heta_graph_create_batch", "heta_graph_destroy",
            "heta_profile_read", "heta_calibration_copy", "heta_calibration_mfma", "heta_cross_rel_project", "heta_cross_rel_project_bwd",
            "heta_cross_rel_project_wgrad", "heta_sparse_adam", "heta_project_batch",
            "heta_project_sum", "heta_project_wgrad_batch", "heta_project_multi", "heta_project_wgrad_multi", "heta_act_bwd_multi", "heta_attn_score", "heta_attn_score_bwd", "heta_attn_score_multi", "heta_attn_score_bwd_multi",
+           "heta_attn_score_tables", "heta_attn_score_bwd_tables", "heta_attn_fold_multi", "heta_attn_fold_bwd_multi", "heta_attn_bwd_dst_multi",
+           "heta_cross_rel_reduce_multi",
            "heta_rel_attn_fwd", "heta_rel_attn_bwd", "heta_rel_attn_fwd_train", "heta_rel_attn_fwd_train_multi", "heta_rel_attn_bwd_src_multi", "heta_attn_bwd_dst", "heta_rel_attn_bwd_src",
            "heta_sample_neighbors", "heta_unique_relabel",
            "heta_cross_rel_aggregate_project", "heta_meta_partition", "heta_sample_neighbors_batch",
@@ -114,6 +116,12 @@ def load_library() -> ctypes.CDLL:
     L.heta_project_multi.argtypes = [vp, i32, vp, vp, i32, vp, i32, vp, vp, vp, i32, vp, vp, i32, vp, i32, vp, vp, vp, vp]
     L.heta_project_wgrad_multi.argtypes = [vp, i32, vp, vp, vp, i32, vp, vp, vp, vp, vp, vp, vp, i32, vp]
     L.heta_act_bwd_multi.argtypes = [i32, vp, vp, i32, vp, vp, vp, vp, vp, vp, vp]
+    L.heta_cross_rel_reduce_multi.argtypes = [vp, i32, vp, vp, vp, vp, vp, i32, vp, vp, vp]
+    L.heta_attn_score_tables.argtypes = [i32, vp, vp, i32, vp, vp, vp, vp, i32, vp, vp]
+    L.heta_attn_score_bwd_tables.argtypes = [vp, i32, vp, vp, i32, vp, vp, vp, vp, i32, vp, vp, vp, vp, vp, vp]
+    L.heta_attn_fold_multi.argtypes = [i32, vp, i32, vp, vp, vp, vp, i32, vp, vp]
+    L.heta_attn_fold_bwd_multi.argtypes = [i32, vp, i32, vp, vp, vp, vp, i32, vp, vp, vp, f32, vp, vp]
+    L.heta_attn_bwd_dst_multi.argtypes = [vp, i32, vp, vp, vp, i32, i32, f32, i32] + [vp] * 16
     L.heta_rel_aggregate_fwd_multi_act.argtypes = [vp, i32, vp, vp, i32, i32, i32, vp]
     L.heta_rel_aggregate_bwd_multi.argtypes = [vp, i32, vp, i32, i32, vp]
     L.heta_sparse_adam_multi.argtypes = [i32, vp, f32, f32, f32, f32, i64, vp]
@@ -769,6 +777,27 @@ def heta_cross_rel_reduce(g: Graph, dst_type: int, partials: List[torch.Tensor],
     return out
 
 
+def heta_cross_rel_reduce_multi(g: Graph, items: Sequence[Sequence], act: int = HETA_ACT_NONE, stream=None) -> None:
+    """heta_cross_rel_reduce of several node types in one call.  items: (dst_type, partials, out)."""
+    if not items:
+        return
+    first, parts, ld, d_out, outs, ld_out = [0], [], [], [], [], []
+    for t, partials, out in items:
+        n = g.ntypes[t][0]
+        m = [_mat(p, "partial", torch.float32) for p in partials]
+        if any(rows < n or cols != m[0][3] or l != m[0][1] for _, l, rows, cols in m):
+            raise HetaError(HETA_ERR_SHAPE, "partials must share shape and leading dimension")
+        po, lo, ro, co = _mat(out, "out", torch.float32)
+        if ro < n or co < m[0][3]:
+            raise HetaError(HETA_ERR_SHAPE, "out too small")
+        parts += [x[0] for x in m]
+        first.append(len(parts))
+        ld.append(m[0][1]), d_out.append(m[0][3]), outs.append(po), ld_out.append(lo)
+    _check(load_library().heta_cross_rel_reduce_multi(
+        g.handle, len(items), _pack("i", [it[0] for it in items]), _pack("i", first), _pack("Q", parts), _pack("q", ld), _pack("i", d_out), act,
+        _pack("Q", outs), _pack("q", ld_out), _stream(stream)))
+
+
 def heta_act_bwd(act: int, h: Optional[torch.Tensor], grad_out: torch.Tensor, grad_in: torch.Tensor,
                  stream=None) -> torch.Tensor:
     n, d = grad_out.shape
@@ -903,6 +932,76 @@ def heta_attn_fold_bwd(W: torch.Tensor, a: torch.Tensor, dwa: torch.Tensor, dW: 
                                 _w_ld(dW) if dW is not None else 0, beta, _dev(da, "da", torch.float32), _stream(stream)))
 
 
+def _score_array(t: torch.Tensor, name: str, rows: int, width: int) -> int:
+    """_scores with every attribute read once."""
+    p, ld, r, c = _mat(t, name, torch.float32)
+    if r < rows or c != width or (ld != width and r > 1):
+        raise HetaError(HETA_ERR_SHAPE, f"{name} must be a contiguous fp32 [>= {rows}, {width}] tensor")
+    return p
+
+
+def _by_dtype(items):
+    """items in lists of one element type of their first tensor"""
+    by: dict = {}
+    for it in items:
+        by.setdefault(it[0].dtype, []).append(it)
+    return by.values()
+
+
+def _fold_args(items):
+    """(addresses, leading dimensions, d_in, d_out, addresses of a, heads, element type) of the weights of a fold call."""
+    dt, heads = items[0][0].dtype, items[0][1].shape[0]
+    if dt not in _DT:
+        raise TypeError(f"unsupported tensor dtype {dt}")
+    ws, pa = [_mat(it[0], "W", dt) for it in items], []
+    for (W, a, *_), (_, _, d_in, d_out) in zip(items, ws):
+        p, _, k, f = _mat(a, "a", torch.float32)
+        if not a.is_contiguous() or k != heads or f * k != d_out:
+            raise HetaError(HETA_ERR_SHAPE, "a must be contiguous [heads, d_out / heads]")
+        pa.append(p)
+    return [w[0] for w in ws], [w[1] for w in ws], [w[2] for w in ws], [w[3] for w in ws], pa, heads, dt
+
+
+def heta_attn_fold_multi(items: Sequence[Sequence], stream=None) -> None:
+    """heta_attn_fold of several relations (one number of heads) in one call per element type.  items: (W, a, wa)."""
+    for part in _by_dtype(items):
+        _fold_part(part, stream)
+
+
+def _fold_part(items, stream) -> None:
+    p_w, ld_w, d_in, d_out, p_a, heads, dt = _fold_args(items)
+    p_wa = []
+    for (_, _, wa), k in zip(items, d_in):
+        if not wa.is_contiguous() or tuple(wa.shape) != (heads, k):
+            raise HetaError(HETA_ERR_SHAPE, "wa must be contiguous [heads, d_in]")
+        p_wa.append(_mat(wa, "wa", torch.float32)[0])
+    _check(load_library().heta_attn_fold_multi(len(items), _pack("Q", p_w), _DT[dt], _pack("q", ld_w), _pack("i", d_in), _pack("i", d_out),
+                                               _pack("Q", p_a), heads, _pack("Q", p_wa), _stream(stream)))
+
+
+def heta_attn_fold_bwd_multi(items: Sequence[Sequence], beta: float = 0.0, stream=None) -> None:
+    """heta_attn_fold_bwd of several relations in one call per element type.  items: (W, a, dwa, dW, da)."""
+    for part in _by_dtype(items):
+        _fold_bwd_part(part, beta, stream)
+
+
+def _fold_bwd_part(items, beta, stream) -> None:
+    p_w, ld_w, d_in, d_out, p_a, heads, dt = _fold_args(items)
+    p_dwa, p_dw, ld_dw, p_da = [], [], [], []
+    for (_, a, dwa, dW, da), k, n in zip(items, d_in, d_out):
+        if not dwa.is_contiguous() or tuple(dwa.shape) != (heads, k):
+            raise HetaError(HETA_ERR_SHAPE, "dwa must be contiguous [heads, d_in]")
+        pw, lw, rw, cw = _mat(dW, "dW", torch.float32)
+        if rw < k or cw < n:
+            raise HetaError(HETA_ERR_SHAPE, "dW is smaller than W")
+        if not da.is_contiguous() or da.shape != a.shape:
+            raise HetaError(HETA_ERR_SHAPE, "da must be contiguous and shaped like a")
+        p_dwa.append(_mat(dwa, "dwa", torch.float32)[0]), p_dw.append(pw), ld_dw.append(lw), p_da.append(_mat(da, "da", torch.float32)[0])
+    _check(load_library().heta_attn_fold_bwd_multi(len(items), _pack("Q", p_w), _DT[dt], _pack("q", ld_w), _pack("i", d_in), _pack("i", d_out),
+                                                   _pack("Q", p_a), heads, _pack("Q", p_dwa), _pack("Q", p_dw), _pack("q", ld_dw), beta,
+                                                   _pack("Q", p_da), _stream(stream)))
+
+
 def heta_attn_score_bwd(g: Graph, x: torch.Tensor, vec: torch.Tensor, per_head: bool, dscore: torch.Tensor,
                         dx: Optional[torch.Tensor] = None, beta: float = 0.0, dvec: Optional[torch.Tensor] = None,
                         d: Optional[int] = None, stream=None) -> None:
@@ -968,6 +1067,52 @@ def heta_attn_score_bwd_multi(g: Graph, x: torch.Tensor, vecs: Sequence[torch.Te
                                        _ptr_array(vecs, "vec", torch.float32), heads, ds,
                                        _dev(dx, "dx", torch.float32), _ld(dx) if dx is not None else 0, beta, dv,
                                        _stream(stream)))
+
+
+def _score_tables(items):
+    """The arguments that the score calls over several tables share.  items: (x, vecs, scores, ...)."""
+    dt, heads = items[0][0].dtype, items[0][1][0].shape[0]
+    if dt not in _DT:
+        raise TypeError(f"unsupported tensor dtype {dt}")
+    first, p_v, p_s = [0], [], []
+    xs = [_mat(it[0], "x", dt) for it in items]
+    for (_, vecs, scores, *_), (_, _, rows, d) in zip(items, xs):
+        for v in vecs:
+            p, ld, k, c = _mat(v, "vec", torch.float32)
+            if k != heads or c != d or (ld != d and k > 1):
+                raise HetaError(HETA_ERR_SHAPE, "every vec must be contiguous [heads, d]")
+            p_v.append(p)
+        if len(scores) != len(vecs):
+            raise HetaError(HETA_ERR_SHAPE, "one score array per vec")
+        p_s += [_score_array(t, "score", rows, heads) for t in scores]
+        first.append(len(p_v))
+    return (_pack("i", first), _pack("Q", [x[0] for x in xs]), _DT[dt], _pack("q", [x[1] for x in xs]), _pack("q", [x[2] for x in xs]),
+            _pack("i", [x[3] for x in xs]), _pack("Q", p_v), heads, _pack("Q", p_s)), xs
+
+
+def heta_attn_score_tables(items: Sequence[Sequence], stream=None) -> None:
+    """heta_attn_score_multi of several tables in one call.  items: (x, vecs, scores)."""
+    for part in _by_dtype([it for it in items if it[1]]):
+        args, xs = _score_tables(part)
+        _check(load_library().heta_attn_score_tables(len(xs), *args, _stream(stream)))
+
+
+def heta_attn_score_bwd_tables(g: Graph, items: Sequence[Sequence], stream=None) -> None:
+    """heta_attn_score_bwd_multi of several tables in one call.  items: (x, vecs, dscores, dx, beta, dvecs)."""
+    for part in _by_dtype([it for it in items if it[1]]):
+        args, xs = _score_tables(part)
+        p_dx, ld_dx, p_dv = [], [], []
+        for (_, vecs, _, dx, _, dvecs), (_, _, rows, d) in zip(part, xs):
+            p, ld, r, c = _mat(dx, "dx", torch.float32)
+            if r < rows or c < d:
+                raise HetaError(HETA_ERR_SHAPE, "dx is smaller than x")
+            p_dx.append(p), ld_dx.append(ld)
+            for v, dv in zip(vecs, dvecs):
+                if not dv.is_contiguous() or dv.shape != v.shape:
+                    raise HetaError(HETA_ERR_SHAPE, "dvec must be contiguous and shaped like vec")
+                p_dv.append(_mat(dv, "dvec", torch.float32)[0])
+        _check(load_library().heta_attn_score_bwd_tables(g.handle, len(xs), *args, _pack("Q", p_dx), _pack("q", ld_dx),
+                                                         _pack("f", [it[4] for it in part]), _pack("Q", p_dv), _stream(stream)))
 
 
 def heta_rel_attn_fwd(g: Graph, rel: int, z: torch.Tensor, el: torch.Tensor, er: torch.Tensor, slope: float,
@@ -1058,6 +1203,45 @@ def heta_attn_bwd_dst(g: Graph, dst_type: int, rels: Sequence[int], slope: float
                                rows(sinv, "sinv", heads), rows(apos, "apos", heads), rows(d_er, "der", heads),
                                rows(pack, "pack", 4 * heads), _stream(stream)))
     return grad_in if relu else grad_out
+
+
+def heta_attn_bwd_dst_multi(g: Graph, items: Sequence[Sequence], slope: float, act: int, stream=None) -> None:
+    """heta_attn_bwd_dst of several node types in one call.  items: (dst_type, rels, h, grad_out, grad_in, o, o_pos, er, smax,
+    sinv, apos, d_er, pack); h and grad_in are used with an activation only."""
+    if not items:
+        return
+    relu = act == HETA_ACT_RELU
+    heads, d = items[0][7][0].shape[1], items[0][5][0].shape[1]
+    first, rels, p_go, ld_go, p_h, ld_h, p_gi, ld_gi, p_o, ld_o, p_pos = [0], [], [], [], [], [], [], [], [], [], []
+    rows: list = [[] for _ in range(6)]
+    f32 = torch.float32
+    for t, rs, h, grad_out, grad_in, o, o_pos, *rest in items:
+        n = g.ntypes[t][0]
+        mo, mp, mg = [_mat(x, "o", f32) for x in o], [_mat(x, "o_pos", f32) for x in o_pos], _mat(grad_out, "grad_out", f32)
+        mats = [mg, *mo, *mp]
+        p_go.append(mg[0]), ld_go.append(mg[1])
+        if relu:
+            mh, mi = _mat(h, "h", f32), _mat(grad_in, "grad_in", f32)
+            mats.append(mh)
+            if mi[2] < mg[2] or mi[3] < mg[3]:
+                raise HetaError(HETA_ERR_SHAPE, "buffers too small")
+            p_h.append(mh[0]), ld_h.append(mh[1]), p_gi.append(mi[0]), ld_gi.append(mi[1])
+        if any(r < n or c < d for _, _, r, c in mats):
+            raise HetaError(HETA_ERR_SHAPE, "a buffer is smaller than the node type needs")
+        if len(mo) != len(rs) or any(a[1] != b[1] for a, b in zip(mo, mp)):
+            raise HetaError(HETA_ERR_SHAPE, "o_pos must match o (leading dimension)")
+        for to, ts, name, width in zip(rows, rest, ("er", "smax", "sinv", "apos", "der", "pack"), (heads,) * 5 + (4 * heads,)):
+            to += [_score_array(x, name, n, width) for x in ts]
+        rels += rs
+        p_o += [m[0] for m in mo]
+        ld_o += [m[1] for m in mo]
+        p_pos += [m[0] for m in mp]
+        first.append(len(rels))
+    opt = lambda fmt, vals: _pack(fmt, vals) if relu else None  # noqa: E731
+    _check(load_library().heta_attn_bwd_dst_multi(
+        g.handle, len(items), _pack("i", [it[0] for it in items]), _pack("i", first), _pack("i", rels), d, heads, slope, act, opt("Q", p_h),
+        opt("q", ld_h), _pack("Q", p_go), _pack("q", ld_go), opt("Q", p_gi), opt("q", ld_gi), _pack("Q", p_o), _pack("Q", p_pos), _pack("q", ld_o),
+        *[_pack("Q", x) for x in rows], _stream(stream)))
 
 
 def heta_rel_attn_bwd_src(g: Graph, rel: int, z: torch.Tensor, el: torch.Tensor, slope: float, pack: torch.Tensor,

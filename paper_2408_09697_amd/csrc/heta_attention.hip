@@ -773,11 +773,28 @@ struct DstParams {
     const float *g, *h; // h: null without an activation
     float *ga;
     int64_t ld_g, ld_h, ld_ga, n;
+    int64_t first; // its first workgroup
     int d, K, F, n_rels;
-    unsigned first; // first workgroup of this launch
     float slope;
     DstItem it[kDstRels];
 };
+// Several destination types in one launch, their workgroups end to end: by itself a type of a few thousand rows takes the
+// 4 to 5 us that any launch takes.
+constexpr int kDstTypes = 4;
+struct DstTypes { // passed by value
+    DstParams t[kDstTypes];
+    int64_t first; // first workgroup of this launch
+    int n;
+};
+// the type that this workgroup serves, and the workgroup's number within it
+__device__ __forceinline__ const DstParams &dst_type_of(const DstTypes &m, int64_t &wg)
+{
+    wg = m.first + blockIdx.x;
+    int c = 0;
+    while (c + 1 < m.n && wg >= m.t[c + 1].first) ++c; // uniform
+    wg -= m.t[c].first;
+    return m.t[c];
+}
 
 __device__ __forceinline__ void dst_store(const DstParams &p, const DstItem &t, int64_t i, int k, float dot, float dpos)
 {
@@ -789,11 +806,13 @@ __device__ __forceinline__ void dst_store(const DstParams &p, const DstItem &t, 
 // Rows of 16-byte chunks, T chunks per lane, L lanes per row (L a power of two; 64 if T > 1), R rows per lane group; heads
 // of whole chunks, for T > 1 a power of two of them.
 template <int R, int T>
-__global__ void __launch_bounds__(256) attn_dst_kernel(DstParams p, int L)
+__global__ void __launch_bounds__(256) attn_dst_kernel(DstTypes m, int L)
 {
+    int64_t wg;
+    const DstParams &p = dst_type_of(m, wg);
     const int lane = threadIdx.x & 63;
     const int G = 64 / L, grp = lane / L, l = lane % L;
-    const int64_t first = ((static_cast<int64_t>(p.first) + blockIdx.x) * 4 + (threadIdx.x >> 6)) * R * G + grp;
+    const int64_t first = (wg * 4 + (threadIdx.x >> 6)) * R * G + grp;
     const int n_chunks = p.d / 4, cph = p.F / 4;
     const bool pow2 = (cph & (cph - 1)) == 0;
     float4 gv[R][T];
@@ -884,10 +903,12 @@ __global__ void __launch_bounds__(256) attn_dst_kernel(DstParams p, int L)
 
 // any other shape: one wavefront per row, head by head; EPC = 4: 16-byte loads, heads of whole chunks
 template <int EPC>
-__global__ void __launch_bounds__(256) attn_dst_any_kernel(DstParams p)
+__global__ void __launch_bounds__(256) attn_dst_any_kernel(DstTypes m)
 {
+    int64_t wg;
+    const DstParams &p = dst_type_of(m, wg);
     const int lane = threadIdx.x & 63;
-    const int64_t i = (static_cast<int64_t>(p.first) + blockIdx.x) * 4 + (threadIdx.x >> 6);
+    const int64_t i = wg * 4 + (threadIdx.x >> 6);
     if (i >= p.n) return; // uniform per wavefront
     const float *g = p.g + i * p.ld_g, *h = p.h ? p.h + i * p.ld_h : nullptr;
     const auto grad = [&](int j, float (&v)[EPC]) { // the gradient behind the activation, columns j ..
@@ -1177,6 +1198,34 @@ struct ScoreMulti {
     int n_sets, K, NV;            // NV = n_sets * K
 };
 
+// Several tables in one launch, their workgroups end to end (by itself a table of a few thousand rows takes the 4 to 5 us
+// that any launch takes, its input gradient 10: the vectors are brought into LDS first).  With the weights' folds, the
+// destination side and the sums over relations laid end to end as well, 69 launches of an attention layer of 64 columns, 4
+// node types and 7 relations (2.1 M edges) become 37: forward and backward 1,206 -> 988 us; 21 M edges of 256 columns, where
+// the small launches are 1 % of the time, 21,355 -> 21,190.
+constexpr int kMultiTables = 8;
+struct ScoreTable {
+    const void *x;
+    float *dx, *part;
+    int64_t ld_x, ld_dx, n, slab_rows, n_slabs;
+    int d, nb, nvc; // nb: workgroups along the rows
+    float beta;
+    unsigned first; // its first workgroup
+    ScoreMulti m;
+};
+struct ScoreTables { // passed by value
+    ScoreTable t[kMultiTables];
+    int n;
+};
+// the table that this workgroup serves, and the workgroup's number within it
+__device__ __forceinline__ const ScoreTable &score_table_of(const ScoreTables &q, unsigned &wg)
+{
+    int c = 0;
+    while (c + 1 < q.n && blockIdx.x >= q.t[c + 1].first) ++c; // uniform
+    wg = blockIdx.x - q.t[c].first;
+    return q.t[c];
+}
+
 using f32x16 = __attribute__((ext_vector_type(16))) float;
 using f32x4 = __attribute__((ext_vector_type(4))) float;
 // pointers kept in LDS: the address space says that they point to global memory
@@ -1223,7 +1272,7 @@ template <> struct Raw4<bf16_t> {
     }
 };
 
-// Scores of 16 NT vectors (blockIdx.y picks them) and 16 rows per tile: the vectors are the first operand, so a
+// Scores of 16 NT vectors (the workgroup's second index picks them) and 16 rows per tile: the vectors are the first operand, so a
 // lane ends with one row's scores of four consecutive vectors - one 16-byte store where a set has a multiple of
 // four heads (VEC).  A lane holds the columns 16 c + 4 h .. + 3 of its vector and of its row (h: its quarter of the
 // wavefront): which k a step multiplies is free as long as both operands agree.  Sums of eight products
@@ -1253,11 +1302,18 @@ template <int NC> __device__ __forceinline__ f32x4 score_sum(const float (&a)[NC
 }
 
 template <typename T, int NC, int NT, bool VEC>
-__global__ void __launch_bounds__(256, 2) attn_score_multi_kernel(const T *x, int64_t ld_x, int64_t n, int d, ScoreMulti m)
+__global__ void __launch_bounds__(256, 2) attn_score_multi_kernel(ScoreTables q)
 {
     __shared__ gf32 *sptr[16 * NT];
+    unsigned wg;
+    const ScoreTable &tab = score_table_of(q, wg);
+    const ScoreMulti &m = tab.m;
+    const T *x = static_cast<const T *>(tab.x);
+    const int64_t ld_x = tab.ld_x, n = tab.n;
+    const int d = tab.d, nb = tab.nb;
     const int lane = threadIdx.x & 63, l = lane & 15, h = lane >> 4;
-    const int v0 = blockIdx.y * 16 * NT;
+    const int v0 = static_cast<int>(wg / nb) * 16 * NT;
+    wg %= nb;
     if (threadIdx.x < 16 * NT) {
         const int v = v0 + threadIdx.x;
         sptr[threadIdx.x] = v < m.NV ? (gf32 *)(pick(m.score, v / m.K) + v % m.K) : nullptr;
@@ -1274,7 +1330,7 @@ __global__ void __launch_bounds__(256, 2) attn_score_multi_kernel(const T *x, in
         }
     }
     __syncthreads();
-    const int64_t wave = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6), step = static_cast<int64_t>(gridDim.x) * 4 * 16;
+    const int64_t wave = static_cast<int64_t>(wg) * 4 + (threadIdx.x >> 6), step = static_cast<int64_t>(nb) * 4 * 16;
     for (int64_t r0 = wave * 16; r0 < n; r0 += step) { // uniform per wavefront
         const int64_t r = r0 + l;
         const T *xr = x + min(r, n - 1) * ld_x; // rows past the end repeat the last one and are not stored
@@ -1307,9 +1363,16 @@ __global__ void __launch_bounds__(256, 2) attn_score_multi_kernel(const T *x, in
 // lane l the second one of four products, so that a row leaves as 16-byte stores of whole cache lines.  The vectors
 // sit in LDS, zero beyond d and up to a multiple of eight vectors; step (c, j) multiplies vector 8 c + 4 h + j.
 template <bool VEC>
-__global__ void __launch_bounds__(256, 3) attn_score_bwd_multi_input_kernel(int64_t n, int d, ScoreMulti m, float *dx, int64_t ld_dx, float beta)
+__global__ void __launch_bounds__(256, 3) attn_score_bwd_multi_input_kernel(ScoreTables q)
 {
     extern __shared__ __align__(16) float vecs[]; // [8 nc][128], then the pointers
+    unsigned wg;
+    const ScoreTable &tab = score_table_of(q, wg);
+    const ScoreMulti &m = tab.m;
+    const int64_t n = tab.n, ld_dx = tab.ld_dx;
+    const int d = tab.d;
+    float *const dx = tab.dx;
+    const float beta = tab.beta;
     const int lane = threadIdx.x & 63, l = lane & 31, h = lane >> 5;
     const int nc = (m.NV + 7) / 8;
     const gf32 **sptr = reinterpret_cast<const gf32 **>(vecs + 8 * nc * kMultiCols);
@@ -1319,7 +1382,7 @@ __global__ void __launch_bounds__(256, 3) attn_score_bwd_multi_input_kernel(int6
     }
     for (int v = threadIdx.x; v < 8 * nc; v += 256) sptr[v] = v < m.NV ? (const gf32 *)(pick(m.score, v / m.K) + v % m.K) : nullptr;
     __syncthreads();
-    const int64_t wave = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6), n_waves = static_cast<int64_t>(gridDim.x) * 4;
+    const int64_t wave = static_cast<int64_t>(wg) * 4 + (threadIdx.x >> 6), n_waves = static_cast<int64_t>(tab.nb) * 4;
     for (int64_t r0 = wave * 32; r0 < n; r0 += n_waves * 32) { // uniform per wavefront
         const int64_t r = min(r0 + l, n - 1);
         f32x16 acc[4];
@@ -1391,25 +1454,30 @@ __global__ void __launch_bounds__(256, 3) attn_score_bwd_multi_input_kernel(int6
 // part[slab][v][128]: the slab's sum over its rows of dscore_v[i] x[i, :].  The contraction runs over the rows, four per
 // step (one per quarter h of the wavefront); a lane's first operand is its vector's dscore, its second the four columns
 // 64 c + 4 l .. + 3 of chunk c, one product each.  A wavefront takes every fourth group of 4 U rows of the slab, the four
-// wavefronts' sums are added in wavefront order through LDS.  16 NT vectors per workgroup (blockIdx.y picks them), NC
+// wavefronts' sums are added in wavefront order through LDS.  16 NT vectors per workgroup (its second index picks them), NC
 // chunks of 64 columns: no product is spent on more.  With 32 vectors and 128 columns whatever is given, two rows per
 // step and the loads behind branches, a pass was bound by the products and by one load after the other: 700,000 rows
 // of 128 columns, bf16 with 1 / 24 vectors 146 / 155 -> 45 / 70 us, fp32 116 / 124 -> 74 / 88; of 64, fp32, 4 vectors 89 -> 38.
 template <typename T, int NC, int NT>
-__global__ void __launch_bounds__(256, NC * NT * sizeof(T) == 16 ? 3 : 4) attn_score_bwd_multi_param_kernel(const T *x, int64_t ld_x, int64_t n, int d, ScoreMulti m, int slab_rows,
-                                                                         float *part)
+__global__ void __launch_bounds__(256, NC * NT * sizeof(T) == 16 ? 3 : 4) attn_score_bwd_multi_param_kernel(ScoreTables q)
 {
     constexpr int U = 4, VT = 16 * NT;
+    unsigned wg;
+    const ScoreTable &tab = score_table_of(q, wg);
+    const ScoreMulti &m = tab.m;
+    const T *x = static_cast<const T *>(tab.x);
+    const int64_t ld_x = tab.ld_x, n = tab.n, slab_rows = tab.slab_rows;
+    const int d = tab.d, nb = tab.nb, tile = static_cast<int>(wg / nb), tiles = tab.nvc / VT;
     __shared__ __align__(16) float buf[VT][kMultiCols];
     const int lane = threadIdx.x & 63, l = lane & 15, h = lane >> 4, w = threadIdx.x >> 6;
-    const int64_t slab = blockIdx.x;
+    const int64_t slab = wg % nb;
     const int64_t i0 = slab * slab_rows, i1 = min(n, i0 + slab_rows);
     // lanes past the vectors and the columns given repeat others; what they sum up is not written out
     const float *ds[NT];
     int col[NC];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-        const int v = min(static_cast<int>(blockIdx.y) * VT + 16 * t + l, m.NV - 1);
+        const int v = min(tile * VT + 16 * t + l, m.NV - 1);
         ds[t] = pick(m.score, v / m.K) + v % m.K;
     }
 #pragma unroll
@@ -1452,8 +1520,8 @@ __global__ void __launch_bounds__(256, NC * NT * sizeof(T) == 16 ? 3 : 4) attn_s
             }
         }
     }
-    for (int q = 0; q < 4; ++q) { // wavefront q adds its sums to the buffer, in order
-        if (w == q) {
+    for (int turn = 0; turn < 4; ++turn) { // wavefront `turn` adds its sums to the buffer, in order
+        if (w == turn) {
 #pragma unroll
             for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -1462,7 +1530,7 @@ __global__ void __launch_bounds__(256, NC * NT * sizeof(T) == 16 ? 3 : 4) attn_s
                     for (int i = 0; i < 4; ++i) {
                         float4 *b = reinterpret_cast<float4 *>(&buf[16 * t + 4 * h + i][64 * c + 4 * l]);
                         float4 s = make_float4(acc[t][c][0][i], acc[t][c][1][i], acc[t][c][2][i], acc[t][c][3][i]);
-                        if (q > 0) {
+                        if (turn > 0) {
                             const float4 o = *b;
                             s.x += o.x; s.y += o.y; s.z += o.z; s.w += o.w;
                         }
@@ -1471,18 +1539,24 @@ __global__ void __launch_bounds__(256, NC * NT * sizeof(T) == 16 ? 3 : 4) attn_s
         }
         __syncthreads();
     }
-    float *o = part + (slab * gridDim.y + blockIdx.y) * (VT * kMultiCols);
+    float *o = tab.part + (slab * tiles + tile) * (VT * kMultiCols);
     for (int t = threadIdx.x * 4; t < VT * kMultiCols; t += 1024)
         if (t % kMultiCols < 64 * NC) *reinterpret_cast<float4 *>(o + t) = *reinterpret_cast<const float4 *>(&buf[0][0] + t);
 }
 
 // dvec_v[c] = sum over the slabs, in slab order per wavefront and wavefront order through LDS (as attn_slab_sum_kernel)
-__global__ void __launch_bounds__(1024) attn_multi_slab_sum_kernel(const float *part, int64_t n_slabs, int nvc, int d, ScoreMulti m)
+__global__ void __launch_bounds__(1024) attn_multi_slab_sum_kernel(ScoreTables q)
 {
     __shared__ float red[16][64];
+    unsigned wg;
+    const ScoreTable &tab = score_table_of(q, wg);
+    const ScoreMulti &m = tab.m;
+    const float *part = tab.part;
+    const int64_t n_slabs = tab.n_slabs;
+    const int d = tab.d;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t elems = static_cast<int64_t>(nvc) * kMultiCols;
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * 64 + lane;
+    const int64_t elems = static_cast<int64_t>(tab.nvc) * kMultiCols;
+    const int64_t t = static_cast<int64_t>(wg) * 64 + lane;
     if ((t - lane) % kMultiCols >= d) return; // uniform: columns that no slab has written
     float a = 0.f;
     if (t < elems) {
@@ -1507,14 +1581,40 @@ __global__ void __launch_bounds__(1024) attn_multi_slab_sum_kernel(const float *
 // One lane per (k, j), so that the sum over f runs in order; the matrix is small, and what counts is the chain of loads of
 // one lane, so sixteen are in flight, on workgroups of one wavefront (128 x 256, 4 heads: 9.5 us one by one, now 3.0, eight
 // lanes per element 2.8; 768 x 1,024 34.0, 5.7 and 5.0).
-template <typename T>
-__global__ void __launch_bounds__(64) attn_fold_kernel(const T *W, int64_t ld_w, int d_in, int K, int F, const float *a, float *wa)
+// The relations of a layer share a launch, their workgroups end to end: seven of 64 x 64 in seven launches 33 us, in one 5.
+constexpr int kFoldItems = 24;
+struct FoldItem {
+    const void *W;
+    const float *a, *dwa;
+    float *wa, *dW, *da;
+    int64_t ld_w, ld_dw;
+    int d_in, d_out;
+    unsigned first, w_blocks; // its first workgroup; backward: workgroups of dW, those of da follow
+};
+struct FoldItems { // passed by value
+    FoldItem it[kFoldItems];
+    int n, K;
+    float beta;
+};
+__device__ __forceinline__ const FoldItem &fold_item_of(const FoldItems &q, unsigned &wg)
 {
-    const int t = blockIdx.x * 64 + threadIdx.x;
+    int c = 0;
+    while (c + 1 < q.n && blockIdx.x >= q.it[c + 1].first) ++c; // uniform
+    wg = blockIdx.x - q.it[c].first;
+    return q.it[c];
+}
+
+template <typename T>
+__global__ void __launch_bounds__(64) attn_fold_kernel(FoldItems q)
+{
+    unsigned wg;
+    const FoldItem &r = fold_item_of(q, wg);
+    const int K = q.K, d_in = r.d_in, F = r.d_out / K;
+    const int t = static_cast<int>(wg) * 64 + threadIdx.x;
     if (t >= K * d_in) return;
     const int k = t / d_in, j = t - k * d_in;
-    const T *w = W + static_cast<int64_t>(j) * ld_w + k * F;
-    a += k * F;
+    const T *w = static_cast<const T *>(r.W) + static_cast<int64_t>(j) * r.ld_w + k * F;
+    const float *a = r.a + k * F;
     float acc = 0.f;
     int f = 0;
     for (; f + 16 <= F; f += 16) {
@@ -1525,7 +1625,7 @@ __global__ void __launch_bounds__(64) attn_fold_kernel(const T *W, int64_t ld_w,
         for (int i = 0; i < 16; ++i) acc = fmaf(x[i], a[f + i], acc);
     }
     for (; f < F; ++f) acc = fmaf(ld1(w + f), a[f], acc);
-    wa[t] = acc;
+    r.wa[t] = acc;
 }
 
 // Its backward, both halves in one launch (two of 4.9 us before, one of 4.9 now at 128 x 256):
@@ -1533,28 +1633,31 @@ __global__ void __launch_bounds__(64) attn_fold_kernel(const T *W, int64_t ld_w,
 //   da[k, f] = sum_j dwa[k, j] W[j, kF + f], one wavefront per (k, f), lanes take j round-robin and are combined by a
 //   fixed butterfly, so the order of the sum is fixed.
 template <typename T>
-__global__ void __launch_bounds__(256) attn_fold_bwd_kernel(const float *dwa, const float *a, const T *W, int64_t ld_w, int d_in, int K, int F,
-                                                            float *dW, int64_t ld_dw, float beta, float *da, unsigned w_blocks)
+__global__ void __launch_bounds__(256) attn_fold_bwd_kernel(FoldItems q)
 {
-    const int d_out = K * F;
-    if (blockIdx.x < w_blocks) {
-        const int t = blockIdx.x * 256 + threadIdx.x;
+    unsigned wg;
+    const FoldItem &r = fold_item_of(q, wg);
+    const int K = q.K, d_in = r.d_in, d_out = r.d_out, F = d_out / K;
+    const float *dwa = r.dwa;
+    const T *W = static_cast<const T *>(r.W);
+    if (wg < r.w_blocks) {
+        const int t = static_cast<int>(wg) * 256 + threadIdx.x;
         if (t >= d_in * d_out) return;
         const int j = t / d_out, c = t - j * d_out;
-        const float v = dwa[(c / F) * d_in + j] * a[c];
-        float *o = dW + static_cast<int64_t>(j) * ld_dw + c;
-        *o = beta != 0.f ? *o + v : v;
+        const float v = dwa[(c / F) * d_in + j] * r.a[c];
+        float *o = r.dW + static_cast<int64_t>(j) * r.ld_dw + c;
+        *o = q.beta != 0.f ? *o + v : v;
         return;
     }
     const int lane = threadIdx.x & 63;
-    const int c = static_cast<int>(blockIdx.x - w_blocks) * 4 + (threadIdx.x >> 6);
+    const int c = static_cast<int>(wg - r.w_blocks) * 4 + (threadIdx.x >> 6);
     if (c >= d_out) return; // uniform per wavefront
     const int k = c / F;
     float acc = 0.f;
-    for (int j = lane; j < d_in; j += 64) acc = fmaf(dwa[k * d_in + j], ld1(W + static_cast<int64_t>(j) * ld_w + c), acc);
+    for (int j = lane; j < d_in; j += 64) acc = fmaf(dwa[k * d_in + j], ld1(W + static_cast<int64_t>(j) * r.ld_w + c), acc);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-    if (lane == 0) da[c] = acc;
+    if (lane == 0) r.da[c] = acc;
 }
 
 heta_status ensure_attn(heta_graph *g, size_t bytes)
@@ -1650,6 +1753,41 @@ struct OutRange {
         : lo(reinterpret_cast<uintptr_t>(p)), hi(p && rows > 0 ? lo + static_cast<uintptr_t>((rows - 1) * ld + d) * esz : lo) {}
     bool overlaps(const OutRange &o) const { return lo < o.hi && o.lo < hi; }
 };
+
+// a table with the vector sets of one call
+ScoreTable score_table(const void *x, int64_t ld_x, int64_t n, int32_t d, int32_t n_sets, int32_t heads, const float *const *vecs,
+                              const float *const *scores)
+{
+    ScoreTable t{};
+    t.x = x;
+    t.ld_x = ld_x;
+    t.n = n;
+    t.d = d;
+    t.m.n_sets = n_sets;
+    t.m.K = heads;
+    t.m.NV = n_sets * heads;
+    for (int j = 0; j < n_sets; ++j) {
+        t.m.vec[j] = vecs[j];
+        t.m.score[j] = const_cast<float *>(scores[j]);
+    }
+    return t;
+}
+
+// launch(tables, k) for the tables of each kind k < n_kinds, up to kMultiTables at a time
+template <typename F> heta_status for_tables_of_a_kind(const std::vector<ScoreTable> &tabs, const std::vector<int> &kind, int n_kinds, F launch)
+{
+    for (int k = 0; k < n_kinds; ++k) {
+        ScoreTables q{};
+        for (size_t i = 0; i <= tabs.size(); ++i) {
+            if (i < tabs.size() && kind[i] == k) q.t[q.n++] = tabs[i];
+            if (q.n == 0 || (q.n < kMultiTables && i < tabs.size())) continue;
+            const heta_status e = launch(q, k);
+            if (e != HETA_OK) return e;
+            q.n = 0;
+        }
+    }
+    return HETA_OK;
+}
 
 } // namespace
 
@@ -1766,154 +1904,290 @@ static bool multi_ok(const void *x, heta_dtype dt, int64_t ld_x, int32_t d, int3
 heta_status heta_attn_score_multi(const void *x, heta_dtype dt, int64_t ld_x, int64_t n, int32_t d, int32_t n_sets,
                                   const float *const *vecs, int32_t heads, float *const *scores, void *hip_stream)
 {
+    const int32_t first[2] = {0, n_sets};
+    return heta_attn_score_tables(1, first, &x, dt, &ld_x, &n, &d, vecs, heads, scores, hip_stream);
+}
+
+heta_status heta_attn_score_tables(int32_t n, const int32_t *first, const void *const *x, heta_dtype dt, const int64_t *ld_x,
+                                   const int64_t *n_rows, const int32_t *d, const float *const *vecs, int32_t heads, float *const *scores,
+                                   void *hip_stream)
+{
     const char *who = "heta_attn_score_multi";
-    if (n_sets < 0 || (n_sets > 0 && (!vecs || !scores))) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
-    if (n_sets == 0) return HETA_OK;
-    for (int j = 0; j < n_sets; ++j)
-        if (!vecs[j] || (n > 0 && !scores[j])) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
-    if (n > 0 && !x) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
-    if (!valid_dtype(dt)) return fail(HETA_ERR_INVALID_ARG, "%s: bad dtype", who);
-    if (n < 0 || d <= 0 || ld_x < d || heads <= 0 || heads > kMaxHeads)
-        return fail(HETA_ERR_SHAPE, "%s: bad shape (n=%lld d=%d ld=%lld heads=%d)", who, (long long)n, d, (long long)ld_x, heads);
+    if (n < 0 || (n > 0 && (!first || !x || !ld_x || !n_rows || !d))) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
+    if (n > 0 && first[0] != 0) return fail(HETA_ERR_INVALID_ARG, "%s: first must start at 0", who);
+    for (int32_t i = 0; i < n; ++i) {
+        const int32_t n_sets = first[i + 1] - first[i];
+        if (n_sets < 0 || (n_sets > 0 && (!vecs || !scores))) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
+        if (n_sets == 0) continue;
+        for (int32_t j = first[i]; j < first[i + 1]; ++j)
+            if (!vecs[j] || (n_rows[i] > 0 && !scores[j])) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
+        if (n_rows[i] > 0 && !x[i]) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
+        if (!valid_dtype(dt)) return fail(HETA_ERR_INVALID_ARG, "%s: bad dtype", who);
+        if (n_rows[i] < 0 || d[i] <= 0 || ld_x[i] < d[i] || heads <= 0 || heads > kMaxHeads)
+            return fail(HETA_ERR_SHAPE, "%s: bad shape (n=%lld d=%d ld=%lld heads=%d)", who, (long long)n_rows[i], d[i], (long long)ld_x[i], heads);
+    }
     hipStream_t st = as_stream(hip_stream);
-    if (!multi_ok(x, dt, ld_x, d, n_sets, heads, vecs)) { // shapes the one-pass kernel does not take: set by set
-        for (int j = 0; j < n_sets; ++j) {
-            heta_status e = heta_attn_score(x, dt, ld_x, n, d, vecs[j], heads, 0, scores[j], hip_stream);
-            if (e != HETA_OK) return e;
+    try {
+        std::vector<ScoreTable> tabs;
+        std::vector<int> kind; // of kernel: chunks of 16 columns, tiles of 16 vectors, 16-byte stores
+        for (int32_t i = 0; i < n; ++i) {
+            const int32_t n_sets = first[i + 1] - first[i];
+            if (n_sets == 0) continue;
+            if (!multi_ok(x[i], dt, ld_x[i], d[i], n_sets, heads, vecs + first[i])) { // shapes the one-pass kernel does not take: set by set
+                for (int32_t j = first[i]; j < first[i + 1]; ++j) {
+                    heta_status e = heta_attn_score(x[i], dt, ld_x[i], n_rows[i], d[i], vecs[j], heads, 0, scores[j], hip_stream);
+                    if (e != HETA_OK) return e;
+                }
+                continue;
+            }
+            if (n_rows[i] == 0) continue;
+            ScoreTable t = score_table(x[i], ld_x[i], n_rows[i], d[i], n_sets, heads, vecs + first[i], scores + first[i]);
+            bool vec4 = heads % 4 == 0;
+            for (int32_t j = first[i]; j < first[i + 1]; ++j) vec4 = vec4 && aligned16(scores[j]);
+            // a wavefront takes tiles of 16 rows; up to 16 vectors leave registers for four workgroups per CU, 32 for two
+            const int nt = t.m.NV <= 16 ? 1 : 2;
+            t.nb = static_cast<int>(std::min<int64_t>((t.n + 63) / 64, nt == 1 ? 1024 : 512));
+            tabs.push_back(t);
+            kind.push_back((d[i] <= 32 ? 0 : d[i] <= 64 ? 4 : 8) + (nt == 1 ? 0 : 2) + (vec4 ? 1 : 0));
         }
-        return HETA_OK;
-    }
-    if (n == 0) return HETA_OK;
-    ScoreMulti m{};
-    m.n_sets = n_sets;
-    m.K = heads;
-    m.NV = n_sets * heads;
-    for (int j = 0; j < n_sets; ++j) {
-        m.vec[j] = vecs[j];
-        m.score[j] = scores[j];
-    }
-    // a wavefront takes tiles of 16 rows; up to 16 vectors leave registers for four workgroups per CU, 32 for two
-    const int nt = m.NV <= 16 ? 1 : 2;
-    const dim3 grid((unsigned)std::min<int64_t>((n + 63) / 64, nt == 1 ? 1024 : 512), (unsigned)((m.NV + 16 * nt - 1) / (16 * nt)));
-    bool vec4 = heads % 4 == 0;
-    for (int j = 0; j < n_sets; ++j) vec4 = vec4 && aligned16(scores[j]);
-    ProfScope prof("attn_score_multi_kernel", st, static_cast<double>(n) * (d * dtype_size(dt) + 4.0 * m.NV), 0);
-#define HETA_SM(TT, NC, NT, V4) hipLaunchKernelGGL((attn_score_multi_kernel<TT, NC, NT, V4>), grid, dim3(256), 0, st, static_cast<const TT *>(x), ld_x, n, (int)d, m)
-#define HETA_SM_V(TT, NC, NT) do { if (vec4) HETA_SM(TT, NC, NT, true); else HETA_SM(TT, NC, NT, false); } while (0)
-#define HETA_SM_N(TT, NC) do { if (nt == 1) HETA_SM_V(TT, NC, 1); else HETA_SM_V(TT, NC, 2); } while (0)
-#define HETA_SM_T(TT) do { if (d <= 32) HETA_SM_N(TT, 2); else if (d <= 64) HETA_SM_N(TT, 4); else HETA_SM_N(TT, 8); } while (0)
-    if (dt == HETA_F32) HETA_SM_T(float);
-    else HETA_SM_T(bf16_t);
+#define HETA_SM(TT, NC, NT, V4) hipLaunchKernelGGL((attn_score_multi_kernel<TT, NC, NT, V4>), dim3(blocks), dim3(256), 0, st, q)
+#define HETA_SM_V(TT, NC, NT) do { if (k & 1) HETA_SM(TT, NC, NT, true); else HETA_SM(TT, NC, NT, false); } while (0)
+#define HETA_SM_N(TT, NC) do { if (k & 2) HETA_SM_V(TT, NC, 2); else HETA_SM_V(TT, NC, 1); } while (0)
+#define HETA_SM_T(TT) do { if (k < 4) HETA_SM_N(TT, 2); else if (k < 8) HETA_SM_N(TT, 4); else HETA_SM_N(TT, 8); } while (0)
+        return for_tables_of_a_kind(tabs, kind, 12, [&](ScoreTables &q, int k) {
+            const unsigned nt = k & 2 ? 2 : 1;
+            unsigned blocks = 0;
+            double bytes = 0;
+            for (int c = 0; c < q.n; ++c) {
+                ScoreTable &t = q.t[c];
+                t.first = blocks;
+                blocks += t.nb * ((t.m.NV + 16 * nt - 1) / (16 * nt));
+                bytes += static_cast<double>(t.n) * (t.d * dtype_size(dt) + 4.0 * t.m.NV);
+            }
+            ProfScope prof("attn_score_multi_kernel", st, bytes, 0);
+            if (dt == HETA_F32) HETA_SM_T(float);
+            else HETA_SM_T(bf16_t);
+            HETA_LAUNCH_CHECK("attn_score_multi_kernel");
+            return HETA_OK;
+        });
 #undef HETA_SM_T
 #undef HETA_SM_N
 #undef HETA_SM_V
 #undef HETA_SM
-    HETA_LAUNCH_CHECK("attn_score_multi_kernel");
-    return HETA_OK;
+    } catch (const std::bad_alloc &) {
+        return fail(HETA_ERR_OOM, "%s: host allocation failed", who);
+    } catch (...) {
+        return fail(HETA_ERR_DEVICE, "%s: unexpected exception", who);
+    }
 }
 
 heta_status heta_attn_score_bwd_multi(heta_graph *g, const void *x, heta_dtype dt, int64_t ld_x, int64_t n, int32_t d,
                                       int32_t n_sets, const float *const *vecs, int32_t heads, const float *const *dscores,
                                       float *dx, int64_t ld_dx, float beta, float *const *dvecs, void *hip_stream)
 {
+    const int32_t first[2] = {0, n_sets};
+    return heta_attn_score_bwd_tables(g, 1, first, &x, dt, &ld_x, &n, &d, vecs, heads, dscores, &dx, &ld_dx, &beta, dvecs, hip_stream);
+}
+
+heta_status heta_attn_score_bwd_tables(heta_graph *g, int32_t n, const int32_t *first, const void *const *x, heta_dtype dt,
+                                       const int64_t *ld_x, const int64_t *n_rows, const int32_t *d, const float *const *vecs, int32_t heads,
+                                       const float *const *dscores, float *const *dx, const int64_t *ld_dx, const float *beta,
+                                       float *const *dvecs, void *hip_stream)
+{
     const char *who = "heta_attn_score_bwd_multi";
-    if (!g || n_sets < 0 || (n_sets > 0 && (!vecs || !dscores))) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
-    if (n_sets == 0) return HETA_OK;
-    for (int j = 0; j < n_sets; ++j)
-        if (!vecs[j] || (n > 0 && !dscores[j])) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
-    if (n > 0 && !x) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
-    if (!valid_dtype(dt)) return fail(HETA_ERR_INVALID_ARG, "%s: bad dtype", who);
-    if (n < 0 || d <= 0 || ld_x < d || heads <= 0 || heads > kMaxHeads || (dx && ld_dx < d))
-        return fail(HETA_ERR_SHAPE, "%s: bad shape (n=%lld d=%d heads=%d)", who, (long long)n, d, heads);
-    if (beta != 0.f && beta != 1.f) return fail(HETA_ERR_SHAPE, "%s: beta must be 0 or 1", who);
+    if (!g || n < 0 || (n > 0 && (!first || !x || !ld_x || !n_rows || !d || (dx && (!ld_dx || !beta)))))
+        return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
+    if (n > 0 && first[0] != 0) return fail(HETA_ERR_INVALID_ARG, "%s: first must start at 0", who);
+    for (int32_t i = 0; i < n; ++i) {
+        const int32_t n_sets = first[i + 1] - first[i];
+        if (n_sets < 0 || (n_sets > 0 && (!vecs || !dscores))) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
+        if (n_sets == 0) continue;
+        for (int32_t j = first[i]; j < first[i + 1]; ++j)
+            if (!vecs[j] || (n_rows[i] > 0 && !dscores[j])) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
+        if (n_rows[i] > 0 && !x[i]) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
+        if (!valid_dtype(dt)) return fail(HETA_ERR_INVALID_ARG, "%s: bad dtype", who);
+        if (n_rows[i] < 0 || d[i] <= 0 || ld_x[i] < d[i] || heads <= 0 || heads > kMaxHeads || (dx && dx[i] && ld_dx[i] < d[i]))
+            return fail(HETA_ERR_SHAPE, "%s: bad shape (n=%lld d=%d heads=%d)", who, (long long)n_rows[i], d[i], heads);
+        if (dx && beta[i] != 0.f && beta[i] != 1.f) return fail(HETA_ERR_SHAPE, "%s: beta must be 0 or 1", who);
+    }
     hipStream_t st = as_stream(hip_stream);
-    const bool dx_ok = !dx || (aligned16(dx) && ld_dx % 4 == 0);
-    if (!multi_ok(x, dt, ld_x, d, n_sets, heads, vecs) || !dx_ok) { // set by set, accumulating into dx
-        for (int j = 0; j < n_sets; ++j) {
-            heta_status e = heta_attn_score_bwd(g, x, dt, ld_x, n, d, vecs[j], heads, 0, dscores[j], dx, ld_dx,
-                                                j == 0 ? beta : 1.f, dvecs ? dvecs[j] : nullptr, hip_stream);
-            if (e != HETA_OK) return e;
+    try {
+        if (n > 1) { // the tables of one call run concurrently
+            std::vector<OutRange> outs;
+            for (int32_t i = 0; i < n; ++i) {
+                std::vector<OutRange> mine;
+                if (first[i + 1] > first[i] && dx && dx[i]) mine.emplace_back(dx[i], n_rows[i], ld_dx[i], d[i], 4);
+                for (int32_t j = first[i]; dvecs && j < first[i + 1]; ++j)
+                    if (dvecs[j]) mine.emplace_back(dvecs[j], heads, d[i], d[i], 4);
+                for (const OutRange &a : mine)
+                    for (const OutRange &b : outs)
+                        if (a.overlaps(b)) return fail(HETA_ERR_INVALID_ARG, "%s: the outputs of two tables overlap", who);
+                outs.insert(outs.end(), mine.begin(), mine.end());
+            }
         }
-        return HETA_OK;
-    }
-    ScoreMulti m{};
-    m.n_sets = n_sets;
-    m.K = heads;
-    m.NV = n_sets * heads;
-    bool any_dvec = false;
-    for (int j = 0; j < n_sets; ++j) {
-        m.vec[j] = vecs[j];
-        m.score[j] = const_cast<float *>(dscores[j]);
-        m.dvec[j] = dvecs ? dvecs[j] : nullptr;
-        any_dvec = any_dvec || m.dvec[j];
-    }
-    const int nt = m.NV <= 16 ? 1 : 2; // tiles of 16 vectors per workgroup of the parameter gradient
-    const int tiles = (m.NV + 16 * nt - 1) / (16 * nt), nvc = tiles * 16 * nt;
-    if (dx && n > 0) {
-        const int nc8 = (m.NV + 7) / 8 * 8;
-        const size_t lds = static_cast<size_t>(nc8) * (kMultiCols * sizeof(float) + sizeof(float *)); // at most 62,400 bytes
-        const int64_t blocks = std::min<int64_t>((n + 127) / 128, 768);
-        bool vec4 = heads % 4 == 0;
-        for (int j = 0; j < n_sets; ++j) vec4 = vec4 && aligned16(dscores[j]);
-        ProfScope prof("attn_score_bwd_input_kernel", st, static_cast<double>(n) * (d * (beta != 0.f ? 8.0 : 4.0) + 4.0 * m.NV), 0);
-        if (vec4) hipLaunchKernelGGL((attn_score_bwd_multi_input_kernel<true>), dim3((unsigned)blocks), dim3(256), lds, st, n, (int)d, m, dx, ld_dx, beta);
-        else hipLaunchKernelGGL((attn_score_bwd_multi_input_kernel<false>), dim3((unsigned)blocks), dim3(256), lds, st, n, (int)d, m, dx, ld_dx, beta);
-        HETA_LAUNCH_CHECK("attn_score_bwd_multi_input_kernel");
-    }
-    if (any_dvec) {
-        // slabs of a multiple of 64 rows (16 per wavefront and step), at most 1,024 slabs: enough workgroups for
-        // four per CU, and the slab sums (8 or 16 KB each) stay small beside the table
-        const int64_t most = dt == HETA_F32 && nt == 2 && d > 64 ? 768 : 1024;
-        const int64_t slab_rows = std::max<int64_t>(128, (n + most * 64 - 1) / (most * 64) * 64);
-        const int64_t n_slabs = (n + slab_rows - 1) / slab_rows;
-        if (n_slabs == 0) {
-            for (int j = 0; j < n_sets; ++j)
-                if (m.dvec[j]) HETA_HIP(hipMemsetAsync(m.dvec[j], 0, static_cast<size_t>(heads) * d * sizeof(float), st));
+        std::vector<ScoreTable> tabs;
+        std::vector<int> vec4_of, kind; // kind of the parameter gradient's kernel: 64-column chunks, tiles of 16 vectors; -1: no dvec asked for
+        for (int32_t i = 0; i < n; ++i) {
+            const int32_t n_sets = first[i + 1] - first[i];
+            if (n_sets == 0) continue;
+            float *const dxi = dx ? dx[i] : nullptr;
+            const float bi = dx ? beta[i] : 0.f;
+            float *const *const dv = dvecs ? dvecs + first[i] : nullptr;
+            const bool dx_ok = !dxi || (aligned16(dxi) && ld_dx[i] % 4 == 0);
+            if (!multi_ok(x[i], dt, ld_x[i], d[i], n_sets, heads, vecs + first[i]) || !dx_ok) { // set by set, accumulating into dx
+                for (int32_t j = 0; j < n_sets; ++j) {
+                    heta_status e = heta_attn_score_bwd(g, x[i], dt, ld_x[i], n_rows[i], d[i], vecs[first[i] + j], heads, 0, dscores[first[i] + j],
+                                                        dxi, dxi ? ld_dx[i] : 0, j == 0 ? bi : 1.f, dv ? dv[j] : nullptr, hip_stream);
+                    if (e != HETA_OK) return e;
+                }
+                continue;
+            }
+            ScoreTable t = score_table(x[i], ld_x[i], n_rows[i], d[i], n_sets, heads, vecs + first[i], dscores + first[i]);
+            bool vec4 = heads % 4 == 0, any_dvec = false;
+            for (int32_t j = 0; j < n_sets; ++j) {
+                t.m.dvec[j] = dv ? dv[j] : nullptr;
+                any_dvec = any_dvec || t.m.dvec[j];
+                vec4 = vec4 && aligned16(dscores[first[i] + j]);
+            }
+            t.dx = dxi;
+            t.ld_dx = dxi ? ld_dx[i] : 0;
+            t.beta = bi;
+            const int nt = t.m.NV <= 16 ? 1 : 2; // tiles of 16 vectors per workgroup of the parameter gradient
+            t.nvc = (t.m.NV + 16 * nt - 1) / (16 * nt) * 16 * nt;
+            // slabs of a multiple of 64 rows (16 per wavefront and step), at most 1,024 slabs: enough workgroups for
+            // four per CU, and the slab sums (8 or 16 KB each) stay small beside the table
+            const int64_t most = dt == HETA_F32 && nt == 2 && t.d > 64 ? 768 : 1024;
+            t.slab_rows = std::max<int64_t>(128, (t.n + most * 64 - 1) / (most * 64) * 64);
+            t.n_slabs = (t.n + t.slab_rows - 1) / t.slab_rows;
+            if (any_dvec && t.slab_rows > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "%s: too many rows", who);
+            tabs.push_back(t);
+            vec4_of.push_back(!t.dx || t.n == 0 ? -1 : vec4 ? 1 : 0);
+            kind.push_back(!any_dvec ? -1 : (nt == 1 ? 0 : 1) + (t.d <= 64 ? 0 : 2));
+        }
+        heta_status e = for_tables_of_a_kind(tabs, vec4_of, 2, [&](ScoreTables &q, int k) {
+            size_t lds = 0; // of the table with the most vectors: at most 62,400 bytes
+            unsigned blocks = 0;
+            double bytes = 0;
+            for (int c = 0; c < q.n; ++c) {
+                ScoreTable &t = q.t[c];
+                lds = std::max(lds, static_cast<size_t>((t.m.NV + 7) / 8 * 8) * (kMultiCols * sizeof(float) + sizeof(float *)));
+                t.nb = static_cast<int>(std::min<int64_t>((t.n + 127) / 128, 768));
+                t.first = blocks;
+                blocks += t.nb;
+                bytes += static_cast<double>(t.n) * (t.d * (t.beta != 0.f ? 8.0 : 4.0) + 4.0 * t.m.NV);
+            }
+            ProfScope prof("attn_score_bwd_input_kernel", st, bytes, 0);
+            if (k) hipLaunchKernelGGL((attn_score_bwd_multi_input_kernel<true>), dim3(blocks), dim3(256), lds, st, q);
+            else hipLaunchKernelGGL((attn_score_bwd_multi_input_kernel<false>), dim3(blocks), dim3(256), lds, st, q);
+            HETA_LAUNCH_CHECK("attn_score_bwd_multi_input_kernel");
             return HETA_OK;
-        }
-        if (slab_rows > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "%s: too many rows", who);
-        heta_status e = ensure_attn(g, static_cast<size_t>(n_slabs) * nvc * kMultiCols * sizeof(float));
+        });
         if (e != HETA_OK) return e;
-        float *part = static_cast<float *>(g->d_attn);
-        ProfScope prof("attn_score_bwd_param_kernel", st, static_cast<double>(n) * (d * dtype_size(dt) + 4.0 * m.NV), 0);
-        const dim3 grid((unsigned)n_slabs, (unsigned)tiles);
-#define HETA_SP(TT, NC, NT) hipLaunchKernelGGL((attn_score_bwd_multi_param_kernel<TT, NC, NT>), grid, dim3(256), 0, st, static_cast<const TT *>(x), ld_x, n, (int)d, m, (int)slab_rows, part)
-#define HETA_SP_N(TT, NC) do { if (nt == 1) HETA_SP(TT, NC, 1); else HETA_SP(TT, NC, 2); } while (0)
-#define HETA_SP_T(TT) do { if (d <= 64) HETA_SP_N(TT, 1); else HETA_SP_N(TT, 2); } while (0)
-        if (dt == HETA_F32) HETA_SP_T(float);
-        else HETA_SP_T(bf16_t);
+        const auto part_bytes = [](const ScoreTable &t) { return static_cast<size_t>(t.n_slabs) * t.nvc * kMultiCols * sizeof(float); };
+        for (size_t i0 = 0; i0 < tabs.size();) { // tables whose slab sums fit the workspace together: their launches, then one sum
+            std::vector<ScoreTable> some;
+            std::vector<int> some_kind;
+            size_t total = 0;
+            while (i0 < tabs.size() && some.size() < kMultiTables) {
+                if (kind[i0] >= 0) {
+                    if (!some.empty() && total + part_bytes(tabs[i0]) > kAttnGroupBytes) break;
+                    some.push_back(tabs[i0]);
+                    some_kind.push_back(kind[i0]);
+                    total += part_bytes(tabs[i0]);
+                }
+                ++i0;
+            }
+            if (some.empty()) continue;
+            e = ensure_attn(g, total);
+            if (e != HETA_OK) return e;
+            float *part = static_cast<float *>(g->d_attn);
+            ScoreTables all{};
+            unsigned sum_blocks = 0;
+            for (size_t c = 0; c < some.size(); ++c) {
+                ScoreTable &t = some[c];
+                t.part = part;
+                part += part_bytes(t) / sizeof(float);
+                t.nb = static_cast<int>(std::max<int64_t>(t.n_slabs, 1));
+                all.t[c] = t;
+                all.t[c].first = sum_blocks;
+                sum_blocks += static_cast<unsigned>((static_cast<int64_t>(t.nvc) * kMultiCols + 63) / 64);
+                if (t.n_slabs == 0) some_kind[c] = -1; // no rows: the sum writes zeros
+            }
+            all.n = static_cast<int>(some.size());
+            e = for_tables_of_a_kind(some, some_kind, 4, [&](ScoreTables &q, int k) {
+                unsigned blocks = 0;
+                double bytes = 0;
+                for (int c = 0; c < q.n; ++c) {
+                    ScoreTable &t = q.t[c];
+                    t.first = blocks;
+                    blocks += t.nb * (t.nvc / (k & 1 ? 32 : 16));
+                    bytes += static_cast<double>(t.n) * (t.d * dtype_size(dt) + 4.0 * t.m.NV);
+                }
+                ProfScope prof("attn_score_bwd_param_kernel", st, bytes, 0);
+#define HETA_SP(TT, NC, NT) hipLaunchKernelGGL((attn_score_bwd_multi_param_kernel<TT, NC, NT>), dim3(blocks), dim3(256), 0, st, q)
+#define HETA_SP_N(TT, NC) do { if (k & 1) HETA_SP(TT, NC, 2); else HETA_SP(TT, NC, 1); } while (0)
+#define HETA_SP_T(TT) do { if (k & 2) HETA_SP_N(TT, 2); else HETA_SP_N(TT, 1); } while (0)
+                if (dt == HETA_F32) HETA_SP_T(float);
+                else HETA_SP_T(bf16_t);
 #undef HETA_SP_T
 #undef HETA_SP_N
 #undef HETA_SP
-        HETA_LAUNCH_CHECK("attn_score_bwd_multi_param_kernel");
-        const int64_t elems = static_cast<int64_t>(nvc) * kMultiCols;
-        hipLaunchKernelGGL(attn_multi_slab_sum_kernel, dim3((unsigned)((elems + 63) / 64)), dim3(1024), 0, st, part, n_slabs, nvc, (int)d, m);
-        HETA_LAUNCH_CHECK("attn_multi_slab_sum_kernel");
+                HETA_LAUNCH_CHECK("attn_score_bwd_multi_param_kernel");
+                return HETA_OK;
+            });
+            if (e != HETA_OK) return e;
+            hipLaunchKernelGGL(attn_multi_slab_sum_kernel, dim3(sum_blocks), dim3(1024), 0, st, all);
+            HETA_LAUNCH_CHECK("attn_multi_slab_sum_kernel");
+        }
+        return HETA_OK;
+    } catch (const std::bad_alloc &) {
+        return fail(HETA_ERR_OOM, "%s: host allocation failed", who);
+    } catch (...) {
+        return fail(HETA_ERR_DEVICE, "%s: unexpected exception", who);
     }
-    return HETA_OK;
 }
 
 heta_status heta_attn_fold(const void *W, heta_dtype w_dt, int64_t ld_w, int32_t d_in, int32_t d_out, const float *a,
                            int32_t heads, float *wa, void *hip_stream)
 {
-    if (!W || !a || !wa) return fail(HETA_ERR_INVALID_ARG, "heta_attn_fold: null argument");
-    if (!valid_dtype(w_dt)) return fail(HETA_ERR_INVALID_ARG, "heta_attn_fold: bad dtype");
-    if (d_in <= 0 || d_out <= 0 || ld_w < d_out || heads <= 0 || heads > kMaxHeads || d_out % heads != 0 ||
-        static_cast<int64_t>(d_in) * d_out > (int64_t(1) << 30))
-        return fail(HETA_ERR_SHAPE, "heta_attn_fold: bad shape (d_in=%d d_out=%d ld_w=%lld heads=%d)", d_in, d_out,
-                    (long long)ld_w, heads);
-    if (reinterpret_cast<uintptr_t>(W) % dtype_size(w_dt) || reinterpret_cast<uintptr_t>(a) % 4 || reinterpret_cast<uintptr_t>(wa) % 4)
-        return fail(HETA_ERR_INVALID_ARG, "heta_attn_fold: pointer not aligned to its element size");
+    return heta_attn_fold_multi(1, &W, w_dt, &ld_w, &d_in, &d_out, &a, heads, &wa, hip_stream);
+}
+
+heta_status heta_attn_fold_multi(int32_t n, const void *const *W, heta_dtype w_dt, const int64_t *ld_w, const int32_t *d_in,
+                                 const int32_t *d_out, const float *const *a, int32_t heads, float *const *wa, void *hip_stream)
+{
+    if (n < 0 || (n > 0 && (!W || !ld_w || !d_in || !d_out || !a || !wa))) return fail(HETA_ERR_INVALID_ARG, "heta_attn_fold: null argument");
+    for (int32_t i = 0; i < n; ++i) {
+        if (!W[i] || !a[i] || !wa[i]) return fail(HETA_ERR_INVALID_ARG, "heta_attn_fold: null argument");
+        if (!valid_dtype(w_dt)) return fail(HETA_ERR_INVALID_ARG, "heta_attn_fold: bad dtype");
+        if (d_in[i] <= 0 || d_out[i] <= 0 || ld_w[i] < d_out[i] || heads <= 0 || heads > kMaxHeads || d_out[i] % heads != 0 ||
+            static_cast<int64_t>(d_in[i]) * d_out[i] > (int64_t(1) << 30))
+            return fail(HETA_ERR_SHAPE, "heta_attn_fold: bad shape (d_in=%d d_out=%d ld_w=%lld heads=%d)", d_in[i], d_out[i],
+                        (long long)ld_w[i], heads);
+        if (reinterpret_cast<uintptr_t>(W[i]) % dtype_size(w_dt) || reinterpret_cast<uintptr_t>(a[i]) % 4 || reinterpret_cast<uintptr_t>(wa[i]) % 4)
+            return fail(HETA_ERR_INVALID_ARG, "heta_attn_fold: pointer not aligned to its element size");
+    }
     hipStream_t st = as_stream(hip_stream);
-    const int F = d_out / heads;
-    const unsigned blocks = static_cast<unsigned>((static_cast<int64_t>(heads) * d_in + 63) / 64);
-    if (w_dt == HETA_F32)
-        hipLaunchKernelGGL(attn_fold_kernel<float>, dim3(blocks), dim3(64), 0, st, static_cast<const float *>(W), ld_w, (int)d_in,
-                           (int)heads, F, a, wa);
-    else
-        hipLaunchKernelGGL(attn_fold_kernel<bf16_t>, dim3(blocks), dim3(64), 0, st, static_cast<const bf16_t *>(W), ld_w, (int)d_in,
-                           (int)heads, F, a, wa);
-    HETA_LAUNCH_CHECK("attn_fold_kernel");
+    for (int32_t i0 = 0; i0 < n; i0 += kFoldItems) {
+        FoldItems q{};
+        q.n = std::min(n - i0, kFoldItems);
+        q.K = heads;
+        unsigned blocks = 0; // of an item at most 2^24 (d_in d_out <= 2^30), of a launch below 2^29
+        for (int c = 0; c < q.n; ++c) {
+            FoldItem &r = q.it[c];
+            r.W = W[i0 + c];
+            r.ld_w = ld_w[i0 + c];
+            r.d_in = d_in[i0 + c];
+            r.d_out = d_out[i0 + c];
+            r.a = a[i0 + c];
+            r.wa = wa[i0 + c];
+            r.first = blocks;
+            blocks += static_cast<unsigned>((static_cast<int64_t>(heads) * r.d_in + 63) / 64);
+        }
+        if (w_dt == HETA_F32) hipLaunchKernelGGL(attn_fold_kernel<float>, dim3(blocks), dim3(64), 0, st, q);
+        else hipLaunchKernelGGL(attn_fold_kernel<bf16_t>, dim3(blocks), dim3(64), 0, st, q);
+        HETA_LAUNCH_CHECK("attn_fold_kernel");
+    }
     return HETA_OK;
 }
 
@@ -1921,27 +2195,58 @@ heta_status heta_attn_fold_bwd(const void *W, heta_dtype w_dt, int64_t ld_w, int
                                int32_t heads, const float *dwa, float *dW, int64_t ld_dw, float beta, float *da,
                                void *hip_stream)
 {
-    if (!W || !a || !dwa) return fail(HETA_ERR_INVALID_ARG, "heta_attn_fold_bwd: null argument");
-    if (!valid_dtype(w_dt)) return fail(HETA_ERR_INVALID_ARG, "heta_attn_fold_bwd: bad dtype");
-    if (d_in <= 0 || d_out <= 0 || ld_w < d_out || heads <= 0 || heads > kMaxHeads || d_out % heads != 0 || (dW && ld_dw < d_out) ||
-        static_cast<int64_t>(d_in) * d_out > (int64_t(1) << 30))
-        return fail(HETA_ERR_SHAPE, "heta_attn_fold_bwd: bad shape (d_in=%d d_out=%d heads=%d)", d_in, d_out, heads);
-    if (beta != 0.f && beta != 1.f) return fail(HETA_ERR_SHAPE, "heta_attn_fold_bwd: beta must be 0 or 1");
-    if (reinterpret_cast<uintptr_t>(W) % dtype_size(w_dt) || reinterpret_cast<uintptr_t>(a) % 4 ||
-        reinterpret_cast<uintptr_t>(dwa) % 4 || reinterpret_cast<uintptr_t>(dW) % 4 || reinterpret_cast<uintptr_t>(da) % 4)
-        return fail(HETA_ERR_INVALID_ARG, "heta_attn_fold_bwd: pointer not aligned to its element size");
+    return heta_attn_fold_bwd_multi(1, &W, w_dt, &ld_w, &d_in, &d_out, &a, heads, &dwa, &dW, &ld_dw, beta, &da, hip_stream);
+}
+
+heta_status heta_attn_fold_bwd_multi(int32_t n, const void *const *W, heta_dtype w_dt, const int64_t *ld_w, const int32_t *d_in,
+                                     const int32_t *d_out, const float *const *a, int32_t heads, const float *const *dwa, float *const *dW,
+                                     const int64_t *ld_dw, float beta, float *const *da, void *hip_stream)
+{
+    if (n < 0 || (n > 0 && (!W || !ld_w || !d_in || !d_out || !a || !dwa || (dW && !ld_dw))))
+        return fail(HETA_ERR_INVALID_ARG, "heta_attn_fold_bwd: null argument");
+    for (int32_t i = 0; i < n; ++i) {
+        float *const dWi = dW ? dW[i] : nullptr, *const dai = da ? da[i] : nullptr;
+        if (!W[i] || !a[i] || !dwa[i]) return fail(HETA_ERR_INVALID_ARG, "heta_attn_fold_bwd: null argument");
+        if (!valid_dtype(w_dt)) return fail(HETA_ERR_INVALID_ARG, "heta_attn_fold_bwd: bad dtype");
+        if (d_in[i] <= 0 || d_out[i] <= 0 || ld_w[i] < d_out[i] || heads <= 0 || heads > kMaxHeads || d_out[i] % heads != 0 ||
+            (dWi && ld_dw[i] < d_out[i]) || static_cast<int64_t>(d_in[i]) * d_out[i] > (int64_t(1) << 30))
+            return fail(HETA_ERR_SHAPE, "heta_attn_fold_bwd: bad shape (d_in=%d d_out=%d heads=%d)", d_in[i], d_out[i], heads);
+        if (beta != 0.f && beta != 1.f) return fail(HETA_ERR_SHAPE, "heta_attn_fold_bwd: beta must be 0 or 1");
+        if (reinterpret_cast<uintptr_t>(W[i]) % dtype_size(w_dt) || reinterpret_cast<uintptr_t>(a[i]) % 4 ||
+            reinterpret_cast<uintptr_t>(dwa[i]) % 4 || reinterpret_cast<uintptr_t>(dWi) % 4 || reinterpret_cast<uintptr_t>(dai) % 4)
+            return fail(HETA_ERR_INVALID_ARG, "heta_attn_fold_bwd: pointer not aligned to its element size");
+    }
     hipStream_t st = as_stream(hip_stream);
-    const int F = d_out / heads;
-    const unsigned w_blocks = dW ? static_cast<unsigned>((static_cast<int64_t>(d_in) * d_out + 255) / 256) : 0;
-    const unsigned a_blocks = da ? static_cast<unsigned>((d_out + 3) / 4) : 0;
-    if (w_blocks + a_blocks == 0) return HETA_OK;
-    if (w_dt == HETA_F32)
-        hipLaunchKernelGGL(attn_fold_bwd_kernel<float>, dim3(w_blocks + a_blocks), dim3(256), 0, st, dwa, a, static_cast<const float *>(W), ld_w,
-                           (int)d_in, (int)heads, F, dW, ld_dw, beta, da, w_blocks);
-    else
-        hipLaunchKernelGGL(attn_fold_bwd_kernel<bf16_t>, dim3(w_blocks + a_blocks), dim3(256), 0, st, dwa, a, static_cast<const bf16_t *>(W), ld_w,
-                           (int)d_in, (int)heads, F, dW, ld_dw, beta, da, w_blocks);
-    HETA_LAUNCH_CHECK("attn_fold_bwd_kernel");
+    const int64_t most = max_blocks(256);
+    for (int32_t i0 = 0; i0 < n;) {
+        FoldItems q{};
+        q.K = heads;
+        q.beta = beta;
+        int64_t blocks = 0; // of an item at most 2^22 + 2^28, fewer than `most` for any matrix that has memory
+        for (; i0 < n && q.n < kFoldItems; ++i0) {
+            const unsigned w_blocks = dW && dW[i0] ? static_cast<unsigned>((static_cast<int64_t>(d_in[i0]) * d_out[i0] + 255) / 256) : 0;
+            const unsigned a_blocks = da && da[i0] ? static_cast<unsigned>((d_out[i0] + 3) / 4) : 0;
+            if (q.n > 0 && blocks + w_blocks + a_blocks > most) break;
+            if (w_blocks + a_blocks == 0) continue;
+            FoldItem &r = q.it[q.n++];
+            r.W = W[i0];
+            r.ld_w = ld_w[i0];
+            r.d_in = d_in[i0];
+            r.d_out = d_out[i0];
+            r.a = a[i0];
+            r.dwa = dwa[i0];
+            r.dW = dW ? dW[i0] : nullptr;
+            r.ld_dw = dW ? ld_dw[i0] : 0;
+            r.da = da ? da[i0] : nullptr;
+            r.first = static_cast<unsigned>(blocks);
+            r.w_blocks = w_blocks;
+            blocks += w_blocks + a_blocks;
+        }
+        if (q.n == 0) continue;
+        if (w_dt == HETA_F32) hipLaunchKernelGGL(attn_fold_bwd_kernel<float>, dim3((unsigned)blocks), dim3(256), 0, st, q);
+        else hipLaunchKernelGGL(attn_fold_bwd_kernel<bf16_t>, dim3((unsigned)blocks), dim3(256), 0, st, q);
+        HETA_LAUNCH_CHECK("attn_fold_bwd_kernel");
+    }
     return HETA_OK;
 }
 
@@ -2165,73 +2470,137 @@ heta_status heta_attn_bwd_dst(heta_graph *g, int32_t dst_type, int32_t n_rels, c
                               const float *const *er, const float *const *smax, const float *const *sinv, const float *const *apos,
                               float *const *der, float *const *pack, void *hip_stream)
 {
+    const int32_t first[2] = {0, n_rels};
+    return heta_attn_bwd_dst_multi(g, 1, &dst_type, first, rels, d, heads, slope, act, &h, &ld_h, &grad_out, &ld_go, &grad_in, &ld_gi, o, o_pos,
+                                   ld_o, er, smax, sinv, apos, der, pack, hip_stream);
+}
+
+heta_status heta_attn_bwd_dst_multi(heta_graph *g, int32_t n, const int32_t *dst_type, const int32_t *first, const int32_t *rels, int32_t d,
+                                    int32_t heads, float slope, heta_act act, const float *const *h, const int64_t *ld_h,
+                                    const float *const *grad_out, const int64_t *ld_go, float *const *grad_in, const int64_t *ld_gi,
+                                    const float *const *o, const float *const *o_pos, const int64_t *ld_o, const float *const *er,
+                                    const float *const *smax, const float *const *sinv, const float *const *apos, float *const *der,
+                                    float *const *pack, void *hip_stream)
+{
     const char *who = "heta_attn_bwd_dst";
     if (!g) return fail(HETA_ERR_INVALID_ARG, "%s: null graph", who);
-    if (dst_type < 0 || dst_type >= (int32_t)g->ntypes.size()) return fail(HETA_ERR_INVALID_ARG, "%s: node type %d out of range", who, dst_type);
-    if (n_rels < 1 || n_rels > kDstRels) return fail(HETA_ERR_SHAPE, "%s: need 1 <= n_rels <= %d", who, kDstRels);
-    if (act != HETA_ACT_NONE && act != HETA_ACT_RELU) return fail(HETA_ERR_INVALID_ARG, "%s: bad act", who);
+    if (n < 0 || (n > 0 && (!dst_type || !first))) return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
+    if (n > 0 && first[0] != 0) return fail(HETA_ERR_INVALID_ARG, "%s: first must start at 0", who);
     const bool relu = act == HETA_ACT_RELU;
-    if (!rels || !grad_out || (relu && (!h || !grad_in)) || !o || !o_pos || !ld_o || !er || !smax || !sinv || !apos || !der || !pack)
-        return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
-    if (heads <= 0 || heads > kMaxHeads || d <= 0 || d % heads != 0 || ld_go < d || (relu && (ld_h < d || ld_gi < d)))
-        return fail(HETA_ERR_SHAPE, "%s: need 1 <= heads <= %d dividing d and d <= ld", who, kMaxHeads);
-    DstParams p{};
-    p.g = grad_out;
-    p.h = relu ? h : nullptr;
-    p.ga = relu ? grad_in : nullptr;
-    p.ld_g = ld_go;
-    p.ld_h = ld_h;
-    p.ld_ga = ld_gi;
-    p.n = g->ntypes[dst_type].num_nodes;
-    p.d = d;
-    p.K = heads;
-    p.F = d / heads;
-    p.n_rels = n_rels;
-    p.slope = slope;
-    uintptr_t all16 = reinterpret_cast<uintptr_t>(grad_out), all4 = 0;
-    int64_t lds = ld_go;
-    if (relu) {
-        all16 |= reinterpret_cast<uintptr_t>(h) | reinterpret_cast<uintptr_t>(grad_in);
-        lds |= ld_h | ld_gi;
+    try {
+        std::vector<DstParams> types;
+        std::vector<int> kind; // 0: 4-byte loads, 1: row by row, 2: rows held in registers
+        std::vector<OutRange> outs;
+        std::vector<double> bytes;
+        int L = 1, T = 1; // lanes per row, chunks per lane
+        for (int32_t i = 0; i < n; ++i) {
+            const int32_t n_rels = first[i + 1] - first[i], t = dst_type[i];
+            if (t < 0 || t >= (int32_t)g->ntypes.size()) return fail(HETA_ERR_INVALID_ARG, "%s: node type %d out of range", who, t);
+            if (n_rels < 1 || n_rels > kDstRels) return fail(HETA_ERR_SHAPE, "%s: need 1 <= n_rels <= %d", who, kDstRels);
+            if (act != HETA_ACT_NONE && act != HETA_ACT_RELU) return fail(HETA_ERR_INVALID_ARG, "%s: bad act", who);
+            if (!rels || !grad_out || !ld_go || !o || !o_pos || !ld_o || !er || !smax || !sinv || !apos || !der || !pack || !grad_out[i] ||
+                (relu && (!h || !grad_in || !ld_h || !ld_gi || !h[i] || !grad_in[i])))
+                return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
+            if (heads <= 0 || heads > kMaxHeads || d <= 0 || d % heads != 0 || ld_go[i] < d || (relu && (ld_h[i] < d || ld_gi[i] < d)))
+                return fail(HETA_ERR_SHAPE, "%s: need 1 <= heads <= %d dividing d and d <= ld", who, kMaxHeads);
+            DstParams p{};
+            p.g = grad_out[i];
+            p.ld_g = ld_go[i];
+            uintptr_t all16 = reinterpret_cast<uintptr_t>(p.g), all4 = 0;
+            int64_t lds = p.ld_g;
+            if (relu) {
+                p.h = h[i];
+                p.ga = grad_in[i];
+                p.ld_h = ld_h[i];
+                p.ld_ga = ld_gi[i];
+                all16 |= reinterpret_cast<uintptr_t>(p.h) | reinterpret_cast<uintptr_t>(p.ga);
+                lds |= p.ld_h | p.ld_ga;
+            }
+            p.n = g->ntypes[t].num_nodes;
+            p.d = d;
+            p.K = heads;
+            p.F = d / heads;
+            p.n_rels = n_rels;
+            p.slope = slope;
+            for (int j = 0; j < n_rels; ++j) {
+                const int q = first[i] + j;
+                if (rels[q] < 0 || rels[q] >= (int32_t)g->rels.size() || g->rels[rels[q]].dst_type != t)
+                    return fail(HETA_ERR_INVALID_ARG, "%s: relation %d does not lead into type %d", who, rels[q], t);
+                if (p.n > 0 && (!o[q] || !o_pos[q] || !er[q] || !smax[q] || !sinv[q] || !apos[q] || !der[q] || !pack[q]))
+                    return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
+                if (ld_o[q] < d) return fail(HETA_ERR_SHAPE, "%s: need d <= ld", who);
+                p.it[j] = DstItem{o[q], o_pos[q], er[q], smax[q], sinv[q], apos[q], der[q], pack[q], ld_o[q]};
+                all16 |= reinterpret_cast<uintptr_t>(o[q]) | reinterpret_cast<uintptr_t>(o_pos[q]);
+                lds |= ld_o[q];
+                all4 |= reinterpret_cast<uintptr_t>(er[q]) | reinterpret_cast<uintptr_t>(smax[q]) | reinterpret_cast<uintptr_t>(sinv[q]) |
+                        reinterpret_cast<uintptr_t>(apos[q]) | reinterpret_cast<uintptr_t>(der[q]);
+                if (!aligned16(pack[q])) return fail(HETA_ERR_INVALID_ARG, "%s: pack not 16-byte aligned", who);
+            }
+            if ((all16 | all4) % 4) return fail(HETA_ERR_INVALID_ARG, "%s: pointer not 4-byte aligned", who);
+            if (n > 1) { // the types of one call run concurrently
+                std::vector<OutRange> mine;
+                if (relu) mine.emplace_back(p.ga, p.n, p.ld_ga, d, 4);
+                for (int j = 0; j < n_rels; ++j) {
+                    mine.emplace_back(p.it[j].der, p.n, heads, heads, 4);
+                    mine.emplace_back(p.it[j].pack, p.n, 4 * heads, 4 * heads, 4);
+                }
+                for (const OutRange &a : mine)
+                    for (const OutRange &b : outs)
+                        if (a.overlaps(b)) return fail(HETA_ERR_INVALID_ARG, "%s: the outputs of two types overlap", who);
+                outs.insert(outs.end(), mine.begin(), mine.end());
+            }
+            if (p.n == 0) continue;
+            const int n_chunks = d / 4, cph = p.F / 4;
+            while (L < n_chunks && L < 64) L <<= 1;
+            while (L * T < n_chunks) T <<= 1;
+            const bool vec = d % 4 == 0 && p.F % 4 == 0 && all16 % 16 == 0 && lds % 4 == 0;
+            const bool one_pass = vec && (T == 1 || (T <= 4 && (cph & (cph - 1)) == 0));
+            types.push_back(p);
+            kind.push_back(one_pass ? 2 : vec ? 1 : 0);
+            bytes.push_back(static_cast<double>(p.n) * (4.0 * d * (1 + (relu ? 2 : 0) + 2 * n_rels) + 36.0 * heads * n_rels));
+        }
+        hipStream_t st = as_stream(hip_stream);
+        for (int k = 2; k >= 0; --k) {
+            DstTypes m{};
+            double group_bytes = 0;
+            for (size_t i = 0; i <= types.size(); ++i) {
+                const bool mine = i < types.size() && kind[i] == k;
+                if (mine) {
+                    m.t[m.n++] = types[i];
+                    group_bytes += bytes[i];
+                }
+                if (m.n == 0 || (m.n < kDstTypes && i < types.size())) continue;
+                // two rows per lane group once that still leaves eight wavefronts per SIMD, else one; one of four chunks per lane
+                int64_t all_rows = 0, blocks = 0;
+                for (int c = 0; c < m.n; ++c) all_rows += m.t[c].n;
+                const int R = k == 2 && T < 4 && all_rows * L >= int64_t(2) * 64 * 8192 ? 2 : 1;
+                const int64_t rows = k == 2 ? static_cast<int64_t>(4) * R * (64 / L) : 4;
+                for (int c = 0; c < m.n; ++c) {
+                    m.t[c].first = blocks;
+                    blocks += (m.t[c].n + rows - 1) / rows;
+                }
+                ProfScope prof("attn_dst_kernel", st, group_bytes, 0);
+                launch_pieces(blocks, 256, [&](unsigned piece, unsigned count) {
+                    m.first = piece;
+                    if (k == 0) hipLaunchKernelGGL(attn_dst_any_kernel<1>, dim3(count), dim3(256), 0, st, m);
+                    else if (k == 1) hipLaunchKernelGGL(attn_dst_any_kernel<4>, dim3(count), dim3(256), 0, st, m);
+                    else if (T == 4) hipLaunchKernelGGL((attn_dst_kernel<1, 4>), dim3(count), dim3(256), 0, st, m, L);
+                    else if (T == 2 && R == 2) hipLaunchKernelGGL((attn_dst_kernel<2, 2>), dim3(count), dim3(256), 0, st, m, L);
+                    else if (T == 2) hipLaunchKernelGGL((attn_dst_kernel<1, 2>), dim3(count), dim3(256), 0, st, m, L);
+                    else if (R == 2) hipLaunchKernelGGL((attn_dst_kernel<2, 1>), dim3(count), dim3(256), 0, st, m, L);
+                    else hipLaunchKernelGGL((attn_dst_kernel<1, 1>), dim3(count), dim3(256), 0, st, m, L);
+                });
+                HETA_LAUNCH_CHECK("attn_dst_kernel");
+                m.n = 0;
+                group_bytes = 0;
+            }
+        }
+        return HETA_OK;
+    } catch (const std::bad_alloc &) {
+        return fail(HETA_ERR_OOM, "%s: host allocation failed", who);
+    } catch (...) {
+        return fail(HETA_ERR_DEVICE, "%s: unexpected exception", who);
     }
-    for (int j = 0; j < n_rels; ++j) {
-        if (rels[j] < 0 || rels[j] >= (int32_t)g->rels.size() || g->rels[rels[j]].dst_type != dst_type)
-            return fail(HETA_ERR_INVALID_ARG, "%s: relation %d does not lead into type %d", who, rels[j], dst_type);
-        if (p.n > 0 && (!o[j] || !o_pos[j] || !er[j] || !smax[j] || !sinv[j] || !apos[j] || !der[j] || !pack[j]))
-            return fail(HETA_ERR_INVALID_ARG, "%s: null argument", who);
-        if (ld_o[j] < d) return fail(HETA_ERR_SHAPE, "%s: need d <= ld", who);
-        p.it[j] = DstItem{o[j], o_pos[j], er[j], smax[j], sinv[j], apos[j], der[j], pack[j], ld_o[j]};
-        all16 |= reinterpret_cast<uintptr_t>(o[j]) | reinterpret_cast<uintptr_t>(o_pos[j]);
-        lds |= ld_o[j];
-        all4 |= reinterpret_cast<uintptr_t>(er[j]) | reinterpret_cast<uintptr_t>(smax[j]) | reinterpret_cast<uintptr_t>(sinv[j]) |
-                reinterpret_cast<uintptr_t>(apos[j]) | reinterpret_cast<uintptr_t>(der[j]);
-        if (!aligned16(pack[j])) return fail(HETA_ERR_INVALID_ARG, "%s: pack not 16-byte aligned", who);
-    }
-    if ((all16 | all4) % 4) return fail(HETA_ERR_INVALID_ARG, "%s: pointer not 4-byte aligned", who);
-    if (p.n == 0) return HETA_OK;
-    hipStream_t st = as_stream(hip_stream);
-    ProfScope prof("attn_dst_kernel", st, static_cast<double>(p.n) * (4.0 * d * (1 + (relu ? 2 : 0) + 2 * n_rels) + 36.0 * heads * n_rels), 0);
-    const int n_chunks = d / 4, cph = p.F / 4;
-    const bool vec = d % 4 == 0 && p.F % 4 == 0 && all16 % 16 == 0 && lds % 4 == 0;
-    int L = 1, T = 1; // lanes per row, chunks per lane
-    while (L < n_chunks && L < 64) L <<= 1;
-    while (L * T < n_chunks) T <<= 1;
-    const bool one_pass = vec && (T == 1 || (T <= 4 && (cph & (cph - 1)) == 0));
-    // two rows per lane group once that still leaves eight wavefronts per SIMD, else one; one of four chunks per lane
-    const int R = one_pass && T < 4 && p.n * L >= int64_t(2) * 64 * 8192 ? 2 : 1;
-    const int64_t rows = one_pass ? static_cast<int64_t>(4) * R * (64 / L) : 4;
-    launch_pieces((p.n + rows - 1) / rows, 256, [&](unsigned first, unsigned count) {
-        p.first = first;
-        if (!vec) hipLaunchKernelGGL(attn_dst_any_kernel<1>, dim3(count), dim3(256), 0, st, p);
-        else if (!one_pass) hipLaunchKernelGGL(attn_dst_any_kernel<4>, dim3(count), dim3(256), 0, st, p);
-        else if (T == 4) hipLaunchKernelGGL((attn_dst_kernel<1, 4>), dim3(count), dim3(256), 0, st, p, L);
-        else if (T == 2 && R == 2) hipLaunchKernelGGL((attn_dst_kernel<2, 2>), dim3(count), dim3(256), 0, st, p, L);
-        else if (T == 2) hipLaunchKernelGGL((attn_dst_kernel<1, 2>), dim3(count), dim3(256), 0, st, p, L);
-        else if (R == 2) hipLaunchKernelGGL((attn_dst_kernel<2, 1>), dim3(count), dim3(256), 0, st, p, L);
-        else hipLaunchKernelGGL((attn_dst_kernel<1, 1>), dim3(count), dim3(256), 0, st, p, L);
-    });
-    HETA_LAUNCH_CHECK("attn_dst_kernel");
-    return HETA_OK;
 }
 
 heta_status heta_rel_attn_bwd_src(heta_graph *g, int32_t rel, const void *z, heta_dtype z_dt, int64_t ld_z, int32_t d, int32_t heads,

@@ -2,6 +2,9 @@
 // the designated worker's step) and the backward of its optional activation.  Pure streaming:
 // every element is read once per partial and written once, 128 bits per lane where the
 // layout allows.
+#include <algorithm>
+#include <utility>
+
 #include "heta_internal.h"
 
 namespace heta {
@@ -11,19 +14,30 @@ constexpr int kMaxPartials = 16;
 struct ReduceParams {
     const float *part[kMaxPartials];
     int n_partials;
-    unsigned first; // first workgroup of this launch
+    int d;
+    int64_t first; // its first workgroup
     int64_t ld, ld_out;
     int64_t n_rows;
-    int d;
-    int relu;
     float *out;
+};
+// Several node types in one launch, their workgroups end to end: by itself a type of a few thousand rows takes the 4 to 5 us
+// that any launch takes.
+constexpr int kReduceTypes = 8;
+struct ReduceTypes { // passed by value
+    ReduceParams t[kReduceTypes];
+    int64_t first; // first workgroup of this launch
+    int n, relu;
 };
 
 template <int V> // V floats per thread (4: vector path, 1: scalar path)
-__global__ void __launch_bounds__(256) cross_rel_reduce_kernel(ReduceParams p)
+__global__ void __launch_bounds__(256) cross_rel_reduce_kernel(ReduceTypes m)
 {
+    const int64_t wg = m.first + blockIdx.x;
+    int q = 0;
+    while (q + 1 < m.n && wg >= m.t[q + 1].first) ++q; // uniform
+    const ReduceParams &p = m.t[q];
     const int per_row = (p.d + V - 1) / V;
-    const int64_t t = (static_cast<int64_t>(p.first) + blockIdx.x) * 256 + threadIdx.x;
+    const int64_t t = (wg - p.first) * 256 + threadIdx.x;
     const int64_t i = t / per_row;
     const int c = static_cast<int>(t % per_row) * V;
     if (i >= p.n_rows) return;
@@ -33,12 +47,12 @@ __global__ void __launch_bounds__(256) cross_rel_reduce_kernel(ReduceParams p)
             const float4 v = *reinterpret_cast<const float4 *>(p.part[k] + i * p.ld + c);
             a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
         }
-        if (p.relu) { a.x = fmaxf(a.x, 0.f); a.y = fmaxf(a.y, 0.f); a.z = fmaxf(a.z, 0.f); a.w = fmaxf(a.w, 0.f); }
+        if (m.relu) { a.x = fmaxf(a.x, 0.f); a.y = fmaxf(a.y, 0.f); a.z = fmaxf(a.z, 0.f); a.w = fmaxf(a.w, 0.f); }
         *reinterpret_cast<float4 *>(p.out + i * p.ld_out + c) = a;
     } else {
         float a = 0.f;
         for (int k = 0; k < p.n_partials; ++k) a += p.part[k][i * p.ld + c];
-        if (p.relu) a = fmaxf(a, 0.f);
+        if (m.relu) a = fmaxf(a, 0.f);
         p.out[i * p.ld_out + c] = a;
     }
 }
@@ -166,43 +180,92 @@ heta_status heta_cross_rel_reduce(const heta_graph *g, int32_t dst_type, const f
                                   int32_t n_partials, int64_t ld, int32_t d_out, heta_act act,
                                   float *out, int64_t ld_out, void *hip_stream)
 {
-    if (!g || !partials || !out) return fail(HETA_ERR_INVALID_ARG, "heta_cross_rel_reduce: null argument");
-    if (dst_type < 0 || dst_type >= (int32_t)g->ntypes.size())
-        return fail(HETA_ERR_INVALID_ARG, "heta_cross_rel_reduce: node type %d out of range", dst_type);
-    if (n_partials < 1 || n_partials > kMaxPartials)
-        return fail(HETA_ERR_INVALID_ARG, "heta_cross_rel_reduce: n_partials must be in [1, %d]", kMaxPartials);
-    if (act != HETA_ACT_NONE && act != HETA_ACT_RELU) return fail(HETA_ERR_INVALID_ARG, "heta_cross_rel_reduce: bad act");
-    if (d_out <= 0 || ld < d_out || ld_out < d_out) return fail(HETA_ERR_SHAPE, "heta_cross_rel_reduce: bad shape");
-    ReduceParams p{};
-    bool vec = (d_out % 4 == 0) && (ld % 4 == 0) && (ld_out % 4 == 0) && aligned16(out);
-    for (int k = 0; k < n_partials; ++k) {
-        if (!partials[k]) return fail(HETA_ERR_INVALID_ARG, "heta_cross_rel_reduce: partial %d is NULL", k);
-        if (reinterpret_cast<uintptr_t>(partials[k]) & 3u)
-            return fail(HETA_ERR_INVALID_ARG, "heta_cross_rel_reduce: partial %d not 4-byte aligned", k);
-        vec = vec && aligned16(partials[k]);
-        p.part[k] = partials[k];
+    if (!partials || !out) return fail(HETA_ERR_INVALID_ARG, "heta_cross_rel_reduce: null argument");
+    const int32_t first[2] = {0, n_partials};
+    return heta_cross_rel_reduce_multi(g, 1, &dst_type, first, partials, &ld, &d_out, act, &out, &ld_out, hip_stream);
+}
+
+heta_status heta_cross_rel_reduce_multi(const heta_graph *g, int32_t n, const int32_t *dst_type, const int32_t *first,
+                                        const float *const *partials, const int64_t *ld, const int32_t *d_out, heta_act act, float *const *outs,
+                                        const int64_t *ld_out, void *hip_stream)
+{
+    if (!g || n < 0 || (n > 0 && (!dst_type || !first || !partials || !ld || !d_out || !outs || !ld_out)))
+        return fail(HETA_ERR_INVALID_ARG, "heta_cross_rel_reduce: null argument");
+    if (n > 0 && first[0] != 0) return fail(HETA_ERR_INVALID_ARG, "heta_cross_rel_reduce: first must start at 0");
+    try {
+        std::vector<ReduceParams> types[2]; // by width of the accesses: one float, four
+        std::vector<int64_t> blocks[2];
+        std::vector<std::pair<uintptr_t, uintptr_t>> ranges;
+        for (int32_t i = 0; i < n; ++i) {
+            if (dst_type[i] < 0 || dst_type[i] >= (int32_t)g->ntypes.size())
+                return fail(HETA_ERR_INVALID_ARG, "heta_cross_rel_reduce: node type %d out of range", dst_type[i]);
+            const int32_t n_partials = first[i + 1] - first[i];
+            if (n_partials < 1 || n_partials > kMaxPartials)
+                return fail(HETA_ERR_INVALID_ARG, "heta_cross_rel_reduce: n_partials must be in [1, %d]", kMaxPartials);
+            if (act != HETA_ACT_NONE && act != HETA_ACT_RELU) return fail(HETA_ERR_INVALID_ARG, "heta_cross_rel_reduce: bad act");
+            if (d_out[i] <= 0 || ld[i] < d_out[i] || ld_out[i] < d_out[i]) return fail(HETA_ERR_SHAPE, "heta_cross_rel_reduce: bad shape");
+            if (!outs[i]) return fail(HETA_ERR_INVALID_ARG, "heta_cross_rel_reduce: null argument");
+            ReduceParams p{};
+            bool vec = (d_out[i] % 4 == 0) && (ld[i] % 4 == 0) && (ld_out[i] % 4 == 0) && aligned16(outs[i]);
+            for (int k = 0; k < n_partials; ++k) {
+                const float *part = partials[first[i] + k];
+                if (!part) return fail(HETA_ERR_INVALID_ARG, "heta_cross_rel_reduce: partial %d is NULL", k);
+                if (reinterpret_cast<uintptr_t>(part) & 3u)
+                    return fail(HETA_ERR_INVALID_ARG, "heta_cross_rel_reduce: partial %d not 4-byte aligned", k);
+                vec = vec && aligned16(part);
+                p.part[k] = part;
+            }
+            if (reinterpret_cast<uintptr_t>(outs[i]) & 3u) return fail(HETA_ERR_INVALID_ARG, "heta_cross_rel_reduce: out not aligned");
+            p.n_partials = n_partials;
+            p.ld = ld[i];
+            p.ld_out = ld_out[i];
+            p.n_rows = g->ntypes[dst_type[i]].num_nodes;
+            p.d = d_out[i];
+            p.out = outs[i];
+            if (p.n_rows == 0) continue;
+            const int64_t threads = p.n_rows * (vec ? p.d / 4 : p.d);
+            if ((threads + 255) / 256 > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "heta_cross_rel_reduce: too large");
+            if (n > 1) { // the types of one call run concurrently: none may write what another one reads or writes
+                const auto range = [&](const float *x, int64_t l) {
+                    const uintptr_t lo = reinterpret_cast<uintptr_t>(x);
+                    return std::make_pair(lo, lo + static_cast<uintptr_t>((p.n_rows - 1) * l + p.d) * sizeof(float));
+                };
+                ranges.push_back(range(p.out, p.ld_out));
+                const auto o = ranges.back();
+                for (size_t q = 0; q + 1 < ranges.size(); ++q)
+                    if (o.first < ranges[q].second && ranges[q].first < o.second)
+                        return fail(HETA_ERR_INVALID_ARG, "heta_cross_rel_reduce: the outputs of two types overlap");
+            }
+            types[vec].push_back(p);
+            blocks[vec].push_back((threads + 255) / 256);
+        }
+        for (int vec = 1; vec >= 0; --vec)
+            for (size_t i0 = 0; i0 < types[vec].size(); i0 += kReduceTypes) {
+                ReduceTypes m{};
+                m.n = static_cast<int>(std::min<size_t>(kReduceTypes, types[vec].size() - i0));
+                m.relu = act == HETA_ACT_RELU;
+                int64_t all = 0;
+                double bytes = 0;
+                for (int q = 0; q < m.n; ++q) {
+                    m.t[q] = types[vec][i0 + q];
+                    m.t[q].first = all;
+                    all += blocks[vec][i0 + q];
+                    bytes += (m.t[q].n_partials + 1.0) * static_cast<double>(m.t[q].n_rows) * m.t[q].d * 4.0;
+                }
+                ProfScope prof("cross_rel_reduce_kernel", as_stream(hip_stream), bytes, 0);
+                launch_pieces(all, 256, [&](unsigned piece, unsigned count) {
+                    m.first = piece;
+                    if (vec) hipLaunchKernelGGL(cross_rel_reduce_kernel<4>, dim3(count), dim3(256), 0, as_stream(hip_stream), m);
+                    else hipLaunchKernelGGL(cross_rel_reduce_kernel<1>, dim3(count), dim3(256), 0, as_stream(hip_stream), m);
+                });
+                HETA_LAUNCH_CHECK("cross_rel_reduce_kernel");
+            }
+        return HETA_OK;
+    } catch (const std::bad_alloc &) {
+        return fail(HETA_ERR_OOM, "heta_cross_rel_reduce: host allocation failed");
+    } catch (...) {
+        return fail(HETA_ERR_DEVICE, "heta_cross_rel_reduce: unexpected exception");
     }
-    if (reinterpret_cast<uintptr_t>(out) & 3u) return fail(HETA_ERR_INVALID_ARG, "heta_cross_rel_reduce: out not aligned");
-    p.n_partials = n_partials;
-    p.ld = ld;
-    p.ld_out = ld_out;
-    p.n_rows = g->ntypes[dst_type].num_nodes;
-    p.d = d_out;
-    p.relu = (act == HETA_ACT_RELU);
-    p.out = out;
-    if (p.n_rows == 0) return HETA_OK;
-    const int64_t threads = p.n_rows * (vec ? d_out / 4 : d_out);
-    const int64_t blocks = (threads + 255) / 256;
-    if (blocks > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "heta_cross_rel_reduce: too large");
-    ProfScope prof("cross_rel_reduce_kernel", as_stream(hip_stream),
-                   (n_partials + 1.0) * static_cast<double>(p.n_rows) * d_out * 4.0, 0);
-    launch_pieces(blocks, 256, [&](unsigned first, unsigned count) {
-        p.first = first;
-        if (vec) hipLaunchKernelGGL(cross_rel_reduce_kernel<4>, dim3(count), dim3(256), 0, as_stream(hip_stream), p);
-        else hipLaunchKernelGGL(cross_rel_reduce_kernel<1>, dim3(count), dim3(256), 0, as_stream(hip_stream), p);
-    });
-    HETA_LAUNCH_CHECK("cross_rel_reduce_kernel");
-    return HETA_OK;
 }
 
 heta_status heta_act_bwd(int64_t n_rows, int32_t d, heta_act act, const float *h, int64_t ld_h,

@@ -5,17 +5,18 @@ sums the modules' outputs over the relations into a destination type, followed b
 module allocates device buffers with torch and issues the C-ABI calls; it computes nothing
 itself.  Per relation r from source type s to destination type t:
 
-    Z_r  = H0_s W_r                         heta_project_batch (all relations leaving s in one launch)
+    Z_r  = H0_s W_r                         heta_project_multi (all relations leaving s in one launch)
     el_r = <Z_r[u, head k], a_r[k]>         = <H0_s[u], (W_r a_r)[k]>: heta_attn_fold, then a score of the input
                                             table (narrower than Z_r, and never rounded to the storage type)
     er_r = <H0_t[v], q_r[k]>                a score of the destination type's table; all scores of one table in
-                                            one pass (heta_attn_score_multi)
+                                            one pass (heta_attn_score_tables)
     O_r  = edge-softmax weighted sum of Z_r heta_rel_attn_fwd_train
     H_t  = ReLU(sum_r O_r)                  heta_cross_rel_reduce
 
 and the backward runs the same chain in reverse (heta_attn_bwd_dst per destination type with the
-activation in it, heta_rel_attn_bwd_src per relation, heta_attn_score_bwd_multi,
-heta_project_wgrad_batch, heta_attn_fold_bwd, heta_project_sum).
+activation in it, heta_rel_attn_bwd_src per relation, heta_attn_score_bwd_tables,
+heta_project_wgrad, heta_attn_fold_bwd, and the summed heta_project).  Each step is one call for all relations or
+node types: what is too small to fill the chip shares its launches.
 """
 from __future__ import annotations
 
@@ -28,6 +29,16 @@ from . import binding as hb
 _MAX_BATCH = 8  # products per batched projection launch
 _MAX_SETS = 8   # score vector sets per one-pass score call
 _MAX_DST = 8    # relations per destination-side pass of the backward
+
+
+def _parts(lists: Dict[int, List], most: int) -> List:
+    """(key, at most `most` entries of its list), every list in order"""
+    return [(k, v[i:i + most]) for k, v in lists.items() for i in range(0, len(v), most)]
+
+
+def _turns(lists: Dict[int, List], most: int) -> List[List]:
+    """The same in turns of one part per key: the parts of one key write the same rows and follow one another."""
+    return [[(k, v[i:i + most]) for k, v in lists.items() if i < len(v)] for i in range(0, max(map(len, lists.values())), most)]
 
 
 class RgatLayer:
@@ -101,64 +112,48 @@ class RgatLayer:
     # ---- forward ------------------------------------------------------------------------------------
     def forward(self, stream=None) -> Dict[int, torch.Tensor]:
         g = self.g
-        for s, rs in self.rels_from.items():
-            for i in range(0, len(rs), _MAX_BATCH):
-                part = rs[i:i + _MAX_BATCH]
-                hb.heta_project_batch([self.tables[s]] * len(part), [self.W[r] for r in part],
-                                      [self.Z[r] for r in part], stream=stream, graph=self.g)
-        for r in self.rels:
-            hb.heta_attn_fold(self.W[r], self.a[r], self.wa[r], stream=stream)
+        hb.heta_project_multi(g, [(g.ntypes[s][0], [self.tables[s]] * len(part), [self.W[r] for r in part], [self.Z[r] for r in part])
+                                  for s, part in _parts(self.rels_from, _MAX_BATCH)], stream=stream)
+        hb.heta_attn_fold_multi([(self.W[r], self.a[r], self.wa[r]) for r in self.rels], stream=stream)
         # every score of a node type's table in one pass over it: el of the relations leaving the type, er of
         # those entering it
-        for t, sets in self._score_sets.items():
-            for i in range(0, len(sets), _MAX_SETS):
-                part = sets[i:i + _MAX_SETS]
-                hb.heta_attn_score_multi(self.tables[t], [self.wa[r] if src else self.q[r] for r, src in part],
-                                         [self.el[r] if src else self.er[r] for r, src in part], stream=stream)
+        hb.heta_attn_score_tables([(self.tables[t], [self.wa[r] if src else self.q[r] for r, src in part],
+                                    [self.el[r] if src else self.er[r] for r, src in part])
+                                   for t, part in _parts(self._score_sets, _MAX_SETS)], stream=stream)
         every = lambda x: [x[r] for r in self.rels]  # noqa: E731
         hb.heta_rel_attn_fwd_train_multi(g, self.rels, every(self.Z), every(self.el), every(self.er), self.slope, every(self.O),
                                          every(self.smax), every(self.sinv), every(self.Opos), every(self.apos), stream=stream)
-        for t, rs in self.rels_into.items():
-            hb.heta_cross_rel_reduce(g, t, [self.O[r] for r in rs], self.H[t], act=self.act, stream=stream)
+        hb.heta_cross_rel_reduce_multi(g, [(t, [self.O[r] for r in rs], self.H[t]) for t, rs in self.rels_into.items()], act=self.act, stream=stream)
         return self.H
 
     # ---- backward -----------------------------------------------------------------------------------
     def backward(self, G: Dict[int, torch.Tensor], stream=None):
         """G[t]: upstream gradient of H_t (fp32).  Fills dW, da, dq per relation and dH0 per node type."""
         g = self.g
-        grads = {}
-        for t, rs in self.rels_into.items():  # activation, der and the packed terms of all relations into t: one pass
-            grad = G[t]
-            for i in range(0, len(rs), _MAX_DST):
-                part = rs[i:i + _MAX_DST]
-                of = lambda x: [x[r] for r in part]  # noqa: E731
-                grad = hb.heta_attn_bwd_dst(g, t, part, self.slope, self.act if i == 0 else hb.HETA_ACT_NONE, self.H[t], grad,
-                                            self._Gact.get(t), of(self.O), of(self.Opos), of(self.er), of(self.smax), of(self.sinv),
-                                            of(self.apos), of(self.d_er), of(self.pack), stream=stream)
-            grads[t] = grad
-        written = set()
+        grads = dict(G)
+        # activation, der and the packed terms of all relations into a type: one pass over its rows, _MAX_DST relations at a time
+        for turn, parts in enumerate(_turns(self.rels_into, _MAX_DST)):
+            act = self.act if turn == 0 else hb.HETA_ACT_NONE
+            each = lambda x, part: [x[r] for r in part]  # noqa: E731
+            hb.heta_attn_bwd_dst_multi(g, [(t, part, self.H[t], grads[t], self._Gact.get(t)) + tuple(
+                each(x, part) for x in (self.O, self.Opos, self.er, self.smax, self.sinv, self.apos, self.d_er, self.pack))
+                for t, part in parts], self.slope, act, stream=stream)
+            if turn == 0 and self.relu:
+                grads.update(self._Gact)
         every = lambda x: [x[r] for r in self.rels]  # noqa: E731
         hb.heta_rel_attn_bwd_src_multi(g, self.rels, every(self.Z), every(self.el), self.slope, every(self.pack),
                                        [grads[g.rels[r][1]] for r in self.rels], every(self.dZ), every(self.d_el), stream=stream)
         # el = <H0_s, wa> reaches the source type's table and, through wa, W_r and a_r; er = <H0_t, q> reaches the
         # destination type's table and gives dq: per node type, all of them in one pass over its table
-        for t, sets in self._score_sets.items():
-            for i in range(0, len(sets), _MAX_SETS):
-                part = sets[i:i + _MAX_SETS]
-                hb.heta_attn_score_bwd_multi(g, self.tables[t], [self.wa[r] if src else self.q[r] for r, src in part],
-                                             [self.d_el[r] if src else self.d_er[r] for r, src in part], dx=self.dH0[t],
-                                             beta=1.0 if t in written else 0.0,
-                                             dvecs=[self.dwa[r] if src else self.dq[r] for r, src in part], stream=stream)
-                written.add(t)
-        for s, rs in self.rels_from.items():
-            for i in range(0, len(rs), _MAX_BATCH):
-                part = rs[i:i + _MAX_BATCH]
-                hb.heta_project_wgrad_batch(g, [self.tables[s]] * len(part), [self.dZ[r] for r in part],
-                                            [self.dW[r] for r in part], gout_two_terms=self.two_terms, stream=stream)
-                for r in part:
-                    hb.heta_attn_fold_bwd(self.W[r], self.a[r], self.dwa[r], dW=self.dW[r], beta=1.0, da=self.da[r],
-                                          stream=stream)
-                hb.heta_project_sum([self.dZ[r] for r in part], [self.W[r] for r in part], self.dH0[s], trans_w=True,
-                                    beta=1.0 if s in written else 0.0, stream=stream, graph=self.g)
-                written.add(s)
+        for turn, parts in enumerate(_turns(self._score_sets, _MAX_SETS)):
+            hb.heta_attn_score_bwd_tables(g, [(self.tables[t], [self.wa[r] if src else self.q[r] for r, src in part],
+                                               [self.d_el[r] if src else self.d_er[r] for r, src in part], self.dH0[t],
+                                               0.0 if turn == 0 else 1.0, [self.dwa[r] if src else self.dq[r] for r, src in part])
+                                              for t, part in parts], stream=stream)
+        hb.heta_project_wgrad_multi(g, [(g.ntypes[s][0], [self.tables[s]] * len(part), [self.dZ[r] for r in part], [self.dW[r] for r in part])
+                                        for s, part in _parts(self.rels_from, _MAX_BATCH)], gout_two_terms=self.two_terms, stream=stream)
+        hb.heta_attn_fold_bwd_multi([(self.W[r], self.a[r], self.dwa[r], self.dW[r], self.da[r]) for r in self.rels], beta=1.0, stream=stream)
+        for parts in _turns(self.rels_from, _MAX_BATCH):
+            hb.heta_project_multi(g, [(g.ntypes[s][0], [self.dZ[r] for r in part], [self.W[r] for r in part], self.dH0[s], hb.HETA_ACT_NONE, 1.0)
+                                      for s, part in parts], trans_w=True, sum=True, stream=stream)
         return self.dW, self.da, self.dq, self.dH0

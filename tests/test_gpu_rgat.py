@@ -488,6 +488,74 @@ def test_folded_score_vector_is_summed_in_order(d_in, heads, F, storage):
     assert torch.equal(wa.cpu(), want.float())
 
 
+@pytest.mark.parametrize("heads,pad", [(4, 4), (3, 4), (2, 1)])
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+def test_calls_over_several_types_equal_their_single_calls(heads, pad, storage):
+    """Workgroups laid end to end: rows at the edges of a workgroup's share and of a launch's number of types, 1 to 8 sets,
+    tables of every kernel (and of none); every output has the bits of the call of its own."""
+    g = rng.stream("tests", f"types{heads}x{pad}{storage}")
+    rows = [1, 129, 4097, 31, 0, 700, 64, 257, 2, 65]
+    cols = [128, 64, 32, 100, 128, 30, 128, 60, 768, 16]
+    sets = [7, 1, 3, 2, 2, 1, 5, 8, 1, 4]
+    graph = heta.heta_graph_create([(n, 4, 0) for n in rows], [(t, t, np.zeros(n + 1, dtype=np.int64), np.zeros(0, dtype=np.int32))
+                                                               for t, n in enumerate(rows)])
+    rand = lambda *shape: g.standard_normal(shape).astype(np.float32)  # noqa: E731
+    new = lambda *shape: torch.full(shape, 7.0, dtype=torch.float32, device="cuda")  # noqa: E731
+    mats = lambda n, d: dev_table(rand(n, d), "f32", pad)  # noqa: E731
+    x = [dev_table(rng.round_to_bf16(rand(n, d)), storage, 2 * pad if storage == "bf16" and pad > 1 else pad) for n, d in zip(rows, cols)]
+    vecs = [[up(rand(heads, d)) for _ in range(k)] for d, k in zip(cols, sets)]
+    scores = [[[new(n, heads) for _ in range(k)] for n, k in zip(rows, sets)] for _ in range(2)]
+    heta.heta_attn_score_tables(list(zip(x, vecs, scores[0])))
+    for t in range(len(rows)):
+        heta.heta_attn_score_multi(x[t], vecs[t], scores[1][t])
+    dx0 = [rand(n, d) for n, d in zip(rows, cols)]
+    dx = [[dev_table(a, "f32", pad) for a in dx0] for _ in range(2)]
+    dvecs = [[[new(heads, d) for _ in range(k)] for d, k in zip(cols, sets)] for _ in range(2)]
+    betas = [float(t % 2) for t in range(len(rows))]
+    heta.heta_attn_score_bwd_tables(graph, [(x[t], vecs[t], scores[0][t], dx[0][t], betas[t], dvecs[0][t]) for t in range(len(rows))])
+    for t in range(len(rows)):
+        heta.heta_attn_score_bwd_multi(graph, x[t], vecs[t], scores[0][t], dx=dx[1][t], beta=betas[t], dvecs=dvecs[1][t])
+
+    F, items = 20, ([], [])
+    for t in range(30):  # more than one launch takes
+        W = dev_table(rng.round_to_bf16(rand(1 + 7 * t, heads * F)), storage, 8 if storage == "bf16" else 4)
+        a, dwa, dW0 = up(rand(heads, F)), up(rand(heads, W.shape[0])), rand(*W.shape)
+        for out in items:
+            out.append((W, a, new(heads, W.shape[0]), dwa, up(dW0), new(heads, F)))
+    heta.heta_attn_fold_multi([it[:3] for it in items[0]])
+    heta.heta_attn_fold_bwd_multi([(W, a, dwa, dW, da) for W, a, _, dwa, dW, da in items[0]], beta=1.0)
+    for W, a, wa, dwa, dW, da in items[1]:
+        heta.heta_attn_fold(W, a, wa)
+        heta.heta_attn_fold_bwd(W, a, dwa, dW=dW, beta=1.0, da=da)
+
+    d = 12 * heads
+    parts = [[mats(n, d) for _ in range(k)] for n, k in zip(rows, sets)]
+    live = [t for t, n in enumerate(rows) if n]
+    sums = [[new(n, d) for n in rows] for _ in range(2)]
+    heta.heta_cross_rel_reduce_multi(graph, [(t, parts[t], sums[0][t]) for t in live], heta.HETA_ACT_RELU)
+    for t in live:
+        heta.heta_cross_rel_reduce(graph, t, parts[t], sums[1][t], heta.HETA_ACT_RELU)
+    cols_of = lambda t, w: [up(rand(rows[t], w)) for _ in range(2)]  # noqa: E731
+    ins = [(t, [t, t], mats(rows[t], d), mats(rows[t], d), [mats(rows[t], d) for _ in range(2)], [mats(rows[t], d) for _ in range(2)],
+            *[cols_of(t, heads) for _ in range(4)]) for t in live]
+    dst = [[(new(rows[t], d), [new(rows[t], heads) for _ in range(2)], [new(rows[t], 4 * heads) for _ in range(2)]) for t in live] for _ in range(2)]
+    heta.heta_attn_bwd_dst_multi(graph, [(t, rs, h, go, gi, *rest, d_er, pack) for (t, rs, h, go, *rest), (gi, d_er, pack) in zip(ins, dst[0])], 0.2,
+                                 heta.HETA_ACT_RELU)
+    for (t, rs, h, go, *rest), (gi, d_er, pack) in zip(ins, dst[1]):
+        heta.heta_attn_bwd_dst(graph, t, rs, 0.2, heta.HETA_ACT_RELU, h, go, gi, *rest, d_er, pack)
+
+    def flat(v):
+        return [v] if isinstance(v, torch.Tensor) else [y for w in v for y in flat(w)]
+
+    for one, two in [scores, dx, dvecs, items, sums, dst]:
+        for p, q in zip(flat(one), flat(two)):
+            assert torch.equal(p, q)
+    with pytest.raises(heta.HetaError, match="overlap"):
+        heta.heta_cross_rel_reduce_multi(graph, [(0, parts[0], sums[0][0]), (0, parts[0], sums[0][0])])
+    with pytest.raises(heta.HetaError, match="overlap"):
+        heta.heta_attn_score_bwd_tables(graph, [(x[0], vecs[0], scores[0][0], dx[0][0], 0.0, dvecs[0][0]), (x[0], vecs[0], scores[0][0], dx[0][0], 0.0, dvecs[1][0])])
+
+
 def test_attention_argument_checks():
     graph = heta.heta_graph_create([(4, 4, 0)], [(0, 0, np.array([0, 1, 2, 2, 2], dtype=np.int64), np.array([1, 0], dtype=np.int32))])
     z = torch.zeros((4, 12), device="cuda")
