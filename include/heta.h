@@ -256,8 +256,8 @@ heta_status heta_rel_project_wgrad(heta_graph *g, int32_t rel, const void *in, h
  *   heta_cross_rel_project_wgrad.
  * Pointer and size arrays are HOST arrays of n entries; shapes and dtypes as in heta_project.
  * g (heta_project_batch, heta_project_sum): optional (NULL allowed) handle whose packing buffer the call may use
- *   to rewrite the weights into the form its kernel reads fastest (fp32 weights as three bf16 terms), on the
- *   same terms as heta_cross_rel_project; the result does not depend on it beyond rounding order. */
+ *   to rewrite the weights into the form its kernel reads fastest (fp32 weights as three bf16 terms, bf16
+ *   weights as [k / 8][column][8 k-values]), on the same terms as heta_cross_rel_project; the result does not depend on it beyond rounding order. */
 heta_status heta_project_batch(heta_graph *g, int64_t n_rows, int32_t n, const void *const *ins, heta_dtype in_dt, const int64_t *ld_in,
                                const int32_t *d_in, const void *const *Ws, heta_dtype w_dt, const int64_t *ld_w,
                                int32_t d_out, int32_t transW, void *const *outs, heta_dtype out_dt,
@@ -295,7 +295,7 @@ heta_status heta_project_wgrad_multi(heta_graph *g, int32_t n, const int32_t *fi
  * ins, Ws, ld_in, d_in, ld_w: HOST arrays of n (1..8) entries; ins[p] device [n_rows, ld_in[p]] of
  * in_dt; Ws[p] device [d_in[p], ld_w[p] >= d_out] of w_dt; out device fp32 [n_rows, ld_out].
  * On a subset of a type's relations with beta = 0 it yields the partial aggregation of that subset.
- * With bf16 inputs and weights the call first rewrites the weights k-contiguous into a buffer of the
+ * With bf16 weights the call first rewrites them as [k / 8][column][8 k-values] into a buffer of the
  * handle (grown on demand: the first call for a larger shape synchronises); with fp32 inputs and weights
  * and enough work for full-size tiles it rewrites the weights there as the three bf16 terms the product is
  * fed with (so does heta_cross_rel_project_bwd).  Calls on one handle that do so must be stream-ordered,

@@ -1201,7 +1201,7 @@ struct ScoreMulti {
 // Several tables in one launch, their workgroups end to end (by itself a table of a few thousand rows takes the 4 to 5 us
 // that any launch takes, its input gradient 10: the vectors are brought into LDS first).  With the weights' folds, the
 // destination side and the sums over relations laid end to end as well, 69 launches of an attention layer of 64 columns, 4
-// node types and 7 relations (2.1 M edges) become 37: forward and backward 1,206 -> 988 us; 21 M edges of 256 columns, where
+// node types and 7 relations (2.1 M edges) become 26: forward and backward 1,206 -> 988 us; 21 M edges of 256 columns, where
 // the small launches are 1 % of the time, 21,355 -> 21,190.
 constexpr int kMultiTables = 8;
 struct ScoreTable {

@@ -387,6 +387,43 @@ template <int BN, int NW> struct Split3Loader {
     }
 };
 
+// The same for a bf16 operand packed as octets (pack_octets_kernel), [k / 8][column][8 k-values], BK / 8 octets a stage.
+// What a load instruction costs is the cache lines that it touches: a k-contiguous matrix gives it 64-byte pieces of 16 rows
+// (32 bytes of 32 where a stage has 16 k-values), this form 1 KB in one piece.  Products of 128 x 256 tiles: six of 500,000 x
+// 300 x 256 sharing their input 1,027 -> 828 us, three of 700,000 x 128 x 256 283 -> 262; input gradients: 300,000 x 256 x
+// 512 280 -> 213, the sum of six 500,000 x 256 x 300 (256 x 320 tiles) 970 -> 931, and 839 with whole lines of A as well.
+template <int BN, int NW, int BK> struct OctetLoader {
+    static constexpr int SLOTS = BK / 8 * (BN / 64);
+    static constexpr int NI = (SLOTS + NW - 1) / NW;
+    static constexpr int STAGE_BYTES = SLOTS * 1024;
+    const char *tile;    // uniform: the chunk of the next tile's first octet, column n0
+    uint32_t off;        // per lane
+    int64_t oct;         // uniform: bytes from octet to octet
+    int last;            // uniform: the last block of 64 columns from n0 on (columns past it are not stored)
+    __device__ __forceinline__ void init(const void *b, int n_pad, int64_t n0, int64_t k0, int lane)
+    {
+        oct = static_cast<int64_t>(n_pad) * 16;
+        tile = static_cast<const char *>(b) + (k0 / 8) * oct + n0 * 16;
+        off = static_cast<uint32_t>(lane) * 16u;
+        last = static_cast<int>((n_pad - n0) / 64) - 1;
+    }
+    __device__ __forceinline__ void issue(uint32_t lds, int wave)
+    {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int slot = (i * NW + wave) % SLOTS; // surplus slots repeat earlier ones (same bytes, same place)
+            const int o = slot / (BN / 64), hn = slot % (BN / 64);
+            load_chunk_to_lds(tile + o * oct + min(hn, last) * 1024, off, lds + slot * 1024);
+        }
+        tile += BK / 8 * oct;
+    }
+    // octet o of column c, of the stage at `stage`
+    __device__ __forceinline__ static uint4 frag(const char *stage, int o, int c)
+    {
+        return *reinterpret_cast<const uint4 *>(stage + (o * BN + c) * 16);
+    }
+};
+
 // One k-step (16 k-values, kv of them valid) of a wavefront's 2 x 2 accumulators with B already in three
 // terms: only A's two fragments are split (88 vector instructions), and the order is pinned with scheduling
 // barriers so that the splitting runs between the twelve MFMAs that need A's leading term alone; the twelve
@@ -604,9 +641,9 @@ __device__ __forceinline__ void store_tile(const GemmParams &p, const GemmCall &
         }
 }
 
-template <bool W3, bool B_DIRECT, typename DB, typename SB_T, typename Staged, typename CT> constexpr int b_stage_bytes()
+template <bool PACKED, bool B_DIRECT, typename DB, typename SB_T, typename Staged, typename CT> constexpr int b_stage_bytes()
 {
-    if constexpr (W3) return DB::STAGE_BYTES;
+    if constexpr (PACKED) return DB::STAGE_BYTES;
     else if constexpr (B_DIRECT) return DB::STAGE_ELEMS * (int)sizeof(SB_T);
     else return Staged::elems * (int)sizeof(CT);
 }
@@ -627,24 +664,25 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
     // when fragments are read); a staged operand lies there in the compute type
     using DA = std::conditional_t<A_DIRECT, DirectLoader<SA_T, A_RC && A_DIRECT, BM, BK, NW>, NoLoader>;
     // X3: fp32 operands as three bf16 terms each - 1: both split when their fragments are read, 2: B comes pre-split, 3: both
-    // split, the products added in the order of 2 (bitwise the same sums)
+    // split, the products added in the order of 2 (bitwise the same sums).  4: a bf16 B packed as octets
     constexpr bool X3_AS_PACKED = X3 == 3;
     // A is flipped where its product's sign alternates (packed weights come in both signs instead): see flip_signs
-    constexpr bool W3 = X3 == 2, X3_FLIP = X3 == 1 ? A_RC && B_RC : X3 == 3 && !B_RC;
-    using DB = std::conditional_t<W3, Split3Loader<BN, NW>, std::conditional_t<B_DIRECT, DirectLoader<SB_T, B_RC && B_DIRECT, BN, BK, NW>, NoLoader>>;
+    constexpr bool W3 = X3 == 2, W1 = X3 == 4, X3_FLIP = X3 == 1 ? A_RC && B_RC : X3 == 3 && !B_RC;
+    using DB = std::conditional_t<W3, Split3Loader<BN, NW>, std::conditional_t<W1, OctetLoader<BN, NW, BK>, std::conditional_t<B_DIRECT, DirectLoader<SB_T, B_RC && B_DIRECT, BN, BK, NW>, NoLoader>>>;
     using SA = std::conditional_t<A_DIRECT, NoLoader, TileLoader<SA_T, CT, A_RC, BM, NT, true, BK>>;
     using SB = std::conditional_t<B_DIRECT, NoLoader, TileLoader<SB_T, CT, B_RC, BN, NT, true, BK>>;
     constexpr bool ANY_STAGED = !A_DIRECT || !B_DIRECT;
     // bytes of one LDS stage / buffer of each operand
     constexpr int A_STRIDE = A_DIRECT ? DA::STAGE_ELEMS * (int)sizeof(SA_T) : LdsTile<CT, A_RC, BM, BK>::elems * (int)sizeof(CT);
-    constexpr int B_STRIDE = b_stage_bytes<W3, B_DIRECT, DB, SB_T, LdsTile<CT, B_RC, BN, BK>, CT>();
+    constexpr int B_STRIDE = b_stage_bytes<W3 || W1, B_DIRECT, DB, SB_T, LdsTile<CT, B_RC, BN, BK>, CT>();
     constexpr int A_BYTES = (A_DIRECT ? ST : 2) * A_STRIDE, B_BYTES = (B_DIRECT ? ST : 2) * B_STRIDE;
     constexpr int LD_PER_TILE = (A_DIRECT ? DA::NI : 0) + (B_DIRECT ? DB::NI : 0);
     static_assert(A_DIRECT || B_DIRECT, "at least one operand is loaded directly");
     static_assert(!B_SPLIT || (B_DIRECT && B_RC && sizeof(SB_T) == 4 && sizeof(CT) == 2), "two-term feeding: direct r-contiguous fp32 B");
     static_assert(ST >= 2 && (ST - 2) * LD_PER_TILE < 64, "vmcnt range");
-    static_assert(!X3 || (A_DIRECT && B_DIRECT && sizeof(SA_T) == 4 && sizeof(SB_T) == 4 && sizeof(CT) == 2 && !B_SPLIT),
+    static_assert(!X3 || W1 || (A_DIRECT && B_DIRECT && sizeof(SA_T) == 4 && sizeof(SB_T) == 4 && sizeof(CT) == 2 && !B_SPLIT),
                   "three-term feeding: both operands direct fp32, bf16 MFMA");
+    static_assert(!W1 || (B_DIRECT && !B_RC && sizeof(SB_T) == 2 && sizeof(CT) == 2), "packed bf16 B");
     static_assert(!W3 || (BK == 16 && MI == 2 && NJ == 2 && !A_RC), "pre-split B: 2 x 2 accumulators, 16 k-values per tile");
     static_assert(A_BYTES % 1024 == 0, "stage addresses stay 1 KB aligned");
     __shared__ __attribute__((aligned(1024))) char ring[A_BYTES + B_BYTES];
@@ -702,6 +740,7 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
         const GemmSeg &g = p.seg[I.s];
         if constexpr (A_DIRECT) da.init(static_cast<const SA_T *>(g.A), g.lda, m0, g.M, I.k, wave, lane);
         if constexpr (W3) db.init(static_cast<const char *>(g.B3) + (negated ? static_cast<int64_t>(g.ko) * g.n_pad * 48 : 0), g.ko, g.n_pad, n0, I.k, lane);
+        else if constexpr (W1) db.init(g.B3, g.n_pad, n0, I.k, lane);
         else if constexpr (B_DIRECT) db.init(static_cast<const SB_T *>(g.B), g.ldb, n0, g.N, I.k, wave, lane);
     };
     auto init_staged = [&]() {
@@ -725,7 +764,7 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
         } else {
             const GemmSeg &g = p.seg[I.s];
             if constexpr (A_DIRECT) da.issue_ragged(a_lds + st * A_STRIDE, wave, lane, kv, g.lda - I.k);
-            if constexpr (W3) db.issue(b_lds + st * B_STRIDE, wave);
+            if constexpr (W3 || W1) db.issue(b_lds + st * B_STRIDE, wave);
             else if constexpr (B_DIRECT) db.issue_ragged(b_lds + st * B_STRIDE, wave, lane, kv, g.ldb - I.k);
         }
         ++ahead;
@@ -810,7 +849,7 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
             } else if constexpr (W3) {
                 // fp32 A split as its fragments are read, B read as the three terms it was packed into
                 x3_step_2x2_presplit<A_RC, BM, BN, BK>(reinterpret_cast<const float *>(At), Bt, wm + l32, wn + l32, half, kv, acc);
-            } else if constexpr (X3 != 0) {
+            } else if constexpr (X3 != 0 && !W1) {
                 // fp32 operands, every product as six bf16 terms (split3_pair)
 #pragma unroll
                 for (int kk = 0; kk < BK; kk += 16) {
@@ -861,7 +900,8 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
                     }
 #pragma unroll
                     for (int jj = 0; jj < NJ; ++jj) {
-                        if constexpr (B_DIRECT && B_RC && sizeof(SB_T) == 4)
+                        if constexpr (W1) b[jj].u = DB::frag(Bt, kk / 8 + half, wn + jj * 32 + l32);
+                        else if constexpr (B_DIRECT && B_RC && sizeof(SB_T) == 4)
                             b[jj].u = dfrag_bf16_rc_from_f32<BN, B_SPLIT>(reinterpret_cast<const float *>(Bt), wn + jj * 32 + l32, kk, half, &bl[jj].u);
                         else if constexpr (B_DIRECT && B_RC)
                             b[jj].u = dfrag_bf16_rc<BN>(reinterpret_cast<const bf16_t *>(Bt), wn + jj * 32 + l32, kk, half);
@@ -953,10 +993,9 @@ static heta_status launch_direct(GemmParams &p, hipStream_t st, const char *name
 // test switch: fp32 products on the fp32 MFMA (32x32x2) instead of as six bf16 terms
 bool g_f32_native = false;
 
-// fewer than a hundred 128 x 128 tiles
-static bool gemm_direct_small(const GemmParams &p)
+// 128 x 128 tiles of a launch
+static int64_t tiles128(const GemmParams &p)
 {
-    if (p.partial) return false;
     int64_t tiles = 0;
     const int n_call = std::max(1, p.n_call);
     for (int c = 0; c < n_call; ++c) {
@@ -968,7 +1007,19 @@ static bool gemm_direct_small(const GemmParams &p)
         }
         tiles += mt * nt * (p.batch ? n_seg : 1);
     }
-    return tiles <= 96;
+    return tiles;
+}
+
+// fewer than a hundred of them
+static bool gemm_direct_small(const GemmParams &p) { return !p.partial && tiles128(p) <= 96; }
+
+// whether several products of a call read the same A
+static bool a_shared(const GemmParams &p)
+{
+    for (int c = 0; p.batch && c < p.n_call; ++c)
+        for (int s = p.call[c].first + 1; s < p.call[c].first + p.call[c].n_seg; ++s)
+            if (p.seg[s].A == p.seg[s - 1].A) return true;
+    return false;
 }
 
 // fp32 products (forward, input gradient) of too little work for packed weights: 64 x 64 tiles that split both operands.
@@ -1090,6 +1141,10 @@ heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, 
         if (n_max > 128)
             return p.split_b ? launch_direct<bf16_t, bf16_t, true, true, float, true, true, 4, 16, 4, 4, true>(p, st, name, bytes, flops)
                              : launch_direct<bf16_t, bf16_t, true, true, float, true, true, 4, 16, 4, 4, false>(p, st, name, bytes, flops);
+        // at most 64 output columns: 128 x 64 tiles, five workgroups per CU (seven of 7,000 .. 110,000 x 128 x 64 56 -> 47 us)
+        if (n_max <= 64)
+            return p.split_b ? launch_direct<bf16_t, bf16_t, true, true, float, true, true, 2, 16, 3, 5, true, 2, 1, 2>(p, st, name, bytes, flops)
+                             : launch_direct<bf16_t, bf16_t, true, true, float, true, true, 2, 16, 3, 5, false, 2, 1, 2>(p, st, name, bytes, flops);
         return p.split_b ? launch_direct<bf16_t, bf16_t, true, true, float, true, true, 2, 16, 4, 3, true>(p, st, name, bytes, flops)
                          : launch_direct<bf16_t, bf16_t, true, true, float, true, true, 2, 16, 4, 3, false>(p, st, name, bytes, flops);
     }
@@ -1114,6 +1169,7 @@ heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, 
     // every tile is a serial chain of MFMAs on one CU while most CUs idle.  64 x 64 tiles (four wavefronts of one
     // accumulator each) cut the chain to a quarter and put four times as many CUs to work.
     const bool small = gemm_direct_small(p), unpacked = f32_product_unpacked(p);
+    const bool octets = b_dt == HETA_BF16 && p.seg[0].B3; // all segments of a launch are packed or none
     *handled = true;
     if (a_dt == HETA_F32 && b_dt == HETA_F32 && !g_f32_native && !a_rc && !unpacked && !p.partial) {
         // B already packed as three bf16 terms by the caller (the weights of a forward or input-gradient product):
@@ -1169,7 +1225,8 @@ heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, 
         if (a_dt == HETA_BF16 && b_dt == HETA_BF16 && !a_rc && b_rc)
             return launch_direct<bf16_t, bf16_t, false, true, bf16_t, true, true, 2, 32, 3, 4, false, 1, 1, 2>(p, st, name, bytes, flops);
         if (a_dt == HETA_F32 && b_dt == HETA_BF16 && !a_rc && !b_rc)
-            return launch_direct<bf16_t, float, false, true, bf16_t, false, true, 2, 32, 3, 4, false, 1, 1, 2>(p, st, name, bytes, flops);
+            return octets ? launch_direct<bf16_t, float, false, true, bf16_t, false, true, 2, 32, 3, 4, false, 1, 1, 2, 4>(p, st, name, bytes, flops)
+                          : launch_direct<bf16_t, float, false, true, bf16_t, false, true, 2, 32, 3, 4, false, 1, 1, 2>(p, st, name, bytes, flops);
     }
     if (a_dt == HETA_F32 && b_dt == HETA_F32) {
 #define HETA_D32(ARC, BRC)                                                                                          \
@@ -1190,19 +1247,40 @@ heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, 
             // 320 output columns in one tile (wavefronts of MI x 5 accumulators): the fp32 rows of A are read once.  256 rows
             // per tile (one workgroup per CU) where the launch still fills the chip several times: W_r^T, re-read by every
             // workgroup, is then loaded once per 256 rows (1.25 -> 0.92 ms on 6 x (500 k x 256)(256 x 300)); else 128 rows.
+            // With packed weights three stages of 32 k-values fit, and a row's piece of a stage is a whole cache line.
             int64_t m_all = 0;
             for (int s = 0; s < p.n_seg; ++s) m_all = std::max(m_all, p.seg[s].M);
             if (m_all >= 256 * 1024)
-                return launch_direct<bf16_t, float, false, true, bf16_t, false, true, 2, 16, 4, 1, false, 2, 5, 4>(p, st, name, bytes, flops);
-            return launch_direct<bf16_t, float, false, true, bf16_t, false, true, 2, 16, 4, 2, false, 1, 5, 4>(p, st, name, bytes, flops);
+                return octets ? launch_direct<bf16_t, float, false, true, bf16_t, false, true, 2, 32, 3, 1, false, 2, 5, 4, 4>(p, st, name, bytes, flops)
+                              : launch_direct<bf16_t, float, false, true, bf16_t, false, true, 2, 16, 4, 1, false, 2, 5, 4>(p, st, name, bytes, flops);
+            return octets ? launch_direct<bf16_t, float, false, true, bf16_t, false, true, 2, 16, 4, 2, false, 1, 5, 4, 4>(p, st, name, bytes, flops)
+                          : launch_direct<bf16_t, float, false, true, bf16_t, false, true, 2, 16, 4, 2, false, 1, 5, 4>(p, st, name, bytes, flops);
         }
+        // at most 64 output columns: 128 x 64 tiles, four workgroups per CU (four of 500,000 x 256 x 7 .. 64 354 -> 209 us; with
+        // 256 x 64 tiles 256)
+        if (octets && n_max <= 64)
+            return launch_direct<bf16_t, float, false, true, bf16_t, false, true, 1, 32, 2, 4, false, 1, 2, 4, 4>(p, st, name, bytes, flops);
+        // Two stages and three workgroups per CU where A's rows are read by several workgroups, or by few: three of 700,000 x
+        // 256 x 128 sharing their input 328 -> 306 us, 1,464 tiles 79 -> 64.  One product of many tiles reads at the
+        // rate of HBM and keeps the third stage: 1.1 M x 256 x 128 255 us, with two 268.
+        if (octets && !wide && (a_shared(p) || tiles128(p) < 4096))
+            return launch_direct<bf16_t, float, false, true, bf16_t, false, true, 2, 32, 2, 3, false, 2, 2, 2, 4>(p, st, name, bytes, flops);
+        if (octets)
+            return wide ? launch_direct<bf16_t, float, false, true, bf16_t, false, true, 4, 16, 4, 4, false, 2, 2, 2, 4>(p, st, name, bytes, flops)
+                        : launch_direct<bf16_t, float, false, true, bf16_t, false, true, 2, 32, 3, 2, false, 2, 2, 2, 4>(p, st, name, bytes, flops);
         return wide ? launch_direct<bf16_t, float, false, true, bf16_t, false, true, 4, 16, 4, 4>(p, st, name, bytes, flops)
                     : launch_direct<bf16_t, float, false, true, bf16_t, false, true, 2, 32, 3, 2>(p, st, name, bytes, flops);
     }
-    if (a_dt == HETA_BF16 && b_dt == HETA_BF16 && !a_rc && !b_rc) { // both k-contiguous bf16 (forward with a packed W_r^T)
+    if (a_dt == HETA_BF16 && b_dt == HETA_BF16 && !a_rc && !b_rc && octets) { // forward with packed weights
+        if (small) return launch_direct<bf16_t, bf16_t, false, true, bf16_t, false, true, 2, 32, 3, 4, false, 1, 1, 2, 4>(p, st, name, bytes, flops);
+        // at most 64 output columns: 128 x 64 tiles, five workgroups per CU (seven of 7,000 .. 110,000 x 128 x 64 43 -> 31 us)
+        if (n_max <= 64) return launch_direct<bf16_t, bf16_t, false, true, bf16_t, false, true, 1, 32, 2, 5, false, 1, 2, 4, 4>(p, st, name, bytes, flops);
+        return wide ? launch_direct<bf16_t, bf16_t, false, true, bf16_t, false, true, 4, 32, 3, 4, false, 2, 2, 2, 4>(p, st, name, bytes, flops)
+                    : launch_direct<bf16_t, bf16_t, false, true, bf16_t, false, true, 2, 32, 3, 3, false, 2, 2, 2, 4>(p, st, name, bytes, flops);
+    }
+    if (a_dt == HETA_BF16 && b_dt == HETA_BF16 && !a_rc && !b_rc) // both k-contiguous bf16
         return wide ? launch_direct<bf16_t, bf16_t, false, true, bf16_t, false, true, 4, 32, 3, 4>(p, st, name, bytes, flops)
                     : launch_direct<bf16_t, bf16_t, false, true, bf16_t, false, true, 2, 32, 3, 3>(p, st, name, bytes, flops);
-    }
     *handled = false;
     return HETA_OK;
 }

@@ -247,31 +247,42 @@ __global__ void __launch_bounds__(NW == 1 ? 256 : 64 * NW) splitk_reduce_kernel(
     *o = (beta != 0.f) ? beta * *o + a : a;
 }
 
-// out[n][k] = W[k][n]: bf16 weight matrices laid out k-contiguous, the form the direct-to-LDS
-// pipeline can copy into LDS as is (an n-contiguous bf16 operand would need pair interleaving).
-// blockIdx.z picks the matrix: the weights of every segment of a product in one launch.
-struct PackSegs {
+// bf16 weight matrices as octets, out[k / 8][n][8 k-values] of B(k, n) = W[k*ldw + n] (TRANS: W[n*ldw + k]), zero beyond K
+// and N: the form that the direct-to-LDS pipeline copies 1 KB at a time.  blockIdx.y picks the matrix: the weights of
+// every segment of a product in one launch.
+struct OctetSegs {
     const bf16_t *W[kMaxLaunchSeg];
-    bf16_t *out[kMaxLaunchSeg];
+    uint4 *out[kMaxLaunchSeg];
     int64_t ldw[kMaxLaunchSeg];
-    int K[kMaxLaunchSeg], N[kMaxLaunchSeg], ld_out[kMaxLaunchSeg];
+    int K[kMaxLaunchSeg], N[kMaxLaunchSeg], ko[kMaxLaunchSeg], n_pad[kMaxLaunchSeg];
+    int vec; // rows of every W 16-byte aligned
 };
-__global__ void __launch_bounds__(256) pack_weight_kernel(PackSegs q)
+template <bool TRANS> __global__ void __launch_bounds__(256) pack_octets_kernel(OctetSegs q)
 {
-    __shared__ bf16_t tile[32][33];
-    const int s = blockIdx.z;
+    const int s = blockIdx.y;
     const bf16_t *W = q.W[s];
-    bf16_t *out = q.out[s];
     const int64_t ldw = q.ldw[s];
-    const int K = q.K[s], N = q.N[s], ld_out = q.ld_out[s];
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5; // 32 x 8
-    const int k0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
-    if (k0 >= ld_out || n0 >= N) return; // uniform per workgroup: a smaller matrix of the launch
-    for (int r = ty; r < 32; r += 8)
-        tile[r][tx] = (k0 + r < K && n0 + tx < N) ? W[static_cast<int64_t>(k0 + r) * ldw + n0 + tx] : bf16_t(0);
-    __syncthreads();
-    for (int r = ty; r < 32; r += 8)
-        if (n0 + r < N && k0 + tx < ld_out) out[static_cast<int64_t>(n0 + r) * ld_out + k0 + tx] = (k0 + tx < K) ? tile[tx][r] : bf16_t(0);
+    const int K = q.K[s], N = q.N[s], ko = q.ko[s], n_pad = q.n_pad[s];
+    const int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    // neighbouring threads: neighbouring columns, or (TRANS) neighbouring octets of a column, as W lies in memory
+    const int n = static_cast<int>(TRANS ? idx / ko : idx % n_pad), o = static_cast<int>(TRANS ? idx % ko : idx / n_pad);
+    if (o >= ko || n >= n_pad) return;
+    if (TRANS && q.vec && 8 * o + 8 <= K && n < N) {
+        q.out[s][static_cast<int64_t>(o) * n_pad + n] = *reinterpret_cast<const uint4 *>(W + n * ldw + 8 * o);
+        return;
+    }
+    uint32_t w[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        uint32_t x[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int k = o * 8 + 2 * j + e;
+            x[e] = (k < K && n < N) ? (TRANS ? W[n * ldw + k] : W[k * ldw + n]) : 0;
+        }
+        w[j] = x[0] | (x[1] << 16);
+    }
+    q.out[s][static_cast<int64_t>(o) * n_pad + n] = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
 // ---- host side -------------------------------------------------------------------------------------
@@ -417,6 +428,57 @@ static heta_status pack_f32_weights(heta_graph *owner, GemmParams &p, int trans,
     return pack_split3_weights(p, trans, owner->d_pack, st);
 }
 
+// bf16 weights through a graph handle: rewritten once per launch as octets into the handle's packing buffer.  A forward
+// product's lie with the contraction index outermost and are always rewritten; an input gradient's can be copied into LDS as
+// they are, and packing them takes a launch (5 us): from 48 k steps of 64 x 64 x 16 on the product gains more.  In us,
+// unpacked and packed (with the packing): 192 tiles of 128 x 128 over 1,024 k-values (48 k steps) 25.0 and 30.4, 544 over 256
+// (34 k) 27.9 and 31.9; seven relations of 64 columns summed into 128 columns of 187,000 rows (60 k) 79.8 and 69.3; 20,000 x
+// 1,024 x 768 (245 k) 60 and 52, three of 700,000 x 256 x 128 376 and 319.
+static heta_status pack_bf16_weights(heta_graph *owner, GemmParams &p, heta_dtype in_dt, int trans, hipStream_t st)
+{
+    if (!owner || g_force_staged || p.partial) return HETA_OK;
+    const auto octets = [](const GemmSeg &g) { return (g.K + 31) / 32 * 4; }; // whole tiles of 32 k-values
+    const auto columns = [](const GemmSeg &g) { return (g.N + 63) / 64 * 64; };
+    size_t bytes = 0;
+    double steps = 0; // of 64 x 64 x 16
+    for (int s = 0; s < p.n_seg; ++s) {
+        const GemmSeg &g = p.seg[s];
+        const int64_t a_row = g.lda * static_cast<int64_t>(dtype_size(in_dt));
+        if (!aligned16(g.A) || a_row % 16 || a_row * 256 >= (int64_t(1) << 31)) return HETA_OK; // not for the direct pipeline
+        if (g.K >= (int64_t(1) << 30) || g.N >= (int64_t(1) << 30) || octets(g) * columns(g) >= (int64_t(1) << 31)) return HETA_OK;
+        bytes += static_cast<size_t>(octets(g) * columns(g)) * 16;
+        steps += static_cast<double>((g.M + 63) / 64) * static_cast<double>((g.N + 63) / 64) * static_cast<double>((g.K + 15) / 16);
+    }
+    if (trans && steps <= 49152) return HETA_OK;
+    heta_status e = ensure_pack(owner, bytes);
+    if (e != HETA_OK) return e;
+    uint4 *dst = static_cast<uint4 *>(owner->d_pack);
+    OctetSegs q{};
+    q.vec = 1;
+    int64_t chunks = 0;
+    for (int s = 0; s < p.n_seg; ++s) {
+        GemmSeg &g = p.seg[s];
+        q.W[s] = static_cast<const bf16_t *>(g.B);
+        q.vec = q.vec && vec_ok(g.B, g.ldb, HETA_BF16);
+        q.out[s] = dst;
+        q.ldw[s] = g.ldb;
+        q.K[s] = static_cast<int>(g.K);
+        q.N[s] = static_cast<int>(g.N);
+        q.ko[s] = static_cast<int>(octets(g));
+        q.n_pad[s] = static_cast<int>(columns(g));
+        chunks = std::max(chunks, octets(g) * columns(g));
+        g.B = g.B3 = dst;
+        g.ldb = 8; // (not walked by rows)
+        g.n_pad = q.n_pad[s];
+        dst += octets(g) * columns(g);
+    }
+    const dim3 grid((unsigned)((chunks + 255) / 256), p.n_seg);
+    if (trans) hipLaunchKernelGGL(pack_octets_kernel<true>, grid, dim3(256), 0, st, q);
+    else hipLaunchKernelGGL(pack_octets_kernel<false>, grid, dim3(256), 0, st, q);
+    HETA_LAUNCH_CHECK("pack_octets_kernel");
+    return HETA_OK;
+}
+
 // out = beta*out + row_scale * sum_s in_s . (W_s or W_s^T): the checked arguments as launch parameters (n_seg 0: no rows)
 static heta_status project_plan(GemmParams &p, int64_t n_rows, int n_seg, const void *const *ins, heta_dtype in_dt, const int64_t *ld_in,
                                 const int32_t *d_in, const void *const *Ws, heta_dtype w_dt, const int64_t *ld_w, int32_t d_out, int32_t transW,
@@ -475,54 +537,22 @@ static heta_status project_plan(GemmParams &p, int64_t n_rows, int n_seg, const 
     return HETA_OK;
 }
 
-// the planned call, or the calls merged into one plan
-static heta_status project_run(GemmParams &p, heta_dtype in_dt, heta_dtype w_dt, int32_t transW, heta_graph *pack_owner, hipStream_t st)
+// the planned call, or the calls merged into one plan.  pack_bwd: whether transposed bf16 weights may go through the packing
+// buffer too (calls that never used it for them may be overlapped by their callers)
+static heta_status project_run(GemmParams &p, heta_dtype in_dt, heta_dtype w_dt, int32_t transW, heta_graph *pack_owner, hipStream_t st,
+                               bool pack_bwd)
 {
     if (p.n_seg == 0) return HETA_OK;
     if (in_dt == HETA_F32 && w_dt == HETA_F32) {
         heta_status pe = pack_f32_weights(pack_owner, p, transW, st);
         if (pe != HETA_OK) return pe;
     }
-    // B[k][n] = W[k][n] is n-contiguous (r-contiguous in the loader's terms); W^T is k-contiguous
-    if (transW) return dispatch_gemm<false, false>(p, in_dt, w_dt, st);
-    if (pack_owner && !g_force_staged && w_dt == HETA_BF16) {
-        // forward with bf16 weights and a graph handle: the small W_r are first rewritten k-contiguous into the
-        // handle's packing buffer, so that both operands can stream into LDS without a register stage (fp32
-        // inputs, an inner layer's embeddings, are rounded to bf16 when their fragments are read, as the
-        // register-staged kernel rounds them when it stages them)
-        bool ok = true;
-        size_t bytes = 0;
-        for (int s = 0; s < p.n_seg; ++s) {
-            const GemmSeg &g = p.seg[s];
-            ok = ok && aligned16(g.A) && (g.lda * static_cast<int64_t>(dtype_size(in_dt))) % 16 == 0;
-            bytes += static_cast<size_t>(g.N) * ((g.K + 7) / 8 * 8) * 2 + 256;
-        }
-        if (ok) {
-            heta_status pe = ensure_pack(pack_owner, bytes);
-            if (pe != HETA_OK) return pe;
-            char *dst = static_cast<char *>(pack_owner->d_pack);
-            PackSegs q{};
-            int ldp_max = 0, n_max = 0;
-            for (int s = 0; s < p.n_seg; ++s) {
-                GemmSeg &g = p.seg[s];
-                const int ldp = static_cast<int>((g.K + 7) / 8 * 8);
-                q.W[s] = static_cast<const bf16_t *>(g.B);
-                q.out[s] = reinterpret_cast<bf16_t *>(dst);
-                q.ldw[s] = g.ldb;
-                q.K[s] = static_cast<int>(g.K);
-                q.N[s] = static_cast<int>(g.N);
-                q.ld_out[s] = ldp;
-                ldp_max = std::max(ldp_max, ldp);
-                n_max = std::max(n_max, q.N[s]);
-                g.B = dst;
-                g.ldb = ldp;
-                dst += (static_cast<size_t>(g.N) * ldp * 2 + 255) / 256 * 256;
-            }
-            hipLaunchKernelGGL(pack_weight_kernel, dim3((n_max + 31) / 32, (ldp_max + 31) / 32, p.n_seg), dim3(256), 0, st, q);
-            HETA_LAUNCH_CHECK("pack_weight_kernel");
-            return dispatch_gemm<false, false>(p, in_dt, w_dt, st);
-        }
+    if (w_dt == HETA_BF16 && (!transW || pack_bwd)) {
+        heta_status pe = pack_bf16_weights(pack_owner, p, in_dt, transW, st);
+        if (pe != HETA_OK) return pe;
     }
+    // B[k][n] = W[k][n] is n-contiguous (r-contiguous in the loader's terms); W^T is k-contiguous
+    if (transW || (w_dt == HETA_BF16 && p.seg[0].B3)) return dispatch_gemm<false, false>(p, in_dt, w_dt, st);
     return dispatch_gemm<false, true>(p, in_dt, w_dt, st);
 }
 
@@ -530,12 +560,13 @@ static heta_status project_impl(int64_t n_rows, int n_seg, const void *const *in
                                 const int32_t *d_in, const void *const *Ws, heta_dtype w_dt, const int64_t *ld_w,
                                 int32_t d_out, int32_t transW, const float *row_scale, int relu, void *out,
                                 int64_t ld_out, float beta, hipStream_t st, const char *who, heta_graph *pack_owner = nullptr,
-                                heta_dtype out_dt = HETA_F32, void *const *outs = nullptr, const int64_t *ld_outs = nullptr)
+                                heta_dtype out_dt = HETA_F32, void *const *outs = nullptr, const int64_t *ld_outs = nullptr,
+                                bool pack_bwd = true)
 {
     GemmParams p;
     heta_status e = project_plan(p, n_rows, n_seg, ins, in_dt, ld_in, d_in, Ws, w_dt, ld_w, d_out, transW, row_scale, relu, out, ld_out, beta, who,
                                  out_dt, outs, ld_outs);
-    return e == HETA_OK ? project_run(p, in_dt, w_dt, transW, pack_owner, st) : e;
+    return e == HETA_OK ? project_run(p, in_dt, w_dt, transW, pack_owner, st, pack_bwd) : e;
 }
 
 // ---- several calls in one launch -------------------------------------------------------------------------------------
@@ -878,7 +909,7 @@ static heta_status project_multi_impl(heta_graph *g, int32_t n, const int32_t *f
                     join(p, plans[j]);
                     plans[j].n_seg = 0;
                 }
-        heta_status e = project_run(p, in_dt, w_dt, transW, g, st);
+        heta_status e = project_run(p, in_dt, w_dt, transW, g, st, true);
         if (e != HETA_OK) return e;
     }
     return HETA_OK;
@@ -974,7 +1005,7 @@ heta_status heta_rel_project(heta_graph *g, int32_t rel, const void *in, heta_dt
     if (rel < 0 || rel >= (int32_t)g->rels.size())
         return fail(HETA_ERR_INVALID_ARG, "heta_rel_project: relation %d out of range", rel);
     return project_impl(g->rels[rel].n_dst, 1, &in, in_dt, &ld_in, &d_in, &W, w_dt, &ld_w, d_out, transW, row_scale, 0,
-                        out, ld_out, beta, as_stream(hip_stream), "heta_rel_project", g, out_dt);
+                        out, ld_out, beta, as_stream(hip_stream), "heta_rel_project", g, out_dt, nullptr, nullptr, false);
 }
 
 heta_status heta_rel_project_wgrad(heta_graph *g, int32_t rel, const void *in, heta_dtype in_dt,
@@ -1048,7 +1079,7 @@ heta_status heta_cross_rel_project_bwd(const heta_graph *g, int32_t dst_type, in
     std::fill(ld_in, ld_in + n, ld_go);
     if ((e = bwd_plan(p, g->ntypes[dst_type].num_nodes, n, ins, ld_in, d_out, Ws, w_dt, ld_w, d_in, dM, dm_dt, ld_dm, who)) != HETA_OK) return e;
     // the handle's packing buffer is scratch memory, not part of the graph it describes
-    return project_run(p, HETA_F32, w_dt, 1, const_cast<heta_graph *>(g), as_stream(hip_stream));
+    return project_run(p, HETA_F32, w_dt, 1, const_cast<heta_graph *>(g), as_stream(hip_stream), false);
 }
 
 heta_status heta_cross_rel_project_wgrad(heta_graph *g, int32_t dst_type, int32_t n, const void *const *ins,

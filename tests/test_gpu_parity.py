@@ -1600,6 +1600,31 @@ def test_project_multi_against_fp64(rows, storage):
     hg.destroy()
 
 
+@pytest.mark.parametrize("n,k,d_out,n_seg", [(70_001, 1000, 33, 1), (70_001, 520, 100, 1), (130_000, 264, 65, 2), (530_000, 104, 72, 1), (70_001, 520, 200, 1),
+                                             (270_000, 72, 300, 1), (70_001, 272, 257, 3), (70_001, 200, 321, 2), (1000, 40, 100, 2)])
+def test_packed_bf16_weights_against_fp64(n, k, d_out, n_seg):
+    """bf16 weights rewritten as octets: every tile that takes them, ragged rows, columns and k-values, forward and (from 48 k
+    steps of 64 x 64 x 16 on) transposed, sums and products sharing their input.  Operands exact in bf16: what remains is the
+    fp32 accumulation."""
+    g = torch.Generator(device="cuda").manual_seed(n + k)
+    hg = heta.heta_graph_create([(1, 1, 0)], [(0, 0, np.zeros(2, dtype=np.int64), np.zeros(0, dtype=np.int32))])
+    rand = lambda *shape: torch.randn(shape, generator=g, device="cuda").to(torch.bfloat16)  # noqa: E731
+    for trans in (False, True):
+        Ws = [rand(d_out, k) if trans else rand(k, d_out if n_seg == 1 else (d_out + 7) // 8 * 8)[:, :d_out] for _ in range(n_seg)]
+        wide = [(w.t() if trans else w).double() for w in Ws]
+        xs = [rand(n, k) for _ in range(n_seg)]
+        if trans:
+            xs = [x.float() for x in xs]
+        out = torch.full((n, d_out), 2.0, device="cuda")
+        heta.heta_project_sum(xs, Ws, out, trans_w=trans, beta=1.0, graph=hg)
+        _close(out, 2.0 + sum(x.double() @ w for x, w in zip(xs, wide)), "f32")
+        outs = [torch.full((n, d_out), float("nan"), device="cuda") for _ in Ws]
+        heta.heta_project_batch([xs[0]] * n_seg, Ws, outs, trans_w=trans, graph=hg)
+        for o, w in zip(outs, wide):
+            _close(o, xs[0].double() @ w, "f32")
+    hg.destroy()
+
+
 @pytest.mark.parametrize("storage", ["f32", "bf16"])
 @pytest.mark.parametrize("rows", [[1, 0, 31, 33], [127, 1000, 4097, 20_000], [200_000, 129, 64, 5000]])
 def test_wgrad_multi_against_fp64(rows, storage):
