@@ -467,6 +467,32 @@ __device__ __forceinline__ void x3_step_2x2_presplit(const float *At, const char
     X3_MM(1, 0, 0, 0); X3_MM(1, 0, 0, 1); X3_MM(1, 1, 0, 0); X3_MM(1, 1, 0, 1);
     X3_MM(1, 0, 1, 0); X3_MM(1, 0, 1, 1); X3_MM(1, 1, 1, 0); X3_MM(1, 1, 1, 1);
     X3_MM(2, 0, 0, 0); X3_MM(2, 0, 0, 1); X3_MM(2, 1, 0, 0); X3_MM(2, 1, 0, 1);
+}
+// the same for 1 x 2 accumulators
+template <bool A_RC, int BM, int BN, int BK>
+__device__ __forceinline__ void x3_step_1x2_presplit(const float *At, const char *Bt, int ra, int cb, int half, int kv, floatx16 (&acc)[1][2])
+{
+    X3Frag a[1];
+    dfrag_load8<A_RC, BM, BK>(At, ra, 0, half, a[0].x);
+    if (kv < BK) { // uniform: the ragged last tile of a segment; k-values from kv on count as zero
+#pragma unroll
+        for (int j = 0; j < 8; ++j) a[0].x[j] = 8 * half + j < kv ? a[0].x[j] : 0.f;
+    }
+    union BF { uint4 u; bf16x8 v; } b[2][3];
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) b[j][t].u = Split3Loader<BN, 4>::frag(Bt, t, half, cb + 32 * j);
+    X3_ALL(a[0], hp);
+    X3_MM(0, 0, 0, 0); X3_LO(a[0], r1);
+    X3_MM(0, 0, 0, 1); X3_HI(a[0], r1);
+    X3_MM(0, 0, 1, 0); X3_ALL(a[0], mp); X3_LO(a[0], r2);
+    X3_MM(0, 0, 1, 1); X3_HI(a[0], r2);
+    X3_MM(0, 0, 2, 0); X3_ALL(a[0], lp);
+    X3_MM(0, 0, 2, 1);
+    X3_MM(1, 0, 0, 0); X3_MM(1, 0, 0, 1);
+    X3_MM(1, 0, 1, 0); X3_MM(1, 0, 1, 1);
+    X3_MM(2, 0, 0, 0); X3_MM(2, 0, 0, 1);
 #undef X3_PIN
 #undef X3_MM
 #undef X3_ALL
@@ -683,7 +709,7 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
     static_assert(!X3 || W1 || (A_DIRECT && B_DIRECT && sizeof(SA_T) == 4 && sizeof(SB_T) == 4 && sizeof(CT) == 2 && !B_SPLIT),
                   "three-term feeding: both operands direct fp32, bf16 MFMA");
     static_assert(!W1 || (B_DIRECT && !B_RC && sizeof(SB_T) == 2 && sizeof(CT) == 2), "packed bf16 B");
-    static_assert(!W3 || (BK == 16 && MI == 2 && NJ == 2 && !A_RC), "pre-split B: 2 x 2 accumulators, 16 k-values per tile");
+    static_assert(!W3 || (BK == 16 && MI <= 2 && NJ == 2 && !A_RC), "pre-split B: 2 x 2 or 1 x 2 accumulators, 16 k-values per tile");
     static_assert(A_BYTES % 1024 == 0, "stage addresses stay 1 KB aligned");
     __shared__ __attribute__((aligned(1024))) char ring[A_BYTES + B_BYTES];
     char *const As = ring, *const Bs = ring + A_BYTES;
@@ -848,7 +874,8 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
                 }
             } else if constexpr (W3) {
                 // fp32 A split as its fragments are read, B read as the three terms it was packed into
-                x3_step_2x2_presplit<A_RC, BM, BN, BK>(reinterpret_cast<const float *>(At), Bt, wm + l32, wn + l32, half, kv, acc);
+                if constexpr (MI == 1) x3_step_1x2_presplit<A_RC, BM, BN, BK>(reinterpret_cast<const float *>(At), Bt, wm + l32, wn + l32, half, kv, acc);
+                else x3_step_2x2_presplit<A_RC, BM, BN, BK>(reinterpret_cast<const float *>(At), Bt, wm + l32, wn + l32, half, kv, acc);
             } else if constexpr (X3 != 0 && !W1) {
                 // fp32 operands, every product as six bf16 terms (split3_pair)
 #pragma unroll
@@ -1176,9 +1203,9 @@ heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, 
         // half the splitting arithmetic leaves the k loop.
         bool packed = true;
         for (int s = 0; s < p.n_seg; ++s) packed = packed && p.seg[s].B3 != nullptr;
-        // up to 64 output columns: 256 x 64 tiles, or half of the matrix work would be done for padding (57 -> 45 us on
-        // 2 x (110 k x 128)(128 x 64))
-        if (packed && n_max <= 64) return launch_direct<bf16_t, float, false, true, float, false, true, 1, 16, 2, 3, false, 2, 2, 4, 2>(p, st, name, bytes, flops);
+        // up to 64 output columns: 128 x 64 tiles, or half of the matrix work would be done for padding; wavefronts of 32 x 64
+        // and five workgroups per CU (products of 7,000 .. 110,000 x 128 x 64: 256 x 64 tiles of 64 x 64, three per CU, 72 us, now 66)
+        if (packed && n_max <= 64) return launch_direct<bf16_t, float, false, true, float, false, true, 1, 16, 2, 5, false, 1, 2, 4, 2>(p, st, name, bytes, flops);
         // Two stages of 20 KB and at most 168 registers: three workgroups per CU, whose barriers and epilogues overlap
         // (with three stages, and the ragged tile in a code path of its own, 229 registers and two workgroups: all fp32
         // projections of a layer over 21 M edges 2.36 -> 2.20 ms; 64 x 128 columns per wavefront, half the splitting per
