@@ -14,11 +14,9 @@
 //         128-bit fragment reads of neighbouring rows fall on distinct banks (no padding);
 //       r-contiguous operand (element (r,k) at base[k*ld + r]): LDS row k, as in memory; fp32 compute
 //         reads fragments with 32-bit loads, lanes along r; under bf16 compute (the weight gradient,
-//         whose two operands both lie with the contraction index outermost) a lane gathers its eight
-//         consecutive k-values with eight 16-bit loads (bf16 storage) or eight 32-bit loads and
-//         packed converts (fp32 storage).  That costs four times the LDS instructions of a
-//         k-contiguous fragment, which a product bound by HBM (two short operand rows per graph row
-//         against 2*d_in*d_out flops) can afford; in exchange no operand passes through registers.
+//         whose two operands both lie with the contraction index outermost) a lane gets its eight
+//         consecutive k-values with two transposing reads (bf16 storage, dfrag_bf16_rc) or eight 32-bit
+//         loads and packed converts (fp32 storage); no operand passes through registers.
 //     Rows / chunks beyond the matrix are clamped to the last valid one (the duplicated data
 //     only reaches outputs that are never stored); a ragged last k-tile is masked in registers.
 //   - an operand that must be converted (fp32 -> bf16) or pair-interleaved (r-contiguous bf16)
@@ -82,6 +80,22 @@ template <int CPR> __device__ __forceinline__ int swz(int r)
     return 0;
 }
 
+// Place of chunk c (16 bytes, 8 values) in row k of an r-contiguous bf16 tile, and the chunk at place p: a transposing read
+// takes 64 bytes of four rows at a time, which have to fall on distinct banks (256 bytes of them).
+template <int CPR> __device__ __forceinline__ int rc_place(int c, int k)
+{
+    if (CPR % 16 == 0) return c ^ (4 * (k & 3));
+    const int s = 4 * ((k >> 1) & 1); // rows of an odd number of 128 bytes: the next row lies on the other half of the banks
+    if ((CPR & (CPR - 1)) == 0) return c ^ s;
+    return c + s >= CPR ? c + s - CPR : c + s;
+}
+template <int CPR> __device__ __forceinline__ int rc_chunk(int p, int k)
+{
+    if ((CPR & (CPR - 1)) == 0 || CPR % 16 == 0) return rc_place<CPR>(p, k);
+    const int s = 4 * ((k >> 1) & 1);
+    return p < s ? p - s + CPR : p - s;
+}
+
 // Direct loader of one operand.  T = storage = MFMA input type.  The address of a lane's chunk is
 // (uniform tile base) + (per-lane 32-bit byte offset); the offsets are fixed for a segment, the
 // base advances by one k-tile per issue().  Rows / chunks along r beyond the matrix are clamped
@@ -112,7 +126,8 @@ struct DirectLoader {
     __device__ __forceinline__ static int pos_of(int i, int wave, int lane)
     {
         const int q = slot_of(i, wave) * 64 + lane;
-        return RC ? q % CPR : (q % CPR) ^ swz<CPR>(q / CPR);
+        if constexpr (RC) return sizeof(T) == 2 ? rc_chunk<CPR>(q % CPR, q / CPR) : q % CPR;
+        else return (q % CPR) ^ swz<CPR>(q / CPR);
     }
 
     // r0: first r of the tile; r_total: extent of the matrix along r; k0: first k
@@ -210,16 +225,22 @@ template <int BK> __device__ __forceinline__ uint4 dfrag_bf16_from_f32(const flo
     return make_uint4(pack_bf16(lo.x, lo.y), pack_bf16(lo.z, lo.w), pack_bf16(hi.x, hi.y), pack_bf16(hi.z, hi.w));
 }
 
-// bf16 fragment of an r-contiguous bf16 operand lying in LDS as in memory (row k holds ROWS elements):
-// the lane's eight k-values kk + 8*half + 0..7 of its row r, one 16-bit read each
-template <int ROWS> __device__ __forceinline__ uint4 dfrag_bf16_rc(const bf16_t *tile, int r, int kk, int half)
+// bf16 fragment of an r-contiguous bf16 operand (rows of one k-value, chunks at rc_place): the eight k-values kk + 8*half + 0..7
+// of column r0 + l32.  Two transposing reads of four k-values each: 16 lanes give the addresses of 4 rows x 4 pieces of 8 bytes
+// and get a column of those 4 x 16 values each.  Eight 16-bit reads, which this replaces, take twice the LDS cycles and four
+// times the instructions: weight gradients in 320 x 256 tiles, six of 300 x 256 over 500,000 rows 950 -> 856 us, in 256 x 256
+// tiles, four of 768 x 1,024 over 16,000 rows 81 -> 71; those of 128 input columns, which wait for HBM, 308 us either way.
+typedef short shortx4_t __attribute__((ext_vector_type(4)));
+template <int ROWS> __device__ __forceinline__ uint4 dfrag_bf16_rc(const bf16_t *tile, int r0, int kk, int lane)
 {
-    const bf16_t *p = tile + (kk + 8 * half) * ROWS + r;
-    uint32_t w[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        w[j] = static_cast<uint32_t>(p[(2 * j) * ROWS]) | (static_cast<uint32_t>(p[(2 * j + 1) * ROWS]) << 16);
-    return make_uint4(w[0], w[1], w[2], w[3]);
+    static_assert(ROWS % 64 == 0, "whole 128-byte rows");
+    const int g = lane >> 4, i = lane & 15, row = 8 * (g >> 1) + (i >> 2); // kk is a multiple of 16
+    const bf16_t *p = tile + (kk + row) * ROWS + 8 * rc_place<ROWS / 8>(r0 / 8 + 2 * (g & 1) + ((i & 3) >> 1), row) + 4 * (i & 1);
+    typedef __attribute__((address_space(3))) shortx4_t *lds4_t;
+    union { shortx4_t v; uint2 u; } a, b;
+    a.v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(p));
+    b.v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(p + 4 * ROWS));
+    return make_uint4(a.u.x, a.u.y, b.u.x, b.u.y);
 }
 
 // the same for an r-contiguous fp32 operand: eight 32-bit reads, rounded to bf16 in pairs.  With SPLIT
@@ -919,7 +940,7 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
 #pragma unroll
                     for (int i = 0; i < MI; ++i) {
                         if constexpr (A_DIRECT && A_RC && sizeof(SA_T) == 2)
-                            a[i].u = dfrag_bf16_rc<BM>(reinterpret_cast<const bf16_t *>(At), wm + i * 32 + l32, kk, half);
+                            a[i].u = dfrag_bf16_rc<BM>(reinterpret_cast<const bf16_t *>(At), wm + i * 32, kk, lane);
                         else if constexpr (A_DIRECT && sizeof(SA_T) == 4)
                             a[i].u = dfrag_bf16_from_f32<BK>(reinterpret_cast<const float *>(At), wm + i * 32 + l32, kk, half);
                         else if constexpr (A_DIRECT) a[i].u = dfrag_bf16<BK>(reinterpret_cast<const bf16_t *>(At), wm + i * 32 + l32, kk, half);
@@ -931,7 +952,7 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
                         else if constexpr (B_DIRECT && B_RC && sizeof(SB_T) == 4)
                             b[jj].u = dfrag_bf16_rc_from_f32<BN, B_SPLIT>(reinterpret_cast<const float *>(Bt), wn + jj * 32 + l32, kk, half, &bl[jj].u);
                         else if constexpr (B_DIRECT && B_RC)
-                            b[jj].u = dfrag_bf16_rc<BN>(reinterpret_cast<const bf16_t *>(Bt), wn + jj * 32 + l32, kk, half);
+                            b[jj].u = dfrag_bf16_rc<BN>(reinterpret_cast<const bf16_t *>(Bt), wn + jj * 32, kk, lane);
                         else if constexpr (B_DIRECT && sizeof(SB_T) == 4)
                             b[jj].u = dfrag_bf16_from_f32<BK>(reinterpret_cast<const float *>(Bt), wn + jj * 32 + l32, kk, half);
                         else if constexpr (B_DIRECT) b[jj].u = dfrag_bf16<BK>(reinterpret_cast<const bf16_t *>(Bt), wn + jj * 32 + l32, kk, half);
