@@ -16,9 +16,12 @@
 // What bounds it is latency: a launch is 4 to 8 us of a few dependent L2 accesses, whatever the block's size, and each
 // launch after the first costs as much again in submission and gap.  So nothing is scanned over the whole block in a
 // launch of its own: a relation has at most 64 or 128 workgroups a side, and each of them adds up the counts of all of
-// them itself.  (The chain of two radix sorts and two scans that it replaces was 22 launches and two fills: whole calls
-// for 14 relations of 2,000 / 5,000 / 40,000 edges 202 / 216 / 445 us, now 99 / 100 / 162; by the host path, with device
-// arrays, 304 / 593 / 2,186.)
+// them itself.  What a stage reads was mostly written by other XCDs a launch before and takes one to four microseconds to
+// arrive: loads go in predicated rounds that are in flight together (a loop unrolled by 16 or 4 runs its remainder one load
+// after the other), elements that two passes need stay in registers, and searches among row offsets are made by a
+// wavefront, 64 places at a time, and then in LDS.  Whole calls for 14 relations of 2,000 / 5,000 / 40,000 edges: by the host path,
+// with device arrays, 328 / 593 / 1,889 us; a chain of two radix sorts and two scans, 22 launches, 209 / 224 / 476; these
+// four with the loads one by one 99 / 100 / 162, now 89 / 87 / 114.
 //
 // A relation's slice of every array is what the other ingest paths produce, bit for bit.  Everything is deterministic:
 // integer atomics only count, every placement is by rank.  Where a workgroup of the first launch finds the caller's
@@ -35,6 +38,7 @@ namespace heta {
 namespace {
 
 constexpr int kMaxBlockRels = 32;
+constexpr int kRounds = 4;                    // elements per lane whose loads are in flight together
 constexpr int kThreads = 256, kWaves = kThreads / 64;
 constexpr int kMaxRowBlocks = 64;             // workgroups per relation over its destination rows, over its edges
 constexpr int kMaxBuckets = 128;              // buckets of sources per relation
@@ -42,6 +46,7 @@ constexpr int kMaxRowsPer = 4096;             // rows per workgroup
 constexpr int kMaxLow = 11;                   // a bucket holds 2^10 or 2^11 sources
 constexpr int64_t kMaxElems = int64_t(1) << 18; // edges + rows of both sides of a relation: fewer (the caller's bound)
 constexpr int kMaxHubs = kMaxElems / kHubMinDeg;
+constexpr int kRowsInLds = 4096;              // offsets that a workgroup over edges searches in LDS
 static_assert(kMaxElems <= int64_t(kMaxRowBlocks) * kMaxRowsPer && kMaxElems <= int64_t(kMaxBuckets) << kMaxLow, "a relation fits its workgroups");
 static_assert(kMaxHubs <= 2 * kThreads, "hub rows of a workgroup: two per thread");
 static_assert(kHubMinDeg == 2 * kThreads, "two degree buckets per thread beside the hubs'");
@@ -97,12 +102,25 @@ __device__ __forceinline__ int seg_of(const int32_t *off, int n, int x)
 }
 
 // the last v in [lo, hi) with rp[v] <= x, lo if there is none
-__device__ __forceinline__ int row_at(const int64_t *rp, int lo, int hi, int64_t x)
+template <typename T> __device__ __forceinline__ int row_at(const T *rp, int lo, int hi, T x)
 {
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
         if (rp[mid] <= x) lo = mid;
         else hi = mid;
+    }
+    return lo;
+}
+
+// the same by a whole wavefront, 64 places at a time: two or three accesses one after another instead of a dozen
+__device__ __forceinline__ int row_at_wave(const int64_t *rp, int lo, int hi, int64_t x)
+{
+    const int lane = threadIdx.x & 63;
+    while (hi - lo > 1) {
+        const int step = (hi - lo + 63) / 64, at = lo + lane * step;
+        const bool below = lane == 0 || (at < hi && rp[at] <= x);
+        lo += (__popcll(__ballot(below)) - 1) * step; // malformed arrays: some place in [lo, hi) all the same
+        hi = min(hi, lo + step);
     }
     return lo;
 }
@@ -154,7 +172,6 @@ __device__ __forceinline__ uint2 block_scan2(uint32_t (*lds)[kWaves], uint32_t a
 // Positions of this lane's elements of kRounds consecutive rounds among those of their buckets: the wavefront's counter of
 // the bucket, plus the lanes below with the same bucket; advances the counters, whose updates a wavefront's LDS accesses
 // take in order.  Whole wavefront.
-constexpr int kRounds = 4;
 __device__ __forceinline__ void stable_slots(uint32_t *cnt, const uint32_t (&bucket)[kRounds], const bool (&live)[kRounds], int bits,
                                              uint32_t (&at)[kRounds])
 {
@@ -213,6 +230,7 @@ __global__ void __launch_bounds__(kThreads) blk_prep_kernel(BlockPlan p, BlockAr
     __shared__ uint32_t buckets[kMaxBuckets];
     __shared__ unsigned long long err;
     __shared__ int first_row, last_row;
+    __shared__ int32_t starts[kRowsInLds];
     const int tid = threadIdx.x, row_blocks = p.row_blk[p.n_rel];
     const bool rows = static_cast<int>(blockIdx.x) < row_blocks;
     const int blk = rows ? blockIdx.x : blockIdx.x - row_blocks;
@@ -244,20 +262,47 @@ __global__ void __launch_bounds__(kThreads) blk_prep_kernel(BlockPlan p, BlockAr
         int32_t *idx = a.csr_idx + p.edge_off[rel];
         uint32_t *row_of = a.row_of + p.edge_off[rel];
         if (tid < kMaxBuckets) buckets[tid] = 0;
+        int32_t c[kRounds];
+        const auto load = [&](int e0) { // all of a round in flight together
+#pragma unroll
+            for (int u = 0; u < kRounds; ++u) c[u] = e0 + u * kThreads < hi ? col[e0 + u * kThreads] : 0;
+        };
+        load(lo + tid);
         if (lo < hi) { // uniform; n_dst > 0
-            if (tid == 0) first_row = row_at(rp, 0, n_dst, lo);
-            if (tid == 64) last_row = row_at(rp, 0, n_dst, hi - 1);
+            const int w = tid >> 6;
+            if (w < 2) {
+                const int r = row_at_wave(rp, 0, n_dst, w == 0 ? lo : hi - 1);
+                if ((tid & 63) == 0) (w == 0 ? first_row : last_row) = r;
+            }
         }
         __syncthreads();
-        for (int e = lo + tid; e < hi; e += kThreads) {
-            int32_t c = col[e];
-            if (c < 0 || c >= n_src) {
-                report(&err, kBadCol, rel, e);
-                c = 0;
+        const int row0 = first_row, n_rows = lo < hi ? last_row + 1 - row0 : 0;
+        const bool in_lds = n_rows <= kRowsInLds; // uniform (malformed offsets: no rows, or some within [0, n_dst))
+        if (in_lds) {
+            for (int v0 = tid; v0 < n_rows; v0 += kRounds * kThreads) {
+                int64_t r[kRounds];
+#pragma unroll
+                for (int u = 0; u < kRounds; ++u) r[u] = v0 + u * kThreads < n_rows ? rp[row0 + v0 + u * kThreads] : 0;
+#pragma unroll
+                for (int u = 0; u < kRounds; ++u)
+                    if (v0 + u * kThreads < n_rows) starts[v0 + u * kThreads] = static_cast<int32_t>(min(r[u], static_cast<int64_t>(E) + 1));
             }
-            idx[e] = c;
-            row_of[e] = static_cast<uint32_t>(row_at(rp, first_row, last_row + 1, e));
-            atomicAdd(&buckets[c >> low], 1u);
+            __syncthreads();
+        }
+        for (int e0 = lo + tid; e0 < hi; e0 += kRounds * kThreads) {
+            if (e0 != lo + tid) load(e0);
+#pragma unroll
+            for (int u = 0; u < kRounds; ++u) {
+                const int e = e0 + u * kThreads;
+                if (e >= hi) continue;
+                if (c[u] < 0 || c[u] >= n_src) {
+                    report(&err, kBadCol, rel, e);
+                    c[u] = 0;
+                }
+                idx[e] = c[u];
+                row_of[e] = static_cast<uint32_t>(in_lds ? row0 + row_at(starts, 0, n_rows, e) : row_at(rp, row0, row0 + n_rows, static_cast<int64_t>(e)));
+                atomicAdd(&buckets[c[u] >> low], 1u);
+            }
         }
         __syncthreads();
         if (tid < kMaxBuckets) a.bucket_counts[static_cast<int64_t>(blk) * kMaxBuckets + tid] = static_cast<uint16_t>(buckets[tid]);
@@ -302,6 +347,19 @@ __device__ __forceinline__ void place_rows(PlaceLds &L, int n, int lo, int hi, i
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int share = per / kWaves; // a multiple of 64
     const int wlo = lo + w * share, whi = min(hi, wlo + share);
+    uint32_t p0[kRounds], deg[kRounds];
+    const auto load_rows = [&](int i0) {
+        uint32_t p1[kRounds];
+#pragma unroll
+        for (int u = 0; u < kRounds; ++u) {
+            const int v = i0 + 64 * u + lane;
+            p0[u] = v < whi ? static_cast<uint32_t>(ptr[v]) : 0;
+            p1[u] = v < whi ? static_cast<uint32_t>(ptr[v + 1]) : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < kRounds; ++u) deg[u] = p1[u] - p0[u];
+    };
+    load_rows(wlo);
     for (int i = tid; i < kWaves * (kDegHist + 3); i += kThreads) (&L.cnt[0][0])[i] = 0;
     if (tid < 6) L.hub[tid / 3][tid % 3] = 0;
     if (tid == 6) L.max_deg = 0;
@@ -314,13 +372,17 @@ __device__ __forceinline__ void place_rows(PlaceLds &L, int n, int lo, int hi, i
         edges = counts[tid].hub_edges;
         chunks = counts[tid].hub_chunks;
     }
-#pragma unroll 16
-    for (int q = 0; q < nb; ++q) {
-        const uint32_t c = reinterpret_cast<const uint32_t *>(counts[q].rows)[j];
-        total0 += c & 0xffffu;
-        total1 += c >> 16;
-        before0 += q < b ? c & 0xffffu : 0;
-        before1 += q < b ? c >> 16 : 0;
+    for (int q0 = 0; q0 < nb; q0 += 16) {
+        uint32_t c[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) c[i] = q0 + i < nb ? reinterpret_cast<const uint32_t *>(counts[q0 + i].rows)[j] : 0;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            total0 += c[i] & 0xffffu;
+            total1 += c[i] >> 16;
+            before0 += q0 + i < b ? c[i] & 0xffffu : 0;
+            before1 += q0 + i < b ? c[i] >> 16 : 0;
+        }
     }
     __syncthreads();
     if (rows > 0) {
@@ -331,11 +393,15 @@ __device__ __forceinline__ void place_rows(PlaceLds &L, int n, int lo, int hi, i
         }
     }
     uint32_t most = 0;
-#pragma unroll 4
-    for (int v = wlo + lane; v < whi; v += 64) {
-        const uint32_t deg = static_cast<uint32_t>(ptr[v + 1] - ptr[v]);
-        atomicAdd(&L.cnt[w][min(deg, static_cast<uint32_t>(kHubMinDeg))], 1u);
-        most = max(most, min(deg, static_cast<uint32_t>(kHubMinDeg)));
+    for (int i0 = wlo; i0 < whi; i0 += 64 * kRounds) { // uniform per wavefront
+        if (i0 != wlo) load_rows(i0);
+#pragma unroll
+        for (int u = 0; u < kRounds; ++u) {
+            if (i0 + 64 * u + lane >= whi) continue;
+            const uint32_t k = min(deg[u], static_cast<uint32_t>(kHubMinDeg));
+            atomicAdd(&L.cnt[w][k], 1u);
+            most = max(most, k);
+        }
     }
     atomicMax(&L.max_deg, most);
     const uint32_t k0 = 2 * j, k1 = k0 + 1;
@@ -378,14 +444,13 @@ __device__ __forceinline__ void place_rows(PlaceLds &L, int n, int lo, int hi, i
     __syncthreads();
     const int bits = 32 - __clz(static_cast<int>(L.max_deg)); // 0 where every row is empty
     for (int i0 = wlo; i0 < whi; i0 += 64 * kRounds) { // uniform per wavefront
-        uint32_t k[kRounds], at[kRounds], p0[kRounds];
+        uint32_t k[kRounds], at[kRounds];
         bool live[kRounds];
+        if (whi - wlo > 64 * kRounds) load_rows(i0); // else they are still there
 #pragma unroll
         for (int u = 0; u < kRounds; ++u) {
-            const int v = i0 + 64 * u + lane;
-            live[u] = v < whi;
-            p0[u] = live[u] ? static_cast<uint32_t>(ptr[v]) : 0;
-            k[u] = live[u] ? min(static_cast<uint32_t>(ptr[v + 1]) - p0[u], static_cast<uint32_t>(kHubMinDeg)) : 0;
+            live[u] = i0 + 64 * u + lane < whi;
+            k[u] = live[u] ? min(deg[u], static_cast<uint32_t>(kHubMinDeg)) : 0;
         }
         stable_slots(L.cnt[w], k, live, bits, at);
 #pragma unroll
@@ -405,16 +470,16 @@ __device__ __forceinline__ void place_rows(PlaceLds &L, int n, int lo, int hi, i
     __syncthreads();
     const int n_hubs = static_cast<int>(counts[b].hub_rows);
     if (n_hubs > 0) { // uniform; two hub rows per thread
-        uint32_t v[2] = {0, 0}, deg[2] = {0, 0}, nc[2];
+        uint32_t v[2] = {0, 0}, hub_deg[2] = {0, 0}, nc[2];
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             if (2 * tid + i < n_hubs) {
                 v[i] = L.hub_row[2 * tid + i];
-                deg[i] = static_cast<uint32_t>(ptr[v[i] + 1] - ptr[v[i]]);
+                hub_deg[i] = static_cast<uint32_t>(ptr[v[i] + 1] - ptr[v[i]]);
             }
-            nc[i] = (deg[i] + kHubChunk - 1) / kHubChunk;
+            nc[i] = (hub_deg[i] + kHubChunk - 1) / kHubChunk;
         }
-        const uint2 first = block_scan2(L.scan, deg[0] + deg[1], nc[0] + nc[1]);
+        const uint2 first = block_scan2(L.scan, hub_deg[0] + hub_deg[1], nc[0] + nc[1]);
         uint32_t s = hub_edges_before + first.x, c0 = chunks_before + first.y;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
@@ -426,20 +491,33 @@ __device__ __forceinline__ void place_rows(PlaceLds &L, int n, int lo, int hi, i
                 for (uint32_t c = 0; c < nc[i]; ++c) {
                     HubChunk d;
                     d.e0 = s + c * kHubChunk;
-                    d.len = static_cast<int32_t>(min(static_cast<uint32_t>(kHubChunk), deg[i] - c * kHubChunk));
+                    d.len = static_cast<int32_t>(min(static_cast<uint32_t>(kHubChunk), hub_deg[i] - c * kHubChunk));
                     d.slot = static_cast<int32_t>(c0 + c);
                     hub_chunks[c0 + c] = d;
                 }
             }
-            s += deg[i];
+            s += hub_deg[i];
             c0 += nc[i];
         }
         __syncthreads();
     }
     if (lo >= hi) return;
-    const int e1 = static_cast<int>(ptr[hi]);
-#pragma unroll 4
-    for (int e = static_cast<int>(ptr[lo]) + tid; e < e1; e += kThreads) sidx[e + L.delta[row_of[e] - lo]] = idx[e];
+    const int e0 = static_cast<int>(ptr[lo]), e1 = static_cast<int>(ptr[hi]);
+    for (int i0 = e0 + tid; i0 < e1; i0 += kRounds * kThreads) {
+        uint32_t row[kRounds];
+        int32_t nbr[kRounds];
+#pragma unroll
+        for (int u = 0; u < kRounds; ++u) {
+            const int e = i0 + u * kThreads;
+            row[u] = e < e1 ? row_of[e] : 0;
+            nbr[u] = e < e1 ? idx[e] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < kRounds; ++u) {
+            const int e = i0 + u * kThreads;
+            if (e < e1) sidx[e + L.delta[row[u] - lo]] = nbr[u];
+        }
+    }
 }
 
 // ---- second launch --------------------------------------------------------------------------------------------------
@@ -460,19 +538,37 @@ __device__ __forceinline__ void spread_edges(SpreadLds &L, const BlockPlan &p, c
     const uint32_t *row_of = a.row_of + p.edge_off[rel];
     uint2 *out = a.spread + p.edge_off[rel];
     const uint16_t *counts = a.bucket_counts + static_cast<int64_t>(p.edge_blk[rel]) * kMaxBuckets;
+    uint32_t c[kRounds], row[kRounds];
+    const auto load = [&](int i0) {
+#pragma unroll
+        for (int u = 0; u < kRounds; ++u) {
+            const int e = i0 + 64 * u + lane;
+            c[u] = e < whi ? static_cast<uint32_t>(idx[e]) : 0;
+            row[u] = e < whi ? row_of[e] : 0;
+        }
+    };
+    load(wlo);
     for (int i = tid; i < kWaves * kMaxBuckets; i += kThreads) (&L.cnt[0][0])[i] = 0;
     uint32_t total = 0, before = 0;
     if (tid < kMaxBuckets) {
-#pragma unroll 16
-        for (int q = 0; q < nb; ++q) {
-            const uint32_t c = counts[q * kMaxBuckets + tid];
-            total += c;
-            before += q < b ? c : 0;
+        for (int q0 = 0; q0 < nb; q0 += 16) {
+            uint32_t n[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) n[i] = q0 + i < nb ? counts[(q0 + i) * kMaxBuckets + tid] : 0;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                total += n[i];
+                before += q0 + i < b ? n[i] : 0;
+            }
         }
     }
     __syncthreads();
-#pragma unroll 4
-    for (int e = wlo + lane; e < whi; e += 64) atomicAdd(&L.cnt[w][idx[e] >> low], 1u);
+    for (int i0 = wlo; i0 < whi; i0 += 64 * kRounds) { // uniform per wavefront
+        if (i0 != wlo) load(i0);
+#pragma unroll
+        for (int u = 0; u < kRounds; ++u)
+            if (i0 + 64 * u + lane < whi) atomicAdd(&L.cnt[w][c[u] >> low], 1u);
+    }
     const uint32_t start = block_scan2(L.scan, total, 0).x; // its barriers come after the last count
     if (tid < kMaxBuckets) {
         uint32_t run = start + before;
@@ -491,14 +587,12 @@ __device__ __forceinline__ void spread_edges(SpreadLds &L, const BlockPlan &p, c
     int bits = 0;
     while ((n_src - 1) >> (low + bits) > 0) ++bits;
     for (int i0 = wlo; i0 < whi; i0 += 64 * kRounds) { // uniform per wavefront
-        uint32_t c[kRounds], row[kRounds], bucket[kRounds], at[kRounds];
+        uint32_t bucket[kRounds], at[kRounds];
         bool live[kRounds];
+        if (whi - wlo > 64 * kRounds) load(i0); // else they are still there
 #pragma unroll
         for (int u = 0; u < kRounds; ++u) {
-            const int e = i0 + 64 * u + lane;
-            live[u] = e < whi;
-            c[u] = live[u] ? static_cast<uint32_t>(idx[e]) : 0;
-            row[u] = live[u] ? row_of[e] : 0;
+            live[u] = i0 + 64 * u + lane < whi;
             bucket[u] = c[u] >> low;
         }
         stable_slots(L.cnt[w], bucket, live, bits, at);
@@ -549,11 +643,21 @@ __global__ void __launch_bounds__(kThreads) blk_columns_kernel(BlockPlan p, Bloc
     int64_t *ptr = a.csc_ptr + p.src_off[rel] + rel;
     int32_t *idx = a.csc_idx + p.edge_off[rel] + e0;
     uint32_t *src_of = a.src_of + p.edge_off[rel] + e0;
+    uint2 pair[kRounds];
+    const auto load = [&](int i0) {
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) pair[r] = i0 + 64 * r + lane < whi ? in[i0 + 64 * r + lane] : make_uint2(u0, 0);
+    };
+    load(wlo);
     for (int i = tid; i < kWaves * SRC; i += kThreads) (&cnt[0][0])[i] = 0;
     hist_clear(hist);
     __syncthreads();
-#pragma unroll 4
-    for (int i = wlo + lane; i < whi; i += 64) atomicAdd(&cnt[w][in[i].x - u0], 1u);
+    for (int i0 = wlo; i0 < whi; i0 += 64 * kRounds) { // uniform per wavefront
+        if (i0 != wlo) load(i0);
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r)
+            if (i0 + 64 * r + lane < whi) atomicAdd(&cnt[w][pair[r].x - u0], 1u);
+    }
     __syncthreads();
     uint32_t deg[PER], sum = 0; // PER consecutive sources per thread
 #pragma unroll
@@ -581,14 +685,12 @@ __global__ void __launch_bounds__(kThreads) blk_columns_kernel(BlockPlan p, Bloc
     __syncthreads();
     hist_store(hist, a.src_counts + blockIdx.x);
     for (int i0 = wlo; i0 < whi; i0 += 64 * kRounds) { // uniform per wavefront
-        uint2 pair[kRounds];
         uint32_t u[kRounds], at[kRounds];
         bool live[kRounds];
+        if (whi - wlo > 64 * kRounds) load(i0); // else they are still there
 #pragma unroll
         for (int r = 0; r < kRounds; ++r) {
-            const int i = i0 + 64 * r + lane;
-            live[r] = i < whi;
-            pair[r] = live[r] ? in[i] : make_uint2(u0, 0);
+            live[r] = i0 + 64 * r + lane < whi;
             u[r] = pair[r].x - u0;
         }
         stable_slots(cnt[w], u, live, low, at);
