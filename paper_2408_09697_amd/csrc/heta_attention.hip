@@ -1362,6 +1362,8 @@ __global__ void __launch_bounds__(256, 2) attn_score_multi_kernel(ScoreTables q)
 // dx[i, :] (+)= sum_v dscore_v[i] vec_v: 32 rows per tile are the first operand, the four columns 4 l .. 4 l + 3 of
 // lane l the second one of four products, so that a row leaves as 16-byte stores of whole cache lines.  The vectors
 // sit in LDS, zero beyond d and up to a multiple of eight vectors; step (c, j) multiplies vector 8 c + 4 h + j.
+// (Brought there element by element, each lane working out its vector, that was half of the time where a table of 100,000
+// rows has 56 vectors: four tables of 187,000 rows together 59 us, now 44.)
 template <bool VEC>
 __global__ void __launch_bounds__(256, 3) attn_score_bwd_multi_input_kernel(ScoreTables q)
 {
@@ -1376,9 +1378,22 @@ __global__ void __launch_bounds__(256, 3) attn_score_bwd_multi_input_kernel(Scor
     const int lane = threadIdx.x & 63, l = lane & 31, h = lane >> 5;
     const int nc = (m.NV + 7) / 8;
     const gf32 **sptr = reinterpret_cast<const gf32 **>(vecs + 8 * nc * kMultiCols);
-    for (int t = threadIdx.x; t < 8 * nc * kMultiCols; t += 256) {
-        const int v = t / kMultiCols, c = t % kMultiCols;
-        vecs[t] = v < m.NV && c < d ? pick(m.vec, v / m.K)[static_cast<int64_t>(v % m.K) * d + c] : 0.f;
+    // one vector per wavefront and load, two columns per lane (d is a multiple of four): which set it belongs to is uniform
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (int v0 = w; v0 < 8 * nc; v0 += 16) {
+        float2 t[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int v = min(v0 + 4 * u, m.NV - 1), set = v / m.K;
+            t[u] = *reinterpret_cast<const float2 *>(m.vec[set] + static_cast<int64_t>(v - set * m.K) * d + (2 * lane < d ? 2 * lane : 0));
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int v = v0 + 4 * u;
+            if (v >= 8 * nc) continue;
+            const bool given = v < m.NV && 2 * lane < d;
+            *reinterpret_cast<float2 *>(vecs + v * kMultiCols + 2 * lane) = given ? t[u] : make_float2(0.f, 0.f);
+        }
     }
     for (int v = threadIdx.x; v < 8 * nc; v += 256) sptr[v] = v < m.NV ? (const gf32 *)(pick(m.score, v / m.K) + v % m.K) : nullptr;
     __syncthreads();
