@@ -3,8 +3,9 @@
 // A heterogeneous graph is handed over as its mono-relation subgraphs (Section 2.1 of the
 // paper), one CSR over destination rows per relation.  Everything index-shaped that the
 // aggregation kernels need later is derived here once and kept on the device: by the kernels of
-// heta_ingest.hip for relations of real size, by the host code below for the small blocks of a
-// sampled mini-batch, where launch latency would dominate.  Both produce the same arrays.
+// heta_ingest.hip for relations of real size, by those of heta_block_ingest.hip for all small relations of a
+// call together (the blocks of a sampled mini-batch, whose arrays are on the device), by the host code below
+// where a few small relations come as host arrays.  All produce the same arrays.
 #include <algorithm>
 #include <atomic>
 #include <cstring>
@@ -51,14 +52,21 @@ heta_status fail(heta_status st, const char *fmt, ...)
 // iteration; each hipMalloc / hipFree pair costs tens of microseconds, hundreds from some 100 MB on, and hipFree waits for
 // the device.  Blocks of up to 256 MiB (the partial weight gradients of two blocks of 4,096 seeds, 768 x 1,024: 30 to 130 MB)
 // are rounded up to a power of two, above 16 MiB to a quarter of one, and kept on a free list per (device, size) when
-// released, up to 1 GiB in total; larger ones go straight to hipMalloc / hipFree.  The list goes back to the device when
-// an allocation fails.  A block must be idle when it is released (the callers synchronise first).
+// released, up to 1 GiB in total, past which those released longest ago go back to the device (kept instead, they left no
+// room for what follows them: training iterations of 768 columns 1,040 us, after layers over larger graphs 1,330); larger
+// ones go straight to hipMalloc / hipFree.  The whole list goes back when an allocation fails.  A block must be idle when it
+// is released (the callers synchronise first).
 namespace {
 constexpr size_t kPoolMaxBlock = size_t(256) << 20, kPoolMaxCached = size_t(1) << 30;
 std::mutex g_pool_mu;
 std::unordered_map<void *, std::pair<int, size_t>> g_pool_blocks;     // live pooled block -> (device, size class)
-std::map<std::pair<int, size_t>, std::vector<void *>> g_pool_free;
+struct FreeBlock {
+    void *p;
+    unsigned long long released; // by the pool's own count of releases
+};
+std::map<std::pair<int, size_t>, std::vector<FreeBlock>> g_pool_free; // every list in order of release
 size_t g_pool_cached = 0;
+unsigned long long g_pool_releases = 0;
 
 size_t pool_class(size_t bytes)
 {
@@ -76,9 +84,9 @@ void pool_give_back(int dev)
     {
         std::lock_guard<std::mutex> lk(g_pool_mu);
         for (auto it = g_pool_free.lower_bound({dev, 0}); it != g_pool_free.end() && it->first.first == dev; it = g_pool_free.erase(it))
-            for (void *p : it->second) {
-                blocks.push_back(p);
-                g_pool_blocks.erase(p);
+            for (const FreeBlock &b : it->second) {
+                blocks.push_back(b.p);
+                g_pool_blocks.erase(b.p);
                 g_pool_cached -= it->first.second;
             }
     }
@@ -99,7 +107,7 @@ hipError_t scratch_alloc(void **out, size_t bytes)
         // the smallest block that is large enough, but not of twice the size
         for (auto it = g_pool_free.lower_bound({dev, cls}); it != g_pool_free.end() && it->first.first == dev && it->first.second < 2 * cls; ++it)
             if (!it->second.empty()) {
-                *out = it->second.back();
+                *out = it->second.back().p;
                 it->second.pop_back();
                 g_pool_cached -= it->first.second;
                 return hipSuccess;
@@ -120,20 +128,28 @@ hipError_t scratch_alloc(void **out, size_t bytes)
 void scratch_free(void *p)
 {
     if (!p) return;
+    std::vector<void *> back; // to the device
     {
         std::lock_guard<std::mutex> lk(g_pool_mu);
-        auto it = g_pool_blocks.find(p);
-        if (it != g_pool_blocks.end()) {
-            const size_t cls = it->second.second;
-            if (g_pool_cached + cls <= kPoolMaxCached) {
-                g_pool_free[it->second].push_back(p);
-                g_pool_cached += cls;
-                return;
+        const auto it = g_pool_blocks.find(p);
+        if (it == g_pool_blocks.end()) {
+            back.push_back(p);
+        } else {
+            const size_t cls = it->second.second; // at most kPoolMaxBlock: there is room for it once others have gone
+            while (g_pool_cached + cls > kPoolMaxCached) {
+                auto oldest = g_pool_free.end();
+                for (auto f = g_pool_free.begin(); f != g_pool_free.end(); ++f)
+                    if (!f->second.empty() && (oldest == g_pool_free.end() || f->second.front().released < oldest->second.front().released)) oldest = f;
+                back.push_back(oldest->second.front().p);
+                g_pool_blocks.erase(oldest->second.front().p);
+                g_pool_cached -= oldest->first.second;
+                oldest->second.erase(oldest->second.begin());
             }
-            g_pool_blocks.erase(it);
+            g_pool_free[it->second].push_back({p, g_pool_releases++});
+            g_pool_cached += cls;
         }
     }
-    (void)hipFree(p);
+    for (void *q : back) (void)hipFree(q);
 }
 
 heta_status ensure_workspace(heta_graph *g, size_t bytes)
