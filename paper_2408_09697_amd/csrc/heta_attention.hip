@@ -1190,6 +1190,7 @@ __global__ void __launch_bounds__(1024) attn_slab_sum_kernel(const float *part, 
 // per-lane FMAs: scores 547 -> 271 us, input gradient 472 -> 224 us; 187,000 bf16 rows with up to 56 vectors (set by set
 // before, above 32): 274 -> 63 and 209 -> 81 us.
 constexpr int kMultiSets = 8, kMultiCols = 128;
+constexpr int kScoreTiles = 4; // tiles of 16 vectors that a workgroup of the forward keeps in LDS
 constexpr int kMultiVecs = 120; // the input gradient keeps all vectors in LDS: 120 * (512 + 8) bytes stay below 64 KB
 struct ScoreMulti {
     const float *vec[kMultiSets]; // [K][d] each
@@ -1208,7 +1209,7 @@ struct ScoreTable {
     const void *x;
     float *dx, *part;
     int64_t ld_x, ld_dx, n, slab_rows, n_slabs;
-    int d, nb, nvc; // nb: workgroups along the rows
+    int d, nb, nvc; // nb: workgroups along the rows; nvc: tiles of vectors per workgroup (forward), vectors in whole tiles (backward)
     float beta;
     unsigned first; // its first workgroup
     ScoreMulti m;
@@ -1248,12 +1249,6 @@ template <> __device__ __forceinline__ void load4<float>(const float *p, float f
     const float4 v = *reinterpret_cast<const float4 *>(p);
     f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
 }
-template <> __device__ __forceinline__ void load4<bf16_t>(const bf16_t *p, float f[4])
-{
-    const uint2 v = *reinterpret_cast<const uint2 *>(p);
-    f[0] = __uint_as_float(v.x << 16); f[1] = __uint_as_float(v.x & 0xffff0000u);
-    f[2] = __uint_as_float(v.y << 16); f[3] = __uint_as_float(v.y & 0xffff0000u);
-}
 
 // the same in two steps: the load, and its four columns
 template <typename T> struct Raw4;
@@ -1272,7 +1267,7 @@ template <> struct Raw4<bf16_t> {
     }
 };
 
-// Scores of 16 NT vectors (the workgroup's second index picks them) and 16 rows per tile: the vectors are the first operand, so a
+// Scores of up to 16 kScoreTiles vectors and 16 rows per tile: the vectors are the first operand, so a
 // lane ends with one row's scores of four consecutive vectors - one 16-byte store where a set has a multiple of
 // four heads (VEC).  A lane holds the columns 16 c + 4 h .. + 3 of its vector and of its row (h: its quarter of the
 // wavefront): which k a step multiplies is free as long as both operands agree.  Sums of eight products
@@ -1301,10 +1296,16 @@ template <int NC> __device__ __forceinline__ f32x4 score_sum(const float (&a)[NC
     return level[NC == 8 ? 3 : NC == 4 ? 2 : 1]; // NC is 2, 4 or 8
 }
 
-template <typename T, int NC, int NT, bool VEC>
-__global__ void __launch_bounds__(256, 2) attn_score_multi_kernel(ScoreTables q)
+// Half of the time of a table of 100,000 rows was the start of each wavefront (its vectors into registers, for two tiles of rows)
+// and the wait for each tile's rows.  So the vectors lie in LDS as the lanes hold them, brought there once per workgroup, up to
+// 64 for one pass over the rows, and the rows of the next tile are on their way while this one's are multiplied.  Four bf16
+// tables of 187,000 rows together with 32 vectors in registers, two workgroups per CU: 50 + 7 us in two launches, now 32 in one;
+// fp32 tables of 1.87 M rows, whose wavefronts had many tiles: 167 + 110 us, now 271.  Four workgroups per CU spill at 128 columns
+// (45 and 501 us).
+template <typename T, int NC, bool VEC>
+__global__ void __launch_bounds__(256, NC == 8 ? 3 : 4) attn_score_multi_kernel(ScoreTables q)
 {
-    __shared__ gf32 *sptr[16 * NT];
+    extern __shared__ __align__(16) float4 svec[]; // [tile][NC][lane], then the pointers
     unsigned wg;
     const ScoreTable &tab = score_table_of(q, wg);
     const ScoreMulti &m = tab.m;
@@ -1312,37 +1313,53 @@ __global__ void __launch_bounds__(256, 2) attn_score_multi_kernel(ScoreTables q)
     const int64_t ld_x = tab.ld_x, n = tab.n;
     const int d = tab.d, nb = tab.nb;
     const int lane = threadIdx.x & 63, l = lane & 15, h = lane >> 4;
-    const int v0 = static_cast<int>(wg / nb) * 16 * NT;
+    const int t0 = static_cast<int>(wg / nb) * tab.nvc, nt = min(tab.nvc, (m.NV + 15) / 16 - t0), v0 = 16 * t0;
     wg %= nb;
-    if (threadIdx.x < 16 * NT) {
+    const int64_t step = static_cast<int64_t>(nb) * 4 * 16;
+    int64_t r0 = (static_cast<int64_t>(wg) * 4 + (threadIdx.x >> 6)) * 16;
+    Raw4<T> next[NC];
+    const auto load = [&](int64_t row0) { // rows past the end repeat the last one and are not stored, columns past it count as zero
+        const T *xr = x + min(row0 + l, n - 1) * ld_x;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) next[c].load(xr + (16 * c + 4 * h < d ? 16 * c + 4 * h : 0));
+    };
+    load(r0);
+    gf32 **sptr = reinterpret_cast<gf32 **>(svec + nt * NC * 64);
+    for (int i0 = threadIdx.x; i0 < nt * NC * 64; i0 += 1024) { // four loads in flight
+        float4 t[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + 256 * u, v = min(v0 + i / (NC * 64) * 16 + l, m.NV - 1), set = v / m.K, col = i / 64 % NC * 16 + 4 * h;
+            t[u] = *reinterpret_cast<const float4 *>(pick(m.vec, set) + static_cast<int64_t>(v - set * m.K) * d + (col < d ? col : 0));
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + 256 * u;
+            if (i >= nt * NC * 64) continue;
+            const bool given = v0 + i / (NC * 64) * 16 + l < m.NV && i / 64 % NC * 16 + 4 * h < d;
+            svec[i] = given ? t[u] : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    }
+    if (static_cast<int>(threadIdx.x) < 16 * nt) {
         const int v = v0 + threadIdx.x;
         sptr[threadIdx.x] = v < m.NV ? (gf32 *)(pick(m.score, v / m.K) + v % m.K) : nullptr;
     }
-    float a[NT][NC][4];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const int v = v0 + 16 * t + l, vc = min(v, m.NV - 1);
-        const float *vec = pick(m.vec, vc / m.K) + static_cast<int64_t>(vc % m.K) * d;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            a[t][c][0] = a[t][c][1] = a[t][c][2] = a[t][c][3] = 0.f;
-            if (v < m.NV && 16 * c + 4 * h < d) load4<float>(vec + 16 * c + 4 * h, a[t][c]);
-        }
-    }
     __syncthreads();
-    const int64_t wave = static_cast<int64_t>(wg) * 4 + (threadIdx.x >> 6), step = static_cast<int64_t>(nb) * 4 * 16;
-    for (int64_t r0 = wave * 16; r0 < n; r0 += step) { // uniform per wavefront
+    for (; r0 < n; r0 += step) { // uniform per wavefront
         const int64_t r = r0 + l;
-        const T *xr = x + min(r, n - 1) * ld_x; // rows past the end repeat the last one and are not stored
         float xv[NC][4];
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            xv[c][0] = xv[c][1] = xv[c][2] = xv[c][3] = 0.f;
-            if (16 * c + 4 * h < d) load4<T>(xr + 16 * c + 4 * h, xv[c]);
-        }
+            next[c].get(xv[c]);
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const f32x4 s = score_sum<NC>(a[t], xv);
+            for (int j = 0; j < 4; ++j) xv[c][j] = 16 * c + 4 * h < d ? xv[c][j] : 0.f;
+        }
+        if (r0 + step < n) load(r0 + step);
+        for (int t = 0; t < nt; ++t) {
+            float a[NC][4];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) load4<float>(reinterpret_cast<const float *>(svec + (t * NC + c) * 64 + lane), a[c]);
+            const f32x4 s = score_sum<NC>(a, xv);
             if (r < n) {
                 if (VEC) {
                     gf32 *o = sptr[16 * t + 4 * h];
@@ -1959,24 +1976,29 @@ heta_status heta_attn_score_tables(int32_t n, const int32_t *first, const void *
             ScoreTable t = score_table(x[i], ld_x[i], n_rows[i], d[i], n_sets, heads, vecs + first[i], scores + first[i]);
             bool vec4 = heads % 4 == 0;
             for (int32_t j = first[i]; j < first[i + 1]; ++j) vec4 = vec4 && aligned16(scores[j]);
-            // a wavefront takes tiles of 16 rows; up to 16 vectors leave registers for four workgroups per CU, 32 for two
-            const int nt = t.m.NV <= 16 ? 1 : 2;
-            t.nb = static_cast<int>(std::min<int64_t>((t.n + 63) / 64, nt == 1 ? 1024 : 512));
+            const int tiles = (t.m.NV + 15) / 16, groups = (tiles + kScoreTiles - 1) / kScoreTiles;
+            t.nvc = (tiles + groups - 1) / groups;
             tabs.push_back(t);
-            kind.push_back((d[i] <= 32 ? 0 : d[i] <= 64 ? 4 : 8) + (nt == 1 ? 0 : 2) + (vec4 ? 1 : 0));
+            kind.push_back((d[i] <= 32 ? 0 : d[i] <= 64 ? 2 : 4) + (vec4 ? 1 : 0));
         }
-#define HETA_SM(TT, NC, NT, V4) hipLaunchKernelGGL((attn_score_multi_kernel<TT, NC, NT, V4>), dim3(blocks), dim3(256), 0, st, q)
-#define HETA_SM_V(TT, NC, NT) do { if (k & 1) HETA_SM(TT, NC, NT, true); else HETA_SM(TT, NC, NT, false); } while (0)
-#define HETA_SM_N(TT, NC) do { if (k & 2) HETA_SM_V(TT, NC, 2); else HETA_SM_V(TT, NC, 1); } while (0)
-#define HETA_SM_T(TT) do { if (k < 4) HETA_SM_N(TT, 2); else if (k < 8) HETA_SM_N(TT, 4); else HETA_SM_N(TT, 8); } while (0)
-        return for_tables_of_a_kind(tabs, kind, 12, [&](ScoreTables &q, int k) {
-            const unsigned nt = k & 2 ? 2 : 1;
-            unsigned blocks = 0;
+#define HETA_SM(TT, NC, V4) hipLaunchKernelGGL((attn_score_multi_kernel<TT, NC, V4>), dim3(blocks), dim3(256), lds, st, q)
+#define HETA_SM_V(TT, NC) do { if (k & 1) HETA_SM(TT, NC, true); else HETA_SM(TT, NC, false); } while (0)
+#define HETA_SM_T(TT) do { if (k < 2) HETA_SM_V(TT, 2); else if (k < 4) HETA_SM_V(TT, 4); else HETA_SM_V(TT, 8); } while (0)
+        return for_tables_of_a_kind(tabs, kind, 6, [&](ScoreTables &q, int k) {
+            // one round of workgroups, as many as are resident (four per CU, three of 128 columns), of the same work each: 64 rows
+            // at a time times their tiles of vectors
+            int64_t work = 0;
+            for (int c = 0; c < q.n; ++c) work += (q.t[c].n + 63) / 64 * ((q.t[c].m.NV + 15) / 16);
+            const int64_t slots = k < 4 ? 1024 : 768, each = (work + slots - 1) / slots;
+            unsigned blocks = 0, lds = 0;
             double bytes = 0;
             for (int c = 0; c < q.n; ++c) {
                 ScoreTable &t = q.t[c];
+                const int64_t rounds = (each + t.nvc - 1) / t.nvc; // of 64 rows
+                t.nb = static_cast<int>(((t.n + 63) / 64 + rounds - 1) / rounds);
                 t.first = blocks;
-                blocks += t.nb * ((t.m.NV + 16 * nt - 1) / (16 * nt));
+                blocks += t.nb * (((t.m.NV + 15) / 16 + t.nvc - 1) / t.nvc);
+                lds = std::max(lds, static_cast<unsigned>(t.nvc) * ((k < 2 ? 2 : k < 4 ? 4 : 8) * 1024 + 16 * 8));
                 bytes += static_cast<double>(t.n) * (t.d * dtype_size(dt) + 4.0 * t.m.NV);
             }
             ProfScope prof("attn_score_multi_kernel", st, bytes, 0);
@@ -1986,7 +2008,6 @@ heta_status heta_attn_score_tables(int32_t n, const int32_t *first, const void *
             return HETA_OK;
         });
 #undef HETA_SM_T
-#undef HETA_SM_N
 #undef HETA_SM_V
 #undef HETA_SM
     } catch (const std::bad_alloc &) {

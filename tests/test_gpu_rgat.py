@@ -81,6 +81,26 @@ def test_attn_score_of_more_rows_than_a_grid_has_wavefronts():
     assert bool(((score - ref).abs() <= 1e-5 * (x * vec).abs().sum(1, keepdim=True)).all())
 
 
+@pytest.mark.parametrize("n,d,heads,n_sets", [(49_153, 128, 4, 4), (200_007, 128, 16, 5), (60_001, 100, 15, 8), (150_000, 36, 8, 7),
+                                             (131_075, 20, 3, 1)])
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+def test_scores_of_more_rows_than_one_round_of_tiles(n, d, heads, n_sets, storage):
+    """Several tiles of rows per wavefront, one or two groups of vectors, NaN in the columns past the table's width."""
+    gen = torch.Generator(device="cuda").manual_seed(n + d)
+    dt = torch.float32 if storage == "f32" else torch.bfloat16
+    wide = torch.full((n, d + 8 if d % 8 == 0 else (d + 7) // 8 * 8), float("nan"), dtype=dt, device="cuda")
+    x = wide[:, :d]
+    x.copy_(torch.randn((n, d), generator=gen, device="cuda"))
+    vecs = [torch.randn((heads, d), generator=gen, device="cuda") for _ in range(n_sets)]
+    scores = [torch.full((n, heads), float("nan"), device="cuda") for _ in range(n_sets)]
+    heta.heta_attn_score_multi(x, vecs, scores)
+    # a score passes through at most 16 roundings (products and sums of eight, pairwise sums), each off by at most 2^-23
+    x64 = x.double()
+    for v, sc in zip(vecs, scores):
+        bound = 16 * 2.0 ** -23 * (x64.abs() @ v.double().abs().T)
+        assert bool(((sc.double() - x64 @ v.double().T).abs() <= bound).all())
+
+
 @pytest.mark.parametrize("n,d,heads,n_sets,pad", [(3000, 128, 4, 6, 4), (1001, 128, 4, 8, 4), (700, 64, 1, 3, 4), (513, 100, 3, 5, 4),
                                                   (40, 128, 16, 2, 4), (1, 8, 2, 1, 4),
                                                   (150, 128, 8, 6, 4),
