@@ -52,7 +52,7 @@ __device__ __forceinline__ float lrelu(float x, float slope) { return x > 0.f ? 
 // 0.4 M edges into 70,000 rows of a power-law relation, 8 heads: forward 106 us, now 35 us; all sweeps of a 4-head
 // layer over 21 M edges 2.7 ms, now 1.75 ms.)
 enum SweepOp { SWEEP_FWD = 0, SWEEP_BWD_CSR = 1, SWEEP_BWD_CSC = 2 };
-enum Phase { PH_ALPHA = 0, PH_BWD_DST = 1, PH_BWD_SRC = 2 };
+enum Phase { PH_ALPHA = 0, PH_BWD_DST = 1 };
 
 struct SweepParams {
     const int64_t *sptr;
@@ -120,24 +120,14 @@ template <> __device__ __forceinline__ void storek<8>(float *p, const float *v)
 __device__ __forceinline__ float signed_weight(float a, bool up) { return __uint_as_float((__float_as_uint(a) & 0x7fffffffu) | (up ? 0u : 0x80000000u)); }
 
 // One edge slot e, heads k0 .. k0+KT-1.  ar: the row's score half; m, inv: shift and 1/denominator of the
-// row (unused by PH_BWD_SRC, which reads the neighbour's); acc: running sum.
+// row; acc: running sum.
 template <int KT, int PH>
 __device__ __forceinline__ void visit(const SweepParams &p, int64_t e, int k0, const float *ar, const float *m,
                                       const float *inv, float *acc)
 {
     const int64_t id = p.sidx[e];
     float x[KT];
-    float mv[KT], iv[KT], dv[KT];
-    if (PH == PH_BWD_SRC) {
-        const float4 *pk = reinterpret_cast<const float4 *>(p.nbr_pack) + id * p.K + k0;
-#pragma unroll
-        for (int k = 0; k < KT; ++k) {
-            const float4 t = pk[k];
-            x[k] = t.x; mv[k] = t.y; iv[k] = t.z; dv[k] = t.w;
-        }
-    } else {
-        loadk<KT>(p.nbr_a + id * p.K + k0, x);
-    }
+    loadk<KT>(p.nbr_a + id * p.K + k0, x);
     float a[KT], gt[KT];
 #pragma unroll
     for (int k = 0; k < KT; ++k) {
@@ -146,17 +136,12 @@ __device__ __forceinline__ void visit(const SweepParams &p, int64_t e, int k0, c
         if (PH == PH_ALPHA) {
             a[k] = expf(sc - m[k]) * inv[k];
             if (p.sign) a[k] = signed_weight(a[k], x[k] > 0.f);
-        } else if (PH == PH_BWD_DST) {
+        } else {
             gt[k] = expf(sc - m[k]) * inv[k] * (x[k] > 0.f ? 1.f : p.slope);
             acc[k] += gt[k];
-        } else {
-            a[k] = expf(sc - mv[k]) * iv[k];
-            gt[k] = a[k] * (x[k] > 0.f ? 1.f : p.slope);
-            acc[k] = fmaf(gt[k], dv[k], acc[k]);
-            a[k] = signed_weight(a[k], x[k] > 0.f);
         }
     }
-    if (PH == PH_ALPHA || PH == PH_BWD_SRC) storek<KT>(p.alpha + e * p.K + k0, a);
+    if (PH == PH_ALPHA) storek<KT>(p.alpha + e * p.K + k0, a);
     if (PH == PH_BWD_DST && p.gate) storek<KT>(p.gate + e * p.K + k0, gt);
 }
 
@@ -259,6 +244,96 @@ __device__ __forceinline__ void fwd_row(const SweepParams &p, int64_t row, int64
     if (live && lane == 0 && p.apos) storek<KT>(p.apos + row * p.K + k0, pos);
 }
 
+// Source side of the backward: a lane has one head of a slot, so that a neighbour's terms arrive as one piece of 16 KT bytes.
+// A load instruction costs the cache lines that it touches, and a lane that loads all heads of its slot touches its line KT
+// times: this sweep over 2.1 M edges of seven relations, 8 heads, 97 -> 68 us (76 with five wavefronts per SIMD instead
+// of six); over 21 M edges, 4 heads, 495 -> 489, and 514 with the short rows one at a time.
+// U slots (j, j + step, ..) of each of R rows of n slots from e0 on, all loads in flight together; acc: the head's sums.
+template <int R, int U>
+__device__ __forceinline__ void bwd_src_slots(const SweepParams &p, const int64_t (&e0)[R], const int (&n)[R], int j, int step, int k, const float (&ar)[R],
+                                              float (&acc)[R])
+{
+    const float4 *pk = reinterpret_cast<const float4 *>(p.nbr_pack);
+    int32_t id[R][U];
+    float4 t[R][U];
+    float term[U];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (n[r] > 0) { // slots past the end repeat the last one
+#pragma unroll
+            for (int u = 0; u < U; ++u) id[r][u] = p.sidx[e0[r] + min(j + u * step, n[r] - 1)];
+        }
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (n[r] > 0) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) t[r][u] = pk[static_cast<int64_t>(id[r][u]) * p.K + k];
+        }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float x = t[r][u].x + ar[r], a = expf(lrelu(x, p.slope) - t[r][u].y) * t[r][u].z;
+            const bool given = j + u * step < n[r];
+            term[u] = given ? a * (x > 0.f ? 1.f : p.slope) * t[r][u].w : 0.f;
+            if (given) p.alpha[(e0[r] + j + u * step) * p.K + k] = signed_weight(a, x > 0.f);
+        }
+#pragma unroll
+        for (int w = U / 2; w > 0; w /= 2)
+#pragma unroll
+            for (int u = 0; u < w; ++u) term[u] += term[u + w];
+        acc[r] += term[0];
+    }
+}
+
+// n slots from e0 on, G lanes; returns the head's sum in all of them
+template <int G, int KT, int U> __device__ __forceinline__ float bwd_src_edges(const SweepParams &p, int64_t e0, int n, int lane, int k, float ar)
+{
+    constexpr int EP = G / KT;
+    const int64_t e[1] = {e0};
+    const int nn[1] = {n};
+    const float arr[1] = {ar};
+    float acc[1] = {0.f};
+    for (int j = lane / KT; j < n; j += EP * U) bwd_src_slots<1, U>(p, e, nn, j, EP, k, arr, acc);
+#pragma unroll
+    for (int off = G / 2; off >= KT; off >>= 1) acc[0] += __shfl_xor(acc[0], off, 64);
+    return acc[0];
+}
+
+// One row of it, G lanes.
+template <int G, int KT, int U> __device__ __forceinline__ void bwd_src_row(const SweepParams &p, int64_t q, bool live, int lane, int k0)
+{
+    const int64_t row = live ? p.perm[q] : 0, e0 = live ? p.sptr[q] : 0, e1 = live ? p.sptr[q + 1] : 0;
+    const int k = k0 + lane % KT;
+    const float sum = bwd_src_edges<G, KT, U>(p, e0, static_cast<int>(e1 - e0), lane, k, p.row_a[row * p.K + k]);
+    if (live && lane < KT) p.corr[row * p.K + k] = sum;
+}
+
+// Rows of up to four edges: KT lanes per row, KT rows each (q + 256 / KT i), R of them at a time.
+template <int KT> __device__ __forceinline__ void bwd_src_short(const SweepParams &p, int64_t q0, int k)
+{
+    constexpr int R = KT < 2 ? 1 : 2;
+    for (int i = 0; i < KT; i += R) {
+        int64_t row[R], e0[R];
+        int n[R];
+        float ar[R], acc[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int64_t q = q0 + (i + r) * (256 / KT), qc = min(q, p.n_rows - 1);
+            row[r] = p.perm[qc];
+            e0[r] = p.sptr[qc];
+            n[r] = q < p.n_rows ? static_cast<int>(p.sptr[qc + 1] - e0[r]) : -1;
+            acc[r] = 0.f;
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) ar[r] = p.row_a[row[r] * p.K + k];
+        bwd_src_slots<R, 4>(p, e0, n, 0, 1, k, ar, acc);
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (n[r] >= 0) p.corr[row[r] * p.K + k] = acc[r];
+    }
+}
+
 // One row: W lanes, at most W NPL edges.
 template <int W, int KT, int NPL, int OP>
 __device__ __forceinline__ void sweep_row(const SweepParams &p, int64_t q, bool live, int lane, int k0)
@@ -280,21 +355,15 @@ __device__ __forceinline__ void sweep_row(const SweepParams &p, int64_t q, bool 
     } else {
 #pragma unroll
         for (int k = 0; k < KT; ++k) acc[k] = 0.f;
-        if (OP == SWEEP_BWD_CSR) {
-            loadk<KT>(p.smax + row * p.K + k0, m);
-            loadk<KT>(p.sinv + row * p.K + k0, inv);
-            sweep_range<W, KT, PH_BWD_DST>(p, e0, e1, lane, k0, ar, m, inv, acc);
-        } else {
-            sweep_range<W, KT, PH_BWD_SRC>(p, e0, e1, lane, k0, ar, nullptr, nullptr, acc);
-        }
+        loadk<KT>(p.smax + row * p.K + k0, m);
+        loadk<KT>(p.sinv + row * p.K + k0, inv);
+        sweep_range<W, KT, PH_BWD_DST>(p, e0, e1, lane, k0, ar, m, inv, acc);
         group_sum<W, KT>(acc);
         if (live && lane == 0) {
-            if (OP == SWEEP_BWD_CSR) {
-                float d[KT];
-                loadk<KT>(p.dot + row * p.K + k0, d);
+            float d[KT];
+            loadk<KT>(p.dot + row * p.K + k0, d);
 #pragma unroll
-                for (int k = 0; k < KT; ++k) acc[k] = (acc[k] - p.dot_shift) * d[k];
-            }
+            for (int k = 0; k < KT; ++k) acc[k] = (acc[k] - p.dot_shift) * d[k];
             storek<KT>(p.corr + row * p.K + k0, acc);
         }
     }
@@ -320,8 +389,14 @@ template <int KT, int OP> __device__ __forceinline__ void sweep_hub_chunk(const 
     const int64_t row = p.perm[hub_of_chunk(p, w)];
     const int64_t e0 = c.e0, e1 = c.e0 + c.len;
     float ar[KT], acc[KT], m[KT], inv[KT];
-    loadk<KT>(p.row_a + row * p.K + k0, ar);
     float *out = p.part + (w * p.K + k0) * 3;
+    if constexpr (OP == SWEEP_BWD_CSC) {
+        const int k = k0 + lane % KT;
+        const float sum = bwd_src_edges<64, KT, KT >= 4 ? 8 : 4>(p, e0, c.len, lane, k, p.row_a[row * p.K + k]);
+        if (lane < KT) out[3 * lane] = sum;
+        return;
+    }
+    loadk<KT>(p.row_a + row * p.K + k0, ar);
     if (OP == SWEEP_FWD) {
         float x[4][KT], pos[KT];
         fwd_stats<64, KT, 4>(p, e0, static_cast<int>(e1 - e0), lane, k0, ar, x, m, acc, pos);
@@ -336,13 +411,9 @@ template <int KT, int OP> __device__ __forceinline__ void sweep_hub_chunk(const 
     } else {
 #pragma unroll
         for (int k = 0; k < KT; ++k) acc[k] = 0.f;
-        if (OP == SWEEP_BWD_CSR) {
-            loadk<KT>(p.smax + row * p.K + k0, m);
-            loadk<KT>(p.sinv + row * p.K + k0, inv);
-            sweep_range<64, KT, PH_BWD_DST>(p, e0, e1, lane, k0, ar, m, inv, acc);
-        } else {
-            sweep_range<64, KT, PH_BWD_SRC>(p, e0, e1, lane, k0, ar, nullptr, nullptr, acc);
-        }
+        loadk<KT>(p.smax + row * p.K + k0, m);
+        loadk<KT>(p.sinv + row * p.K + k0, inv);
+        sweep_range<64, KT, PH_BWD_DST>(p, e0, e1, lane, k0, ar, m, inv, acc);
         group_sum<64, KT>(acc);
         if (lane == 0) {
 #pragma unroll
@@ -359,9 +430,10 @@ template <int N> struct SweepMulti {
 };
 static_assert(sizeof(SweepMulti<kSweepMulti>) <= 3840, "kernel arguments are limited to 4 KB");
 
-// All row classes of all schedules in one launch: relation and class follow from the workgroup's index (uniform).
+// All row classes of all schedules in one launch: relation and class follow from the workgroup's index (uniform).  Six wavefronts per
+// SIMD on the source side: with seven its gathers spill.
 template <int KT, int OP, int N>
-__global__ void __launch_bounds__(256) attn_rows_kernel(SweepMulti<N> m)
+__global__ void __launch_bounds__(256, OP == SWEEP_BWD_CSC ? 6 : 1) attn_rows_kernel(SweepMulti<N> m)
 {
     int i = 0;
 #pragma unroll
@@ -375,10 +447,17 @@ __global__ void __launch_bounds__(256) attn_rows_kernel(SweepMulti<N> m)
         if (w < p.n_hub_chunks) sweep_hub_chunk<KT, OP>(p, w, lane, k0); // uniform per wavefront
     } else if (b < p.b_mid) {
         const int64_t q = p.q_wave + static_cast<int64_t>(b - p.b_wave) * 4 + (threadIdx.x >> 6);
-        if (q < p.q_mid) sweep_row<64, KT, 8, OP>(p, q, true, lane, k0);
+        if (q < p.q_mid) {
+            if constexpr (OP == SWEEP_BWD_CSC) bwd_src_row<64, KT, KT >= 4 ? 8 : 4>(p, q, true, lane, k0);
+            else sweep_row<64, KT, 8, OP>(p, q, true, lane, k0);
+        }
     } else if (b < p.b_short) {
         const int64_t q = p.q_mid + static_cast<int64_t>(b - p.b_mid) * 32 + (threadIdx.x >> 3);
-        sweep_row<8, KT, 4, OP>(p, q, q < p.q_short, threadIdx.x & 7, k0); // every lane of the wavefront takes part in the sums
+        // every lane of the wavefront takes part in the sums
+        if constexpr (OP == SWEEP_BWD_CSC) bwd_src_row<8, KT, KT >= 4 ? 8 : 4>(p, q, q < p.q_short, threadIdx.x & 7, k0);
+        else sweep_row<8, KT, 4, OP>(p, q, q < p.q_short, threadIdx.x & 7, k0);
+    } else if constexpr (OP == SWEEP_BWD_CSC) {
+        bwd_src_short<KT>(p, p.q_short + static_cast<int64_t>(b - p.b_short) * 256 + threadIdx.x / KT, k0 + threadIdx.x % KT);
     } else {
         const int64_t q = p.q_short + static_cast<int64_t>(b - p.b_short) * 256 + threadIdx.x;
         if (q < p.n_rows) sweep_row<1, KT, 4, OP>(p, q, true, 0, k0);
