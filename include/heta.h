@@ -278,7 +278,8 @@ heta_status heta_project_wgrad_batch(heta_graph *g, int64_t n_rows, int32_t n, c
  * heta_project_wgrad_multi: dW[s] = ins[s]^T . gouts[s] (d_in[s] x d_out[i]) over n_rows[i] rows; workspace and
  *   gout_two_terms as in heta_cross_rel_project_wgrad.
  * Items that a launch of their own would leave part of the chip idle share one: they run concurrently, so no two outputs may
- * overlap (checked).  g: handle whose packing buffer (and workspace) the call uses.  All arrays are HOST arrays; shapes,
+ * overlap (checked).  What shares a launch does not change a result: an item's is, bit for bit, that of a call of its own.
+ * g: handle whose packing buffer (and workspace) the call uses.  All arrays are HOST arrays; shapes,
  * dtypes and errors as in the calls above, detected before anything is launched.  n = 0 is a no-op. */
 heta_status heta_project_multi(heta_graph *g, int32_t n, const int32_t *first, const int64_t *n_rows, int32_t sum, const void *const *ins,
                                heta_dtype in_dt, const int64_t *ld_in, const int32_t *depth, const void *const *Ws, heta_dtype w_dt,

@@ -42,6 +42,11 @@ struct GemmCall {
     const float *row_scale;
 };
 
+// How an fp32 product (forward, input gradient) is formed, by its size.  The form decides the order in which the terms of its
+// sums are added, and which rows get the negative product: the last bits of the result.  Each call's follows from that call
+// alone, and only calls whose form comes to the same bits share a launch, so that no result depends on what shares its launch.
+enum ProductForm { kFormNone = 0, kFormSmall, kFormModerate, kFormPacked };
+
 struct GemmParams {
     GemmSeg seg[kMaxLaunchSeg];
     int n_seg;
@@ -57,6 +62,7 @@ struct GemmParams {
     int64_t k_per_split; // multiple of BK
     int n_split;
     int as_packed;       // fp32 product of a call whose larger launches pack B: the same order of sums where this one does not
+    int form;            // how an fp32 product is formed (ProductForm), 0 for others
     int both_signs;      // B3 holds the terms of B and, behind them, those of -B (input gradients)
     int partial;         // write raw partial products [split][M][ldc] (ldc = N) instead of the output
     int64_t mt, nt;      // tile counts (maximum over the segments in batch mode)
@@ -275,8 +281,10 @@ extern bool g_f32_native; // test switch, see heta_test_hooks.h
 // (trans = 1, an input gradient: the terms of B and behind them those of -B, see flip_signs); zero beyond K and N.
 size_t split3_weight_bytes(int64_t K, int64_t N, int trans);
 heta_status pack_split3_weights(GemmParams &p, int trans, void *out, hipStream_t st);
-// whether an fp32 product is small enough to split both operands in its kernel instead of packing one beforehand
-bool f32_product_unpacked(const GemmParams &p);
+// the form of one call's fp32 product: all but kFormPacked split both operands in their kernel instead of packing one beforehand
+ProductForm f32_product_form(const GemmParams &p);
+double product_steps(const GemmParams &p); // of 64 x 64 x 16
+constexpr double kUnpackedSteps = 16384;
 int wgrad_tile_rows(const GemmParams &p);
 // whether the direct pipeline takes the launch (alignment, extents)
 bool gemm_direct_takes(const GemmParams &p, heta_dtype a_dt, heta_dtype b_dt);

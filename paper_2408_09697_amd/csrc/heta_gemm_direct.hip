@@ -760,7 +760,8 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
     const int64_t n0 = static_cast<int64_t>(rest % call.nt) * BN;
     const int64_t m0 = static_cast<int64_t>(p.partial ? rest / call.nt : outer) * BM;
     const int64_t split = p.partial ? outer : 0;
-    const bool negated = (X3_FLIP || (W3 && p.both_signs)) && (outer & 1); // uniform
+    // packed products of at most 64 columns: every 256 rows, as products of 256 x 64 tiles; the others every row block
+    const bool negated = (X3_FLIP || (W3 && p.both_signs)) && ((W3 && MI == 1 ? outer >> 1 : outer) & 1); // uniform
     const uint32_t flip = negated ? 0x80000000u : 0u;
     const GemmSeg &out_seg = p.seg[s0];
     if (m0 >= out_seg.M || n0 >= out_seg.N) return; // uniform per workgroup
@@ -1075,13 +1076,18 @@ static bool a_shared(const GemmParams &p)
 // 13.1 (6,000 steps of 64 x 64 x 16), three of 24,000 x 128 x 64 21.9 and 18.0 (9,000), 100,000 x 64 x 100 27.7 and 24.0
 // (12,500), two of 60,000 x 128 x 64 27.0 and 24.1 (15,000), two of 70,000 30.9 and 27.5 (17,500), 20,000 x 512 x 100 33.4
 // and 32.9 (20,000), two of 160,000 x 24 x 100 40.5 and 46.4 (20,000), 48,000 x 128 x 256 29.7 and 33.4 (24,000).
-bool f32_product_unpacked(const GemmParams &p)
+ProductForm f32_product_form(const GemmParams &p)
 {
-    if (p.partial) return false;
+    if (p.partial) return kFormNone;
+    return gemm_direct_small(p) ? kFormSmall : product_steps(p) <= kUnpackedSteps ? kFormModerate : kFormPacked;
+}
+
+double product_steps(const GemmParams &p)
+{
     double steps = 0;
     for (int s = 0; s < p.n_seg; ++s)
         steps += static_cast<double>((p.seg[s].M + 63) / 64) * static_cast<double>((p.seg[s].N + 63) / 64) * static_cast<double>((p.seg[s].K + 15) / 16);
-    return steps <= 16384 || gemm_direct_small(p);
+    return steps;
 }
 
 static int64_t split3_octets(int64_t K) { return (K + 15) / 16 * 2; }
@@ -1216,10 +1222,12 @@ heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, 
     // Fewer than a hundred 128 x 128 tiles (the projections of a sampled mini-batch block: a few thousand rows):
     // every tile is a serial chain of MFMAs on one CU while most CUs idle.  64 x 64 tiles (four wavefronts of one
     // accumulator each) cut the chain to a quarter and put four times as many CUs to work.
-    const bool small = gemm_direct_small(p), unpacked = f32_product_unpacked(p);
+    const bool f32 = a_dt == HETA_F32 && b_dt == HETA_F32;
+    const int form = f32 && !p.form ? f32_product_form(p) : p.form;
+    const bool small = f32 ? form == kFormSmall : gemm_direct_small(p), unpacked = form == kFormSmall || form == kFormModerate;
     const bool octets = b_dt == HETA_BF16 && p.seg[0].B3; // all segments of a launch are packed or none
     *handled = true;
-    if (a_dt == HETA_F32 && b_dt == HETA_F32 && !g_f32_native && !a_rc && !unpacked && !p.partial) {
+    if (f32 && !g_f32_native && !a_rc && !unpacked && !p.partial) {
         // B already packed as three bf16 terms by the caller (the weights of a forward or input-gradient product):
         // half the splitting arithmetic leaves the k loop.
         bool packed = true;
@@ -1233,7 +1241,7 @@ heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, 
         // MFMA but two workgroups per CU: 2.25)
         if (packed) return launch_direct<bf16_t, float, false, true, float, false, true, 2, 16, 2, 3, false, 2, 2, 2, 2>(p, st, name, bytes, flops);
     }
-    if (a_dt == HETA_F32 && b_dt == HETA_F32 && !g_f32_native) {
+    if (f32 && !g_f32_native) {
         // fp32 operands, fp32-exact products as six bf16 MFMA terms each (see split3_pair), fp32 accumulation
         // 128 x 128 tiles (four wavefronts, three workgroups per CU) also where the output is wider: the
         // 128 x 256 tile's eight wavefronts need more than the 128 registers that two workgroups per CU allow,

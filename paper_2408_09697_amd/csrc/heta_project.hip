@@ -206,8 +206,9 @@ struct SplitSegs { // passed by value
     const float *part[kMaxLaunchSeg];
     float *out[kMaxLaunchSeg];
     int64_t M[kMaxLaunchSeg], ldo[kMaxLaunchSeg];
-    int32_t N[kMaxLaunchSeg], n_split[kMaxLaunchSeg];
-    float beta[kMaxLaunchSeg];
+    int32_t N[kMaxLaunchSeg], n_split[kMaxLaunchSeg], chains[kMaxLaunchSeg];
+    float beta;
+    int n;
     unsigned first; // first workgroup of this launch
 };
 // NW wavefronts per 64 elements: wavefront w adds the splits w, w + NW, ... (eight loads in flight), the NW sums are
@@ -215,15 +216,15 @@ struct SplitSegs { // passed by value
 // chain on a few dozen workgroups, 8,192 elements x 688 splits took 17.4 us, now 8); one, four of them in a workgroup,
 // below 32 splits of 196,608 elements and more, which are three wavefronts per SIMD by themselves (whole weight
 // gradients with four and with one: three of 2,000 rows, 768 x 1,024, bf16 65.7 / 57.5 us; one of 9,000 rows 49.0 / 45.0,
-// of 110,000 rows, 789 x 256, 107.8 / 100.4; of 500 rows, 128 x 256, fp32 17.3 / 18.2).
-template <int NW>
-__global__ void __launch_bounds__(NW == 1 ? 256 : 64 * NW) splitk_reduce_kernel(SplitSegs g)
+// of 110,000 rows, 789 x 256, 107.8 / 100.4; of 500 rows, 128 x 256, fp32 17.3 / 18.2).  The number follows from each
+// gradient's own call, whatever shares the launch: it decides the order of the sum.
+static int split_chains(int64_t n_split, int64_t out_elems) { return n_split >= 128 ? 16 : n_split >= 32 || out_elems < 196608 ? 4 : 1; }
+template <int NW> __device__ __forceinline__ void splitk_reduce(const SplitSegs &g, float (*red)[64])
 {
-    __shared__ float red[NW][64];
     const int lane = threadIdx.x & 63, w = NW == 1 ? 0 : threadIdx.x >> 6;
     const int seg = blockIdx.y, n_split = g.n_split[seg];
     const int64_t N = g.N[seg], total = g.M[seg] * N;
-    const float beta = g.beta[seg];
+    const float beta = g.beta;
     const int64_t block = static_cast<int64_t>(g.first) + blockIdx.x;
     const int64_t t = NW == 1 ? block * 256 + threadIdx.x : block * 64 + lane;
     const float *part = g.part[seg];
@@ -245,6 +246,18 @@ __global__ void __launch_bounds__(NW == 1 ? 256 : 64 * NW) splitk_reduce_kernel(
     const int64_t m = t / N, n = t % N;
     float *o = g.out[seg] + m * g.ldo[seg] + n;
     *o = (beta != 0.f) ? beta * *o + a : a;
+}
+// 16 chains each, or (256 threads) four and one
+__global__ void __launch_bounds__(1024) splitk_reduce16_kernel(SplitSegs g)
+{
+    __shared__ float red[16][64];
+    splitk_reduce<16>(g, red);
+}
+__global__ void __launch_bounds__(256) splitk_reduce_kernel(SplitSegs g)
+{
+    __shared__ float red[4][64];
+    if (g.chains[blockIdx.y] == 1) splitk_reduce<1>(g, red); // uniform
+    else splitk_reduce<4>(g, red);
 }
 
 // bf16 weight matrices as octets, out[k / 8][n][8 k-values] of B(k, n) = W[k*ldw + n] (TRANS: W[n*ldw + k]), zero beyond K
@@ -416,7 +429,7 @@ static heta_status pack_f32_weights(heta_graph *owner, GemmParams &p, int trans,
 {
     if (!owner || g_force_staged || g_f32_native || p.partial) return HETA_OK;
     p.as_packed = 1;
-    if (f32_product_unpacked(p)) return HETA_OK;
+    if (p.form != kFormPacked) return HETA_OK;
     size_t bytes = 0;
     for (int s = 0; s < p.n_seg; ++s) {
         const GemmSeg &g = p.seg[s];
@@ -544,6 +557,7 @@ static heta_status project_run(GemmParams &p, heta_dtype in_dt, heta_dtype w_dt,
 {
     if (p.n_seg == 0) return HETA_OK;
     if (in_dt == HETA_F32 && w_dt == HETA_F32) {
+        if (p.form == kFormNone) p.form = f32_product_form(p);
         heta_status pe = pack_f32_weights(pack_owner, p, transW, st);
         if (pe != HETA_OK) return pe;
     }
@@ -591,18 +605,23 @@ static bool merges(const GemmParams &p, heta_dtype a_dt, heta_dtype b_dt)
     }
     return tiles <= kMergeTiles;
 }
-// whether call `q` (both `merges`) joins the calls in `p`
-static bool joins(const GemmParams &p, const GemmParams &q)
+// Whether call `q` (both `merges`) joins the calls in `p`.  fp32 products keep the bits that each has by itself: those of
+// one form do, and forward products of the upper two, which add their terms in one order (input gradients of the two form
+// the negative product for other rows).
+static bool joins(const GemmParams &p, const GemmParams &q, int32_t transW)
 {
+    if (p.form != q.form && (transW || p.form == kFormSmall || q.form == kFormSmall)) return false;
     return std::max(1, p.n_call) < kMaxCalls && p.n_seg + q.n_seg <= kMaxLaunchSeg && p.batch == q.batch && p.out_bf16 == q.out_bf16 &&
            width_class(p) == width_class(q);
 }
-static void join(GemmParams &p, const GemmParams &q)
+static void join(GemmParams &p, const GemmParams &q, int32_t transW)
 {
     const auto call_of = [](const GemmParams &x, int first) { return GemmCall{first, x.n_seg, 0, 0, 0, 1, 0x7fffffff, x.relu, x.beta, x.row_scale}; };
     if (p.n_call == 0) p.call[p.n_call++] = call_of(p, 0);
     p.call[p.n_call++] = call_of(q, p.n_seg);
     for (int s = 0; s < q.n_seg; ++s) p.seg[p.n_seg++] = q.seg[s];
+    p.form = std::max(p.form, q.form);
+    if (p.form == kFormModerate && !transW && product_steps(p) > kUnpackedSteps) p.form = kFormPacked;
 }
 
 // dM_s = gout . W_s^T for every s: products of one depth whose outputs differ in width
@@ -747,8 +766,8 @@ static heta_status wgrad_run(heta_graph *g, const Wgrad *calls, int n_calls, het
 {
     const WgradKind kind = wgrad_kind(calls[0], in_dt);
     GemmParams p{};
-    int64_t out_elems = 0;
     int64_t n_split[kMaxCalls], split_max = 1, ws_elems = 0;
+    int chains[kMaxCalls];
     for (int c = 0; c < n_calls; ++c) {
         const Wgrad &w = calls[c];
         int64_t elems = 0;
@@ -767,7 +786,7 @@ static heta_status wgrad_run(heta_graph *g, const Wgrad *calls, int n_calls, het
         }
         const WgradSplit split = wgrad_split(w, kind, in_dt);
         n_split[c] = split.n;
-        out_elems += elems;
+        chains[c] = split_chains(split.n, elems);
         ws_elems += n_split[c] * elems;
         split_max = std::max(split_max, n_split[c]);
         p.k_per_split = split.k_tiles_each * split.k_tile;
@@ -777,42 +796,45 @@ static heta_status wgrad_run(heta_graph *g, const Wgrad *calls, int n_calls, het
     }
     heta_status e = ensure_workspace(g, static_cast<size_t>(ws_elems) * sizeof(float));
     if (e != HETA_OK) return e;
-    SplitSegs segs{};
-    int64_t total_max = 0;
-    double bytes = 0;
+    SplitSegs sums[2] = {}; // of 16 chains, of fewer
+    int64_t blocks[2] = {};
+    double bytes[2] = {};
     float *ws = static_cast<float *>(g->d_ws);
     for (int c = 0, at = 0; c < n_calls; ++c)
         for (int s = 0; s < calls[c].n_seg; ++s, ++at) {
             const int64_t total = static_cast<int64_t>(calls[c].d_in[s]) * calls[c].d_out;
             p.seg[at].C = ws;
             ws += n_split[c] * total;
-            segs.part[at] = p.seg[at].C;
-            segs.out[at] = calls[c].dW[s];
-            segs.M[at] = calls[c].d_in[s];
-            segs.ldo[at] = calls[c].ld_dw[s];
-            segs.N[at] = calls[c].d_out;
-            segs.n_split[at] = static_cast<int32_t>(n_split[c]);
-            segs.beta[at] = beta;
-            total_max = std::max(total_max, total);
-            bytes += (n_split[c] + 1.0) * total * 4.0;
+            const int k = chains[c] == 16 ? 0 : 1;
+            SplitSegs &g = sums[k];
+            g.part[g.n] = p.seg[at].C;
+            g.out[g.n] = calls[c].dW[s];
+            g.M[g.n] = calls[c].d_in[s];
+            g.ldo[g.n] = calls[c].ld_dw[s];
+            g.N[g.n] = calls[c].d_out;
+            g.n_split[g.n] = static_cast<int32_t>(n_split[c]);
+            g.chains[g.n++] = chains[c];
+            g.beta = beta;
+            blocks[k] = std::max(blocks[k], chains[c] == 1 ? (total + 255) / 256 : (total + 63) / 64);
+            bytes[k] += (n_split[c] + 1.0) * total * 4.0;
         }
     p.batch = 1;
     p.n_split = static_cast<int>(split_max);
     p.partial = 1;
     p.split_b = (gout_two_terms && in_dt == HETA_BF16) ? 1 : 0;
     if ((e = dispatch_gemm<true, true>(p, in_dt, HETA_F32, st, in_dt == HETA_F32 ? 32 : 64)) != HETA_OK) return e;
-    ProfScope prof("splitk_reduce_kernel", st, bytes, 0);
-    const int nw = split_max >= 128 ? 16 : split_max >= 32 || out_elems < 196608 ? 4 : 1;
-    const int64_t per_block = nw == 1 ? 256 : 64;
-    launch_pieces((total_max + per_block - 1) / per_block, nw == 1 ? 256 : 64 * nw, [&](unsigned first, unsigned count) {
-        segs.first = first;
-        const dim3 grid(count, (unsigned)p.n_seg);
-        const auto launch = [&](auto kernel, int threads) { hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, st, segs); };
-        if (nw == 16) launch(splitk_reduce_kernel<16>, 1024);
-        else if (nw == 4) launch(splitk_reduce_kernel<4>, 256);
-        else launch(splitk_reduce_kernel<1>, 256);
-    });
-    HETA_LAUNCH_CHECK("splitk_reduce_kernel");
+    for (int k = 0; k < 2; ++k) {
+        SplitSegs &g = sums[k];
+        if (g.n == 0) continue;
+        ProfScope prof("splitk_reduce_kernel", st, bytes[k], 0);
+        launch_pieces(blocks[k], k == 0 ? 1024 : 256, [&](unsigned first, unsigned count) {
+            g.first = first;
+            const dim3 grid(count, (unsigned)g.n);
+            if (k == 0) hipLaunchKernelGGL(splitk_reduce16_kernel, grid, dim3(1024), 0, st, g);
+            else hipLaunchKernelGGL(splitk_reduce_kernel, grid, dim3(256), 0, st, g);
+        });
+        HETA_LAUNCH_CHECK("splitk_reduce_kernel");
+    }
     return HETA_OK;
 }
 
@@ -892,6 +914,8 @@ static heta_status project_multi_impl(heta_graph *g, int32_t n, const int32_t *f
     // the outputs are written side by side
     const int64_t elt = static_cast<int64_t>(dtype_size(out_dt));
     std::vector<const GemmSeg *> written;
+    if (in_dt == HETA_F32 && w_dt == HETA_F32)
+        for (GemmParams &p : plans) p.form = f32_product_form(p);
     for (const GemmParams &p : plans)
         for (int s = 0; s < (p.batch ? p.n_seg : std::min(p.n_seg, 1)); ++s) {
             const GemmSeg &a = p.seg[s];
@@ -905,8 +929,8 @@ static heta_status project_multi_impl(heta_graph *g, int32_t n, const int32_t *f
         if (p.n_seg == 0) continue; // no rows, or joined already
         if (merges(p, in_dt, w_dt))
             for (int32_t j = i + 1; j < n; ++j)
-                if (plans[j].n_seg > 0 && merges(plans[j], in_dt, w_dt) && joins(p, plans[j])) {
-                    join(p, plans[j]);
+                if (plans[j].n_seg > 0 && merges(plans[j], in_dt, w_dt) && joins(p, plans[j], transW)) {
+                    join(p, plans[j], transW);
                     plans[j].n_seg = 0;
                 }
         heta_status e = project_run(p, in_dt, w_dt, transW, g, st, true);

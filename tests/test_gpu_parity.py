@@ -1647,6 +1647,57 @@ def test_wgrad_multi_against_fp64(rows, storage):
     hg.destroy()
 
 
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+@pytest.mark.parametrize("widths", [(64, 40), (100, 128), (200, 256)])
+def test_products_do_not_depend_on_what_shares_their_launch(widths, storage):
+    """Items of every form (small, moderate, with packed weights) together, and each by itself, bit for bit."""
+    g = torch.Generator(device="cuda").manual_seed(widths[0])
+    hg = heta.heta_graph_create([(1, 1, 0)], [(0, 0, np.zeros(2, dtype=np.int64), np.zeros(0, dtype=np.int32))])
+    dt = torch.float32 if storage == "f32" else torch.bfloat16
+    rand = lambda *shape, dtype=torch.float32: torch.randn(shape, generator=g, device="cuda").to(dtype)  # noqa: E731
+    for trans in (False, True):
+        a_dt = torch.float32 if trans else dt
+        for total in (True, False):
+            items = []
+            for i, n in enumerate([300, 9000, 50_000, 20_000, 100_000, 77]):
+                ins = [rand(n, 128, dtype=a_dt) for _ in range(1 + i % 2)]
+                Ws = [rand(*((widths[i % 2], 128) if trans else (128, (widths[i % 2] + 7) // 8 * 8)), dtype=dt)[:, :128 if trans else widths[i % 2]] for _ in ins]
+                outs = rand(n, widths[i % 2]) if total else [rand(n, widths[i % 2]) for _ in ins]
+                items.append((n, ins, Ws, outs, i % 2, float(i % 3 == 0)) if total else (n, ins, Ws, outs))
+            alone = [it[:3] + (it[3].clone() if total else [o.clone() for o in it[3]],) + it[4:] for it in items]
+            heta.heta_project_multi(hg, items, trans_w=trans, sum=total)
+            for it, one in zip(items, alone):
+                heta.heta_project_multi(hg, [one], trans_w=trans, sum=total)
+                for a, b in zip([it[3]] if total else it[3], [one[3]] if total else one[3]):
+                    assert torch.equal(a, b), (trans, total, it[0])
+    items = []
+    for n, d_in in ((90, 128), (3000, 128), (16_000, 100), (40_000, 24), (120_000, 128)):
+        items.append((n, [rand(n, d_in, dtype=dt) if dt == torch.float32 else _padded_rand(rng.stream("tests", f"share/{n}"), n, d_in, dt)],
+                      [rand(n, widths[0])], [torch.empty((d_in, widths[0]), device="cuda")]))
+    heta.heta_project_wgrad_multi(hg, items, gout_two_terms=True)
+    for n, ins, gouts, dW in items:
+        one = [torch.empty_like(w) for w in dW]
+        heta.heta_project_wgrad_batch(hg, ins, gouts, one, gout_two_terms=True)
+        assert all(torch.equal(a, b) for a, b in zip(dW, one)), n
+    hg.destroy()
+
+
+def test_packed_input_gradients_of_narrow_outputs_change_sign_every_256_rows():
+    """The row blocks that form the negative product are 256 rows high whatever the tile: one row repeated gives one result per
+    block, and the two kinds of block differ in the last bits."""
+    g = torch.Generator(device="cuda").manual_seed(3)
+    hg = heta.heta_graph_create([(1, 1, 0)], [(0, 0, np.zeros(2, dtype=np.int64), np.zeros(0, dtype=np.int32))])
+    n = 160_000  # 2,500 x 8 steps of 64 x 64 x 16: packed
+    x = torch.randn((1, 128), generator=g, device="cuda").expand(n, 128).contiguous()
+    w = torch.randn((64, 128), generator=g, device="cuda")
+    out = torch.empty((n, 64), device="cuda")
+    heta.heta_project_sum([x], [w], out, trans_w=True, graph=hg)
+    blocks = out.view(-1, 256, 64)
+    assert torch.equal(blocks, blocks[:, :1].expand_as(blocks))
+    assert torch.equal(blocks[2:], blocks[:-2]) and not torch.equal(blocks[0], blocks[1])
+    hg.destroy()
+
+
 @pytest.mark.parametrize("d,n_items", [(64, 4), (7, 3), (100, 17)])
 def test_act_bwd_multi(d, n_items):
     """Gradients of several node types behind a ReLU, vectorised or not, in one launch or (more than 16) one by one."""
