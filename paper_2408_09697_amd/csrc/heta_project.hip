@@ -372,19 +372,9 @@ static void gemm_cost(const GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, dou
     }
 }
 
-template <bool A_RC, bool B_RC>
-static heta_status dispatch_gemm(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, hipStream_t st, int bk = 32)
+// one call by the register-staged kernel
+template <bool A_RC, bool B_RC> static heta_status staged_gemm(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, hipStream_t st, int bk)
 {
-    if (!g_force_staged) {
-        // the direct-to-LDS pipeline takes every launch whose operands have 16-byte rows
-        double bytes, flops;
-        gemm_cost(p, a_dt, b_dt, &bytes, &flops);
-        const bool f32 = a_dt == HETA_F32 && b_dt == HETA_F32;
-        const char *name = f32 ? (p.partial ? "gemm_wgrad_f32" : "gemm_f32") : (p.partial ? "gemm_wgrad_bf16" : "gemm_bf16");
-        bool handled = false;
-        heta_status e = launch_gemm_direct(p, a_dt, b_dt, A_RC, B_RC, st, name, bytes, flops, &handled);
-        if (e != HETA_OK || handled) return e;
-    }
     int64_t n_max = 0;
     bool vec = true; // 128-bit loads need every operand of the launch to qualify
     for (int s = 0; s < p.n_seg; ++s) {
@@ -402,6 +392,37 @@ static heta_status dispatch_gemm(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt
     if (a_dt == HETA_BF16 && b_dt == HETA_F32) { HETA_GEMM(bf16_t, bf16_t, float); }
     HETA_GEMM(bf16_t, bf16_t, bf16_t);
 #undef HETA_GEMM
+}
+
+template <bool A_RC, bool B_RC>
+static heta_status dispatch_gemm(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, hipStream_t st, int bk = 32)
+{
+    if (!g_force_staged) {
+        // the direct-to-LDS pipeline takes every launch whose operands have 16-byte rows
+        double bytes, flops;
+        gemm_cost(p, a_dt, b_dt, &bytes, &flops);
+        const bool f32 = a_dt == HETA_F32 && b_dt == HETA_F32;
+        const char *name = f32 ? (p.partial ? "gemm_wgrad_f32" : "gemm_f32") : (p.partial ? "gemm_wgrad_bf16" : "gemm_bf16");
+        bool handled = false;
+        heta_status e = launch_gemm_direct(p, a_dt, b_dt, A_RC, B_RC, st, name, bytes, flops, &handled);
+        if (e != HETA_OK || handled) return e;
+    }
+    if (p.n_call <= 1) return staged_gemm<A_RC, B_RC>(p, a_dt, b_dt, st, bk);
+    for (int c = 0; c < p.n_call; ++c) { // the staged kernel knows nothing of calls: one launch each
+        const GemmCall &call = p.call[c];
+        GemmParams one = p;
+        one.n_call = 0;
+        one.n_seg = call.n_seg;
+        std::copy(p.seg + call.first, p.seg + call.first + call.n_seg, one.seg);
+        one.row_scale = call.row_scale;
+        one.beta = call.beta;
+        one.relu = call.relu;
+        one.n_split = call.n_split;
+        one.k_per_split = call.n_split > 1 ? call.k_per_split : int64_t(1) << 40;
+        heta_status e = staged_gemm<A_RC, B_RC>(one, a_dt, b_dt, st, bk);
+        if (e != HETA_OK) return e;
+    }
+    return HETA_OK;
 }
 
 static bool misaligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) != 0; }
@@ -597,7 +618,8 @@ static int width_class(const GemmParams &p)
 }
 static bool merges(const GemmParams &p, heta_dtype a_dt, heta_dtype b_dt)
 {
-    if (g_force_staged || !gemm_direct_takes(p, a_dt, b_dt)) return false;
+    // (the direct pipeline has no kernel for bf16 inputs with fp32 weights)
+    if (g_force_staged || (a_dt == HETA_BF16 && b_dt == HETA_F32) || !gemm_direct_takes(p, a_dt, b_dt)) return false;
     int64_t tiles = 0;
     for (int s = 0; s < p.n_seg; ++s) {
         const int64_t t = ((p.seg[s].M + 127) / 128) * ((p.seg[s].N + 127) / 128);

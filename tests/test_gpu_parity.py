@@ -1647,6 +1647,36 @@ def test_wgrad_multi_against_fp64(rows, storage):
     hg.destroy()
 
 
+@pytest.mark.parametrize("in_dt,w_dt", [(torch.bfloat16, torch.float32), (torch.float32, torch.bfloat16), (torch.bfloat16, torch.bfloat16)])
+@pytest.mark.parametrize("pad", [0, 1])
+def test_project_multi_of_mixed_types_against_fp64(in_dt, w_dt, pad):
+    """Every pair of element types, whichever kernel takes it (pad: rows that no 16-byte load takes), items of unequal rows: sums
+    with beta and ReLU, and independent products.  The product rounds both operands to bf16; what remains is the accumulation."""
+    g = torch.Generator(device="cuda").manual_seed(11 + pad)
+    hg = heta.heta_graph_create([(1, 1, 0)], [(0, 0, np.zeros(2, dtype=np.int64), np.zeros(0, dtype=np.int32))])
+    rand = lambda n, d, dt: torch.randn((n, d + 7 & ~7 if not pad else d + 1), generator=g, device="cuda").to(dt)[:, :d]  # noqa: E731
+    wide = lambda x: x.to(torch.bfloat16).double()  # noqa: E731
+    for trans in (False, True):
+        for d_out in (40, 128, 264):
+            sums, batch, refs = [], [], []
+            for i, (n, k) in enumerate(((1000, 64), (3, 128), (70, 100), (517, 64))):
+                ins = [rand(n, k, in_dt) for _ in range(1 + i % 2)]
+                Ws = [rand(d_out, k, w_dt) if trans else rand(k, d_out, w_dt) for _ in ins]
+                each = [wide(x) @ (wide(w).t() if trans else wide(w)) for x, w in zip(ins, Ws)]
+                out = rand(n, d_out, torch.float32)
+                total = sum(each) + (out.double() if i == 2 else 0.0)
+                refs.append((each, total.relu() if i == 1 else total))
+                sums.append((n, ins, Ws, out, heta.HETA_ACT_RELU if i == 1 else heta.HETA_ACT_NONE, float(i == 2)))
+                batch.append((n, ins, Ws, [torch.full((n, d_out), 7.0, device="cuda") for _ in ins]))
+            heta.heta_project_multi(hg, sums, trans_w=trans, sum=True)
+            heta.heta_project_multi(hg, batch, trans_w=trans)
+            for one, many, (each, total) in zip(sums, batch, refs):
+                _close(one[3], total, "f32")
+                for o, r in zip(many[3], each):
+                    _close(o, r, "f32")
+    hg.destroy()
+
+
 @pytest.mark.parametrize("storage", ["f32", "bf16"])
 @pytest.mark.parametrize("widths", [(64, 40), (100, 128), (200, 256)])
 def test_products_do_not_depend_on_what_shares_their_launch(widths, storage):
