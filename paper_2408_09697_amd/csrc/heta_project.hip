@@ -781,6 +781,22 @@ static WgradSplit wgrad_split(const Wgrad &c, const WgradKind &kind, heta_dtype 
     return WgradSplit{std::max<int64_t>(1, (k_tiles + each - 1) / each), each, BK};
 }
 
+// appends the products of a call to a plan
+static void wgrad_segs(GemmParams &p, const Wgrad &w)
+{
+    for (int s = 0; s < w.n_seg; ++s) {
+        GemmSeg &q = p.seg[p.n_seg++];
+        q.A = w.ins[s];    // A[m = column of `in`][k = graph row] : r-contiguous
+        q.lda = w.ld_in[s];
+        q.B = w.gouts[s];  // B[k = graph row][n] : r-contiguous
+        q.ldb = w.ld_go[s];
+        q.M = w.d_in[s];
+        q.N = w.d_out;
+        q.K = w.n_rows;
+        q.ldc = w.d_out;
+    }
+}
+
 // The listed calls (checked; of one kind if there are several) in one launch, their partial sums in another.  Calls that
 // share a launch keep their splits: splits of one length that fill the chip together would be longer, and longer sums are
 // further from 64 bits (9.4e-7 -> 1.3e-6, layer of 21 M edges).
@@ -794,18 +810,8 @@ static heta_status wgrad_run(heta_graph *g, const Wgrad *calls, int n_calls, het
         const Wgrad &w = calls[c];
         int64_t elems = 0;
         const int first = p.n_seg;
-        for (int s = 0; s < w.n_seg; ++s) {
-            GemmSeg &q = p.seg[p.n_seg++];
-            q.A = w.ins[s];    // A[m = column of `in`][k = graph row] : r-contiguous
-            q.lda = w.ld_in[s];
-            q.B = w.gouts[s];  // B[k = graph row][n] : r-contiguous
-            q.ldb = w.ld_go[s];
-            q.M = w.d_in[s];
-            q.N = w.d_out;
-            q.K = w.n_rows;
-            q.ldc = w.d_out;
-            elems += q.M * q.N;
-        }
+        wgrad_segs(p, w);
+        for (int s = first; s < p.n_seg; ++s) elems += p.seg[s].M * p.seg[s].N;
         const WgradSplit split = wgrad_split(w, kind, in_dt);
         n_split[c] = split.n;
         chains[c] = split_chains(split.n, elems);
@@ -987,7 +993,13 @@ static heta_status wgrad_multi_impl(heta_graph *g, int32_t n, const int32_t *fir
     // calls of 10^4 to 10^6 rows, 128 x 256, 1.34 ms together and 1.13 one by one; four of 900 to 110,000 rows, 128 x 64, 76 us
     // together and 112).  Calls without rows leave zeros and go alone.
     const auto shares = [&](const Wgrad &c, const WgradKind &kind) {
-        return (kind.bf16_direct || kind.f32_terms) && c.n_rows > 0 && wgrad_split(c, kind, in_dt).k_tiles_each <= kMergeKTiles;
+        if (!(kind.bf16_direct || kind.f32_terms) || c.n_rows == 0) return false;
+        const WgradSplit split = wgrad_split(c, kind, in_dt);
+        GemmParams p{};
+        wgrad_segs(p, c);
+        p.n_split = static_cast<int>(split.n);
+        p.k_per_split = split.k_tiles_each * split.k_tile;
+        return split.k_tiles_each <= kMergeKTiles && gemm_direct_takes(p, in_dt, HETA_F32);
     };
     std::vector<char> done(n, 0);
     for (int32_t i = 0; i < n; ++i) {

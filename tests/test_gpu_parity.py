@@ -1678,6 +1678,33 @@ def test_project_multi_of_mixed_types_against_fp64(in_dt, w_dt, pad):
 
 
 @pytest.mark.parametrize("storage", ["f32", "bf16"])
+def test_wgrad_multi_of_rows_far_apart(storage):
+    """Rows 8 MB apart (columns of a very wide matrix), which the direct pipeline does not take, beside ordinary ones of other
+    split counts: each the bits of its own call."""
+    g = torch.Generator(device="cuda").manual_seed(5)
+    hg = heta.heta_graph_create([(1, 1, 0)], [(0, 0, np.zeros(2, dtype=np.int64), np.zeros(0, dtype=np.int32))])
+    dt = torch.float32 if storage == "f32" else torch.bfloat16
+    far = torch.empty((140, 1 << 21), device="cuda")
+    rand = lambda n, d, dtype=torch.float32: torch.randn((n, d), generator=g, device="cuda").to(dtype)  # noqa: E731
+    items = []
+    for n, wide in ((2000, False), (140, True), (300, False), (33, True)):
+        go = rand(n, 128)
+        if wide:
+            at = 256 * len(items)
+            far[:n, at:at + 128] = go
+            go = far[:n, at:at + 128]
+        items.append((n, [rand(n, 64, dt)], [go], [torch.full((64, 128), 7.0, device="cuda")]))
+    heta.heta_project_wgrad_multi(hg, items, gout_two_terms=True)
+    for n, ins, gouts, dW in items:
+        one = [torch.empty_like(dW[0])]
+        heta.heta_project_wgrad_batch(hg, ins, gouts, one, gout_two_terms=True)
+        assert torch.equal(one[0], dW[0]), n
+        ref = ins[0].double().t() @ gouts[0].double()
+        assert float((dW[0].double() - ref).abs().max()) <= 1e-4 * float(ref.abs().max())  # two bf16 terms: 2^-16 of every product
+    hg.destroy()
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
 @pytest.mark.parametrize("widths", [(64, 40), (100, 128), (200, 256)])
 def test_products_do_not_depend_on_what_shares_their_launch(widths, storage):
     """Items of every form (small, moderate, with packed weights) together, and each by itself, bit for bit."""
