@@ -256,8 +256,9 @@ heta_status heta_rel_project_wgrad(heta_graph *g, int32_t rel, const void *in, h
  *   heta_cross_rel_project_wgrad.
  * Pointer and size arrays are HOST arrays of n entries; shapes and dtypes as in heta_project.
  * g (heta_project_batch, heta_project_sum): optional (NULL allowed) handle whose packing buffer the call may use
- *   to rewrite the weights into the form its kernel reads fastest (fp32 weights as three bf16 terms, bf16
- *   weights as [k / 8][column][8 k-values]), on the same terms as heta_cross_rel_project; the result does not depend on it beyond rounding order. */
+ *   to rewrite the weights into the form its kernel reads fastest (fp32 weights as three bf16 terms; bf16
+ *   weights as [k / 8][column][8 k-values], but not with transW), on the same terms as heta_cross_rel_project; the
+ *   result does not depend on it beyond rounding order. */
 heta_status heta_project_batch(heta_graph *g, int64_t n_rows, int32_t n, const void *const *ins, heta_dtype in_dt, const int64_t *ld_in,
                                const int32_t *d_in, const void *const *Ws, heta_dtype w_dt, const int64_t *ld_w,
                                int32_t d_out, int32_t transW, void *const *outs, heta_dtype out_dt,
@@ -279,7 +280,7 @@ heta_status heta_project_wgrad_batch(heta_graph *g, int64_t n_rows, int32_t n, c
  *   gout_two_terms as in heta_cross_rel_project_wgrad.
  * Items that a launch of their own would leave part of the chip idle share one: they run concurrently, so no two outputs may
  * overlap (checked).  What shares a launch does not change a result: an item's is, bit for bit, that of a call of its own.
- * g: handle whose packing buffer (and workspace) the call uses.  All arrays are HOST arrays; shapes,
+ * g: handle whose packing buffer (also for transposed bf16 weights) and workspace the call uses.  All arrays are HOST arrays; shapes,
  * dtypes and errors as in the calls above, detected before anything is launched.  n = 0 is a no-op. */
 heta_status heta_project_multi(heta_graph *g, int32_t n, const int32_t *first, const int64_t *n_rows, int32_t sum, const void *const *ins,
                                heta_dtype in_dt, const int64_t *ld_in, const int32_t *depth, const void *const *Ws, heta_dtype w_dt,

@@ -571,8 +571,9 @@ static heta_status project_plan(GemmParams &p, int64_t n_rows, int n_seg, const 
     return HETA_OK;
 }
 
-// the planned call, or the calls merged into one plan.  pack_bwd: whether transposed bf16 weights may go through the packing
-// buffer too (calls that never used it for them may be overlapped by their callers)
+// The planned call, or the calls merged into one plan.  pack_bwd: whether transposed bf16 weights may go through the packing
+// buffer too.  heta_project_multi only: callers of the single calls may run those on several streams or capture the first
+// one, neither of which a shared buffer that grows allows.
 static heta_status project_run(GemmParams &p, heta_dtype in_dt, heta_dtype w_dt, int32_t transW, heta_graph *pack_owner, hipStream_t st,
                                bool pack_bwd)
 {
@@ -595,13 +596,12 @@ static heta_status project_impl(int64_t n_rows, int n_seg, const void *const *in
                                 const int32_t *d_in, const void *const *Ws, heta_dtype w_dt, const int64_t *ld_w,
                                 int32_t d_out, int32_t transW, const float *row_scale, int relu, void *out,
                                 int64_t ld_out, float beta, hipStream_t st, const char *who, heta_graph *pack_owner = nullptr,
-                                heta_dtype out_dt = HETA_F32, void *const *outs = nullptr, const int64_t *ld_outs = nullptr,
-                                bool pack_bwd = true)
+                                heta_dtype out_dt = HETA_F32, void *const *outs = nullptr, const int64_t *ld_outs = nullptr)
 {
     GemmParams p;
     heta_status e = project_plan(p, n_rows, n_seg, ins, in_dt, ld_in, d_in, Ws, w_dt, ld_w, d_out, transW, row_scale, relu, out, ld_out, beta, who,
                                  out_dt, outs, ld_outs);
-    return e == HETA_OK ? project_run(p, in_dt, w_dt, transW, pack_owner, st, pack_bwd) : e;
+    return e == HETA_OK ? project_run(p, in_dt, w_dt, transW, pack_owner, st, false) : e;
 }
 
 // ---- several calls in one launch -------------------------------------------------------------------------------------
@@ -1063,7 +1063,7 @@ heta_status heta_rel_project(heta_graph *g, int32_t rel, const void *in, heta_dt
     if (rel < 0 || rel >= (int32_t)g->rels.size())
         return fail(HETA_ERR_INVALID_ARG, "heta_rel_project: relation %d out of range", rel);
     return project_impl(g->rels[rel].n_dst, 1, &in, in_dt, &ld_in, &d_in, &W, w_dt, &ld_w, d_out, transW, row_scale, 0,
-                        out, ld_out, beta, as_stream(hip_stream), "heta_rel_project", g, out_dt, nullptr, nullptr, false);
+                        out, ld_out, beta, as_stream(hip_stream), "heta_rel_project", g, out_dt);
 }
 
 heta_status heta_rel_project_wgrad(heta_graph *g, int32_t rel, const void *in, heta_dtype in_dt,

@@ -1603,8 +1603,8 @@ def test_project_multi_against_fp64(rows, storage):
 @pytest.mark.parametrize("n,k,d_out,n_seg", [(70_001, 1000, 33, 1), (70_001, 520, 100, 1), (130_000, 264, 65, 2), (530_000, 104, 72, 1), (70_001, 520, 200, 1),
                                              (270_000, 72, 300, 1), (70_001, 272, 257, 3), (70_001, 200, 321, 2), (1000, 40, 100, 2)])
 def test_packed_bf16_weights_against_fp64(n, k, d_out, n_seg):
-    """bf16 weights rewritten as octets: every tile that takes them, ragged rows, columns and k-values, forward and (from 48 k
-    steps of 64 x 64 x 16 on) transposed, sums and products sharing their input.  Operands exact in bf16: what remains is the
+    """bf16 weights rewritten as octets: every tile that takes them, ragged rows, columns and k-values, forward and (heta_project_multi,
+    from 48 k steps of 64 x 64 x 16 on) transposed, sums and products sharing their input.  Operands exact in bf16: what remains is the
     fp32 accumulation."""
     g = torch.Generator(device="cuda").manual_seed(n + k)
     hg = heta.heta_graph_create([(1, 1, 0)], [(0, 0, np.zeros(2, dtype=np.int64), np.zeros(0, dtype=np.int32))])
@@ -1622,6 +1622,37 @@ def test_packed_bf16_weights_against_fp64(n, k, d_out, n_seg):
         heta.heta_project_batch([xs[0]] * n_seg, Ws, outs, trans_w=trans, graph=hg)
         for o, w in zip(outs, wide):
             _close(o, xs[0].double() @ w, "f32")
+        if trans:  # the single calls leave transposed weights as they are
+            out.fill_(2.0)
+            heta.heta_project_multi(hg, [(n, xs, Ws, out, heta.HETA_ACT_NONE, 1.0)], trans_w=True, sum=True)
+            _close(out, 2.0 + sum(x.double() @ w for x, w in zip(xs, wide)), "f32")
+            outs = [o.fill_(float("nan")) for o in outs]
+            heta.heta_project_multi(hg, [(n, [xs[0]] * n_seg, Ws, outs)], trans_w=True)
+            for o, w in zip(outs, wide):
+                _close(o, xs[0].double() @ w, "f32")
+    hg.destroy()
+
+
+def test_transposed_bf16_products_take_no_buffer_of_the_handle():
+    """A first call can be captured: it allocates nothing.  Replays against the eager result."""
+    g = torch.Generator(device="cuda").manual_seed(9)
+    hg = heta.heta_graph_create([(1, 1, 0)], [(0, 0, np.zeros(2, dtype=np.int64), np.zeros(0, dtype=np.int32))])
+    n, k, d = 100_000, 128, 256  # 50,016 steps of 64 x 64 x 16
+    x = torch.randn((n, k), generator=g, device="cuda")
+    w = torch.randn((d, k), generator=g, device="cuda").to(torch.bfloat16)
+    total, each = torch.empty((n, d), device="cuda"), torch.empty((n, d), device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        heta.heta_project_sum([x], [w], total, trans_w=True, graph=hg)
+        heta.heta_project_batch([x], [w], [each], trans_w=True, graph=hg)
+    eager = torch.empty_like(total)
+    for turn in range(3):
+        x.mul_(0.5)
+        total.zero_(), each.zero_()
+        graph.replay()
+        heta.heta_project_sum([x], [w], eager, trans_w=True, graph=hg)
+        torch.cuda.synchronize()
+        assert torch.equal(total, eager) and torch.equal(each, eager), turn
     hg.destroy()
 
 
