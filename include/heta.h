@@ -17,7 +17,8 @@
  * Conventions for every call
  *   - "device" pointers are HIP device memory of the current device; "host" pointers are
  *     ordinary process memory.  The library never takes ownership of a caller's buffer and
- *     never frees one.  It owns only heta_graph handles and what hangs off them.
+ *     never frees one.  It owns heta_graph handles, what hangs off them, and the scratch that it recycles
+ *     (heta_scratch_release).
  *   - Matrices are row-major with a leading dimension `ld` counted in ELEMENTS.
  *   - Every compute call is asynchronous on the given HIP stream (`hip_stream` is a
  *     hipStream_t passed as void*, NULL = the default stream) and performs no hidden
@@ -116,6 +117,10 @@ heta_status heta_graph_create_batch(int32_t n_graphs, const heta_ntype *const *n
                                     const heta_relation *const *rels, const int32_t *n_rels, uint32_t flags,
                                     heta_graph **out);
 heta_status heta_graph_destroy(heta_graph *g); /* NULL is accepted; synchronises the device */
+/* The library recycles the device blocks of its scratch, workspaces and small handles: those released stay with it for the
+ * next call, at most 1 GiB per device while a handle is alive, and 256 MiB in blocks of at most 16 MiB afterwards.  This
+ * gives all that lie idle on the current device back to it (when the caller's own allocator has run out, for instance). */
+heta_status heta_scratch_release(void);
 /* Device bytes the handle holds for index data (adjacency in both directions, schedules, 1/deg);
  * arrays shared through reverse_of count once. */
 heta_status heta_graph_index_bytes(const heta_graph *g, int64_t *bytes);

@@ -24,7 +24,7 @@ HETA_SUM, HETA_MEAN = 0, 1
 HETA_ACT_NONE, HETA_ACT_RELU = 0, 1
 HETA_PTRS_ON_DEVICE = 1
 
-EXPORTS = ["heta_graph_create", "heta_graph_create_batch", "heta_graph_destroy", "heta_graph_get_csc", "heta_graph_get_degrees",
+EXPORTS = ["heta_graph_create", "heta_graph_create_batch", "heta_graph_destroy", "heta_scratch_release", "heta_graph_get_csc", "heta_graph_get_degrees",
            "heta_feature_gather", "heta_check_ids", "heta_rel_aggregate_fwd", "heta_rel_aggregate_bwd",
            "heta_rel_aggregate_fwd_multi", "heta_rel_aggregate_fwd_multi_act", "heta_rel_aggregate_bwd_multi",
            "heta_project", "heta_rel_project", "heta_rel_project_wgrad", "heta_cross_rel_reduce",
@@ -342,6 +342,11 @@ def heta_graph_get_csc(g: Graph, rel: int):
     row = np.zeros(n_e, dtype=np.int32)
     _check(load_library().heta_graph_get_csc(g.handle, rel, colptr.ctypes.data, row.ctypes.data))
     return colptr, row
+
+
+def heta_scratch_release() -> None:
+    """Gives the device blocks that the library keeps for its next calls, and that lie idle, back to the current device."""
+    _check(load_library().heta_scratch_release())
 
 
 def heta_graph_index_bytes(g: Graph) -> int:

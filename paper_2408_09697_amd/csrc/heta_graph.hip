@@ -52,12 +52,14 @@ heta_status fail(heta_status st, const char *fmt, ...)
 // iteration; each hipMalloc / hipFree pair costs tens of microseconds, hundreds from some 100 MB on, and hipFree waits for
 // the device.  Blocks of up to 256 MiB (the partial weight gradients of two blocks of 4,096 seeds, 768 x 1,024: 30 to 130 MB)
 // are rounded up to a power of two, above 16 MiB to a quarter of one, and kept on a free list per (device, size) when
-// released, up to 1 GiB in total, past which those released longest ago go back to the device (kept instead, they left no
+// released, up to 1 GiB per device, past which those released longest ago go back to the device (kept instead, they left no
 // room for what follows them: training iterations of 768 columns 1,040 us, after layers over larger graphs 1,330); larger
-// ones go straight to hipMalloc / hipFree.  The whole list goes back when an allocation fails.  A block must be idle when it
-// is released (the callers synchronise first).
+// ones go straight to hipMalloc / hipFree.  With the process's last handle go the blocks past 16 MiB and what exceeds 256 MiB
+// per device: what handles that come and go one at a time live on.  All of a device's go when an allocation fails, and by
+// heta_scratch_release.  A block must be idle when it is released (the callers synchronise first).
 namespace {
 constexpr size_t kPoolMaxBlock = size_t(256) << 20, kPoolMaxCached = size_t(1) << 30;
+constexpr size_t kPoolIdleBlock = size_t(16) << 20, kPoolIdleCached = size_t(256) << 20; // without a handle
 std::mutex g_pool_mu;
 std::unordered_map<void *, std::pair<int, size_t>> g_pool_blocks;     // live pooled block -> (device, size class)
 struct FreeBlock {
@@ -65,32 +67,52 @@ struct FreeBlock {
     unsigned long long released; // by the pool's own count of releases
 };
 std::map<std::pair<int, size_t>, std::vector<FreeBlock>> g_pool_free; // every list in order of release
-size_t g_pool_cached = 0;
+std::map<int, size_t> g_pool_cached; // bytes on a device's free lists
 unsigned long long g_pool_releases = 0;
+std::atomic<int64_t> g_handles{0};
 
 size_t pool_class(size_t bytes)
 {
     size_t cls = 256;
     while (cls < bytes) cls <<= 1;
-    if (cls <= size_t(16) << 20) return cls;
+    if (cls <= kPoolIdleBlock) return cls;
     const size_t step = cls / 8; // a quarter of the power of two below
     return (bytes + step - 1) / step * step;
 }
 
-// everything on the current device's free lists back to the device
-void pool_give_back(int dev)
+// Takes from a device's free lists the blocks of more than `largest` bytes, then those released longest ago until at most
+// `most` bytes are left: for the caller to free.  With the lock held.
+void pool_evict(int dev, size_t largest, size_t most, std::vector<void *> &out)
 {
-    std::vector<void *> blocks;
+    const auto first = g_pool_free.lower_bound({dev, 0}), end = g_pool_free.lower_bound({dev + 1, 0});
+    size_t &cached = g_pool_cached[dev];
+    const auto take_oldest = [&](decltype(g_pool_free)::iterator f) {
+        out.push_back(f->second.front().p);
+        g_pool_blocks.erase(f->second.front().p);
+        cached -= f->first.second;
+        f->second.erase(f->second.begin());
+    };
+    for (auto f = first; f != end; ++f)
+        while (f->first.second > largest && !f->second.empty()) take_oldest(f);
+    while (cached > most) {
+        auto oldest = end;
+        for (auto f = first; f != end; ++f)
+            if (!f->second.empty() && (oldest == end || f->second.front().released < oldest->second.front().released)) oldest = f;
+        take_oldest(oldest);
+    }
+}
+
+// A device's free lists (dev < 0: every device's) down to these bounds.
+void pool_give_back(int dev, size_t largest, size_t most)
+{
+    std::vector<void *> back;
     {
         std::lock_guard<std::mutex> lk(g_pool_mu);
-        for (auto it = g_pool_free.lower_bound({dev, 0}); it != g_pool_free.end() && it->first.first == dev; it = g_pool_free.erase(it))
-            for (const FreeBlock &b : it->second) {
-                blocks.push_back(b.p);
-                g_pool_blocks.erase(b.p);
-                g_pool_cached -= it->first.second;
-            }
+        if (dev >= 0) pool_evict(dev, largest, most, back);
+        else
+            for (const auto &d : g_pool_cached) pool_evict(d.first, largest, most, back);
     }
-    for (void *p : blocks) (void)hipFree(p);
+    for (void *p : back) (void)hipFree(p);
 }
 } // namespace
 
@@ -109,14 +131,14 @@ hipError_t scratch_alloc(void **out, size_t bytes)
             if (!it->second.empty()) {
                 *out = it->second.back().p;
                 it->second.pop_back();
-                g_pool_cached -= it->first.second;
+                g_pool_cached[dev] -= it->first.second;
                 return hipSuccess;
             }
     }
     e = hipMalloc(out, cls);
     if (e == hipErrorOutOfMemory) {
         (void)hipGetLastError();
-        pool_give_back(dev);
+        pool_give_back(dev, 0, 0);
         e = hipMalloc(out, cls);
     }
     if (e != hipSuccess || !pooled) return e;
@@ -135,18 +157,18 @@ void scratch_free(void *p)
         if (it == g_pool_blocks.end()) {
             back.push_back(p);
         } else {
-            const size_t cls = it->second.second; // at most kPoolMaxBlock: there is room for it once others have gone
-            while (g_pool_cached + cls > kPoolMaxCached) {
-                auto oldest = g_pool_free.end();
-                for (auto f = g_pool_free.begin(); f != g_pool_free.end(); ++f)
-                    if (!f->second.empty() && (oldest == g_pool_free.end() || f->second.front().released < oldest->second.front().released)) oldest = f;
-                back.push_back(oldest->second.front().p);
-                g_pool_blocks.erase(oldest->second.front().p);
-                g_pool_cached -= oldest->first.second;
-                oldest->second.erase(oldest->second.begin());
+            const int dev = it->second.first;
+            const size_t cls = it->second.second;
+            const bool live = g_handles > 0;
+            const size_t largest = live ? kPoolMaxBlock : kPoolIdleBlock;
+            if (cls > largest) {
+                back.push_back(p);
+                g_pool_blocks.erase(it);
+            } else { // there is room for it once others have gone
+                pool_evict(dev, largest, (live ? kPoolMaxCached : kPoolIdleCached) - cls, back);
+                g_pool_free[it->second].push_back({p, g_pool_releases++});
+                g_pool_cached[dev] += cls;
             }
-            g_pool_free[it->second].push_back({p, g_pool_releases++});
-            g_pool_cached += cls;
         }
     }
     for (void *q : back) (void)hipFree(q);
@@ -408,6 +430,7 @@ static void destroy(heta_graph *g)
     scratch_free(g->d_pack);
     (void)hipFree(g->d_attn);
     delete g;
+    if (--g_handles == 0) pool_give_back(-1, kPoolIdleBlock, kPoolIdleCached);
 }
 
 // Host-only checks of one relation's arguments and CSR; touches no device.
@@ -985,6 +1008,7 @@ static heta_status new_graph(const heta_ntype *ntypes, int32_t n_ntypes, heta_gr
         delete g;
         return st;
     }
+    ++g_handles;
     *out = g;
     return HETA_OK;
 }
@@ -1123,6 +1147,18 @@ heta_status heta_ingest_force(int32_t mode)
 heta_status heta_graph_destroy(heta_graph *g)
 {
     destroy(g);
+    return HETA_OK;
+}
+
+heta_status heta_scratch_release(void)
+{
+    int dev = 0;
+    HETA_HIP(hipGetDevice(&dev));
+    try {
+        pool_give_back(dev, 0, 0);
+    } catch (...) { // the list of what is to be freed
+        return fail(HETA_ERR_OOM, "heta_scratch_release: host allocation failed");
+    }
     return HETA_OK;
 }
 

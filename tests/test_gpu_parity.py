@@ -1786,6 +1786,29 @@ def test_packed_input_gradients_of_narrow_outputs_change_sign_every_256_rows():
     hg.destroy()
 
 
+def test_scratch_release_gives_recycled_blocks_back():
+    """Workspaces of destroyed handles stay with the library for the next one, until they are asked back."""
+    x, go = torch.randn((60_000, 768), device="cuda"), torch.randn((60_000, 1024), device="cuda")
+    dW = torch.empty((768, 1024), device="cuda")
+
+    def handles(n):
+        hgs = []
+        for _ in range(n):
+            hgs.append(heta.heta_graph_create([(1, 1, 0)], [(0, 0, np.zeros(2, dtype=np.int64), np.zeros(0, dtype=np.int32))]))
+            heta.heta_project_wgrad_batch(hgs[-1], [x], [go], [dW])
+        free = torch.cuda.mem_get_info()[0]
+        for hg in hgs:
+            hg.destroy()
+        return free
+
+    handles(1)  # what the first call loads stays
+    heta.heta_scratch_release()
+    before = torch.cuda.mem_get_info()[0]
+    assert before - handles(3) >= 3 * dW.numel() * 4  # one partial sum each at least
+    heta.heta_scratch_release()
+    assert before - torch.cuda.mem_get_info()[0] <= 4 << 20  # what the runtime keeps for itself
+
+
 @pytest.mark.parametrize("d,n_items", [(64, 4), (7, 3), (100, 17)])
 def test_act_bwd_multi(d, n_items):
     """Gradients of several node types behind a ReLU, vectorised or not, in one launch or (more than 16) one by one."""
