@@ -1448,6 +1448,15 @@ def heta_sample_hop(g: Graph, rels: Sequence[int], dst_ids: Sequence[torch.Tenso
         uniq_caps[g.rels[r][0]] += c
     uniq_caps = [min(c, g.ntypes[t][0]) for t, c in enumerate(uniq_caps)]
     n_ptr, n_uniq, n_cap = sum(sizes) + n, sum(uniq_caps), sum(caps)
+    if n_cap > 1 << 24:  # local ids by capacity would take more than 64 MB: at the sampled size, for one more wait
+        sampled = heta_sample_neighbors_batch(g, rels, dst_ids, fanout, seeds, stream)
+        of = [[i for i, r in enumerate(rels) if g.rels[r][0] == t] for t in range(n_types)]
+        sets = heta_unique_relabel_batch([[sampled[i][1] for i in items] for items in of], [nt[0] for nt in g.ntypes], stream)
+        cols = [None] * n
+        for items, (_, local) in zip(of, sets):
+            for i, l in zip(items, local):
+                cols[i] = l
+        return [rowptr for rowptr, _ in sampled], cols, [uniq for uniq, _ in sets]
     # row offsets and unique ids in one allocation, local ids in one, the global source ids in a third that goes on return
     kept = torch.empty(n_ptr + n_uniq, dtype=torch.int64, device=dev)
     local = torch.empty(max(1, n_cap), dtype=torch.int32, device=dev)
@@ -1474,6 +1483,8 @@ def heta_sample_hop(g: Graph, rels: Sequence[int], dst_ids: Sequence[torch.Tenso
     for c, used in zip(uniq_caps, n_unique):
         parts += [used, c - used]
     cut = kept.split_with_sizes(parts)
+    if n_uniq - sum(n_unique) > 1 << 21:  # as for the local ids below
+        cut = [c.clone() for c in cut[:n]] + [c.clone() if i % 2 == 0 else c for i, c in enumerate(cut[n:])]
     parts = []
     for c, used in zip(caps, counts):
         parts += [used, c - used]

@@ -311,3 +311,26 @@ def test_sample_hop_equals_its_two_calls(n_types, rels, n_nodes, n_dst, fanout):
         heta.heta_sample_hop(hg, list(range(len(rels))), bad, fanout, seeds)
     assert e.value.status == heta.HETA_ERR_INVALID_ARG
     hg.destroy()
+
+
+@pytest.mark.parametrize("n_dst,fanout", [(300_000, 64), (200_000, 40)])
+def test_memory_of_a_large_hop(n_dst, fanout):
+    """Few edges below a large fan-out: what is kept is of the sampled size, and of more than 64 MB of local ids none is taken
+    by capacity (8 bytes of global source ids per destination and fan-out are)."""
+    g = rng.stream("tests", f"hop-memory/{n_dst}")
+    n_src = 9_000_000
+    deg = g.integers(0, 4, size=n_dst)
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    hg = heta.heta_graph_create([(n_src, 4, 0), (n_dst, 4, 0)], [(0, 1, rowptr, g.integers(0, n_src, size=int(rowptr[-1]), dtype=np.int32))])
+    dst = torch.arange(n_dst, device="cuda")
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    torch.cuda.reset_peak_memory_stats()
+    before = torch.cuda.memory_allocated()
+    kept = heta.heta_sample_hop(hg, [0], [dst], fanout, [3])
+    capacity, edges = n_dst * fanout, int(rowptr[-1])
+    if capacity > 1 << 24:
+        assert torch.cuda.max_memory_allocated() - before <= 8 * capacity + 8 * (n_dst + 1) + 12 * edges + (8 << 20)
+    assert torch.cuda.memory_allocated() - before <= 8 * (n_dst + 1) + 12 * edges + (16 << 20)
+    assert kept[0][0].numel() == n_dst + 1 and int(kept[0][0][-1]) == edges == kept[1][0].numel()
+    hg.destroy()
