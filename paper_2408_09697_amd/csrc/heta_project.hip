@@ -208,7 +208,6 @@ struct SplitSegs { // passed by value
     int64_t M[kMaxLaunchSeg], ldo[kMaxLaunchSeg];
     int32_t N[kMaxLaunchSeg], n_split[kMaxLaunchSeg], chains[kMaxLaunchSeg];
     float beta;
-    int n;
     unsigned first; // first workgroup of this launch
 };
 // NW wavefronts per 64 elements: wavefront w adds the splits w, w + NW, ... (eight loads in flight), the NW sums are
@@ -219,14 +218,15 @@ struct SplitSegs { // passed by value
 // of 110,000 rows, 789 x 256, 107.8 / 100.4; of 500 rows, 128 x 256, fp32 17.3 / 18.2).  The number follows from each
 // gradient's own call, whatever shares the launch: it decides the order of the sum.
 static int split_chains(int64_t n_split, int64_t out_elems) { return n_split >= 128 ? 16 : n_split >= 32 || out_elems < 196608 ? 4 : 1; }
-template <int NW> __device__ __forceinline__ void splitk_reduce(const SplitSegs &g, float (*red)[64])
+// NT threads: NT / (64 NW) times 64 elements.
+template <int NW, int NT> __device__ __forceinline__ void splitk_reduce(const SplitSegs &g, float (*red)[64])
 {
-    const int lane = threadIdx.x & 63, w = NW == 1 ? 0 : threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, w = wave % NW;
     const int seg = blockIdx.y, n_split = g.n_split[seg];
     const int64_t N = g.N[seg], total = g.M[seg] * N;
     const float beta = g.beta;
     const int64_t block = static_cast<int64_t>(g.first) + blockIdx.x;
-    const int64_t t = NW == 1 ? block * 256 + threadIdx.x : block * 64 + lane;
+    const int64_t t = (block * (NT / (64 * NW)) + wave / NW) * 64 + lane;
     const float *part = g.part[seg];
     float a = 0.f;
     if (t < total) {
@@ -234,30 +234,27 @@ template <int NW> __device__ __forceinline__ void splitk_reduce(const SplitSegs 
         for (int s = w; s < n_split; s += NW) a += part[static_cast<int64_t>(s) * total + t];
     }
     if (NW > 1) {
-        red[w][lane] = a;
+        red[wave][lane] = a;
         __syncthreads();
     }
     if (w != 0 || t >= total) return;
     if (NW > 1) {
         a = 0.f;
 #pragma unroll
-        for (int i = 0; i < NW; ++i) a += red[i][lane];
+        for (int i = 0; i < NW; ++i) a += red[wave + i][lane];
     }
     const int64_t m = t / N, n = t % N;
     float *o = g.out[seg] + m * g.ldo[seg] + n;
     *o = (beta != 0.f) ? beta * *o + a : a;
 }
-// 16 chains each, or (256 threads) four and one
-__global__ void __launch_bounds__(1024) splitk_reduce16_kernel(SplitSegs g)
+// 1,024 threads where a gradient of the launch has 16 chains, else 256
+template <int NT> __global__ void __launch_bounds__(NT) splitk_reduce_kernel(SplitSegs g)
 {
-    __shared__ float red[16][64];
-    splitk_reduce<16>(g, red);
-}
-__global__ void __launch_bounds__(256) splitk_reduce_kernel(SplitSegs g)
-{
-    __shared__ float red[4][64];
-    if (g.chains[blockIdx.y] == 1) splitk_reduce<1>(g, red); // uniform
-    else splitk_reduce<4>(g, red);
+    __shared__ float red[NT / 64][64];
+    const int chains = g.chains[blockIdx.y]; // uniform
+    if (NT == 1024 && chains == 16) splitk_reduce<NT / 64, NT>(g, red);
+    else if (chains == 4) splitk_reduce<4, NT>(g, red);
+    else splitk_reduce<1, NT>(g, red);
 }
 
 // bf16 weight matrices as octets, out[k / 8][n][8 k-values] of B(k, n) = W[k*ldw + n] (TRANS: W[n*ldw + k]), zero beyond K
@@ -824,45 +821,41 @@ static heta_status wgrad_run(heta_graph *g, const Wgrad *calls, int n_calls, het
     }
     heta_status e = ensure_workspace(g, static_cast<size_t>(ws_elems) * sizeof(float));
     if (e != HETA_OK) return e;
-    SplitSegs sums[2] = {}; // of 16 chains, of fewer
-    int64_t blocks[2] = {};
-    double bytes[2] = {};
+    SplitSegs sums{};
+    int64_t blocks = 0;
+    double bytes = 0;
+    const int threads = *std::max_element(chains, chains + n_calls) == 16 ? 1024 : 256;
     float *ws = static_cast<float *>(g->d_ws);
     for (int c = 0, at = 0; c < n_calls; ++c)
         for (int s = 0; s < calls[c].n_seg; ++s, ++at) {
             const int64_t total = static_cast<int64_t>(calls[c].d_in[s]) * calls[c].d_out;
             p.seg[at].C = ws;
             ws += n_split[c] * total;
-            const int k = chains[c] == 16 ? 0 : 1;
-            SplitSegs &g = sums[k];
-            g.part[g.n] = p.seg[at].C;
-            g.out[g.n] = calls[c].dW[s];
-            g.M[g.n] = calls[c].d_in[s];
-            g.ldo[g.n] = calls[c].ld_dw[s];
-            g.N[g.n] = calls[c].d_out;
-            g.n_split[g.n] = static_cast<int32_t>(n_split[c]);
-            g.chains[g.n++] = chains[c];
-            g.beta = beta;
-            blocks[k] = std::max(blocks[k], chains[c] == 1 ? (total + 255) / 256 : (total + 63) / 64);
-            bytes[k] += (n_split[c] + 1.0) * total * 4.0;
+            sums.part[at] = p.seg[at].C;
+            sums.out[at] = calls[c].dW[s];
+            sums.M[at] = calls[c].d_in[s];
+            sums.ldo[at] = calls[c].ld_dw[s];
+            sums.N[at] = calls[c].d_out;
+            sums.n_split[at] = static_cast<int32_t>(n_split[c]);
+            sums.chains[at] = chains[c];
+            const int64_t per_block = threads / chains[c];
+            blocks = std::max(blocks, (total + per_block - 1) / per_block);
+            bytes += (n_split[c] + 1.0) * total * 4.0;
         }
+    sums.beta = beta;
     p.batch = 1;
     p.n_split = static_cast<int>(split_max);
     p.partial = 1;
     p.split_b = (gout_two_terms && in_dt == HETA_BF16) ? 1 : 0;
     if ((e = dispatch_gemm<true, true>(p, in_dt, HETA_F32, st, in_dt == HETA_F32 ? 32 : 64)) != HETA_OK) return e;
-    for (int k = 0; k < 2; ++k) {
-        SplitSegs &g = sums[k];
-        if (g.n == 0) continue;
-        ProfScope prof("splitk_reduce_kernel", st, bytes[k], 0);
-        launch_pieces(blocks[k], k == 0 ? 1024 : 256, [&](unsigned first, unsigned count) {
-            g.first = first;
-            const dim3 grid(count, (unsigned)g.n);
-            if (k == 0) hipLaunchKernelGGL(splitk_reduce16_kernel, grid, dim3(1024), 0, st, g);
-            else hipLaunchKernelGGL(splitk_reduce_kernel, grid, dim3(256), 0, st, g);
-        });
-        HETA_LAUNCH_CHECK("splitk_reduce_kernel");
-    }
+    ProfScope prof("splitk_reduce_kernel", st, bytes, 0);
+    launch_pieces(blocks, threads, [&](unsigned first, unsigned count) {
+        sums.first = first;
+        const dim3 grid(count, (unsigned)p.n_seg);
+        if (threads == 1024) hipLaunchKernelGGL(splitk_reduce_kernel<1024>, grid, dim3(1024), 0, st, sums);
+        else hipLaunchKernelGGL(splitk_reduce_kernel<256>, grid, dim3(256), 0, st, sums);
+    });
+    HETA_LAUNCH_CHECK("splitk_reduce_kernel");
     return HETA_OK;
 }
 
