@@ -213,6 +213,7 @@ class Graph:
         self._h = ctypes.c_void_p(handle)
         self.ntypes = ntypes          # [(num_nodes, feat_dim, learnable)]
         self.rels = rel_meta          # [(src_type, dst_type, num_edges)]
+        self.sampled = False          # a sampled block, which lives for one pass (sample_blocks)
 
     @property
     def handle(self):

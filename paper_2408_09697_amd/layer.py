@@ -131,9 +131,9 @@ class RafLayer:
         self.Zp = {r: padded(graph.n_src(r), d_out, m_dtype) for r in self.pf}
         self.H = {t: torch.empty((graph.ntypes[t][0], d_out), dtype=torch.float32, device=dev)
                   for t in self.rels_into}
-        # The backward's buffers: now, so that no pass allocates - but for a sampled block's layer (a row map, a part of the
-        # relations), which lives for one pass, when they are first asked for: one that serves never needs them.
-        if src_gid is None and rels is None:
+        # The backward's buffers: now, so that no pass allocates - but for a sampled block's layer, which lives for one pass,
+        # when they are first asked for: one that serves never needs them.
+        if not graph.sampled:
             _ = self.dM, self.Ghat, self.dW, self.dH0, self.dtable, self._Gact
 
     @cached_property

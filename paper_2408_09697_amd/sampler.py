@@ -54,6 +54,8 @@ def sample_blocks(base: hb.Graph, seed_type: int, seeds: torch.Tensor, fanouts: 
         frontier = [u if u.numel() else None for u in src_ids]
     # the blocks' handles (CSC, 1/deg, schedules of every relation of every hop) in one build
     graphs = hb.heta_graph_create_batch(specs, flags=hb.HETA_PTRS_ON_DEVICE)
+    for g in graphs:
+        g.sampled = True
     blocks = [DeviceBlock(g, *p) for g, p in zip(graphs, parts)]
     blocks.reverse()
     return blocks

@@ -625,6 +625,21 @@ def test_layer_config1_relation_split_equals_whole():
     hg.destroy()
 
 
+def test_no_pass_of_a_layer_over_some_relations_allocates():
+    """A worker's share of a full graph has its backward's buffers from the start; a sampled block's layer makes them when asked."""
+    p = workloads.config1()
+    hg = make_graph(p)
+    G = {t: torch.from_numpy(np.ascontiguousarray(g, dtype=np.float32)).cuda() for t, g in p.G.items()}
+    for sampled in (False, True):
+        hg.sampled = sampled
+        layer = make_layer(p, hg, rels=[0, 2])
+        layer.forward()
+        before = torch.cuda.memory_allocated()
+        layer.backward(G)
+        assert (torch.cuda.memory_allocated() > before) == sampled
+    hg.destroy()
+
+
 def test_layer_config1_meta_partitions_sum_to_the_whole():
     """The relation sets that the library's meta-partitioning deals to two partitions (Section 5), each run
     as its own layer: the partial aggregations of the target type add up to the whole layer's
