@@ -2283,24 +2283,26 @@ heta_status heta_attn_fold_multi(int32_t n, const void *const *W, heta_dtype w_d
             return fail(HETA_ERR_INVALID_ARG, "heta_attn_fold: pointer not aligned to its element size");
     }
     hipStream_t st = as_stream(hip_stream);
-    for (int32_t i0 = 0; i0 < n; i0 += kFoldItems) {
+    const int64_t most = max_blocks(64);
+    for (int32_t i0 = 0; i0 < n;) {
         FoldItems q{};
-        q.n = std::min(n - i0, kFoldItems);
         q.K = heads;
-        unsigned blocks = 0; // of an item at most 2^24 (d_in d_out <= 2^30), of a launch below 2^29
-        for (int c = 0; c < q.n; ++c) {
-            FoldItem &r = q.it[c];
-            r.W = W[i0 + c];
-            r.ld_w = ld_w[i0 + c];
-            r.d_in = d_in[i0 + c];
-            r.d_out = d_out[i0 + c];
-            r.a = a[i0 + c];
-            r.wa = wa[i0 + c];
-            r.first = blocks;
-            blocks += static_cast<unsigned>((static_cast<int64_t>(heads) * r.d_in + 63) / 64);
+        int64_t blocks = 0; // of an item at most 2^24 (heads divides d_out, and d_in d_out <= 2^30)
+        for (; i0 < n && q.n < kFoldItems; ++i0) {
+            const int64_t mine = (static_cast<int64_t>(heads) * d_in[i0] + 63) / 64;
+            if (blocks + mine > most) break;
+            FoldItem &r = q.it[q.n++];
+            r.W = W[i0];
+            r.ld_w = ld_w[i0];
+            r.d_in = d_in[i0];
+            r.d_out = d_out[i0];
+            r.a = a[i0];
+            r.wa = wa[i0];
+            r.first = static_cast<unsigned>(blocks);
+            blocks += mine;
         }
-        if (w_dt == HETA_F32) hipLaunchKernelGGL(attn_fold_kernel<float>, dim3(blocks), dim3(64), 0, st, q);
-        else hipLaunchKernelGGL(attn_fold_kernel<bf16_t>, dim3(blocks), dim3(64), 0, st, q);
+        if (w_dt == HETA_F32) hipLaunchKernelGGL(attn_fold_kernel<float>, dim3((unsigned)blocks), dim3(64), 0, st, q);
+        else hipLaunchKernelGGL(attn_fold_kernel<bf16_t>, dim3((unsigned)blocks), dim3(64), 0, st, q);
         HETA_LAUNCH_CHECK("attn_fold_kernel");
     }
     return HETA_OK;

@@ -734,3 +734,17 @@ def test_attention_is_bitwise_reproducible_run_to_run():
     for a, b in zip(*runs):
         assert torch.equal(a, b)
     graph.destroy()
+
+
+def test_fold_of_more_than_2_32_elements():
+    """Five relations of 2^30 elements each: more threads than one launch has."""
+    heads, d_in = 16, 1 << 26
+    W = torch.randn((d_in, heads), device="cuda", dtype=torch.bfloat16)
+    a = [torch.full((heads, 1), 0.5 * (i + 1), device="cuda") for i in range(5)]
+    wa = [torch.empty((heads, d_in), device="cuda") for _ in a]
+    heta.heta_attn_fold_multi([(W, x, out) for x, out in zip(a, wa)])
+    for x, out in zip(a, wa):  # d_out / heads is 1: each element is one product
+        for j in range(0, d_in, 1 << 24):
+            assert torch.equal(out[:, j:j + (1 << 24)], (W[j:j + (1 << 24)].float() * x.view(1, -1)).t())
+    del W, wa, out
+    torch.cuda.empty_cache()
