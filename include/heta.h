@@ -283,10 +283,11 @@ heta_status heta_project_wgrad_batch(heta_graph *g, int64_t n_rows, int32_t n, c
  *   bf16 output takes neither.
  * heta_project_wgrad_multi: dW[s] = ins[s]^T . gouts[s] (d_in[s] x d_out[i]) over n_rows[i] rows; workspace and
  *   gout_two_terms as in heta_cross_rel_project_wgrad.
- * Items that a launch of their own would leave part of the chip idle share one: they run concurrently, so no two outputs may
- * overlap (checked).  What shares a launch does not change a result: an item's is, bit for bit, that of a call of its own.
- * g: handle whose packing buffer (also for transposed bf16 weights) and workspace the call uses.  All arrays are HOST arrays; shapes,
- * dtypes and errors as in the calls above, detected before anything is launched.  n = 0 is a no-op. */
+ * Items that a launch of their own would leave part of the chip idle share one: they run concurrently and in any order, so no
+ * output may overlap another one, or what another item reads (checked; column slices of one buffer do not overlap).  What
+ * shares a launch does not change a result: an item's is, bit for bit, that of a call of its own.  g: handle whose packing
+ * buffer (also for transposed bf16 weights) and workspace the call uses.  All arrays are HOST arrays; shapes, dtypes and
+ * errors as in the calls above, detected before anything is launched.  n = 0 is a no-op. */
 heta_status heta_project_multi(heta_graph *g, int32_t n, const int32_t *first, const int64_t *n_rows, int32_t sum, const void *const *ins,
                                heta_dtype in_dt, const int64_t *ld_in, const int32_t *depth, const void *const *Ws, heta_dtype w_dt,
                                const int64_t *ld_w, const int32_t *width, int32_t transW, void *const *outs, heta_dtype out_dt,
@@ -355,7 +356,8 @@ heta_status heta_cross_rel_reduce(const heta_graph *g, int32_t dst_type, const f
                                   int32_t n_partials, int64_t ld, int32_t d_out, heta_act act,
                                   float *out, int64_t ld_out, void *hip_stream);
 /* The same for n node types, launched together: type i adds partials[first[i] .. first[i+1]-1] (first: n + 1 entries from 0)
- * into outs[i].  HOST arrays; no output may overlap another one, or a partial of another type.  n = 0 is a no-op. */
+ * into outs[i].  HOST arrays; no output may overlap another one, or a partial of another type (checked; column slices of one
+ * buffer do not overlap).  n = 0 is a no-op. */
 heta_status heta_cross_rel_reduce_multi(const heta_graph *g, int32_t n, const int32_t *dst_type, const int32_t *first,
                                         const float *const *partials, const int64_t *ld, const int32_t *d_out, heta_act act, float *const *outs,
                                         const int64_t *ld_out, void *hip_stream);

@@ -44,6 +44,41 @@ template <typename F> void launch_pieces(int64_t blocks, int threads, F launch)
         launch(static_cast<unsigned>(first), static_cast<unsigned>(blocks - first < most ? blocks - first : most));
 }
 
+// The memory of `rows` rows of `d` elements, `ld` apart.  Rows of one pitch that lie side by side (column slices of one
+// buffer) share none.
+struct RowRange {
+    uintptr_t lo = 0, hi = 0;
+    uint64_t pitch = 0, width = 0;
+    RowRange() = default;
+    RowRange(const void *p, int64_t rows, int64_t ld, int64_t d, size_t elt)
+        : lo(reinterpret_cast<uintptr_t>(p)), hi(p && rows > 0 ? lo + static_cast<uintptr_t>((rows - 1) * ld + d) * elt : lo),
+          pitch(static_cast<uint64_t>(ld) * elt), width(static_cast<uint64_t>(d) * elt)
+    {
+    }
+    bool overlaps(const RowRange &o) const
+    {
+        if (!(lo < o.hi && o.lo < hi)) return false;
+        if (pitch != o.pitch) return true;
+        const uint64_t at = o.lo >= lo ? (o.lo - lo) % pitch : (pitch - (lo - o.lo) % pitch) % pitch; // o's column in this row
+        return at < width || at + o.width > pitch;
+    }
+};
+struct ItemRange : RowRange { // of one item of a call whose items run concurrently
+    int item;
+    ItemRange(int i, const RowRange &r) : RowRange(r), item(i) {}
+};
+// Whether an output overlaps another one, or what another item reads.
+inline bool items_collide(const std::vector<ItemRange> &outs, const std::vector<ItemRange> &ins)
+{
+    for (size_t i = 0; i < outs.size(); ++i) {
+        for (size_t j = 0; j < i; ++j)
+            if (outs[i].overlaps(outs[j])) return true;
+        for (const ItemRange &in : ins)
+            if (in.item != outs[i].item && outs[i].overlaps(in)) return true;
+    }
+    return false;
+}
+
 // ---- row schedule of one direction of one relation ----------------------------------------------
 // Rows are the reduction's output rows: destinations for the CSR (forward), sources for the CSC
 // (backward).  `perm` lists the rows by descending degree (stable, so ascending row id within a

@@ -879,14 +879,6 @@ static heta_status wgrad_impl(heta_graph *g, int64_t n_rows, int n_seg, const vo
     return e == HETA_OK ? wgrad_run(g, &call, 1, in_dt, gout_two_terms, beta, st) : e;
 }
 
-// whether the byte ranges of n rows of `bytes` (pitch `pitch`) at a and at b share memory
-static bool rows_overlap(const void *a, int64_t na, int64_t pa, int64_t wa, const void *b, int64_t nb, int64_t pb, int64_t wb)
-{
-    if (na <= 0 || nb <= 0) return false;
-    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
-    return x < y + static_cast<uintptr_t>((nb - 1) * pb + wb) && y < x + static_cast<uintptr_t>((na - 1) * pa + wa);
-}
-
 static heta_status project_multi_impl(heta_graph *g, int32_t n, const int32_t *first, const int64_t *n_rows, int32_t sum, const void *const *ins,
                                       heta_dtype in_dt, const int64_t *ld_in, const int32_t *depth, const void *const *Ws, heta_dtype w_dt,
                                       const int64_t *ld_w, const int32_t *width, int32_t transW, void *const *outs, heta_dtype out_dt,
@@ -932,19 +924,19 @@ static heta_status project_multi_impl(heta_graph *g, int32_t n, const int32_t *f
         }
         if (e != HETA_OK) return e;
     }
-    // the outputs are written side by side
-    const int64_t elt = static_cast<int64_t>(dtype_size(out_dt));
-    std::vector<const GemmSeg *> written;
+    // the items run side by side, and not in the order given
+    std::vector<ItemRange> written, read;
+    for (int32_t i = 0; i < n; ++i)
+        for (int s = 0; s < plans[i].n_seg; ++s) {
+            const GemmSeg &a = plans[i].seg[s];
+            if (plans[i].batch || s == 0) written.emplace_back(i, RowRange(a.C, a.M, a.ldc, a.N, dtype_size(out_dt)));
+            if (n == 1) continue;
+            read.emplace_back(i, RowRange(a.A, a.M, a.lda, a.K, dtype_size(in_dt)));
+            read.emplace_back(i, RowRange(a.B, transW ? a.N : a.K, a.ldb, transW ? a.K : a.N, dtype_size(w_dt)));
+        }
+    if (items_collide(written, read)) return fail(HETA_ERR_INVALID_ARG, "%s: an output overlaps another one or what another item reads", who);
     if (in_dt == HETA_F32 && w_dt == HETA_F32)
         for (GemmParams &p : plans) p.form = f32_product_form(p);
-    for (const GemmParams &p : plans)
-        for (int s = 0; s < (p.batch ? p.n_seg : std::min(p.n_seg, 1)); ++s) {
-            const GemmSeg &a = p.seg[s];
-            for (const GemmSeg *b : written)
-                if (rows_overlap(a.C, a.M, a.ldc * elt, a.N * elt, b->C, b->M, b->ldc * elt, b->N * elt))
-                    return fail(HETA_ERR_INVALID_ARG, "%s: outputs overlap", who);
-            written.push_back(&a);
-        }
     for (int32_t i = 0; i < n; ++i) {
         GemmParams &p = plans[i];
         if (p.n_seg == 0) continue; // no rows, or joined already
@@ -976,12 +968,15 @@ static heta_status wgrad_multi_impl(heta_graph *g, int32_t n, const int32_t *fir
         heta_status e = wgrad_check(calls.back(), in_dt, who);
         if (e != HETA_OK) return e;
     }
+    std::vector<ItemRange> written, read;
     for (int32_t i = 0; i < n; ++i)
-        for (int32_t s = first[i]; s < first[i + 1]; ++s)
-            for (int32_t j = 0; j <= i; ++j)
-                for (int32_t t = first[j]; t < first[j + 1] && t < s; ++t)
-                    if (rows_overlap(dW[s], d_in[s], ld_dw[s] * 4, d_out[i] * 4, dW[t], d_in[t], ld_dw[t] * 4, d_out[j] * 4))
-                        return fail(HETA_ERR_INVALID_ARG, "%s: outputs overlap", who);
+        for (int32_t s = first[i]; s < first[i + 1]; ++s) {
+            written.emplace_back(i, RowRange(dW[s], d_in[s], ld_dw[s], d_out[i], 4));
+            if (n == 1) continue;
+            read.emplace_back(i, RowRange(ins[s], n_rows[i], ld_in[s], d_in[s], dtype_size(in_dt)));
+            read.emplace_back(i, RowRange(gouts[s], n_rows[i], ld_go[s], d_out[i], 4));
+        }
+    if (items_collide(written, read)) return fail(HETA_ERR_INVALID_ARG, "%s: an output overlaps another one or what another item reads", who);
     // Calls of few k-tiles per split share a launch; the others fill the chip for long enough by themselves (kMergeKTiles: five
     // calls of 10^4 to 10^6 rows, 128 x 256, 1.34 ms together and 1.13 one by one; four of 900 to 110,000 rows, 128 x 64, 76 us
     // together and 112).  Calls without rows leave zeros and go alone.

@@ -3,7 +3,6 @@
 // every element is read once per partial and written once, 128 bits per lane where the
 // layout allows.
 #include <algorithm>
-#include <utility>
 
 #include "heta_internal.h"
 
@@ -195,7 +194,7 @@ heta_status heta_cross_rel_reduce_multi(const heta_graph *g, int32_t n, const in
     try {
         std::vector<ReduceParams> types[2]; // by width of the accesses: one float, four
         std::vector<int64_t> blocks[2];
-        std::vector<std::pair<uintptr_t, uintptr_t>> ranges;
+        std::vector<ItemRange> written, read;
         for (int32_t i = 0; i < n; ++i) {
             if (dst_type[i] < 0 || dst_type[i] >= (int32_t)g->ntypes.size())
                 return fail(HETA_ERR_INVALID_ARG, "heta_cross_rel_reduce: node type %d out of range", dst_type[i]);
@@ -225,20 +224,14 @@ heta_status heta_cross_rel_reduce_multi(const heta_graph *g, int32_t n, const in
             if (p.n_rows == 0) continue;
             const int64_t threads = p.n_rows * (vec ? p.d / 4 : p.d);
             if ((threads + 255) / 256 > 0x7fffffff) return fail(HETA_ERR_UNSUPPORTED, "heta_cross_rel_reduce: too large");
-            if (n > 1) { // the types of one call run concurrently: none may write what another one reads or writes
-                const auto range = [&](const float *x, int64_t l) {
-                    const uintptr_t lo = reinterpret_cast<uintptr_t>(x);
-                    return std::make_pair(lo, lo + static_cast<uintptr_t>((p.n_rows - 1) * l + p.d) * sizeof(float));
-                };
-                ranges.push_back(range(p.out, p.ld_out));
-                const auto o = ranges.back();
-                for (size_t q = 0; q + 1 < ranges.size(); ++q)
-                    if (o.first < ranges[q].second && ranges[q].first < o.second)
-                        return fail(HETA_ERR_INVALID_ARG, "heta_cross_rel_reduce: the outputs of two types overlap");
+            if (n > 1) { // the types of one call run concurrently
+                written.emplace_back(i, RowRange(p.out, p.n_rows, p.ld_out, p.d, sizeof(float)));
+                for (int k = 0; k < n_partials; ++k) read.emplace_back(i, RowRange(p.part[k], p.n_rows, p.ld, p.d, sizeof(float)));
             }
             types[vec].push_back(p);
             blocks[vec].push_back((threads + 255) / 256);
         }
+        if (items_collide(written, read)) return fail(HETA_ERR_INVALID_ARG, "heta_cross_rel_reduce: an output overlaps another type's output or partial");
         for (int vec = 1; vec >= 0; --vec)
             for (size_t i0 = 0; i0 < types[vec].size(); i0 += kReduceTypes) {
                 ReduceTypes m{};

@@ -1801,6 +1801,34 @@ def test_packed_input_gradients_of_narrow_outputs_change_sign_every_256_rows():
     hg.destroy()
 
 
+def test_items_that_meet_in_memory_are_refused_and_column_slices_accepted():
+    g = torch.Generator(device="cuda").manual_seed(2)
+    n = 96
+    hg = heta.heta_graph_create([(n, 1, 0)] * 2, [(0, 0, np.zeros(n + 1, dtype=np.int64), np.zeros(0, dtype=np.int32))])
+    rand = lambda *shape: torch.randn(shape, generator=g, device="cuda")  # noqa: E731
+    x, w, wide = [rand(n, 64) for _ in range(2)], [rand(64, 64) for _ in range(2)], torch.full((n, 160), 7.0, device="cuda")
+    part = [wide[:, :64], wide[:, 96:]]
+    other = [rand(n, 64) for _ in range(2)]
+    refused = [
+        lambda: heta.heta_project_multi(hg, [(n, [x[0]], [w[0]], [other[0]]), (n, [other[0]], [w[1]], [other[1]])]),
+        lambda: heta.heta_project_multi(hg, [(n, [x[0]], [w[0]], [other[0]]), (n, [x[1]], [other[0][:64]], [other[1]])]),
+        lambda: heta.heta_project_multi(hg, [(n, [x[0]], [w[0]], wide[:, :64]), (n, [x[1]], [w[1]], wide[:, 63:127])], sum=True),
+        lambda: heta.heta_project_multi(hg, [(n - 1, [x[0]], [w[0]], wide[1:, 96:]), (n, [x[1]], [w[1]], wide[:, 60:124])], sum=True),
+        lambda: heta.heta_project_wgrad_multi(hg, [(n, [x[0]], [x[1]], [other[0][:64]]), (n, [x[0]], [other[0]], [other[1][:64]])]),
+        lambda: heta.heta_cross_rel_reduce_multi(hg, [(0, [x[0], x[1]], other[0]), (1, [x[0], other[0]], other[1])]),
+    ]
+    for call in refused:
+        with pytest.raises(heta.HetaError) as e:
+            call()
+        assert e.value.status == heta.HETA_ERR_INVALID_ARG
+    heta.heta_project_multi(hg, [(n, [a], [b], o) for a, b, o in zip(x, w, part)], sum=True)
+    for a, b, o in zip(x, w, part):
+        _close(o, a.double() @ b.double(), "f32")
+    heta.heta_cross_rel_reduce_multi(hg, [(t, [x[t], w[0].new_zeros((n, 64))], part[t]) for t in range(2)])
+    assert all(torch.equal(o, a) for o, a in zip(part, x)) and bool((wide[:, 64:96] == 7.0).all())
+    hg.destroy()
+
+
 def test_scratch_release_gives_recycled_blocks_back():
     """Workspaces of destroyed handles stay with the library for the next one, until they are asked back."""
     x, go = torch.randn((60_000, 768), device="cuda"), torch.randn((60_000, 1024), device="cuda")
