@@ -254,6 +254,7 @@ __global__ void __launch_bounds__(kThreads) blk_prep_kernel(BlockPlan p, BlockAr
             hist_add(hist, static_cast<uint32_t>(min(max(deg, static_cast<int64_t>(0)), static_cast<int64_t>(E))));
         }
         if (tid == 0 && hi == n_dst) ptr[n_dst] = E;
+        if (tid == 0 && n_dst == 0 && rp[0] != 0) report(&err, kBadPtr0, rel, 0);
         __syncthreads();
         hist_store(hist, a.row_counts + blk);
     } else {

@@ -1801,6 +1801,20 @@ def test_packed_input_gradients_of_narrow_outputs_change_sign_every_256_rows():
     hg.destroy()
 
 
+@pytest.mark.parametrize("mode", [0, 1, 3])
+def test_offsets_of_a_relation_without_destinations_are_checked(mode):
+    heta.heta_ingest_force(mode)
+    try:
+        rels = lambda at: [(0, 1, torch.tensor([0, 1, 2], device="cuda"), torch.tensor([0, 1], dtype=torch.int32, device="cuda")),  # noqa: E731
+                           (0, 2, torch.tensor([at], device="cuda"), torch.zeros(0, dtype=torch.int32, device="cuda"))]
+        heta.heta_graph_create([(2, 4, 0), (2, 4, 0), (0, 4, 0)], rels(0), heta.HETA_PTRS_ON_DEVICE).destroy()
+        with pytest.raises(heta.HetaError) as e:
+            heta.heta_graph_create([(2, 4, 0), (2, 4, 0), (0, 4, 0)], rels(5), heta.HETA_PTRS_ON_DEVICE)
+        assert e.value.status == heta.HETA_ERR_BAD_CSR
+    finally:
+        heta.heta_ingest_force(0)
+
+
 def test_items_that_meet_in_memory_are_refused_and_column_slices_accepted():
     g = torch.Generator(device="cuda").manual_seed(2)
     n = 96
