@@ -299,7 +299,6 @@ heta_status heta_act_bwd_multi(int32_t n, const int64_t *n_rows, const int32_t *
         return fail(HETA_ERR_INVALID_ARG, "heta_act_bwd_multi: null argument");
     if (act != HETA_ACT_NONE && act != HETA_ACT_RELU) return fail(HETA_ERR_INVALID_ARG, "heta_act_bwd_multi: bad act");
     const int relu = act == HETA_ACT_RELU;
-    bool vec = true;
     for (int32_t i = 0; i < n; ++i) {
         if (!grad_out[i] || !grad_in[i] || (relu && !h[i])) return fail(HETA_ERR_INVALID_ARG, "heta_act_bwd_multi: null argument");
         if (n_rows[i] < 0 || d[i] <= 0 || ld_go[i] < d[i] || ld_gi[i] < d[i] || (relu && ld_h[i] < d[i]))
@@ -307,16 +306,30 @@ heta_status heta_act_bwd_multi(int32_t n, const int64_t *n_rows, const int32_t *
         if ((reinterpret_cast<uintptr_t>(grad_out[i]) & 3u) || (reinterpret_cast<uintptr_t>(grad_in[i]) & 3u) ||
             (relu && (reinterpret_cast<uintptr_t>(h[i]) & 3u)))
             return fail(HETA_ERR_INVALID_ARG, "heta_act_bwd_multi: pointer not 4-byte aligned");
-        vec = vec && d[i] % 4 == 0 && ld_go[i] % 4 == 0 && ld_gi[i] % 4 == 0 && aligned16(grad_out[i]) && aligned16(grad_in[i]) &&
-              (!relu || (ld_h[i] % 4 == 0 && aligned16(h[i])));
     }
-    int64_t blocks = 0;
-    double bytes = 0;
-    for (int32_t i = 0; i < n; ++i) {
-        blocks += (n_rows[i] * (vec ? d[i] / 4 : d[i]) + 255) / 256;
-        bytes += (relu ? 3.0 : 2.0) * static_cast<double>(n_rows[i]) * d[i] * 4.0;
+    ActItems kinds[2] = {}; // by width of the accesses: one float, four
+    int64_t blocks[2] = {};
+    double bytes[2] = {};
+    for (int32_t i = 0; i < n && n <= kMaxActs; ++i) {
+        const bool vec = d[i] % 4 == 0 && ld_go[i] % 4 == 0 && ld_gi[i] % 4 == 0 && aligned16(grad_out[i]) && aligned16(grad_in[i]) &&
+                         (!relu || (ld_h[i] % 4 == 0 && aligned16(h[i])));
+        ActItems &a = kinds[vec];
+        const int k = a.n++;
+        a.relu = relu;
+        a.h[k] = relu ? h[i] : nullptr;
+        a.ld_h[k] = relu ? ld_h[i] : 0;
+        a.go[k] = grad_out[i];
+        a.ld_go[k] = ld_go[i];
+        a.gi[k] = grad_in[i];
+        a.ld_gi[k] = ld_gi[i];
+        a.n_rows[k] = n_rows[i];
+        a.d[k] = d[i];
+        a.blk0[k] = static_cast<uint32_t>(blocks[vec]);
+        blocks[vec] += (n_rows[i] * (vec ? d[i] / 4 : d[i]) + 255) / 256;
+        a.blk0[k + 1] = static_cast<uint32_t>(blocks[vec]);
+        bytes[vec] += (relu ? 3.0 : 2.0) * static_cast<double>(n_rows[i]) * d[i] * 4.0;
     }
-    if (n > kMaxActs || blocks > max_blocks(256)) { // more than one launch takes: item by item
+    if (n > kMaxActs || blocks[0] > max_blocks(256) || blocks[1] > max_blocks(256)) { // more than one launch takes: item by item
         for (int32_t i = 0; i < n; ++i) {
             heta_status e = heta_act_bwd(n_rows[i], d[i], act, relu ? h[i] : nullptr, relu ? ld_h[i] : d[i], grad_out[i], ld_go[i], grad_in[i], ld_gi[i],
                                          hip_stream);
@@ -324,28 +337,14 @@ heta_status heta_act_bwd_multi(int32_t n, const int64_t *n_rows, const int32_t *
         }
         return HETA_OK;
     }
-    if (blocks == 0) return HETA_OK;
-    ActItems a{};
-    a.n = n;
-    a.relu = relu;
-    blocks = 0;
-    for (int32_t i = 0; i < n; ++i) {
-        a.h[i] = relu ? h[i] : nullptr;
-        a.ld_h[i] = relu ? ld_h[i] : 0;
-        a.go[i] = grad_out[i];
-        a.ld_go[i] = ld_go[i];
-        a.gi[i] = grad_in[i];
-        a.ld_gi[i] = ld_gi[i];
-        a.n_rows[i] = n_rows[i];
-        a.d[i] = d[i];
-        a.blk0[i] = static_cast<uint32_t>(blocks);
-        blocks += (n_rows[i] * (vec ? d[i] / 4 : d[i]) + 255) / 256;
+    for (int vec = 1; vec >= 0; --vec) {
+        if (blocks[vec] == 0) continue;
+        ProfScope prof("act_bwd_kernel", as_stream(hip_stream), bytes[vec], 0);
+        const dim3 grid(static_cast<unsigned>(blocks[vec]));
+        if (vec) hipLaunchKernelGGL(act_bwd_multi_kernel<4>, grid, dim3(256), 0, as_stream(hip_stream), kinds[vec]);
+        else hipLaunchKernelGGL(act_bwd_multi_kernel<1>, grid, dim3(256), 0, as_stream(hip_stream), kinds[vec]);
+        HETA_LAUNCH_CHECK("act_bwd_multi_kernel");
     }
-    a.blk0[n] = static_cast<uint32_t>(blocks);
-    ProfScope prof("act_bwd_kernel", as_stream(hip_stream), bytes, 0);
-    if (vec) hipLaunchKernelGGL(act_bwd_multi_kernel<4>, dim3((unsigned)blocks), dim3(256), 0, as_stream(hip_stream), a);
-    else hipLaunchKernelGGL(act_bwd_multi_kernel<1>, dim3((unsigned)blocks), dim3(256), 0, as_stream(hip_stream), a);
-    HETA_LAUNCH_CHECK("act_bwd_multi_kernel");
     return HETA_OK;
 }
 

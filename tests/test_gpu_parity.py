@@ -1873,6 +1873,8 @@ def test_act_bwd_multi(d, n_items):
     rows = [1 + (97 * i * i) % 1000 for i in range(n_items)]
     h, go = ([torch.from_numpy(g.standard_normal((n, d)).astype(np.float32)).cuda() for n in rows] for _ in range(2))
     gi = [torch.full_like(x, 5.0) for x in go]
+    if n_items == 4:  # one of them at an odd address
+        go[1] = torch.cat([go[1].new_zeros(1), go[1].flatten()])[1:].view(rows[1], d)
     heta.heta_act_bwd_multi(heta.HETA_ACT_RELU, h, go, gi)
     for a, b, c in zip(h, go, gi):
         assert torch.equal(c, torch.where(a > 0, b, torch.zeros_like(b)))
