@@ -118,7 +118,7 @@ heta_status heta_graph_create_batch(int32_t n_graphs, const heta_ntype *const *n
                                     heta_graph **out);
 heta_status heta_graph_destroy(heta_graph *g); /* NULL is accepted; synchronises the device */
 /* The library recycles the device blocks of its scratch, workspaces and small handles: those released stay with it for the
- * next call, at most 1 GiB per device while a handle is alive, and 256 MiB in blocks of at most 16 MiB afterwards.  This
+ * next call, at most 1 GiB per device while a handle is alive and 256 MiB afterwards.  This
  * gives all that lie idle on the current device back to it (when the caller's own allocator has run out, for instance). */
 heta_status heta_scratch_release(void);
 /* Device bytes the handle holds for index data (adjacency in both directions, schedules, 1/deg);

@@ -54,12 +54,12 @@ heta_status fail(heta_status st, const char *fmt, ...)
 // are rounded up to a power of two, above 16 MiB to a quarter of one, and kept on a free list per (device, size) when
 // released, up to 1 GiB per device, past which those released longest ago go back to the device (kept instead, they left no
 // room for what follows them: training iterations of 768 columns 1,040 us, after layers over larger graphs 1,330); larger
-// ones go straight to hipMalloc / hipFree.  With the process's last handle go the blocks past 16 MiB and what exceeds 256 MiB
-// per device: what handles that come and go one at a time live on.  All of a device's go when an allocation fails, and by
+// ones go straight to hipMalloc / hipFree.  With the process's last handle goes what exceeds 256 MiB per device, the rest
+// being what handles that come and go one at a time live on.  All of a device's go when an allocation fails, and by
 // heta_scratch_release.  A block must be idle when it is released (the callers synchronise first).
 namespace {
 constexpr size_t kPoolMaxBlock = size_t(256) << 20, kPoolMaxCached = size_t(1) << 30;
-constexpr size_t kPoolIdleBlock = size_t(16) << 20, kPoolIdleCached = size_t(256) << 20; // without a handle
+constexpr size_t kPoolIdleCached = size_t(256) << 20; // without a handle
 std::mutex g_pool_mu;
 std::unordered_map<void *, std::pair<int, size_t>> g_pool_blocks;     // live pooled block -> (device, size class)
 struct FreeBlock {
@@ -75,42 +75,37 @@ size_t pool_class(size_t bytes)
 {
     size_t cls = 256;
     while (cls < bytes) cls <<= 1;
-    if (cls <= kPoolIdleBlock) return cls;
+    if (cls <= size_t(16) << 20) return cls;
     const size_t step = cls / 8; // a quarter of the power of two below
     return (bytes + step - 1) / step * step;
 }
 
-// Takes from a device's free lists the blocks of more than `largest` bytes, then those released longest ago until at most
-// `most` bytes are left: for the caller to free.  With the lock held.
-void pool_evict(int dev, size_t largest, size_t most, std::vector<void *> &out)
+// Takes those released longest ago from a device's free lists until at most `most` bytes are left, for the caller to free.
+// With the lock held.
+void pool_evict(int dev, size_t most, std::vector<void *> &out)
 {
     const auto first = g_pool_free.lower_bound({dev, 0}), end = g_pool_free.lower_bound({dev + 1, 0});
     size_t &cached = g_pool_cached[dev];
-    const auto take_oldest = [&](decltype(g_pool_free)::iterator f) {
-        out.push_back(f->second.front().p);
-        g_pool_blocks.erase(f->second.front().p);
-        cached -= f->first.second;
-        f->second.erase(f->second.begin());
-    };
-    for (auto f = first; f != end; ++f)
-        while (f->first.second > largest && !f->second.empty()) take_oldest(f);
     while (cached > most) {
         auto oldest = end;
         for (auto f = first; f != end; ++f)
             if (!f->second.empty() && (oldest == end || f->second.front().released < oldest->second.front().released)) oldest = f;
-        take_oldest(oldest);
+        out.push_back(oldest->second.front().p);
+        g_pool_blocks.erase(oldest->second.front().p);
+        cached -= oldest->first.second;
+        oldest->second.erase(oldest->second.begin());
     }
 }
 
-// A device's free lists (dev < 0: every device's) down to these bounds.
-void pool_give_back(int dev, size_t largest, size_t most)
+// A device's free lists (dev < 0: every device's) down to `most` bytes.
+void pool_give_back(int dev, size_t most)
 {
     std::vector<void *> back;
     {
         std::lock_guard<std::mutex> lk(g_pool_mu);
-        if (dev >= 0) pool_evict(dev, largest, most, back);
+        if (dev >= 0) pool_evict(dev, most, back);
         else
-            for (const auto &d : g_pool_cached) pool_evict(d.first, largest, most, back);
+            for (const auto &d : g_pool_cached) pool_evict(d.first, most, back);
     }
     for (void *p : back) (void)hipFree(p);
 }
@@ -138,7 +133,7 @@ hipError_t scratch_alloc(void **out, size_t bytes)
     e = hipMalloc(out, cls);
     if (e == hipErrorOutOfMemory) {
         (void)hipGetLastError();
-        pool_give_back(dev, 0, 0);
+        pool_give_back(dev, 0);
         e = hipMalloc(out, cls);
     }
     if (e != hipSuccess || !pooled) return e;
@@ -159,16 +154,9 @@ void scratch_free(void *p)
         } else {
             const int dev = it->second.first;
             const size_t cls = it->second.second;
-            const bool live = g_handles > 0;
-            const size_t largest = live ? kPoolMaxBlock : kPoolIdleBlock;
-            if (cls > largest) {
-                back.push_back(p);
-                g_pool_blocks.erase(it);
-            } else { // there is room for it once others have gone
-                pool_evict(dev, largest, (live ? kPoolMaxCached : kPoolIdleCached) - cls, back);
-                g_pool_free[it->second].push_back({p, g_pool_releases++});
-                g_pool_cached[dev] += cls;
-            }
+            pool_evict(dev, (g_handles > 0 ? kPoolMaxCached : kPoolIdleCached) - cls, back); // cls is at most kPoolMaxBlock
+            g_pool_free[it->second].push_back({p, g_pool_releases++});
+            g_pool_cached[dev] += cls;
         }
     }
     for (void *q : back) (void)hipFree(q);
@@ -430,7 +418,7 @@ static void destroy(heta_graph *g)
     scratch_free(g->d_pack);
     (void)hipFree(g->d_attn);
     delete g;
-    if (--g_handles == 0) pool_give_back(-1, kPoolIdleBlock, kPoolIdleCached);
+    if (--g_handles == 0) pool_give_back(-1, kPoolIdleCached);
 }
 
 // Host-only checks of one relation's arguments and CSR; touches no device.
@@ -1155,7 +1143,7 @@ heta_status heta_scratch_release(void)
     int dev = 0;
     HETA_HIP(hipGetDevice(&dev));
     try {
-        pool_give_back(dev, 0, 0);
+        pool_give_back(dev, 0);
     } catch (...) { // the list of what is to be freed
         return fail(HETA_ERR_OOM, "heta_scratch_release: host allocation failed");
     }
