@@ -40,11 +40,12 @@ struct GemmCall {
     int relu;
     float beta;
     const float *row_scale;
+    int form;            // ProductForm
 };
 
 // How an fp32 product (forward, input gradient) is formed, by its size.  The form decides the order in which the terms of its
 // sums are added, and which rows get the negative product: the last bits of the result.  Each call's follows from that call
-// alone, and only calls whose form comes to the same bits share a launch, so that no result depends on what shares its launch.
+// alone, and only calls whose forms one kernel can keep share a launch, so that no result depends on what shares its launch.
 enum ProductForm { kFormNone = 0, kFormSmall, kFormModerate, kFormPacked };
 
 struct GemmParams {
@@ -62,7 +63,7 @@ struct GemmParams {
     int64_t k_per_split; // multiple of BK
     int n_split;
     int as_packed;       // fp32 product of a call whose larger launches pack B: the same order of sums where this one does not
-    int form;            // how an fp32 product is formed (ProductForm), 0 for others
+    int form;            // how an fp32 product is formed (ProductForm; calls that share a launch: the largest), 0 for others
     int both_signs;      // B3 holds the terms of B and, behind them, those of -B (input gradients)
     int partial;         // write raw partial products [split][M][ldc] (ldc = N) instead of the output
     int64_t mt, nt;      // tile counts (maximum over the segments in batch mode)

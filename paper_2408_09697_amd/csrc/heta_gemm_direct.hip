@@ -688,6 +688,11 @@ __device__ __forceinline__ void store_tile(const GemmParams &p, const GemmCall &
         }
 }
 
+__device__ __forceinline__ uint4 select(bool first, uint4 a, uint4 b)
+{
+    return make_uint4(first ? a.x : b.x, first ? a.y : b.y, first ? a.z : b.z, first ? a.w : b.w);
+}
+
 template <bool PACKED, bool B_DIRECT, typename DB, typename SB_T, typename Staged, typename CT> constexpr int b_stage_bytes()
 {
     if constexpr (PACKED) return DB::STAGE_BYTES;
@@ -711,10 +716,11 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
     // when fragments are read); a staged operand lies there in the compute type
     using DA = std::conditional_t<A_DIRECT, DirectLoader<SA_T, A_RC && A_DIRECT, BM, BK, NW>, NoLoader>;
     // X3: fp32 operands as three bf16 terms each - 1: both split when their fragments are read, 2: B comes pre-split, 3: both
-    // split, the products added in the order of 2 (bitwise the same sums).  4: a bf16 B packed as octets
+    // split, the products added in the order of 2 (bitwise the same sums).  4: a bf16 B packed as octets.  5: 3, with calls of
+    // the small form among them, whose products are added in the order of 1
     constexpr bool X3_AS_PACKED = X3 == 3;
     // A is flipped where its product's sign alternates (packed weights come in both signs instead): see flip_signs
-    constexpr bool W3 = X3 == 2, W1 = X3 == 4, X3_FLIP = X3 == 1 ? A_RC && B_RC : X3 == 3 && !B_RC;
+    constexpr bool W3 = X3 == 2, W1 = X3 == 4, X3_FLIP = X3 == 1 ? A_RC && B_RC : (X3 == 3 || X3 == 5) && !B_RC;
     using DB = std::conditional_t<W3, Split3Loader<BN, NW>, std::conditional_t<W1, OctetLoader<BN, NW, BK>, std::conditional_t<B_DIRECT, DirectLoader<SB_T, B_RC && B_DIRECT, BN, BK, NW>, NoLoader>>>;
     using SA = std::conditional_t<A_DIRECT, NoLoader, TileLoader<SA_T, CT, A_RC, BM, NT, true, BK>>;
     using SB = std::conditional_t<B_DIRECT, NoLoader, TileLoader<SB_T, CT, B_RC, BN, NT, true, BK>>;
@@ -761,7 +767,8 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
     const int64_t m0 = static_cast<int64_t>(p.partial ? rest / call.nt : outer) * BM;
     const int64_t split = p.partial ? outer : 0;
     // packed products of at most 64 columns: every 256 rows, as products of 256 x 64 tiles; the others every row block
-    const bool negated = (X3_FLIP || (W3 && p.both_signs)) && ((W3 && MI == 1 ? outer >> 1 : outer) & 1); // uniform
+    const bool small_call = X3 == 5 && call.form == kFormSmall; // uniform
+    const bool negated = !small_call && (X3_FLIP || (W3 && p.both_signs)) && ((W3 && MI == 1 ? outer >> 1 : outer) & 1); // uniform
     const uint32_t flip = negated ? 0x80000000u : 0u;
     const GemmSeg &out_seg = p.seg[s0];
     if (m0 >= out_seg.M || n0 >= out_seg.N) return; // uniform per workgroup
@@ -931,6 +938,11 @@ __global__ void __launch_bounds__(64 * WMW * WN, OCC) gemm_direct_kernel(GemmPar
                                 Frag fa, fb;
                                 fa.u = a3[i][TA[q]];
                                 fb.u = b3[jj][TB[q]];
+                                if constexpr (X3 == 5) { // selects: a branch between two orders, or two loops, cost more than a launch
+                                    constexpr int PA[6] = {0, 0, 0, 1, 1, 2}, PB[6] = {0, 1, 2, 0, 1, 0};
+                                    if (PA[q] != TA[q]) fa.u = select(small_call, fa.u, a3[i][PA[q]]);
+                                    if (PB[q] != TB[q]) fb.u = select(small_call, fb.u, b3[jj][PB[q]]);
+                                }
                                 acc[i][jj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa.v, fb.v, acc[i][jj], 0, 0, 0);
                             }
                 }
@@ -1160,7 +1172,7 @@ heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, 
     if (!gemm_direct_takes(p, a_dt, b_dt)) return HETA_OK;
     if (p.n_call == 0) {
         p.n_call = 1;
-        p.call[0] = GemmCall{0, p.n_seg, 0, 0, 0, p.n_split, static_cast<int32_t>(std::min<int64_t>(p.k_per_split, 0x7fffffff)), p.relu, p.beta, p.row_scale};
+        p.call[0] = GemmCall{0, p.n_seg, 0, 0, 0, p.n_split, static_cast<int32_t>(std::min<int64_t>(p.k_per_split, 0x7fffffff)), p.relu, p.beta, p.row_scale, p.form};
     }
     int64_t n_max = 0;
     for (int s = 0; s < p.n_seg; ++s) n_max = std::max(n_max, p.seg[s].N);
@@ -1225,6 +1237,8 @@ heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, 
     const bool f32 = a_dt == HETA_F32 && b_dt == HETA_F32;
     const int form = f32 && !p.form ? f32_product_form(p) : p.form;
     const bool small = f32 ? form == kFormSmall : gemm_direct_small(p), unpacked = form == kFormSmall || form == kFormModerate;
+    bool mixed = false; // calls of the small form among moderate ones
+    for (int c = 0; c < p.n_call; ++c) mixed = mixed || (p.call[c].form == kFormSmall && form == kFormModerate);
     const bool octets = b_dt == HETA_BF16 && p.seg[0].B3; // all segments of a launch are packed or none
     *handled = true;
     if (f32 && !g_f32_native && !a_rc && !unpacked && !p.partial) {
@@ -1269,6 +1283,7 @@ heta_status launch_gemm_direct(GemmParams &p, heta_dtype a_dt, heta_dtype b_dt, 
            : small && chain ? launch_direct<bf16_t, float, false, true, float, BRC, true, 2, 32, 3, 3, false, 1, 1, 2, 1>(p, st, name, bytes, flops) \
            : small || !p.as_packed                                                                                                                 \
                ? launch_direct<bf16_t, float, false, true, float, BRC, true, 2, 16, 3, 4, false, 1, 1, 2, 1>(p, st, name, bytes, flops)             \
+           : mixed ? launch_direct<bf16_t, float, false, true, float, BRC, true, 2, 16, 3, 4, false, 1, 1, 2, 5>(p, st, name, bytes, flops)         \
                : launch_direct<bf16_t, float, false, true, float, BRC, true, 2, 16, 3, 4, false, 1, 1, 2, 3>(p, st, name, bytes, flops)
         if (!a_rc && b_rc) { HETA_X32(true); }
         if (!a_rc && !b_rc) { HETA_X32(false); }

@@ -624,23 +624,32 @@ static bool merges(const GemmParams &p, heta_dtype a_dt, heta_dtype b_dt)
     }
     return tiles <= kMergeTiles;
 }
-// Whether call `q` (both `merges`) joins the calls in `p`.  fp32 products keep the bits that each has by itself: those of
-// one form do, and forward products of the upper two, which add their terms in one order (input gradients of the two form
-// the negative product for other rows).
+static bool has_small(const GemmParams &p)
+{
+    bool any = p.n_call == 0 && p.form == kFormSmall;
+    for (int c = 0; c < p.n_call; ++c) any = any || p.call[c].form == kFormSmall;
+    return any;
+}
+// Whether call `q` (both `merges`) joins the calls in `p`.  fp32 products keep the bits that each has by itself: calls of one
+// form do; small ones beside moderate ones, whose kernel then adds their terms in their own order; and moderate beside packed
+// forward products, which add theirs in one order (input gradients of the two form the negative product for other rows).
 static bool joins(const GemmParams &p, const GemmParams &q, int32_t transW)
 {
-    if (p.form != q.form && (transW || p.form == kFormSmall || q.form == kFormSmall)) return false;
+    const int more = std::max(p.form, q.form);
+    const bool small = more != kFormSmall && (has_small(p) || has_small(q));
+    if (more == kFormPacked && (small || (transW && p.form != q.form))) return false;
+    if (small && product_steps(p) + product_steps(q) > kUnpackedSteps) return false;
     return std::max(1, p.n_call) < kMaxCalls && p.n_seg + q.n_seg <= kMaxLaunchSeg && p.batch == q.batch && p.out_bf16 == q.out_bf16 &&
            width_class(p) == width_class(q);
 }
 static void join(GemmParams &p, const GemmParams &q, int32_t transW)
 {
-    const auto call_of = [](const GemmParams &x, int first) { return GemmCall{first, x.n_seg, 0, 0, 0, 1, 0x7fffffff, x.relu, x.beta, x.row_scale}; };
+    const auto call_of = [](const GemmParams &x, int first) { return GemmCall{first, x.n_seg, 0, 0, 0, 1, 0x7fffffff, x.relu, x.beta, x.row_scale, x.form}; };
     if (p.n_call == 0) p.call[p.n_call++] = call_of(p, 0);
     p.call[p.n_call++] = call_of(q, p.n_seg);
     for (int s = 0; s < q.n_seg; ++s) p.seg[p.n_seg++] = q.seg[s];
     p.form = std::max(p.form, q.form);
-    if (p.form == kFormModerate && !transW && product_steps(p) > kUnpackedSteps) p.form = kFormPacked;
+    if (p.form == kFormModerate && !transW && !has_small(p) && product_steps(p) > kUnpackedSteps) p.form = kFormPacked;
 }
 
 // dM_s = gout . W_s^T for every s: products of one depth whose outputs differ in width
@@ -817,7 +826,7 @@ static heta_status wgrad_run(heta_graph *g, const Wgrad *calls, int n_calls, het
         p.k_per_split = split.k_tiles_each * split.k_tile;
         if (n_calls > 1)
             p.call[p.n_call++] = GemmCall{first, w.n_seg, 0, 0, 0, static_cast<int32_t>(n_split[c]),
-                                          static_cast<int32_t>(std::min<int64_t>(p.k_per_split, 0x7fffffff)), 0, 0.f, nullptr};
+                                          static_cast<int32_t>(std::min<int64_t>(p.k_per_split, 0x7fffffff)), 0, 0.f, nullptr, kFormNone};
     }
     heta_status e = ensure_workspace(g, static_cast<size_t>(ws_elems) * sizeof(float));
     if (e != HETA_OK) return e;
