@@ -1439,7 +1439,8 @@ def heta_unique_relabel_batch(groups: Sequence[Sequence[torch.Tensor]], id_limit
 
 def heta_sample_hop(g: Graph, rels: Sequence[int], dst_ids: Sequence[torch.Tensor], fanout: int, seeds: Sequence[int], stream=None):
     """One hop of a mini-batch: heta_sample_neighbors_batch and, per node type, heta_unique_relabel of the relations leaving
-    it, in one call (one synchronisation).  Returns (rowptr per item, local source ids per item, unique ids per node type)."""
+    it, in one call (one synchronisation; in two where the local ids would take more than 64 MB by capacity).  Returns (rowptr
+    per item, local source ids per item, unique ids per node type)."""
     n, n_types = len(rels), len(g.ntypes)
     dev = dst_ids[0].device if n else torch.device("cuda")
     sizes = [int(d.numel()) for d in dst_ids]

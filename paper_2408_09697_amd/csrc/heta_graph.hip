@@ -199,8 +199,9 @@ struct PinnedRegion {
     size_t cap = 0;
 };
 static thread_local PinnedRegion t_pinned; // never freed: it lives as long as the thread builds graphs
-// Small relations handed over as DEVICE arrays are built on the host: their arrays come back through
-// this second page-locked buffer, all copies of a graph queued at once and awaited together.
+// Small relations handed over as DEVICE arrays that do not take the block build (more than 32 of them in a call, or a forced
+// path) are built on the host: their arrays come back through this second page-locked buffer, all copies of a graph queued
+// at once and awaited together.
 static thread_local PinnedRegion t_download;
 
 struct StagedCsr {
@@ -525,13 +526,12 @@ static heta_status differs_from_device(const T *caller, bool on_device, const T 
     return done(st);
 }
 
-// Relations below this many edges + rows are ingested on the host: a few microseconds of CPU work
-// beat the launch latencies of the device pipeline (sampled mini-batch blocks); everything larger
-// is built by the kernels of heta_ingest.hip.  heta_ingest_force() overrides the choice.
+// Relations of this many edges + rows and more are built one by one by the kernels of heta_ingest.hip, whose twenty launches
+// each are lost on smaller ones.  heta_ingest_force() overrides the choice.
 constexpr int64_t kDeviceIngestMin = 1 << 18;
 // The small relations of one call together (a sampled block) go through the whole-block device ingest when their arrays lie
 // on the device already, or add up to this many edges + rows (and are at most 32 relations).  Host arrays below it are
-// built on the host, which needs one copy.
+// built on the host: a few microseconds of work and one copy.
 constexpr int64_t kBlockIngestMin = 1 << 16;
 static int g_ingest_mode = 0; // 0 = by size, 1 = host, 2 = per-relation device kernels, 3 = small relations by the whole-block device ingest
 
